@@ -15,9 +15,9 @@ __device__ __forceinline__ float load_logit(const void *base, int dtype, int64_t
 // The up to 32 consecutive entries id0 .. id0 + epl - 1 of a row that a thread owns (epl a multiple of 8; entries
 // at or past `hi`, and octets past epl, read as -inf), as four octets.  Every load is unconditional, so that all
 // of a thread's loads are in flight together (a load inside a branch is waited for inside that branch): an
-// aligned bf16 octet that lies wholly inside the range is one 16-byte load, any other octet asks for the row's
-// first entries instead and is patched with element loads afterwards (at most one octet of a chunk straddles the
-// end of the row).  vec_ok: the row is 16-byte aligned and holds at least 8 entries.
+// bf16 octet that lies wholly inside the range is one 16-byte load (at whatever address), any other octet asks for the
+// row's first entries instead and is patched with element loads afterwards (at most one octet of a chunk straddles the
+// end of the row).  vec_ok: the row holds at least 8 entries.
 __device__ __forceinline__ void load_logits32(const void *row, int dtype, int id0, int epl, int hi, bool vec_ok,
                                               float x[4][8]) {
     if (dtype == DT_BF16 && vec_ok) {  // uniform
@@ -26,7 +26,7 @@ __device__ __forceinline__ void load_logits32(const void *row, int dtype, int id
         for (int j = 0; j < 4; ++j) {
             const int id = id0 + 8 * j;
             const bool full = 8 * j < epl && id + 8 <= hi;
-            raw[j] = *(const uint4 *)((const uint16_t *)row + (full ? id : 0));
+            raw[j] = load16((const uint16_t *)row + (full ? id : 0));
         }
         __builtin_amdgcn_sched_barrier(0);  // every request is out before the first conversion
 #pragma unroll
@@ -98,7 +98,7 @@ __device__ __forceinline__ void sample_row_block(const AcceptArgs &a, int64_t g,
     const int epl = a.chunk_elems / 256;
     const int lo = cstar * a.chunk_elems, hi = min(a.V, lo + a.chunk_elems);
     const int id0 = lo + tid * epl;
-    const bool vec_ok = ((uintptr_t)row & 15) == 0 && a.V >= 8;  // id0 is a multiple of 8
+    const bool vec_ok = a.V >= 8;
     // a thread owns at most 32 entries (four octets): all asked for at once and kept, the thread that
     // holds the crossing walks its registers and nothing is read twice
     float x[4][8];

@@ -32,6 +32,21 @@ __device__ __forceinline__ u32 key_idx(u64 k) { return 0xFFFFFFFFu - (u32)k; }
 
 __device__ __forceinline__ float bf16_bits_to_float(uint16_t b) { return __uint_as_float((u32)b << 16); }
 
+// 16 bytes of a logit row.  The address is only known to be a multiple of the element size: one load all the same (the
+// hardware takes any address), so a row of an odd vocabulary streams like an aligned one.  Non-temporal: a step reads a
+// logit once, and lines that do not displace each other in the caches on the way stream faster (1.25 GB of target rows:
+// 192 us, 6.5 TB/s, against 207 us).
+typedef u32 u32x4_any2 __attribute__((ext_vector_type(4), aligned(2)));
+typedef u32 u32x4_any4 __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ uint4 load16(const uint16_t *p) {
+    const u32x4_any2 v = __builtin_nontemporal_load((const u32x4_any2 *)p);
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ uint4 load16(const float *p) {
+    const u32x4_any4 v = __builtin_nontemporal_load((const u32x4_any4 *)p);
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+
 // ---- wave64 primitives -------------------------------------------------------------------
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & 63); }
 
