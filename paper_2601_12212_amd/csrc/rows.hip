@@ -88,31 +88,6 @@ __device__ __forceinline__ RowMeta row_meta(const RowArgs &a, int64_t g) {
     return m;
 }
 
-// ------------------------------------------------- rank at most 64 keys, keep the k best --
-// Keys are held one per lane (lanes >= n hold 0) and are distinct.  Each lane ranks its key by
-// comparing against every lane's key through readlane: no LDS traffic, no wait inside the loop.
-// The key of rank r < k is handed to emit(r, key).
-template <typename Emit>
-__device__ __forceinline__ void rank_emit_lanes(u64 mine, int n, int k, Emit emit) {
-    int rank = 0;
-    for (int i = 0; i < n; ++i) rank += (readlane_u64(mine, i) > mine) ? 1 : 0;
-    if (lane_id() < n && rank < k) emit(rank, mine);
-}
-
-// k-th largest of one 32-bit key per lane (k <= 64), by bitwise bisection over ballots.
-// LOWBIT: lowest key bit that can differ between lanes (16 for keys derived from bf16).
-template <int LOWBIT>
-__device__ __forceinline__ u32 wave_kth_largest(u32 key, int k) {
-    u32 t = 0;
-    for (int bit = 31; bit >= LOWBIT; --bit) {
-        u32 cand = t | (1u << bit);
-        int cnt = __popcll(__ballot(key >= cand));
-        if (cnt >= k) t = cand;
-    }
-    if (LOWBIT > 0 && !(t >> 31)) t |= (1u << LOWBIT) - 1u;  // negative floats: low key bits are all ones
-    return t;
-}
-
 // -------------------------------------------------------------------- chunk loading -----
 // Element (n, e) of a lane, n < NL, e < 8, has id = base + n*512 + e with
 // base = chunk*256*8*NL + wave*64*8*NL + lane*8: one coalesced 16-byte load per (lane, n).
@@ -211,6 +186,19 @@ __device__ __forceinline__ float2 wave_lse_partial(const float (&x)[E], float mx
 // Pure stream: every wave reads its 64*8*NL elements once and leaves behind one maximum per
 // lane and one (max, sum) pair per wave.  No LDS, no barrier.  All selection happens later on
 // the lane maxima, which are 8*NL times fewer than the logits.
+template <bool BF16>
+using LaneMax = std::conditional_t<BF16, uint16_t, float>;
+template <bool BF16>
+__device__ __forceinline__ LaneMax<BF16> lane_max_pack(float v) {
+    if constexpr (BF16) return (uint16_t)(__float_as_uint(v) >> 16);
+    else return v;
+}
+template <bool BF16>
+__device__ __forceinline__ float lane_max_value(LaneMax<BF16> v) {
+    if constexpr (BF16) return bf16_bits_to_float(v);
+    else return v;
+}
+
 template <int MODE, int NL, bool BF16, bool VEC>
 __global__ __launch_bounds__(256) void row_stream_kernel(RowArgs a) {
     constexpr int E = 8 * NL;
@@ -231,32 +219,85 @@ __global__ __launch_bounds__(256) void row_stream_kernel(RowArgs a) {
     float mx = x[0];
 #pragma unroll
     for (int j = 1; j < E; ++j) mx = fmaxf(mx, x[j]);
-    const int64_t wslot = (g * gridDim.x + c) * 4 + w;
-    a.lane_max[wslot * 64 + lane] = mx;
+    // lane maxima in the row's own precision (exact), the four waves of a chunk interleaved
+    const int64_t chunk = g * gridDim.x + c;
+    ((LaneMax<BF16> *)a.lane_max)[chunk * 256 + lane * 4 + w] = lane_max_pack<BF16>(mx);
     if (a.want_lse) {
         const float2 p = wave_lse_partial<E>(x, mx, a.inv_t);
-        if (lane == 0) a.part_ms[wslot] = p;
+        if (lane == 0) a.part_ms[chunk * 4 + w] = p;
     }
 }
 
 // ------------------------------------------------------------- selection kernel (top-k rows) --
 // One workgroup per row, working on the row's S*256 lane maxima:
-//   1. every thread takes the maximum of its S lane maxima; each wave finds the k-th largest of
-//      its 64 thread maxima (ballot bisection); the largest of the four, T0, is a lower bound of
-//      the row's k-th largest lane maximum (loose: up to a few hundred lane maxima reach it);
-//   2. the lane maxima >= T0 go into a histogram over their distance from T0 in steps of the upper
-//      16 key bits (for bf16 data: in representable values), and a scan from the top names the bin
-//      of the k-th largest lane maximum.  Its lower edge T1 is a lower bound of the row's k-th
-//      largest ELEMENT (k different lanes hold an element >= T1), and only lanes whose maximum
-//      reaches T1 ("hot" lanes: k of them plus ties at the edge) can hold a winner;
-//   3. the hot lanes' 8*NL elements are read again (they sit in L2), elements >= T1 are keyed
-//      by (value, id) and ranked by counting.
-// More than 128 hot lanes or candidates (rows dominated by ties, fewer than k finite entries)
-// switch to an exact but slow extract-max loop over the whole row.
+//   1. every thread takes the maximum of the lane maxima it holds; the 256 thread maxima meet in LDS as 16-bit keys
+//      (the upper half of the ordered integer image: all of it for bf16 data) and every wave finds the k-th largest by
+//      itself, four keys to a lane, by bisection over ballots.  T, the lower edge of that key, is a lower bound of the
+//      row's k-th largest ELEMENT (k threads hold one >= T), and because a thread's lane maxima come from places far
+//      apart in the row, little more than k lane maxima reach it;
+//   2. the 8*NL elements of the lanes that reach T are read again, (lane, load) pairs over the threads, and the elements
+//      >= T are keyed by (value, id) and ranked by counting.
+// More than 128 such elements (clusters, ties), or a vocabulary of more than 16 chunks, take a second bound first: a
+// histogram of the lane maxima that reach T names the bin of the k-th largest lane maximum.  If that leaves too many as
+// well (rows dominated by ties, fewer than k finite entries), an exact but slow extract-max loop over the row decides.
+// The kernel is two dependent trips to memory (2 x 1.5 us) and the wave arithmetic between them.
 #define SEL_CAP 128
+#define SEL_WAVE_CAP 64  // hot lanes of one wave
 __device__ __forceinline__ float load_elem(const RowArgs &a, int64_t g, int id) {
     if (a.dtype == DT_BF16) return bf16_bits_to_float(((const uint16_t *)a.logits)[g * a.row_stride + id]);
     return ((const float *)a.logits)[g * a.row_stride + id];
+}
+// The eight elements from id0 on of row g; returns where they really start (group_start), those before id0 and past the
+// row are -inf.
+template <bool BF16>
+__device__ __forceinline__ int load_octet(const RowArgs &a, int64_t g, int id0, bool vec, float (&xv)[8]) {
+    if (!vec) {  // uniform
+#pragma unroll
+        for (int e = 0; e < 8; ++e) xv[e] = load_elem(a, g, min(id0 + e, a.V - 1));
+#pragma unroll
+        for (int e = 0; e < 8; ++e) xv[e] = id0 + e < a.V ? xv[e] : -INFINITY;
+        return id0;
+    }
+    const int start = group_start(a.V, id0);
+    if (BF16) {
+        const uint4 r = load16((const uint16_t *)a.logits + g * a.row_stride + start);
+        const u32 rr[4] = {r.x, r.y, r.z, r.w};
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            xv[2 * p] = __uint_as_float(rr[p] << 16);
+            xv[2 * p + 1] = __uint_as_float(rr[p] & 0xFFFF0000u);
+        }
+    } else {
+        const float *src = (const float *)a.logits + g * a.row_stride + start;
+        const uint4 r0 = load16(src), r1 = load16(src + 4);
+        const u32 rr[8] = {r0.x, r0.y, r0.z, r0.w, r1.x, r1.y, r1.z, r1.w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) xv[e] = __uint_as_float(rr[e]);
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) xv[e] = start + e >= id0 ? xv[e] : -INFINITY;
+    return start;
+}
+// smallest float whose ordered image has these upper 16 bits (the bin of -inf holds nothing else)
+__device__ __forceinline__ float key_edge(u32 k16) { return k16 <= 0x007Fu ? -INFINITY : unord32(k16 << 16); }
+// k-th largest of the 256 16-bit keys held four to a lane
+__device__ __forceinline__ u32 wave_kth_of_256(const u32 (&ky)[4], int k) {
+    auto reach = [&](u32 t) {  // how many keys are >= t
+        int n = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) n += __popcll(__ballot(ky[i] >= t));
+        return n;
+    };
+    // the k-th is nearly always within 255 of the largest (bf16: two powers of two): eight steps instead of sixteen
+    const u32 top = wave_max_u32(max(max(ky[0], ky[1]), max(ky[2], ky[3])));
+    u32 t = top > 255u ? top - 255u : 0u;
+    int bits = 8;
+    if (t > 0u && reach(t) < k) { t = 0u; bits = 16; }
+    for (int bit = bits - 1; bit >= 0; --bit) {
+        const u32 cand = t + (1u << bit);
+        if (reach(cand) >= k) t = cand;
+    }
+    return t;
 }
 
 template <int MODE, bool BF16>
@@ -266,14 +307,27 @@ __global__ __launch_bounds__(256) void row_select_kernel(RowArgs a, int nl, int 
     const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int V = a.V, E = 8 * nl;
     const int n_lanes = S * 256;
-    const float *lm = a.lane_max + g * n_lanes;
+    typedef LaneMax<BF16> LM;
+    const LM *lm = (const LM *)a.lane_max + g * n_lanes;
     // the lane maxima do not depend on the row's metadata (two dependent global reads): ask for them
     // first, and wave 3 for the row's (max, sum) partials.  Rows that turn out to be dead have their
     // slots in the workspace all the same.
+    // Thread tid holds lane maxima 4 (256 i + tid) .. + 3, i < S / 4 (the same lane of a chunk's four waves: one load),
+    // or, in rows of up to three chunks, 256 j + tid, j < S.
+    const bool quads = S >= 4;
+    struct alignas(4 * sizeof(LM)) Quad { LM v[4]; };
     float it[16];
     if (S <= 16) {
+        if (quads) {
+            Quad q[4];
 #pragma unroll
-        for (int j = 0; j < 16; ++j) it[j] = lm[min(j, S - 1) * 256 + tid];
+            for (int i = 0; i < 4; ++i) q[i] = ((const Quad *)lm)[min(256 * i + tid, S * 64 - 1)];
+#pragma unroll
+            for (int j = 0; j < 16; ++j) it[j] = lane_max_value<BF16>(q[j >> 2].v[j & 3]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 3; ++j) it[j] = lane_max_value<BF16>(lm[min(j, S - 1) * 256 + tid]);
+        }
     }
     const bool lse_wave = w == 3 && a.want_lse && lse;
     float2 pm = make_float2(-INFINITY, 0.f);
@@ -282,11 +336,11 @@ __global__ __launch_bounds__(256) void row_select_kernel(RowArgs a, int nl, int 
     if (!meta.valid) return;
     const int k = meta.k;
 
-    __shared__ float s_T[4];
+    __shared__ __attribute__((aligned(16))) uint16_t s_key[256];
     __shared__ __attribute__((aligned(16))) u32 s_hist[256];
-    __shared__ int s_hot[SEL_CAP];
+    __shared__ int s_hot[4 * SEL_WAVE_CAP];
     __shared__ int s_h;
-    __shared__ u64 s_fin[SEL_CAP];
+    __shared__ __attribute__((aligned(16))) u64 s_fin[SEL_CAP];
     __shared__ int s_n2;
     __shared__ u64 s_best[4];
 
@@ -299,36 +353,126 @@ __global__ __launch_bounds__(256) void row_select_kernel(RowArgs a, int nl, int 
         tv[r] = viable ? v : -INFINITY;
         if (ti) ti[r] = viable ? (int32_t)id : -1;
     };
+    // ---- the row's log-sum-exp, by wave 3 ----------------------------------------------------------------
+    auto row_lse = [&]() {
+        if (!lse_wave) return;
+        const float cexp = 1.4426950408889634f * a.inv_t;
+        float M = -INFINITY, Ssum = 0.f;
+        if (S <= 16) {
+            if (lane < S * 4) { M = pm.x; Ssum = pm.y; }
+        } else {
+            for (int i = lane; i < S * 4; i += 64) {
+                const float2 p = a.part_ms[g * S * 4 + i];
+                const float M2 = fmaxf(M, p.x);
+                if (M2 != -INFINITY)
+                    Ssum = Ssum * __builtin_amdgcn_exp2f((M - M2) * cexp) + p.y * __builtin_amdgcn_exp2f((p.x - M2) * cexp);
+                M = M2;
+            }
+        }
+        const float Mw = wave_max(M);
+        float term = (Ssum > 0.f) ? Ssum * __builtin_amdgcn_exp2f((M - Mw) * cexp) : 0.f;
+        term = wave_sum(term);
+        if (lane == 0) lse[meta.out] = (Mw == -INFINITY) ? -INFINITY : Mw * a.inv_t + __logf(term);
+    };
+    // The eight elements of load n of lane maximum i (chunk, lane, wave): those that reach T become candidates, room for
+    // them with one LDS add.
+    const int nl_log2 = nl == 4 ? 2 : nl == 2 ? 1 : 0;  // chunk multipliers are 1, 2 or 4
+    auto reread = [&](int i, int n, float T) {
+        const int id0 = (i >> 8) * (256 * E) + (i & 3) * (64 * E) + ((i >> 2) & 63) * 8 + n * 512;
+        float xv[8];
+        const int start = load_octet<BF16>(a, g, id0, vec, xv);
+        int hits = 0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) hits += xv[e] >= T ? 1 : 0;
+        if (hits > 0) {
+            int slot = atomicAdd(&s_n2, hits);
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (xv[e] >= T) {
+                    if (slot < SEL_CAP) s_fin[slot] = make_key(xv[e], (u32)(start + e));
+                    ++slot;
+                }
+        }
+    };
+    // candidate t ranks itself against all n2 keys (LDS broadcasts, eight in flight)
+    auto rank_and_emit = [&](int n2) {
+        if (tid < SEL_CAP && (tid & ~63) < n2) {  // the waves that hold a candidate
+            const u64 mine = tid < n2 ? s_fin[tid] : 0ull;
+            int r0 = 0, r1 = 0;
+            for (int j0 = 0; j0 < n2; j0 += 8) {
+                u64 o[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) o[j] = s_fin[min(j0 + j, SEL_CAP - 1)];
+#pragma unroll
+                for (int j = 0; j < 8; j += 2) {  // s_fin[n2 ..] may hold anything: masked
+                    r0 += j0 + j < n2 && o[j] > mine ? 1 : 0;
+                    r1 += j0 + j + 1 < n2 && o[j + 1] > mine ? 1 : 0;
+                }
+            }
+            if (tid < n2 && r0 + r1 < k) emit(r0 + r1, mine);
+        }
+    };
 
-    // ---- 1. thread maxima, per-wave k-th largest, T0 ------------------------------------------
+    // ---- 1. thread maxima and T -------------------------------------------------------------------
     float tmax = -INFINITY;
     if (S <= 16) {
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
-            it[j] = j < S ? it[j] : -INFINITY;
+            const bool have = quads ? 256 * (j >> 2) + tid < S * 64 : j < S;
+            it[j] = have ? it[j] : -INFINITY;
             tmax = fmaxf(tmax, it[j]);
         }
     } else {
-        for (int j = 0; j < S; ++j) tmax = fmaxf(tmax, lm[j * 256 + tid]);
+        for (int j = 0; j < S; ++j) tmax = fmaxf(tmax, lane_max_value<BF16>(lm[j * 256 + tid]));
     }
-    const float Tw = unord32(wave_kth_largest<BF16 ? 16 : 0>(ord32(tmax), k));
-    if (lane == 0) s_T[w] = Tw;
+    s_key[tid] = (uint16_t)(ord32(tmax) >> 16);
     if (tid == 0) { s_n2 = 0; s_h = 0; }
+    __syncthreads();
+    const uint2 k4 = ((const uint2 *)s_key)[lane];
+    const u32 ky[4] = {k4.x & 0xFFFFu, k4.x >> 16, k4.y & 0xFFFFu, k4.y >> 16};
+    const u32 key0 = wave_kth_of_256(ky, k);
+    const float T0 = key_edge(key0);
+
+    // ---- 2. the lanes that reach T, read again ------------------------------------------------------
+    if (S <= 16) {
+        // Every wave by itself: its hot lanes into a list of its own (a prefix sum over the lanes instead of an LDS
+        // counter, no barrier), then (hot lane, load n) pairs over its lanes.
+        u32 hot = 0;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) hot |= (it[j] >= T0 ? 1u : 0u) << j;
+        const int mine = __popc(hot), incl = wave_scan_incl_i32(mine);
+        const int h = __builtin_amdgcn_readlane(incl, 63);
+        if (h > SEL_WAVE_CAP) {  // ties: this bound does not cut
+            if (lane == 0) s_n2 = SEL_CAP + 1;
+        } else {
+            int *list = s_hot + w * SEL_WAVE_CAP;
+            for (int at = incl - mine; hot; hot &= hot - 1) {
+                const int j = __builtin_ctz(hot);
+                list[at++] = quads ? 4 * (256 * (j >> 2) + tid) + (j & 3) : 256 * j + tid;
+            }
+            __builtin_amdgcn_wave_barrier();
+            for (int q = lane; q < h * nl; q += 64) reread(list[q >> nl_log2], q & (nl - 1), T0);
+        }
+        __syncthreads();
+        const int n2 = s_n2;
+        row_lse();
+        if (n2 <= SEL_CAP) {
+            rank_and_emit(n2);
+            return;
+        }
+        __syncthreads();  // s_n2 has been read
+        if (tid == 0) s_n2 = 0;
+    } else {
+        row_lse();
+    }
+
+    // ---- second bound: histogram of the lane maxima >= T0; its scan from the top gives T1 ------------
+    auto lane_val = [&](int j) { return lane_max_value<BF16>(lm[j * 256 + tid]); };
     s_hist[tid] = 0u;
     __syncthreads();
-    const float T0 = fmaxf(fmaxf(s_T[0], s_T[1]), fmaxf(s_T[2], s_T[3]));
-
-    // ---- 2. histogram of the lane maxima >= T0; its scan from the top gives T1 ------------------
-    const u32 key0 = ord32(T0) >> 16;
-    if (S <= 16) {
-#pragma unroll
-        for (int j = 0; j < 16; ++j)
-            if (it[j] >= T0) atomicAdd(&s_hist[min((ord32(it[j]) >> 16) - key0, 255u)], 1u);
-    } else {
-        for (int j = 0; j < S; ++j) {
-            const float v = lm[j * 256 + tid];
-            if (v >= T0) atomicAdd(&s_hist[min((ord32(v) >> 16) - key0, 255u)], 1u);
-        }
+    for (int j = 0; j < S; ++j) {
+        const float v = lane_val(j);
+        if (v >= T0) atomicAdd(&s_hist[min((ord32(v) >> 16) - key0, 255u)], 1u);
     }
     __syncthreads();
     // every wave by itself: lane L holds bins 4(63-L) .. 4(63-L)+3, so an ascending lane scan walks the
@@ -352,127 +496,26 @@ __global__ __launch_bounds__(256) void row_select_kernel(RowArgs a, int nl, int 
         n_hot = acc;
         // the lower edge of that bin: the smallest float whose upper 16 key bits are the bin's (bin 255 also
         // holds everything farther up: its lower edge still bounds all of it)
-        T1 = unord32((key0 + (u32)(4 * (63 - ls) + dg)) << 16);
-        T1 = fmaxf(T1, T0);  // bin 0 starts at T0 itself, not at the edge below it
+        T1 = key_edge(key0 + (u32)(4 * (63 - ls) + dg));
     }
-    bool slow = n_hot > SEL_CAP || n_hot < k;  // uniform over the workgroup
-
-    // ---- the row's log-sum-exp, by wave 3: called where the other waves wait for memory anyway ----------
-    bool lse_done = false;
-    auto row_lse = [&]() {
-        lse_done = true;
-        if (!lse_wave) return;
-        const float cexp = 1.4426950408889634f * a.inv_t;
-        float M = -INFINITY, Ssum = 0.f;
-        if (S <= 16) {
-            if (lane < S * 4) { M = pm.x; Ssum = pm.y; }
-        } else {
-            for (int i = lane; i < S * 4; i += 64) {
-                const float2 p = a.part_ms[g * S * 4 + i];
-                const float M2 = fmaxf(M, p.x);
-                if (M2 != -INFINITY)
-                    Ssum = Ssum * __builtin_amdgcn_exp2f((M - M2) * cexp) + p.y * __builtin_amdgcn_exp2f((p.x - M2) * cexp);
-                M = M2;
+    if (n_hot <= SEL_CAP && n_hot >= k) {  // uniform over the workgroup
+        for (int j = 0; j < S; ++j)
+            if (lane_val(j) >= T1) {
+                const int at = atomicAdd(&s_h, 1);
+                if (at < SEL_CAP) s_hot[at] = j * 256 + tid;
             }
-        }
-        const float Mw = wave_max(M);
-        float term = (Ssum > 0.f) ? Ssum * __builtin_amdgcn_exp2f((M - Mw) * cexp) : 0.f;
-        term = wave_sum(term);
-        if (lane == 0) lse[meta.out] = (Mw == -INFINITY) ? -INFINITY : Mw * a.inv_t + __logf(term);
-    };
-
-    if (!slow) {
-        // ---- 3. the hot lanes, in any order: a thread reserves room for its hits with one LDS add ----
-        {
-            int mine = 0;
-            if (S <= 16) {
-#pragma unroll
-                for (int j = 0; j < 16; ++j) mine += it[j] >= T1 ? 1 : 0;
-                if (mine > 0) {
-                    int at = atomicAdd(&s_h, mine);
-#pragma unroll
-                    for (int j = 0; j < 16; ++j)
-                        if (it[j] >= T1) { if (at < SEL_CAP) s_hot[at] = j * 256 + tid; ++at; }
-                }
-            } else {
-                for (int j = 0; j < S; ++j)
-                    if (lm[j * 256 + tid] >= T1) {
-                        const int at = atomicAdd(&s_h, 1);
-                        if (at < SEL_CAP) s_hot[at] = j * 256 + tid;
-                    }
-            }
-        }
         __syncthreads();
         const int h = min(s_h, SEL_CAP);
-        const int nl_log2 = nl == 4 ? 2 : nl == 2 ? 1 : 0;  // chunk multipliers are 1, 2 or 4
-        if (h * nl <= 192) row_lse();  // wave 3 has no hot lane to re-read: it merges while the others wait for theirs
-        // ---- 4. re-read the hot lanes: (hot lane, load n) pairs spread over the threads ----
-        for (int q = tid; q < h * nl; q += 256) {
-            const int gl = s_hot[q >> nl_log2], n = q & (nl - 1);
-            const int c = gl >> 8, ww = (gl >> 6) & 3, l = gl & 63;
-            const int id0 = c * (256 * E) + ww * (64 * E) + l * 8 + n * 512;
-            float xv[8];
-            if (BF16 && vec && id0 + 8 <= V) {
-                const uint4 r = load16((const uint16_t *)a.logits + g * a.row_stride + id0);
-                const u32 rr[4] = {r.x, r.y, r.z, r.w};
-#pragma unroll
-                for (int p = 0; p < 4; ++p) {
-                    xv[2 * p] = __uint_as_float(rr[p] << 16);
-                    xv[2 * p + 1] = __uint_as_float(rr[p] & 0xFFFF0000u);
-                }
-            } else if (!BF16 && vec && id0 + 8 <= V) {
-                const float *src = (const float *)a.logits + g * a.row_stride + id0;
-                const uint4 r0 = load16(src), r1 = load16(src + 4);
-                const u32 rr[8] = {r0.x, r0.y, r0.z, r0.w, r1.x, r1.y, r1.z, r1.w};
-#pragma unroll
-                for (int e = 0; e < 8; ++e) xv[e] = __uint_as_float(rr[e]);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) xv[e] = load_elem(a, g, min(id0 + e, V - 1));
-#pragma unroll
-                for (int e = 0; e < 8; ++e) xv[e] = id0 + e < V ? xv[e] : -INFINITY;
-            }
-            int hits = 0;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) hits += xv[e] >= T1 ? 1 : 0;
-            if (hits > 0) {
-                int slot = atomicAdd(&s_n2, hits);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    if (xv[e] >= T1) {
-                        if (slot < SEL_CAP) s_fin[slot] = make_key(xv[e], (u32)(id0 + e));
-                        ++slot;
-                    }
-                }
-            }
-        }
-        if (h * nl > 192) row_lse();
+        for (int q = tid; q < h * nl; q += 256) reread(s_hot[q >> nl_log2], q & (nl - 1), T1);
         __syncthreads();
         const int n2 = s_n2;
         if (n2 <= SEL_CAP) {
-            // ---- 5. candidate t ranks itself against all n2 keys (LDS broadcasts, eight in flight) ----
-            if (tid < SEL_CAP && (tid & ~63) < n2) {  // the waves that hold a candidate
-                const u64 mine = tid < n2 ? s_fin[tid] : 0ull;
-                int r0 = 0, r1 = 0;
-                for (int j0 = 0; j0 < n2; j0 += 8) {
-                    u64 o[8];
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) o[j] = s_fin[min(j0 + j, SEL_CAP - 1)];
-#pragma unroll
-                    for (int j = 0; j < 8; j += 2) {  // s_fin[n2 ..] may hold anything: masked
-                        r0 += j0 + j < n2 && o[j] > mine ? 1 : 0;
-                        r1 += j0 + j + 1 < n2 && o[j + 1] > mine ? 1 : 0;
-                    }
-                }
-                if (tid < n2 && r0 + r1 < k) emit(r0 + r1, mine);
-            }
+            rank_and_emit(n2);
             return;
         }
-        slow = true;
     }
 
     // ---- exact fallback: k rounds of "largest key below the previous winner" ----------------
-    if (!lse_done) row_lse();
     u64 prev = ~0ull;
     for (int r = 0; r < k; ++r) {
         u64 best = 0ull;
