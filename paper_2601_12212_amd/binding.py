@@ -1,4 +1,5 @@
-"""ctypes binding of libdt.so.  Argument marshalling only."""
+"""Binding of libdt.so.  Argument marshalling only: the launching entry points go through the native module _dtcall
+(csrc/pycall.c), the host-only ones through ctypes."""
 import ctypes as C
 import os
 
@@ -11,6 +12,7 @@ DT_TREE_EARLY_STOP = 1
 DT_ACCEPT_GREEDY, DT_ACCEPT_STOCHASTIC, DT_ACCEPT_SAMPLED = 0, 1, 2
 
 _lib = None
+_call = None
 
 
 class DtError(RuntimeError):
@@ -86,13 +88,17 @@ def dt_init():
         raise DtError("dt_init", rc)
 
 
-def _ptr(t):
-    return None if t is None else t.data_ptr()
+def _native():
+    """The marshalling module, bound to torch's dtypes and current stream on first use."""
+    global _call
+    if _call is None:
+        load_library()  # says so if nothing is built
+        import torch
 
-
-def _stream():
-    import torch
-    return torch.cuda.current_stream().cuda_stream
+        from . import _dtcall
+        _dtcall.setup(torch.float32, torch.bfloat16, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+        _call = _dtcall
+    return _call
 
 
 def _dtype(t):
@@ -116,48 +122,40 @@ def dt_workspace_bytes(batch, total_rows, V, TT_cap, Hq, D):
 
 
 def dt_topk_rows(logits, k, top_val, top_id, lse, ws):
-    n_rows, V = logits.shape
-    _check("dt_topk_rows", load_library().dt_topk_rows(
-        _stream(), _ptr(logits), _dtype(logits), n_rows, V, logits.stride(0), k, _ptr(top_val), _ptr(top_id),
-        _ptr(lse), _ptr(ws), ws.numel() * ws.element_size()))
+    rc = (_call or _native()).topk_rows(logits, k, top_val, top_id, lse, ws)
+    if rc:
+        raise DtError("dt_topk_rows", rc)
 
 
 def dt_topk_rows_static(logits, k, top_val, top_id, lse):
-    n_rows, V = logits.shape
-    _check("dt_topk_rows_static", load_library().dt_topk_rows_static(
-        _stream(), _ptr(logits), _dtype(logits), n_rows, V, logits.stride(0), k, _ptr(top_val), _ptr(top_id),
-        _ptr(lse)))
+    rc = (_call or _native()).topk_rows_static(logits, k, top_val, top_id, lse)
+    if rc:
+        raise DtError("dt_topk_rows_static", rc)
 
 
 def dt_build_tree(params, draft_logits, row_off, total_rows, root_token, TT_cap, n_nodes, tokens, parents, depth,
                   score, logp, src_row, anc_mask, ws, flags=0):
-    batch = params.shape[0]
-    V = draft_logits.shape[1]
-    _check("dt_build_tree", load_library().dt_build_tree(
-        _stream(), batch, _ptr(params), _ptr(draft_logits), _dtype(draft_logits), V, draft_logits.stride(0),
-        _ptr(row_off), total_rows, _ptr(root_token), TT_cap, _ptr(n_nodes), _ptr(tokens), _ptr(parents),
-        _ptr(depth), _ptr(score), _ptr(logp), _ptr(src_row), _ptr(anc_mask), _ptr(ws),
-        ws.numel() * ws.element_size(), flags))
+    rc = (_call or _native()).build_tree(params, draft_logits, row_off, total_rows, root_token, TT_cap, n_nodes, tokens, parents,
+                                         depth, score, logp, src_row, anc_mask, ws, flags)
+    if rc:
+        raise DtError("dt_build_tree", rc)
 
 
 def dt_tree_attention(q, k_tree, v_tree, n_nodes, k_prefix_ptrs, v_prefix_ptrs, prefix_len, max_prefix_len,
                       kv_stride_tok, kv_stride_head, anc_mask, scale, out, ws):
-    batch, TT_cap, Hq, D = q.shape
-    Hkv = k_tree.shape[2]
-    _check("dt_tree_attention", load_library().dt_tree_attention(
-        _stream(), batch, _dtype(q), Hq, Hkv, D, scale, _ptr(q), _ptr(k_tree), _ptr(v_tree), _ptr(n_nodes),
-        _ptr(k_prefix_ptrs), _ptr(v_prefix_ptrs), _ptr(prefix_len), max_prefix_len, kv_stride_tok, kv_stride_head,
-        _ptr(anc_mask), TT_cap, _ptr(out), _ptr(ws), 0 if ws is None else ws.numel() * ws.element_size()))
+    rc = (_call or _native()).tree_attention(q, k_tree, v_tree, n_nodes, k_prefix_ptrs, v_prefix_ptrs, prefix_len, max_prefix_len,
+                                             kv_stride_tok, kv_stride_head, anc_mask, scale, out, ws)
+    if rc:
+        raise DtError("dt_tree_attention", rc)
 
 
 def dt_accept(mode, temperature, target_logits, n_nodes, tokens, parents, depth, logp, anc_mask, philox_seed,
               philox_step, accept_len, best_node, path_nodes, out_tokens, node_argmax, ws):
-    batch, TT_cap, V = target_logits.shape
-    _check("dt_accept", load_library().dt_accept(
-        _stream(), batch, mode, temperature, _ptr(target_logits), _dtype(target_logits), V, target_logits.stride(1),
-        _ptr(n_nodes), _ptr(tokens), _ptr(parents), _ptr(depth), _ptr(logp), _ptr(anc_mask), TT_cap, philox_seed,
-        philox_step, _ptr(accept_len), _ptr(best_node), _ptr(path_nodes), _ptr(out_tokens), _ptr(node_argmax),
-        _ptr(ws), ws.numel() * ws.element_size()))
+    rc = (_call or _native()).accept_tree(mode, temperature, target_logits, n_nodes, tokens, parents, depth, logp, anc_mask,
+                                          philox_seed, philox_step, accept_len, best_node, path_nodes, out_tokens, node_argmax,
+                                          ws)
+    if rc:
+        raise DtError("dt_accept", rc)
 
 
 def dt_level_state_bytes(batch):
@@ -169,20 +167,18 @@ def dt_level_state_bytes(batch):
 def dt_expand_level(level, params, level_logits, rows_per_seq, prefix_len, TT_cap, state, n_expand, exp_token,
                     exp_parent_slot, exp_row, exp_pos, exp_mask, ws, flags=0):
     """level_logits: [batch * R, V] with R = 1 at level 1, rows_per_seq otherwise."""
-    batch = params.shape[0]
-    V = level_logits.shape[1]
-    _check("dt_expand_level", load_library().dt_expand_level(
-        _stream(), batch, level, _ptr(params), _ptr(level_logits), _dtype(level_logits), V, level_logits.stride(0),
-        rows_per_seq, _ptr(prefix_len), TT_cap, _ptr(state), _ptr(n_expand), _ptr(exp_token), _ptr(exp_parent_slot),
-        _ptr(exp_row), _ptr(exp_pos), _ptr(exp_mask), _ptr(ws), ws.numel() * ws.element_size(), flags))
+    rc = (_call or _native()).expand_level(level, params, level_logits, rows_per_seq, prefix_len, TT_cap, state, n_expand, exp_token,
+                                           exp_parent_slot, exp_row, exp_pos, exp_mask, ws, flags)
+    if rc:
+        raise DtError("dt_expand_level", rc)
 
 
 def dt_finish_tree(params, V, root_token, TT_cap, state, n_nodes, tokens, parents, depth, score, logp, src_row,
                    anc_mask, flags=0):
-    batch = params.shape[0]
-    _check("dt_finish_tree", load_library().dt_finish_tree(
-        _stream(), batch, _ptr(params), V, _ptr(root_token), TT_cap, _ptr(state), _ptr(n_nodes), _ptr(tokens),
-        _ptr(parents), _ptr(depth), _ptr(score), _ptr(logp), _ptr(src_row), _ptr(anc_mask), flags))
+    rc = (_call or _native()).finish_tree(params, V, root_token, TT_cap, state, n_nodes, tokens, parents, depth, score, logp,
+                                          src_row, anc_mask, flags)
+    if rc:
+        raise DtError("dt_finish_tree", rc)
 
 
 def dt_action_table():
@@ -203,13 +199,11 @@ def dt_policy_workspace_bytes(batch, F, H):
 def dt_policy_step(features, W1, b1, W2, b2, W3, b3, action_table, cache_interval, sample, philox_seed, philox_step,
                    cache_step, cached_action, params_out, action_out, queried_out, logits_out, ws):
     """features [batch, F]; W1 [F,H], W2 [H,H], W3 [H,A] float32 ([in][out]); action_table int32 [A,3] on the device."""
-    batch, F = features.shape
-    H, A = W3.shape
-    _check("dt_policy_step", load_library().dt_policy_step(
-        _stream(), batch, _dtype(features), _ptr(features), features.stride(0), F, H, A, _ptr(W1), _ptr(b1), _ptr(W2),
-        _ptr(b2), _ptr(W3), _ptr(b3), _ptr(action_table), cache_interval, int(sample), philox_seed, philox_step,
-        _ptr(cache_step), _ptr(cached_action), _ptr(params_out), _ptr(action_out), _ptr(queried_out), _ptr(logits_out),
-        _ptr(ws), ws.numel() * ws.element_size()))
+    rc = (_call or _native()).policy_step(features, W1, b1, W2, b2, W3, b3, action_table, cache_interval, sample, philox_seed,
+                                          philox_step, cache_step, cached_action, params_out, action_out, queried_out,
+                                          logits_out, ws)
+    if rc:
+        raise DtError("dt_policy_step", rc)
 
 
 def dt_commit(dtype_of, Hkv, D, k_tree_ptrs, v_tree_ptrs, k_prefix_ptrs, v_prefix_ptrs, prefix_len, prefix_cap,
@@ -217,11 +211,11 @@ def dt_commit(dtype_of, Hkv, D, k_tree_ptrs, v_tree_ptrs, k_prefix_ptrs, v_prefi
               next_root_token):
     """k_tree_ptrs / v_tree_ptrs: int64 device tensors [n_layers]; k_prefix_ptrs / v_prefix_ptrs: [n_layers, batch];
     dtype_of: any tensor of the cache dtype."""
-    n_layers, batch = k_prefix_ptrs.shape
-    _check("dt_commit", load_library().dt_commit(
-        _stream(), batch, n_layers, _dtype(dtype_of), Hkv, D, _ptr(k_tree_ptrs), _ptr(v_tree_ptrs), _ptr(k_prefix_ptrs),
-        _ptr(v_prefix_ptrs), _ptr(prefix_len), _ptr(prefix_cap), kv_stride_tok, kv_stride_head, _ptr(n_nodes),
-        _ptr(path_nodes), _ptr(accept_len), _ptr(out_tokens), TT_cap, _ptr(new_prefix_len), _ptr(next_root_token)))
+    rc = (_call or _native()).commit(dtype_of, Hkv, D, k_tree_ptrs, v_tree_ptrs, k_prefix_ptrs, v_prefix_ptrs, prefix_len, prefix_cap,
+                                     kv_stride_tok, kv_stride_head, n_nodes, path_nodes, accept_len, out_tokens, TT_cap,
+                                     new_prefix_len, next_root_token)
+    if rc:
+        raise DtError("dt_commit", rc)
 
 
 def dt_profile_enable(max_launches):
@@ -238,6 +232,7 @@ def dt_profile_read(kernel_id):
 
 def dt_reward_step(accept_len, count_bonus, elapsed_seconds, cache_step, reward_sum, reward_steps, reward_avg,
                    interval_done, elapsed_per_seq=None):
-    _check("dt_reward_step", load_library().dt_reward_step(
-        _stream(), accept_len.shape[0], _ptr(accept_len), int(count_bonus), float(elapsed_seconds), _ptr(elapsed_per_seq),
-        _ptr(cache_step), _ptr(reward_sum), _ptr(reward_steps), _ptr(reward_avg), _ptr(interval_done)))
+    rc = (_call or _native()).reward_step(accept_len, count_bonus, elapsed_seconds, cache_step, reward_sum, reward_steps, reward_avg,
+                                          interval_done, elapsed_per_seq)
+    if rc:
+        raise DtError("dt_reward_step", rc)

@@ -1,11 +1,14 @@
-"""Compile the HIP kernels and the C ABI into paper_2601_12212_amd/libdt.so (gfx950 only)."""
+"""Compile the HIP kernels and the C ABI into paper_2601_12212_amd/libdt.so (gfx950 only), and the argument marshalling of
+the Python binding into paper_2601_12212_amd/_dtcall.so (gcc; finds libdt.so beside itself)."""
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdt.so")
+PYCALL = os.path.join(HERE, "_dtcall.so")
 SOURCES = ["api.cpp", "profile.cpp", "rows.hip", "tree.hip", "attention.hip", "accept.hip", "commit.hip", "policy.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          # packed-FP32 code generation is switched off: some of its instruction forms have given wrong
@@ -35,6 +38,10 @@ def build(verbose=False):
     tmp = LIB + ".tmp%d" % os.getpid()
     subprocess.check_call([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs)
     os.replace(tmp, LIB)
+    tmp = PYCALL + ".tmp%d" % os.getpid()
+    subprocess.check_call(["gcc", "-O2", "-shared", "-fPIC", "-Wall", "-I" + sysconfig.get_paths()["include"],
+                           os.path.join(CSRC, "pycall.c"), "-o", tmp, "-L" + HERE, "-l:libdt.so", "-Wl,-rpath,$ORIGIN"])
+    os.replace(tmp, PYCALL)
     return LIB
 
 
