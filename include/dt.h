@@ -184,7 +184,7 @@ int dt_build_tree(void *stream, int batch, const dt_params *params, const void *
  *       cannot check them; the kernels read 16 bytes at a time from them)
  *   max_prefix_len : host upper bound of prefix_len[] (sizes the launch)
  * Arithmetic: bf16 inputs, fp32 accumulation, fp32 softmax, output rounded to bf16; fp32 inputs are
- * handled entirely in fp32.  bf16 with D == 128 and both strides multiples of 8 elements runs on the
+ * handled entirely in fp32.  bf16 with D == 128 or D == 64 and both strides multiples of 8 elements runs on the
  * matrix cores; every other combination with D <= 128 runs on a plain vector-ALU kernel (correct, slow).
  * Errors: Hq % Hkv != 0, scale <= 0, negative strides, q / k_tree / v_tree / out not 16-byte aligned
  * -> DT_ERR_INVALID_ARG; D > 128, batch > 8191 or Hq > 65535 -> DT_ERR_LIMIT.

@@ -175,7 +175,7 @@ __global__ __launch_bounds__(256) void node_sample_kernel(AcceptArgs a) {
 
 __global__ __launch_bounds__(256) void accept_kernel(AcceptArgs a) {
     const int b = blockIdx.x, tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
-    const int N = min(max(a.n_nodes[b], 1), a.TT_cap);
+    const int n_raw = a.n_nodes[b];
     const int64_t o = (int64_t)b * a.TT_cap;
     const bool stochastic = a.mode == DT_ACCEPT_STOCHASTIC;
     const bool sampled = a.mode == DT_ACCEPT_SAMPLED;  // node_sample_kernel has drawn every node's token
@@ -190,37 +190,41 @@ __global__ __launch_bounds__(256) void accept_kernel(AcceptArgs a) {
     __shared__ double s_wtot[4];
     __shared__ int s_bonus;
 
-    // ---- everything a node needs later is requested now, so the loads overlap the merge -------
-    int my_tok = 0, my_par = 0, my_dep = 0;
-    u64 my_m0 = 0ull, my_m1 = 0ull;
-    float my_logp = 0.f;
-    if (tid < N) {
-        my_tok = a.tokens[o + tid];
-        my_par = a.parents[o + tid];
-        my_dep = a.depth[o + tid];
-        my_m0 = a.anc_mask[(o + tid) * DT_MASK_WORDS];
-        my_m1 = a.anc_mask[(o + tid) * DT_MASK_WORDS + 1];
-        if (stochastic) my_logp = a.logp[o + tid];
-    }
+    // ---- everything a node needs later, and the row partials, are requested before the node count is back: one trip to
+    //      memory instead of two (padded entries and rows belong to the buffers; what they hold is not used) --------------
+    const int me = min(tid, a.TT_cap - 1);
+    const int my_tok = a.tokens[o + me], my_par = a.parents[o + me], my_dep = a.depth[o + me];
+    const u64 my_m0 = a.anc_mask[(o + me) * DT_MASK_WORDS], my_m1 = a.anc_mask[(o + me) * DT_MASK_WORDS + 1];
+    const float my_logp = stochastic ? a.logp[o + me] : 0.f;
+    // four adjacent lanes share a row, each takes every fourth chunk; rows tid / 4 and 64 + tid / 4
+    const int part = tid & 3;
+    u64 key0[2][4];
+    float2 p0[2][4];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+        if (64 * h < a.TT_cap) {  // uniform
+            const int64_t g = o + min(64 * h + (tid >> 2), a.TT_cap - 1);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int c = min(part + 4 * u, S - 1);  // past the end: the last chunk again, ignored below
+                key0[h][u] = a.part_keys[g * S + c];
+                if (stochastic) p0[h][u] = a.part_ms[g * S + c];
+            }
+        }
+    const int N = min(max(n_raw, 1), a.TT_cap);
 
-    // ---- merge the row partials: four adjacent lanes share a row, each takes every fourth chunk --
+    // ---- merge the row partials --------------------------------------------------------------------
     {
         const float cexp = 1.4426950408889634f * inv_t;
-        const int part = tid & 3;
-        for (int i0 = 0; i0 < N; i0 += 64) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int i0 = 64 * h;
+            if (i0 >= N) break;  // uniform
             const int i = i0 + (tid >> 2);
             const int64_t g = o + min(i, N - 1);
             u64 best = 0ull;
             float M = -INFINITY, Ssum = 0.f;
-            for (int c0 = part; c0 < S; c0 += 16) {  // four chunks per trip to memory
-                u64 key[4];
-                float2 p[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int c = min(c0 + 4 * u, S - 1);  // past the end: the last chunk again, ignored below
-                    key[u] = a.part_keys[g * S + c];
-                    if (stochastic) p[u] = a.part_ms[g * S + c];
-                }
+            auto take = [&](int c0, const u64 (&key)[4], const float2 (&p)[4]) {
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     if (c0 + 4 * u >= S) continue;
@@ -233,6 +237,18 @@ __global__ __launch_bounds__(256) void accept_kernel(AcceptArgs a) {
                         M = M2;
                     }
                 }
+            };
+            take(part, key0[h], p0[h]);
+            for (int c0 = part + 16; c0 < S; c0 += 16) {  // four chunks per trip to memory
+                u64 key[4];
+                float2 p[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int c = min(c0 + 4 * u, S - 1);
+                    key[u] = a.part_keys[g * S + c];
+                    if (stochastic) p[u] = a.part_ms[g * S + c];
+                }
+                take(c0, key, p);
             }
 #pragma unroll
             for (int off = 1; off <= 2; off <<= 1) {  // the four lanes of the row

@@ -136,22 +136,7 @@ __device__ __forceinline__ float half_swap_sum(float x) {
 #define ATT_ROWS_PER_WAVE 32
 #define ATT_WAVES 4
 #define ATT_MTILE (ATT_ROWS_PER_WAVE * ATT_WAVES)
-#define K_PITCH (128 + 8)   // bf16 elements per K row in LDS (272 B: conflict-free 16 B reads)
-// bf16 elements per row of a row-major V tile (288 B): the transposing read takes 4 rows x 32 B
-// per 16 lanes, and a pitch of 8 banks modulo 32 spreads those four rows over all 32 banks
-#define V_PITCH (128 + 32)
-#define VT_PITCH 40         // bf16 elements per V^T row in LDS (80 B)
-#define ATT_MAX_SPLITS 16
 #define LAZY_LOG2 8.0f        // how far (in powers of two) a probability may exceed 1 before the reference maximum moves
-
-// position of key kk (0..31) inside a V^T row: 16-byte unit (step, lane half) then index,
-// mirroring which accumulator registers of S^T a lane holds (rows 8*(i/4) + 4*half + i%4).
-__device__ __forceinline__ int vt_pos(int kk) {
-    const int step = kk >> 4, q = kk & 15;
-    const int half = (q >> 2) & 1, idx = ((q >> 3) << 2) | (q & 3);
-    return step * 16 + half * 8 + idx;
-}
-
 
 // 32-bit visibility window of one query over keys t0 .. t0+31, where off = t0 - L (uniform): the
 // prefix keys (negative positions) are visible, tree key j is visible iff bit j of the node's
@@ -663,8 +648,13 @@ __global__ __launch_bounds__(256) void attn_gang_combine_kernel(AttnArgs a, int 
 // into padded tiles (one workgroup per unit, short key ranges), and four waves that load straight
 // into LDS (DIRECT: several workgroups per unit, one wave per SIMD, so latency is hidden inside the
 // wave by having every operand read of a block in flight at once).
-#define KT_ELEMS (ATT_KB * K_PITCH)              // per-wave K tile: 32 rows of 272 B
-#define WT_ELEMS (KT_ELEMS + ATT_KB * V_PITCH)   // both tiles of a wave (V: 32 rows of 288 B): 17.5 KB
+// Staged layout, both tiles row-major with padded rows of bf16 elements.  K: the 16 B reads of 16 consecutive rows fall
+// into 16 different slots of 256 B (pitch 272 B at D = 128, 144 B at D = 64).  V: the transposing read takes 4 rows x 64 B
+// per 32 lanes, which fall into four different 64-byte groups (pitch 320 B, 192 B).
+template <int D>
+struct WaveTile {
+    static constexpr int K_PITCH = D + 8, V_PITCH = D + 32, K_ELEMS = ATT_KB * K_PITCH, ELEMS = K_ELEMS + ATT_KB * V_PITCH;
+};
 #define WD_TILE (ATT_KB * 256)                  // direct layout: one K or V tile of a wave, unpadded rows
 #define WD_STAGE (2 * WD_TILE)                  // K tile + V tile of one stage
 #define WD_LDS_BYTES (4 * 2 * WD_STAGE)         // four waves, two stages: 128 KB
@@ -674,14 +664,15 @@ __global__ __launch_bounds__(256) void attn_gang_combine_kernel(AttnArgs a, int 
 // (Merging in the last workgroup to arrive was tried: the device-scope release/acquire it needs
 // writes back and invalidates the whole L2 of the XCD and cost far more than a second launch.)
 struct SplitBuf {
-    float4 *o;    // [unit, KS, 4 waves, 4, 64 lanes]: the owner waves' output registers
+    float4 *o;    // [unit, KS, D/32 waves, 4, 64 lanes]: the owner waves' output registers
     float2 *ml;   // [unit, KS, 32]: (max, sum) per query row
 };
 
 template <int D, int NW, bool DIRECT>
 __global__ __launch_bounds__(64 * NW) void attn_wave_kernel(AttnArgs a, int KS, SplitBuf sb) {
-    static_assert(D == 128 && (NW == 4 || NW == 8) && (!DIRECT || NW == 4), "shape");
+    static_assert((D == 128 || D == 64) && (NW == 4 || NW == 8) && (!DIRECT || (NW == 4 && D == 128)), "shape");
     constexpr int KSTEPS = D / 16, DBLK = D / 32;
+    constexpr int K_PITCH = WaveTile<D>::K_PITCH, V_PITCH = WaveTile<D>::V_PITCH;
     const int G = a.Hq / a.Hkv;
     // blockIdx.x = kv head: workgroups are dealt to the 8 XCDs round-robin by linear id, so every
     // row block and split of one kv head lands on one XCD and shares its L2 copy of that head's K/V
@@ -708,8 +699,8 @@ __global__ __launch_bounds__(64 * NW) void attn_wave_kernel(AttnArgs a, int KS, 
     // LDS: NW private tiles during the loop, then the exchange area of the partial results
     extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];
     __shared__ float s_m[NW][32], s_l[NW][32];
-    __bf16 *kt = (__bf16 *)s_dyn + w * WT_ELEMS;   // staged layout (!DIRECT): padded rows
-    __bf16 *vt = kt + KT_ELEMS;
+    __bf16 *kt = (__bf16 *)s_dyn + w * WaveTile<D>::ELEMS;   // staged layout (!DIRECT): padded rows
+    __bf16 *vt = kt + WaveTile<D>::K_ELEMS;
     unsigned char *wtile = s_dyn + w * 2 * WD_STAGE;  // direct layout: two stages of (K tile, V tile), 256-byte rows
 
     bf16x8 qreg[KSTEPS];
@@ -878,32 +869,33 @@ __global__ __launch_bounds__(64 * NW) void attn_wave_kernel(AttnArgs a, int KS, 
                         __builtin_shufflevector(vlo[db][st], vhi[db][st], 0, 1, 2, 3, 4, 5, 6, 7), pb[st], oacc[db], 0, 0, 0);
         }
     } else {
-    const int kq = lane >> 4, dc = lane & 15;
-    // Loading role of a lane, the same for K and V: load i takes key (i>>2)*16 + 4*kq + (i&3) of
-    // the block, columns 8dc..8dc+7, so 16 lanes cover one 256-byte row (fully coalesced).
+    // Loading role of a lane, the same for K and V: load i takes key RPL i + lane / LPR of the block, columns 8 dc ..
+    // 8 dc + 7, so the LPR lanes of a row cover it (fully coalesced).
     // Inside the prefix the address is a uniform block base plus a fixed 32-bit lane offset.
-    u32 loff[8];
+    constexpr int LPR = D / 8, RPL = 64 / LPR, NLD = ATT_KB / RPL;
+    const int kq = lane / LPR, dc = lane % LPR;
+    u32 loff[NLD];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) loff[i] = (u32)(((i >> 2) * 16 + 4 * kq + (i & 3)) * stok + 8 * dc) * 2u;
+    for (int i = 0; i < NLD; ++i) loff[i] = (u32)((RPL * i + kq) * stok + 8 * dc) * 2u;
     const bool small_stride = (int64_t)ATT_KB * stok * 2 < ((int64_t)1 << 31);
 
-    // Every load is unconditional, so the sixteen loads of a block are in flight together.  Keys
+    // Every load is unconditional, so the loads of a block are in flight together.  Keys
     // past the end are read from the last valid row; their scores are masked to -inf below, so
     // their probabilities are exactly 0 and the duplicated V rows contribute nothing.
-    bf16x8 kn[8], vn[8];
+    bf16x8 kn[NLD], vn[NLD];
     auto fetch = [&](int kb) {
         if (small_stride && kb * ATT_KB + ATT_KB <= L) {  // block inside the prefix (uniform test)
             const gbytep kbase = (gbytep)(kpre + (int64_t)kb * ATT_KB * stok);
             const gbytep vbase = (gbytep)(vpre + (int64_t)kb * ATT_KB * stok);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
+            for (int i = 0; i < NLD; ++i) {
                 kn[i] = *(gbf16x8p)(kbase + loff[i]);
                 vn[i] = *(gbf16x8p)(vbase + loff[i]);
             }
         } else {                                           // block touching the tree keys or the end
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int t = min(kb * ATT_KB + (i >> 2) * 16 + 4 * kq + (i & 3), Tk - 1);
+            for (int i = 0; i < NLD; ++i) {
+                const int t = min(kb * ATT_KB + RPL * i + kq, Tk - 1);
                 const int64_t o = (t < L ? (int64_t)t * stok : (int64_t)(t - L) * stree) + 8 * dc;
                 kn[i] = gload8((t < L ? kpre : ktree) + o);
                 vn[i] = gload8((t < L ? vpre : vtree) + o);
@@ -917,8 +909,8 @@ __global__ __launch_bounds__(64 * NW) void attn_wave_kernel(AttnArgs a, int KS, 
         // The prefetched block goes straight into the wave's two LDS tiles, both row-major, which
         // frees its registers for the next prefetch, issued before any arithmetic on this block.
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int r = (i >> 2) * 16 + 4 * kq + (i & 3);
+        for (int i = 0; i < NLD; ++i) {
+            const int r = RPL * i + kq;
             *(bf16x8 *)(kt + r * K_PITCH + 8 * dc) = kn[i];
             *(bf16x8 *)(vt + r * V_PITCH + 8 * dc) = vn[i];
         }
@@ -1000,7 +992,8 @@ __global__ __launch_bounds__(64 * NW) void attn_wave_kernel(AttnArgs a, int KS, 
     // ---- the partial results meet ----------------------------------------------------------------
     float l_tot = half_swap_sum(l_run);
     __syncthreads();  // all private tiles are dead
-    // exchange layout: float4 slot (slice, q, lane) at ((slice*16 + q)*64 + lane), q = 4 db + i/4
+    // exchange layout: float4 slot (slice, q, lane) at ((slice*XQ + q)*64 + lane), q = 4 db + i/4
+    constexpr int XQ = 4 * DBLK;
     float4 *xb = (float4 *)s_dyn;
     if (NW == 8) {
         // stage A: wave w+4 hands its whole partial to wave w
@@ -1010,7 +1003,7 @@ __global__ __launch_bounds__(64 * NW) void attn_wave_kernel(AttnArgs a, int KS, 
             for (int db = 0; db < DBLK; ++db)
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    xb[((w - 4) * 16 + db * 4 + q) * 64 + lane] =
+                    xb[((w - 4) * XQ + db * 4 + q) * 64 + lane] =
                         make_float4(oacc[db][4 * q], oacc[db][4 * q + 1], oacc[db][4 * q + 2], oacc[db][4 * q + 3]);
         }
         __syncthreads();
@@ -1022,7 +1015,7 @@ __global__ __launch_bounds__(64 * NW) void attn_wave_kernel(AttnArgs a, int KS, 
             for (int db = 0; db < DBLK; ++db)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const float4 o = xb[(w * 16 + db * 4 + q) * 64 + lane];
+                    const float4 o = xb[(w * XQ + db * 4 + q) * 64 + lane];
                     oacc[db][4 * q] = oacc[db][4 * q] * f1 + o.x * f2;
                     oacc[db][4 * q + 1] = oacc[db][4 * q + 1] * f1 + o.y * f2;
                     oacc[db][4 * q + 2] = oacc[db][4 * q + 2] * f1 + o.z * f2;
@@ -1033,7 +1026,7 @@ __global__ __launch_bounds__(64 * NW) void attn_wave_kernel(AttnArgs a, int KS, 
         }
         __syncthreads();
     }
-    // stage B: waves 0..3; wave w finishes output columns [32w, 32w+32)
+    // stage B: waves 0..3; wave w < D/32 finishes output columns [32w, 32w+32)
     if (w < 4) {
         if (half == 0) { s_m[w][col] = m_run; s_l[w][col] = l_tot; }
 #pragma unroll
@@ -1041,12 +1034,12 @@ __global__ __launch_bounds__(64 * NW) void attn_wave_kernel(AttnArgs a, int KS, 
             if (db == w) continue;
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                xb[(w * 16 + db * 4 + q) * 64 + lane] =
+                xb[(w * XQ + db * 4 + q) * 64 + lane] =
                     make_float4(oacc[db][4 * q], oacc[db][4 * q + 1], oacc[db][4 * q + 2], oacc[db][4 * q + 3]);
         }
     }
     __syncthreads();
-    if (w >= 4) return;
+    if (w >= DBLK) return;
     float Mx = fmaxf(fmaxf(s_m[0][col], s_m[1][col]), fmaxf(s_m[2][col], s_m[3][col]));
     const float Mu = Mx == -INFINITY ? 0.f : Mx;
     float f[4], Lsum = 0.f;
@@ -1068,7 +1061,7 @@ __global__ __launch_bounds__(64 * NW) void attn_wave_kernel(AttnArgs a, int KS, 
         if (ww == w) continue;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const float4 o = xb[(ww * 16 + w * 4 + q) * 64 + lane];
+            const float4 o = xb[(ww * XQ + w * 4 + q) * 64 + lane];
             res[4 * q] += o.x * f[ww];
             res[4 * q + 1] += o.y * f[ww];
             res[4 * q + 2] += o.z * f[ww];
@@ -1078,7 +1071,7 @@ __global__ __launch_bounds__(64 * NW) void attn_wave_kernel(AttnArgs a, int KS, 
     if (KS > 1) {
         // ---- leave this workgroup's partial for the merge kernel ---------------------------------
         const int64_t unit = ((int64_t)b * a.Hkv + h) * gridDim.y + blockIdx.y;
-        float4 *pw = sb.o + ((unit * KS + ks) * 4 + w) * 4 * 64;
+        float4 *pw = sb.o + ((unit * KS + ks) * DBLK + w) * 4 * 64;
 #pragma unroll
         for (int q = 0; q < 4; ++q) pw[q * 64 + lane] = make_float4(res[4 * q], res[4 * q + 1], res[4 * q + 2], res[4 * q + 3]);
         if (w == 0 && half == 0) sb.ml[(unit * KS + ks) * 32 + col] = make_float2(Mx, Lsum);
@@ -1098,42 +1091,62 @@ __global__ __launch_bounds__(64 * NW) void attn_wave_kernel(AttnArgs a, int KS, 
 
 // Merge of the KS partials of every (sequence, kv head, 32-row block): thread (w, lane) owns the
 // same 16 output values it would own in the single-split epilogue, so the partials are read
-// back in exactly the layout they were written in.
+// back in exactly the layout they were written in.  Four partials at a time, all their loads asked for before the first
+// is used and before the node count that says which rows exist (a loop that waited for each partial's statistics and then
+// for its values was up to six trips to memory long: 4.7 us on the 8B shape with three splits).
 template <int D>
-__global__ __launch_bounds__(256) void attn_wave_merge_kernel(AttnArgs a, int KS, SplitBuf sb) {
+__global__ __launch_bounds__(2 * D) void attn_wave_merge_kernel(AttnArgs a, int KS, SplitBuf sb) {
+    constexpr int DBLK = D / 32;
     const int G = a.Hq / a.Hkv;
     const int b = blockIdx.z, h = blockIdx.x;
-    const int N = min(max(a.n_nodes[b], 1), a.TT_cap);
-    const int M = N * G;
     const int m0 = blockIdx.y * 32;
-    if (m0 >= M) return;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int half = lane >> 5, col = lane & 31;
     const int mq = m0 + col;
-    if (mq >= M) return;
-    const int node = mq / G, hq = h * G + mq % G;
     const float c = a.scale * 1.4426950408889634f;
     const int64_t unit = ((int64_t)b * a.Hkv + h) * gridDim.y + blockIdx.y;
-    float Mall = -INFINITY;
-    for (int s2 = 0; s2 < KS; ++s2) Mall = fmaxf(Mall, sb.ml[(unit * KS + s2) * 32 + col].x);
-    const float Ma = Mall == -INFINITY ? 0.f : Mall;
-    float res[16], Lsum = 0.f;
+    const int n_raw = a.n_nodes[b];
+    float M = -INFINITY, Lsum = 0.f;
+    float res[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) res[i] = 0.f;
-    for (int s2 = 0; s2 < KS; ++s2) {
-        const float2 ml = sb.ml[(unit * KS + s2) * 32 + col];
-        const float fs = __builtin_amdgcn_exp2f((ml.x - Ma) * c);
-        Lsum += ml.y * fs;
-        const float4 *pr = sb.o + ((unit * KS + s2) * 4 + w) * 4 * 64;
+    for (int s0 = 0; s0 < KS; s0 += 4) {
+        float2 ml[4];
+        float4 o[4][4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float4 o = pr[q * 64 + lane];
-            res[4 * q] += o.x * fs;
-            res[4 * q + 1] += o.y * fs;
-            res[4 * q + 2] += o.z * fs;
-            res[4 * q + 3] += o.w * fs;
+        for (int u = 0; u < 4; ++u) ml[u] = sb.ml[(unit * KS + min(s0 + u, KS - 1)) * 32 + col];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const float4 *pr = sb.o + ((unit * KS + min(s0 + u, KS - 1)) * DBLK + w) * 4 * 64;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) o[u][q] = pr[q * 64 + lane];
         }
+        __builtin_amdgcn_sched_barrier(0);
+        float Mn = M;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) Mn = fmaxf(Mn, ml[u].x);  // past the last split: that split again
+        const float Mu = Mn == -INFINITY ? 0.f : Mn;
+        const float keep = __builtin_amdgcn_exp2f((M - Mu) * c);
+        Lsum *= keep;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) res[i] *= keep;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const float fs = s0 + u < KS ? __builtin_amdgcn_exp2f((ml[u].x - Mu) * c) : 0.f;
+            Lsum += ml[u].y * fs;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                res[4 * q] += o[u][q].x * fs;
+                res[4 * q + 1] += o[u][q].y * fs;
+                res[4 * q + 2] += o[u][q].z * fs;
+                res[4 * q + 3] += o[u][q].w * fs;
+            }
+        }
+        M = Mn;
     }
+    const int N = min(max(n_raw, 1), a.TT_cap);
+    if (mq >= N * G) return;
+    const int node = mq / G, hq = h * G + mq % G;
     const float inv = Lsum > 0.f ? 1.0f / Lsum : 0.f;
     __bf16 *op = (__bf16 *)a.out + (((int64_t)b * a.TT_cap + node) * a.Hq + hq) * D + 32 * w;
 #pragma unroll
@@ -1246,7 +1259,10 @@ __global__ __launch_bounds__(64) void attn_simple_kernel(AttnArgs a) {
 // LDS beyond 64 KB has to be asked for, once per device (dt_init)
 hipError_t attn_init() {
     hipError_t e = hipFuncSetAttribute((const void *)attn_wave_kernel<128, 8, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       8 * WT_ELEMS * 2);
+                                       8 * WaveTile<128>::ELEMS * 2);
+    if (e == hipSuccess)
+        e = hipFuncSetAttribute((const void *)attn_wave_kernel<64, 8, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                8 * WaveTile<64>::ELEMS * 2);
     if (e == hipSuccess)
         e = hipFuncSetAttribute((const void *)attn_wave_kernel<128, 4, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 WD_LDS_BYTES);
@@ -1263,23 +1279,57 @@ static size_t gang_bytes(int D, int n_cu) {
     return (size_t)2 * n_cu * 2 * ATT_MTILE * ((size_t)D * 4 + 8) + 64 * GS_WORDS * 4;
 }
 
-// scratch of the small-batch key splits: per (sequence, kv head, 32-row block) and split
-static size_t wave_split_bytes(int batch, int TT_cap, int Hq) {
-    return (size_t)batch * ((TT_cap * Hq + 31) / 32 + Hq) * (4 * 4 * 64 * 16 + 32 * 8);
-}
+// scratch of one key split of the small-batch kernel, per (sequence, kv head, 32-row block)
+static size_t wave_unit_bytes(int D) { return (size_t)(D / 32) * 4 * 64 * 16 + 32 * 8; }
 
 size_t attn_workspace_bytes(int batch, int TT_cap, int Hq, int D, int n_cu) {
-    if (D != 128) return 0;
-    const size_t w8 = wave_split_bytes(batch, TT_cap, Hq) * 8, g = gang_bytes(D, n_cu);
+    if (D != 128 && D != 64) return 0;
+    const size_t units = (size_t)batch * ((TT_cap * Hq + 31) / 32 + Hq);
+    const size_t w8 = units * wave_unit_bytes(D) * 8, g = D == 128 ? gang_bytes(D, n_cu) : 0;
     const size_t cap = (size_t)256 << 20;
     const size_t want = w8 > g ? w8 : g;
     return want < cap ? want : cap;
 }
 
+// The small-batch kernel and, with key splits, its merge.
+// Key splits: towards one workgroup per compute unit, but only while a split still owns about eleven key blocks -- below
+// that the fixed cost of a workgroup (query load, first fetch, LDS exchange) plus the merge launch outweighs the shorter
+// loop (measured).
+template <int D>
+static int wave_launch(const AttnArgs &a, hipStream_t st, hipError_t *err) {
+    const int G = a.Hq / a.Hkv;
+    const int mblocks = (a.TT_cap * G + 31) / 32;
+    const int64_t units = (int64_t)a.batch * a.Hkv * mblocks;
+    const int nb_max = (a.max_prefix_len + a.TT_cap + ATT_KB - 1) / ATT_KB;
+    int KS = (int)(256 / units);
+    if (KS > 8) KS = 8;
+    if (KS > nb_max / 11) KS = nb_max / 11;
+    const size_t per_split = (size_t)units * wave_unit_bytes(D);
+    if (KS > 1 && (!a.ws || (size_t)KS * per_split > a.ws_bytes)) KS = a.ws ? (int)(a.ws_bytes / per_split) : 1;
+    if (KS < 1) KS = 1;
+    SplitBuf sb;
+    sb.o = (float4 *)a.ws;
+    sb.ml = (float2 *)((char *)a.ws + (size_t)units * KS * (D / 32) * 4 * 64 * 16);
+    dim3 grid(a.Hkv, mblocks, a.batch * KS);
+    if (KS > 1) {  // several workgroups per unit: four waves each
+        if constexpr (D == 128)  // one workgroup per compute unit (128 KB of LDS)
+            launch_kernel(KID_ATTN, st, attn_wave_kernel<D, 4, true>, grid, dim3(256), WD_LDS_BYTES, a, KS, sb);
+        else
+            launch_kernel(KID_ATTN, st, attn_wave_kernel<D, 4, false>, grid, dim3(256), 4 * WaveTile<D>::ELEMS * 2, a, KS, sb);
+        *err = hipGetLastError();
+        if (*err != hipSuccess) return DT_ERR_HIP;
+        launch_kernel(KID_ATTN_COMBINE, st, attn_wave_merge_kernel<D>, dim3(a.Hkv, mblocks, a.batch), dim3(2 * D), 0, a, KS, sb);
+    } else {       // one workgroup per unit: eight waves (two per SIMD)
+        launch_kernel(KID_ATTN, st, attn_wave_kernel<D, 8, false>, grid, dim3(512), 8 * WaveTile<D>::ELEMS * 2, a, KS, sb);
+    }
+    *err = hipGetLastError();
+    return *err == hipSuccess ? DT_OK : DT_ERR_HIP;
+}
+
 int attn_launch(const AttnArgs &a, hipStream_t st, hipError_t *err) {
     *err = hipSuccess;
     if (a.batch <= 0) return DT_OK;
-    const bool mfma = a.dtype == DT_BF16 && a.D == 128 && a.kv_stride_tok % 8 == 0 && a.kv_stride_head % 8 == 0;
+    const bool mfma = a.dtype == DT_BF16 && (a.D == 128 || a.D == 64) && a.kv_stride_tok % 8 == 0 && a.kv_stride_head % 8 == 0;
     if (!mfma) {
         if (a.D > 128) return DT_ERR_LIMIT;
         dim3 grid(a.TT_cap, a.Hq, a.batch);
@@ -1291,38 +1341,9 @@ int attn_launch(const AttnArgs &a, hipStream_t st, hipError_t *err) {
     const int G = a.Hq / a.Hkv;
     const int mtiles = (a.TT_cap * G + ATT_MTILE - 1) / ATT_MTILE;
     const int base_wgs = a.batch * a.Hkv * mtiles;
-    if (base_wgs < 128) {
-        // few (sequence, kv head, row tile) items: the barrier-free small-batch kernel
-        // Key splits: towards one workgroup per compute unit, but only while a split still owns
-        // about 20 key blocks -- below that the fixed cost of a workgroup (query load, first
-        // fetch, LDS exchange) plus the merge launch outweighs the shorter loop (measured).
-        const int mblocks = (a.TT_cap * G + 31) / 32;
-        const int units = a.batch * a.Hkv * mblocks;
-        const int nb_max = (a.max_prefix_len + a.TT_cap + ATT_KB - 1) / ATT_KB;
-        int KS = 256 / units;
-        if (KS > 8) KS = 8;
-        if (KS > nb_max / 11) KS = nb_max / 11;
-        const size_t per_split = (size_t)units * (4 * 4 * 64 * 16 + 32 * 8);
-        if (KS > 1 && (!a.ws || (size_t)KS * per_split > a.ws_bytes)) KS = a.ws ? (int)(a.ws_bytes / per_split) : 1;
-        if (KS < 1) KS = 1;
-        int nw_sel = KS > 1 ? 4 : 8;
-        SplitBuf sb;
-        sb.o = (float4 *)a.ws;
-        sb.ml = (float2 *)((char *)a.ws + (size_t)units * KS * 4 * 4 * 64 * 16);
-        dim3 grid(a.Hkv, mblocks, a.batch * KS);
-        if (nw_sel == 4)  // several workgroups per unit: four waves each, one workgroup per compute unit (128 KB of LDS)
-            launch_kernel(KID_ATTN, st, attn_wave_kernel<128, 4, true>, grid, dim3(256), WD_LDS_BYTES, a, KS, sb);
-        else              // one workgroup per unit: eight waves (two per SIMD), 136 KB of LDS
-            launch_kernel(KID_ATTN, st, attn_wave_kernel<128, 8, false>, grid, dim3(512), 8 * WT_ELEMS * 2, a, KS, sb);
-        if (KS > 1) {
-            *err = hipGetLastError();
-            if (*err != hipSuccess) return DT_ERR_HIP;
-            launch_kernel(KID_ATTN_COMBINE, st, attn_wave_merge_kernel<128>, dim3(a.Hkv, mblocks, a.batch), dim3(256), 0,
-                          a, KS, sb);
-        }
-        *err = hipGetLastError();
-        return *err == hipSuccess ? DT_OK : DT_ERR_HIP;
-    }
+    // few (sequence, kv head, row tile) items: the barrier-free small-batch kernel (64-wide heads: always)
+    if (a.D == 64) return wave_launch<64>(a, st, err);
+    if (base_wgs < 128) return wave_launch<128>(a, st, err);
     // Fewer whole (sequence, kv head, row tile) items than four rounds of two workgroups per compute
     // unit: the balanced schedule (needs one lane per sequence and a slot for every tile count).
     const int P = 2 * a.n_cu / a.Hkv;

@@ -1,0 +1,34 @@
+"""GPU parity of the attention kernels that serve 64-wide heads (matrix cores) and every other head size (plain ALU), at
+the edges of their tiles: row counts around 32, key counts around a block, key splits, and head sizes around the widths
+that decide how a row is loaded."""
+import numpy as np
+import pytest
+
+import dt_synth
+from tests._cases import oracle_case
+from tests.test_gpu_parity import check_case
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _cfg(dtype, D, params, prefix_len, Hq, Hkv):
+    return dt_synth.StepConfig("shape", dtype, Hq, Hkv, D, 1031, params, prefix_len, seed=5)
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(4, 4), (14, 2), (8, 1)])
+@pytest.mark.parametrize("prefix_len", [[0, 1, 31], [32, 33, 64], [700, 1500, 5]])
+def test_heads_of_64(Hq, Hkv, prefix_len):
+    # 1, 32 and 65 nodes: with 1, 7 or 8 query heads per kv head the 32-row blocks are full, ragged and nearly empty; the
+    # long prefixes split their keys over several workgroups, the short ones do not
+    check_case(oracle_case(0, cfg=_cfg("bf16", 64, [(1, 1, 1), (32, 5, 6), (65, 4, 6)], prefix_len, Hq, Hkv)))
+
+
+def test_heads_of_64_large_batch_and_head_major():
+    rng = np.random.default_rng(6)
+    params = [(int(rng.choice([1, 17, 40, 96])), 4, 5) for _ in range(40)]
+    plen = [int(rng.choice([0, 63, 130, 400])) for _ in range(40)]
+    case = oracle_case(0, cfg=_cfg("bf16", 64, params, plen, 16, 4))
+    check_case(case)
+    check_case(case, kv_head_major=True)
