@@ -1159,100 +1159,144 @@ __global__ __launch_bounds__(2 * D) void attn_wave_merge_kernel(AttnArgs a, int 
 }
 
 // ------------------------------------------------------------------------------ fp32 path --
-// One wave per (node, head).  Keys are taken 64 at a time: lane j scores key j, the wave
-// agrees on the running maximum, then lane c accumulates output columns c, c+64.
+// One workgroup per (node, head), four waves that take 64-key blocks in turn: lane j scores key j, the wave agrees on the
+// running maximum, then lane c accumulates output columns c (and c + 64, NC = 2).  The waves' results meet in LDS.  What
+// bounds it at the sizes it is meant for is trips to memory: the K row of a lane (16-byte loads, VEC) and half of the
+// block's V rows are asked for together, the other half behind the scores.  One wave per (node, head) that walked all keys
+// with 4-byte loads took 16.5 us on the tiny fp32 configuration (8 nodes, 4 heads, 136 keys).
 template <typename T>
 __device__ __forceinline__ float ld(const T *p);
 template <>
 __device__ __forceinline__ float ld<float>(const float *p) { return *p; }
 template <>
 __device__ __forceinline__ float ld<uint16_t>(const uint16_t *p) { return bf16_bits_to_float(*p); }
+// sixteen bytes at any element address
+__device__ __forceinline__ void ld16(const float *p, float *x) {
+    const u32x4_any4 v = *(const u32x4_any4 *)p;
+    x[0] = __uint_as_float(v.x); x[1] = __uint_as_float(v.y); x[2] = __uint_as_float(v.z); x[3] = __uint_as_float(v.w);
+}
+__device__ __forceinline__ void ld16(const uint16_t *p, float *x) {
+    const u32x4_any2 v = *(const u32x4_any2 *)p;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        x[2 * i] = __uint_as_float(v[i] << 16);
+        x[2 * i + 1] = __uint_as_float(v[i] & 0xFFFF0000u);
+    }
+}
 
-template <typename T>
-__global__ __launch_bounds__(64) void attn_simple_kernel(AttnArgs a) {
-    const int node = blockIdx.x, hq = blockIdx.y, b = blockIdx.z, lane = threadIdx.x;
-    const int N = min(max(a.n_nodes[b], 1), a.TT_cap);
+template <typename T, int NC, bool VEC>
+__global__ __launch_bounds__(256) void attn_simple_kernel(AttnArgs a) {
+    const int node = blockIdx.x, hq = blockIdx.y, b = blockIdx.z, tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n_raw = a.n_nodes[b], l_raw = a.prefix_len[b];
+    const T *kpre = (const T *)a.k_prefix[b], *vpre = (const T *)a.v_prefix[b];
+    const int N = min(max(n_raw, 1), a.TT_cap);
     if (node >= N) return;
     const int D = a.D, G = a.Hq / a.Hkv, h = hq / G;
-    const int L = max(a.prefix_len[b], 0), Tk = L + N;
+    const int L = max(l_raw, 0), Tk = L + N;
     const int64_t row = ((int64_t)b * a.TT_cap + node) * a.Hq + hq;
     const T *q = (const T *)a.q + row * D;
-    const T *kpre = (const T *)a.k_prefix[b], *vpre = (const T *)a.v_prefix[b];
-    const T *ktree = (const T *)a.k_tree + (int64_t)b * a.TT_cap * a.Hkv * D;
-    const T *vtree = (const T *)a.v_tree + (int64_t)b * a.TT_cap * a.Hkv * D;
+    const T *ktree = (const T *)a.k_tree + ((int64_t)b * a.TT_cap * a.Hkv + h) * D;
+    const T *vtree = (const T *)a.v_tree + ((int64_t)b * a.TT_cap * a.Hkv + h) * D;
+    kpre += (int64_t)h * a.kv_stride_head;
+    vpre += (int64_t)h * a.kv_stride_head;
     const u64 mask0 = a.anc_mask[((int64_t)b * a.TT_cap + node) * DT_MASK_WORDS];
     const u64 mask1 = a.anc_mask[((int64_t)b * a.TT_cap + node) * DT_MASK_WORDS + 1];
 
-    __shared__ float s_q[128];
-    for (int cidx = lane; cidx < D; cidx += 64) s_q[cidx] = ld(q + cidx);
+    __shared__ __attribute__((aligned(16))) float s_q[128];
+    __shared__ float s_m[4], s_l[4], s_o[4][128];
+    if (tid < 128) s_q[tid] = tid < D ? ld(q + tid) : 0.f;
     __syncthreads();
 
-    float m_run = -INFINITY, l_run = 0.f, o0 = 0.f, o1 = 0.f;
-    for (int t0 = 0; t0 < Tk; t0 += 64) {
-        const int t = t0 + lane;
+    constexpr int PER = 16 / sizeof(T);  // elements of a 16-byte load
+    constexpr int VB = 32;               // V rows in flight together
+    float m_run = -INFINITY, l_lane = 0.f, o[NC];
+#pragma unroll
+    for (int i = 0; i < NC; ++i) o[i] = 0.f;
+    for (int t0 = w * 64; t0 < Tk; t0 += 256) {
+        const int t = t0 + lane, tc = min(t, Tk - 1);
         bool vis = t < Tk;
         if (vis && t >= L) {
             const int j = t - L;
             vis = ((j < 64 ? mask0 : mask1) >> (j & 63)) & 1ull;
         }
-        float s = -INFINITY;
-        if (vis) {
-            const T *kp = t < L ? kpre + (int64_t)t * a.kv_stride_tok + (int64_t)h * a.kv_stride_head
-                                : ktree + ((int64_t)(t - L) * a.Hkv + h) * D;
-            // four partial sums, 64 loads requested together: the row is read at memory latency once per
-            // 64 elements, not once per element
-            float d4[4] = {0.f, 0.f, 0.f, 0.f};
-            int cidx = 0;
-            for (; cidx + 64 <= D; cidx += 64) {
+        const T *kp = tc < L ? kpre + (int64_t)tc * a.kv_stride_tok : ktree + (int64_t)(tc - L) * a.Hkv * D;
+        // V rows j0 .. j0 + VB - 1 of the block, lane's columns (columns past D repeat the last one and are never stored,
+        // rows past the end repeat the last one and weigh 0): unconditional, a load in a branch is waited for there
+        float v[VB][NC];
+        auto v_request = [&](int j0) {
+#pragma unroll
+            for (int u = 0; u < VB; ++u) {
+                const int tj = min(t0 + j0 + u, Tk - 1);
+                const T *vp = tj < L ? vpre + (int64_t)tj * a.kv_stride_tok : vtree + (int64_t)(tj - L) * a.Hkv * D;
+#pragma unroll
+                for (int i = 0; i < NC; ++i) v[u][i] = ld(vp + min(lane + 64 * i, D - 1));
+            }
+        };
+        float d4[4] = {0.f, 0.f, 0.f, 0.f};
+        bool first = true;
+        int c0 = 0;
+        if (VEC) {
+            for (; c0 + 64 <= D; c0 += 64) {
                 float kv[64];
 #pragma unroll
-                for (int u = 0; u < 64; ++u) kv[u] = ld(kp + cidx + u);
+                for (int u = 0; u < 64; u += PER) ld16(kp + c0 + u, kv + u);
+                if (first) v_request(0);
+                first = false;
                 __builtin_amdgcn_sched_barrier(0);  // all requests before the first use
 #pragma unroll
-                for (int u = 0; u < 64; ++u) d4[u & 3] = fmaf(s_q[cidx + u], kv[u], d4[u & 3]);
+                for (int u = 0; u < 64; ++u) d4[u & 3] = fmaf(s_q[c0 + u], kv[u], d4[u & 3]);
             }
-            for (; cidx < D; ++cidx) d4[0] = fmaf(s_q[cidx], ld(kp + cidx), d4[0]);
-            s = ((d4[0] + d4[1]) + (d4[2] + d4[3])) * a.scale;
+            for (; c0 + PER <= D; c0 += PER) {
+                float kv[PER];
+                ld16(kp + c0, kv);
+#pragma unroll
+                for (int u = 0; u < PER; ++u) d4[u & 3] = fmaf(s_q[c0 + u], kv[u], d4[u & 3]);
+            }
         }
+        for (; c0 < D; ++c0) d4[0] = fmaf(s_q[c0], ld(kp + c0), d4[0]);
+        if (first) v_request(0);
+        const float s = vis ? ((d4[0] + d4[1]) + (d4[2] + d4[3])) * a.scale : -INFINITY;
         const float m_new = fmaxf(m_run, wave_max(s));
         if (m_new == -INFINITY) continue;
         const float alpha = __expf(m_run - m_new);
         const float p = vis ? __expf(s - m_new) : 0.f;
-        l_run = l_run * alpha + wave_sum(p);
-        o0 *= alpha; o1 *= alpha;
+        l_lane = l_lane * alpha + p;
+#pragma unroll
+        for (int i = 0; i < NC; ++i) o[i] *= alpha;
         m_run = m_new;
-        // V rows sixteen at a time, all their loads requested before the first is used; keys past the end
-        // repeat the last row with probability 0
-        const int cnt = min(64, Tk - t0);
-        for (int j0 = 0; j0 < cnt; j0 += 16) {
-            float v0[16], v1[16];
 #pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                const int tj = min(t0 + j0 + u, Tk - 1);
-                const T *vp = tj < L ? vpre + (int64_t)tj * a.kv_stride_tok + (int64_t)h * a.kv_stride_head
-                                     : vtree + ((int64_t)(tj - L) * a.Hkv + h) * D;
-                v0[u] = ld(vp + min(lane, D - 1));        // unconditional (columns past D repeat the last one and
-                v1[u] = ld(vp + min(lane + 64, D - 1));   // are never stored): a load in a branch is waited for there
+        for (int j0 = 0; j0 < 64; j0 += VB) {
+            if (j0 > 0) {
+                if (t0 + j0 >= Tk) break;
+                v_request(j0);
             }
-            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                const float pj = __shfl(p, j0 + u, 64);  // lanes at and past cnt hold 0
-                o0 = pj != 0.f ? fmaf(pj, v0[u], o0) : o0;   // a hidden key's row is not even multiplied by 0
-                o1 = pj != 0.f ? fmaf(pj, v1[u], o1) : o1;
+            for (int u = 0; u < VB; ++u) {
+                const float pj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(p), j0 + u));
+#pragma unroll
+                for (int i = 0; i < NC; ++i)
+                    o[i] = pj != 0.f ? fmaf(pj, v[u][i], o[i]) : o[i];  // a hidden key's row is not even multiplied by 0
             }
         }
     }
-    const float inv = l_run > 0.f ? 1.0f / l_run : 0.f;
-    if (sizeof(T) == 4) {
-        float *op = (float *)a.out + row * D;
-        if (lane < D) op[lane] = o0 * inv;
-        if (lane + 64 < D) op[lane + 64] = o1 * inv;
-    } else {
-        __bf16 *op = (__bf16 *)a.out + row * D;
-        if (lane < D) op[lane] = (__bf16)(o0 * inv);
-        if (lane + 64 < D) op[lane + 64] = (__bf16)(o1 * inv);
+    const float l_run = wave_sum(l_lane);
+    if (lane == 0) { s_m[w] = m_run; s_l[w] = l_run; }
+#pragma unroll
+    for (int i = 0; i < NC; ++i) s_o[w][lane + 64 * i] = o[i];
+    __syncthreads();
+    if (tid >= D) return;
+    const float M = fmaxf(fmaxf(s_m[0], s_m[1]), fmaxf(s_m[2], s_m[3])), Mu = M == -INFINITY ? 0.f : M;
+    float lt = 0.f, ot = 0.f;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const float f = __expf(s_m[v] - Mu);
+        lt = fmaf(s_l[v], f, lt);
+        ot = fmaf(s_o[v][tid], f, ot);
     }
+    const float res = lt > 0.f ? ot * (1.0f / lt) : 0.f;
+    if (sizeof(T) == 4) ((float *)a.out)[row * D + tid] = res;
+    else ((__bf16 *)a.out)[row * D + tid] = (__bf16)res;
 }
 
 // ------------------------------------------------------------------------------- launchers --
@@ -1332,9 +1376,18 @@ int attn_launch(const AttnArgs &a, hipStream_t st, hipError_t *err) {
     const bool mfma = a.dtype == DT_BF16 && (a.D == 128 || a.D == 64) && a.kv_stride_tok % 8 == 0 && a.kv_stride_head % 8 == 0;
     if (!mfma) {
         if (a.D > 128) return DT_ERR_LIMIT;
-        dim3 grid(a.TT_cap, a.Hq, a.batch);
-        if (a.dtype == DT_BF16) launch_kernel(KID_ATTN, st, attn_simple_kernel<uint16_t>, grid, dim3(64), 0, a);
-        else launch_kernel(KID_ATTN, st, attn_simple_kernel<float>, grid, dim3(64), 0, a);
+        const dim3 grid(a.TT_cap, a.Hq, a.batch);
+        auto go = [&](auto kernel) { launch_kernel(KID_ATTN, st, kernel, grid, dim3(256), 0, a); };
+        // 16-byte loads of a K row need no alignment, only a row that is long enough for them to be worth it
+        if (a.dtype == DT_BF16) {
+            if (a.D > 64) go(attn_simple_kernel<uint16_t, 2, true>);
+            else if (a.D >= 8) go(attn_simple_kernel<uint16_t, 1, true>);
+            else go(attn_simple_kernel<uint16_t, 1, false>);
+        } else {
+            if (a.D > 64) go(attn_simple_kernel<float, 2, true>);
+            else if (a.D >= 4) go(attn_simple_kernel<float, 1, true>);
+            else go(attn_simple_kernel<float, 1, false>);
+        }
         *err = hipGetLastError();
         return *err == hipSuccess ? DT_OK : DT_ERR_HIP;
     }

@@ -32,3 +32,11 @@ def test_heads_of_64_large_batch_and_head_major():
     case = oracle_case(0, cfg=_cfg("bf16", 64, params, plen, 16, 4))
     check_case(case)
     check_case(case, kv_head_major=True)
+
+
+@pytest.mark.parametrize("dtype,D", [("f32", D) for D in (1, 3, 4, 20, 63, 64, 65, 68, 127, 128)] +
+                         [("bf16", D) for D in (7, 8, 20, 72, 80, 96, 112)])
+def test_plain_kernel_head_sizes(dtype, D):
+    # rows shorter than one 16-byte load, a multiple of it or not, one and two columns per lane; key counts below, at and
+    # past one block, and enough for every wave to have several
+    check_case(oracle_case(0, cfg=_cfg(dtype, D, [(1, 1, 1), (20, 4, 3), (70, 4, 6)], [0, 44, 600], 4, 2)))
