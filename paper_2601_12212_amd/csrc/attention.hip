@@ -13,6 +13,8 @@
 // fp32 path: plain ALU kernel, one wave per (node, head); a correctness path for small
 // problems and for head sizes the MFMA path does not cover.
 
+#include <type_traits>
+
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -21,6 +23,7 @@ namespace dt {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 // Global-address-space views: pointers fetched from memory (the per-sequence prefix pointers)
 // would otherwise be generic, and generic loads also count against the LDS wait counter.
@@ -52,9 +55,12 @@ __device__ __forceinline__ bf16x8 lds_load128(u32 addr) {
 }
 // One global_load_lds_dwordx4 with the address split into a wave-uniform base (scalar registers) and a 32-bit
 // per-lane byte offset, the LDS destination (wave-uniform, the lanes' 16 bytes follow each other) in M0: no
-// vector arithmetic per load, and no 64-bit per-lane pointers to keep and advance.
+// vector arithmetic per load, and no 64-bit per-lane pointers to keep and advance.  OFF is added to the global address; the
+// instruction adds its offset to the LDS address as well, so M0 holds the destination less OFF.
+template <int OFF>
 __device__ __forceinline__ void load_to_lds16(const void __attribute__((address_space(1))) *base, u32 lane_off, u32 lds_addr) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lane_off), "s"(base), "s"(lds_addr)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3" ::"v"(lane_off), "s"(base),
+                 "s"(lds_addr - OFF), "n"(OFF)
                  : "memory", "m0");
 }
 // a 64-bit value that is the same in every lane, moved to scalar registers where the compiler has not seen that
@@ -159,17 +165,17 @@ __device__ __forceinline__ u32 vis_window(int off, u64 mask0, u64 mask1) {
 // buffered with one barrier per block: the loads of block i+1 are in flight while block i is
 // multiplied, and cost neither registers nor LDS-write instructions.
 //
-// Both tiles are row-major with unpadded 256-byte rows; bank conflicts are avoided by storing
-// the 16-byte chunk c of row r at chunk position c ^ f(r) (the permutation is applied on the
-// global side: lane p of a row fetches chunk p ^ f(r)):
-//   K: f(r) = r % 16.  The A-operand read of S^T = K Q^T has 16 lanes read the same chunk of 16
-//      consecutive rows, which now sit at 16 different chunk positions (all 64 banks).
-//   V: f(r) = 4 (r % 4) + (r / 4) % 4.  The transposing read takes 4 rows x 64 B per 32 lanes;
-//      the four rows now sit in four different 64-byte groups.
+// A tile is four sub-tiles of 64 keys x 64 bytes (32 columns), row after row.  A 1 KB load is sixteen keys of one sub-tile;
+// the operand reads find everything but a lane's own row at immediate offsets (two address registers for K, one for V), and
+// no read has a bank conflict:
+//   K: chunk c (16 bytes) of row r sits at position c ^ (r / 4 % 4) of its 64 bytes (the permutation is applied on the
+//      global side), so that the A-operand read of S^T = K Q^T, the same chunk of 16 consecutive rows, takes 16 different
+//      16-byte slots of 256 bytes;
+//   V: the transposing read takes 4 rows x 64 B per 32 lanes, 256 consecutive bytes.
 #define TILE_KEYS 64
 #define TILE_BYTES (TILE_KEYS * 256)     // one K or V tile
-#define STAGE_BYTES (2 * TILE_BYTES)     // K tile + V tile of one stage
-#define TILE_LDS_BYTES (2 * STAGE_BYTES)
+#define SUB_BYTES (TILE_KEYS * 64)       // a quarter of its columns
+#define TILE_LDS_BYTES (4 * TILE_BYTES)  // two K tiles, then two V tiles
 typedef char __attribute__((address_space(3))) *ldsp;
 
 // Where a (sequence, row tile, key range) result goes: the output rows directly when the range is
@@ -183,7 +189,7 @@ struct TileDest {
 // Rows m0 .. m0+127 of (sequence b, kv head h) against key blocks kb0 .. kb1-1 of that sequence.
 // Called by all 256 threads of the workgroup; ends behind a barrier, so calls can follow each other.
 template <int D>
-__device__ __forceinline__ void tile_segment(const AttnArgs &a, unsigned char *s_dyn, int h, int b, int m0, int kb0,
+__device__ __forceinline__ void tile_segment(const AttnArgs &a, unsigned char *s_dyn, int h, int b, int m0, int rot, int kb0,
                                              int kb1, TileDest dst) {
     static_assert(D == 128, "head dim");
     constexpr int KSTEPS = D / 16, DBLK = D / 32;
@@ -196,8 +202,11 @@ __device__ __forceinline__ void tile_segment(const AttnArgs &a, unsigned char *s
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, col = lane & 31;
-    const bool active = m0 + 32 * w < M;  // waves past the last row only help with the loads
-    const int mq = m0 + 32 * w + col;
+    // Wave w works on rows 32 rb .. of the tile.  Waves past the last row only help with the loads; `rot` spreads them over
+    // the SIMDs, so that two half-filled tiles on one compute unit do not leave the same ones idle.
+    const int rb = (w + rot) & 3;
+    const bool active = m0 + 32 * rb < M;
+    const int mq = m0 + 32 * rb + col;
     const bool qvalid = mq < M;
     const int node = qvalid ? mq / G : 0;
     const int hq = h * G + (qvalid ? mq % G : 0);
@@ -208,9 +217,6 @@ __device__ __forceinline__ void tile_segment(const AttnArgs &a, unsigned char *s
 #pragma unroll
         for (int s = 0; s < KSTEPS; ++s) qreg[s] = *(const bf16x8 *)(qp + 16 * s + 8 * half);  // rows past M read node 0: unused
     }
-    const u64 mask0 = a.anc_mask[((int64_t)b * a.TT_cap + node) * DT_MASK_WORDS];
-    const u64 mask1 = a.anc_mask[((int64_t)b * a.TT_cap + node) * DT_MASK_WORDS + 1];
-
     f32x16 oacc[DBLK];
 #pragma unroll
     for (int db = 0; db < DBLK; ++db)
@@ -224,191 +230,246 @@ __device__ __forceinline__ void tile_segment(const AttnArgs &a, unsigned char *s
     const gbf16p ktree = (gbf16p)a.k_tree + ((int64_t)b * a.TT_cap * a.Hkv + h) * D;
     const gbf16p vtree = (gbf16p)a.v_tree + ((int64_t)b * a.TT_cap * a.Hkv + h) * D;
     const int64_t stok = a.kv_stride_tok, stree = (int64_t)a.Hkv * D;
-    // Loading role of a thread, the same for K and V: load i takes key 16 i + tid/16 of the block
-    // and lands at chunk position tid%16 of that row, so it fetches chunk (tid%16) ^ f(row); the
-    // 16 lanes of a row still cover its 256 bytes.  f(row) does not depend on i (16 | 16 i).
-    const int krow = tid >> 4, cpos = tid & 15;
-    const int kchunk = cpos ^ krow, vchunk = cpos ^ (((krow & 3) << 2) | (krow >> 2));
-    // inside the prefix: a lane's byte offset from the first of its load's sixteen rows (the same for all four loads)
+    // Loading role of a thread: load i takes 64-byte column group i of keys 16 w .. 16 w + 15 of the block, lane l key
+    // 16 w + l / 4 and chunk position l % 4 of it: consecutive lanes fill consecutive 16 bytes of the sub-tile.
+    const int krow = 16 * w + (lane >> 2), vchunk = lane & 3, kchunk = vchunk ^ ((lane >> 4) & 3);
+    // inside the prefix: a lane's byte offset from the block's first row (the same for the four loads, 64 bytes apart)
     const u32 koffp = (u32)(krow * stok + 8 * kchunk) * 2u, voffp = (u32)(krow * stok + 8 * vchunk) * 2u;
     const bool small_stride = (int64_t)TILE_KEYS * stok * 2 < ((int64_t)1 << 31);
 
     // Every load is unconditional.  Keys past the end are read from the last valid row; their
     // scores are masked to -inf below, so their probabilities are exactly 0 and the duplicated V
-    // rows contribute nothing.  LDS destination of wave w, load i: rows 16 i + 4 w .. + 3.
-    auto fetch = [&](int kb, int stage) {
-        const ldsp kdst = (ldsp)s_dyn + stage * STAGE_BYTES + 4 * w * 256;
-        const ldsp vdst = kdst + TILE_BYTES;
+    // rows contribute nothing.
+    auto fetch = [&](int kb, u32 tile, gbf16p pre, gbf16p tree, u32 poff, int chunk) {
+        const ldsp dst = (ldsp)s_dyn + tile + w * 1024;
         if (small_stride && kb * TILE_KEYS + TILE_KEYS <= L) {  // block inside the prefix (uniform test)
-            const u32 kl = (u32)(uintptr_t)kdst, vl = (u32)(uintptr_t)vdst;
-            const gbytep kbase = uniform_ptr((gbytep)(kpre + (int64_t)kb * TILE_KEYS * stok));
-            const gbytep vbase = uniform_ptr((gbytep)(vpre + (int64_t)kb * TILE_KEYS * stok));
-            const int64_t step = uniform_i64(16 * stok * 2);  // bytes between the first rows of two loads
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                load_to_lds16(kbase + i * step, koffp, kl + i * 16 * 256);
-                load_to_lds16(vbase + i * step, voffp, vl + i * 16 * 256);
-            }
+            const u32 dl = (u32)(uintptr_t)dst;
+            const gbytep base = uniform_ptr((gbytep)(pre + (int64_t)kb * TILE_KEYS * stok));
+            load_to_lds16<0>(base, poff, dl);
+            load_to_lds16<64>(base, poff, dl + SUB_BYTES);
+            load_to_lds16<128>(base, poff, dl + 2 * SUB_BYTES);
+            load_to_lds16<192>(base, poff, dl + 3 * SUB_BYTES);
         } else {                                                 // block touching the tree keys or the end
+            const int t = min(kb * TILE_KEYS + krow, Tk - 1);
+            const gbf16p src = (t < L ? pre + (int64_t)t * stok : tree + (int64_t)(t - L) * stree) + 8 * chunk;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int t = min(kb * TILE_KEYS + 16 * i + krow, Tk - 1);
-                const int64_t o = t < L ? (int64_t)t * stok : (int64_t)(t - L) * stree;
-                __builtin_amdgcn_global_load_lds((gbytep)((t < L ? kpre : ktree) + o + 8 * kchunk), kdst + i * 16 * 256,
-                                                 16, 0, 0);
-                __builtin_amdgcn_global_load_lds((gbytep)((t < L ? vpre : vtree) + o + 8 * vchunk), vdst + i * 16 * 256,
-                                                 16, 0, 0);
-            }
+            for (int i = 0; i < 4; ++i)
+                __builtin_amdgcn_global_load_lds((gbytep)(src + 32 * i), dst + i * SUB_BYTES, 16, 0, 0);
         }
     };
+    auto fetch_k = [&](int kb, int stage) { fetch(kb, stage * TILE_BYTES, kpre, ktree, koffp, kchunk); };
+    auto fetch_v = [&](int kb, int stage) { fetch(kb, 2 * TILE_BYTES + stage * TILE_BYTES, vpre, vtree, voffp, vchunk); };
 
-    // Operand read offsets (bytes inside a tile).
-    // K, A operand of S^T: lane (col, half), k-step s reads chunk 2s + half of row 32 j + col.
-    u32 koff[KSTEPS];
-#pragma unroll
-    for (int s = 0; s < KSTEPS; ++s) koff[s] = (u32)(col * 256 + (((2 * s + half) ^ (col & 15)) << 4));
+    // Operand read addresses; everything but the lane's own part is an immediate offset.
+    // K, A operand of S^T: lane (col, half), k-step s reads chunk 2s + half of row 32 j + col: sub-tile s / 2, chunk
+    // 2 (s % 2) + half of it, at position chunk ^ (row / 4 % 4).
+    const u32 lds0 = (u32)(uintptr_t)(ldsp)s_dyn;
+    const u32 koff[2] = {lds0 + (u32)(col * 64 + ((half ^ ((col >> 2) & 3)) << 4)),
+                         lds0 + (u32)(col * 64 + (((2 + half) ^ ((col >> 2) & 3)) << 4))};
     // V, A operand of O^T = V^T P^T through the transposing read.  Lane (column d = 32 db + col,
     // half) needs, for e = 0..7, V[key 16 st + 8 (e/4) + 4 half + e%4][d]: two reads of 4 keys.  In
     // a 16-lane group lane p16 = 4 r0 + q points at key r0 of the quadruple, columns 4q .. 4q+3 of
-    // the group's 16 columns: chunk 4 db + 2 a + q/2 (a = second 16-lane group of the half), byte
-    // 8 (q%2) inside it.  Row 16 st + 8 hi + 4 half + r0 has f = 4 r0 + 2 hi + half.
+    // the group's 16 columns: sub-tile db, byte 32 grp + 8 q of the row (grp = second 16-lane group of the half).
     const int p16 = lane & 15, r0 = p16 >> 2, q4 = p16 & 3, grp = (lane >> 4) & 1;
-    u32 voff[DBLK][2];
-#pragma unroll
-    for (int db = 0; db < DBLK; ++db)
-#pragma unroll
-        for (int hi = 0; hi < 2; ++hi)
-            voff[db][hi] = (u32)((8 * hi + 4 * half + r0) * 256 +
-                                 (((4 * db + 2 * grp + (q4 >> 1)) ^ (4 * r0 + 2 * hi + half)) << 4) + 8 * (q4 & 1));
+    const u32 voff = lds0 + (u32)((4 * half + r0) * 64 + 32 * grp + 8 * q4);
 
-    fetch(kb0, 0);
-    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's part of the block is in LDS
-    __syncthreads();
-    for (int kb = kb0; kb < kb1; ++kb) {
-        const int cur = (kb - kb0) & 1;
-        if (kb + 1 < kb1) fetch(kb + 1, cur ^ 1);  // the other stage was last read before the previous barrier
-        if (active) {
-            const unsigned char *kt = s_dyn + cur * STAGE_BYTES;  // K tile of this stage, its V tile behind it
-            // ---- S^T: 64 keys x 32 queries as two 32x32 blocks -----------------------------------
-            // The LDS reads are bare instructions with hand-kept waits: eight K reads (four k-steps of both
-            // 32-key halves) stay in flight ahead of the MFMAs, and the first half of the V reads is issued
-            // as soon as the K operands are consumed, so that it lands during the softmax.  (Scheduled by the
-            // compiler, a read was waited for in full a dozen times per block, and a wait for the next
-            // block's global loads stood in front of the first V read.)
-            const u32 kl = (u32)(uintptr_t)(ldsp)kt, vl = kl + TILE_BYTES;
-            f32x16 sacc[2];
+    // Scores of a block: two 32x32 blocks, S[j] = keys 32 j .. 32 j + 31.
+    struct Scores { f32x16 v[2]; };
+    f32x16 zero16;
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
+    for (int i = 0; i < 16; ++i) zero16[i] = 0.f;
+    // only blocks that contain tree keys (or the end) need the mask
+    auto mask = [&](int kb, Scores &S) {
+        const int tbase = kb * TILE_KEYS;
+        if (tbase + TILE_KEYS <= L) return;
+        // read where it is needed, at most three blocks of a sequence: four registers fewer in all others
+        const u64 *am = a.anc_mask + ((int64_t)b * a.TT_cap + node) * DT_MASK_WORDS;
+        const u64 mask0 = am[0], mask1 = am[1];
+        __builtin_amdgcn_s_waitcnt(0x0f70);  // or the compiler waits for them, and for the tiles, in every block
 #pragma unroll
-                for (int i = 0; i < 16; ++i) sacc[j][i] = 0.f;
-            bf16x8 ka[16];  // read i: k-step i / 2, half i % 2
-#define K_READ(i) ka[i] = lds_load128_at<((i) & 1) * 32 * 256>(kl + koff[(i) >> 1]);
-#define QK_STEP(i)                                                                                            \
-            lds_wait<((i) < 8 ? 7 : 15 - (i))>(ka[i]);                                                        \
-            sacc[(i) & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[i], qreg[(i) >> 1], sacc[(i) & 1], 0, 0, 0);
-            K_READ(0) K_READ(1) K_READ(2) K_READ(3) K_READ(4) K_READ(5) K_READ(6) K_READ(7)
-            QK_STEP(0) K_READ(8) __builtin_amdgcn_sched_barrier(0);
-            QK_STEP(1) K_READ(9) __builtin_amdgcn_sched_barrier(0);
-            QK_STEP(2) K_READ(10) __builtin_amdgcn_sched_barrier(0);
-            QK_STEP(3) K_READ(11) __builtin_amdgcn_sched_barrier(0);
-            QK_STEP(4) K_READ(12) __builtin_amdgcn_sched_barrier(0);
-            QK_STEP(5) K_READ(13) __builtin_amdgcn_sched_barrier(0);
-            QK_STEP(6) K_READ(14) __builtin_amdgcn_sched_barrier(0);
-            QK_STEP(7) K_READ(15) __builtin_amdgcn_sched_barrier(0);
-            QK_STEP(8) __builtin_amdgcn_sched_barrier(0);
-            QK_STEP(9) __builtin_amdgcn_sched_barrier(0);
-            QK_STEP(10) __builtin_amdgcn_sched_barrier(0);
-            QK_STEP(11) __builtin_amdgcn_sched_barrier(0);
-            QK_STEP(12) __builtin_amdgcn_sched_barrier(0);
-            QK_STEP(13) __builtin_amdgcn_sched_barrier(0);
-            QK_STEP(14) __builtin_amdgcn_sched_barrier(0);
-            QK_STEP(15) __builtin_amdgcn_sched_barrier(0);
-#undef K_READ
-#undef QK_STEP
-            // V operands of the first 32 keys (MFMA n = 4 st + db of that half): two transposing reads each
-            bf16x4 vlo[16], vhi[16];
-#define V_READ(n)                                                                                              \
-            vlo[n] = lds_load_tr4<(32 * ((n) >> 3) + 16 * (((n) >> 2) & 1)) * 256>(vl + voff[(n) & 3][0]);     \
-            vhi[n] = lds_load_tr4<(32 * ((n) >> 3) + 16 * (((n) >> 2) & 1)) * 256>(vl + voff[(n) & 3][1]);
-            V_READ(0) V_READ(1) V_READ(2) V_READ(3) V_READ(4) V_READ(5) V_READ(6) V_READ(7)
-            __builtin_amdgcn_sched_barrier(0);
-            const int tbase = kb * TILE_KEYS;
-            if (tbase + TILE_KEYS > L) {  // only blocks that contain tree keys (or the end) need the mask
+        for (int j = 0; j < 2; ++j) {
+            const u32 vis = vis_window(tbase + 32 * j - L, mask0, mask1) >> (4 * half);
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    const u32 vis = vis_window(tbase + 32 * j - L, mask0, mask1) >> (4 * half);
-#pragma unroll
-                    for (int i = 0; i < 16; ++i)
-                        sacc[j][i] = ((vis >> (8 * (i >> 2) + (i & 3))) & 1u) ? sacc[j][i] : -INFINITY;
-                }
-            }
-            // ---- online softmax over the 64 keys (this lane: one query, 32 of the keys) ----------
-            float mloc = sacc[0][0];
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) mloc = fmaxf(mloc, sacc[j][i]);
-            mloc = half_swap_max(mloc);
-            // m_run is a reference, not the exact running maximum: it moves only when a block's maximum
-            // lies more than LAZY_LOG2 binary orders above it.  Until then probabilities may reach
-            // 2^LAZY_LOG2 instead of 1 (harmless in fp32 sums and in bf16's relative precision) and the 64
-            // multiplies that rescale the output accumulators are not spent: with unit-variance keys the
-            // reference settles on the first block.  (-inf - -inf is NaN: a fully hidden block moves nothing.)
-            const bool move = (mloc - m_run) * c > LAZY_LOG2;
-            const float m_new = move ? mloc : m_run;
-            const float m_use = m_new == -INFINITY ? 0.f : m_new;
-            const float alpha = move ? __builtin_amdgcn_exp2f((m_run - m_use) * c) : 1.0f;  // m_run = -inf -> 0
-            const float nmc = -m_use * c;
-            float psum = 0.f;
-            bf16x8 pb[2][2];
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const float p = __builtin_amdgcn_exp2f(fmaf(sacc[j][i], c, nmc));
-                    psum += p;
-                    pb[j][i >> 3][i & 7] = (__bf16)p;
-                }
-            l_run = l_run * alpha + psum;
-            m_run = m_new;
-            if (__ballot(alpha != 1.0f)) {  // the running maximum moved for some query of this wave
-#pragma unroll
-                for (int db = 0; db < DBLK; ++db)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) oacc[db][i] *= alpha;
-            }
-            // ---- O^T += V^T P^T ------------------------------------------------------------------
-            // MFMA n (half n / 8, k-step (n / 4) % 2, output block n % 4); the reads of the second half are
-            // issued one MFMA at a time behind the first half's MFMAs
-#define PV_STEP(n, W)                                                                                          \
-            lds_wait2<W>(vlo[n], vhi[n]);                                                                      \
-            oacc[(n) & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(                                           \
-                __builtin_shufflevector(vlo[n], vhi[n], 0, 1, 2, 3, 4, 5, 6, 7), pb[(n) >> 3][((n) >> 2) & 1], \
-                oacc[(n) & 3], 0, 0, 0);
-            PV_STEP(0, 0) V_READ(8) __builtin_amdgcn_sched_barrier(0);
-            PV_STEP(1, 2) V_READ(9) __builtin_amdgcn_sched_barrier(0);
-            PV_STEP(2, 4) V_READ(10) __builtin_amdgcn_sched_barrier(0);
-            PV_STEP(3, 6) V_READ(11) __builtin_amdgcn_sched_barrier(0);
-            PV_STEP(4, 8) V_READ(12) __builtin_amdgcn_sched_barrier(0);
-            PV_STEP(5, 10) V_READ(13) __builtin_amdgcn_sched_barrier(0);
-            PV_STEP(6, 12) V_READ(14) __builtin_amdgcn_sched_barrier(0);
-            PV_STEP(7, 14) V_READ(15) __builtin_amdgcn_sched_barrier(0);
-            PV_STEP(8, 14) __builtin_amdgcn_sched_barrier(0);
-            PV_STEP(9, 12) __builtin_amdgcn_sched_barrier(0);
-            PV_STEP(10, 10) __builtin_amdgcn_sched_barrier(0);
-            PV_STEP(11, 8) __builtin_amdgcn_sched_barrier(0);
-            PV_STEP(12, 6) __builtin_amdgcn_sched_barrier(0);
-            PV_STEP(13, 4) __builtin_amdgcn_sched_barrier(0);
-            PV_STEP(14, 2) __builtin_amdgcn_sched_barrier(0);
-            PV_STEP(15, 0)
-            // the "memory" clobber keeps the next iteration's loads into this stage behind this block's reads
-            asm volatile("" ::: "memory");
-#undef PV_STEP
-#undef V_READ
+            for (int i = 0; i < 16; ++i) S.v[j][i] = ((vis >> (8 * (i >> 2) + (i & 3))) & 1u) ? S.v[j][i] : -INFINITY;
         }
-        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's part of the next block has landed
+    };
+    // m_run is a reference, not the exact running maximum: it moves only when a block's maximum
+    // lies more than LAZY_LOG2 binary orders above it.  Until then probabilities may reach
+    // 2^LAZY_LOG2 instead of 1 (harmless in fp32 sums and in bf16's relative precision) and the 64
+    // multiplies that rescale the output accumulators are not spent: with unit-variance keys the
+    // reference settles on the first block.  (-inf - -inf is NaN: a fully hidden block moves nothing.)
+    float nmc = 0.f;
+    auto move_reference = [&](float mloc) {
+        mloc = half_swap_max(mloc);
+        const bool move = (mloc - m_run) * c > LAZY_LOG2;
+        const float m_new = move ? mloc : m_run;
+        const float m_use = m_new == -INFINITY ? 0.f : m_new;
+        const float alpha = move ? __builtin_amdgcn_exp2f((m_run - m_use) * c) : 1.0f;  // m_run = -inf -> 0
+        nmc = -m_use * c;
+        l_run *= alpha;
+        m_run = m_new;
+        if (__ballot(alpha != 1.0f)) {  // the reference moved for some query of this wave
+#pragma unroll
+            for (int db = 0; db < DBLK; ++db)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) oacc[db][i] *= alpha;
+        }
+    };
+
+    // One block: O += V(kb)^T P(kb)^T, and under it the scores of block kb + 1.  A wave that runs S^T, softmax and O^T of
+    // the same block one after the other leaves the matrix pipe idle during its softmax and the vector pipe during its
+    // MFMAs, and two such waves on a SIMD fall into step.  Here the two products of different blocks are independent of
+    // the softmax arithmetic between them, so every MFMA is followed by a few vector instructions of the other block, which
+    // issue while it runs:
+    //   MFMA s of K(kb + 1) Q^T:  exponentials of block kb (20 of a lane's 32)
+    //   MFMA n of V(kb)^T P^T:    the other 12, then the maximum of block kb + 1
+    // All LDS operand reads are bare instructions with hand-kept waits, eight K reads or seven V read pairs ahead of their
+    // MFMA (V pairs start behind the last K reads).  P: CUR is the stage of V(kb); K(kb + 1) is in stage CUR ^ 1.
+    // EXP_A(e), EXP_B(e): elements 2e and 2e + 1 of the lane's 32 (element i of S[j] is 16 j + i).  The multiply-add as an
+    // instruction and the empty asm statements keep each of them where it is written: left alone, the compiler gathers the
+    // multiply-adds in front of all MFMAs and the conversions behind them.
+#define PIN(x) asm volatile("" : "+v"(x));
+#define SCALED(y, e) asm volatile("v_fma_f32 %0, %1, %2, %3" : "=v"(y) : "v"(S.v[(e) >> 4][(e) & 15]), "v"(c), "v"(nmc));
+#define EXP_A(e)                                                                                              \
+        {                                                                                                      \
+            float y;                                                                                           \
+            SCALED(y, 2 * (e))                                                                                 \
+            pe = __builtin_amdgcn_exp2f(y);                                                                    \
+            PIN(pe)                                                                                            \
+        }
+#define EXP_B(e)                                                                                              \
+        {                                                                                                      \
+            float y;                                                                                           \
+            SCALED(y, 2 * (e) + 1)                                                                             \
+            const float pf = __builtin_amdgcn_exp2f(y);                                                        \
+            psum0 += pe;                                                                                       \
+            psum1 += pf;                                                                                       \
+            bf16x2 pk = {(__bf16)pe, (__bf16)pf};                                                              \
+            pw[e] = __builtin_bit_cast(u32, pk);                                                               \
+            PIN(pw[e])                                                                                         \
+        }
+#define K_READ(i) ka[i] = lds_load128_at<(CUR ^ 1) * TILE_BYTES + ((i) >> 2) * SUB_BYTES + ((i) & 1) * 32 * 64>(koff[((i) >> 1) & 1]);
+#define QK_MFMA(i, W)                                                                                         \
+        lds_wait<W>(ka[i]);                                                                                    \
+        T.v[(i) & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[i], qreg[(i) >> 1], (i) < 2 ? zero16 : T.v[(i) & 1], 0, 0, 0); \
+        __builtin_amdgcn_sched_barrier(0);
+#define V_READ(n)                                                                                             \
+        vlo[n] = lds_load_tr4<(2 + CUR) * TILE_BYTES + ((n) & 3) * SUB_BYTES + 16 * ((n) >> 2) * 64>(voff);         \
+        vhi[n] = lds_load_tr4<(2 + CUR) * TILE_BYTES + ((n) & 3) * SUB_BYTES + (16 * ((n) >> 2) + 8) * 64>(voff);
+#define PV_MFMA(n, W)                                                                                         \
+        lds_wait2<W>(vlo[n], vhi[n]);                                                                          \
+        oacc[(n) & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(                                               \
+            __builtin_shufflevector(vlo[n], vhi[n], 0, 1, 2, 3, 4, 5, 6, 7), p_operand(&pw[4 * ((n) >> 2)]),   \
+            oacc[(n) & 3], 0, 0, 0);                                                                           \
+        __builtin_amdgcn_sched_barrier(0);
+#define FENCE __builtin_amdgcn_sched_barrier(0);
+    // (an instruction of its own: fmaxf on MFMA results costs two more per pair to quiet NaNs.  The scores were finished by
+    // MFMAs at least three MFMAs back, longer than the distance the hardware asks for before a vector read.)
+#define MAX2(i)                                                                                               \
+        asm volatile("v_max3_f32 %0, %0, %1, %2" : "+v"(mloc) : "v"(T.v[(i) >> 3][(2 * (i)) & 15]), "v"(T.v[(i) >> 3][(2 * (i) + 1) & 15]));
+    auto p_operand = [](const u32 *wd) {
+        const uint4 v = make_uint4(wd[0], wd[1], wd[2], wd[3]);
+        return __builtin_bit_cast(bf16x8, v);
+    };
+    auto block = [&](auto cur_c, int kb, Scores &S, Scores &T) {
+        constexpr int CUR = decltype(cur_c)::value;
+        const bool next = kb + 1 < kb1;  // uniform
+        if (kb + 2 < kb1) fetch_k(kb + 2, CUR);      // K(kb) was last read before the previous barrier,
+        if (next) fetch_v(kb + 1, CUR ^ 1);          // V(kb - 1) too
+        if (active) {
+            float psum0 = 0.f, psum1 = 0.f, pe;
+            u32 pw[16];  // the probabilities as pairs of bf16
+            bf16x4 vlo[16], vhi[16];
+            if (next) {
+                bf16x8 ka[16];  // read i: k-step i / 2, half i % 2
+                K_READ(0) K_READ(1) K_READ(2) K_READ(3) K_READ(4) K_READ(5) K_READ(6) K_READ(7) FENCE
+                EXP_A(0) FENCE
+                QK_MFMA(0, 7) K_READ(8) EXP_B(0) FENCE
+                QK_MFMA(1, 7) K_READ(9) EXP_A(1) FENCE
+                QK_MFMA(2, 7) K_READ(10) EXP_B(1) FENCE
+                QK_MFMA(3, 7) K_READ(11) EXP_A(2) FENCE
+                QK_MFMA(4, 7) K_READ(12) EXP_B(2) FENCE
+                QK_MFMA(5, 7) K_READ(13) EXP_A(3) FENCE
+                QK_MFMA(6, 7) K_READ(14) EXP_B(3) FENCE
+                QK_MFMA(7, 7) K_READ(15) EXP_A(4) FENCE
+                QK_MFMA(8, 7) V_READ(0) EXP_B(4) FENCE
+                QK_MFMA(9, 8) V_READ(1) EXP_A(5) FENCE
+                QK_MFMA(10, 9) V_READ(2) EXP_B(5) FENCE
+                QK_MFMA(11, 10) V_READ(3) EXP_A(6) FENCE
+                QK_MFMA(12, 11) V_READ(4) EXP_B(6) EXP_A(7) FENCE
+                QK_MFMA(13, 12) V_READ(5) EXP_B(7) EXP_A(8) FENCE
+                QK_MFMA(14, 13) V_READ(6) EXP_B(8) EXP_A(9) FENCE
+                QK_MFMA(15, 14) EXP_B(9) FENCE
+            } else {
+                V_READ(0) V_READ(1) V_READ(2) V_READ(3) V_READ(4) V_READ(5) V_READ(6) FENCE
+                EXP_A(0) EXP_B(0) EXP_A(1) EXP_B(1) EXP_A(2) EXP_B(2) EXP_A(3) EXP_B(3) EXP_A(4) EXP_B(4)
+                EXP_A(5) EXP_B(5) EXP_A(6) EXP_B(6) EXP_A(7) EXP_B(7) EXP_A(8) EXP_B(8) EXP_A(9) EXP_B(9) FENCE
+            }
+            PV_MFMA(0, 12) V_READ(7) EXP_A(10) FENCE
+            PV_MFMA(1, 12) V_READ(8) EXP_B(10) FENCE
+            if (next) mask(kb + 1, T);
+            float mloc = -INFINITY;
+            PV_MFMA(2, 12) V_READ(9) EXP_A(11) MAX2(0) FENCE
+            PV_MFMA(3, 12) V_READ(10) EXP_B(11) MAX2(1) FENCE
+            PV_MFMA(4, 12) V_READ(11) EXP_A(12) MAX2(2) FENCE
+            PV_MFMA(5, 12) V_READ(12) EXP_B(12) MAX2(3) FENCE
+            PV_MFMA(6, 12) V_READ(13) EXP_A(13) MAX2(4) FENCE
+            PV_MFMA(7, 12) V_READ(14) EXP_B(13) MAX2(5) FENCE
+            PV_MFMA(8, 12) V_READ(15) EXP_A(14) MAX2(6) FENCE
+            PV_MFMA(9, 12) EXP_B(14) MAX2(7) FENCE
+            PV_MFMA(10, 10) EXP_A(15) MAX2(8) FENCE
+            PV_MFMA(11, 8) EXP_B(15) MAX2(9) FENCE
+            PV_MFMA(12, 6) MAX2(10) MAX2(11) FENCE
+            PV_MFMA(13, 4) MAX2(12) MAX2(13) FENCE
+            PV_MFMA(14, 2) MAX2(14) MAX2(15) FENCE
+            PV_MFMA(15, 0)
+            l_run += psum0 + psum1;
+            if (next) move_reference(mloc);
+            // the "memory" clobber keeps the next block's loads into these stages behind this block's reads
+            asm volatile("" ::: "memory");
+        }
+        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's part of the next tiles has landed
         __syncthreads();
+    };
+    Scores S0, S1;
+    fetch_k(kb0, 0);
+    fetch_v(kb0, 0);
+    if (kb0 + 1 < kb1) fetch_k(kb0 + 1, 1);
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's part of the tiles is in LDS
+    __syncthreads();
+    if (active) {  // scores of the first block
+        constexpr int CUR = 1;
+        Scores &T = S0;
+        bf16x8 ka[16];
+        K_READ(0) K_READ(1) K_READ(2) K_READ(3) K_READ(4) K_READ(5) K_READ(6) K_READ(7) FENCE
+        QK_MFMA(0, 7) K_READ(8) FENCE QK_MFMA(1, 7) K_READ(9) FENCE QK_MFMA(2, 7) K_READ(10) FENCE QK_MFMA(3, 7) K_READ(11) FENCE
+        QK_MFMA(4, 7) K_READ(12) FENCE QK_MFMA(5, 7) K_READ(13) FENCE QK_MFMA(6, 7) K_READ(14) FENCE QK_MFMA(7, 7) K_READ(15) FENCE
+        QK_MFMA(8, 7) FENCE QK_MFMA(9, 6) FENCE QK_MFMA(10, 5) FENCE QK_MFMA(11, 4) FENCE
+        QK_MFMA(12, 3) FENCE QK_MFMA(13, 2) FENCE QK_MFMA(14, 1) FENCE QK_MFMA(15, 0)
+        mask(kb0, S0);
+        float mloc = -INFINITY;
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) mloc = fmaxf(mloc, S0.v[j][i]);
+        move_reference(mloc);
+        asm volatile("" ::: "memory");
     }
+    __syncthreads();  // K stage 0 is free
+    for (int kb = kb0; kb < kb1; kb += 2) {
+        block(std::integral_constant<int, 0>(), kb, S0, S1);
+        if (kb + 1 < kb1) block(std::integral_constant<int, 1>(), kb + 1, S1, S0);
+    }
+#undef PIN
+#undef SCALED
+#undef EXP_A
+#undef EXP_B
+#undef K_READ
+#undef QK_MFMA
+#undef V_READ
+#undef PV_MFMA
+#undef FENCE
+#undef MAX2
 
     // ---- epilogue -------------------------------------------------------------------------------
     const float l_tot = half_swap_sum(l_run);
@@ -426,7 +487,7 @@ __device__ __forceinline__ void tile_segment(const AttnArgs &a, unsigned char *s
                 *(bf16x4 *)(op + 32 * db + 8 * q + 4 * half) = o4;
             }
     } else {
-        const int rit = 32 * w + col;  // row inside the tile
+        const int rit = 32 * rb + col;  // row inside the tile
         float *op = dst.o + (int64_t)rit * D;
 #pragma unroll
         for (int db = 0; db < DBLK; ++db)
@@ -439,8 +500,8 @@ __device__ __forceinline__ void tile_segment(const AttnArgs &a, unsigned char *s
     }
 }
 
-// One workgroup per (kv head, row tile, sequence), the whole key range: enough of them to fill
-// the chip several times over.  blockIdx.x = kv head: workgroups are dealt to the 8 XCDs
+// One workgroup per (kv head, row tile, sequence), the whole key range: for batches that the balanced schedule below does
+// not take.  blockIdx.x = kv head: workgroups are dealt to the 8 XCDs
 // round-robin by linear id, so all row tiles of one kv head land on one XCD and share its L2
 // copy of that head's K/V.
 template <int D>
@@ -454,10 +515,10 @@ __global__ __launch_bounds__(256, 2) void attn_tile_kernel(AttnArgs a) {
     dst.direct = true;
     dst.o = nullptr;
     dst.ml = nullptr;
-    tile_segment<D>(a, s_dyn, h, b, m0, 0, nb, dst);
+    tile_segment<D>(a, s_dyn, h, b, m0, blockIdx.y + blockIdx.z, 0, nb, dst);
 }
 
-// ---- balanced schedule for batches that cannot fill the chip with whole (sequence, tile) items --
+// ---- balanced schedule -----------------------------------------------------------------------------
 // Each kv head gets P workgroup slots (two per compute unit over all heads).  Sequences are
 // grouped into classes by their number of row tiles m; the key blocks of a class's sequences,
 // concatenated in batch order, form its C_m "columns" of cost m each.  Class m is given g_m
@@ -579,7 +640,7 @@ __global__ __launch_bounds__(256, 2) void attn_gang_kernel(AttnArgs a, int P, in
         const int which = csb < lo ? 0 : 1;
         dst.o = part.o + (slot * 2 + which) * ATT_MTILE * D;
         dst.ml = part.ml + (slot * 2 + which) * ATT_MTILE;
-        tile_segment<D>(a, s_dyn, h, b, tile * ATT_MTILE, kb0, kb1, dst);
+        tile_segment<D>(a, s_dyn, h, b, tile * ATT_MTILE, j, kb0, kb1, dst);
     }
 }
 
@@ -1397,11 +1458,12 @@ int attn_launch(const AttnArgs &a, hipStream_t st, hipError_t *err) {
     // few (sequence, kv head, row tile) items: the barrier-free small-batch kernel (64-wide heads: always)
     if (a.D == 64) return wave_launch<64>(a, st, err);
     if (base_wgs < 128) return wave_launch<128>(a, st, err);
-    // Fewer whole (sequence, kv head, row tile) items than four rounds of two workgroups per compute
-    // unit: the balanced schedule (needs one lane per sequence and a slot for every tile count).
+    // The balanced schedule wherever its plan fits (one lane per sequence, a slot for every tile count): also for batches of
+    // thousands of whole (sequence, kv head, row tile) items, whose lengths differ (64 sequences of 256 .. 4,096 keys: 295 us
+    // with one workgroup per item, 234 + 15.7 us balanced).
     const int P = 2 * a.n_cu / a.Hkv;
-    const bool gang = base_wgs < 8 * a.n_cu && a.batch <= 64 && mtiles <= 63 && P >= mtiles * (mtiles + 1) / 2 &&
-                      a.ws && (size_t)a.Hkv * P * 2 * ATT_MTILE * ((size_t)a.D * 4 + 8) + 64 * GS_WORDS * 4 <= a.ws_bytes;
+    const bool gang = a.batch <= 64 && mtiles <= 63 && P >= mtiles * (mtiles + 1) / 2 && a.ws &&
+                      (size_t)a.Hkv * P * 2 * ATT_MTILE * ((size_t)a.D * 4 + 8) + 64 * GS_WORDS * 4 <= a.ws_bytes;
     if (!gang) {
         launch_kernel(KID_ATTN, st, attn_tile_kernel<128>, dim3(a.Hkv, mtiles, a.batch), dim3(256), TILE_LDS_BYTES, a);
         *err = hipGetLastError();
