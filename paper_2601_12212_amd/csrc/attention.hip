@@ -57,18 +57,25 @@ __device__ __forceinline__ bf16x8 lds_load128(u32 addr) {
 // per-lane byte offset, the LDS destination (wave-uniform, the lanes' 16 bytes follow each other) in M0: no
 // vector arithmetic per load, and no 64-bit per-lane pointers to keep and advance.  OFF is added to the global address; the
 // instruction adds its offset to the LDS address as well, so M0 holds the destination less OFF.
+// The hardware asks for five wait states between a vector instruction that writes a scalar register (readfirstlane, the
+// reload of a spilled one) and a memory instruction that reads it, and the compiler does not see the memory instruction in
+// here: the first of a group of loads from one base keeps that distance itself.
 template <int OFF>
 __device__ __forceinline__ void load_to_lds16(const void __attribute__((address_space(1))) *base, u32 lane_off, u32 lds_addr) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3" ::"v"(lane_off), "s"(base),
-                 "s"(lds_addr - OFF), "n"(OFF)
-                 : "memory", "m0");
+    if constexpr (OFF == 0)
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lane_off), "s"(base), "s"(lds_addr)
+                     : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3" ::"v"(lane_off), "s"(base),
+                     "s"(lds_addr - OFF), "n"(OFF)
+                     : "memory", "m0");
 }
-// a 64-bit value that is the same in every lane, moved to scalar registers where the compiler has not seen that
-__device__ __forceinline__ int64_t uniform_i64(int64_t v) {
-    const u32 lo = __builtin_amdgcn_readfirstlane((u32)v), hi = __builtin_amdgcn_readfirstlane((u32)((u64)v >> 32));
-    return (int64_t)(((u64)hi << 32) | lo);
+// a pointer that is the same in every lane, moved to scalar registers where the compiler has not seen that
+__device__ __forceinline__ gbf16p uniform_ptr(gbf16p p) {
+    const u64 v = (u64)(uintptr_t)p;
+    const u32 lo = __builtin_amdgcn_readfirstlane((u32)v), hi = __builtin_amdgcn_readfirstlane((u32)(v >> 32));
+    return (gbf16p)(uintptr_t)(((u64)hi << 32) | lo);
 }
-__device__ __forceinline__ gbytep uniform_ptr(gbytep p) { return (gbytep)uniform_i64((int64_t)(uintptr_t)p); }
 template <int OFF>
 __device__ __forceinline__ bf16x8 lds_load128_at(u32 addr) {
     bf16x8 v;
@@ -225,8 +232,8 @@ __device__ __forceinline__ void tile_segment(const AttnArgs &a, unsigned char *s
     float m_run = -INFINITY, l_run = 0.f;
     const float c = a.scale * 1.4426950408889634f;
 
-    const gbf16p kpre = (gbf16p)a.k_prefix[b] + (int64_t)h * a.kv_stride_head;
-    const gbf16p vpre = (gbf16p)a.v_prefix[b] + (int64_t)h * a.kv_stride_head;
+    const gbf16p kpre = uniform_ptr((gbf16p)a.k_prefix[b] + (int64_t)h * a.kv_stride_head);
+    const gbf16p vpre = uniform_ptr((gbf16p)a.v_prefix[b] + (int64_t)h * a.kv_stride_head);
     const gbf16p ktree = (gbf16p)a.k_tree + ((int64_t)b * a.TT_cap * a.Hkv + h) * D;
     const gbf16p vtree = (gbf16p)a.v_tree + ((int64_t)b * a.TT_cap * a.Hkv + h) * D;
     const int64_t stok = a.kv_stride_tok, stree = (int64_t)a.Hkv * D;
@@ -244,7 +251,7 @@ __device__ __forceinline__ void tile_segment(const AttnArgs &a, unsigned char *s
         const ldsp dst = (ldsp)s_dyn + tile + w * 1024;
         if (small_stride && kb * TILE_KEYS + TILE_KEYS <= L) {  // block inside the prefix (uniform test)
             const u32 dl = (u32)(uintptr_t)dst;
-            const gbytep base = uniform_ptr((gbytep)(pre + (int64_t)kb * TILE_KEYS * stok));
+            const gbytep base = (gbytep)(pre + (int64_t)kb * TILE_KEYS * stok);
             load_to_lds16<0>(base, poff, dl);
             load_to_lds16<64>(base, poff, dl + SUB_BYTES);
             load_to_lds16<128>(base, poff, dl + 2 * SUB_BYTES);
