@@ -463,8 +463,15 @@ __device__ __forceinline__ void tile_segment(const AttnArgs &a, unsigned char *s
         asm volatile("" ::: "memory");
     }
     __syncthreads();  // K stage 0 is free
+    // The two workgroups of a compute unit have equal work, but a SIMD issues the older of two ready waves, so the first to
+    // arrive finished 15 us of 110 before the second, which then ran alone at 60 % of the pair's rate.  The wave in the odd slot
+    // goes first in every other block instead: both end within 5 us (4 sequences of a 70B step 121 -> 117 us, 64 wide trees
+    // 240 -> 231; odd slots first in every block: 120 and 236).
+    const bool odd_slot = __builtin_amdgcn_s_getreg((3 << 11) | 4) & 1;  // HW_ID, 4 bits from bit 0: wave slot of the SIMD
     for (int kb = kb0; kb < kb1; kb += 2) {
+        if (odd_slot) __builtin_amdgcn_s_setprio(1);
         block(std::integral_constant<int, 0>(), kb, S0, S1);
+        if (odd_slot) __builtin_amdgcn_s_setprio(0);
         if (kb + 1 < kb1) block(std::integral_constant<int, 1>(), kb + 1, S1, S0);
     }
 #undef PIN
