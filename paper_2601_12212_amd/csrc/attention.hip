@@ -4,15 +4,16 @@
 // the N dimension of S^T = K Q^T so that every lane owns ONE query column of the 32x32
 // score block: the softmax statistics are lane-local plus one exchange with lane^32.  The
 // probabilities come out of the S^T accumulator in exactly the register layout the B
-// operand of O^T = V^T P^T wants, so P never leaves registers.  K tiles are staged in LDS
-// row-major, V tiles transposed ([d][key], key order permuted to match the accumulator
-// layout).  The prefix may be split across workgroups (partial max / sum / O, merged by a
-// second kernel) when a batch offers too few (sequence, kv head, row tile) items to fill
-// the chip.  The ancestor bitset is applied only to key blocks that contain tree keys.
+// operand of O^T = V^T P^T wants, so P never leaves registers.  K and V tiles are staged in LDS
+// row-major; the V operand comes from the transposing LDS read.  The keys of a sequence may be split
+// across workgroups, which leave partial max / sum / O, when a batch offers too few
+// (sequence, kv head, row tile) items to fill the chip (small batches, merged by a second kernel) or items of
+// different lengths (large batches, merged by the workgroup that comes last).  The ancestor bitset is
+// applied only to key blocks that contain tree keys.
 //
-// fp32 path: plain ALU kernel, one wave per (node, head); a correctness path for small
-// problems and for head sizes the MFMA path does not cover.
+// Other head sizes and fp32: plain ALU kernel, one workgroup per (node, head).
 
+#include <atomic>
 #include <type_traits>
 
 #include "common.hpp"
@@ -185,19 +186,38 @@ __device__ __forceinline__ u32 vis_window(int off, u64 mask0, u64 mask1) {
 #define TILE_LDS_BYTES (4 * TILE_BYTES)  // two K tiles, then two V tiles
 typedef char __attribute__((address_space(3))) *ldsp;
 
-// Where a (sequence, row tile, key range) result goes: the output rows directly when the range is
-// the whole sequence, else 128 partial rows (unnormalised O, running max, sum) for the combine.
-struct TileDest {
-    bool direct;
-    float *o;     // [128, D]
-    float2 *ml;   // [128]
+// One key range of a (sequence, row tile): the `me`-th of `parts`.  With more than one, the workgroups leave partials
+// (unnormalised O, running max, sum) and the one that comes last puts them together; partial i lies at index
+// 2 (slot + i step), the first at 2 slot + 1.  Values are 64-bit words in the order in which a row block's lanes hold them,
+// since the same lanes of another workgroup read them.
+struct TileParts {
+    int parts, me;
+    int slot, step;
+    u64 *o;       // [.., D / 4, 256]
+    u64 *ml;      // [.., 128]
+    u64 *count;   // partials left so far, in the low 16 bits, if the others are `tag`; anything else counts as none
+    u64 tag;
 };
+// Partials and counts cross between workgroups that may sit on different XCDs, whose L2 caches are not coherent: relaxed
+// atomics at agent scope go through to the memory side word by word, where a fence would write back and drop the whole L2.
+__device__ __forceinline__ void put_agent(u64 *p, u64 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ u64 get_agent(u64 *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// One more partial is there: true for the last of `parts`, which also clears the count.
+__device__ __forceinline__ bool arrive_last(u64 *count, u64 tag, int parts) {
+    u64 old = get_agent(count);
+    for (;;) {  // a failed exchange means that another of the parts came: at most `parts` turns
+        const int n = (old & ~(u64)0xffff) == tag ? (int)(old & 0xffff) + 1 : 1;
+        if (__hip_atomic_compare_exchange_strong(count, &old, n == parts ? 0 : tag | n, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT))
+            return n == parts;
+    }
+}
 
 // Rows m0 .. m0+127 of (sequence b, kv head h) against key blocks kb0 .. kb1-1 of that sequence.
 // Called by all 256 threads of the workgroup; ends behind a barrier, so calls can follow each other.
 template <int D>
 __device__ __forceinline__ void tile_segment(const AttnArgs &a, unsigned char *s_dyn, int h, int b, int m0, int rot, int kb0,
-                                             int kb1, TileDest dst) {
+                                             int kb1, const TileParts &pt) {
     static_assert(D == 128, "head dim");
     constexpr int KSTEPS = D / 16, DBLK = D / 32;
     const int G = a.Hq / a.Hkv;
@@ -486,32 +506,84 @@ __device__ __forceinline__ void tile_segment(const AttnArgs &a, unsigned char *s
 #undef MAX2
 
     // ---- epilogue -------------------------------------------------------------------------------
-    const float l_tot = half_swap_sum(l_run);
-    if (!qvalid) return;
-    if (dst.direct) {
-        const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-        __bf16 *op = (__bf16 *)a.out + (((int64_t)b * a.TT_cap + node) * a.Hq + hq) * D;
+    float l_tot = half_swap_sum(l_run);
+    if (pt.parts > 1) {
+        // The last part's workgroup usually finds the others' partials there, and then leaves none of its own.
+        __shared__ int s_last[2];
+        if (tid == 0) s_last[0] = get_agent(pt.count) == (pt.tag | (pt.parts - 1));
+        __syncthreads();
+        const int mine = 32 * rb + col;
+        if (!s_last[0]) {
+            if (active) {
+                const int64_t at = 2 * (pt.slot + pt.me * pt.step) + (pt.me == 0);
+                u64 *op = pt.o + at * (D / 4 * 256) + 64 * rb + lane;
 #pragma unroll
-        for (int db = 0; db < DBLK; ++db)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                bf16x4 o4;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) o4[e] = (__bf16)(oacc[db][q * 4 + e] * inv);
-                *(bf16x4 *)(op + 32 * db + 8 * q + 4 * half) = o4;
+                for (int i = 0; i < D / 4; ++i)
+                    put_agent(op + i * 256, __builtin_bit_cast(u64, make_float2(oacc[i >> 3][(2 * i) & 15], oacc[i >> 3][(2 * i + 1) & 15])));
+                if (half == 0) put_agent(pt.ml + at * ATT_MTILE + mine, __builtin_bit_cast(u64, make_float2(m_run, l_tot)));
             }
-    } else {
-        const int rit = 32 * rb + col;  // row inside the tile
-        float *op = dst.o + (int64_t)rit * D;
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the stores are there before the count says so
+            __syncthreads();
+            if (tid == 0) s_last[1] = arrive_last(pt.count, pt.tag, pt.parts);
+            __syncthreads();
+            if (!s_last[1]) return;
+        } else if (tid == 0) {
+            put_agent(pt.count, 0);
+        }
+        asm volatile("" ::: "memory");
+        if (active) {
+            // in the order of the parts, whoever came last: the same sum each time
+            float M = -INFINITY, l = 0.f;
+            f32x16 acc[DBLK];
 #pragma unroll
-        for (int db = 0; db < DBLK; ++db)
+            for (int db = 0; db < DBLK; ++db)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                float4 o4 = make_float4(oacc[db][q * 4], oacc[db][q * 4 + 1], oacc[db][q * 4 + 2], oacc[db][q * 4 + 3]);
-                *(float4 *)(op + 32 * db + 8 * q + 4 * half) = o4;
+                for (int i = 0; i < 16; ++i) acc[db][i] = 0.f;
+            for (int i = 0; i < pt.parts; ++i) {
+                float2 ml = make_float2(m_run, l_tot);
+                f32x16 o[DBLK];
+                if (i == pt.me) {
+#pragma unroll
+                    for (int db = 0; db < DBLK; ++db) o[db] = oacc[db];
+                } else {
+                    const int64_t at = 2 * (pt.slot + i * pt.step) + (i == 0);
+                    u64 *op = pt.o + at * (D / 4 * 256) + 64 * rb + lane;
+                    ml = __builtin_bit_cast(float2, get_agent(pt.ml + at * ATT_MTILE + mine));
+#pragma unroll
+                    for (int e = 0; e < D / 4; ++e) {
+                        const float2 v = __builtin_bit_cast(float2, get_agent(op + e * 256));
+                        o[e >> 3][(2 * e) & 15] = v.x;
+                        o[e >> 3][(2 * e + 1) & 15] = v.y;
+                    }
+                }
+                const bool some = ml.y > 0.f;  // a range whose keys were all hidden weighs nothing
+                const float M2 = some ? fmaxf(M, ml.x) : M;
+                const float keep = some ? __builtin_amdgcn_exp2f((M - M2) * c) : 1.f;  // first partial: exp2(-inf) = 0
+                const float wgt = some ? __builtin_amdgcn_exp2f((ml.x - M2) * c) : 0.f;
+#pragma unroll
+                for (int db = 0; db < DBLK; ++db)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) acc[db][e] = acc[db][e] * keep + o[db][e] * wgt;
+                l = l * keep + ml.y * wgt;
+                M = M2;
             }
-        if (half == 0) dst.ml[rit] = make_float2(m_run, l_tot);
+            l_tot = l;
+#pragma unroll
+            for (int db = 0; db < DBLK; ++db) oacc[db] = acc[db];
+        }
     }
+    if (!qvalid) return;
+    const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
+    __bf16 *op = (__bf16 *)a.out + (((int64_t)b * a.TT_cap + node) * a.Hq + hq) * D;
+#pragma unroll
+    for (int db = 0; db < DBLK; ++db)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            bf16x4 o4;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o4[e] = (__bf16)(oacc[db][q * 4 + e] * inv);
+            *(bf16x4 *)(op + 32 * db + 8 * q + 4 * half) = o4;
+        }
 }
 
 // One workgroup per (kv head, row tile, sequence), the whole key range: for batches that the balanced schedule below does
@@ -525,11 +597,9 @@ __global__ __launch_bounds__(256, 2) void attn_tile_kernel(AttnArgs a) {
     const int N = min(max(a.n_nodes[b], 1), a.TT_cap);
     if (m0 >= N * (a.Hq / a.Hkv)) return;
     const int nb = (max(a.prefix_len[b], 0) + N + TILE_KEYS - 1) / TILE_KEYS;
-    TileDest dst;
-    dst.direct = true;
-    dst.o = nullptr;
-    dst.ml = nullptr;
-    tile_segment<D>(a, s_dyn, h, b, m0, blockIdx.y + blockIdx.z, 0, nb, dst);
+    TileParts whole = {};
+    whole.parts = 1;
+    tile_segment<D>(a, s_dyn, h, b, m0, blockIdx.y + blockIdx.z, 0, nb, whole);
 }
 
 // ---- balanced schedule -----------------------------------------------------------------------------
@@ -540,16 +610,19 @@ __global__ __launch_bounds__(256, 2) void attn_tile_kernel(AttnArgs a) {
 // its K/V together and share it in L2); gang j takes columns [j T_m, (j+1) T_m) of the class, with
 // T_m = ceil(C_m / g_m), and the g_m are the ones that minimise max_m T_m under sum m g_m <= P.
 // A slot therefore works through a few (sequence, tile, key range) segments of near-equal total
-// length.  A sequence cut by a range boundary leaves partials: per slot one "head" (its first
+// length.  A sequence cut by a range boundary leaves partials: per slot at most one "head" (its first
 // segment, when that sequence began in an earlier gang) and one "tail" (a sequence that began
-// here and runs on).  Every wave derives the plan by itself from n_nodes / prefix_len with wave
+// here and runs on), and the slot of its first gang holds the count of them.  The last workgroup to come
+// merges: a merge kernel of its own read every partial back from memory after all had been written, 9 to 16 us
+// of a launch of 62 to 240, while here a head is written early and read once by the workgroup that ends with the tail.
+// Every wave derives the plan by itself from n_nodes / prefix_len with wave
 // operations (sequence b in lane b: batch <= 64; class m in lane m), so no barrier is involved.
 struct GangPartial {
-    float *o;     // [Hkv, P, 2, 128, D]
-    float2 *ml;   // [Hkv, P, 2, 128]
-    int *seq;     // [batch, 8]: where sequence b's partials are (written by the attention kernel)
+    u64 *o;       // [Hkv, P, 2, D / 4, 256]
+    u64 *ml;      // [Hkv, P, 2, 128]
+    u64 *count;   // [Hkv, P]
+    u64 tag;      // of this launch: what the memory held before it never looks like a count
 };
-enum { GS_FIRST = 0, GS_LAST, GS_BASE, GS_CLS, GS_T, GS_START, GS_WORDS = 8 };
 
 __device__ __forceinline__ int wave_excl_scan_i32(int v, int lane) {
     int x = v;
@@ -614,27 +687,6 @@ __global__ __launch_bounds__(256, 2) void attn_gang_kernel(AttnArgs a, int P, in
             else base += span;
         }
     }
-    // Slots y, y+P, .. of head 0 also leave sequence y's entry of the table the combine kernel reads:
-    // first and last gang of the sequence, first slot, tile count and gang width of its class, and
-    // its first column.
-    if (h == 0 && threadIdx.x < 64) {
-        for (int b = y; b < a.batch; b += P) {
-            const int mb = __builtin_amdgcn_readlane(p.mt, b), nbb = __builtin_amdgcn_readlane(p.nb, b);
-            int bs = 0;
-            for (int m = 1; m < mb; ++m) bs += m * __builtin_amdgcn_readlane(p.g, m);
-            const int Tb = __builtin_amdgcn_readlane(p.T, mb);
-            const int csb = __builtin_amdgcn_readlane(wave_excl_scan_i32(p.mt == mb ? p.nb : 0, lane), b);
-            if (lane == 0) {
-                int *e = part.seq + b * GS_WORDS;
-                e[GS_FIRST] = csb / Tb;
-                e[GS_LAST] = (csb + nbb - 1) / Tb;
-                e[GS_BASE] = bs;
-                e[GS_CLS] = mb;
-                e[GS_T] = Tb;
-                e[GS_START] = csb;
-            }
-        }
-    }
     if (cls == 0) return;  // spare slot
     const int j = (y - base) / cls, tile = (y - base) % cls;
     const int Tc = __builtin_amdgcn_readlane(p.T, cls), Cc = __builtin_amdgcn_readlane(p.C, cls);
@@ -643,74 +695,23 @@ __global__ __launch_bounds__(256, 2) void attn_gang_kernel(AttnArgs a, int P, in
     const int val = p.mt == cls ? p.nb : 0;
     const int cs = wave_excl_scan_i32(val, lane);
     u64 segs = __ballot(val > 0 && cs < hi && cs + val > lo);
-    const int64_t slot = (int64_t)h * P + y;
     while (segs) {
         const int b = (int)__builtin_ctzll(segs);
         segs &= segs - 1;
         const int csb = __builtin_amdgcn_readlane(cs, b), nbb = __builtin_amdgcn_readlane(val, b);
         const int kb0 = max(lo, csb) - csb, kb1 = min(hi, csb + nbb) - csb;
-        TileDest dst;
-        dst.direct = kb0 == 0 && kb1 == nbb;
-        const int which = csb < lo ? 0 : 1;
-        dst.o = part.o + (slot * 2 + which) * ATT_MTILE * D;
-        dst.ml = part.ml + (slot * 2 + which) * ATT_MTILE;
-        tile_segment<D>(a, s_dyn, h, b, tile * ATT_MTILE, j, kb0, kb1, dst);
+        const int jf = csb / Tc, jl = (csb + nbb - 1) / Tc;  // its first and last gang
+        TileParts pt;
+        pt.parts = jl - jf + 1;
+        pt.me = j - jf;
+        pt.slot = h * P + base + jf * cls + tile;
+        pt.step = cls;
+        pt.o = part.o;
+        pt.ml = part.ml;
+        pt.count = part.count + pt.slot;
+        pt.tag = part.tag;
+        tile_segment<D>(a, s_dyn, h, b, tile * ATT_MTILE, j, kb0, kb1, pt);
     }
-}
-
-// Merge of the partials of the balanced schedule: one thread per (row, 4 output columns) of
-// sequence blockIdx.y.  A sequence that stayed inside one gang was written directly.
-template <int D>
-__global__ __launch_bounds__(256) void attn_gang_combine_kernel(AttnArgs a, int P, GangPartial part) {
-    const int b = blockIdx.y;
-    const int *e = part.seq + b * GS_WORDS;
-    const int jf = e[GS_FIRST], jl = e[GS_LAST];
-    if (jf == jl) return;
-    const int base = e[GS_BASE], cls = e[GS_CLS], Tc = e[GS_T], csb = e[GS_START];
-    const int N = min(max(a.n_nodes[b], 1), a.TT_cap);
-    const int G = a.Hq / a.Hkv;
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int c4 = (int)(idx % (D / 4));
-    const int64_t r = idx / (D / 4);  // row inside the sequence: node * Hq + head
-    if (r >= (int64_t)N * a.Hq) return;
-    const int node = (int)(r / a.Hq), hq = (int)(r % a.Hq), h = hq / G;
-    const int mq = node * G + hq % G, tile = mq / ATT_MTILE, rit = mq % ATT_MTILE;
-    const float c = a.scale * 1.4426950408889634f;
-    auto prow = [&](int j) {
-        const int64_t slot = (int64_t)h * P + base + j * cls + tile;
-        return (slot * 2 + (csb < j * Tc ? 0 : 1)) * ATT_MTILE + rit;
-    };
-    // Four partials at a time, every load asked for before any is used (a load that waited for the
-    // previous partial's weight would make the kernel one memory round trip per partial long); the
-    // running maximum moves as in the attention kernel itself.
-    float M = -INFINITY, l = 0.f;
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int j0 = jf; j0 <= jl; j0 += 4) {
-        float2 ml[4];
-        float4 o[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int64_t pr = prow(min(j0 + u, jl));
-            ml[u] = part.ml[pr];
-            o[u] = *(const float4 *)(part.o + pr * D + c4 * 4);
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            if (j0 + u > jl || !(ml[u].y > 0.f)) continue;  // a range whose keys were all hidden weighs nothing
-            const float M2 = fmaxf(M, ml[u].x);
-            const float keep = __builtin_amdgcn_exp2f((M - M2) * c);  // first partial: exp2(-inf) = 0
-            const float wgt = __builtin_amdgcn_exp2f((ml[u].x - M2) * c);
-            acc.x = acc.x * keep + o[u].x * wgt; acc.y = acc.y * keep + o[u].y * wgt;
-            acc.z = acc.z * keep + o[u].z * wgt; acc.w = acc.w * keep + o[u].w * wgt;
-            l = l * keep + ml[u].y * wgt;
-            M = M2;
-        }
-    }
-    const float inv = l > 0.f ? 1.0f / l : 0.f;
-    bf16x4 o4;
-    o4[0] = (__bf16)(acc.x * inv); o4[1] = (__bf16)(acc.y * inv);
-    o4[2] = (__bf16)(acc.z * inv); o4[3] = (__bf16)(acc.w * inv);
-    *(bf16x4 *)((__bf16 *)a.out + ((int64_t)b * a.TT_cap * a.Hq + r) * D + c4 * 4) = o4;
 }
 
 // ------------------------------------------------------------------- small-batch kernel -----
@@ -1393,10 +1394,9 @@ hipError_t attn_init() {
 }
 
 // scratch of the balanced large-batch schedule: (kv heads x slots per head) <= 2 x compute units
-// slots, two partials of 128 rows each, and the table of up to 64 sequences
-static size_t gang_bytes(int D, int n_cu) {
-    return (size_t)2 * n_cu * 2 * ATT_MTILE * ((size_t)D * 4 + 8) + 64 * GS_WORDS * 4;
-}
+// slots, two partials of 128 rows and a count each
+static size_t gang_slot_bytes(int D) { return 2 * ATT_MTILE * ((size_t)D * 4 + 8) + 8; }
+static size_t gang_bytes(int D, int n_cu) { return (size_t)2 * n_cu * gang_slot_bytes(D); }
 
 // scratch of one key split of the small-batch kernel, per (sequence, kv head, 32-row block)
 static size_t wave_unit_bytes(int D) { return (size_t)(D / 32) * 4 * 64 * 16 + 32 * 8; }
@@ -1474,25 +1474,23 @@ int attn_launch(const AttnArgs &a, hipStream_t st, hipError_t *err) {
     if (base_wgs < 128) return wave_launch<128>(a, st, err);
     // The balanced schedule wherever its plan fits (one lane per sequence, a slot for every tile count): also for batches of
     // thousands of whole (sequence, kv head, row tile) items, whose lengths differ (64 sequences of 256 .. 4,096 keys: 295 us
-    // with one workgroup per item, 234 + 15.7 us balanced).
+    // with one workgroup per item, 234 balanced).
     const int P = 2 * a.n_cu / a.Hkv;
     const bool gang = a.batch <= 64 && mtiles <= 63 && P >= mtiles * (mtiles + 1) / 2 && a.ws &&
-                      (size_t)a.Hkv * P * 2 * ATT_MTILE * ((size_t)a.D * 4 + 8) + 64 * GS_WORDS * 4 <= a.ws_bytes;
+                      (size_t)a.Hkv * P * gang_slot_bytes(a.D) <= a.ws_bytes;
     if (!gang) {
         launch_kernel(KID_ATTN, st, attn_tile_kernel<128>, dim3(a.Hkv, mtiles, a.batch), dim3(256), TILE_LDS_BYTES, a);
         *err = hipGetLastError();
         return *err == hipSuccess ? DT_OK : DT_ERR_HIP;
     }
+    static std::atomic<u64> launches{0};
+    const size_t slots = (size_t)a.Hkv * P;
     GangPartial part;
-    part.o = (float *)a.ws;
-    part.ml = (float2 *)((char *)a.ws + (size_t)a.Hkv * P * 2 * ATT_MTILE * a.D * 4);
-    part.seq = (int *)((char *)a.ws + (size_t)a.Hkv * P * 2 * ATT_MTILE * ((size_t)a.D * 4 + 8));
+    part.o = (u64 *)a.ws;
+    part.ml = part.o + slots * 2 * ATT_MTILE * (a.D / 2);
+    part.count = part.ml + slots * 2 * ATT_MTILE;
+    part.tag = (launches.fetch_add(1, std::memory_order_relaxed) + 1) * 0x9e3779b97f4a7c15ull & ~(u64)0xffff;
     launch_kernel(KID_ATTN, st, attn_gang_kernel<128>, dim3(a.Hkv, P), dim3(256), TILE_LDS_BYTES, a, P, mtiles, part);
-    *err = hipGetLastError();
-    if (*err != hipSuccess) return DT_ERR_HIP;
-    const int64_t items = (int64_t)a.TT_cap * a.Hq * (a.D / 4);
-    launch_kernel(KID_ATTN_COMBINE, st, attn_gang_combine_kernel<128>, dim3((unsigned)((items + 255) / 256), a.batch),
-                  dim3(256), 0, a, P, part);
     *err = hipGetLastError();
     return *err == hipSuccess ? DT_OK : DT_ERR_HIP;
 }

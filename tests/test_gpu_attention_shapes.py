@@ -1,12 +1,12 @@
 """GPU parity of the attention kernels that serve 64-wide heads (matrix cores) and every other head size (plain ALU), at
 the edges of their tiles: row counts around 32, key counts around a block, key splits, and head sizes around the widths
-that decide how a row is loaded."""
+that decide how a row is loaded; and of the large-batch schedule where it cuts sequences into key ranges."""
 import numpy as np
 import pytest
 
 import dt_synth
 from tests._cases import oracle_case
-from tests.test_gpu_parity import check_case
+from tests.test_gpu_parity import check_case, make_step
 
 pytestmark = pytest.mark.gpu
 
@@ -40,3 +40,24 @@ def test_plain_kernel_head_sizes(dtype, D):
     # rows shorter than one 16-byte load, a multiple of it or not, one and two columns per lane; key counts below, at and
     # past one block, and enough for every wave to have several
     check_case(oracle_case(0, cfg=_cfg(dtype, D, [(1, 1, 1), (20, 4, 3), (70, 4, 6)], [0, 44, 600], 4, 2)))
+
+
+@pytest.mark.parametrize("plen", [[5000] + [0, 1, 63, 64, 65] * 4, [300 + 97 * (i % 23) for i in range(64)]],
+                         ids=["one_long", "batch_64"])
+def test_balanced_schedule_cut_sequences(plen):
+    # one sequence cut into many key ranges among short ones, and the largest batch that the schedule takes; the partials are
+    # merged by whichever workgroup comes last, with the same bits each time and whatever the workspace held before
+    params = [(1 if i % 7 == 3 else 30 + 3 * (i % 5), 4, 6) for i in range(len(plen))]
+    case = oracle_case(0, cfg=_cfg("bf16", 128, params, plen, 8, 8))
+    check_case(case)
+    st = make_step(case)
+    st.build_tree()
+    st.tree_attention()
+    first = st.out.clone()
+    for fill in (0x00, 0xff, 0x3f):
+        st.ws.fill_(fill)
+        st.out.fill_(7.0)
+        st.tree_attention()
+        for b in range(len(plen)):
+            n = case.trees[b]["n_nodes"]
+            assert torch.equal(st.out[b, :n].view(torch.int16), first[b, :n].view(torch.int16)), (b, fill)
