@@ -2,18 +2,22 @@
 // ancestor bitsets.  One workgroup of eight waves per sequence; the whole candidate pool (at most
 // k + (d-1)k^2 = 7200 scores) lives in LDS.
 //
-// Selections ("the n best by (score desc, pool index asc)") never sort.
-//  * A level of up to 128 candidates (k <= 11) is ranked by counting: every candidate counts the candidates with
-//    a larger key, the work split over the waves by (64 candidates) x (a slice of the others), the
-//    others read as LDS broadcasts.  Every wave then forms the chosen set by itself from the partial
-//    counts, so the next level's scores follow without another barrier.
-//  * Everything else (larger levels, the rerank over the pool, exact ties that straddle a cut) is cut by
-//    score buckets: one LDS histogram over floor(-8 score) and one scan name the bucket that holds the
-//    cut, the few candidates inside it rank themselves one against the other, everything in a better
-//    bucket is taken; one workgroup-wide prefix count hands out positions in pool-index order (of equal
-//    keys the lowest indices first).  A bucket too crowded for that goes through a radix selection over
-//    the order-preserving integer image of the score (four 8-bit digits, one histogram and one barrier
-//    per digit, every wave scanning the 256 bins by itself).
+// Selections ("the n best by (score desc, pool index asc)") never sort.  What bounds the kernel is a chain of dependent
+// instructions, LDS trips and barriers (a lone wave issues one instruction in about eight cycles), not the work in it:
+//  * Levels of up to 256 candidates (k <= 16) are expanded by one wave from start to end, without a barrier.  The worst of the
+//    k parents' best children is a bound that at least k candidates reach; from there the wave bisects the
+//    order-preserving integer image of the scores: a step counts the keys above a scalar by ballots, 5 steps on average.
+//  * Larger levels are scored by all waves, which also collect what lies above that bound (2 to 7 k); one wave cuts the list.
+//  * The rerank over the pool is cut by score buckets: one LDS histogram and one scan name the bucket that holds the
+//    cut, the few candidates inside it rank themselves one against the other, everything in a better bucket is taken.
+//    A pool of more than 1024 is thinned first, by a bound that enough of the threads' best candidates reach.
+//  * A bucket, or a thinned list, that equal scores make too crowded goes through a radix selection over the integer image
+//    (four 8-bit digits, one histogram and one barrier per digit, every wave scanning the 256 bins by itself).
+// Eight waves that shared every level (pairs counted for k <= 11, score buckets beyond), two to five barriers per level, took
+// 11.0 us for (TT, d, k) = (60, 6, 10), 10.9 for (64, 7, 8), 20 for (96, 8, 12) and 30 for the slowest of a batch with k up to
+// 32; this takes 7.7, 6.9, 13.2 and 22.6.
+#include <stddef.h>
+
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -21,14 +25,18 @@ namespace dt {
 
 
 #define DT_P_MAX (DT_K_MAX + (DT_D_MAX - 1) * DT_K_MAX * DT_K_MAX)
-#ifndef TREE_NT
 #define TREE_NT 512               // threads of the workgroup
-#endif
 #define TREE_NW (TREE_NT / 64)    // its waves
-#define COUNT_MAX 128             // largest level ranked by counting (beyond it the bucket cut is faster: measured)
+#define NARROW_K 16               // levels of at most NARROW_K^2 candidates: one wave
+#define LIST_CAP 1024             // most candidates that a thinning may leave
 #define BUCKET_CAP 64             // most candidates of one score bucket that are ranked one against the other
+#define SHARE_MAX 15              // most candidates per thread of a pool, an odd number
 
-__device__ __forceinline__ u32 score_key(float s) { return ord32(s); }
+// order-preserving integer image of a score (ord32; adding zero folds -0 onto +0)
+__device__ __forceinline__ u32 score_key(float s) {
+    const u32 u = __float_as_uint(s + 0.0f);
+    return u ^ ((u32)((int)u >> 31) | 0x80000000u);
+}
 #define KEY_NEG_INF 0x007FFFFFu   // key of -inf: a candidate that does not exist
 
 // x / dv for 0 <= x < 8192 and 1 <= dv <= 1024 with inv = 1.0f / dv (any rounding within two ulp):
@@ -62,21 +70,95 @@ __device__ __forceinline__ Decoded decode(int p, const PoolShape &s) {
     return d;
 }
 
+// An expanded node: score, pool index, and the slots of its ancestors and itself, five bits per level.
+struct __attribute__((aligned(16))) Parent {
+    float score;
+    int index;
+    u64 path;
+};
 struct TreeLds {
-    float score[DT_P_MAX];         // lp of a candidate, then its cumulative score
-    float lp[DT_P_MAX];            // its own log-probability and token, kept for the emission: the
-    int tok[DT_P_MAX];             // kernel then ends without another trip to memory
+    float score[DT_P_MAX];         // cumulative score of a candidate
+    float lp[DT_P_MAX];            // its own log-probability (-inf: does not exist) and token, kept for the
+    int tok[DT_P_MAX];             // emission: the kernel then ends without another trip to memory
     int16_t node[DT_P_MAX];        // node number after the rerank, -1: not kept
     int8_t slot[DT_P_MAX];         // slot in its level's expanded set, -1: not expanded
-    int exp[DT_D_MAX][DT_K_MAX];   // pool index of slot s of level l
-    u32 key[2][COUNT_MAX];         // keys of the level being ranked by counting (levels alternate)
-    int rank[2][COUNT_MAX];        // how many keys of the level lie above each (summed by LDS adds)
+    Parent par[DT_D_MAX][DT_K_MAX + 1];  // slot s of level l; slots without a node, and the last entry: score -inf
     u32 hist[4][256];              // one histogram per radix digit
-    int wtot[TREE_NW];             // per-wave totals of the position scan
+    u32 best[TREE_NT];             // best key of every thread's share of a large pool
     u64 mem[BUCKET_CAP];           // (key, index) of the candidates in the bucket that holds the cut
-    int memn;
+    float list_score[LIST_CAP];    // what a thinning leaves, in pool order
+    int16_t list[LIST_CAP];
+    int16_t sel[DT_TT_MAX];        // the kept candidates, in pool order
+    int wtot[2 * TREE_NW];         // per-wave totals
+    int p_end, n_exp, memn;
 };
 
+// ---- selection inside a wave ---------------------------------------------------------------------------
+// How many of the keys that a wave holds lie above t (uniform).  The compares go to scalar register pairs of their own, four
+// at a time (the compiler's sequence sends each through VCC and waits for it before the next).
+template <int G>
+__device__ __forceinline__ int count_above(const u32 (&key)[G], u32 t) {
+    int c = 0;
+    if constexpr (G % 4 == 0) {
+#pragma unroll
+        for (int q = 0; q < G; q += 4) {
+            u64 m0, m1, m2, m3;
+            asm("v_cmp_lt_u32_e64 %0, %8, %4\n\tv_cmp_lt_u32_e64 %1, %8, %5\n\tv_cmp_lt_u32_e64 %2, %8, %6\n\tv_cmp_lt_u32_e64 %3, %8, %7"
+                : "=&s"(m0), "=&s"(m1), "=&s"(m2), "=&s"(m3)
+                : "v"(key[q]), "v"(key[q + 1]), "v"(key[q + 2]), "v"(key[q + 3]), "s"(t));
+            c += (__popcll(m0) + __popcll(m1)) + (__popcll(m2) + __popcll(m3));
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < G; ++q) c += __popcll(__builtin_amdgcn_ballot_w64(key[q] > t));
+    }
+    return c;
+}
+// The `keep` best of the keys that a wave holds (key q of lane i is candidate i + 64 q), equal keys by ascending candidate;
+// all viable ones if they are fewer.  The caller knows bounds: lo is KEY_NEG_INF or lies below at
+// least `keep` keys, no key lies above hi.  Returns how many were chosen (uniform).
+template <int G>
+__device__ __forceinline__ int wave_select(const u32 (&key)[G], int keep, u32 lo, u32 hi, bool (&chosen)[G]) {
+    int c = count_above<G>(key, lo), equal = 0;  // equal > 0: that many of the keys equal to lo are chosen too
+    if (c > keep) {
+        // more than `keep` above lo, fewer above hi = lo + width
+        u32 width = hi - lo;
+        for (int step = 0; step < (G < 4 ? 7 : 10); ++step) {
+            const u32 half = width >> 1, mid = lo + half;
+            c = count_above<G>(key, mid);
+            width -= half;
+            lo = c >= keep ? mid : lo;
+            if (c == keep) break;
+        }
+        hi = lo + width;
+        // Candidates close together, or equal: from here on a candidate of those in (lo, hi] divides them.
+        while (c != keep) {
+            u32 any = 0u;
+#pragma unroll
+            for (int q = 0; q < G; ++q) any = key[q] > lo && key[q] <= hi ? key[q] : any;
+            const u32 pivot = (u32)__builtin_amdgcn_readlane((int)any, __builtin_ctzll(__builtin_amdgcn_ballot_w64(any != 0u)));
+            c = count_above<G>(key, pivot - 1u);
+            if (c < keep) hi = pivot - 1u;
+            else if (c == keep) lo = pivot - 1u;
+            else {
+                lo = pivot;
+                c = count_above<G>(key, pivot);
+                if (c < keep) { equal = keep - c; c = keep; }
+            }
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < G; ++q) chosen[q] = key[q] > lo;
+    if (equal) {
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+            const u64 eq = __builtin_amdgcn_ballot_w64(key[q] == lo);
+            chosen[q] = chosen[q] || (key[q] == lo && (int)lanes_below(eq) < equal);
+            equal -= min(equal, (int)__popcll(eq));
+        }
+    }
+    return c;
+}
 // ---- radix selection ---------------------------------------------------------------------------------
 // Key of the keep-th best of score[0..n), keep = min(keep_max, #viable): returns keep (uniform), thr and
 // need_eq = how many candidates with key == thr belong to the chosen set.  Whole workgroup; ends
@@ -176,66 +258,288 @@ __device__ __forceinline__ int block_enumerate(const float *score, int n, u32 th
     return (total & 0xFFFF) + min(total >> 16, need_eq);
 }
 
-// Positions of flagged candidates: thread t owns candidates [t C, t C + C) and their flags (bit c of
-// `flags`); f(index, position) for every flagged one, positions counted in ascending index.  Returns
-// the number of flagged candidates (uniform).  Whole workgroup; one barrier inside.
-template <typename F>
-__device__ __forceinline__ int block_positions(int C, u32 flags, TreeLds &S, F f) {
-    const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int own = __popc(flags);
-    const int incl = wave_scan_incl_i32(own);
-    if (lane == 63) S.wtot[w] = incl;
-    __syncthreads();
-    int base = 0, total = 0;
-#pragma unroll
-    for (int v = 0; v < TREE_NW; ++v) {
-        const int t = S.wtot[v];
-        base += v < w ? t : 0;
-        total += t;
+// ---- expansion ---------------------------------------------------------------------------------------
+// Bounds of a level's cut: the best children of k nodes (lane s < k: key `fk` of slot s's, rows descend) are k candidates, so
+// at least k lie above `lo`; none lies above `hi`.
+__device__ __forceinline__ void level_bounds(u32 fk, int k, u32 &lo, u32 &hi) {
+    const bool viable = lane_id() < k && fk > KEY_NEG_INF;
+    u32 x = viable ? fk : 0u, y = viable ? ~fk : 0u;  // the maxima over lanes 0 .. 31 end in lane 31
+#define STEP(CTRL, ROWS)                                          \
+    x = max(x, (u32)dpp_mov<CTRL, ROWS>(0, (int)x));              \
+    y = max(y, (u32)dpp_mov<CTRL, ROWS>(0, (int)y));
+    STEP(0x111, 0xf) STEP(0x112, 0xf) STEP(0x114, 0xf) STEP(0x118, 0xf) STEP(0x142, 0xa)
+#undef STEP
+    hi = (u32)__builtin_amdgcn_readlane((int)x, 31);
+    lo = __popcll(__builtin_amdgcn_ballot_w64(viable)) == k ? ~(u32)__builtin_amdgcn_readlane((int)y, 31) - 1u : KEY_NEG_INF;
+}
+__device__ __forceinline__ void put_parent(TreeLds &S, int l, int pos, float score, int index, u64 above) {
+    Parent pr;
+    pr.score = score;
+    pr.index = index;
+    pr.path = above | (u64)pos << (5 * (l - 1));
+    S.par[l][pos] = pr;
+    S.slot[index] = (int8_t)pos;
+}
+// Level 1, by one wave: every viable candidate is expanded.
+__device__ __forceinline__ int choose_first(TreeLds &S, int k, float sc) {
+    const int lane = lane_id();
+    const u64 m = __builtin_amdgcn_ballot_w64(lane < k && score_key(sc) > KEY_NEG_INF);
+    if ((m >> lane) & 1ull) put_parent(S, 1, (int)lanes_below(m), sc, lane, 0ull);
+    return __popcll(m);
+}
+// What the draft model is handed for its next pass, by one wave: node s of the set chosen at level l.
+__device__ __forceinline__ void emit_level(const TreeArgs &a, const TreeLds &S, int b, int l, int k, int n_exp) {
+    const int lane = lane_id();
+    if (lane < n_exp) {
+        const Parent pr = S.par[l][lane];
+        const Decoded dc = decode(pr.index, pool_shape(k));
+        const int64_t e = (int64_t)b * DT_K_MAX + lane;
+        a.exp_token[e] = S.tok[pr.index];
+        a.exp_parent_slot[e] = l == 1 ? -1 : dc.slot;
+        a.exp_row[e] = 1 + (l - 1) * k + lane;
+        a.exp_pos[e] = (a.prefix_len ? max(a.prefix_len[b], 0) : 0) + l;
+        // draft-side mask over draft rows: the root's row, the rows of the ancestors, its own
+        u64 w0 = 1ull, w1 = 0ull, w2 = 0ull, w3 = 0ull;
+        for (int j = 1; j <= l; ++j) {
+            const int r = 1 + (j - 1) * k + (int)((pr.path >> (5 * (j - 1))) & 31);
+            const u64 bit = 1ull << (r & 63);
+            const int wd = r >> 6;
+            w0 |= wd == 0 ? bit : 0ull; w1 |= wd == 1 ? bit : 0ull;
+            w2 |= wd == 2 ? bit : 0ull; w3 |= wd == 3 ? bit : 0ull;
+        }
+        a.exp_mask[e * 4] = w0; a.exp_mask[e * 4 + 1] = w1;
+        a.exp_mask[e * 4 + 2] = w2; a.exp_mask[e * 4 + 3] = w3;
     }
-    int pos = base + incl - own;
-    for (int c = 0; c < C; ++c)
-        if ((flags >> c) & 1u) f(tid * C + c, pos++);
-    return total;
+    if (lane == 0) { a.n_expand[b] = n_exp; a.state_n_exp[b] = n_exp; }
 }
 
-// The keep_max best of score[0..n) (fewer if fewer are viable), visited in ascending index.  Whole
-// workgroup; the calls of f are followed by a barrier.
+// All levels, by one wave: G candidates per lane, 64 G >= k^2.  Returns the end of the pool (levels computed so far), or -1
+// when only level `xl` was wanted and has been written.  LDS is written and read by this wave alone, in order.
+template <int G>
+__device__ __forceinline__ int levels_narrow(const TreeArgs &a, TreeLds &S, int b, int k, int d, int TT) {
+    const int lane = lane_id(), xl = a.expand_level, kk = k * k;
+    const PoolShape ps = pool_shape(k);
+    int parent[G], at[G];  // of candidate lane + 64 q: its parent's slot, its pool index
+    float own[G];          // of the next level: own log-probabilities, and of slot `lane`'s best child
+    int best_at = k + min(lane, k - 1) * k;
+    float best_own = S.lp[best_at];
+#pragma unroll
+    for (int q = 0; q < G; ++q) {
+        parent[q] = lane + 64 * q < kk ? fdiv(lane + 64 * q, ps.inv_k) : DT_K_MAX;
+        at[q] = k + lane + 64 * q;
+        own[q] = S.lp[at[q]];
+    }
+    if (lane < DT_D_MAX) S.par[lane][DT_K_MAX].score = -INFINITY;
+    const float sc1 = lane < k ? S.lp[lane] : -INFINITY;
+    if (lane < k) S.score[lane] = sc1;
+    // token count of Algorithm 2's expansion loop: the root plus the viable candidates proposed so far
+    int tok_count = 1 + __popcll(__builtin_amdgcn_ballot_w64(sc1 > -INFINITY));
+    const int l_end = xl > 0 ? xl + 1 : d;
+    int l = 1, p_end = k, n_exp = 0;
+    if (l < l_end && !(a.early_stop && tok_count >= TT)) n_exp = choose_first(S, k, sc1);
+    while (n_exp > 0) {
+        if (l == xl) {
+            emit_level(a, S, b, l, k, n_exp);
+            return -1;
+        }
+        // slots beyond the expanded set own no node: their candidates do not exist
+        if (n_exp < k && lane >= n_exp && lane < DT_K_MAX) S.par[l][lane].score = -INFINITY;
+        // level l + 1: score = score[parent] + lp
+        float sc[G];
+        u64 path[G];
+        const float f = S.par[l][min(lane, DT_K_MAX)].score + best_own;
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+            const Parent pr = S.par[l][parent[q]];
+            sc[q] = pr.score + own[q];
+            path[q] = pr.path;
+        }
+#pragma unroll
+        for (int q = 0; q < G; ++q)
+            if (lane + 64 * q < kk) S.score[at[q]] = sc[q];
+        p_end += kk;
+        ++l;
+        if (l == l_end) break;  // the deepest level is not expanded
+        if (a.early_stop) {
+#pragma unroll
+            for (int q = 0; q < G; ++q) tok_count += __popcll(__builtin_amdgcn_ballot_w64(sc[q] > -INFINITY));
+            n_exp = 0;
+            if (tok_count >= TT) break;
+        }
+        // asked for before the choice (past the deepest level: whatever is there)
+        best_at += kk;
+        best_own = S.lp[best_at];
+#pragma unroll
+        for (int q = 0; q < G; ++q) own[q] = S.lp[at[q] + kk];
+        u32 key[G], lo, hi;
+        bool chosen[G];
+#pragma unroll
+        for (int q = 0; q < G; ++q) key[q] = score_key(sc[q]);
+        level_bounds(score_key(f), k, lo, hi);
+        n_exp = wave_select<G>(key, k, lo, hi, chosen);
+        int before = 0;
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+            const u64 m = __builtin_amdgcn_ballot_w64(chosen[q]);
+            const int pos = (int)__builtin_amdgcn_mbcnt_hi((u32)(m >> 32), __builtin_amdgcn_mbcnt_lo((u32)m, (u32)before));
+            if (chosen[q]) put_parent(S, l, pos, sc[q], at[q], path[q]);
+            before += __popcll(m);
+            at[q] += kk;
+        }
+    }
+    if (xl > 0) {  // an earlier level had nothing viable to expand, or the token count ended the expansion
+        if (lane == 0) { a.n_expand[b] = 0; a.state_n_exp[b] = 0; }
+        return -1;
+    }
+    return p_end;
+}
+
+// The k best of n candidates of level l, by one wave; index_at: their pool indices.
+template <int G, typename I>
+__device__ __forceinline__ int choose_wide(TreeLds &S, int l, int lo, int k, int n, u32 lo_key, u32 hi_key, const float *score,
+                                           I index_at) {
+    const int lane = lane_id();
+    const PoolShape ps = pool_shape(k);
+    float sc[G];
+    u32 key[G];
+    bool chosen[G];
+#pragma unroll
+    for (int q = 0; q < G; ++q) {
+        sc[q] = score[min(lane + 64 * q, n - 1)];
+        key[q] = lane + 64 * q < n ? score_key(sc[q]) : 0u;
+    }
+    const int c = wave_select<G>(key, k, lo_key, hi_key, chosen);
+    int before = 0;
+#pragma unroll
+    for (int q = 0; q < G; ++q) {
+        const u64 m = __builtin_amdgcn_ballot_w64(chosen[q]);
+        const int pos = (int)__builtin_amdgcn_mbcnt_hi((u32)(m >> 32), __builtin_amdgcn_mbcnt_lo((u32)m, (u32)before));
+        if (chosen[q]) {
+            const int index = index_at(lane + 64 * q);
+            put_parent(S, l, pos, sc[q], index, S.par[l - 1][fdiv(index - lo, ps.inv_k)].path);
+        }
+        before += __popcll(m);
+    }
+    return c;
+}
+// All levels of more than NARROW_K^2 candidates, by all waves (k^2 <= 2 TREE_NT: two candidates per thread).  As above.
+__device__ __forceinline__ int levels_wide(const TreeArgs &a, TreeLds &S, int b, int k, int d, int TT) {
+    const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int xl = a.expand_level, kk = k * k;
+    const PoolShape ps = pool_shape(k);
+    int parent[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) parent[q] = tid + TREE_NT * q < kk ? fdiv(tid + TREE_NT * q, ps.inv_k) : DT_K_MAX;
+    if (tid < DT_D_MAX) S.par[tid][DT_K_MAX].score = -INFINITY;
+    const float sc1 = lane < k ? S.lp[lane] : -INFINITY;
+    if (tid < k) S.score[tid] = sc1;
+    int tok_count = 1 + __popcll(__builtin_amdgcn_ballot_w64(sc1 > -INFINITY));
+    u32 lo_key = KEY_NEG_INF, hi_key = 0u;
+    int lo = 0, p_end = k, c = 0;
+    const int l_end = xl > 0 ? xl + 1 : d;
+    for (int l = 1; l < l_end; ++l) {
+        if (a.early_stop && tok_count >= TT) break;  // uniform
+        const int nlo = k + (l - 1) * kk;
+        float first = -INFINITY, own[2] = {0.f, 0.f};
+        if (l != xl) {
+            first = S.lp[nlo + min(lane, k - 1) * k];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) own[q] = S.lp[nlo + min(tid + TREE_NT * q, kk - 1)];
+        }
+        if (w == 0) {
+            int n;
+            if (l == 1) n = choose_first(S, k, sc1);
+            else if (c == 0) n = 0;
+            else if (c <= 256)
+                n = choose_wide<4>(S, l, lo, k, c, lo_key, hi_key, S.list_score, [&](int i) { return (int)S.list[i]; });
+            else if (c <= 512)
+                n = choose_wide<8>(S, l, lo, k, c, lo_key, hi_key, S.list_score, [&](int i) { return (int)S.list[i]; });
+            else  // equal scores
+                n = choose_wide<16>(S, l, lo, k, kk, lo_key, hi_key, S.score + lo, [&](int i) { return lo + i; });
+            if (lane >= n && lane < DT_K_MAX) S.par[l][lane].score = -INFINITY;
+            if (lane == 0) S.n_exp = n;
+            if (l == xl) emit_level(a, S, b, l, k, n);
+        }
+        if (l == xl) return -1;
+        __syncthreads();
+        if (S.n_exp == 0) break;
+        // every wave: the bound; two candidates per thread scored; those above it into the list
+        const float f = S.par[l][min(lane, DT_K_MAX)].score + first;
+        float sc[2];
+        u32 key[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) sc[q] = S.par[l][parent[q]].score + own[q];
+        level_bounds(score_key(f), k, lo_key, hi_key);
+        u64 m[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            key[q] = score_key(sc[q]);
+            if (tid + TREE_NT * q < kk) S.score[nlo + tid + TREE_NT * q] = sc[q];
+            m[q] = __builtin_amdgcn_ballot_w64(key[q] > lo_key);
+        }
+        if (lane == 0) {
+            S.wtot[w] = __popcll(m[0]);
+            S.wtot[TREE_NW + w] = __popcll(m[1]);
+        }
+        if (a.early_stop) tok_count += __syncthreads_count(sc[0] > -INFINITY) + __syncthreads_count(sc[1] > -INFINITY);
+        else __syncthreads();
+        const int wt = S.wtot[lane & (2 * TREE_NW - 1)], upto = wave_scan_incl_i32(wt);  // lanes 0 .. 15
+        const int at[2] = {__builtin_amdgcn_readlane(upto - wt, w), __builtin_amdgcn_readlane(upto - wt, TREE_NW + w)};
+        c = __builtin_amdgcn_readlane(upto, 2 * TREE_NW - 1);
+        if (c <= 512)
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                if (key[q] > lo_key) {
+                    const int i = at[q] + (int)lanes_below(m[q]);
+                    S.list_score[i] = sc[q];
+                    S.list[i] = (int16_t)(nlo + tid + TREE_NT * q);
+                }
+        __syncthreads();
+        lo = nlo;
+        p_end = nlo + kk;
+    }
+    if (xl > 0) {
+        if (tid == 0) { a.n_expand[b] = 0; a.state_n_exp[b] = 0; }
+        return -1;
+    }
+    return p_end;
+}
+
+// ---- rerank ---------------------------------------------------------------------------------------------
+// 64 keys reach the worst of the lanes' best ones, 128 the worst of their second best (keep < 128).
+template <int G>
+__device__ __forceinline__ void lane_bounds(const u32 (&key)[G], int keep, u32 &lo, u32 &hi) {
+    u32 m1 = 0u, m2 = 0u;
+#pragma unroll
+    for (int q = 0; q < G; ++q) {
+        m2 = max(m2, min(m1, key[q]));
+        m1 = max(m1, key[q]);
+    }
+    const u32 bound = ~wave_max_u32(~(keep <= 64 ? m1 : m2));
+    lo = bound > KEY_NEG_INF ? bound - 1u : KEY_NEG_INF;
+    hi = wave_max_u32(m1);
+}
+// The keep_max best of score[0..n) (fewer if fewer are viable), f(index, position) in ascending index.  Whole workgroup,
+// n <= CT TREE_NT, hist[0], mem and memn cleared.
 //
-// Scores are log-probabilities, so floor(-8 score), capped at 255, spreads them over buckets that are
-// ordered like the scores.  One histogram and one scan name the bucket that holds the cut; the few
+// floor(scale (top - score)), kept within 0 .. 255, spreads the scores over buckets that are
+// ordered like them.  One histogram and one scan name the bucket that holds the cut; the few
 // candidates inside it are ranked one against the other by (key desc, index asc), everything in a better
-// bucket is taken.  A bucket with more than BUCKET_CAP candidates (many equal scores, or scores below
-// -32) goes through the radix selection instead.  CT: candidates per thread when known at compile time
-// (their scores then stay in registers), 0: any number up to 32.
+// bucket is taken.  A bucket with more than BUCKET_CAP candidates (many equal scores, or the last one)
+// goes through the radix selection instead.
 // (clamped as a float first: converting a float beyond the int range would be undefined)
-__device__ __forceinline__ int score_bucket(float sc) { return max((int)fminf(sc * -8.0f, 255.0f), 0); }
 __device__ __forceinline__ u64 member_key(u32 key, int i) { return ((u64)key << 32) | (u32)(0x7FFFFFFF - i); }
 
 template <int CT, typename F>
-__device__ __forceinline__ int block_select_t(const float *score, int n, int keep_max, TreeLds &S, F f) {
-    const int tid = threadIdx.x, lane = lane_id();
-    const int C = CT > 0 ? CT : (n + TREE_NT - 1) / TREE_NT;  // consecutive candidates per thread
-    constexpr int CR = CT > 0 ? CT : 1;
-    float sc[CR];
-    if (tid < 256) S.hist[0][tid] = 0u;
-    if (tid < BUCKET_CAP) S.mem[tid] = 0ull;
-    if (tid == 0) S.memn = 0;
-    __syncthreads();
-    if (CT > 0) {
+__device__ __forceinline__ int block_select(const float *score, int n, float top, float scale, int keep_max, TreeLds &S, F f) {
+    auto score_bucket = [&](float s) { return (int)fmaxf(fminf((top - s) * scale, 255.0f), 0.0f); };
+    const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    float sc[CT];
 #pragma unroll
-        for (int c = 0; c < CR; ++c) sc[c] = score[min(tid * CT + c, n - 1)];
-#pragma unroll
-        for (int c = 0; c < CR; ++c) {
-            if (tid * CT + c >= n) sc[c] = -INFINITY;
-            if (sc[c] > -INFINITY) atomicAdd(&S.hist[0][score_bucket(sc[c])], 1u);
-        }
-    } else {
-        for (int c = 0; c < C; ++c) {
-            const int i = tid * C + c;
-            const float v = score[min(i, n - 1)];
-            if (i < n && v > -INFINITY) atomicAdd(&S.hist[0][score_bucket(v)], 1u);
-        }
+    for (int c = 0; c < CT; ++c) {
+        const float v = score[min(tid * CT + c, n - 1)];
+        sc[c] = tid * CT + c < n ? v : -INFINITY;
+        if (sc[c] > -INFINITY) atomicAdd(&S.hist[0][score_bucket(sc[c])], 1u);
     }
     __syncthreads();
     // every wave: lane L holds buckets 4L .. 4L+3, best scores first
@@ -262,164 +566,83 @@ __device__ __forceinline__ int block_select_t(const float *score, int n, int kee
     const int B = 4 * ls + dg;
     const int need = keep - above;  // how many of bucket B belong to the set: 1 .. hB
     if (hB > BUCKET_CAP) {
+        __syncthreads();  // the histogram has been read
         u32 thr;
         int need_eq;
         if (block_radix_cut(score, n, keep_max, S, thr, need_eq) <= 0) return 0;
-        const int taken = block_enumerate(score, n, thr, need_eq, S, f);
-        __syncthreads();
-        return taken;
+        return block_enumerate(score, n, thr, need_eq, S, f);
     }
-    // flags of the candidates in better buckets, and of those in bucket B
-    u32 sure = 0u, inb = 0u;
-    if (CT > 0) {
+    // the candidates in better buckets, and those in bucket B
+    bool sure[CT], inb[CT];
 #pragma unroll
-        for (int c = 0; c < CR; ++c) {
-            const int bk = score_bucket(sc[c]);
-            const bool ok = sc[c] > -INFINITY;
-            sure |= (ok && bk < B ? 1u : 0u) << c;
-            inb |= (ok && bk == B ? 1u : 0u) << c;
-        }
-    } else {
-        for (int c = 0; c < C; ++c) {
-            const int i = tid * C + c;
-            const float v = score[min(i, n - 1)];
-            const int bk = score_bucket(v);
-            const bool ok = i < n && v > -INFINITY;
-            sure |= (ok && bk < B ? 1u : 0u) << c;
-            inb |= (ok && bk == B ? 1u : 0u) << c;
-        }
+    for (int c = 0; c < CT; ++c) {
+        const int bk = score_bucket(sc[c]);
+        sure[c] = sc[c] > -INFINITY && bk < B;
+        inb[c] = sc[c] > -INFINITY && bk == B;
     }
     if (need < hB) {  // the cut runs through bucket B: its members rank themselves
-        auto key_of = [&](int c) { return member_key(score_key(CT > 0 ? sc[CT > 0 ? c : 0] : score[tid * C + c]), tid * C + c); };
-        if (CT > 0) {
 #pragma unroll
-            for (int c = 0; c < CR; ++c)
-                if ((inb >> c) & 1u) S.mem[atomicAdd(&S.memn, 1)] = key_of(c);
-        } else {
-            for (int c = 0; c < C; ++c)
-                if ((inb >> c) & 1u) S.mem[atomicAdd(&S.memn, 1)] = key_of(c);
-        }
+        for (int c = 0; c < CT; ++c)
+            if (inb[c]) S.mem[atomicAdd(&S.memn, 1)] = member_key(score_key(sc[c]), tid * CT + c);
         __syncthreads();
-        if (inb) {
-            // entries past the hB members are zero and rank below every member
-            auto rank_of = [&](u64 mine) {
-                int rank = 0;
-                for (int j0 = 0; j0 < hB; j0 += 8) {
-                    u64 o[8];
+        bool any = false;
+        u64 mine[CT];
+        int rank[CT];
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) o[j] = S.mem[j0 + j];
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) rank += o[j] > mine ? 1 : 0;
-                }
-                return rank;
-            };
-            if (CT > 0) {
-#pragma unroll
-                for (int c = 0; c < CR; ++c)
-                    if (((inb >> c) & 1u) && rank_of(key_of(c)) < need) sure |= 1u << c;
-            } else {
-                for (int c = 0; c < C; ++c)
-                    if (((inb >> c) & 1u) && rank_of(key_of(c)) < need) sure |= 1u << c;
-            }
+        for (int c = 0; c < CT; ++c) {
+            any = any || inb[c];
+            mine[c] = member_key(score_key(sc[c]), tid * CT + c);
+            rank[c] = 0;
         }
+        if (any)
+            for (int j0 = 0; j0 < hB; j0 += 8) {  // entries past the hB members are zero and rank below every member
+                u64 o[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) o[j] = S.mem[j0 + j];
+#pragma unroll
+                for (int c = 0; c < CT; ++c)
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) rank[c] += o[j] > mine[c] ? 1 : 0;
+            }
+#pragma unroll
+        for (int c = 0; c < CT; ++c) sure[c] = sure[c] || (inb[c] && rank[c] < need);
     } else {
-        sure |= inb;
+#pragma unroll
+        for (int c = 0; c < CT; ++c) sure[c] = sure[c] || inb[c];
     }
-    const int taken = block_positions(C, sure, S, f);
+    // positions in ascending index
+    int below = 0, own = 0;
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+        const u64 m = __builtin_amdgcn_ballot_w64(sure[c]);
+        below += (int)lanes_below(m);
+        own += __popcll(m);
+    }
+    if (lane == 0) S.wtot[w] = own;
     __syncthreads();
-    return taken;
-}
-template <typename F>
-__device__ __forceinline__ int block_select(const float *score, int n, int keep_max, TreeLds &S, F f) {
-    if (n <= TREE_NT) return block_select_t<1>(score, n, keep_max, S, f);
-    if (n <= 2 * TREE_NT) return block_select_t<2>(score, n, keep_max, S, f);
-    return block_select_t<0>(score, n, keep_max, S, f);
-}
-
-// c_i += (o_i > mine) for the four keys of o.  Written out so that the four compares go to four scalar
-// register pairs and the four adds-with-carry follow them: no result is needed by the next instruction,
-// where the compiler's own sequence (compare into VCC, add from VCC) waits on every pair.
-__device__ __forceinline__ void count_above4(const uint4 o, u32 mine, int &c0, int &c1, int &c2, int &c3) {
-    u64 m0, m1, m2, m3;
-    asm(
-        "v_cmp_gt_u32_e64 %[m0], %[ox], %[mine]\n\t"
-        "v_cmp_gt_u32_e64 %[m1], %[oy], %[mine]\n\t"
-        "v_cmp_gt_u32_e64 %[m2], %[oz], %[mine]\n\t"
-        "v_cmp_gt_u32_e64 %[m3], %[ow], %[mine]\n\t"
-        "v_addc_co_u32_e64 %[c0], %[m0], 0, %[c0], %[m0]\n\t"
-        "v_addc_co_u32_e64 %[c1], %[m1], 0, %[c1], %[m1]\n\t"
-        "v_addc_co_u32_e64 %[c2], %[m2], 0, %[c2], %[m2]\n\t"
-        "v_addc_co_u32_e64 %[c3], %[m3], 0, %[c3], %[m3]\n\t"
-        : [c0] "+v"(c0), [c1] "+v"(c1), [c2] "+v"(c2), [c3] "+v"(c3), [m0] "=&s"(m0), [m1] "=&s"(m1),
-          [m2] "=&s"(m2), [m3] "=&s"(m3)
-        : [ox] "v"(o.x), [oy] "v"(o.y), [oz] "v"(o.z), [ow] "v"(o.w), [mine] "v"(mine));
-}
-
-// ---- ranking a level by counting ---------------------------------------------------------------------
-// key[0 .. 64 G) holds the keys of the level's n candidates (zero beyond n), G = ceil(n / 64) <= 2, and
-// rank[0 .. 64 G) is zero.  Wave w counts, for the 64 candidates of group w % G, the keys above
-// theirs within slice w / G of the level, and adds that to their rank.  Ties are counted as "not above",
-// so candidates of equal key share a rank; the caller detects a tie that straddles the cut by the size
-// of the chosen set.
-template <int G>
-__device__ __forceinline__ void level_count(const u32 *key, int *rank) {
-    static_assert(G == 1 || G == 2, "groups of 64 candidates");
-    constexpr int H = G == 1 ? TREE_NW : TREE_NW / 2;  // slices
-    constexpr int PER = 64 * G / H;                                           // keys per slice (padding included)
-    const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (w < G * H) {
-        const int g = w % G, h = w / G;
-        const u32 mine = key[g * 64 + lane];
-        const uint4 *other = (const uint4 *)&key[h * PER];
-        int c0 = 0, c1 = 0, c2 = 0, c3 = 0;
+    int pos = below, total = 0;
 #pragma unroll
-        for (int j = 0; j < PER / 4; ++j) count_above4(other[j], mine, c0, c1, c2, c3);
-        atomicAdd(&rank[g * 64 + lane], (c0 + c1) + (c2 + c3));
-    }
-}
-// Every wave by itself, after the barrier that follows level_count: the chosen set of the level (rank
-// below k among the viable candidates; all of them when n <= k, rank then is not read), positions in
-// ascending index.  Returns the size of the set, or -1 when equal keys straddle the cut (nothing has
-// been written then).  f(index, position) is called by every wave for every chosen candidate.
-template <int G, typename F>
-__device__ __forceinline__ int level_choose(const u32 *key, const int *rank, int n, int k, F f) {
-    const int lane = lane_id();
-    u64 m[G];
-    int chosen = 0, viable = 0;
-    u32 ky[G];
-    int rk[G];
-#pragma unroll
-    for (int q = 0; q < G; ++q) {  // all loads first
-        ky[q] = key[q * 64 + lane];
-        rk[q] = n <= k ? 0 : rank[q * 64 + lane];
+    for (int v = 0; v < TREE_NW; ++v) {
+        const int t = S.wtot[v];
+        pos += v < w ? t : 0;
+        total += t;
     }
 #pragma unroll
-    for (int q = 0; q < G; ++q) {
-        const bool ok = ky[q] > KEY_NEG_INF;
-        m[q] = __builtin_amdgcn_ballot_w64(ok && rk[q] < k);
-        viable += __popcll(__builtin_amdgcn_ballot_w64(ok));
-        chosen += __popcll(m[q]);
-    }
-    if (chosen != min(k, viable)) return -1;
-    int before = 0;
-#pragma unroll
-    for (int q = 0; q < G; ++q) {
-        if ((m[q] >> lane) & 1ull) f(q * 64 + lane, before + (int)lanes_below(m[q]));
-        before += __popcll(m[q]);
-    }
-    return chosen;
+    for (int c = 0; c < CT; ++c)
+        if (sure[c]) f(tid * CT + c, pos++);
+    return total;
 }
 
 __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
     const int b = blockIdx.x, tid = threadIdx.x;
     // Row results of sequence b: rows b * seq_rows .. (the same block layout for the one-shot build and
     // the level-at-a-time state), so nothing about them depends on the sequence's parameters.  The first
-    // 64 rows are requested before the parameters have arrived: one trip to memory instead of two.
+    // 96 rows are requested before the parameters have arrived: one trip to memory instead of two.
     const int64_t r0 = (int64_t)b * a.seq_rows;
     const float *tv = a.top_val + r0 * DT_K_MAX;
     const int32_t *ti = a.top_id + r0 * DT_K_MAX;
     const float *lse = a.lse + r0;
-    constexpr int EARLY = 4;  // entries per thread read ahead: rows 0 .. EARLY * TREE_NT / DT_K_MAX - 1
+    constexpr int EARLY = 6;  // entries per thread read ahead: rows 0 .. EARLY * TREE_NT / DT_K_MAX - 1
     float ev[EARLY], el[EARLY];
     int et[EARLY];
 #pragma unroll
@@ -429,6 +652,14 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
         et[j] = ti[e];
         el[j] = lse[e / DT_K_MAX];
     }
+    extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];  // 135 KB: more than a static array may hold
+    TreeLds &S = *reinterpret_cast<TreeLds *>(s_dyn);
+    static_assert(DT_P_MAX % 16 == 0 && offsetof(TreeLds, node) % 16 == 0 && offsetof(TreeLds, slot) % 16 == 0, "16-byte stores");
+    for (int i = tid; i < DT_P_MAX / 8; i += TREE_NT) ((uint4 *)S.node)[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
+    for (int i = tid; i < DT_P_MAX / 16; i += TREE_NT) ((uint4 *)S.slot)[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
+    if (tid < 256) S.hist[0][tid] = 0u;
+    if (tid < BUCKET_CAP) S.mem[tid] = 0ull;
+    if (tid == 0) S.memn = 0;
     const dt_params prm = a.params[b];
     // one-shot build: rows past the span the sequence owns were never reduced; they count as rows
     // without a viable token (the level-at-a-time state has no such span: its rows arrive level by level)
@@ -437,11 +668,6 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
     const int k = min(max(prm.k, 1), min(DT_K_MAX, a.V));
     const int xl = a.expand_level;  // > 0: only the nodes of level xl that are expanded next
     const int64_t o = (int64_t)b * a.TT_cap;
-    const PoolShape ps = pool_shape(k);
-    const int kk = k * k;
-
-    extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];  // 116 KB: more than a static array may hold
-    TreeLds &S = *reinterpret_cast<TreeLds *>(s_dyn);
 
     if (xl > 0 && (TT == 1 || xl >= d)) {  // nothing is drafted below level d
         if (tid == 0) { a.n_expand[b] = 0; a.state_n_exp[b] = 0; }
@@ -463,8 +689,7 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
     }
     // Candidates through level d, or through level xl when only that level's choice is wanted (the
     // rows of deeper levels do not exist yet).  Every candidate's own log-probability is known up front: the draft row that would
-    // produce pool index p is fixed by p alone (only its parent is decided later).  Park
-    // lp in the score array; the level loop turns it into the cumulative score in place.
+    // produce pool index p is fixed by p alone (only its parent is decided later).
     // Entry (row, rank) with rank < k is candidate p = rank (row 0) or k + (row - 1) k + rank.
     const int R = xl > 0 ? 1 + (xl - 1) * k : 1 + (d - 1) * k;  // rows that hold candidates
     const int owned = (int)min(max(span, (int64_t)0), (int64_t)DT_STATE_ROWS);
@@ -472,144 +697,164 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
         const int row = e / DT_K_MAX, rank = e % DT_K_MAX;
         if (row < R && rank < k) {
             const int p = row == 0 ? rank : k + (row - 1) * k + rank;
-            const float own = v - row_lse;
-            const float lp = v > -INFINITY && row < owned ? own : -INFINITY;
-            S.score[p] = lp;
-            S.lp[p] = own;
+            S.lp[p] = v > -INFINITY && row < owned ? v - row_lse : -INFINITY;
             S.tok[p] = token;
-            S.node[p] = -1;
-            S.slot[p] = -1;
-            if (row == 0) S.key[1][p] = score_key(lp);  // level 1 is chosen first
         }
     };
 #pragma unroll
     for (int j = 0; j < EARLY; ++j) place(tid + j * TREE_NT, ev[j], et[j], el[j]);
-    for (int e = tid + EARLY * TREE_NT; e < R * DT_K_MAX; e += TREE_NT) place(e, tv[e], ti[e], lse[e / DT_K_MAX]);
-    if (tid < 64 && tid >= k) S.key[1][tid] = 0u;
-    for (int t = tid; t < COUNT_MAX; t += TREE_NT) S.rank[0][t] = 0;
+    // the other rows in one more trip
+    constexpr int MORE = (DT_STATE_ROWS * DT_K_MAX + TREE_NT - 1) / TREE_NT - EARLY;
+    const int more = (R * DT_K_MAX + TREE_NT - 1) / TREE_NT - EARLY;
+    if (more > 0) {
+        float xv[MORE], xs[MORE];
+        int xt[MORE];
+#pragma unroll
+        for (int j = 0; j < MORE; ++j)
+            if (j < more) {
+                const int e = min(tid + (EARLY + j) * TREE_NT, R * DT_K_MAX - 1);
+                xv[j] = tv[e];
+                xt[j] = ti[e];
+                xs[j] = lse[e / DT_K_MAX];
+            }
+#pragma unroll
+        for (int j = 0; j < MORE; ++j)
+            if (j < more) place(tid + (EARLY + j) * TREE_NT, xv[j], xt[j], xs[j]);
+    }
     __syncthreads();
 
-    // ---- expansion, level by level -----------------------------------------------------------
-    int p_end = k;  // pool indices below p_end hold real scores (levels computed so far)
-    const int l_end = xl > 0 ? xl + 1 : d;
-    // token count of Algorithm 2's expansion loop: the root plus the viable candidates proposed so far
-    int tok_count = a.early_stop ? 1 + __syncthreads_count(tid < k && S.score[tid] > -INFINITY) : 0;
-    for (int l = 1; l < l_end; ++l) {
-        if (a.early_stop && tok_count >= TT) break;  // uniform: no further level is expanded
-        const int lo = l == 1 ? 0 : k + (l - 2) * kk;
-        const int n = l == 1 ? k : kk;
-        int *exp_l = S.exp[l];
-        auto put = [&](int i, int pos) {
-            exp_l[pos] = lo + i;
-            S.slot[lo + i] = (int8_t)pos;
-        };
-        int n_exp = -1;
-        if (n <= COUNT_MAX) {
-            // (after the barrier that published the keys) count, publish the ranks, choose in every wave
-            const u32 *key = S.key[l & 1];
-            int *rank = S.rank[l & 1];
-            const int G = (n + 63) >> 6;
-            if (n > k) {  // otherwise every viable candidate is chosen
-                if (G == 1) level_count<1>(key, rank);
-                else level_count<2>(key, rank);
-                __syncthreads();
-            }
-            if (G == 1) n_exp = level_choose<1>(key, rank, n, k, put);
-            else n_exp = level_choose<2>(key, rank, n, k, put);
+    // ---- expansion -------------------------------------------------------------------------------
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = lane_id();
+    int p_end = 0;
+    if (k > NARROW_K) {
+        p_end = levels_wide(a, S, b, k, d, TT);
+        if (xl > 0) return;
+        __syncthreads();  // the levels may have ended without one
+    } else {
+        if (w == 0) {
+            if (k <= 8) p_end = levels_narrow<1>(a, S, b, k, d, TT);
+            else if (k <= 11) p_end = levels_narrow<2>(a, S, b, k, d, TT);
+            else p_end = levels_narrow<4>(a, S, b, k, d, TT);
+            if (lane == 0) S.p_end = p_end;
         }
-        if (n_exp < 0) n_exp = block_select(S.score + lo, n, k, S, put);
-        if (l == xl) {
-            // ---- what the draft model is handed for its next pass: node s of the chosen set ----------
-            if (tid < n_exp) {
-                const int pi = exp_l[tid];
-                const Decoded dc = decode(pi, ps);
-                const int64_t e = (int64_t)b * DT_K_MAX + tid;
-                a.exp_token[e] = S.tok[pi];
-                a.exp_parent_slot[e] = l == 1 ? -1 : dc.slot;
-                const int own = 1 + (l - 1) * k + tid;
-                a.exp_row[e] = own;
-                a.exp_pos[e] = (a.prefix_len ? max(a.prefix_len[b], 0) : 0) + l;
-                // draft-side mask over draft rows: the root's row, the rows of the ancestors, its own
-                u64 m0 = 1ull, m1 = 0ull, m2 = 0ull, m3 = 0ull;
-                auto set = [&](int r) {
-                    const u64 bit = 1ull << (r & 63);
-                    const int wd = r >> 6;
-                    m0 |= wd == 0 ? bit : 0ull; m1 |= wd == 1 ? bit : 0ull;
-                    m2 |= wd == 2 ? bit : 0ull; m3 |= wd == 3 ? bit : 0ull;
-                };
-                set(own);
-                // the slot of an expanded candidate is read from S.exp, which every wave wrote for itself
-                int lv = l, sl = dc.slot;  // level of the current node, slot of its parent
-                for (int guard = 0; guard < DT_D_MAX && lv > 1; ++guard) {
-                    set(1 + (lv - 2) * k + sl);
-                    const Decoded dp = decode(S.exp[lv - 1][sl], ps);
-                    --lv;
-                    sl = dp.slot;
-                }
-                a.exp_mask[e * 4] = m0; a.exp_mask[e * 4 + 1] = m1;
-                a.exp_mask[e * 4 + 2] = m2; a.exp_mask[e * 4 + 3] = m3;
-            }
-            if (tid == 0) { a.n_expand[b] = n_exp; a.state_n_exp[b] = n_exp; }
-            return;
-        }
-        if (n_exp == 0) break;
-        // next level: score = score[parent] + lp, and the keys for its ranking.  exp_l is read by the
-        // wave that wrote it (every wave writes the whole set) or after block_select's barrier.
-        const int nlo = k + (l - 1) * kk;
-        const int npad = kk <= COUNT_MAX ? ((kk + 63) & ~63) : kk;
-        int fresh = 0;  // viable candidates this thread has just scored (at most two: kk <= 2 TREE_NT)
-        for (int t = tid; t < npad; t += TREE_NT) {
-            const int tc = min(t, kk - 1);
-            const int s = fdiv(tc, ps.inv_k);
-            // slots beyond the expanded set own no node: their candidates do not exist
-            const float par = S.score[exp_l[min(s, n_exp - 1)]], own = S.score[nlo + tc];
-            const float sc = s < n_exp ? par + own : -INFINITY;
-            if (t < kk) S.score[nlo + t] = sc;
-            fresh += t < kk && sc > -INFINITY;
-            if (kk <= COUNT_MAX) {  // the other pair of arrays: slower waves may still be choosing from this level's
-                S.key[(l + 1) & 1][t] = t < kk ? score_key(sc) : 0u;
-                S.rank[(l + 1) & 1][t] = 0;
-            }
-        }
-        p_end = nlo + kk;
-        if (a.early_stop) tok_count += __syncthreads_count(fresh >= 1) + __syncthreads_count(fresh >= 2);
-        else __syncthreads();
+        if (xl > 0) return;
+        __syncthreads();
+        p_end = S.p_end;
     }
-
-    if (xl > 0) {  // an earlier level had nothing viable to expand, or the token count ended the expansion
-        if (tid == 0) { a.n_expand[b] = 0; a.state_n_exp[b] = 0; }
-        return;
-    }
-    __syncthreads();  // the level loop may have been left right after a wave-local choice
 
     // ---- rerank: the TT-1 best of the whole pool ----------------------------------------------
-    const int keep = block_select(S.score, p_end, TT - 1, S, [&](int i, int pos) { S.node[i] = (int16_t)(pos + 1); });
+    auto kept = [&](int i, int pos) {
+        S.node[i] = (int16_t)(pos + 1);
+        S.sel[pos] = (int16_t)i;
+    };
+    // 256 buckets over the best 32 or 16 nats: the larger the pool, the closer to its top the cut
+    const float scale = p_end <= 256 ? 8.0f : 16.0f;
+    int keep;
+    if (p_end <= TREE_NT) {
+        keep = block_select<1>(S.score, p_end, S.score[0], scale, TT - 1, S, kept);
+    } else if (p_end <= 2 * TREE_NT) {
+        keep = block_select<2>(S.score, p_end, S.score[0], scale, TT - 1, S, kept);
+    } else {
+        // the threads' best ones, each of candidates TREE_NT apart (the children of one node are neighbours)
+        u32 best = 0u;
+#pragma unroll
+        for (int c = 0; c < SHARE_MAX; ++c) {
+            const int i = tid + TREE_NT * c;
+            const u32 kv = score_key(S.score[min(i, p_end - 1)]);
+            best = max(best, i < p_end ? kv : 0u);
+        }
+        S.best[tid] = best;
+        __syncthreads();
+        // every wave by itself: a bound that TT - 1 of them reach, and not many more
+        u32 bk[TREE_NW], lo, hi;
+#pragma unroll
+        for (int q = 0; q < TREE_NW; ++q) bk[q] = S.best[64 * q + lane];
+        lane_bounds<TREE_NW>(bk, TT - 1, lo, hi);
+        int n = count_above<TREE_NW>(bk, lo);
+        while (n > 320 && hi - lo > 1u) {
+            const u32 mid = lo + ((hi - lo) >> 1);
+            const int nm = count_above<TREE_NW>(bk, mid);
+            if (nm >= TT - 1) { lo = mid; n = nm; }
+            else hi = mid;
+        }
+        // What lies above, in pool order: consecutive candidates per thread, an odd number of them (64 lanes then read 64 banks).
+        const int C = ((p_end + TREE_NT - 1) / TREE_NT) | 1;
+        u32 over = 0u;
+#pragma unroll
+        for (int c = 0; c < SHARE_MAX; ++c) {
+            const float v = S.score[min(tid * C + c, p_end - 1)];
+            over |= (c < C && tid * C + c < p_end && score_key(v) > lo ? 1u : 0u) << c;
+        }
+        const int own = __popc(over), incl = wave_scan_incl_i32(own);
+        if (lane == 63) S.wtot[w] = incl;
+        __syncthreads();
+        int at = incl - own, total = 0;
+#pragma unroll
+        for (int v = 0; v < TREE_NW; ++v) {
+            const int nv = S.wtot[v];
+            at += v < w ? nv : 0;
+            total += nv;
+        }
+        if (total <= LIST_CAP) {  // uniform
+            for (; over; over &= over - 1u) {
+                const int i = tid * C + __builtin_ctz(over);
+                S.list_score[at] = S.score[i];
+                S.list[at] = (int16_t)i;
+                ++at;
+            }
+            __syncthreads();
+            auto kept_of_list = [&](int i, int pos) { kept(S.list[i], pos); };
+            const float top = S.score[0], range = top - (lo > KEY_NEG_INF ? unord32(lo) : top - 32.0f);
+            const float fit = range > 0.0f ? 255.0f / range : 8.0f;
+            if (total <= TREE_NT) keep = total == 0 ? 0 : block_select<1>(S.list_score, total, top, fit, TT - 1, S, kept_of_list);
+            else keep = block_select<2>(S.list_score, total, top, fit, TT - 1, S, kept_of_list);
+        } else {  // equal scores
+            __syncthreads();  // wtot has been read
+            u32 thr;
+            int need_eq;
+            keep = block_radix_cut(S.score, p_end, TT - 1, S, thr, need_eq);
+            if (keep > 0) keep = block_enumerate(S.score, p_end, thr, need_eq, S, kept);
+        }
+    }
+    __syncthreads();
     if (tid == 0) a.n_nodes[b] = keep + 1;
 
     // ---- emission -------------------------------------------------------------------------------
-    for (int p = tid; p < p_end; p += TREE_NT) {
-        const int n = S.node[p];
-        if (n < 0) continue;
-        const Decoded dc = decode(p, ps);
-        int par_pool = dc.level == 1 ? -1 : S.exp[dc.level - 1][dc.slot];
+    // (a wave issues one instruction in eight cycles at best, two waves twice as many: two threads per node)
+    const int t = tid & (DT_TT_MAX - 1);
+    if (t >= keep || tid >= 2 * DT_TT_MAX) return;
+    const int p = S.sel[t], n = t + 1;
+    const Decoded dc = decode(p, pool_shape(k));
+    if (tid >= DT_TT_MAX) {
+        const int slot = S.slot[p];
         a.tokens[o + n] = S.tok[p];
-        a.parents[o + n] = par_pool < 0 ? 0 : max((int)S.node[par_pool], 0);
         a.depth[o + n] = dc.level;
         a.score[o + n] = S.score[p];
         a.logp[o + n] = S.lp[p];
-        a.src_row[o + n] = S.slot[p] >= 0 ? 1 + (dc.level - 1) * k + S.slot[p] : -1;
-        u64 m0 = 1ull, m1 = 0ull;  // the root
-        int nn = n, pp = par_pool;
-        for (int guard = 0; guard <= DT_D_MAX; ++guard) {
-            if (nn < 64) m0 |= 1ull << nn; else m1 |= 1ull << (nn - 64);
-            if (pp < 0) break;
-            nn = max((int)S.node[pp], 0);
-            const Decoded dp = decode(pp, ps);
-            pp = dp.level == 1 ? -1 : S.exp[dp.level - 1][dp.slot];
-        }
-        a.anc_mask[(o + n) * DT_MASK_WORDS] = m0;
-        a.anc_mask[(o + n) * DT_MASK_WORDS + 1] = m1;
+        a.src_row[o + n] = slot >= 0 ? 1 + (dc.level - 1) * k + slot : -1;
+        return;
     }
+    // the ancestors: their slots stand in the parent's path
+    const u64 path = dc.level > 1 ? S.par[dc.level - 1][dc.slot].path : 0ull;
+    int up[DT_D_MAX - 1], parent = 0;
+#pragma unroll
+    for (int j = 1; j < DT_D_MAX; ++j) {
+        const int index = S.par[j][(path >> (5 * (j - 1))) & 31].index;
+        up[j - 1] = j < dc.level ? index : 0;
+    }
+#pragma unroll
+    for (int j = 1; j < DT_D_MAX; ++j) up[j - 1] = j < dc.level ? max((int)S.node[up[j - 1]], 0) : 0;
+    u64 m0 = 1ull | (n < 64 ? 1ull << n : 0ull), m1 = n < 64 ? 0ull : 1ull << (n - 64);  // the root and itself
+#pragma unroll
+    for (int j = 1; j < DT_D_MAX; ++j) {
+        const u64 bit = 1ull << (up[j - 1] & 63);
+        m0 |= up[j - 1] < 64 ? bit : 0ull;
+        m1 |= up[j - 1] < 64 ? 0ull : bit;
+        parent = j < dc.level ? up[j - 1] : parent;
+    }
+    a.parents[o + n] = parent;
+    a.anc_mask[(o + n) * DT_MASK_WORDS] = m0;
+    a.anc_mask[(o + n) * DT_MASK_WORDS + 1] = m1;
 }
 
 
