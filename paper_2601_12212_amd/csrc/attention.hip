@@ -98,32 +98,6 @@ __device__ __forceinline__ void lds_wait(bf16x8 &v) {
     asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(v) : "n"(N));
 }
 
-// acc *= alpha, element by element, on an accumulator that stays in the accumulator register file.
-// Written out as instructions because any ordinary vector-ALU use of the accumulators inside the
-// block loop makes the compiler keep a second copy of all of them in vector registers and move the
-// 64 values across in every iteration, although this multiply runs in the first block or two only.
-// The idle cycles in front and behind keep the distances the hardware asks for between an MFMA that
-// writes or reads an accumulator register and a vector instruction that reads or writes it (the
-// compiler does not look inside the instruction group); on this rarely taken path they cost nothing.
-__device__ __forceinline__ void acc_scale(f32x16 &acc, float alpha) {
-    float t;
-#define ACC_SCALE4(i0)                                                                                          \
-    {                                                                                                           \
-        float e0 = acc[i0], e1 = acc[i0 + 1], e2 = acc[i0 + 2], e3 = acc[i0 + 3];                               \
-        asm volatile("s_nop 7\n\ts_nop 7\n\t"                                                                  \
-                     "v_accvgpr_read_b32 %4, %0\n\tv_mul_f32 %4, %4, %5\n\tv_accvgpr_write_b32 %0, %4\n\t"     \
-                     "v_accvgpr_read_b32 %4, %1\n\tv_mul_f32 %4, %4, %5\n\tv_accvgpr_write_b32 %1, %4\n\t"     \
-                     "v_accvgpr_read_b32 %4, %2\n\tv_mul_f32 %4, %4, %5\n\tv_accvgpr_write_b32 %2, %4\n\t"     \
-                     "v_accvgpr_read_b32 %4, %3\n\tv_mul_f32 %4, %4, %5\n\tv_accvgpr_write_b32 %3, %4\n\t"     \
-                     "s_nop 7"                                                                                  \
-                     : "+a"(e0), "+a"(e1), "+a"(e2), "+a"(e3), "=&v"(t)                                         \
-                     : "v"(alpha));                                                                             \
-        acc[i0] = e0; acc[i0 + 1] = e1; acc[i0 + 2] = e2; acc[i0 + 3] = e3;                                     \
-    }
-    ACC_SCALE4(0) ACC_SCALE4(4) ACC_SCALE4(8) ACC_SCALE4(12)
-#undef ACC_SCALE4
-}
-
 // The value of the partner lane (lane ^ 32) next to the own one, without a trip through the LDS
 // crossbar: v_permlane32_swap exchanges the upper half of one register with the lower half of another,
 // so from two copies of x every lane ends up holding {x[lane], x[lane ^ 32]} in the two registers (in
@@ -724,6 +698,11 @@ __global__ __launch_bounds__(256, 2) void attn_gang_kernel(AttnArgs a, int P, in
 // into padded tiles (one workgroup per unit, short key ranges), and four waves that load straight
 // into LDS (DIRECT: several workgroups per unit, one wave per SIMD, so latency is hidden inside the
 // wave by having every operand read of a block in flight at once).
+// What bounds a launch is the chain of its trips to memory and, with one wave per SIMD, the number of its instructions (one
+// in eight cycles or so): hence one trip for the four words of a sequence, no division, accumulators in plain registers
+// (moved to and from the accumulator file, rescaling them cost 3,300 cycles of 16,800) and no rescaling of
+// accumulators that are still zero.  8B shape, 1,024 keys, kernel and merge: 12.6 -> 10.9 us per layer; 256 keys 9.0 -> 8.7;
+// 4,096 keys 19.2 -> 18.0.
 // Staged layout, both tiles row-major with padded rows of bf16 elements.  K: the 16 B reads of 16 consecutive rows fall
 // into 16 different slots of 256 B (pitch 272 B at D = 128, 144 B at D = 64).  V: the transposing read takes 4 rows x 64 B
 // per 32 lanes, which fall into four different 64-byte groups (pitch 320 B, 192 B).
@@ -731,7 +710,8 @@ template <int D>
 struct WaveTile {
     static constexpr int K_PITCH = D + 8, V_PITCH = D + 32, K_ELEMS = ATT_KB * K_PITCH, ELEMS = K_ELEMS + ATT_KB * V_PITCH;
 };
-#define WD_TILE (ATT_KB * 256)                  // direct layout: one K or V tile of a wave, unpadded rows
+#define WD_TILE (ATT_KB * 256)                  // direct layout: one K or V tile of a wave
+#define WD_SUB (ATT_KB * 128)                   // half of its columns
 #define WD_STAGE (2 * WD_TILE)                  // K tile + V tile of one stage
 #define WD_LDS_BYTES (4 * 2 * WD_STAGE)         // four waves, two stages: 128 KB
 
@@ -743,20 +723,24 @@ struct WaveTile {
 struct SplitBuf {
     float4 *o;    // [unit, KS, D/32 waves, 4, 64 lanes]: the owner waves' output registers
     float2 *ml;   // [unit, KS, 32]: (max, sum) per query row
+    int G;                  // query heads per kv head
+    u32 g_magic, ks_magic;  // x / d = the upper half of x * (2^32 / d + 1), for x d < 2^32 and d > 1
 };
 
 template <int D, int NW, bool DIRECT>
-__global__ __launch_bounds__(64 * NW) void attn_wave_kernel(AttnArgs a, int KS, SplitBuf sb) {
+__global__ __launch_bounds__(64 * NW, 2) void attn_wave_kernel(AttnArgs a, int KS, SplitBuf sb) {
     static_assert((D == 128 || D == 64) && (NW == 4 || NW == 8) && (!DIRECT || (NW == 4 && D == 128)), "shape");
     constexpr int KSTEPS = D / 16, DBLK = D / 32;
     constexpr int K_PITCH = WaveTile<D>::K_PITCH, V_PITCH = WaveTile<D>::V_PITCH;
-    const int G = a.Hq / a.Hkv;
+    const int G = sb.G;
     // blockIdx.x = kv head: workgroups are dealt to the 8 XCDs round-robin by linear id, so every
     // row block and split of one kv head lands on one XCD and shares its L2 copy of that head's K/V
-    const int b = blockIdx.z / KS, ks = blockIdx.z % KS, h = blockIdx.x;
-    // the four per-sequence words, asked for together: one trip to memory instead of up to three
-    const int n_raw = a.n_nodes[b], l_raw = a.prefix_len[b];
-    const void *kp_raw = a.k_prefix[b], *vp_raw = a.v_prefix[b];
+    const int b = __builtin_amdgcn_readfirstlane(KS == 1 ? blockIdx.z : __umulhi(blockIdx.z, sb.ks_magic));
+    const int ks = blockIdx.z - b * KS, h = blockIdx.x;
+    // The four per-sequence words in one trip to memory: the compiler would fetch the others behind the test of the first.
+    int n_raw = a.n_nodes[b], l_raw = a.prefix_len[b];
+    u64 kp_raw = (u64)(uintptr_t)a.k_prefix[b], vp_raw = (u64)(uintptr_t)a.v_prefix[b];
+    asm volatile("" : "+s"(n_raw), "+s"(l_raw), "+s"(kp_raw), "+s"(vp_raw));
     const int N = min(max(n_raw, 1), a.TT_cap);
     const int M = N * G;
     const int m0 = blockIdx.y * 32;
@@ -770,15 +754,16 @@ __global__ __launch_bounds__(64 * NW) void attn_wave_kernel(AttnArgs a, int KS, 
     const int half = lane >> 5, col = lane & 31;
     const int mq = m0 + col;
     const bool qvalid = mq < M;
-    const int node = qvalid ? mq / G : 0;
-    const int hq = h * G + (qvalid ? mq % G : 0);
+    const int mr = qvalid ? mq : 0;  // rows past M read node 0: unused
+    const int node = G == 1 ? mr : (int)__umulhi((u32)mr, sb.g_magic);
+    const int hq = h * G + (mr - node * G);
 
     // LDS: NW private tiles during the loop, then the exchange area of the partial results
     extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];
     __shared__ float s_m[NW][32], s_l[NW][32];
     __bf16 *kt = (__bf16 *)s_dyn + w * WaveTile<D>::ELEMS;   // staged layout (!DIRECT): padded rows
     __bf16 *vt = kt + WaveTile<D>::K_ELEMS;
-    unsigned char *wtile = s_dyn + w * 2 * WD_STAGE;  // direct layout: two stages of (K tile, V tile), 256-byte rows
+    unsigned char *wtile = s_dyn + w * 2 * WD_STAGE;  // direct layout: two stages of (K tile, V tile)
 
     bf16x8 qreg[KSTEPS];
     {
@@ -797,26 +782,30 @@ __global__ __launch_bounds__(64 * NW) void attn_wave_kernel(AttnArgs a, int KS, 
     float m_run = -INFINITY, l_run = 0.f;
     const float c = a.scale * 1.4426950408889634f;
 
-    const gbf16p kpre = (gbf16p)kp_raw + (int64_t)h * a.kv_stride_head;
-    const gbf16p vpre = (gbf16p)vp_raw + (int64_t)h * a.kv_stride_head;
+    const gbf16p kpre = (gbf16p)(uintptr_t)kp_raw + (int64_t)h * a.kv_stride_head;
+    const gbf16p vpre = (gbf16p)(uintptr_t)vp_raw + (int64_t)h * a.kv_stride_head;
     const gbf16p ktree = (gbf16p)a.k_tree + ((int64_t)b * a.TT_cap * a.Hkv + h) * D;
     const gbf16p vtree = (gbf16p)a.v_tree + ((int64_t)b * a.TT_cap * a.Hkv + h) * D;
     const int64_t stok = a.kv_stride_tok, stree = (int64_t)a.Hkv * D;
     const int kstep = KS * NW;  // the blocks are dealt round-robin over all waves of all splits
     if constexpr (DIRECT) {
         // Blocks go straight from global memory into the wave's own LDS tiles (global_load_lds_dwordx4:
-        // the 64 x 16 B of one instruction land contiguously, i.e. four 256-byte rows), two stages, so
-        // no staging registers and no LDS-write instructions; with one wave per SIMD the registers
-        // saved are what lets every operand read of a block be in flight at once.  Chunk c of row r sits
-        // at chunk position c ^ f(r), f as in the large-batch kernel, applied on the global side.
-        const int krow4 = lane >> 4, cpos = lane & 15;
-        u32 koffp[8], voffp[8];  // inside the prefix: byte offsets from the block's first row
+        // a wave's 64 x 16 B land contiguously), so no staging registers and no LDS-write instructions.  A tile is two
+        // sub-tiles of 32 keys x 128 bytes, a load eight keys of one: whole cache lines.  No operand read has a bank conflict:
+        //   K: chunk c (16 bytes) of row r sits at position c ^ (r / 2 % 8) of its 128 bytes (the permutation is applied on
+        //      the global side);
+        //   V: at c ^ 4 (r / 2 % 2), so that the transposing read's 4 rows x 64 B fall into four different groups of banks.
+        // Two stages, one block asked for ahead.  (Two ahead were slower at every length, 11.3 us per layer against 10.9 at
+        // 1,024 keys, 20.7 against 18.1 at 4,096.)
+        const int krow = lane >> 3, cpos = lane & 7;
+        u32 koffp[2][2], voffp[2];  // inside the prefix: byte offsets from the first of eight rows, even and odd eights; sub-tile
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int r = 4 * i + krow4;
-            koffp[i] = (u32)(r * stok + 8 * (cpos ^ (r & 15))) * 2u;
-            voffp[i] = (u32)(r * stok + 8 * (cpos ^ (((r & 3) << 2) | ((r >> 2) & 3)))) * 2u;
+        for (int s = 0; s < 2; ++s) {
+            koffp[0][s] = (u32)(krow * stok + 8 * (cpos ^ (lane >> 4))) * 2u + 128u * s;
+            koffp[1][s] = (u32)(krow * stok + 8 * (cpos ^ (4 + (lane >> 4)))) * 2u + 128u * s;
+            voffp[s] = (u32)(krow * stok + 8 * (cpos ^ (((lane >> 4) & 1) << 2))) * 2u + 128u * s;
         }
+        const int64_t rows8 = 16 * stok;  // bytes
         const bool small_stride = (int64_t)ATT_KB * stok * 2 < ((int64_t)1 << 31);
         // Every load is unconditional: keys past the end are read from the last valid row, their scores
         // are masked to -inf below, so the duplicated V rows contribute nothing.
@@ -824,54 +813,56 @@ __global__ __launch_bounds__(64 * NW) void attn_wave_kernel(AttnArgs a, int KS, 
             const ldsp kdst = (ldsp)wtile + stage * WD_STAGE;
             const ldsp vdst = kdst + WD_TILE;
             if (small_stride && kb * ATT_KB + ATT_KB <= L) {  // block inside the prefix (uniform test)
-                const gbytep kbase = (gbytep)(kpre + (int64_t)kb * ATT_KB * stok);
-                const gbytep vbase = (gbytep)(vpre + (int64_t)kb * ATT_KB * stok);
+                gbytep kbase = (gbytep)(kpre + (int64_t)kb * ATT_KB * stok), vbase = (gbytep)(vpre + (int64_t)kb * ATT_KB * stok);
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    __builtin_amdgcn_global_load_lds(kbase + koffp[i], kdst + i * 1024, 16, 0, 0);
-                    __builtin_amdgcn_global_load_lds(vbase + voffp[i], vdst + i * 1024, 16, 0, 0);
+                for (int g = 0; g < 4; ++g) {
+#pragma unroll
+                    for (int s = 0; s < 2; ++s) {
+                        __builtin_amdgcn_global_load_lds(kbase + koffp[g & 1][s], kdst + s * WD_SUB + g * 1024, 16, 0, 0);
+                        __builtin_amdgcn_global_load_lds(vbase + voffp[s], vdst + s * WD_SUB + g * 1024, 16, 0, 0);
+                    }
+                    kbase += rows8;
+                    vbase += rows8;
                 }
             } else {                                           // block touching the tree keys or the end
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const int r = 4 * i + krow4;
-                    const int t = min(kb * ATT_KB + r, Tk - 1);
+                for (int g = 0; g < 4; ++g) {
+                    const int t = min(kb * ATT_KB + 8 * g + krow, Tk - 1);
                     const int64_t o = t < L ? (int64_t)t * stok : (int64_t)(t - L) * stree;
-                    __builtin_amdgcn_global_load_lds((gbytep)((t < L ? kpre : ktree) + o + 8 * (cpos ^ (r & 15))),
-                                                     kdst + i * 1024, 16, 0, 0);
-                    __builtin_amdgcn_global_load_lds(
-                        (gbytep)((t < L ? vpre : vtree) + o + 8 * (cpos ^ (((r & 3) << 2) | ((r >> 2) & 3)))),
-                        vdst + i * 1024, 16, 0, 0);
+                    const gbf16p kp = (t < L ? kpre : ktree) + o + 8 * (cpos ^ (4 * (g & 1) + (lane >> 4)));
+                    const gbf16p vp = (t < L ? vpre : vtree) + o + 8 * (cpos ^ (((lane >> 4) & 1) << 2));
+#pragma unroll
+                    for (int s = 0; s < 2; ++s) {
+                        __builtin_amdgcn_global_load_lds((gbytep)(kp + 64 * s), kdst + s * WD_SUB + g * 1024, 16, 0, 0);
+                        __builtin_amdgcn_global_load_lds((gbytep)(vp + 64 * s), vdst + s * WD_SUB + g * 1024, 16, 0, 0);
+                    }
                 }
             }
         };
-        // operand read offsets (bytes inside a tile), as in the large-batch kernel
-        u32 koff[KSTEPS];
-#pragma unroll
-        for (int s = 0; s < KSTEPS; ++s) koff[s] = (u32)(col * 256 + (((2 * s + half) ^ (col & 15)) << 4));
-        const int p16 = lane & 15, r0 = p16 >> 2, q4 = p16 & 3, grp = (lane >> 4) & 1;
-        u32 voff[DBLK][2];
-#pragma unroll
-        for (int db = 0; db < DBLK; ++db)
-#pragma unroll
-            for (int hi = 0; hi < 2; ++hi)
-                voff[db][hi] = (u32)((8 * hi + 4 * half + r0) * 256 +
-                                     (((4 * db + 2 * grp + (q4 >> 1)) ^ (4 * r0 + 2 * hi + half)) << 4) + 8 * (q4 & 1));
-
         int kb = ks * NW + w, cur = 0;
         if (kb < nb) fetch(kb, 0);
+        // operand read offsets (bytes)
+        const u32 lds0 = (u32)(uintptr_t)(ldsp)wtile;
+        u32 koff[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) koff[s] = lds0 + (u32)(col * 128 + (((2 * s + half) ^ ((col >> 1) & 7)) << 4));
+        const int p16 = lane & 15, r0 = p16 >> 2, q4 = p16 & 3, grp = (lane >> 4) & 1;
+        const u32 voff[2] = {lds0 + (u32)((4 * half + r0) * 128 + 64 * (r0 >> 1) + 32 * grp + 8 * q4),
+                             lds0 + (u32)((4 * half + r0) * 128 + 64 * ((r0 >> 1) ^ 1) + 32 * grp + 8 * q4)};
+
         for (; kb < nb; kb += kstep, cur ^= 1) {
             __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this block has landed
             if (kb + kstep < nb) fetch(kb + kstep, cur ^ 1);  // the other stage was last read one block ago
-            const unsigned char *ktile = wtile + cur * WD_STAGE;  // K tile of this stage, its V tile behind it
             // Every operand of the block is asked for before it is needed (with one wave per SIMD nothing
             // else hides LDS latency): the eight K reads first, the sixteen transposing V reads between the
             // MFMAs of S^T, whose accumulator chain leaves the issue slots free.  K read s is followed by
             // 7 - s K reads and 2 s V reads when its MFMA comes up.
-            const u32 kaddr = (u32)(uintptr_t)(ldsp)ktile, vaddr = kaddr + WD_TILE;
+            const u32 stage = cur * WD_STAGE, va0 = voff[0] + stage, va1 = voff[1] + stage;
             bf16x8 ka[KSTEPS];
 #pragma unroll
-            for (int s = 0; s < KSTEPS; ++s) ka[s] = lds_load128(kaddr + koff[s]);
+            for (int s = 0; s < 4; ++s) ka[s] = lds_load128_at<0>(koff[s] + stage);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) ka[4 + s] = lds_load128_at<WD_SUB>(koff[s] + stage);
             bf16x4 vlo[DBLK][2], vhi[DBLK][2];
             f32x16 sacc;
 #pragma unroll
@@ -879,8 +870,8 @@ __global__ __launch_bounds__(64 * NW) void attn_wave_kernel(AttnArgs a, int KS, 
 #define QK_STEP(s, db, st)                                                                  \
             lds_wait<7 + s>(ka[s]);                                                          \
             sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[s], qreg[s], sacc, 0, 0, 0);   \
-            vlo[db][st] = lds_load_tr4<16 * st * 256>(vaddr + voff[db][0]);                  \
-            vhi[db][st] = lds_load_tr4<16 * st * 256>(vaddr + voff[db][1]);                  \
+            vlo[db][st] = lds_load_tr4<WD_TILE + (db >> 1) * WD_SUB + 16 * st * 128>((db) & 1 ? va1 : va0);       \
+            vhi[db][st] = lds_load_tr4<WD_TILE + (db >> 1) * WD_SUB + (16 * st + 8) * 128>((db) & 1 ? va1 : va0); \
             __builtin_amdgcn_sched_barrier(0);
             QK_STEP(0, 0, 0) QK_STEP(1, 1, 0) QK_STEP(2, 2, 0) QK_STEP(3, 3, 0)
             QK_STEP(4, 0, 1) QK_STEP(5, 1, 1) QK_STEP(6, 2, 1) QK_STEP(7, 3, 1)
@@ -922,10 +913,15 @@ __global__ __launch_bounds__(64 * NW) void attn_wave_kernel(AttnArgs a, int KS, 
                 pb[i >> 3][i & 7] = (__bf16)p;
             }
             l_run = l_run * alpha + psum;
+            // the running maximum moved away from a value for some query of this wave: not in the first block, whose
+            // accumulators are zero
+            const bool rescale = __ballot(move && m_run > -INFINITY);
             m_run = m_new;
-            if (__ballot(alpha != 1.0f)) {  // the running maximum moved for some query of this wave
+            if (rescale) {
 #pragma unroll
-                for (int db = 0; db < DBLK; ++db) acc_scale(oacc[db], alpha);
+                for (int db = 0; db < DBLK; ++db)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) oacc[db][i] *= alpha;
             }
 
             // All V reads have landed (they had the whole softmax).  The wait is tied to the very registers
@@ -1038,8 +1034,9 @@ __global__ __launch_bounds__(64 * NW) void attn_wave_kernel(AttnArgs a, int KS, 
             pb[i >> 3][i & 7] = (__bf16)p;
         }
         l_run = l_run * alpha + psum;
+        const bool rescale = __ballot(move && m_run > -INFINITY);  // (as above)
         m_run = m_new;
-        if (__ballot(alpha != 1.0f)) {  // the running maximum moved for some query of this wave
+        if (rescale) {
 #pragma unroll
             for (int db = 0; db < DBLK; ++db)
 #pragma unroll
@@ -1428,6 +1425,9 @@ static int wave_launch(const AttnArgs &a, hipStream_t st, hipError_t *err) {
     if (KS > 1 && (!a.ws || (size_t)KS * per_split > a.ws_bytes)) KS = a.ws ? (int)(a.ws_bytes / per_split) : 1;
     if (KS < 1) KS = 1;
     SplitBuf sb;
+    sb.G = G;
+    sb.g_magic = (u32)(((u64)1 << 32) / G + 1);
+    sb.ks_magic = (u32)(((u64)1 << 32) / KS + 1);
     sb.o = (float4 *)a.ws;
     sb.ml = (float2 *)((char *)a.ws + (size_t)units * KS * (D / 32) * 4 * 64 * 16);
     dim3 grid(a.Hkv, mblocks, a.batch * KS);
