@@ -116,6 +116,27 @@ __device__ __forceinline__ u64 readlane_u64(u64 v, int lane) {
     return ((u64)hi << 32) | lo;
 }
 
+// How many of the keys that a wave holds lie above t (uniform).  The compares go to scalar register pairs of their own, four
+// at a time (the compiler's sequence sends each through VCC and waits for it before the next).
+template <int G>
+__device__ __forceinline__ int count_above(const u32 (&key)[G], u32 t) {
+    int c = 0;
+    if constexpr (G % 4 == 0) {
+#pragma unroll
+        for (int q = 0; q < G; q += 4) {
+            u64 m0, m1, m2, m3;
+            asm("v_cmp_lt_u32_e64 %0, %8, %4\n\tv_cmp_lt_u32_e64 %1, %8, %5\n\tv_cmp_lt_u32_e64 %2, %8, %6\n\tv_cmp_lt_u32_e64 %3, %8, %7"
+                : "=&s"(m0), "=&s"(m1), "=&s"(m2), "=&s"(m3)
+                : "v"(key[q]), "v"(key[q + 1]), "v"(key[q + 2]), "v"(key[q + 3]), "s"(t));
+            c += (__popcll(m0) + __popcll(m1)) + (__popcll(m2) + __popcll(m3));
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < G; ++q) c += __popcll(__builtin_amdgcn_ballot_w64(key[q] > t));
+    }
+    return c;
+}
+
 // Philox4x32-10 (Salmon et al., SC'11): first output word for counter (c0,c1,c2,c3), key (k0,k1).
 __device__ __forceinline__ u32 philox4x32_10_word0(u32 c0, u32 c1, u32 c2, u32 c3, u32 k0, u32 k1) {
 #pragma unroll

@@ -280,28 +280,32 @@ __device__ __forceinline__ int load_octet(const RowArgs &a, int64_t g, int id0, 
 }
 // smallest float whose ordered image has these upper 16 bits (the bin of -inf holds nothing else)
 __device__ __forceinline__ float key_edge(u32 k16) { return k16 <= 0x007Fu ? -INFINITY : unord32(k16 << 16); }
-// k-th largest of the 256 16-bit keys held four to a lane
+// The k-th largest, or a key between it and the next, of the 256 16-bit keys held four to a lane (k <= 64).
+// Bisection between the worst and the best of the lanes' best keys (64 keys reach the worst), about four steps of a
+// hundred cycles (the exact k-th between fixed ends, counted pair by pair, was nine steps and 1,600 cycles of the 10,200 that
+// a workgroup took; 1,000 now).
 __device__ __forceinline__ u32 wave_kth_of_256(const u32 (&ky)[4], int k) {
-    auto reach = [&](u32 t) {  // how many keys are >= t
-        int n = 0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) n += __popcll(__ballot(ky[i] >= t));
-        return n;
-    };
-    // the k-th is nearly always within 255 of the largest (bf16: two powers of two): eight steps instead of sixteen
-    const u32 top = wave_max_u32(max(max(ky[0], ky[1]), max(ky[2], ky[3])));
-    u32 t = top > 255u ? top - 255u : 0u;
-    int bits = 8;
-    if (t > 0u && reach(t) < k) { t = 0u; bits = 16; }
-    for (int bit = bits - 1; bit >= 0; --bit) {
-        const u32 cand = t + (1u << bit);
-        if (reach(cand) >= k) t = cand;
+    const u32 best = max(max(ky[0], ky[1]), max(ky[2], ky[3]));
+    u32 hi = best, rest = ~best;
+#define STEP(CTRL, ROWS)                                               \
+    hi = max(hi, (u32)dpp_mov<CTRL, ROWS>(0, (int)hi));                \
+    rest = max(rest, (u32)dpp_mov<CTRL, ROWS>(0, (int)rest));
+    STEP(0x111, 0xf) STEP(0x112, 0xf) STEP(0x114, 0xf) STEP(0x118, 0xf) STEP(0x142, 0xa) STEP(0x143, 0xc)
+#undef STEP
+    hi = (u32)__builtin_amdgcn_readlane((int)hi, 63);
+    u32 lo = ~(u32)__builtin_amdgcn_readlane((int)rest, 63);  // reached by k keys, hi + 1 by none
+    while (hi > lo) {
+        const u32 mid = lo + ((hi - lo + 1u) >> 1);
+        const int n = count_above<4>(ky, mid - 1u);
+        if (n >= k) lo = mid;
+        else hi = mid - 1u;
+        if (n == k) break;
     }
-    return t;
+    return lo;
 }
 
 template <int MODE, bool BF16>
-__global__ __launch_bounds__(256) void row_select_kernel(RowArgs a, int nl, int S, int vec, float *top_val,
+__global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, int S, int vec, float *top_val,
                                                          int32_t *top_id, float *lse, int out_stride) {
     const int64_t g = blockIdx.x;
     const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -397,16 +401,16 @@ __global__ __launch_bounds__(256) void row_select_kernel(RowArgs a, int nl, int 
     // candidate t ranks itself against all n2 keys (LDS broadcasts, eight in flight)
     auto rank_and_emit = [&](int n2) {
         if (tid < SEL_CAP && (tid & ~63) < n2) {  // the waves that hold a candidate
-            const u64 mine = tid < n2 ? s_fin[tid] : 0ull;
+            const u64 mine = s_fin[tid];
             int r0 = 0, r1 = 0;
-            for (int j0 = 0; j0 < n2; j0 += 8) {
+            for (int j0 = 0; j0 < n2; j0 += 8) {  // the list is zero behind its n2 keys
                 u64 o[8];
 #pragma unroll
-                for (int j = 0; j < 8; ++j) o[j] = s_fin[min(j0 + j, SEL_CAP - 1)];
+                for (int j = 0; j < 8; ++j) o[j] = s_fin[j0 + j];
 #pragma unroll
-                for (int j = 0; j < 8; j += 2) {  // s_fin[n2 ..] may hold anything: masked
-                    r0 += j0 + j < n2 && o[j] > mine ? 1 : 0;
-                    r1 += j0 + j + 1 < n2 && o[j + 1] > mine ? 1 : 0;
+                for (int j = 0; j < 8; j += 2) {
+                    r0 += o[j] > mine ? 1 : 0;
+                    r1 += o[j + 1] > mine ? 1 : 0;
                 }
             }
             if (tid < n2 && r0 + r1 < k) emit(r0 + r1, mine);
@@ -426,6 +430,7 @@ __global__ __launch_bounds__(256) void row_select_kernel(RowArgs a, int nl, int 
         for (int j = 0; j < S; ++j) tmax = fmaxf(tmax, lane_max_value<BF16>(lm[j * 256 + tid]));
     }
     s_key[tid] = (uint16_t)(ord32(tmax) >> 16);
+    if (tid < SEL_CAP) s_fin[tid] = 0ull;
     if (tid == 0) { s_n2 = 0; s_h = 0; }
     __syncthreads();
     const uint2 k4 = ((const uint2 *)s_key)[lane];
@@ -461,6 +466,7 @@ __global__ __launch_bounds__(256) void row_select_kernel(RowArgs a, int nl, int 
             return;
         }
         __syncthreads();  // s_n2 has been read
+        if (tid < SEL_CAP) s_fin[tid] = 0ull;
         if (tid == 0) s_n2 = 0;
     } else {
         row_lse();

@@ -94,26 +94,6 @@ struct TreeLds {
 };
 
 // ---- selection inside a wave ---------------------------------------------------------------------------
-// How many of the keys that a wave holds lie above t (uniform).  The compares go to scalar register pairs of their own, four
-// at a time (the compiler's sequence sends each through VCC and waits for it before the next).
-template <int G>
-__device__ __forceinline__ int count_above(const u32 (&key)[G], u32 t) {
-    int c = 0;
-    if constexpr (G % 4 == 0) {
-#pragma unroll
-        for (int q = 0; q < G; q += 4) {
-            u64 m0, m1, m2, m3;
-            asm("v_cmp_lt_u32_e64 %0, %8, %4\n\tv_cmp_lt_u32_e64 %1, %8, %5\n\tv_cmp_lt_u32_e64 %2, %8, %6\n\tv_cmp_lt_u32_e64 %3, %8, %7"
-                : "=&s"(m0), "=&s"(m1), "=&s"(m2), "=&s"(m3)
-                : "v"(key[q]), "v"(key[q + 1]), "v"(key[q + 2]), "v"(key[q + 3]), "s"(t));
-            c += (__popcll(m0) + __popcll(m1)) + (__popcll(m2) + __popcll(m3));
-        }
-    } else {
-#pragma unroll
-        for (int q = 0; q < G; ++q) c += __popcll(__builtin_amdgcn_ballot_w64(key[q] > t));
-    }
-    return c;
-}
 // The `keep` best of the keys that a wave holds (key q of lane i is candidate i + 64 q), equal keys by ascending candidate;
 // all viable ones if they are fewer.  The caller knows bounds: lo is KEY_NEG_INF or lies below at
 // least `keep` keys, no key lies above hi.  Returns how many were chosen (uniform).
