@@ -194,7 +194,7 @@ int dt_topk_rows(void *stream, const void *logits, dt_dtype t, int64_t n_rows, i
         return DT_ERR_INVALID_ARG;
     if (!topk_v_ok(V) || k < 1 || k > DT_K_MAX || k > V) return DT_ERR_LIMIT;
     if (n_rows == 0) return DT_OK;
-    const int nl = dt::rows_topk_nl(V), S = dt::rows_chunks_per_row(V, nl);
+    const int S = dt::rows_chunks_per_row(V, dt::rows_topk_nl(V));
     if (n_rows > GRID_X_MAX) return DT_ERR_LIMIT;
     if (!ws || (uintptr_t)ws % 256) return DT_ERR_WORKSPACE;
     TopkScratch rs = topk_scratch(ws, n_rows, S);
@@ -207,9 +207,7 @@ int dt_topk_rows(void *stream, const void *logits, dt_dtype t, int64_t n_rows, i
     a.lane_max = rs.lane_max; a.part_ms = rs.ms;
     hipStream_t st = (hipStream_t)stream;
     (void)hipGetLastError();  // a stale error left by another HIP user of this process is not ours
-    hipError_t e = dt::rows_launch_stream(a, n_rows, nl, st);
-    if (e != hipSuccess) return hip_fail(e);
-    e = dt::rows_launch_select(a, n_rows, nl, top_val, top_id, lse, k, st);
+    hipError_t e = dt::rows_launch_topk(a, n_rows, top_val, top_id, lse, k, st);
     if (e != hipSuccess) return hip_fail(e);
     return DT_OK;
 }
@@ -243,7 +241,7 @@ int dt_build_tree(void *stream, int batch, const dt_params *params, const void *
         return DT_ERR_INVALID_ARG;
     if (!topk_v_ok(V) || TT_cap < 1 || TT_cap > DT_TT_MAX) return DT_ERR_LIMIT;
     if (total_rows < batch) return DT_ERR_INVALID_ARG;  // every sequence owns at least its root row
-    const int nl = dt::rows_topk_nl(V), S = dt::rows_chunks_per_row(V, nl);
+    const int S = dt::rows_chunks_per_row(V, dt::rows_topk_nl(V));
     if (total_rows > GRID_X_MAX) return DT_ERR_LIMIT;
     if (!ws || (uintptr_t)ws % 256) return DT_ERR_WORKSPACE;
     char *wsd = (char *)ws;
@@ -264,9 +262,7 @@ int dt_build_tree(void *stream, int batch, const dt_params *params, const void *
     a.lane_max = rs.lane_max; a.part_ms = rs.ms;
     hipStream_t st = (hipStream_t)stream;
     (void)hipGetLastError();  // a stale error left by another HIP user of this process is not ours
-    hipError_t e = dt::rows_launch_stream(a, total_rows, nl, st);
-    if (e != hipSuccess) return hip_fail(e);
-    e = dt::rows_launch_select(a, total_rows, nl, top_val, top_id, lse, DT_K_MAX, st);
+    hipError_t e = dt::rows_launch_topk(a, total_rows, top_val, top_id, lse, DT_K_MAX, st);
     if (e != hipSuccess) return hip_fail(e);
 
     dt::TreeArgs ta = {};
@@ -377,7 +373,7 @@ int dt_expand_level(void *stream, int batch, int level, const dt_params *params,
     if (!topk_v_ok(V) || TT_cap < 1 || TT_cap > DT_TT_MAX) return DT_ERR_LIMIT;
     const int rps = level == 1 ? 1 : rows_per_seq;
     const int64_t total_rows = (int64_t)batch * rps;
-    const int nl = dt::rows_topk_nl(V), S = dt::rows_chunks_per_row(V, nl);
+    const int S = dt::rows_chunks_per_row(V, dt::rows_topk_nl(V));
     if (!ws || (uintptr_t)ws % 256) return DT_ERR_WORKSPACE;
     TopkScratch rs = topk_scratch(ws, total_rows, S);
     if (rs.bytes > ws_bytes) return DT_ERR_WORKSPACE;
@@ -393,9 +389,7 @@ int dt_expand_level(void *stream, int batch, int level, const dt_params *params,
     a.lane_max = rs.lane_max; a.part_ms = rs.ms;
     hipStream_t st = (hipStream_t)stream;
     (void)hipGetLastError();  // a stale error left by another HIP user of this process is not ours
-    hipError_t e = dt::rows_launch_stream(a, total_rows, nl, st);
-    if (e != hipSuccess) return hip_fail(e);
-    e = dt::rows_launch_select(a, total_rows, nl, ls.top_val, ls.top_id, ls.lse, DT_K_MAX, st);
+    hipError_t e = dt::rows_launch_topk(a, total_rows, ls.top_val, ls.top_id, ls.lse, DT_K_MAX, st);
     if (e != hipSuccess) return hip_fail(e);
 
     dt::TreeArgs ta = {};

@@ -56,9 +56,8 @@ struct RowArgs {
 int rows_chunks_per_row(int V, int nl);
 int rows_topk_nl(int V);                    // chunk multiplier of the top-k passes
 int rows_pick_nl(int64_t n_rows, int V);    // chunk multiplier of the arg max pass
-hipError_t rows_launch_stream(const RowArgs &a, int64_t n_rows, int nl, hipStream_t st);
-hipError_t rows_launch_select(const RowArgs &a, int64_t n_rows, int nl, float *top_val, int32_t *top_id, float *lse,
-                              int out_stride, hipStream_t st);
+hipError_t rows_launch_topk(const RowArgs &a, int64_t n_rows, float *top_val, int32_t *top_id, float *lse, int out_stride,
+                            hipStream_t st);
 hipError_t rows_launch_argmax(const RowArgs &a, int64_t n_rows, int nl, hipStream_t st);
 
 // ------------------------------------------------------------------ tree kernel (tree.hip)

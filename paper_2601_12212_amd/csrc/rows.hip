@@ -1,7 +1,8 @@
 // Row kernels: top-k and log-sum-exp over vocabulary rows (draft rows: k best + lse;
 // target rows: arg max, and lse of row/T for stochastic acceptance).
 //
-// Top-k rows take two passes.  The first is a pure stream: a row is cut into chunks of
+// Top-k rows of up to 16,384 entries are held by one workgroup each (row_topk_kernel).  Longer ones take two passes.  The
+// first is a pure stream: a row is cut into chunks of
 // 256*8*NL elements, each lane reads 8*NL of them with coalesced 16-byte loads and leaves
 // only its maximum (plus one (max, sum-exp) pair per wave).  The second works on those lane
 // maxima, 8*NL times fewer than the logits: the k-th largest lane maximum bounds the k-th
@@ -199,7 +200,7 @@ __device__ __forceinline__ float lane_max_value(LaneMax<BF16> v) {
     else return v;
 }
 
-template <int MODE, int NL, bool BF16, bool VEC>
+template <int MODE, int NL, bool BF16>
 __global__ __launch_bounds__(256) void row_stream_kernel(RowArgs a) {
     constexpr int E = 8 * NL;
     // workgroup (chunk c, row g): the chunk rides in grid x, the row in y and -- past 65,535 rows -- z
@@ -211,11 +212,11 @@ __global__ __launch_bounds__(256) void row_stream_kernel(RowArgs a) {
     if (g >= a.n_rows) return;
     // early: the row's elements are on their way while the (dependent, scalar) reads of its metadata are waited for
     RawChunk<NL, BF16> raw;
-    if (a.early_load) chunk_request<NL, BF16, VEC>(a, g, base, raw);
+    if (a.early_load) chunk_request<NL, BF16, true>(a, g, base, raw);
     if (!row_meta<MODE>(a, g).valid) return;
-    if (!a.early_load) chunk_request<NL, BF16, VEC>(a, g, base, raw);
+    if (!a.early_load) chunk_request<NL, BF16, true>(a, g, base, raw);
     float x[E];
-    chunk_finish<NL, BF16, VEC>(a, g, base, (c + 1) * (256 * E), raw, x);
+    chunk_finish<NL, BF16, true>(a, g, base, (c + 1) * (256 * E), raw, x);
     float mx = x[0];
 #pragma unroll
     for (int j = 1; j < E; ++j) mx = fmaxf(mx, x[j]);
@@ -250,14 +251,7 @@ __device__ __forceinline__ float load_elem(const RowArgs &a, int64_t g, int id) 
 // The eight elements from id0 on of row g; returns where they really start (group_start), those before id0 and past the
 // row are -inf.
 template <bool BF16>
-__device__ __forceinline__ int load_octet(const RowArgs &a, int64_t g, int id0, bool vec, float (&xv)[8]) {
-    if (!vec) {  // uniform
-#pragma unroll
-        for (int e = 0; e < 8; ++e) xv[e] = load_elem(a, g, min(id0 + e, a.V - 1));
-#pragma unroll
-        for (int e = 0; e < 8; ++e) xv[e] = id0 + e < a.V ? xv[e] : -INFINITY;
-        return id0;
-    }
+__device__ __forceinline__ int load_octet(const RowArgs &a, int64_t g, int id0, float (&xv)[8]) {
     const int start = group_start(a.V, id0);
     if (BF16) {
         const uint4 r = load16((const uint16_t *)a.logits + g * a.row_stride + start);
@@ -304,8 +298,9 @@ __device__ __forceinline__ u32 wave_kth_of_256(const u32 (&ky)[4], int k) {
     return lo;
 }
 
+// (eight waves per SIMD: left alone the compiler takes 76 registers in one mode, 29.3 us for 64 sequences instead of 26.3)
 template <int MODE, bool BF16>
-__global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, int S, int vec, float *top_val,
+__global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, int S, float *top_val,
                                                          int32_t *top_id, float *lse, int out_stride) {
     const int64_t g = blockIdx.x;
     const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -316,22 +311,15 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
     // the lane maxima do not depend on the row's metadata (two dependent global reads): ask for them
     // first, and wave 3 for the row's (max, sum) partials.  Rows that turn out to be dead have their
     // slots in the workspace all the same.
-    // Thread tid holds lane maxima 4 (256 i + tid) .. + 3, i < S / 4 (the same lane of a chunk's four waves: one load),
-    // or, in rows of up to three chunks, 256 j + tid, j < S.
-    const bool quads = S >= 4;
+    // Thread tid holds lane maxima 4 (256 i + tid) .. + 3, i < S / 4 (the same lane of a chunk's four waves: one load).
     struct alignas(4 * sizeof(LM)) Quad { LM v[4]; };
     float it[16];
     if (S <= 16) {
-        if (quads) {
-            Quad q[4];
+        Quad q[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) q[i] = ((const Quad *)lm)[min(256 * i + tid, S * 64 - 1)];
+        for (int i = 0; i < 4; ++i) q[i] = ((const Quad *)lm)[min(256 * i + tid, S * 64 - 1)];
 #pragma unroll
-            for (int j = 0; j < 16; ++j) it[j] = lane_max_value<BF16>(q[j >> 2].v[j & 3]);
-        } else {
-#pragma unroll
-            for (int j = 0; j < 3; ++j) it[j] = lane_max_value<BF16>(lm[min(j, S - 1) * 256 + tid]);
-        }
+        for (int j = 0; j < 16; ++j) it[j] = lane_max_value<BF16>(q[j >> 2].v[j & 3]);
     }
     const bool lse_wave = w == 3 && a.want_lse && lse;
     float2 pm = make_float2(-INFINITY, 0.f);
@@ -384,7 +372,7 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
     auto reread = [&](int i, int n, float T) {
         const int id0 = (i >> 8) * (256 * E) + (i & 3) * (64 * E) + ((i >> 2) & 63) * 8 + n * 512;
         float xv[8];
-        const int start = load_octet<BF16>(a, g, id0, vec, xv);
+        const int start = load_octet<BF16>(a, g, id0, xv);
         int hits = 0;
 #pragma unroll
         for (int e = 0; e < 8; ++e) hits += xv[e] >= T ? 1 : 0;
@@ -422,8 +410,7 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
     if (S <= 16) {
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
-            const bool have = quads ? 256 * (j >> 2) + tid < S * 64 : j < S;
-            it[j] = have ? it[j] : -INFINITY;
+            it[j] = 256 * (j >> 2) + tid < S * 64 ? it[j] : -INFINITY;
             tmax = fmaxf(tmax, it[j]);
         }
     } else {
@@ -453,7 +440,7 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
             int *list = s_hot + w * SEL_WAVE_CAP;
             for (int at = incl - mine; hot; hot &= hot - 1) {
                 const int j = __builtin_ctz(hot);
-                list[at++] = quads ? 4 * (256 * (j >> 2) + tid) + (j & 3) : 256 * j + tid;
+                list[at++] = 4 * (256 * (j >> 2) + tid) + (j & 3);
             }
             __builtin_amdgcn_wave_barrier();
             for (int q = lane; q < h * nl; q += 64) reread(list[q >> nl_log2], q & (nl - 1), T0);
@@ -541,6 +528,162 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
             else { tv[r] = -INFINITY; if (ti) ti[r] = -1; }
         }
         prev = best;  // 0 once the row is exhausted: nothing is below it, later slots stay empty
+    }
+}
+
+// ---------------------------------------------------- rows that one workgroup holds (top-k rows) --
+// A row of up to 32,768 entries stays in the registers of one workgroup, 8 NL elements per thread: the thread maxima meet in LDS,
+// T is found as in the selection kernel, and the elements that reach it come straight from the registers.  One launch and one
+// trip to memory where the two passes take two and three.  NT threads: the fewest that hold the row with NL <= 4.
+template <int MODE, int NL, bool BF16, bool VEC, int NT>
+__global__ __launch_bounds__(NT, NL == 4 ? 4 : 8) void row_topk_kernel(RowArgs a, float *top_val, int32_t *top_id, float *lse, int out_stride) {
+    constexpr int E = 8 * NL, NW = NT / 64;
+    const int64_t g = blockIdx.x;
+    const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int V = a.V, base = w * (64 * E) + lane * 8;
+    RawChunk<NL, BF16> raw;
+    if (a.early_load) chunk_request<NL, BF16, VEC>(a, g, base, raw);
+    const RowMeta meta = row_meta<MODE>(a, g);
+    if (!meta.valid) return;
+    const int k = meta.k;
+    if (!a.early_load) chunk_request<NL, BF16, VEC>(a, g, base, raw);
+
+    __shared__ __attribute__((aligned(16))) uint16_t s_key[NT];  // [lane][wave]
+    __shared__ float2 s_ms[NW];
+    __shared__ __attribute__((aligned(16))) u64 s_fin[SEL_CAP];
+    __shared__ int s_n, s_cnt[3];
+    if (tid < SEL_CAP) s_fin[tid] = 0ull;
+    if (tid < 3) s_cnt[tid] = 0;
+    if (tid == 0) s_n = 0;
+
+    float x[E];
+    chunk_finish<NL, BF16, VEC>(a, g, base, NT * E, raw, x);
+    float gmx[NL], mx = -INFINITY;  // of each group of eight, and of all
+#pragma unroll
+    for (int n = 0; n < NL; ++n) {
+        gmx[n] = x[8 * n];
+#pragma unroll
+        for (int e = 1; e < 8; ++e) gmx[n] = fmaxf(gmx[n], x[8 * n + e]);
+        mx = fmaxf(mx, gmx[n]);
+    }
+    s_key[lane * NW + w] = (uint16_t)(ord32(mx) >> 16);
+    if (a.want_lse) {
+        const float2 p = wave_lse_partial<E>(x, mx, a.inv_t);
+        if (lane == 0) s_ms[w] = p;
+    }
+    __syncthreads();
+    // 256 slots of NW / 4 threads each: k slots that reach T hold k elements that do
+    u32 ky[4];
+    {
+        uint16_t kv[NW];
+        __builtin_memcpy(kv, __builtin_assume_aligned(&s_key[lane * NW], NW * 2), NW * 2);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            ky[i] = kv[i];
+#pragma unroll
+            for (int j = i + 4; j < NW; j += 4) ky[i] = max(ky[i], (u32)kv[j]);
+        }
+    }
+    const float T = key_edge(wave_kth_of_256(ky, k));
+    auto id_of = [&](int n, int e) {
+        const int id0 = base + n * 512;
+        return (VEC ? group_start(V, id0) : id0) + e;
+    };
+    auto push = [&](bool in, int j) {
+        if (__builtin_amdgcn_ballot_w64(in)) {  // uniform: few elements get here
+            if (in) {
+                const int at = atomicAdd(&s_n, 1);
+                if (at < SEL_CAP) s_fin[at] = make_key(x[j], (u32)id_of(j >> 3, j & 7));
+            }
+        }
+    };
+#pragma unroll
+    for (int n = 0; n < NL; ++n)
+        if (__builtin_amdgcn_ballot_w64(gmx[n] >= T && gmx[n] > -INFINITY)) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) push(x[8 * n + e] >= T && x[8 * n + e] > -INFINITY, 8 * n + e);
+        }
+    __syncthreads();
+    int n = s_n;
+    if (n > SEL_CAP) {
+        // Clusters or equal values: the exact k-th key by bisection, then, of the elements equal to it, the exact last id.
+        int step = 0;
+        auto total = [&](int own) {  // sum over the workgroup; three counters in turn, so that one barrier does
+            const int sum = wave_sum_i32(own);
+            if (lane == 0) atomicAdd(&s_cnt[step % 3], sum);
+            __syncthreads();
+            const int v = s_cnt[step % 3];
+            if (tid == 0) s_cnt[(step + 2) % 3] = 0;
+            ++step;
+            return v;
+        };
+        u32 lo = ord32(T), hi = 0xFFFFFFFFu;  // at least k keys reach lo, none lies above hi
+        if (lo <= 0x007FFFFFu) lo = 0x00800000u;  // -inf does not count
+        int c = n;
+        while (hi > lo && c > k) {
+            const u32 mid = lo + ((hi - lo) >> 1) + 1u;
+            int own = 0;
+#pragma unroll
+            for (int j = 0; j < E; ++j) own += ord32(x[j]) >= mid ? 1 : 0;
+            const int m = total(own);
+            if (m >= k) { lo = mid; c = m; }
+            else hi = mid - 1u;
+        }
+        int id_hi = 0x7FFFFFFF;  // of the elements equal to lo: those up to this id
+        if (c > k) {
+            int own = 0;
+#pragma unroll
+            for (int j = 0; j < E; ++j) own += ord32(x[j]) > lo ? 1 : 0;
+            const int need = k - total(own);
+            int id_lo = 0;  // the smallest id with `need` of them at or below it
+            id_hi = V - 1;
+            while (id_hi > id_lo) {
+                const int mid = (id_lo + id_hi) >> 1;
+                own = 0;
+#pragma unroll
+                for (int j = 0; j < E; ++j) own += ord32(x[j]) == lo && id_of(j >> 3, j & 7) <= mid ? 1 : 0;
+                if (total(own) >= need) id_hi = mid;
+                else id_lo = mid + 1;
+            }
+        }
+        __syncthreads();  // the count has been read
+        if (tid < SEL_CAP) s_fin[tid] = 0ull;
+        if (tid == 0) s_n = 0;
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < E; ++j) push(ord32(x[j]) > lo || (ord32(x[j]) == lo && id_of(j >> 3, j & 7) <= id_hi), j);
+        __syncthreads();
+        n = s_n;
+    }
+    float *tv = top_val + meta.out * out_stride;
+    int32_t *ti = top_id + meta.out * out_stride;
+    if (tid < SEL_CAP && (tid & ~63) < n) {  // candidate tid ranks itself against all (zeros behind the n keys)
+        const u64 mine = s_fin[tid];
+        int rank = 0;
+        for (int j0 = 0; j0 < n; j0 += 8) {
+            u64 o[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) o[j] = s_fin[j0 + j];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) rank += o[j] > mine ? 1 : 0;
+        }
+        if (tid < n && rank < k) {
+            tv[rank] = key_val(mine);
+            ti[rank] = (int32_t)key_idx(mine);
+        }
+    }
+    if (w == NW - 1) {
+        if (lane >= n && lane < k) {  // fewer than k viable entries
+            tv[lane] = -INFINITY;
+            ti[lane] = -1;
+        }
+        if (a.want_lse) {
+            const float cexp = 1.4426950408889634f * a.inv_t;
+            const float2 p = lane < NW ? s_ms[min(lane, NW - 1)] : make_float2(-INFINITY, 0.f);
+            const float M = wave_max(p.x);
+            const float sum = wave_sum(p.y > 0.f ? p.y * __builtin_amdgcn_exp2f((p.x - M) * cexp) : 0.f);
+            if (lane == 0) lse[meta.out] = M == -INFINITY ? -INFINITY : M * a.inv_t + __logf(sum);
+        }
     }
 }
 
@@ -634,64 +777,94 @@ static dim3 rows_grid(int chunks, int64_t n_rows) {
     return dim3((unsigned)chunks, (unsigned)ny, (unsigned)((n_rows + ny - 1) / ny));
 }
 
-// f(NL, BF16, VEC) with the three as compile-time constants.  Rows of fewer than eight entries hold no 16-byte group:
-// element loads, and one chunk of the smallest size.
+// f(MODE, BF16) with both as compile-time constants
 template <typename F>
-static void rows_dispatch(const RowArgs &a, int nl, F f) {
+static void by_mode_and_type(const RowArgs &a, F f) {
     using std::integral_constant;
-    auto pick = [&](auto bf16) {
-        if (a.V < 8) f(integral_constant<int, 1>(), bf16, integral_constant<bool, false>());
-        else if (nl == 4) f(integral_constant<int, 4>(), bf16, integral_constant<bool, true>());
-        else if (nl == 2) f(integral_constant<int, 2>(), bf16, integral_constant<bool, true>());
-        else f(integral_constant<int, 1>(), bf16, integral_constant<bool, true>());
+    auto typed = [&](auto mode) {
+        if (a.dtype == DT_BF16) f(mode, integral_constant<bool, true>());
+        else f(mode, integral_constant<bool, false>());
     };
-    if (a.dtype == DT_BF16) pick(integral_constant<bool, true>());
-    else pick(integral_constant<bool, false>());
+    if (a.mode == ROWS_DRAFT) typed(integral_constant<int, ROWS_DRAFT>());
+    else if (a.mode == ROWS_LEVEL) typed(integral_constant<int, ROWS_LEVEL>());
+    else typed(integral_constant<int, ROWS_UNIFORM>());
 }
 
-// top-k rows, pass 1: lane maxima and (max, sum) partials
 // Launches of at most this many workgroups are latency bound: their rows are read before they are known
 // to be live.  Larger ones are bandwidth bound, and the bytes of a dead row would cost time: a launch sized for the limits
 // that a policy may set on the device is mostly dead rows (two sequences, 450 rows of 128,256 for the widest action:
 // 21.8 us when all were read, 8-13 us when a row's liveness is looked up first).
 static const int64_t EARLY_LOAD_WGS = 2048;
 
-hipError_t rows_launch_stream(const RowArgs &a_in, int64_t n_rows, int nl, hipStream_t st) {
-    if (n_rows <= 0) return hipSuccess;
+// top-k rows, pass 1: lane maxima and (max, sum) partials
+static hipError_t launch_stream(const RowArgs &a_in, int64_t n_rows, int nl, hipStream_t st) {
     RowArgs a = a_in;
     const int64_t S = rows_chunks_per_row(a.V, nl);
     a.early_load = n_rows * S <= EARLY_LOAD_WGS;
     const int kid = a.mode == ROWS_DRAFT ? KID_ROWS_DRAFT : KID_ROWS_UNIFORM;
     a.n_rows = n_rows;
     const dim3 sgrid = rows_grid((int)S, n_rows);
-    rows_dispatch(a, nl, [&](auto NLc, auto BF, auto VC) {
-        constexpr int NL = decltype(NLc)::value;
-        constexpr bool BF16 = decltype(BF)::value, VEC = decltype(VC)::value;
-        if (a.mode == ROWS_DRAFT) launch_kernel(kid, st, row_stream_kernel<ROWS_DRAFT, NL, BF16, VEC>, sgrid, dim3(256), 0, a);
-        else if (a.mode == ROWS_LEVEL) launch_kernel(kid, st, row_stream_kernel<ROWS_LEVEL, NL, BF16, VEC>, sgrid, dim3(256), 0, a);
-        else launch_kernel(kid, st, row_stream_kernel<ROWS_UNIFORM, NL, BF16, VEC>, sgrid, dim3(256), 0, a);
-    });
+    using std::integral_constant;
+    auto go = [&](auto mode, auto bf16) {
+        constexpr int MODE = decltype(mode)::value;
+        constexpr bool BF = decltype(bf16)::value;
+        if (nl == 4) launch_kernel(kid, st, row_stream_kernel<MODE, 4, BF>, sgrid, dim3(256), 0, a);
+        else if (nl == 2) launch_kernel(kid, st, row_stream_kernel<MODE, 2, BF>, sgrid, dim3(256), 0, a);
+        else launch_kernel(kid, st, row_stream_kernel<MODE, 1, BF>, sgrid, dim3(256), 0, a);
+    };
+    by_mode_and_type(a, go);
     return hipGetLastError();
 }
 
 // top-k rows, pass 2: selection on the lane maxima
-hipError_t rows_launch_select(const RowArgs &a, int64_t n_rows, int nl, float *top_val, int32_t *top_id, float *lse,
-                              int out_stride, hipStream_t st) {
-    if (n_rows <= 0) return hipSuccess;
+static hipError_t launch_select(const RowArgs &a, int64_t n_rows, int nl, float *top_val, int32_t *top_id, float *lse,
+                                int out_stride, hipStream_t st) {
     const int S = rows_chunks_per_row(a.V, nl);
-    const int vec = a.V >= 8 ? 1 : 0;
-    auto go = [&](auto kernel) {
-        launch_kernel(KID_ROWS_MERGE, st, kernel, dim3((unsigned)n_rows), dim3(256), 0, a, nl, S, vec, top_val, top_id, lse, out_stride);
-    };
-    if (a.dtype == DT_BF16)
-        a.mode == ROWS_DRAFT   ? go(row_select_kernel<ROWS_DRAFT, true>)
-        : a.mode == ROWS_LEVEL ? go(row_select_kernel<ROWS_LEVEL, true>)
-                               : go(row_select_kernel<ROWS_UNIFORM, true>);
-    else
-        a.mode == ROWS_DRAFT   ? go(row_select_kernel<ROWS_DRAFT, false>)
-        : a.mode == ROWS_LEVEL ? go(row_select_kernel<ROWS_LEVEL, false>)
-                               : go(row_select_kernel<ROWS_UNIFORM, false>);
+    by_mode_and_type(a, [&](auto mode, auto bf16) {
+        launch_kernel(KID_ROWS_MERGE, st, row_select_kernel<decltype(mode)::value, decltype(bf16)::value>, dim3((unsigned)n_rows),
+                      dim3(256), 0, a, nl, S, top_val, top_id, lse, out_stride);
+    });
     return hipGetLastError();
+}
+
+// rows that a workgroup holds
+static hipError_t launch_held(const RowArgs &a_in, int64_t n_rows, float *top_val, int32_t *top_id, float *lse, int out_stride,
+                              hipStream_t st) {
+    RowArgs a = a_in;
+    a.early_load = n_rows * rows_chunks_per_row(a.V, 4) <= EARLY_LOAD_WGS;
+    a.n_rows = n_rows;
+    const int kid = a.mode == ROWS_DRAFT ? KID_ROWS_DRAFT : KID_ROWS_UNIFORM;
+    by_mode_and_type(a, [&](auto mode, auto bf16) {
+        constexpr int MODE = decltype(mode)::value;
+        constexpr bool BF = decltype(bf16)::value;
+        auto go = [&](auto kernel, int nt) {
+            launch_kernel(kid, st, kernel, dim3((unsigned)n_rows), dim3(nt), 0, a, top_val, top_id, lse, out_stride);
+        };
+        if (a.V < 8) go(row_topk_kernel<MODE, 1, BF, false, 256>, 256);  // no 16-byte group: element loads
+        else if (a.V <= 256 * 8) go(row_topk_kernel<MODE, 1, BF, true, 256>, 256);
+        else if (a.V <= 256 * 16) go(row_topk_kernel<MODE, 2, BF, true, 256>, 256);
+        else if (a.V <= 512 * 16) go(row_topk_kernel<MODE, 2, BF, true, 512>, 512);
+        else if (!BF || a.V <= 1024 * 16) go(row_topk_kernel<MODE, 2, BF, true, 1024>, 1024);
+        else if constexpr (BF) go(row_topk_kernel<MODE, 4, BF, true, 1024>, 1024);
+    });
+    return hipGetLastError();
+}
+
+// Top-k rows.  a: its scratch (lane_max, part_ms) is that of rows_topk_nl(V) chunks.
+// One workgroup holds rows of up to 16,384 entries: 51 rows of 1,000 / 4,000 / 8,192 / 16,000 bf16 entries 7.4 / 8.0 / 7.8 / 8.4
+// us in two passes, 4.6 / 5.4 / 5.4 / 6.7 held; 2,000 rows 13.8 / 16.2 / 19.9 / 29, held 8.1 / 10.1 / 15.4 / 29.  Up to twice as long
+// ones in bf16 while every row has a compute unit to itself (32,000 entries: 51 rows 8.7 -> 8.1, 200 rows 11.6 -> 8.9, but
+// 600 rows 18.5 -> 21.1: the two passes spread a row over more of the chip; fp32 51 rows 9.2 -> 10.3).
+#define HELD_V_MAX 16384
+#define HELD_ROWS_MAX 256  // of 2 HELD_V_MAX entries
+hipError_t rows_launch_topk(const RowArgs &a, int64_t n_rows, float *top_val, int32_t *top_id, float *lse, int out_stride,
+                            hipStream_t st) {
+    if (n_rows <= 0) return hipSuccess;
+    if (a.V <= HELD_V_MAX || (a.V <= 2 * HELD_V_MAX && a.dtype == DT_BF16 && n_rows <= HELD_ROWS_MAX))
+        return launch_held(a, n_rows, top_val, top_id, lse, out_stride, st);
+    const int nl = rows_topk_nl(a.V);
+    const hipError_t e = launch_stream(a, n_rows, nl, st);
+    return e != hipSuccess ? e : launch_select(a, n_rows, nl, top_val, top_id, lse, out_stride, st);
 }
 
 // arg max rows (target logits)
@@ -701,10 +874,16 @@ hipError_t rows_launch_argmax(const RowArgs &a_in, int64_t n_rows, int nl, hipSt
     a.early_load = n_rows * rows_chunks_per_row(a.V, nl) <= EARLY_LOAD_WGS;
     a.n_rows = n_rows;
     const dim3 grid = rows_grid(rows_chunks_per_row(a.V, nl), n_rows);
-    rows_dispatch(a, nl, [&](auto NLc, auto BF, auto VC) {
-        launch_kernel(KID_ROWS_TARGET, st, row_argmax_kernel<decltype(NLc)::value, decltype(BF)::value, decltype(VC)::value>,
-                      grid, dim3(256), 0, a);
-    });
+    auto go = [&](auto bf16) {
+        constexpr bool BF = decltype(bf16)::value;
+        auto launch = [&](auto kernel) { launch_kernel(KID_ROWS_TARGET, st, kernel, grid, dim3(256), 0, a); };
+        if (a.V < 8) launch(row_argmax_kernel<1, BF, false>);  // no 16-byte group: element loads
+        else if (nl == 4) launch(row_argmax_kernel<4, BF, true>);
+        else if (nl == 2) launch(row_argmax_kernel<2, BF, true>);
+        else launch(row_argmax_kernel<1, BF, true>);
+    };
+    if (a.dtype == DT_BF16) go(std::integral_constant<bool, true>());
+    else go(std::integral_constant<bool, false>());
     return hipGetLastError();
 }
 

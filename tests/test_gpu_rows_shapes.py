@@ -1,0 +1,49 @@
+"""GPU parity of row top-k at the sizes where it changes its path: rows held by one workgroup (256, 512 and 1024 threads, 8 to
+32 entries each), the two-pass path beyond, one chunk more than the selection keeps in registers, odd strides, and rows whose
+clusters or equal values defeat the first bound."""
+import numpy as np
+import pytest
+
+import dt_synth
+from oracle import ref
+from tests.test_gpu_parity import check_topk, dev_logits
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("V", [7, 8, 9, 300, 2047, 2048, 2049, 4096, 4097, 8191, 8193, 16384, 16385, 32768, 32769, 65537, 131072, 131081])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_topk_rows_around_the_edges_of_its_paths(V, bf16):
+    rng = np.random.default_rng(V)
+    x = (rng.standard_normal((6, V)) * 3).astype(np.float32)
+    x[1] = 40.0 + rng.integers(0, 3, V)                       # three values: ties everywhere
+    x[2, V // 3:V // 3 + 200] += 50.0                         # a cluster of neighbours
+    x[3] = -np.inf
+    x[3, rng.integers(0, V, 5)] = 1.5                         # at most five viable entries
+    x[4, -1] = x[4, 0] = 30.0                                 # the ends of the row
+    for k in sorted({1, min(V, 20), min(V, 32)}):
+        check_topk(dt_synth.f32_to_bf16_bits(x) if bf16 else x, k)
+
+
+@pytest.mark.parametrize("V,n", [(20000, 256), (20000, 257), (1000, 700)])
+def test_topk_rows_of_many_rows(V, n):
+    x = (np.random.default_rng(n).standard_normal((n, V)) * 3).astype(np.float32)
+    check_topk(dt_synth.f32_to_bf16_bits(x), 9)
+
+
+@pytest.mark.parametrize("V", [1001, 8190, 16381, 40001])
+def test_topk_rows_at_any_two_byte_address(V):
+    import paper_2601_12212_amd as dt
+    rng = np.random.default_rng(V)
+    R, k = 5, 12
+    buf = dt_synth.f32_to_bf16_bits((rng.standard_normal((R, V + 3)) * 3).astype(np.float32))
+    val = torch.empty((R, k), dtype=torch.float32, device="cuda")
+    idx = torch.empty((R, k), dtype=torch.int32, device="cuda")
+    lse = torch.empty(R, dtype=torch.float32, device="cuda")
+    ws = torch.zeros(dt.dt_workspace_bytes(1, R, V, 8, 1, 64), dtype=torch.uint8, device="cuda")
+    dt.dt_topk_rows(dev_logits(buf)[:, 1:V + 1], k, val, idx, lse, ws)
+    torch.cuda.synchronize()
+    wval, widx, _ = ref.topk_rows(np.ascontiguousarray(buf[:, 1:V + 1]), k)
+    assert np.array_equal(idx.cpu().numpy(), widx) and np.array_equal(val.cpu().numpy(), wval)
