@@ -101,6 +101,14 @@ __device__ __forceinline__ int wave_scan_incl_i32(int v) {
     DT_DPP_REDUCE(v, 0, i_add, id_i, id_i)
     return v;
 }
+// the same in double (two moves a step instead of two trips through LDS)
+__device__ __forceinline__ double wave_scan_incl_f64(double v) {
+#define STEP(CTRL, ROWS)                                                                           \
+    v += __hiloint2double(dpp_mov<CTRL, ROWS>(0, __double2hiint(v)), dpp_mov<CTRL, ROWS>(0, __double2loint(v)));
+    STEP(0x111, 0xf) STEP(0x112, 0xf) STEP(0x114, 0xf) STEP(0x118, 0xf) STEP(0x142, 0xa) STEP(0x143, 0xc)
+#undef STEP
+    return v;
+}
 // 64-bit maximum: the high words first, then the low words of the lanes that hold that high word.
 __device__ __forceinline__ u64 wave_max_u64(u64 v) {
     const u32 hi = wave_max_u32((u32)(v >> 32));
@@ -114,6 +122,10 @@ __device__ __forceinline__ u64 shfl_xor_u64(u64 v, int o) {
 __device__ __forceinline__ u64 readlane_u64(u64 v, int lane) {
     u32 lo = __builtin_amdgcn_readlane((u32)v, lane), hi = __builtin_amdgcn_readlane((u32)(v >> 32), lane);
     return ((u64)hi << 32) | lo;
+}
+
+__device__ __forceinline__ double readlane_f64(double v, int lane) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane), __builtin_amdgcn_readlane(__double2loint(v), lane));
 }
 
 // How many of the keys that a wave holds lie above t (uniform).  The compares go to scalar register pairs of their own, four
