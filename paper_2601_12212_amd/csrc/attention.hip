@@ -1232,7 +1232,7 @@ __global__ __launch_bounds__(2 * D) void attn_wave_merge_kernel(AttnArgs a, int 
     }
 }
 
-// ------------------------------------------------------------------------------ fp32 path --
+// --------------------------------------------------------------- fp32 path, other head sizes --
 // One workgroup per (node, head), four waves that take 64-key blocks in turn: lane j scores key j, the wave agrees on the
 // running maximum, then lane c accumulates output columns c (and c + 64, NC = 2).  The waves' results meet in LDS.  What
 // bounds it at the sizes it is meant for is trips to memory: the K row of a lane (16-byte loads, VEC) and half of the
@@ -1373,6 +1373,141 @@ __global__ __launch_bounds__(256) void attn_simple_kernel(AttnArgs a) {
     else ((__bf16 *)a.out)[row * D + tid] = (__bf16)res;
 }
 
+// Heads of 64 and 128 in fp32: one workgroup per (node, head), eight waves, 32 keys of each in turn.  Sixteen lanes share a
+// key, lane c of them columns 4c .. 4c+3 of every 64, so that K and V rows come in whole and a lane that has summed a score
+// (four DPP rotations) has the V columns that it weighs: each group of sixteen lanes keeps a softmax of its own over every
+// fourth key, nothing crosses groups before the end.  What bounds it is the chain of trips to memory, two: the words of
+// the sequence (with the query), then all of a wave's K and V rows.  Tiny fp32 configuration (8 nodes, 4 heads, 136 keys):
+// 8.7 us in the kernel above (64-key blocks of four waves, one key to a lane, 4-byte V loads), 4.6 here.
+typedef const float __attribute__((address_space(1))) *gfloatp;
+__device__ __forceinline__ void ld16(gfloatp p, float *x) {
+    typedef const u32x4_any4 __attribute__((address_space(1))) *g16;
+    const u32x4_any4 v = *(g16)p;
+    x[0] = __uint_as_float(v.x); x[1] = __uint_as_float(v.y); x[2] = __uint_as_float(v.z); x[3] = __uint_as_float(v.w);
+}
+template <int CTRL>
+__device__ __forceinline__ float row_rotate_add(float v) {
+    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int D>
+__global__ __launch_bounds__(512) void attn_f32_kernel(AttnArgs a) {
+    constexpr int C = D / 64, U = 8, W = 8;  // 16-byte pieces of a lane's row, keys of a group in flight, waves
+    const int node = blockIdx.x, hq = blockIdx.y, b = blockIdx.z, tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), grp = lane >> 4, col = (lane & 15) * 4;
+    int n_raw = a.n_nodes[b], l_raw = a.prefix_len[b];
+    const float *kpre = (const float *)a.k_prefix[b], *vpre = (const float *)a.v_prefix[b];
+    const int h = hq / (a.Hq / a.Hkv);
+    const int64_t row = ((int64_t)b * a.TT_cap + node) * a.Hq + hq;
+    u64 mask0 = a.anc_mask[((int64_t)b * a.TT_cap + node) * DT_MASK_WORDS];
+    u64 mask1 = a.anc_mask[((int64_t)b * a.TT_cap + node) * DT_MASK_WORDS + 1];
+    float q[C][4];
+#pragma unroll
+    for (int i = 0; i < C; ++i) ld16((gfloatp)a.q + row * D + 64 * i + col, q[i]);
+    // here, all at once (left alone, the words are read one behind the other, where they are first used)
+    asm volatile("" : "+s"(n_raw), "+s"(l_raw), "+s"(kpre), "+s"(vpre), "+s"(mask0), "+s"(mask1));
+    const int N = min(max(n_raw, 1), a.TT_cap);
+    if (node >= N) return;
+    const int L = max(l_raw, 0), Tk = L + N;
+    const float *ktree = (const float *)a.k_tree + ((int64_t)b * a.TT_cap * a.Hkv + h) * D + col;
+    const float *vtree = (const float *)a.v_tree + ((int64_t)b * a.TT_cap * a.Hkv + h) * D + col;
+    kpre += (int64_t)h * a.kv_stride_head + col;
+    vpre += (int64_t)h * a.kv_stride_head + col;
+    const float c2 = a.scale * 1.4426950408889634f;
+
+    float m_run = -INFINITY, l_run = 0.f, o[C][4];
+#pragma unroll
+    for (int i = 0; i < C; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[i][e] = 0.f;
+    for (int t0 = w * (4 * U); t0 < Tk; t0 += W * 4 * U) {
+        float k[U][C][4], v[U][C][4], s[U];
+        const float *vp[U];
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            const int t = min(t0 + 4 * j + grp, Tk - 1);
+            const bool pre = t < L;
+            const int64_t off = pre ? (int64_t)((u64)(u32)t * (u64)a.kv_stride_tok) : (int64_t)((t - L) * (a.Hkv * D));
+            const float *kp = (pre ? kpre : ktree) + off;
+            vp[j] = (pre ? vpre : vtree) + off;
+#pragma unroll
+            for (int i = 0; i < C; ++i) ld16((gfloatp)kp + 64 * i, k[j][i]);
+        }
+#pragma unroll
+        for (int j = 0; j < U; ++j)
+#pragma unroll
+            for (int i = 0; i < C; ++i) ld16((gfloatp)vp[j] + 64 * i, v[j][i]);
+        __builtin_amdgcn_sched_barrier(0);  // all requests before the first use
+        float m_new = m_run;
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            const int t = t0 + 4 * j + grp, tt = t - L;
+            const u32 bit = (u32)((tt < 64 ? mask0 : mask1) >> (tt & 63)) & 1u;
+            const bool vis = (t < Tk) & ((tt < 0) | (bit != 0u));
+            float d = 0.f;
+#pragma unroll
+            for (int i = 0; i < C; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) d = fmaf(q[i][e], k[j][i][e], d);
+            d = row_rotate_add<0x128>(d);
+            d = row_rotate_add<0x124>(d);
+            d = row_rotate_add<0x122>(d);
+            d = row_rotate_add<0x121>(d);
+            s[j] = vis ? d * c2 : -INFINITY;
+            m_new = fmaxf(m_new, s[j]);
+        }
+        const float m_ref = m_new == -INFINITY ? 0.f : m_new;  // a group without a visible key yet
+        const float alpha = __builtin_amdgcn_exp2f(m_run - m_ref);
+        l_run *= alpha;
+#pragma unroll
+        for (int i = 0; i < C; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[i][e] *= alpha;
+        m_run = m_new;
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            const float p = __builtin_amdgcn_exp2f(s[j] - m_ref);
+            l_run += p;
+#pragma unroll
+            for (int i = 0; i < C; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    o[i][e] = s[j] != -INFINITY ? fmaf(p, v[j][i][e], o[i][e]) : o[i][e];  // a hidden key's row is not even multiplied by 0
+        }
+    }
+    // the four groups of the wave, then the waves
+    __shared__ __attribute__((aligned(16))) float s_o[W][D];
+    __shared__ float s_m[W], s_l[W];
+    const float M = wave_max(m_run), Mr = M == -INFINITY ? 0.f : M;
+    const float f = __builtin_amdgcn_exp2f(m_run - Mr);
+    auto over_groups = [&](float x) {
+        x += __shfl_xor(x, 16, 64);
+        return half_swap_sum(x);
+    };
+    const float l_wave = over_groups(l_run * f);
+#pragma unroll
+    for (int i = 0; i < C; ++i) {
+        float4 r;
+        r.x = over_groups(o[i][0] * f); r.y = over_groups(o[i][1] * f);
+        r.z = over_groups(o[i][2] * f); r.w = over_groups(o[i][3] * f);
+        if (grp == 0) *(float4 *)&s_o[w][64 * i + col] = r;
+    }
+    if (lane == 0) { s_m[w] = M; s_l[w] = l_wave; }
+    __syncthreads();
+    if (tid >= D) return;
+    float Mt = s_m[0];
+#pragma unroll
+    for (int v = 1; v < W; ++v) Mt = fmaxf(Mt, s_m[v]);
+    const float Mu = Mt == -INFINITY ? 0.f : Mt;
+    float lt = 0.f, ot = 0.f;
+#pragma unroll
+    for (int v = 0; v < W; ++v) {
+        const float g = __builtin_amdgcn_exp2f(s_m[v] - Mu);
+        lt = fmaf(s_l[v], g, lt);
+        ot = fmaf(s_o[v][tid], g, ot);
+    }
+    ((float *)a.out)[row * D + tid] = lt > 0.f ? ot * (1.0f / lt) : 0.f;
+}
+
 // ------------------------------------------------------------------------------- launchers --
 // LDS beyond 64 KB has to be asked for, once per device (dt_init)
 hipError_t attn_init() {
@@ -1459,6 +1594,9 @@ int attn_launch(const AttnArgs &a, hipStream_t st, hipError_t *err) {
             if (a.D > 64) go(attn_simple_kernel<uint16_t, 2, true>);
             else if (a.D >= 8) go(attn_simple_kernel<uint16_t, 1, true>);
             else go(attn_simple_kernel<uint16_t, 1, false>);
+        } else if (a.D == 64 || a.D == 128) {
+            if (a.D == 64) launch_kernel(KID_ATTN, st, attn_f32_kernel<64>, grid, dim3(512), 0, a);
+            else launch_kernel(KID_ATTN, st, attn_f32_kernel<128>, grid, dim3(512), 0, a);
         } else {
             if (a.D > 64) go(attn_simple_kernel<float, 2, true>);
             else if (a.D >= 4) go(attn_simple_kernel<float, 1, true>);
