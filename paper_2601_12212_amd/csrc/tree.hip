@@ -293,6 +293,11 @@ __device__ __forceinline__ void emit_level(const TreeArgs &a, const TreeLds &S, 
     if (lane == 0) { a.n_expand[b] = n_exp; a.state_n_exp[b] = n_exp; }
 }
 
+// Score of a candidate.  A parent that does not exist (score -inf) has no children, whatever stands where their own
+// log-probabilities would: LDS that nothing wrote (lanes past the level's candidates), a state row of an earlier step, a row
+// of logits that belongs to no node.  (-inf plus an infinity or a NaN there would be a NaN, whose key lies above all.)
+__device__ __forceinline__ float child_score(float parent, float own) { return parent == -INFINITY ? -INFINITY : parent + own; }
+
 // All levels, by one wave: G candidates per lane, 64 G >= k^2.  Returns the end of the pool (levels computed so far), or -1
 // when only level `xl` was wanted and has been written.  LDS is written and read by this wave alone, in order.
 template <int G>
@@ -327,11 +332,11 @@ __device__ __forceinline__ int levels_narrow(const TreeArgs &a, TreeLds &S, int 
         // level l + 1: score = score[parent] + lp
         float sc[G];
         u64 path[G];
-        const float f = S.par[l][min(lane, DT_K_MAX)].score + best_own;
+        const float f = child_score(S.par[l][min(lane, DT_K_MAX)].score, best_own);
 #pragma unroll
         for (int q = 0; q < G; ++q) {
             const Parent pr = S.par[l][parent[q]];
-            sc[q] = pr.score + own[q];
+            sc[q] = child_score(pr.score, own[q]);
             path[q] = pr.path;
         }
 #pragma unroll
@@ -444,11 +449,11 @@ __device__ __forceinline__ int levels_wide(const TreeArgs &a, TreeLds &S, int b,
         __syncthreads();
         if (S.n_exp == 0) break;
         // every wave: the bound; two candidates per thread scored; those above it into the list
-        const float f = S.par[l][min(lane, DT_K_MAX)].score + first;
+        const float f = child_score(S.par[l][min(lane, DT_K_MAX)].score, first);
         float sc[2];
         u32 key[2];
 #pragma unroll
-        for (int q = 0; q < 2; ++q) sc[q] = S.par[l][parent[q]].score + own[q];
+        for (int q = 0; q < 2; ++q) sc[q] = child_score(S.par[l][parent[q]].score, own[q]);
         level_bounds(score_key(f), k, lo_key, hi_key);
         u64 m[2];
 #pragma unroll
