@@ -185,7 +185,9 @@ int dt_build_tree(void *stream, int batch, const dt_params *params, const void *
  *   max_prefix_len : host upper bound of prefix_len[] (sizes the launch)
  * Arithmetic: bf16 inputs, fp32 accumulation, fp32 softmax, output rounded to bf16; fp32 inputs are
  * handled entirely in fp32.  bf16 with D == 128 or D == 64 and both strides multiples of 8 elements runs on the
- * matrix cores; every other combination with D <= 128 runs on a plain vector-ALU kernel (correct, slow).
+ * matrix cores; every other combination with D <= 128 runs on a plain vector-ALU kernel (correct, slow).  The
+ * probabilities stay in fp32 throughout, except that D == 128 on the matrix cores rounds them to bf16 for the
+ * product with V (their sum is taken before).
  * Errors: Hq % Hkv != 0, scale <= 0, negative strides, q / k_tree / v_tree / out not 16-byte aligned
  * -> DT_ERR_INVALID_ARG; D > 128, batch > 8191 or Hq > 65535 -> DT_ERR_LIMIT.
  */

@@ -61,3 +61,31 @@ def test_balanced_schedule_cut_sequences(plen):
         for b in range(len(plen)):
             n = case.trees[b]["n_nodes"]
             assert torch.equal(st.out[b, :n].view(torch.int16), first[b, :n].view(torch.int16)), (b, fill)
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(4, 4), (14, 2)])
+@pytest.mark.parametrize("prefix_len", [[0, 1, 31], [700, 1500, 5], [4000, 300, 64]])
+def test_heads_of_64_keep_their_probabilities_in_32_bits(Hq, Hkv, prefix_len):
+    # against 64-bit arithmetic: one rounding of the result to bf16 (half an ulp, at most 2^-8 of it), and 32-bit scores,
+    # exponentials and sums, whose relative errors (some 2^-21 where scores reach 8 binary orders) weigh sum_j p_j |v_j|.
+    # Probabilities rounded to bf16 would be off by up to 2^-9 of that sum.
+    cfg = _cfg("bf16", 64, [(1, 1, 1), (32, 5, 6), (65, 4, 6)], prefix_len, Hq, Hkv)
+    case = oracle_case(0, cfg=cfg)
+    st = make_step(case)
+    st.build_tree()
+    st.tree_attention()
+    for b in range(cfg.B):
+        n = case.trees[b]["n_nodes"]
+        q, kt, vt, kp, vp = (torch.from_numpy(dt_synth.as_f32(x).copy()).double() for x in dt_synth.qkv(cfg, b))
+        k, v = torch.cat([kp, kt[:n]]), torch.cat([vp, vt[:n]])
+        words = case.trees[b]["anc_mask"]
+        tree = torch.tensor([[int(words[i, j // 64]) >> (j % 64) & 1 for j in range(n)] for i in range(n)], dtype=torch.bool)
+        sees = torch.cat([torch.ones(n, kp.shape[0], dtype=torch.bool), tree], 1)
+        got = st.out[b, :n].double().cpu()
+        for h in range(Hq):
+            g = h // (Hq // Hkv)
+            s = (q[:n, h] @ k[:, g].t() * st.scale).masked_fill(~sees, -np.inf)
+            p = torch.softmax(s, 1)
+            want, weight = p @ v[:, g], p @ v[:, g].abs()
+            over = (got[:, h] - want).abs() - want.abs() * 2.0 ** -8 - weight * 2.0 ** -19
+            assert float(over.max()) <= 0, (b, h, float(over.max()))
