@@ -187,7 +187,8 @@ int dt_build_tree(void *stream, int batch, const dt_params *params, const void *
  * handled entirely in fp32.  bf16 with D == 128 or D == 64 and both strides multiples of 8 elements runs on the
  * matrix cores; every other combination with D <= 128 runs on a plain vector-ALU kernel (correct, slow).  The
  * probabilities stay in fp32 throughout, except that D == 128 on the matrix cores rounds them to bf16 for the
- * product with V (their sum is taken before).
+ * product with V (their sum is taken before).  That path also multiplies the V rows of hidden tree keys by zero, so they
+ * have to be finite; on every other path they may hold anything.
  * Errors: Hq % Hkv != 0, scale <= 0, negative strides, q / k_tree / v_tree / out not 16-byte aligned
  * -> DT_ERR_INVALID_ARG; D > 128, batch > 8191 or Hq > 65535 -> DT_ERR_LIMIT.
  */

@@ -89,3 +89,42 @@ def test_heads_of_64_keep_their_probabilities_in_32_bits(Hq, Hkv, prefix_len):
             want, weight = p @ v[:, g], p @ v[:, g].abs()
             over = (got[:, h] - want).abs() - want.abs() * 2.0 ** -8 - weight * 2.0 ** -19
             assert float(over.max()) <= 0, (b, h, float(over.max()))
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(4, 4), (14, 2)])
+@pytest.mark.parametrize("L", [0, 45, 1410])
+def test_heads_of_64_do_not_multiply_the_values_of_hidden_keys(Hq, Hkv, L):
+    # infinities and a NaN in V of one tree token (one in the middle, and the last, which also pads the last block): the nodes
+    # that see it get them, the others what they get without them, up to the order of 32-bit sums.  Visible everywhere when
+    # they stand in the prefix.
+    cfg = _cfg("bf16", 64, [(65, 4, 6)], [L], Hq, Hkv)
+    case = oracle_case(0, cfg=cfg)
+    st = make_step(case)
+    st.build_tree()
+    st.tree_attention()
+    n = case.trees[0]["n_nodes"]
+    clean = st.out[0, :n].float()
+    words = case.trees[0]["anc_mask"]
+    odd = torch.tensor([float("inf"), float("-inf"), float("nan")], device="cuda")
+
+    def check(sees, what):
+        st.tree_attention()
+        got = st.out[0, :n].float()
+        seen = got[sees][:, :, 10:13]
+        assert bool((torch.isposinf(seen[..., 0]) & torch.isneginf(seen[..., 1]) & torch.isnan(seen[..., 2])).all()), what
+        got[:, :, 10:13] = torch.where(sees[:, None, None], clean[:, :, 10:13], got[:, :, 10:13])
+        # one bf16 ulp of the result: both sides are one rounding of 32-bit sums
+        assert bool(((got - clean).abs() <= clean.abs() * 2.0 ** -7 + 1e-6).all()), what
+
+    for j in (n // 2, n - 1):
+        keep = st.v_tree[0, j].clone()
+        st.v_tree[0, j, :, 10:13] = odd.to(st.v_tree.dtype)
+        sees = torch.tensor([bool(int(words[i, j // 64]) >> (j % 64) & 1) for i in range(n)], device="cuda")
+        assert 0 < int(sees.sum()) < n
+        check(sees, j)
+        st.v_tree[0, j] = keep
+    for t in {0, L // 2, L - 1} if L else ():
+        keep = st.v_prefix[0][t].clone()
+        st.v_prefix[0][t, :, 10:13] = odd.to(st.v_prefix[0].dtype)
+        check(torch.ones(n, dtype=torch.bool, device="cuda"), "prefix %d" % t)
+        st.v_prefix[0][t] = keep
