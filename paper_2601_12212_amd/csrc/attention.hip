@@ -1217,7 +1217,9 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_wave_kernel(AttnArgs a, int K
 // same 16 output values it would own in the single-split epilogue, so the partials are read
 // back in exactly the layout they were written in.  Four partials at a time, all their loads asked for before the first
 // is used and before the node count that says which rows exist (a loop that waited for each partial's statistics and then
-// for its values was up to six trips to memory long: 4.7 us on the 8B shape with three splits).
+// for its values was up to six trips to memory long: 4.7 us on the 8B shape with three splits).  Fewer than four are read as
+// what they are: the last one again, weighed by zero, in the place of a missing fourth turned an infinity of that split into a
+// NaN, and its loads cost 0.4 us a launch (32 layers of the 8B shape, three splits: 380 us; this: 367).
 template <int D>
 __global__ __launch_bounds__(2 * D) void attn_wave_merge_kernel(AttnArgs a, int KS, SplitBuf sb) {
     constexpr int DBLK = D / 32;
@@ -1234,29 +1236,30 @@ __global__ __launch_bounds__(2 * D) void attn_wave_merge_kernel(AttnArgs a, int 
     float res[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) res[i] = 0.f;
-    for (int s0 = 0; s0 < KS; s0 += 4) {
-        float2 ml[4];
-        float4 o[4][4];
+    auto join = [&](auto n_c, int s0) {  // partials s0 .. s0 + n - 1
+        constexpr int n = decltype(n_c)::value;
+        float2 ml[n];
+        float4 o[n][4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) ml[u] = sb.ml[(unit * KS + min(s0 + u, KS - 1)) * 32 + col];
+        for (int u = 0; u < n; ++u) ml[u] = sb.ml[(unit * KS + s0 + u) * 32 + col];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const float4 *pr = sb.o + ((unit * KS + min(s0 + u, KS - 1)) * DBLK + w) * 4 * 64;
+        for (int u = 0; u < n; ++u) {
+            const float4 *pr = sb.o + ((unit * KS + s0 + u) * DBLK + w) * 4 * 64;
 #pragma unroll
             for (int q = 0; q < 4; ++q) o[u][q] = pr[q * 64 + lane];
         }
         __builtin_amdgcn_sched_barrier(0);
         float Mn = M;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) Mn = fmaxf(Mn, ml[u].x);  // past the last split: that split again
+        for (int u = 0; u < n; ++u) Mn = fmaxf(Mn, ml[u].x);
         const float Mu = Mn == -INFINITY ? 0.f : Mn;
         const float keep = __builtin_amdgcn_exp2f((M - Mu) * c);
         Lsum *= keep;
 #pragma unroll
         for (int i = 0; i < 16; ++i) res[i] *= keep;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const float fs = s0 + u < KS ? __builtin_amdgcn_exp2f((ml[u].x - Mu) * c) : 0.f;
+        for (int u = 0; u < n; ++u) {
+            const float fs = __builtin_amdgcn_exp2f((ml[u].x - Mu) * c);
             Lsum += ml[u].y * fs;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
@@ -1267,7 +1270,13 @@ __global__ __launch_bounds__(2 * D) void attn_wave_merge_kernel(AttnArgs a, int 
             }
         }
         M = Mn;
-    }
+    };
+    using std::integral_constant;
+    int s0 = 0;
+    for (; s0 + 4 <= KS; s0 += 4) join(integral_constant<int, 4>(), s0);
+    if (KS - s0 == 3) join(integral_constant<int, 3>(), s0);
+    else if (KS - s0 == 2) join(integral_constant<int, 2>(), s0);
+    else if (KS - s0 == 1) join(integral_constant<int, 1>(), s0);
     const int N = min(max(n_raw, 1), a.TT_cap);
     if (mq >= N * G) return;
     const int node = mq / G, hq = h * G + mq % G;

@@ -128,3 +128,29 @@ def test_heads_of_64_do_not_multiply_the_values_of_hidden_keys(Hq, Hkv, L):
         st.v_prefix[0][t, :, 10:13] = odd.to(st.v_prefix[0].dtype)
         check(torch.ones(n, dtype=torch.bool, device="cuda"), "prefix %d" % t)
         st.v_prefix[0][t] = keep
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("L", [330, 700, 1060, 1410, 1760, 2110, 2460, 2810])
+def test_an_infinite_value_in_any_key_split(D, L):
+    # one short sequence: its keys are dealt over 1 to 8 workgroups (a split per eleven 32-key blocks) and the partials merged;
+    # an infinite V element of a visible prefix key makes that column infinite, whichever split holds the key
+    cfg = _cfg("bf16", D, [(32, 5, 6)], [L], 4, 4)
+    case = oracle_case(0, cfg=cfg)
+    st = make_step(case)
+    st.build_tree()
+    st.tree_attention()
+    n = case.trees[0]["n_nodes"]
+    clean = st.out[0, :n].clone()
+    keep = st.v_prefix[0].clone()
+    for block in range(0, L // 32, 3):
+        st.v_prefix[0].copy_(keep)
+        st.v_prefix[0][32 * block + block % 32, :, 5] = float("inf")
+        st.tree_attention()
+        got = st.out[0, :n]
+        assert bool(torch.isposinf(got[:, :, 5]).all()), block
+        a, b = (x[:, :, [c for c in range(D) if c != 5]].float() for x in (got, clean))
+        # 64-wide heads take the second product of that block in another order: one bf16 ulp of the result
+        over = (a - b).abs() - (b.abs() * 2.0 ** -7 + 1e-6 if D == 64 else 0.0)
+        w = int(over.argmax())
+        assert float(over.max()) <= 0, (block, w, float(a.flatten()[w]), float(b.flatten()[w]))
