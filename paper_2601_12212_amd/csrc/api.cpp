@@ -76,8 +76,9 @@ int cu_count_for_sizing() {
     return 256;
 }
 
-// launch grids: x up to 2^31 - 1 workgroups, y and z up to 65535; rows ride in y and z (65535^2 of them),
-// and the row selection takes one workgroup per row in x
+// launch grids: x up to 2^31 - 1 workgroups and 2^32 - 1 threads, y and z up to 65535 workgroups.  Streamed rows ride in y and
+// z (65535^2 of them); the row selection takes one workgroup of 256 threads per row in x, so that a top-k of 2^24 rows or more
+// ends in HIP's own error
 constexpr int64_t GRID_X_MAX = 2147483647ll;
 constexpr int GRID_YZ_MAX = 65535;
 

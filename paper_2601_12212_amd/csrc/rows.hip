@@ -855,12 +855,18 @@ static hipError_t launch_held(const RowArgs &a_in, int64_t n_rows, float *top_va
 // us in two passes, 4.6 / 5.4 / 5.4 / 6.7 held; 2,000 rows 13.8 / 16.2 / 19.9 / 29, held 8.1 / 10.1 / 15.4 / 29.  Up to twice as long
 // ones in bf16 while every row has a compute unit to itself (32,000 entries: 51 rows 8.7 -> 8.1, 200 rows 11.6 -> 8.9, but
 // 600 rows 18.5 -> 21.1: the two passes spread a row over more of the chip; fp32 51 rows 9.2 -> 10.3).
+// A workgroup takes a row in grid x, where a launch may have 2^32 - 1 threads: more rows of 512 or 1,024 threads than that go
+// through the two passes, whose 256 threads a row reach further.  (Rows on in grid y, and a test for its overhang, cost every
+// launch 0.3 us.)
 #define HELD_V_MAX 16384
 #define HELD_ROWS_MAX 256  // of 2 HELD_V_MAX entries
+static int held_threads(int V) { return V <= 256 * 16 ? 256 : V <= 512 * 16 ? 512 : 1024; }
 hipError_t rows_launch_topk(const RowArgs &a, int64_t n_rows, float *top_val, int32_t *top_id, float *lse, int out_stride,
                             hipStream_t st) {
     if (n_rows <= 0) return hipSuccess;
-    if (a.V <= HELD_V_MAX || (a.V <= 2 * HELD_V_MAX && a.dtype == DT_BF16 && n_rows <= HELD_ROWS_MAX))
+    const int nt = held_threads(a.V);
+    if ((a.V <= HELD_V_MAX && (nt == 256 || n_rows * nt <= 0xFFFFFFFFll)) ||
+        (a.V <= 2 * HELD_V_MAX && a.dtype == DT_BF16 && n_rows <= HELD_ROWS_MAX))
         return launch_held(a, n_rows, top_val, top_id, lse, out_stride, st);
     const int nl = rows_topk_nl(a.V);
     const hipError_t e = launch_stream(a, n_rows, nl, st);

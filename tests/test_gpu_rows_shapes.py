@@ -6,6 +6,8 @@ import pytest
 
 import dt_synth
 from oracle import ref
+from paper_2601_12212_amd import dt_workspace_bytes
+from tests._cases import TREE_MARGIN, assert_tree_equal
 from tests.test_gpu_parity import check_topk, dev_logits
 
 pytestmark = pytest.mark.gpu
@@ -47,3 +49,23 @@ def test_topk_rows_at_any_two_byte_address(V):
     torch.cuda.synchronize()
     wval, widx, _ = ref.topk_rows(np.ascontiguousarray(buf[:, 1:V + 1]), k)
     assert np.array_equal(idx.cpu().numpy(), widx) and np.array_equal(val.cpu().numpy(), wval)
+
+
+def test_a_launch_of_more_threads_than_one_grid_dimension_takes():
+    # 2^22 rows, each held by a workgroup of 1,024 threads; all but the tree's own rows belong to no tree (and are not read)
+    from paper_2601_12212_amd.step import Step
+    n, V, TT, d, k = 1 << 22, 8193, 30, 4, 5
+    if torch.cuda.mem_get_info()[0] < 110e9:
+        pytest.skip("needs 92 GB of device memory")
+    rows = dt_synth.f32_to_bf16_bits((np.random.default_rng(8).standard_normal((1 + (d - 1) * k, V)) * 3).astype(np.float32))
+    want = ref.build_tree(rows, TT, d, k, 3)
+    assert want["min_margin"] >= TREE_MARGIN
+    st = Step([(TT, d, k)], [1], 4, 4, 64, V)
+    st.draft_logits, st.total_rows = torch.empty((n, V), dtype=torch.bfloat16, device="cuda"), n
+    st.ws = torch.empty(dt_workspace_bytes(1, n, V, TT, 4, 64), dtype=torch.uint8, device="cuda")
+    st.set_draft(0, rows)
+    st.set_root_token(0, 3)
+    st.build_tree()
+    assert_tree_equal(st.tree(0), want)
+    del st
+    torch.cuda.empty_cache()
