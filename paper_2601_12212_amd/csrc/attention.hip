@@ -57,22 +57,22 @@ __device__ __forceinline__ bf16x8 lds_load128(u32 addr) {
     asm volatile("ds_read_b128 %0, %1" : "=v"(v) : "v"(addr));
     return v;
 }
-// One global_load_lds_dwordx4 with the address split into a wave-uniform base (scalar registers) and a 32-bit
-// per-lane byte offset, the LDS destination (wave-uniform, the lanes' 16 bytes follow each other) in M0: no
-// vector arithmetic per load, and no 64-bit per-lane pointers to keep and advance.  OFF is added to the global address; the
-// instruction adds its offset to the LDS address as well, so M0 holds the destination less OFF.
+// Four global_load_lds_dwordx4, 64 bytes apart in memory and STEP bytes apart in LDS, with the address split into a
+// wave-uniform base (scalar registers) and a 32-bit per-lane byte offset, the LDS destination (wave-uniform, the lanes' 16 bytes
+// follow each other) in M0: no vector arithmetic per load, and no 64-bit per-lane pointers to keep and advance.  The
+// instruction adds its offset to the LDS address as well, so M0 holds the destination less that.
 // The hardware asks for five wait states between a vector instruction that writes a scalar register (readfirstlane, the
-// reload of a spilled one) and a memory instruction that reads it, and the compiler does not see the memory instruction in
-// here: the first of a group of loads from one base keeps that distance itself.
-template <int OFF>
-__device__ __forceinline__ void load_to_lds16(const void __attribute__((address_space(1))) *base, u32 lane_off, u32 lds_addr) {
-    if constexpr (OFF == 0)
-        asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lane_off), "s"(base), "s"(lds_addr)
-                     : "memory", "m0");
-    else
-        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3" ::"v"(lane_off), "s"(base),
-                     "s"(lds_addr - OFF), "n"(OFF)
-                     : "memory", "m0");
+// reload of a spilled one) and a memory instruction that reads it, and the compiler does not see the memory instructions in
+// here: the group keeps that distance itself in front of its first load, and is one statement, so that nothing can be put
+// between the loads.
+template <int STEP>
+__device__ __forceinline__ void load4_to_lds16(const void __attribute__((address_space(1))) *base, u32 lane_off, u32 lds_addr) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, %1\n\t"
+                 "s_add_u32 m0, m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:64\n\t"
+                 "s_add_u32 m0, m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:128\n\t"
+                 "s_add_u32 m0, m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:192" ::"v"(lane_off),
+                 "s"(base), "s"(lds_addr), "n"(STEP - 64)
+                 : "memory", "m0", "scc");
 }
 // a pointer that is the same in every lane, moved to scalar registers where the compiler has not seen that
 __device__ __forceinline__ gbf16p uniform_ptr(gbf16p p) {
@@ -249,10 +249,7 @@ __device__ __forceinline__ void tile_segment(const AttnArgs &a, unsigned char *s
         if (small_stride && kb * TILE_KEYS + TILE_KEYS <= L) {  // block inside the prefix (uniform test)
             const u32 dl = (u32)(uintptr_t)dst;
             const gbytep base = (gbytep)(pre + (int64_t)kb * TILE_KEYS * stok);
-            load_to_lds16<0>(base, poff, dl);
-            load_to_lds16<64>(base, poff, dl + SUB_BYTES);
-            load_to_lds16<128>(base, poff, dl + 2 * SUB_BYTES);
-            load_to_lds16<192>(base, poff, dl + 3 * SUB_BYTES);
+            load4_to_lds16<SUB_BYTES>(base, poff, dl);
         } else {                                                 // block touching the tree keys or the end
             const int t = min(kb * TILE_KEYS + krow, Tk - 1);
             const gbf16p src = (t < L ? pre + (int64_t)t * stok : tree + (int64_t)(t - L) * stree) + 8 * chunk;
