@@ -190,11 +190,125 @@ __device__ __forceinline__ bool arrive_last(u64 *count, u64 tag, int parts) {
     }
 }
 
+// Many parts: a batch of few kv heads with one sequence far longer than the others.  Counted in one after the other on one
+// word, and read one after the other by one workgroup at the rate that a compute unit is fed, they took 1 to 1.6 us each.  More
+// than SERIAL_PARTS leave marks on words of their own instead, and their workgroups stay to see the last mark (for at most
+// STAY_TICKS: nothing depends on who is still there); whoever sees all of them takes slices of the tile, one after the other,
+// until there are none left.  Two kv heads, one sequence of 32,768 keys among 63 of 256 (170 parts): 208 us before, 40 so; seven
+// query heads to each of two kv heads, one of 16,384 among 15 of 128 (52 parts): 130 and 42; eight kv heads, one of 8,192
+// among 15 of 256 (18 parts): 55 and 46.  (Marks, but all parts read by the last to come: 132, 78, 54; a merge kernel: 53,
+// 46, 51.)
+#define SERIAL_PARTS 8
+#define MERGE_SLICES 16
+#define STAY_TICKS 5000  // of 10 ns
+struct SharedMerge {
+    TileParts pt;
+    u64 *marks;   // [slots, 2] `tag` once a partial has been left, anything else before
+    bool stay;    // nothing else waits for this workgroup
+    __bf16 *out;  // of (sequence, kv head): row node * Hq + group head
+    int m0, rb, M, G, Hq;
+    float c;
+};
+__device__ __forceinline__ int64_t part_at(const TileParts &pt, int i) { return 2 * (int64_t)(pt.slot + i * pt.step) + (i == 0); }
+// The next slice to take.  Part 1 lies inside its sequence, so nothing in this launch leaves a mark as a first part there.
+__device__ __forceinline__ u64 *next_slice(const SharedMerge &s) { return s.marks + 2 * (int64_t)(s.pt.slot + s.pt.step) + 1; }
+// One wave: marks its part and looks for the others'.  True if all of them are there and the merge has not been taken entirely.
+__device__ __forceinline__ bool mark_and_stay(const SharedMerge &s, int lane) {
+    if (s.pt.me == 0) {  // before the mark: whoever sees all marks sees a number of this launch
+        if (lane == 0) put_agent(next_slice(s), 0);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+    if (lane == 0) put_agent(s.marks + part_at(s.pt, s.pt.me), s.pt.tag);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // of the last two parts at least one sees the other's mark
+    const u32 t0 = (u32)__builtin_amdgcn_s_memrealtime();
+    for (;;) {
+        bool all = true, mine = false;
+        for (int i0 = 0; i0 < s.pt.parts; i0 += 64) {
+            const int i = min(i0 + lane, s.pt.parts - 1);
+            const bool there = get_agent(s.marks + part_at(s.pt, i)) == s.pt.tag;
+            all = all && __builtin_amdgcn_ballot_w64(!there) == 0ull;
+            mine = mine || __builtin_amdgcn_ballot_w64(there && i == s.pt.me) != 0ull;
+        }
+        if (all) return true;
+        if (!mine || !s.stay || (u32)__builtin_amdgcn_s_memrealtime() - t0 > STAY_TICKS) return false;
+        __builtin_amdgcn_s_sleep(8);
+    }
+}
+template <int D>
+__device__ __forceinline__ void merge_shared(SharedMerge s) {
+    __shared__ int s_word[2];
+    int tid = threadIdx.x, one = 1;
+    asm volatile("" : "+v"(tid), "+v"(one), "+s"(s.pt.tag));  // what follows from these stays out of the key loop's registers
+    const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), half = lane >> 5;
+    const int row = 32 * s.rb + (lane & 31), mq = s.m0 + row;
+    if (w == 0) {
+        const bool help = mark_and_stay(s, lane);
+        if (lane == 0) s_word[0] = help;
+    }
+    __syncthreads();
+    if (!s_word[0]) return;
+    asm volatile("" ::: "memory");
+    constexpr int E = D / 4 / MERGE_SLICES, U = 16;  // 64-bit words of a slice per thread, parts in flight
+    int slice;
+    for (;;) {
+        if (tid == 0) s_word[1] = (int)__hip_atomic_fetch_add(next_slice(s), one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        slice = s_word[1];
+        __syncthreads();
+        if (slice >= MERGE_SLICES) break;    // uniform
+        if (s.m0 + 32 * s.rb >= s.M) continue;  // a wave without rows
+        float m = -INFINITY, l = 0.f;
+        float2 acc[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) acc[e] = make_float2(0.f, 0.f);
+        for (int i0 = 0; i0 < s.pt.parts; i0 += U) {
+            u64 mlw[U], ow[U][E];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t at = part_at(s.pt, min(i0 + u, s.pt.parts - 1));
+                mlw[u] = get_agent(s.pt.ml + at * ATT_MTILE + row);
+#pragma unroll
+                for (int e = 0; e < E; ++e) ow[u][e] = get_agent(s.pt.o + at * (D / 4 * 256) + (slice * E + e) * 256 + 64 * s.rb + lane);
+            }
+            __builtin_amdgcn_sched_barrier(0);  // all requests before the first use
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const float2 ml = __builtin_bit_cast(float2, mlw[u]);
+                if (i0 + u < s.pt.parts && ml.y > 0.f) {  // a range whose keys were all hidden weighs nothing
+                    const float m2 = fmaxf(m, ml.x);
+                    const float keep = __builtin_amdgcn_exp2f((m - m2) * s.c);  // first partial: exp2(-inf) = 0
+                    const float wgt = __builtin_amdgcn_exp2f((ml.x - m2) * s.c);
+#pragma unroll
+                    for (int e = 0; e < E; ++e) {
+                        const float2 v = __builtin_bit_cast(float2, ow[u][e]);
+                        acc[e].x = acc[e].x * keep + v.x * wgt;
+                        acc[e].y = acc[e].y * keep + v.y * wgt;
+                    }
+                    l = l * keep + ml.y * wgt;
+                    m = m2;
+                }
+            }
+        }
+        if (mq >= s.M) continue;
+        const float inv = l > 0.f ? 1.0f / l : 0.f;
+        __bf16 *op = s.out + ((int64_t)(mq / s.G) * s.Hq + mq % s.G) * D + 4 * half;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int i = 2 * (slice * E + e);  // element i of the lane's: column 32 (i / 16) + 8 (i % 16 / 4) + 4 half + i % 4
+            const bf16x2 v = {(__bf16)(acc[e].x * inv), (__bf16)(acc[e].y * inv)};
+            *(bf16x2 *)(op + 32 * (i >> 4) + 8 * ((i & 15) >> 2) + (i & 3)) = v;
+        }
+    }
+    // The first to find nothing left takes the marks away: a replayed graph has the same tag.
+    if (slice == MERGE_SLICES)
+        for (int i = tid; i < s.pt.parts; i += 256) put_agent(s.marks + part_at(s.pt, i), 0);
+}
+
 // Rows m0 .. m0+127 of (sequence b, kv head h) against key blocks kb0 .. kb1-1 of that sequence.
 // Called by all 256 threads of the workgroup; ends behind a barrier, so calls can follow each other.
 template <int D>
 __device__ __forceinline__ void tile_segment(const AttnArgs &a, unsigned char *s_dyn, int h, int b, int m0, int rot, int kb0,
-                                             int kb1, const TileParts &pt) {
+                                             int kb1, const TileParts &pt, int slots, bool stay) {
     static_assert(D == 128, "head dim");
     constexpr int KSTEPS = D / 16, DBLK = D / 32;
     const int G = a.Hq / a.Hkv;
@@ -482,15 +596,18 @@ __device__ __forceinline__ void tile_segment(const AttnArgs &a, unsigned char *s
     // ---- epilogue -------------------------------------------------------------------------------
     float l_tot = half_swap_sum(l_run);
     if (pt.parts > 1) {
+        int word = lane;
+        asm volatile("" : "+v"(word));  // as above: the addresses are worked out here
         // The last part's workgroup usually finds the others' partials there, and then leaves none of its own.
         __shared__ int s_last[2];
-        if (tid == 0) s_last[0] = get_agent(pt.count) == (pt.tag | (pt.parts - 1));
+        const bool many = __builtin_expect(pt.parts > SERIAL_PARTS, 0);
+        if (tid == 0) s_last[0] = !many && get_agent(pt.count) == (pt.tag | (pt.parts - 1));
         __syncthreads();
         const int mine = 32 * rb + col;
         if (!s_last[0]) {
             if (active) {
                 const int64_t at = 2 * (pt.slot + pt.me * pt.step) + (pt.me == 0);
-                u64 *op = pt.o + at * (D / 4 * 256) + 64 * rb + lane;
+                u64 *op = pt.o + at * (D / 4 * 256) + 64 * rb + word;
 #pragma unroll
                 for (int i = 0; i < D / 4; ++i)
                     put_agent(op + i * 256, __builtin_bit_cast(u64, make_float2(oacc[i >> 3][(2 * i) & 15], oacc[i >> 3][(2 * i + 1) & 15])));
@@ -498,6 +615,17 @@ __device__ __forceinline__ void tile_segment(const AttnArgs &a, unsigned char *s
             }
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the stores are there before the count says so
             __syncthreads();
+            if (many) {
+                SharedMerge sm;
+                sm.pt = pt;
+                sm.marks = pt.ml + (int64_t)slots * (2 * ATT_MTILE + 1);
+                sm.stay = stay;
+                sm.out = (__bf16 *)a.out + ((int64_t)b * a.TT_cap * a.Hq + h * G) * D;
+                sm.m0 = m0; sm.rb = rb; sm.M = M; sm.G = G; sm.Hq = a.Hq;
+                sm.c = c;
+                merge_shared<D>(sm);
+                return;
+            }
             if (tid == 0) s_last[1] = arrive_last(pt.count, pt.tag, pt.parts);
             __syncthreads();
             if (!s_last[1]) return;
@@ -521,7 +649,7 @@ __device__ __forceinline__ void tile_segment(const AttnArgs &a, unsigned char *s
                     for (int db = 0; db < DBLK; ++db) o[db] = oacc[db];
                 } else {
                     const int64_t at = 2 * (pt.slot + i * pt.step) + (i == 0);
-                    u64 *op = pt.o + at * (D / 4 * 256) + 64 * rb + lane;
+                    u64 *op = pt.o + at * (D / 4 * 256) + 64 * rb + word;
                     ml = __builtin_bit_cast(float2, get_agent(pt.ml + at * ATT_MTILE + mine));
 #pragma unroll
                     for (int e = 0; e < D / 4; ++e) {
@@ -548,7 +676,9 @@ __device__ __forceinline__ void tile_segment(const AttnArgs &a, unsigned char *s
     }
     if (!qvalid) return;
     const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-    __bf16 *op = (__bf16 *)a.out + (((int64_t)b * a.TT_cap + node) * a.Hq + hq) * D;
+    int h4 = 4 * half;
+    asm volatile("" : "+v"(h4));  // as above
+    __bf16 *op = (__bf16 *)a.out + h4 + (((int64_t)b * a.TT_cap + node) * a.Hq + hq) * D;
 #pragma unroll
     for (int db = 0; db < DBLK; ++db)
 #pragma unroll
@@ -556,7 +686,7 @@ __device__ __forceinline__ void tile_segment(const AttnArgs &a, unsigned char *s
             bf16x4 o4;
 #pragma unroll
             for (int e = 0; e < 4; ++e) o4[e] = (__bf16)(oacc[db][q * 4 + e] * inv);
-            *(bf16x4 *)(op + 32 * db + 8 * q + 4 * half) = o4;
+            *(bf16x4 *)(op + 32 * db + 8 * q) = o4;
         }
 }
 
@@ -573,7 +703,7 @@ __global__ __launch_bounds__(256, 2) void attn_tile_kernel(AttnArgs a) {
     const int nb = (max(a.prefix_len[b], 0) + N + TILE_KEYS - 1) / TILE_KEYS;
     TileParts whole = {};
     whole.parts = 1;
-    tile_segment<D>(a, s_dyn, h, b, m0, blockIdx.y + blockIdx.z, 0, nb, whole);
+    tile_segment<D>(a, s_dyn, h, b, m0, blockIdx.y + blockIdx.z, 0, nb, whole, 0, false);
 }
 
 // ---- balanced schedule -----------------------------------------------------------------------------
@@ -586,16 +716,17 @@ __global__ __launch_bounds__(256, 2) void attn_tile_kernel(AttnArgs a) {
 // A slot therefore works through a few (sequence, tile, key range) segments of near-equal total
 // length.  A sequence cut by a range boundary leaves partials: per slot at most one "head" (its first
 // segment, when that sequence began in an earlier gang) and one "tail" (a sequence that began
-// here and runs on), and the slot of its first gang holds the count of them.  The last workgroup to come
-// merges: a merge kernel of its own read every partial back from memory after all had been written, 9 to 16 us
-// of a launch of 62 to 240, while here a head is written early and read once by the workgroup that ends with the tail.
+// here and runs on), and the slot of its first gang holds the count of them.  The last workgroup to come merges them, or, if
+// they are many, those that have stayed for it together: a merge kernel of its own read every partial back from memory after
+// all had been written, 9 to 16 us of a launch of 62 to 240, while here a head is written early and read once by the workgroup
+// that ends with the tail.
 // Every wave derives the plan by itself from n_nodes / prefix_len with wave
 // operations (sequence b in lane b: batch <= 64; class m in lane m), so no barrier is involved.
 struct GangPartial {
     u64 *o;       // [Hkv, P, 2, D / 4, 256]
     u64 *ml;      // [Hkv, P, 2, 128]
-    u64 *count;   // [Hkv, P]
-    u64 tag;      // of this launch: what the memory held before it never looks like a count
+    u64 *count;   // [Hkv, P], and behind them the marks, [Hkv, P, 2]
+    u64 tag;      // of this launch: what the memory held before it never looks like a count or a mark
 };
 
 __device__ __forceinline__ int wave_excl_scan_i32(int v, int lane) {
@@ -684,7 +815,7 @@ __global__ __launch_bounds__(256, 2) void attn_gang_kernel(AttnArgs a, int P, in
         pt.ml = part.ml;
         pt.count = part.count + pt.slot;
         pt.tag = part.tag;
-        tile_segment<D>(a, s_dyn, h, b, tile * ATT_MTILE, j, kb0, kb1, pt);
+        tile_segment<D>(a, s_dyn, h, b, tile * ATT_MTILE, j, kb0, kb1, pt, a.Hkv * P, !segs);
     }
 }
 
@@ -1583,8 +1714,8 @@ hipError_t attn_init() {
 }
 
 // scratch of the balanced large-batch schedule: (kv heads x slots per head) <= 2 x compute units
-// slots, two partials of 128 rows and a count each
-static size_t gang_slot_bytes(int D) { return 2 * ATT_MTILE * ((size_t)D * 4 + 8) + 8; }
+// slots, two partials of 128 rows with their marks and a count each
+static size_t gang_slot_bytes(int D) { return 2 * ATT_MTILE * ((size_t)D * 4 + 8) + 3 * 8; }
 static size_t gang_bytes(int D, int n_cu) { return (size_t)2 * n_cu * gang_slot_bytes(D); }
 
 // scratch of one key split of the small-batch kernel, per (sequence, kv head, 32-row block)

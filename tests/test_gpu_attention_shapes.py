@@ -154,3 +154,45 @@ def test_an_infinite_value_in_any_key_split(D, L):
         over = (a - b).abs() - (b.abs() * 2.0 ** -7 + 1e-6 if D == 64 else 0.0)
         w = int(over.argmax())
         assert float(over.max()) <= 0, (block, w, float(a.flatten()[w]), float(b.flatten()[w]))
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,TT,long", [(16, 14, 2, 64, 6000), (64, 2, 2, 40, 5000), (16, 32, 8, 96, 7000)])
+def test_balanced_schedule_merges_of_many_parts(B, Hq, Hkv, TT, long):
+    # one long sequence among short ones, cut into 50, 80 and 18 key ranges of one sequence: the merge is shared by the
+    # workgroups that are there.  Against the oracle; then the same bits whatever the workspace held before, and from a replayed
+    # graph whose launch keeps its number while lengths (so what is cut where) and workspace change between the replays.
+    params = [(TT if b % 5 < 4 else 9, 5, 6) for b in range(B)]
+    case = oracle_case(0, cfg=_cfg("bf16", 128, params, [long] + [7 + 40 * (b % 5) for b in range(1, B)], Hq, Hkv))
+    st = check_case(case)
+    lengths = [st.prefix_len.clone()]
+    for cut in (2, 64):
+        lengths.append(torch.clamp(lengths[0] // cut, min=1))
+
+    def run():
+        st.tree_attention()
+        return [st.out[b, :case.trees[b]["n_nodes"]].view(torch.int16).clone() for b in range(B)]
+
+    want = []
+    for plen in lengths:
+        st.prefix_len.copy_(plen)
+        want.append(run())
+        for fill in (0x00, 0xff, 0x3f):
+            st.ws.fill_(fill)
+            st.out.fill_(7.0)
+            assert all(torch.equal(x, y) for x, y in zip(run(), want[-1])), fill
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        g = torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(g, stream=side):
+            st.tree_attention()
+    for rep, (which, fill) in enumerate([(0, None), (0, None), (1, None), (2, 0x5a), (1, None), (0, 0xff), (0, None)]):
+        st.prefix_len.copy_(lengths[which])
+        if fill is not None:
+            st.ws.fill_(fill)
+        st.out.fill_(7.0)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        got = [st.out[b, :case.trees[b]["n_nodes"]].view(torch.int16) for b in range(B)]
+        assert all(torch.equal(x, y) for x, y in zip(got, want[which])), rep
