@@ -9,10 +9,11 @@
 // row-major; the V operand comes from the transposing LDS read.  The keys of a sequence may be split
 // across workgroups, which leave partial max / sum / O, when a batch offers too few
 // (sequence, kv head, row tile) items to fill the chip (small batches, merged by a second kernel) or items of
-// different lengths (large batches, merged by the workgroup that comes last).  The ancestor bitset is
-// applied only to key blocks that contain tree keys.
+// different lengths (large batches, merged by the workgroup that comes last, or by all that stayed to see it come).
+// The ancestor bitset is applied only to key blocks that contain tree keys.
 //
-// Other head sizes and fp32: plain ALU kernel, one workgroup per (node, head).
+// fp32 heads of 64 and 128: sixteen lanes to a key (attn_f32_kernel); every other head size and type, and bf16 caches whose
+// strides are not multiples of 16 bytes: attn_simple_kernel.  Plain ALU kernels, one workgroup per (node, head).
 
 #include <atomic>
 #include <type_traits>
@@ -48,15 +49,6 @@ __device__ __forceinline__ bf16x4 lds_read_tr4(const __bf16 *p) {
     return __builtin_bit_cast(bf16x4, v);
 }
 
-// The same two LDS reads as bare instructions, for loops that keep the wait counters by hand: the
-// compiler neither counts them nor guards them with a wait for outstanding global_load_lds traffic
-// (it cannot tell a read of one tile from a read of the tile still being filled).  lds_wait<N> lets at
-// most N later LDS operations stay outstanding and ties the wait to the register it releases.
-__device__ __forceinline__ bf16x8 lds_load128(u32 addr) {
-    bf16x8 v;
-    asm volatile("ds_read_b128 %0, %1" : "=v"(v) : "v"(addr));
-    return v;
-}
 // Four global_load_lds_dwordx4, 64 bytes apart in memory and STEP bytes apart in LDS, with the address split into a
 // wave-uniform base (scalar registers) and a 32-bit per-lane byte offset, the LDS destination (wave-uniform, the lanes' 16 bytes
 // follow each other) in M0: no vector arithmetic per load, and no 64-bit per-lane pointers to keep and advance.  The
@@ -80,6 +72,10 @@ __device__ __forceinline__ gbf16p uniform_ptr(gbf16p p) {
     const u32 lo = __builtin_amdgcn_readfirstlane((u32)v), hi = __builtin_amdgcn_readfirstlane((u32)(v >> 32));
     return (gbf16p)(uintptr_t)(((u64)hi << 32) | lo);
 }
+// The same two LDS reads as bare instructions, for loops that keep the wait counters by hand: the
+// compiler neither counts them nor guards them with a wait for outstanding global_load_lds traffic
+// (it cannot tell a read of one tile from a read of the tile still being filled).  lds_wait<N> lets at
+// most N later LDS operations stay outstanding and ties the wait to the register it releases.
 template <int OFF>
 __device__ __forceinline__ bf16x8 lds_load128_at(u32 addr) {
     bf16x8 v;
@@ -1795,7 +1791,10 @@ int attn_launch(const AttnArgs &a, hipStream_t st, hipError_t *err) {
     const int G = a.Hq / a.Hkv;
     const int mtiles = (a.TT_cap * G + ATT_MTILE - 1) / ATT_MTILE;
     const int base_wgs = a.batch * a.Hkv * mtiles;
-    // few (sequence, kv head, row tile) items: the barrier-free small-batch kernel (64-wide heads: always)
+    // Few (sequence, kv head, row tile) items: the barrier-free small-batch kernel.  64-wide heads take it at every batch: the
+    // large-batch tiles are laid out for 128 columns, and against the plain kernel (the same call on a cache whose strides keep
+    // it off the matrix cores) it is ahead at both ends, one sequence of 8 nodes and 40 keys 5.1 us against 7.5, 3 of 64 and
+    // 1,500 12.9 against 206, 64 of 128 and 4,000 455 against 19,500.
     if (a.D == 64) return wave_launch<64>(a, st, err);
     if (base_wgs < 128) return wave_launch<128>(a, st, err);
     // The balanced schedule wherever its plan fits (one lane per sequence, a slot for every tile count): also for batches of

@@ -166,12 +166,4 @@ __device__ __forceinline__ float philox_uniform(u64 seed, u64 step, u32 seq, u32
     return (float)(x >> 8) * (1.0f / 16777216.0f);
 }
 
-// (max, sum of exp relative to max) pairs: the associative combine of log-sum-exp partials.
-__device__ __forceinline__ void lse_combine(float &m, float &s, float m2, float s2) {
-    float M = fmaxf(m, m2);
-    if (M == -INFINITY) { m = M; s = 0.f; return; }
-    s = s * __expf(m - M) + s2 * __expf(m2 - M);
-    m = M;
-}
-
 }  // namespace dt
