@@ -194,6 +194,8 @@ __device__ __forceinline__ bool arrive_last(u64 *count, u64 tag, int parts) {
 // query heads to each of two kv heads, one of 16,384 among 15 of 128 (52 parts): 130 and 42; eight kv heads, one of 8,192
 // among 15 of 256 (18 parts): 55 and 46.  (Marks, but all parts read by the last to come: 132, 78, 54; a merge kernel: 53,
 // 46, 51.)
+// Fewer parts are read faster by one workgroup that has the last of them in registers than left, marked and shared: 16 ragged
+// sequences in up to 3 parts 155 us a step, 177 shared; 8 of up to 5, four layers, 497 and 507 to 522.
 #define SERIAL_PARTS 8
 #define MERGE_SLICES 16
 #define STAY_TICKS 5000  // of 10 ns

@@ -78,7 +78,7 @@ struct __attribute__((aligned(16))) Parent {
 };
 struct TreeLds {
     float score[DT_P_MAX];         // cumulative score of a candidate
-    float lp[DT_P_MAX];            // its own log-probability (-inf: does not exist) and token, kept for the
+    float lp[DT_P_MAX];            // its own log-probability (finite, or -inf: does not exist) and token, kept for the
     int tok[DT_P_MAX];             // emission: the kernel then ends without another trip to memory
     int16_t node[DT_P_MAX];        // node number after the rerank, -1: not kept
     int8_t slot[DT_P_MAX];         // slot in its level's expanded set, -1: not expanded
@@ -293,11 +293,6 @@ __device__ __forceinline__ void emit_level(const TreeArgs &a, const TreeLds &S, 
     if (lane == 0) { a.n_expand[b] = n_exp; a.state_n_exp[b] = n_exp; }
 }
 
-// Score of a candidate.  A parent that does not exist (score -inf) has no children, whatever stands where their own
-// log-probabilities would: LDS that nothing wrote (lanes past the level's candidates), a state row of an earlier step, a row
-// of logits that belongs to no node.  (-inf plus an infinity or a NaN there would be a NaN, whose key lies above all.)
-__device__ __forceinline__ float child_score(float parent, float own) { return parent == -INFINITY ? -INFINITY : parent + own; }
-
 // All levels, by one wave: G candidates per lane, 64 G >= k^2.  Returns the end of the pool (levels computed so far), or -1
 // when only level `xl` was wanted and has been written.  LDS is written and read by this wave alone, in order.
 template <int G>
@@ -311,7 +306,7 @@ __device__ __forceinline__ int levels_narrow(const TreeArgs &a, TreeLds &S, int 
 #pragma unroll
     for (int q = 0; q < G; ++q) {
         parent[q] = lane + 64 * q < kk ? fdiv(lane + 64 * q, ps.inv_k) : DT_K_MAX;
-        at[q] = k + lane + 64 * q;
+        at[q] = k + min(lane + 64 * q, kk - 1);  // no candidate: the last one's place, and a parent that does not exist
         own[q] = S.lp[at[q]];
     }
     if (lane < DT_D_MAX) S.par[lane][DT_K_MAX].score = -INFINITY;
@@ -332,11 +327,11 @@ __device__ __forceinline__ int levels_narrow(const TreeArgs &a, TreeLds &S, int 
         // level l + 1: score = score[parent] + lp
         float sc[G];
         u64 path[G];
-        const float f = child_score(S.par[l][min(lane, DT_K_MAX)].score, best_own);
+        const float f = S.par[l][min(lane, DT_K_MAX)].score + best_own;
 #pragma unroll
         for (int q = 0; q < G; ++q) {
             const Parent pr = S.par[l][parent[q]];
-            sc[q] = child_score(pr.score, own[q]);
+            sc[q] = pr.score + own[q];
             path[q] = pr.path;
         }
 #pragma unroll
@@ -449,11 +444,11 @@ __device__ __forceinline__ int levels_wide(const TreeArgs &a, TreeLds &S, int b,
         __syncthreads();
         if (S.n_exp == 0) break;
         // every wave: the bound; two candidates per thread scored; those above it into the list
-        const float f = child_score(S.par[l][min(lane, DT_K_MAX)].score, first);
+        const float f = S.par[l][min(lane, DT_K_MAX)].score + first;
         float sc[2];
         u32 key[2];
 #pragma unroll
-        for (int q = 0; q < 2; ++q) sc[q] = child_score(S.par[l][parent[q]].score, own[q]);
+        for (int q = 0; q < 2; ++q) sc[q] = S.par[l][parent[q]].score + own[q];
         level_bounds(score_key(f), k, lo_key, hi_key);
         u64 m[2];
 #pragma unroll
@@ -682,7 +677,10 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
         const int row = e / DT_K_MAX, rank = e % DT_K_MAX;
         if (row < R && rank < k) {
             const int p = row == 0 ? rank : k + (row - 1) * k + rank;
-            S.lp[p] = v > -INFINITY && row < owned ? v - row_lse : -INFINITY;
+            // Neither +inf nor a NaN: children of slots without a node (score -inf) count on -inf plus this being -inf,
+            // and their rows may hold anything: a state row of an earlier step, logits that belong to no node.
+            const float lp = v - row_lse;
+            S.lp[p] = lp < INFINITY && row < owned ? lp : -INFINITY;
             S.tok[p] = token;
         }
     };
