@@ -28,8 +28,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef u32 u32x4 __attribute__((ext_vector_type(4)));
-typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 // Global-address-space views: pointers fetched from memory (the per-sequence prefix pointers)
 // would otherwise be generic, and generic loads also count against the LDS wait counter.
 typedef const __bf16 __attribute__((address_space(1))) *gbf16p;
@@ -920,7 +918,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_wave_kernel(AttnArgs a, int K
     // 64-wide heads keep their probabilities in 32 bits: as the sum of three bf16 numbers, 24 bits of significand, which
     // multiply the same V operand one after the other.  Error against 64-bit arithmetic over 1 to 8 sequences of 16 to 4,000
     // keys: 1.6616e-3 of the result, what the plain kernel has (the rounding of the result itself), against 2.0231e-3 with
-    // probabilities rounded to bf16; a step of three such sequences takes 44.6 us instead of 43.4.
+    // probabilities rounded to bf16.  It costs a step of three sequences 0.6 us of 43.8, and where every compute unit has work
+    // for several rounds a third: 16 sequences of 96 nodes and 2,000 keys 74 -> 100 us, 64 of 1,000 keys 188 -> 234.
     constexpr int PARTS = D == 64 ? 3 : 1;
     if constexpr (DIRECT) {
         // Blocks go straight from global memory into the wave's own LDS tiles (global_load_lds_dwordx4:
@@ -1110,6 +1109,9 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_wave_kernel(AttnArgs a, int K
         }
     };
 
+    // All blocks of this wave; by_key: the second product in 32 bits, key by key (a loop of its own: a branch in the other one
+    // made the compiler copy the accumulators in every block, 10 % of it)
+    auto walk = [&](auto by_key) __attribute__((always_inline)) {
     int kb = ks * NW + w;
     if (kb < nb) fetch(kb);
     for (; kb < nb; kb += kstep) {
@@ -1120,18 +1122,6 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_wave_kernel(AttnArgs a, int K
             const int r = RPL * i + kq;
             *(bf16x8 *)(kt + r * K_PITCH + 8 * dc) = kn[i];
             *(bf16x8 *)(vt + r * V_PITCH + 8 * dc) = vn[i];
-        }
-        // An infinity or a NaN in V must not reach the queries that give its key no weight, and the parts of a probability
-        // must not meet it with different signs: such a block's second product is taken in 32 bits, key by key.  (The test: 0.3 us of a step of 45.)
-        bool finite = true;  // uniform
-        if constexpr (PARTS > 1) {
-            u16x2 top = {0, 0};  // largest magnitude of the lane's V elements
-#pragma unroll
-            for (int i = 0; i < NLD; ++i)
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    top = __builtin_elementwise_max(top, __builtin_bit_cast(u16x2, __builtin_bit_cast(u32x4, vn[i])[e] & 0x7FFF7FFFu));
-            finite = !__builtin_amdgcn_ballot_w64(max(top[0], top[1]) >= 0x7F80);
         }
         if (kb + kstep < nb) fetch(kb + kstep);
 
@@ -1177,13 +1167,16 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_wave_kernel(AttnArgs a, int K
         for (int i = 0; i < 16; ++i) {
             const float p = __builtin_amdgcn_exp2f(fmaf(sacc[i], c, nmc));
             psum += p;
-            sacc[i] = p;
-            float rest = p;
+            if constexpr (decltype(by_key)::value) sacc[i] = p;
+            if constexpr (PARTS == 1) pb[0][i >> 3][i & 7] = (__bf16)p;
+            else {
+                float rest = p;
 #pragma unroll
-            for (int q = 0; q < PARTS; ++q) {
-                const __bf16 part = (__bf16)rest;
-                pb[q][i >> 3][i & 7] = part;
-                rest -= (float)part;  // exact
+                for (int q = 0; q < PARTS; ++q) {  // the upper half of what is left; every remainder is exact
+                    const u32 part = __float_as_uint(rest) & 0xFFFF0000u;
+                    pb[q][i >> 3][i & 7] = __builtin_bit_cast(__bf16, (uint16_t)(part >> 16));
+                    rest -= __uint_as_float(part);
+                }
             }
         }
         l_run = l_run * alpha + psum;
@@ -1199,7 +1192,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_wave_kernel(AttnArgs a, int K
         // O^T += V^T P^T.  The A operand of lane (column d = 32db + col, half) holds, for e = 0..7,
         // V[key 16st + 8(e/4) + 4half + e%4][d]: two transposing LDS reads of 4 keys each.  In a
         // 16-lane group lane p = 4j+q points at key j of the quadruple, columns d0 + 4q..4q+3.
-        if (finite) {
+        if constexpr (!decltype(by_key)::value) {
             const int p16 = lane & 15;
             const __bf16 *vbase = vt + (4 * half + (p16 >> 2)) * V_PITCH + 16 * ((lane >> 4) & 1) + 4 * (p16 & 3);
 #pragma unroll
@@ -1213,7 +1206,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_wave_kernel(AttnArgs a, int K
                     for (int q = 0; q < PARTS; ++q)
                         oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pb[q][st], oacc[db], 0, 0, 0);
                 }
-        } else if constexpr (PARTS > 1) {
+        } else {
             float *pt = (float *)kt;  // [32 keys][32 queries], in the place of the K tile, which has been read
             static_assert(ATT_KB * 32 * 4 <= WaveTile<D>::K_ELEMS * 2, "probabilities in the K tile");
             asm volatile("" ::: "memory");  // the tile changes its type: nothing moves across
@@ -1234,6 +1227,27 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_wave_kernel(AttnArgs a, int K
                     }
             }
             asm volatile("" ::: "memory");
+        }
+    }
+    };
+    walk(std::false_type());
+    if constexpr (PARTS > 1) {
+        // An infinity or a NaN in V must not reach the queries that give its key no weight, and the parts of a probability must
+        // not meet it with different signs.  Whatever it meets, it leaves an accumulator that is not finite: then the wave
+        // starts again and takes its second products in 32 bits, key by key.
+        float odd = 0.f;
+#pragma unroll
+        for (int db = 0; db < DBLK; ++db)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) odd = fmaf(oacc[db][i], 0.f, odd);
+        if (__builtin_amdgcn_ballot_w64(odd != 0.f)) {
+            m_run = -INFINITY;
+            l_run = 0.f;
+#pragma unroll
+            for (int db = 0; db < DBLK; ++db)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) oacc[db][i] = 0.f;
+            walk(std::true_type());
         }
     }
 
