@@ -11,7 +11,7 @@ for the other bf16 configurations (`per_config`), and the CPU oracle timed on th
 Inputs are synthetic and resident in HBM before any timed region.  A timed loop rotates over `copies`
 distinct input sets (16 x 34 MB > the 256 MB last-level cache) so that every step streams its logits and KV
 from HBM.  The rotation is captured once in a HIP graph and replayed (a step is three library calls = seven
-kernels; launch overhead would otherwise be most of a 50 us step); --eager times plain stream launches.
+kernels; launch overhead would otherwise be most of a 40 us step); --eager times plain stream launches.
 """
 import argparse
 import json

@@ -44,7 +44,7 @@ def kernels(db, cmd):
                                                          "%dx%dx%d" % (r[6], r[7], r[8]), r[9]))
     tot = sum(r[5] for r in rows if OURS in r[0])
     calls = max((r[1] for r in rows if "tree_kernel" in r[0]), default=0)
-    if calls:
+    if calls and all(abs(r[1] - calls) <= 1 for r in rows if OURS in r[0]):  # every kernel once a step
         print("# sum of the library's kernels per step: %.2f us over %d steps" % (tot / 1e3 / calls, calls))
 
 
