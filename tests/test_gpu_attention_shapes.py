@@ -5,8 +5,9 @@ import numpy as np
 import pytest
 
 import dt_synth
+from oracle import ref
 from tests._cases import oracle_case
-from tests.test_gpu_parity import check_case, make_step
+from tests.test_gpu_parity import assert_attention, check_case, make_step
 
 pytestmark = pytest.mark.gpu
 
@@ -196,3 +197,22 @@ def test_balanced_schedule_merges_of_many_parts(B, Hq, Hkv, TT, long):
         torch.cuda.synchronize()
         got = [st.out[b, :case.trees[b]["n_nodes"]].view(torch.int16) for b in range(B)]
         assert all(torch.equal(x, y) for x, y in zip(got, want[which])), rep
+
+
+def test_shared_merge_at_its_edges():
+    # one block to a part: a sequence of n blocks has n parts.  The most that one workgroup merges and one more, the parts that
+    # are in flight together, the marks that a wave looks at together
+    B, TT = 64, 40
+    cfg = _cfg("bf16", 128, [(TT, 5, 6)] * B, [64 * 80 - TT] + [7 + 40 * (b % 3) for b in range(1, B)], 2, 2)
+    case = oracle_case(0, cfg=cfg)
+    st = make_step(case)
+    st.build_tree()
+    n = case.trees[0]["n_nodes"]
+    assert n == TT
+    q, kt, vt, kp, vp = dt_synth.qkv(cfg, 0)
+    for blocks in (8, 9, 16, 17, 32, 33, 64, 65, 80):
+        L = 64 * blocks - TT
+        st.prefix_len[0] = L
+        st.tree_attention()
+        want = ref.tree_attention(q[:n], kt[:n], vt[:n], kp[:L], vp[:L], case.trees[0]["anc_mask"], st.scale)
+        assert_attention(st.attention_out(0), want, "bf16", "%d parts" % blocks)
