@@ -111,7 +111,7 @@ inline ArgmaxScratch argmax_scratch(void *ws, int64_t rows, int S) {
     r.bytes = kb + align_up((size_t)rows * S * 8);
     return r;
 }
-struct TopkScratch {  // top-k rows: [rows, S*256] lane maxima, [rows, S*4] (max, sum) pairs
+struct TopkScratch {  // top-k rows: [rows, S*128] maxima of pairs of lanes (room for [rows, S*256] floats), [rows, S*4] (max, sum) pairs
     float *lane_max;
     float2 *ms;
     size_t bytes;

@@ -42,7 +42,7 @@ struct RowArgs {
     int want_lse;
     float inv_t;          // 1 / temperature applied inside the exponentials
     unsigned long long *part_keys;  // arg max rows: [rows, S] best key of every chunk
-    void *lane_max;       // top-k rows: [rows, S*256] one maximum per lane, in the type of the logits
+    void *lane_max;       // top-k rows: [rows, S*128] one maximum per pair of lanes, in the type of the logits
     float2 *part_ms;      // (max, sum exp((x-max)*inv_t)): [rows, S] (arg max rows), [rows, S*4] (top-k rows)
     // ROWS_LEVEL: rows of one level of every sequence, results scattered into the build state
     int level, rows_per_seq, state_rows;

@@ -3,10 +3,10 @@
 //
 // Top-k rows of up to 16,384 entries are held by one workgroup each (row_topk_kernel).  Longer ones take two passes.  The
 // first is a pure stream: a row is cut into chunks of
-// 256*8*NL elements, each lane reads 8*NL of them with coalesced 16-byte loads and leaves
+// 256*8*NL elements, each lane reads 8*NL of them with coalesced 16-byte loads, and a pair of lanes leaves
 // only its maximum (plus one (max, sum-exp) pair per wave).  The second works on those lane
-// maxima, 8*NL times fewer than the logits: the k-th largest lane maximum bounds the k-th
-// largest element from below, so only the ~k lanes that reach it are read again and their
+// maxima, 16*NL times fewer than the logits: the k-th largest lane maximum bounds the k-th
+// largest element from below, so only the ~k pairs that reach it are read again and their
 // elements ranked by 64-bit (value, id) keys -- exact under (value desc, id asc).  Rows
 // dominated by ties fall back to a slow exact loop.
 #include <type_traits>
@@ -185,8 +185,10 @@ __device__ __forceinline__ float2 wave_lse_partial(const float (&x)[E], float mx
 
 // ------------------------------------------------------------ streaming kernel (top-k rows) --
 // Pure stream: every wave reads its 64*8*NL elements once and leaves behind one maximum per
-// lane and one (max, sum) pair per wave.  No LDS, no barrier.  All selection happens later on
-// the lane maxima, which are 8*NL times fewer than the logits.
+// pair of lanes and one (max, sum) pair per wave.  No LDS, no barrier.  All selection happens later on
+// the lane maxima, which are 16*NL times fewer than the logits.
+// (One per lane, the four waves of a chunk interleaved, was 3 % of the traffic, in 2-byte pieces eight bytes apart: 1.55 GB of
+// rows 299 us, 292 with a pair's maximum and a wave's side by side; 156 MB 31.9 and 30.2.)
 template <bool BF16>
 using LaneMax = std::conditional_t<BF16, uint16_t, float>;
 template <bool BF16>
@@ -200,43 +202,55 @@ __device__ __forceinline__ float lane_max_value(LaneMax<BF16> v) {
     else return v;
 }
 
-template <int MODE, int NL, bool BF16>
-__global__ __launch_bounds__(256) void row_stream_kernel(RowArgs a) {
+// CPW chunks of a row per workgroup, one after the other, the next one's elements on their way while one is worked on.
+template <int MODE, int NL, bool BF16, int CPW>
+__global__ __launch_bounds__(256) void row_stream_kernel(RowArgs a, int S) {
     constexpr int E = 8 * NL;
-    // workgroup (chunk c, row g): the chunk rides in grid x, the row in y and -- past 65,535 rows -- z
+    // workgroup (chunks c0 .., row g): the chunks ride in grid x, the row in y and -- past 65,535 rows -- z
     // (no division in front of the loads: a streaming workgroup's life is one trip to memory long)
     const int64_t g = (int64_t)blockIdx.z * gridDim.y + blockIdx.y;
-    const int c = blockIdx.x;
+    const int c0 = blockIdx.x * CPW;
     const int lane = lane_id(), w = threadIdx.x >> 6;
-    const int base = c * (256 * E) + w * (64 * E) + lane * 8;
+    const int base = c0 * (256 * E) + w * (64 * E) + lane * 8;
     if (g >= a.n_rows) return;
     // early: the row's elements are on their way while the (dependent, scalar) reads of its metadata are waited for
-    RawChunk<NL, BF16> raw;
-    if (a.early_load) chunk_request<NL, BF16, true>(a, g, base, raw);
+    RawChunk<NL, BF16> raw[CPW > 1 ? 2 : 1];
+    if (a.early_load) chunk_request<NL, BF16, true>(a, g, base, raw[0]);
     if (!row_meta<MODE>(a, g).valid) return;
-    if (!a.early_load) chunk_request<NL, BF16, true>(a, g, base, raw);
-    float x[E];
-    chunk_finish<NL, BF16, true>(a, g, base, (c + 1) * (256 * E), raw, x);
-    float mx = x[0];
+    if (!a.early_load) chunk_request<NL, BF16, true>(a, g, base, raw[0]);
 #pragma unroll
-    for (int j = 1; j < E; ++j) mx = fmaxf(mx, x[j]);
-    // lane maxima in the row's own precision (exact), the four waves of a chunk interleaved
-    const int64_t chunk = g * gridDim.x + c;
-    ((LaneMax<BF16> *)a.lane_max)[chunk * 256 + lane * 4 + w] = lane_max_pack<BF16>(mx);
-    if (a.want_lse) {
-        const float2 p = wave_lse_partial<E>(x, mx, a.inv_t);
-        if (lane == 0) a.part_ms[chunk * 4 + w] = p;
+    for (int i = 0; i < CPW; ++i) {
+        const int c = c0 + i;
+        if (CPW > 1 && c >= S) return;
+        if (i + 1 < CPW) chunk_request<NL, BF16, true>(a, g, base + (i + 1) * (256 * E), raw[(i + 1) & 1]);  // past the row: its last elements again
+        float x[E];
+        chunk_finish<NL, BF16, true>(a, g, base + i * (256 * E), (c + 1) * (256 * E), raw[i & 1], x);
+        float mx = x[0];
+#pragma unroll
+        for (int j = 1; j < E; ++j) mx = fmaxf(mx, x[j]);
+        // maxima of two lanes in the row's own precision (exact)
+        const int64_t chunk = g * S + c;
+        const float mx2 = fmaxf(mx, __int_as_float(dpp_mov<0xB1, 0xf>(0, __float_as_int(mx))));  // lane ^ 1
+        if ((lane & 1) == 0) {
+            LaneMax<BF16> *lm = (LaneMax<BF16> *)a.lane_max + chunk * 128 + w * 32 + (lane >> 1);
+            if (CPW > 1) __builtin_nontemporal_store(lane_max_pack<BF16>(mx2), lm);
+            else *lm = lane_max_pack<BF16>(mx2);
+        }
+        if (a.want_lse) {
+            const float2 p = wave_lse_partial<E>(x, mx, a.inv_t);
+            if (lane == 0) a.part_ms[chunk * 4 + w] = p;
+        }
     }
 }
 
 // ------------------------------------------------------------- selection kernel (top-k rows) --
-// One workgroup per row, working on the row's S*256 lane maxima:
+// One workgroup per row, working on the row's S*128 lane maxima:
 //   1. every thread takes the maximum of the lane maxima it holds; the 256 thread maxima meet in LDS as 16-bit keys
 //      (the upper half of the ordered integer image: all of it for bf16 data) and every wave finds the k-th largest by
 //      itself, four keys to a lane, by bisection over ballots.  T, the lower edge of that key, is a lower bound of the
 //      row's k-th largest ELEMENT (k threads hold one >= T), and because a thread's lane maxima come from places far
 //      apart in the row, little more than k lane maxima reach it;
-//   2. the 8*NL elements of the lanes that reach T are read again, (lane, load) pairs over the threads, and the elements
+//   2. the 16*NL elements of the pairs of lanes that reach T are read again, (pair, group of eight) over the threads, and the elements
 //      >= T are keyed by (value, id) and ranked by counting.
 // More than 128 such elements (clusters, ties), or a vocabulary of more than 16 chunks, take a second bound first: a
 // histogram of the lane maxima that reach T names the bin of the k-th largest lane maximum.  If that leaves too many as
@@ -305,21 +319,21 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
     const int64_t g = blockIdx.x;
     const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int V = a.V, E = 8 * nl;
-    const int n_lanes = S * 256;
+    const int n_lm = S * 128;
     typedef LaneMax<BF16> LM;
-    const LM *lm = (const LM *)a.lane_max + g * n_lanes;
+    const LM *lm = (const LM *)a.lane_max + g * n_lm;
     // the lane maxima do not depend on the row's metadata (two dependent global reads): ask for them
     // first, and wave 3 for the row's (max, sum) partials.  Rows that turn out to be dead have their
     // slots in the workspace all the same.
-    // Thread tid holds lane maxima 4 (256 i + tid) .. + 3, i < S / 4 (the same lane of a chunk's four waves: one load).
+    // Thread tid holds lane maxima 4 (256 i + tid) .. + 3, i < S / 8.
     struct alignas(4 * sizeof(LM)) Quad { LM v[4]; };
-    float it[16];
+    float it[8];
     if (S <= 16) {
-        Quad q[4];
+        Quad q[2];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) q[i] = ((const Quad *)lm)[min(256 * i + tid, S * 64 - 1)];
+        for (int i = 0; i < 2; ++i) q[i] = ((const Quad *)lm)[min(256 * i + tid, S * 32 - 1)];
 #pragma unroll
-        for (int j = 0; j < 16; ++j) it[j] = lane_max_value<BF16>(q[j >> 2].v[j & 3]);
+        for (int j = 0; j < 8; ++j) it[j] = lane_max_value<BF16>(q[j >> 2].v[j & 3]);
     }
     const bool lse_wave = w == 3 && a.want_lse && lse;
     float2 pm = make_float2(-INFINITY, 0.f);
@@ -366,11 +380,11 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
         term = wave_sum(term);
         if (lane == 0) lse[meta.out] = (Mw == -INFINITY) ? -INFINITY : Mw * a.inv_t + __logf(term);
     };
-    // The eight elements of load n of lane maximum i (chunk, lane, wave): those that reach T become candidates, room for
-    // them with one LDS add.
-    const int nl_log2 = nl == 4 ? 2 : nl == 2 ? 1 : 0;  // chunk multipliers are 1, 2 or 4
+    // Eight elements of lane maximum i (chunk, wave, pair of lanes), those of load n / 2 and lane n % 2 of the pair: the ones that
+    // reach T become candidates, room for them with one LDS add.
+    const int per_log2 = nl == 4 ? 3 : nl == 2 ? 2 : 1;  // groups of eight: chunk multipliers are 1, 2 or 4
     auto reread = [&](int i, int n, float T) {
-        const int id0 = (i >> 8) * (256 * E) + (i & 3) * (64 * E) + ((i >> 2) & 63) * 8 + n * 512;
+        const int id0 = (i >> 7) * (256 * E) + ((i >> 5) & 3) * (64 * E) + (2 * (i & 31) + (n & 1)) * 8 + (n >> 1) * 512;
         float xv[8];
         const int start = load_octet<BF16>(a, g, id0, xv);
         int hits = 0;
@@ -409,12 +423,12 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
     float tmax = -INFINITY;
     if (S <= 16) {
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            it[j] = 256 * (j >> 2) + tid < S * 64 ? it[j] : -INFINITY;
+        for (int j = 0; j < 8; ++j) {
+            it[j] = 256 * (j >> 2) + tid < S * 32 ? it[j] : -INFINITY;
             tmax = fmaxf(tmax, it[j]);
         }
     } else {
-        for (int j = 0; j < S; ++j) tmax = fmaxf(tmax, lane_max_value<BF16>(lm[j * 256 + tid]));
+        for (int i = tid; i < n_lm; i += 256) tmax = fmaxf(tmax, lane_max_value<BF16>(lm[i]));
     }
     s_key[tid] = (uint16_t)(ord32(tmax) >> 16);
     if (tid < SEL_CAP) s_fin[tid] = 0ull;
@@ -431,7 +445,7 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
         // counter, no barrier), then (hot lane, load n) pairs over its lanes.
         u32 hot = 0;
 #pragma unroll
-        for (int j = 0; j < 16; ++j) hot |= (it[j] >= T0 ? 1u : 0u) << j;
+        for (int j = 0; j < 8; ++j) hot |= (it[j] >= T0 ? 1u : 0u) << j;
         const int mine = __popc(hot), incl = wave_scan_incl_i32(mine);
         const int h = __builtin_amdgcn_readlane(incl, 63);
         if (h > SEL_WAVE_CAP) {  // ties: this bound does not cut
@@ -443,7 +457,7 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
                 list[at++] = 4 * (256 * (j >> 2) + tid) + (j & 3);
             }
             __builtin_amdgcn_wave_barrier();
-            for (int q = lane; q < h * nl; q += 64) reread(list[q >> nl_log2], q & (nl - 1), T0);
+            for (int q = lane; q < h << per_log2; q += 64) reread(list[q >> per_log2], q & ((1 << per_log2) - 1), T0);
         }
         __syncthreads();
         const int n2 = s_n2;
@@ -460,11 +474,11 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
     }
 
     // ---- second bound: histogram of the lane maxima >= T0; its scan from the top gives T1 ------------
-    auto lane_val = [&](int j) { return lane_max_value<BF16>(lm[j * 256 + tid]); };
+    auto lane_val = [&](int i) { return lane_max_value<BF16>(lm[i]); };
     s_hist[tid] = 0u;
     __syncthreads();
-    for (int j = 0; j < S; ++j) {
-        const float v = lane_val(j);
+    for (int i = tid; i < n_lm; i += 256) {
+        const float v = lane_val(i);
         if (v >= T0) atomicAdd(&s_hist[min((ord32(v) >> 16) - key0, 255u)], 1u);
     }
     __syncthreads();
@@ -492,14 +506,14 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
         T1 = key_edge(key0 + (u32)(4 * (63 - ls) + dg));
     }
     if (n_hot <= SEL_CAP && n_hot >= k) {  // uniform over the workgroup
-        for (int j = 0; j < S; ++j)
-            if (lane_val(j) >= T1) {
+        for (int i = tid; i < n_lm; i += 256)
+            if (lane_val(i) >= T1) {
                 const int at = atomicAdd(&s_h, 1);
-                if (at < SEL_CAP) s_hot[at] = j * 256 + tid;
+                if (at < SEL_CAP) s_hot[at] = i;
             }
         __syncthreads();
         const int h = min(s_h, SEL_CAP);
-        for (int q = tid; q < h * nl; q += 256) reread(s_hot[q >> nl_log2], q & (nl - 1), T1);
+        for (int q = tid; q < h << per_log2; q += 256) reread(s_hot[q >> per_log2], q & ((1 << per_log2) - 1), T1);
         __syncthreads();
         const int n2 = s_n2;
         if (n2 <= SEL_CAP) {
@@ -795,6 +809,11 @@ static void by_mode_and_type(const RowArgs &a, F f) {
 // that a policy may set on the device is mostly dead rows (two sequences, 450 rows of 128,256 for the widest action:
 // 21.8 us when all were read, 8-13 us when a row's liveness is looked up first).
 static const int64_t EARLY_LOAD_WGS = 2048;
+// Launches of more chunks than this take two to a workgroup: the trip in front of the loads (whose row is it, is it live) is made half
+// as often, and the second chunk's elements are on their way under the exponentials of the first.  1.55 GB of draft rows (96,700 chunks)
+// 291 -> 266 us, 667 MB (41,600) 125 -> 116, 357 MB (22,300) 65 -> 63.5; 156 MB (9,700) 30.1 against 30.6, 87 MB (5,400) 18.4 against
+// 19.8; four to a workgroup 267, - , - , 32.0, 21.4.
+static const int64_t PAIR_CHUNKS = 16384;
 
 // top-k rows, pass 1: lane maxima and (max, sum) partials
 static hipError_t launch_stream(const RowArgs &a_in, int64_t n_rows, int nl, hipStream_t st) {
@@ -803,14 +822,21 @@ static hipError_t launch_stream(const RowArgs &a_in, int64_t n_rows, int nl, hip
     a.early_load = n_rows * S <= EARLY_LOAD_WGS;
     const int kid = a.mode == ROWS_DRAFT ? KID_ROWS_DRAFT : KID_ROWS_UNIFORM;
     a.n_rows = n_rows;
-    const dim3 sgrid = rows_grid((int)S, n_rows);
     using std::integral_constant;
     auto go = [&](auto mode, auto bf16) {
         constexpr int MODE = decltype(mode)::value;
         constexpr bool BF = decltype(bf16)::value;
-        if (nl == 4) launch_kernel(kid, st, row_stream_kernel<MODE, 4, BF>, sgrid, dim3(256), 0, a);
-        else if (nl == 2) launch_kernel(kid, st, row_stream_kernel<MODE, 2, BF>, sgrid, dim3(256), 0, a);
-        else launch_kernel(kid, st, row_stream_kernel<MODE, 1, BF>, sgrid, dim3(256), 0, a);
+        auto launch = [&](auto nl_c) {
+            constexpr int NL = decltype(nl_c)::value;
+            auto with = [&](auto kernel, int cpw) {
+                launch_kernel(kid, st, kernel, rows_grid((int)((S + cpw - 1) / cpw), n_rows), dim3(256), 0, a, (int)S);
+            };
+            if (n_rows * S > PAIR_CHUNKS) with(row_stream_kernel<MODE, NL, BF, 2>, 2);
+            else with(row_stream_kernel<MODE, NL, BF, 1>, 1);
+        };
+        if (nl == 4) launch(integral_constant<int, 4>());
+        else if (nl == 2) launch(integral_constant<int, 2>());
+        else launch(integral_constant<int, 1>());
     };
     by_mode_and_type(a, go);
     return hipGetLastError();

@@ -35,6 +35,34 @@ def test_topk_rows_of_many_rows(V, n):
     check_topk(dt_synth.f32_to_bf16_bits(x), 9)
 
 
+@pytest.mark.parametrize("V,n,bf16", [(32769, 1821, True), (65537, 1821, True), (131072, 1025, True), (131081, 1000, True),
+                                      (16385, 1821, False), (65536, 1025, False)])
+def test_topk_rows_of_launches_that_take_two_chunks_to_a_workgroup(V, n, bf16):
+    """More than 16,384 chunks: odd and even numbers of them to a row, a last one of one element, nine elements and whole."""
+    import paper_2601_12212_amd as dt
+    k, R = 20, 7
+    x = (np.random.default_rng(V + n).standard_normal((R, V)) * 3).astype(np.float32)
+    x[1] = 40.0 + np.random.default_rng(V).integers(0, 3, V)   # three values: ties everywhere
+    x[2, V // 3:V // 3 + 200] += 50.0                          # a cluster of neighbours
+    x[3, -1] = x[3, 0] = 30.0                                  # the ends of the row
+    x[4] = -np.inf
+    x[4, [0, 8, V // 2, V - 2, V - 1]] = 1.5                   # five viable entries
+    rows = dt_synth.f32_to_bf16_bits(x) if bf16 else x
+    wval, widx, wlse = ref.topk_rows(rows, k)
+    which = torch.arange(n, device="cuda") % R
+    logits = dev_logits(rows)[which].contiguous()
+    val = torch.empty((n, k), dtype=torch.float32, device="cuda")
+    idx = torch.empty((n, k), dtype=torch.int32, device="cuda")
+    lse = torch.empty(n, dtype=torch.float32, device="cuda")
+    ws = torch.full((dt.dt_workspace_bytes(1, n, V, 8, 1, 64),), 0x7f, dtype=torch.uint8, device="cuda")
+    dt.dt_topk_rows(logits, k, val, idx, lse, ws)
+    torch.cuda.synchronize()
+    which = which.cpu().numpy()
+    assert np.array_equal(idx.cpu().numpy(), widx[which]) and np.array_equal(val.cpu().numpy(), wval[which])
+    # as for smaller launches: fp32 partial sums against double ones
+    assert np.all(np.abs(lse.cpu().numpy() - wlse[which]) <= 4e-6 * np.maximum(1.0, np.abs(wlse[which])))
+
+
 @pytest.mark.parametrize("V", [1001, 8190, 16381, 40001])
 def test_topk_rows_at_any_two_byte_address(V):
     import paper_2601_12212_amd as dt
