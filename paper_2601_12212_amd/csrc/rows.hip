@@ -549,10 +549,16 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
 // A row of up to 32,768 entries stays in the registers of one workgroup, 8 NL elements per thread: the thread maxima meet in LDS,
 // T is found as in the selection kernel, and the elements that reach it come straight from the registers.  One launch and one
 // trip to memory where the two passes take two and three.  NT threads: the fewest that hold the row with NL <= 4.
+// Behind that trip the waves' instructions bound it, four waves to a SIMD with 1,024 threads: T is found by wave 0 alone while the
+// others sum their exponentials, not by every wave for itself (by all, 50 rows of 8,000 / 16,000 / 32,000 bf16 entries 5.0 / 6.0 /
+// 7.1 us, 2,000 of 1,000 / 8,000 / 16,000 7.3 / 13.7 / 24.9; by one 4.6 / 5.2 / 6.7 and 6.4 / 12.3 / 20.9).  In a small launch with a wave to a SIMD
+// the barrier that this takes costs what it saves, or more (5 rows of 1,024 fp32 entries 3.53 and 3.61): there every wave finds T.
+#define SMALL_ROWS 512  // most rows of a launch that leaves the SIMDs a wave or two of 256-thread workgroups
 template <int MODE, int NL, bool BF16, bool VEC, int NT>
 __global__ __launch_bounds__(NT, NL == 4 ? 4 : 8) void row_topk_kernel(RowArgs a, float *top_val, int32_t *top_id, float *lse, int out_stride) {
     constexpr int E = 8 * NL, NW = NT / 64;
-    const int64_t g = blockIdx.x;
+    const bool lse_wg = a.lse_apart && (int64_t)blockIdx.x >= a.n_rows;
+    const int64_t g = lse_wg ? (int64_t)blockIdx.x - a.n_rows : (int64_t)blockIdx.x;
     const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int V = a.V, base = w * (64 * E) + lane * 8;
     RawChunk<NL, BF16> raw;
@@ -566,6 +572,7 @@ __global__ __launch_bounds__(NT, NL == 4 ? 4 : 8) void row_topk_kernel(RowArgs a
     __shared__ float2 s_ms[NW];
     __shared__ __attribute__((aligned(16))) u64 s_fin[SEL_CAP];
     __shared__ int s_n, s_cnt[3];
+    __shared__ float s_T;
     if (tid < SEL_CAP) s_fin[tid] = 0ull;
     if (tid < 3) s_cnt[tid] = 0;
     if (tid == 0) s_n = 0;
@@ -581,14 +588,31 @@ __global__ __launch_bounds__(NT, NL == 4 ? 4 : 8) void row_topk_kernel(RowArgs a
         mx = fmaxf(mx, gmx[n]);
     }
     s_key[lane * NW + w] = (uint16_t)(ord32(mx) >> 16);
-    if (a.want_lse) {
+    const bool want_lse = a.want_lse && lse_wg == a.lse_apart;
+    auto lse_partial = [&]() {
         const float2 p = wave_lse_partial<E>(x, mx, a.inv_t);
         if (lane == 0) s_ms[w] = p;
+    };
+    auto row_lse = [&]() {  // by one wave, from the waves' partials
+        const float cexp = 1.4426950408889634f * a.inv_t;
+        const float2 p = lane < NW ? s_ms[min(lane, NW - 1)] : make_float2(-INFINITY, 0.f);
+        const float M = wave_max(p.x);
+        const float sum = wave_sum(p.y > 0.f ? p.y * __builtin_amdgcn_exp2f((p.x - M) * cexp) : 0.f);
+        if (lane == 0) lse[meta.out] = M == -INFINITY ? -INFINITY : M * a.inv_t + __logf(sum);
+    };
+    if (lse_wg) {  // uniform over the workgroup
+        lse_partial();
+        __syncthreads();
+        if (w == 0) row_lse();
+        return;
     }
+    const bool by_one = NT >= 512 || a.n_rows > SMALL_ROWS;
+    if (!by_one && want_lse) lse_partial();
     __syncthreads();
     // 256 slots of NW / 4 threads each: k slots that reach T hold k elements that do
-    u32 ky[4];
-    {
+    float T;
+    if (!by_one || w == 0) {
+        u32 ky[4];
         uint16_t kv[NW];
         __builtin_memcpy(kv, __builtin_assume_aligned(&s_key[lane * NW], NW * 2), NW * 2);
 #pragma unroll
@@ -597,8 +621,18 @@ __global__ __launch_bounds__(NT, NL == 4 ? 4 : 8) void row_topk_kernel(RowArgs a
 #pragma unroll
             for (int j = i + 4; j < NW; j += 4) ky[i] = max(ky[i], (u32)kv[j]);
         }
+        T = key_edge(wave_kth_of_256(ky, k));
     }
-    const float T = key_edge(wave_kth_of_256(ky, k));
+    if (by_one) {
+        if (w == 0) {
+            if (lane == 0) s_T = T;
+        } else if (want_lse) {
+            lse_partial();
+        }
+        __syncthreads();
+        T = s_T;
+        if (w == 0 && want_lse) lse_partial();
+    }
     auto id_of = [&](int n, int e) {
         const int id0 = base + n * 512;
         return (VEC ? group_start(V, id0) : id0) + e;
@@ -691,13 +725,7 @@ __global__ __launch_bounds__(NT, NL == 4 ? 4 : 8) void row_topk_kernel(RowArgs a
             tv[lane] = -INFINITY;
             ti[lane] = -1;
         }
-        if (a.want_lse) {
-            const float cexp = 1.4426950408889634f * a.inv_t;
-            const float2 p = lane < NW ? s_ms[min(lane, NW - 1)] : make_float2(-INFINITY, 0.f);
-            const float M = wave_max(p.x);
-            const float sum = wave_sum(p.y > 0.f ? p.y * __builtin_amdgcn_exp2f((p.x - M) * cexp) : 0.f);
-            if (lane == 0) lse[meta.out] = M == -INFINITY ? -INFINITY : M * a.inv_t + __logf(sum);
-        }
+        if (want_lse) row_lse();
     }
 }
 
@@ -853,18 +881,25 @@ static hipError_t launch_select(const RowArgs &a, int64_t n_rows, int nl, float 
     return hipGetLastError();
 }
 
-// rows that a workgroup holds
+// Rows that a workgroup holds.
+static int held_threads(int V) { return V <= 256 * 16 ? 256 : V <= 512 * 16 ? 512 : 1024; }
+// While every row of 1,024 threads leaves another compute unit idle, its exponentials are summed there, by a workgroup of its own that
+// reads the row as well: 16 waves sum 32,000 exponentials in 0.6 us (50 rows of 32,000 bf16 entries 6.7 -> 6.1 us, 120 rows 7.1 -> 6.2,
+// 16,000 entries 5.2 -> 4.95 and 5.4 -> 5.05; 50 rows of 8,000, 512 threads, 4.65 -> 4.80).
+#define APART_ROWS 128
 static hipError_t launch_held(const RowArgs &a_in, int64_t n_rows, float *top_val, int32_t *top_id, float *lse, int out_stride,
                               hipStream_t st) {
     RowArgs a = a_in;
     a.early_load = n_rows * rows_chunks_per_row(a.V, 4) <= EARLY_LOAD_WGS;
     a.n_rows = n_rows;
+    a.lse_apart = a.want_lse && n_rows <= APART_ROWS && held_threads(a.V) == 1024;
+    const int64_t wgs = a.lse_apart ? 2 * n_rows : n_rows;
     const int kid = a.mode == ROWS_DRAFT ? KID_ROWS_DRAFT : KID_ROWS_UNIFORM;
     by_mode_and_type(a, [&](auto mode, auto bf16) {
         constexpr int MODE = decltype(mode)::value;
         constexpr bool BF = decltype(bf16)::value;
         auto go = [&](auto kernel, int nt) {
-            launch_kernel(kid, st, kernel, dim3((unsigned)n_rows), dim3(nt), 0, a, top_val, top_id, lse, out_stride);
+            launch_kernel(kid, st, kernel, dim3((unsigned)wgs), dim3(nt), 0, a, top_val, top_id, lse, out_stride);
         };
         if (a.V < 8) go(row_topk_kernel<MODE, 1, BF, false, 256>, 256);  // no 16-byte group: element loads
         else if (a.V <= 256 * 8) go(row_topk_kernel<MODE, 1, BF, true, 256>, 256);
@@ -886,7 +921,6 @@ static hipError_t launch_held(const RowArgs &a_in, int64_t n_rows, float *top_va
 // launch 0.3 us.)
 #define HELD_V_MAX 16384
 #define HELD_ROWS_MAX 256  // of 2 HELD_V_MAX entries
-static int held_threads(int V) { return V <= 256 * 16 ? 256 : V <= 512 * 16 ? 512 : 1024; }
 hipError_t rows_launch_topk(const RowArgs &a, int64_t n_rows, float *top_val, int32_t *top_id, float *lse, int out_stride,
                             hipStream_t st) {
     if (n_rows <= 0) return hipSuccess;

@@ -39,8 +39,20 @@ def test_topk_rows_of_many_rows(V, n):
                                       (16385, 1821, False), (65536, 1025, False)])
 def test_topk_rows_of_launches_that_take_two_chunks_to_a_workgroup(V, n, bf16):
     """More than 16,384 chunks: odd and even numbers of them to a row, a last one of one element, nine elements and whole."""
+    check_repeated_rows(V, n, bf16)
+
+
+# the most rows whose exponentials workgroups of their own sum, and one more; the most 256-thread rows whose waves all find
+# the bound, and one more; 512 threads
+@pytest.mark.parametrize("V,n,bf16", [(32768, 128, True), (32768, 129, True), (8193, 128, False), (8193, 129, False),
+                                      (4096, 512, True), (4096, 513, True), (9, 513, False), (8192, 513, True)])
+def test_topk_rows_that_a_workgroup_holds(V, n, bf16):
+    check_repeated_rows(V, n, bf16)
+
+
+def check_repeated_rows(V, n, bf16):
     import paper_2601_12212_amd as dt
-    k, R = 20, 7
+    k, R = min(20, V), 7
     x = (np.random.default_rng(V + n).standard_normal((R, V)) * 3).astype(np.float32)
     x[1] = 40.0 + np.random.default_rng(V).integers(0, 3, V)   # three values: ties everywhere
     x[2, V // 3:V // 3 + 200] += 50.0                          # a cluster of neighbours
