@@ -550,14 +550,13 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
 // T is found as in the selection kernel, and the elements that reach it come straight from the registers.  One launch and one
 // trip to memory where the two passes take two and three.  NT threads: the fewest that hold the row with NL <= 4.
 // Behind that trip the waves' instructions bound it, four waves to a SIMD with 1,024 threads: T is found by wave 0 alone while the
-// others sum their exponentials, not by every wave for itself (by all, 50 rows of 8,000 / 16,000 / 32,000 bf16 entries 5.0 / 6.0 /
+// others sum their exponentials (ONE), not by every wave for itself (by all, 50 rows of 8,000 / 16,000 / 32,000 bf16 entries 5.0 / 6.0 /
 // 7.1 us, 2,000 of 1,000 / 8,000 / 16,000 7.3 / 13.7 / 24.9; by one 4.6 / 5.2 / 6.7 and 6.4 / 12.3 / 20.9).  In a small launch with a wave to a SIMD
 // the barrier that this takes costs what it saves, or more (5 rows of 1,024 fp32 entries 3.53 and 3.61): there every wave finds T.
-#define SMALL_ROWS 512  // most rows of a launch that leaves the SIMDs a wave or two of 256-thread workgroups
-template <int MODE, int NL, bool BF16, bool VEC, int NT>
+template <int MODE, int NL, bool BF16, bool VEC, int NT, bool ONE>
 __global__ __launch_bounds__(NT, NL == 4 ? 4 : 8) void row_topk_kernel(RowArgs a, float *top_val, int32_t *top_id, float *lse, int out_stride) {
     constexpr int E = 8 * NL, NW = NT / 64;
-    const bool lse_wg = a.lse_apart && (int64_t)blockIdx.x >= a.n_rows;
+    const bool lse_wg = NT == 1024 && a.lse_apart && (int64_t)blockIdx.x >= a.n_rows;
     const int64_t g = lse_wg ? (int64_t)blockIdx.x - a.n_rows : (int64_t)blockIdx.x;
     const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int V = a.V, base = w * (64 * E) + lane * 8;
@@ -588,7 +587,7 @@ __global__ __launch_bounds__(NT, NL == 4 ? 4 : 8) void row_topk_kernel(RowArgs a
         mx = fmaxf(mx, gmx[n]);
     }
     s_key[lane * NW + w] = (uint16_t)(ord32(mx) >> 16);
-    const bool want_lse = a.want_lse && lse_wg == a.lse_apart;
+    const bool want_lse = a.want_lse && (NT < 1024 || lse_wg == a.lse_apart);
     auto lse_partial = [&]() {
         const float2 p = wave_lse_partial<E>(x, mx, a.inv_t);
         if (lane == 0) s_ms[w] = p;
@@ -606,12 +605,11 @@ __global__ __launch_bounds__(NT, NL == 4 ? 4 : 8) void row_topk_kernel(RowArgs a
         if (w == 0) row_lse();
         return;
     }
-    const bool by_one = NT >= 512 || a.n_rows > SMALL_ROWS;
-    if (!by_one && want_lse) lse_partial();
+    if (!ONE && want_lse) lse_partial();
     __syncthreads();
     // 256 slots of NW / 4 threads each: k slots that reach T hold k elements that do
     float T;
-    if (!by_one || w == 0) {
+    if (!ONE || w == 0) {
         u32 ky[4];
         uint16_t kv[NW];
         __builtin_memcpy(kv, __builtin_assume_aligned(&s_key[lane * NW], NW * 2), NW * 2);
@@ -623,7 +621,7 @@ __global__ __launch_bounds__(NT, NL == 4 ? 4 : 8) void row_topk_kernel(RowArgs a
         }
         T = key_edge(wave_kth_of_256(ky, k));
     }
-    if (by_one) {
+    if constexpr (ONE) {
         if (w == 0) {
             if (lane == 0) s_T = T;
         } else if (want_lse) {
@@ -887,6 +885,7 @@ static int held_threads(int V) { return V <= 256 * 16 ? 256 : V <= 512 * 16 ? 51
 // reads the row as well: 16 waves sum 32,000 exponentials in 0.6 us (50 rows of 32,000 bf16 entries 6.7 -> 6.1 us, 120 rows 7.1 -> 6.2,
 // 16,000 entries 5.2 -> 4.95 and 5.4 -> 5.05; 50 rows of 8,000, 512 threads, 4.65 -> 4.80).
 #define APART_ROWS 128
+#define SMALL_ROWS 512  // most rows of a launch that leaves a SIMD a wave or two of 256-thread workgroups
 static hipError_t launch_held(const RowArgs &a_in, int64_t n_rows, float *top_val, int32_t *top_id, float *lse, int out_stride,
                               hipStream_t st) {
     RowArgs a = a_in;
@@ -901,12 +900,15 @@ static hipError_t launch_held(const RowArgs &a_in, int64_t n_rows, float *top_va
         auto go = [&](auto kernel, int nt) {
             launch_kernel(kid, st, kernel, dim3((unsigned)wgs), dim3(nt), 0, a, top_val, top_id, lse, out_stride);
         };
-        if (a.V < 8) go(row_topk_kernel<MODE, 1, BF, false, 256>, 256);  // no 16-byte group: element loads
-        else if (a.V <= 256 * 8) go(row_topk_kernel<MODE, 1, BF, true, 256>, 256);
-        else if (a.V <= 256 * 16) go(row_topk_kernel<MODE, 2, BF, true, 256>, 256);
-        else if (a.V <= 512 * 16) go(row_topk_kernel<MODE, 2, BF, true, 512>, 512);
-        else if (!BF || a.V <= 1024 * 16) go(row_topk_kernel<MODE, 2, BF, true, 1024>, 1024);
-        else if constexpr (BF) go(row_topk_kernel<MODE, 4, BF, true, 1024>, 1024);
+        const bool one = n_rows > SMALL_ROWS;
+        if (a.V < 8) go(row_topk_kernel<MODE, 1, BF, false, 256, false>, 256);  // no 16-byte group: element loads
+        else if (a.V <= 256 * 8 && one) go(row_topk_kernel<MODE, 1, BF, true, 256, true>, 256);
+        else if (a.V <= 256 * 8) go(row_topk_kernel<MODE, 1, BF, true, 256, false>, 256);
+        else if (a.V <= 256 * 16 && one) go(row_topk_kernel<MODE, 2, BF, true, 256, true>, 256);
+        else if (a.V <= 256 * 16) go(row_topk_kernel<MODE, 2, BF, true, 256, false>, 256);
+        else if (a.V <= 512 * 16) go(row_topk_kernel<MODE, 2, BF, true, 512, true>, 512);
+        else if (!BF || a.V <= 1024 * 16) go(row_topk_kernel<MODE, 2, BF, true, 1024, true>, 1024);
+        else if constexpr (BF) go(row_topk_kernel<MODE, 4, BF, true, 1024, true>, 1024);
     });
     return hipGetLastError();
 }
