@@ -15,8 +15,11 @@
 //    (four 8-bit digits, one histogram and one barrier per digit, every wave scanning the 256 bins by itself).
 // Eight waves that shared every level (pairs counted for k <= 11, score buckets beyond), two to five barriers per level, took
 // 11.0 us for (TT, d, k) = (60, 6, 10), 10.9 for (64, 7, 8), 20 for (96, 8, 12) and 30 for the slowest of a batch with k up to
-// 32; this takes 7.7, 6.9, 13.2 and 22.6.
+// 32; this takes 7.6, 6.8, 12.6 and 21.9.  What a lane, a thread or a list holds is sized in steps by k and by the pool, since each
+// element more is instructions more in the chain (figures beside the steps: launches replayed one behind the other).
 #include <stddef.h>
+
+#include <type_traits>
 
 #include "common.hpp"
 #include "kernels.hpp"
@@ -402,14 +405,16 @@ __device__ __forceinline__ int choose_wide(TreeLds &S, int l, int lo, int k, int
     }
     return c;
 }
-// All levels of more than NARROW_K^2 candidates, by all waves (k^2 <= 2 TREE_NT: two candidates per thread).  As above.
+// All levels of more than NARROW_K^2 candidates, by all waves: Q candidates per thread, k^2 <= Q TREE_NT.  As above.  (Two per thread,
+// and lists of up to 128 candidates cut four to a lane instead of two: (TT, d, k) = (80, 6, 20) 14.1 us, 13.3 so.)
+template <int Q>
 __device__ __forceinline__ int levels_wide(const TreeArgs &a, TreeLds &S, int b, int k, int d, int TT) {
     const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int xl = a.expand_level, kk = k * k;
     const PoolShape ps = pool_shape(k);
-    int parent[2];
+    int parent[Q];
 #pragma unroll
-    for (int q = 0; q < 2; ++q) parent[q] = tid + TREE_NT * q < kk ? fdiv(tid + TREE_NT * q, ps.inv_k) : DT_K_MAX;
+    for (int q = 0; q < Q; ++q) parent[q] = tid + TREE_NT * q < kk ? fdiv(tid + TREE_NT * q, ps.inv_k) : DT_K_MAX;
     if (tid < DT_D_MAX) S.par[tid][DT_K_MAX].score = -INFINITY;
     const float sc1 = lane < k ? S.lp[lane] : -INFINITY;
     if (tid < k) S.score[tid] = sc1;
@@ -420,16 +425,18 @@ __device__ __forceinline__ int levels_wide(const TreeArgs &a, TreeLds &S, int b,
     for (int l = 1; l < l_end; ++l) {
         if (a.early_stop && tok_count >= TT) break;  // uniform
         const int nlo = k + (l - 1) * kk;
-        float first = -INFINITY, own[2] = {0.f, 0.f};
+        float first = -INFINITY, own[Q] = {};
         if (l != xl) {
             first = S.lp[nlo + min(lane, k - 1) * k];
 #pragma unroll
-            for (int q = 0; q < 2; ++q) own[q] = S.lp[nlo + min(tid + TREE_NT * q, kk - 1)];
+            for (int q = 0; q < Q; ++q) own[q] = S.lp[nlo + min(tid + TREE_NT * q, kk - 1)];
         }
         if (w == 0) {
             int n;
             if (l == 1) n = choose_first(S, k, sc1);
             else if (c == 0) n = 0;
+            else if (c <= 128)
+                n = choose_wide<2>(S, l, lo, k, c, lo_key, hi_key, S.list_score, [&](int i) { return (int)S.list[i]; });
             else if (c <= 256)
                 n = choose_wide<4>(S, l, lo, k, c, lo_key, hi_key, S.list_score, [&](int i) { return (int)S.list[i]; });
             else if (c <= 512)
@@ -443,32 +450,36 @@ __device__ __forceinline__ int levels_wide(const TreeArgs &a, TreeLds &S, int b,
         if (l == xl) return -1;
         __syncthreads();
         if (S.n_exp == 0) break;
-        // every wave: the bound; two candidates per thread scored; those above it into the list
+        // every wave: the bound; Q candidates per thread scored; those above it into the list
         const float f = S.par[l][min(lane, DT_K_MAX)].score + first;
-        float sc[2];
-        u32 key[2];
+        float sc[Q];
+        u32 key[Q];
 #pragma unroll
-        for (int q = 0; q < 2; ++q) sc[q] = S.par[l][parent[q]].score + own[q];
+        for (int q = 0; q < Q; ++q) sc[q] = S.par[l][parent[q]].score + own[q];
         level_bounds(score_key(f), k, lo_key, hi_key);
-        u64 m[2];
+        u64 m[Q];
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
+        for (int q = 0; q < Q; ++q) {
             key[q] = score_key(sc[q]);
             if (tid + TREE_NT * q < kk) S.score[nlo + tid + TREE_NT * q] = sc[q];
             m[q] = __builtin_amdgcn_ballot_w64(key[q] > lo_key);
         }
         if (lane == 0) {
             S.wtot[w] = __popcll(m[0]);
-            S.wtot[TREE_NW + w] = __popcll(m[1]);
+            S.wtot[TREE_NW + w] = Q == 2 ? __popcll(m[Q - 1]) : 0;
         }
-        if (a.early_stop) tok_count += __syncthreads_count(sc[0] > -INFINITY) + __syncthreads_count(sc[1] > -INFINITY);
-        else __syncthreads();
+        if (a.early_stop) {
+            tok_count += __syncthreads_count(sc[0] > -INFINITY);
+            if (Q == 2) tok_count += __syncthreads_count(sc[Q - 1] > -INFINITY);
+        } else {
+            __syncthreads();
+        }
         const int wt = S.wtot[lane & (2 * TREE_NW - 1)], upto = wave_scan_incl_i32(wt);  // lanes 0 .. 15
         const int at[2] = {__builtin_amdgcn_readlane(upto - wt, w), __builtin_amdgcn_readlane(upto - wt, TREE_NW + w)};
         c = __builtin_amdgcn_readlane(upto, 2 * TREE_NW - 1);
         if (c <= 512)
 #pragma unroll
-            for (int q = 0; q < 2; ++q)
+            for (int q = 0; q < Q; ++q)
                 if (key[q] > lo_key) {
                     const int i = at[q] + (int)lanes_below(m[q]);
                     S.list_score[i] = sc[q];
@@ -710,13 +721,14 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = lane_id();
     int p_end = 0;
     if (k > NARROW_K) {
-        p_end = levels_wide(a, S, b, k, d, TT);
+        p_end = k * k <= TREE_NT ? levels_wide<1>(a, S, b, k, d, TT) : levels_wide<2>(a, S, b, k, d, TT);
         if (xl > 0) return;
         __syncthreads();  // the levels may have ended without one
     } else {
         if (w == 0) {
             if (k <= 8) p_end = levels_narrow<1>(a, S, b, k, d, TT);
             else if (k <= 11) p_end = levels_narrow<2>(a, S, b, k, d, TT);
+            else if (k <= 13) p_end = levels_narrow<3>(a, S, b, k, d, TT);  // four per lane: (96, 8, 12) 10.8 us, 10.4 so
             else p_end = levels_narrow<4>(a, S, b, k, d, TT);
             if (lane == 0) S.p_end = p_end;
         }
@@ -738,14 +750,29 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
     } else if (p_end <= 2 * TREE_NT) {
         keep = block_select<2>(S.score, p_end, S.score[0], scale, TT - 1, S, kept);
     } else {
+        // Consecutive candidates per thread, an odd number of them (64 lanes then read 64 banks).  The loops over them are unrolled, and
+        // three lengths of them there: with the longest for every pool, and every index held to the pool's end, (80, 6, 16) took 10.5
+        // us and (80, 6, 20) 13.3; 9.7 and 12.6 so.  Past the pool's end they read what follows the scores in LDS, and use none of it.
+        const int C = ((p_end + TREE_NT - 1) / TREE_NT) | 1;
+        static_assert((TREE_NT - 1) * SHARE_MAX + SHARE_MAX <= 2 * DT_P_MAX, "the scores and what follows them");
+        auto by_share = [&](auto f) __attribute__((always_inline)) {
+            using std::integral_constant;
+            if (C <= 5) f(integral_constant<int, 5>());
+            else if (C <= 9) f(integral_constant<int, 9>());
+            else f(integral_constant<int, SHARE_MAX>());
+        };
+        const float *pool = (const float *)s_dyn;  // S.score
+        static_assert(offsetof(TreeLds, score) == 0 && offsetof(TreeLds, lp) == DT_P_MAX * sizeof(float), "the scores come first");
         // the threads' best ones, each of candidates TREE_NT apart (the children of one node are neighbours)
         u32 best = 0u;
+        by_share([&](auto share) __attribute__((always_inline)) {
 #pragma unroll
-        for (int c = 0; c < SHARE_MAX; ++c) {
-            const int i = tid + TREE_NT * c;
-            const u32 kv = score_key(S.score[min(i, p_end - 1)]);
-            best = max(best, i < p_end ? kv : 0u);
-        }
+            for (int c = 0; c < decltype(share)::value; ++c) {
+                const int i = tid + TREE_NT * c;
+                const u32 kv = score_key(pool[i]);
+                best = max(best, i < p_end ? kv : 0u);
+            }
+        });
         S.best[tid] = best;
         __syncthreads();
         // every wave by itself: a bound that TT - 1 of them reach, and not many more
@@ -760,14 +787,15 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
             if (nm >= TT - 1) { lo = mid; n = nm; }
             else hi = mid;
         }
-        // What lies above, in pool order: consecutive candidates per thread, an odd number of them (64 lanes then read 64 banks).
-        const int C = ((p_end + TREE_NT - 1) / TREE_NT) | 1;
+        // what lies above, in pool order
         u32 over = 0u;
+        by_share([&](auto share) __attribute__((always_inline)) {
 #pragma unroll
-        for (int c = 0; c < SHARE_MAX; ++c) {
-            const float v = S.score[min(tid * C + c, p_end - 1)];
-            over |= (c < C && tid * C + c < p_end && score_key(v) > lo ? 1u : 0u) << c;
-        }
+            for (int c = 0; c < decltype(share)::value; ++c) {
+                const u32 kv = score_key(pool[tid * C + c]);
+                over |= (c < C && tid * C + c < p_end && kv > lo ? 1u : 0u) << c;
+            }
+        });
         const int own = __popc(over), incl = wave_scan_incl_i32(own);
         if (lane == 63) S.wtot[w] = incl;
         __syncthreads();
@@ -779,13 +807,13 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
             total += nv;
         }
         if (total <= LIST_CAP) {  // uniform
-            for (; over; over &= over - 1u) {
-                const int i = tid * C + __builtin_ctz(over);
-                S.list_score[at] = S.score[i];
-                S.list[at] = (int16_t)i;
-                ++at;
-            }
+            for (; over; over &= over - 1u) S.list[at++] = (int16_t)(tid * C + __builtin_ctz(over));
             __syncthreads();
+            // every thread the scores that it is going to look at (read where the list is made, one behind the other, they cost (128, 8, 32)
+            // 0.35 us more)
+            const int share = total <= TREE_NT ? 1 : 2;
+            for (int c = 0; c < share; ++c)
+                if (tid * share + c < total) S.list_score[tid * share + c] = S.score[S.list[tid * share + c]];
             auto kept_of_list = [&](int i, int pos) { kept(S.list[i], pos); };
             const float top = S.score[0], range = top - (lo > KEY_NEG_INF ? unord32(lo) : top - 32.0f);
             const float fit = range > 0.0f ? 255.0f / range : 8.0f;

@@ -42,3 +42,9 @@ def test_paths_of_the_expansion_and_of_the_rerank(TT, d, k):
     rows = np.zeros((1 + (d - 1) * k, 900), np.float32)
     rows[:, 300] = 1.0
     assert_tree_equal(_build(rows, True, TT, d, k), ref.build_tree(dt_synth.f32_to_bf16_bits(rows), TT, d, k, 3), "ties " + tag)
+
+
+# three and four candidates per lane, one and two per thread, pools whose threads hold up to 5, 9 and 15
+@pytest.mark.parametrize("TT,d,k", [(90, 5, 13), (90, 5, 14), (90, 6, 22), (90, 6, 23), (90, 5, 32), (90, 6, 32)])
+def test_paths_sized_by_k_and_by_the_pool(TT, d, k):
+    test_paths_of_the_expansion_and_of_the_rerank(TT, d, k)
