@@ -1,5 +1,5 @@
 """Binding of libdt.so.  Argument marshalling only: the launching entry points go through the native module _dtcall
-(csrc/pycall.c), the host-only ones through ctypes."""
+(csrc/pycall.cpp), the host-only ones through ctypes."""
 import ctypes as C
 import os
 

@@ -1,5 +1,6 @@
 """Compile the HIP kernels and the C ABI into paper_2601_12212_amd/libdt.so (gfx950 only), and the argument marshalling of
-the Python binding into paper_2601_12212_amd/_dtcall.so (gcc; finds libdt.so beside itself)."""
+the Python binding into paper_2601_12212_amd/_dtcall.so (g++; finds libdt.so beside itself, torch's libraries where the
+interpreter has loaded them)."""
 import os
 import subprocess
 import sys
@@ -39,8 +40,14 @@ def build(verbose=False):
     subprocess.check_call([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs)
     os.replace(tmp, LIB)
     tmp = PYCALL + ".tmp%d" % os.getpid()
-    subprocess.check_call(["gcc", "-O2", "-shared", "-fPIC", "-Wall", "-I" + sysconfig.get_paths()["include"],
-                           os.path.join(CSRC, "pycall.c"), "-o", tmp, "-L" + HERE, "-l:libdt.so", "-Wl,-rpath,$ORIGIN"])
+    import torch
+    tdir = os.path.dirname(torch.__file__)
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-I" + sysconfig.get_paths()["include"],
+                           "-isystem", os.path.join(tdir, "include"),
+                           "-isystem", os.path.join(tdir, "include", "torch", "csrc", "api", "include"),
+                           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch.compiled_with_cxx11_abi(),
+                           os.path.join(CSRC, "pycall.cpp"), "-o", tmp, "-L" + HERE, "-l:libdt.so", "-Wl,-rpath,$ORIGIN",
+                           "-L" + os.path.join(tdir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"])
     os.replace(tmp, PYCALL)
     return LIB
 

@@ -1,32 +1,55 @@
 /*
  * Argument marshalling between the Python binding and the C ABI: tensors -> device pointers, sizes and strides, the
  * current torch stream -> hipStream_t.  One native call per entry point: an eager step at batch 1 is six kernel launches
- * of about 3.4 us of host time each, and marshalling its three calls through ctypes and torch's Python-level stream
- * object cost another 5.5 us per call (2.8 of them the stream); here it is about 1 us.
+ * of about 3 us of host time each, and marshalling its three calls through ctypes and torch's Python-level stream
+ * object cost another 5.5 us per call (2.8 of them the stream).  The fifteen arguments of a level step take 1.28 us through the
+ * interpreter's methods of a tensor and 0.40 read from the tensor itself: the headline tree drafted level by level, bound by the
+ * host, 101 -> 96 us.
  *
  * Every function takes the positional arguments of its namesake in binding.py and returns the dt_status as an int.
- * Tensors are anything with data_ptr(), shape, stride(), dtype and nbytes.  The interpreter lock is released during the
- * library call.
+ * Tensors are anything with data_ptr(), shape, stride(), dtype and nbytes.  Those of a torch.Tensor (not of a class derived from it,
+ * which may have its own) are read without the interpreter.  The interpreter lock is released during the library call.
  */
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
+
+#include <torch/csrc/autograd/python_variable.h>
 
 #include "../../include/dt.h"
 
 static PyObject *g_f32, *g_bf16, *g_get_device, *g_get_stream;  /* set by setup() */
 static PyObject *s_data_ptr, *s_shape, *s_stride, *s_dtype, *s_nbytes;
 
+/* a device pointer, or a stream: what the library's parameter is a pointer to */
+struct Ptr {
+    void *p;
+    template <typename T>
+    operator T *() const { return (T *)p; }
+};
+
+/* f(tensor) if t is a torch.Tensor.  False if it is not, or if f throws: the interpreter's way then says why. */
+template <typename F>
+static bool direct(PyObject *t, F f) {
+    if ((PyObject *)Py_TYPE(t) != THPVariableClass) return false;
+    try {
+        return f(THPVariable_Unpack(t));
+    } catch (...) {
+        return false;
+    }
+}
+
 /* Each helper does nothing once an error is set, so a call's arguments are converted in a row and checked once. */
-static void *ptr(PyObject *t) {
+static Ptr ptr(PyObject *t) {
     void *p = NULL;
     PyObject *r;
-    if (t == Py_None || PyErr_Occurred()) return NULL;
+    if (t == Py_None || PyErr_Occurred()) return Ptr{NULL};
+    if (direct(t, [&](const at::Tensor &x) { p = x.data_ptr(); return true; })) return Ptr{p};
     r = PyObject_CallMethodNoArgs(t, s_data_ptr);
     if (r) {
         p = PyLong_AsVoidPtr(r);
         Py_DECREF(r);
     }
-    return p;
+    return Ptr{p};
 }
 static long long num(PyObject *o) { return PyErr_Occurred() ? 0 : PyLong_AsLongLong(o); }
 static int inum(PyObject *o) {
@@ -42,6 +65,13 @@ static void shape(PyObject *t, int n, int exact, long long *out) {
     int i;
     for (i = 0; i < n; ++i) out[i] = 0;
     if (PyErr_Occurred()) return;
+    if (direct(t, [&](const at::Tensor &x) {
+            const auto sizes = x.sizes();
+            if (exact ? (int)sizes.size() != n : (int)sizes.size() < n) return false;
+            for (int j = 0; j < n; ++j) out[j] = sizes[j];
+            return true;
+        }))
+        return;
     s = PyObject_GetAttr(t, s_shape);
     if (!s) return;
     if (!PyTuple_Check(s) || (exact ? PyTuple_GET_SIZE(s) != n : PyTuple_GET_SIZE(s) < n))
@@ -54,6 +84,7 @@ static long long stride(PyObject *t, long dim) {
     PyObject *d, *r;
     long long v = 0;
     if (PyErr_Occurred()) return 0;
+    if (direct(t, [&](const at::Tensor &x) { v = x.stride(dim); return true; })) return v;
     d = PyLong_FromLong(dim);
     r = d ? PyObject_CallMethodOneArg(t, s_stride, d) : NULL;
     if (r) v = num(r);
@@ -65,6 +96,12 @@ static dt_dtype dtype(PyObject *t) {
     dt_dtype v = DT_F32;
     PyObject *d;
     if (PyErr_Occurred()) return v;
+    if (direct(t, [&](const at::Tensor &x) {
+            const at::ScalarType s = x.scalar_type();
+            v = s == at::kBFloat16 ? DT_BF16 : DT_F32;
+            return s == at::kBFloat16 || s == at::kFloat;
+        }))
+        return v;
     d = PyObject_GetAttr(t, s_dtype);
     if (!d) return v;
     if (d == g_bf16) v = DT_BF16;
@@ -76,6 +113,7 @@ static size_t nbytes(PyObject *t) {
     PyObject *r;
     size_t v = 0;
     if (t == Py_None || PyErr_Occurred()) return 0;
+    if (direct(t, [&](const at::Tensor &x) { v = x.nbytes(); return true; })) return v;
     r = PyObject_GetAttr(t, s_nbytes);
     if (r) {
         v = (size_t)num(r);
@@ -84,20 +122,20 @@ static size_t nbytes(PyObject *t) {
     return v;
 }
 /* torch's current stream on the current device */
-static void *stream(void) {
+static Ptr stream(void) {
     void *p = NULL;
     PyObject *dev, *st;
-    if (PyErr_Occurred()) return NULL;
+    if (PyErr_Occurred()) return Ptr{NULL};
     if (!g_get_stream) {
         PyErr_SetString(PyExc_RuntimeError, "setup() has not been called");
-        return NULL;
+        return Ptr{NULL};
     }
     dev = PyObject_CallNoArgs(g_get_device);
     st = dev ? PyObject_CallOneArg(g_get_stream, dev) : NULL;
     if (st) p = PyLong_AsVoidPtr(st);
     Py_XDECREF(dev);
     Py_XDECREF(st);
-    return p;
+    return Ptr{p};
 }
 
 #define NEED(n)                                                                                      \
@@ -117,7 +155,7 @@ static void *stream(void) {
 /* logits, k, top_val, top_id, lse, ws */
 FN(topk_rows) {
     NEED(6)
-    void *const st = stream(), *const x = ptr(a[0]), *const v = ptr(a[2]), *const i = ptr(a[3]), *const l = ptr(a[4]), *const w = ptr(a[5]);
+    const Ptr st = stream(), x = ptr(a[0]), v = ptr(a[2]), i = ptr(a[3]), l = ptr(a[4]), w = ptr(a[5]);
     const dt_dtype t = dtype(a[0]);
     const long long row = stride(a[0], 0);
     const int k = inum(a[1]);
@@ -129,7 +167,7 @@ FN(topk_rows) {
 /* logits, k, top_val, top_id, lse */
 FN(topk_rows_static) {
     NEED(5)
-    void *const st = stream(), *const x = ptr(a[0]), *const v = ptr(a[2]), *const i = ptr(a[3]), *const l = ptr(a[4]);
+    const Ptr st = stream(), x = ptr(a[0]), v = ptr(a[2]), i = ptr(a[3]), l = ptr(a[4]);
     const dt_dtype t = dtype(a[0]);
     const long long row = stride(a[0], 0);
     const int k = inum(a[1]);
@@ -141,9 +179,9 @@ FN(topk_rows_static) {
    anc_mask, ws, flags */
 FN(build_tree) {
     NEED(16)
-    void *const st = stream(), *const prm = ptr(a[0]), *const x = ptr(a[1]), *const off = ptr(a[2]), *const root = ptr(a[4]);
-    void *o[8];
-    void *const w = ptr(a[14]);
+    const Ptr st = stream(), prm = ptr(a[0]), x = ptr(a[1]), off = ptr(a[2]), root = ptr(a[4]);
+    Ptr o[8];
+    const Ptr w = ptr(a[14]);
     const dt_dtype t = dtype(a[1]);
     const long long row = stride(a[1], 0), rows = num(a[3]);
     const int cap = inum(a[5]), flags = inum(a[15]);
@@ -160,9 +198,9 @@ FN(build_tree) {
    anc_mask, scale, out, ws */
 FN(tree_attention) {
     NEED(14)
-    void *const st = stream();
-    void *p[7];
-    void *const mask = ptr(a[10]), *const out = ptr(a[12]), *const w = ptr(a[13]);
+    const Ptr st = stream();
+    Ptr p[7];
+    const Ptr mask = ptr(a[10]), out = ptr(a[12]), w = ptr(a[13]);
     const dt_dtype t = dtype(a[0]);
     const int maxlen = inum(a[7]);
     const long long stok = num(a[8]), shead = num(a[9]);
@@ -181,9 +219,9 @@ FN(tree_attention) {
    best_node, path_nodes, out_tokens, node_argmax, ws */
 FN(accept_tree) {
     NEED(17)
-    void *const st = stream(), *const x = ptr(a[2]);
-    void *p[6], *o[5];
-    void *const w = ptr(a[16]);
+    const Ptr st = stream(), x = ptr(a[2]);
+    Ptr p[6], o[5];
+    const Ptr w = ptr(a[16]);
     const int mode = inum(a[0]);
     const float temp = fnum(a[1]);
     const dt_dtype t = dtype(a[2]);
@@ -202,9 +240,9 @@ FN(accept_tree) {
    exp_pos, exp_mask, ws, flags */
 FN(expand_level) {
     NEED(15)
-    void *const st = stream(), *const prm = ptr(a[1]), *const x = ptr(a[2]), *const len = ptr(a[4]), *const state = ptr(a[6]);
-    void *o[6];
-    void *const w = ptr(a[13]);
+    const Ptr st = stream(), prm = ptr(a[1]), x = ptr(a[2]), len = ptr(a[4]), state = ptr(a[6]);
+    Ptr o[6];
+    const Ptr w = ptr(a[13]);
     const dt_dtype t = dtype(a[2]);
     const long long row = stride(a[2], 0);
     const int level = inum(a[0]), R = inum(a[3]), cap = inum(a[5]), flags = inum(a[14]);
@@ -220,8 +258,8 @@ FN(expand_level) {
 /* params, V, root_token, TT_cap, state, n_nodes, tokens, parents, depth, score, logp, src_row, anc_mask, flags */
 FN(finish_tree) {
     NEED(14)
-    void *const st = stream(), *const prm = ptr(a[0]), *const root = ptr(a[2]), *const state = ptr(a[4]);
-    void *o[8];
+    const Ptr st = stream(), prm = ptr(a[0]), root = ptr(a[2]), state = ptr(a[4]);
+    Ptr o[8];
     const int V = inum(a[1]), cap = inum(a[3]), flags = inum(a[13]);
     long long b[1];
     int i;
@@ -233,9 +271,9 @@ FN(finish_tree) {
    cached_action, params_out, action_out, queried_out, logits_out, ws */
 FN(policy_step) {
     NEED(19)
-    void *const st = stream();
-    void *p[8], *o[6];
-    void *const w = ptr(a[18]);
+    const Ptr st = stream();
+    Ptr p[8], o[6];
+    const Ptr w = ptr(a[18]);
     const dt_dtype t = dtype(a[0]);
     const long long row = stride(a[0], 0);
     const int interval = inum(a[8]), sample = inum(a[9]);
@@ -254,9 +292,9 @@ FN(policy_step) {
    kv_stride_head, n_nodes, path_nodes, accept_len, out_tokens, TT_cap, new_prefix_len, next_root_token */
 FN(commit) {
     NEED(18)
-    void *const st = stream();
-    void *p[6], *q[4];
-    void *const len = ptr(a[16]), *const root = ptr(a[17]);
+    const Ptr st = stream();
+    Ptr p[6], q[4];
+    const Ptr len = ptr(a[16]), root = ptr(a[17]);
     const dt_dtype t = dtype(a[0]);
     const int Hkv = inum(a[1]), D = inum(a[2]), cap = inum(a[15]);
     const long long stok = num(a[9]), shead = num(a[10]);
@@ -272,8 +310,8 @@ FN(commit) {
    elapsed_per_seq */
 FN(reward_step) {
     NEED(9)
-    void *const st = stream(), *const len = ptr(a[0]), *const per = ptr(a[8]);
-    void *p[5];
+    const Ptr st = stream(), len = ptr(a[0]), per = ptr(a[8]);
+    Ptr p[5];
     const int bonus = inum(a[1]);
     const float secs = fnum(a[2]);
     long long b[1];

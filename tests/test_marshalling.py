@@ -1,0 +1,72 @@
+"""The native argument marshalling reads a torch.Tensor itself and anything else through its methods: both ways have to see the
+same pointers, sizes, strides, types and byte counts, and to refuse the same objects.  Every call here is refused before a launch."""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2601_12212_amd import _dtcall  # noqa: E402
+
+
+class Duck:
+    """A tensor's methods, and not its type."""
+
+    def __init__(self, t):
+        self._t = t
+
+    def __getattr__(self, name):
+        return getattr(self._t, name)
+
+
+class Derived(torch.Tensor):
+    pass
+
+
+@pytest.fixture
+def call():
+    _dtcall.setup(torch.float32, torch.bfloat16, lambda: 0, lambda device: 0)
+    yield _dtcall
+    _dtcall.setup(torch.float32, torch.bfloat16, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+
+
+def _rows(**kw):
+    """Arguments of topk_rows: refused for want of a workspace unless something else is wrong first."""
+    a = dict(logits=torch.zeros(4, 64), k=3, val=torch.zeros(4, 3), id=torch.zeros(4, 3, dtype=torch.int32), lse=torch.zeros(4),
+             ws=torch.zeros(1024, dtype=torch.uint8))
+    a.update(kw)
+    return list(a.values())
+
+
+aligned = torch.zeros(4096, dtype=torch.uint8)
+aligned = aligned[-aligned.data_ptr() % 256:][:1024]
+CASES = {
+    "a workspace too small": _rows(ws=aligned[:256], logits=torch.zeros(2, 40000, dtype=torch.bfloat16)),
+    "a misaligned workspace": _rows(ws=aligned[1:], logits=torch.zeros(2, 40000)),
+    "no workspace": _rows(ws=None, logits=torch.zeros(2, 40000)),
+    "rows that overlap": _rows(logits=torch.zeros(512).as_strided((4, 64), (32, 1))),
+    "no output": _rows(val=None),
+    "too many of a row": _rows(k=400),
+    "an integer type": _rows(logits=torch.zeros(4, 64, dtype=torch.int32)),
+    "half precision": _rows(logits=torch.zeros(4, 64, dtype=torch.float16)),
+    "one dimension": _rows(logits=torch.zeros(64)),
+    "three dimensions": _rows(logits=torch.zeros(2, 4, 64)),
+    "no dimension": _rows(logits=torch.zeros(())),
+    "no storage": _rows(logits=torch.zeros(4, 64).to_sparse()),
+    "not a tensor": _rows(logits=7),
+}
+
+
+def _outcome(call, args):
+    try:
+        return call.topk_rows(*args)
+    except Exception as e:  # noqa: BLE001
+        return type(e), str(e)
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_tensors_and_other_objects_are_read_alike(call, name):
+    args = CASES[name]
+    want = _outcome(call, [Duck(a) if isinstance(a, torch.Tensor) else a for a in args])
+    assert want != 0
+    assert _outcome(call, args) == want
+    assert _outcome(call, [a.as_subclass(Derived) if isinstance(a, torch.Tensor) and a.layout == torch.strided else a
+                           for a in args]) == want
