@@ -15,6 +15,7 @@
 // fp32 heads of 64 and 128: sixteen lanes to a key (attn_f32_kernel); every other head size and type, and bf16 caches whose
 // strides are not multiples of 16 bytes: attn_simple_kernel.  Plain ALU kernels, one workgroup per (node, head).
 
+#include <algorithm>
 #include <atomic>
 #include <type_traits>
 
@@ -1758,19 +1759,36 @@ size_t attn_workspace_bytes(int batch, int TT_cap, int Hq, int D, int n_cu) {
     return want < cap ? want : cap;
 }
 
+// Over how many workgroups the keys of a (sequence, kv head, 32-row block) are dealt: nb blocks of 32 keys, `units` such row blocks.
+// At most one workgroup per compute unit (more, with 64-wide heads, which leave room for them, lose: 84 units of 34 blocks 9.9
+// us in 3 splits, 11.2 in 4), and 8.  Split, the four waves of a workgroup take ceil(nb / 4 KS) rounds of about 0.8 us, and each split costs the
+// merge 0.12 us and 1/200 more for every unit: whichever number of splits is cheapest by that.
+// Unsplit, eight waves take half as many rounds as four and need no merge, but a round of theirs is longer, 128-wide heads' by
+// far more: the line lies where the two sides met, us per layer, unsplit against the best split:
+//   128-wide heads, 16 units: 8 blocks 7.6 | 7.3, 9: 8.0 | 7.6, 13: 10.0 | 8.3, 23: 12.2 | 9.0;  64 units: 10: 8.5 | 8.5, 13: 10.1 | 9.2,
+//     21: 11.9 | 9.7, 30: 13.4 | 10.2;  80 units: 9: 9.0 | 9.2, 11: 9.5 | 9.2, 21: 13.1 | 10.7;  128 units: 11: 9.0 | 9.7, 13: 10.3 | 9.7;
+//   64-wide heads, 28 units: 27: 8.6 | 8.9, 31: 9.8 | 9.2, 43: 11.4 | 9.8;  84 units: 27: 9.2 | 9.9, 31: 10.1 | 9.9, 43: 11.5 | 10.8, in two
+//     splits 52: 12.5 | 12.7, 66: 14.9 | 14.5.
+// (A split for every eleven blocks: 64 units of 21 blocks 11.9, of 30 10.7, 80 units of 31 14.4; 64-wide heads, 84 units of 27 10.3.)
+static int wave_splits(int D, int64_t units, int64_t nb) {
+    const int most = (int)std::min<int64_t>(8, 256 / units);
+    const int least = D == 128 ? (most == 8 ? 9 : most >= 3 ? 11 : 13) : (most >= 3 ? 29 : 60);
+    if (most < 2 || nb < least) return 1;
+    int best = 2;
+    auto cost = [&](int n) { return 80 * ((nb + 4 * n - 1) / (4 * n)) + (12 + units / 2) * n; };
+    for (int n = 3; n <= most; ++n)
+        if (cost(n) < cost(best)) best = n;
+    return best;
+}
+
 // The small-batch kernel and, with key splits, its merge.
-// Key splits: towards one workgroup per compute unit, but only while a split still owns about eleven key blocks -- below
-// that the fixed cost of a workgroup (query load, first fetch, LDS exchange) plus the merge launch outweighs the shorter
-// loop (measured).
 template <int D>
 static int wave_launch(const AttnArgs &a, hipStream_t st, hipError_t *err) {
     const int G = a.Hq / a.Hkv;
     const int mblocks = (a.TT_cap * G + 31) / 32;
     const int64_t units = (int64_t)a.batch * a.Hkv * mblocks;
-    const int nb_max = (a.max_prefix_len + a.TT_cap + ATT_KB - 1) / ATT_KB;
-    int KS = (int)(256 / units);
-    if (KS > 8) KS = 8;
-    if (KS > nb_max / 11) KS = nb_max / 11;
+    const int64_t nb_max = ((int64_t)a.max_prefix_len + a.TT_cap + ATT_KB - 1) / ATT_KB;
+    int KS = wave_splits(D, units, nb_max);
     const size_t per_split = (size_t)units * wave_unit_bytes(D);
     if (KS > 1 && (!a.ws || (size_t)KS * per_split > a.ws_bytes)) KS = a.ws ? (int)(a.ws_bytes / per_split) : 1;
     if (KS < 1) KS = 1;

@@ -134,7 +134,7 @@ def test_heads_of_64_do_not_multiply_the_values_of_hidden_keys(Hq, Hkv, L):
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("L", [330, 700, 1060, 1410, 1760, 2110, 2460, 2810])
 def test_an_infinite_value_in_any_key_split(D, L):
-    # one short sequence: its keys are dealt over 1 to 8 workgroups (a split per eleven 32-key blocks) and the partials merged;
+    # one short sequence: its keys are dealt over 1 to 8 workgroups (the more, the longer it is) and the partials merged;
     # an infinite V element of a visible prefix key makes that column infinite, whichever split holds the key
     cfg = _cfg("bf16", D, [(32, 5, 6)], [L], 4, 4)
     case = oracle_case(0, cfg=cfg)
@@ -216,3 +216,12 @@ def test_shared_merge_at_its_edges():
         st.tree_attention()
         want = ref.tree_attention(q[:n], kt[:n], vt[:n], kp[:L], vp[:L], case.trees[0]["anc_mask"], st.scale)
         assert_attention(st.attention_out(0), want, "bf16", "%d parts" % blocks)
+
+
+# four units (a kv head's 32 rows each) of one block up to 1 to 8 splits, and both sides of the lines where splits begin: 9, 11
+# and 13 blocks of 128-wide heads with room for eight, three and two, 29 and 60 blocks of 64-wide ones with room for three and two
+@pytest.mark.parametrize("D,Hkv,L", [(128, 4, L) for L in (224, 225, 352, 353, 480, 608, 736, 864, 992)] +
+                         [(128, 72, L) for L in (288, 289, 353, 481)] + [(128, 100, L) for L in (352, 353, 481)] +
+                         [(64, 4, L) for L in (864, 865, 993, 1121, 1500, 1800)] + [(64, 72, 865), (64, 100, 1856), (64, 100, 1857)])
+def test_numbers_of_key_splits(D, Hkv, L):
+    check_case(oracle_case(0, cfg=_cfg("bf16", D, [(32, 5, 6)], [L], Hkv, Hkv)))
