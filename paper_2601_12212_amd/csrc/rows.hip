@@ -325,13 +325,13 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
     // the lane maxima do not depend on the row's metadata (two dependent global reads): ask for them
     // first, and wave 3 for the row's (max, sum) partials.  Rows that turn out to be dead have their
     // slots in the workspace all the same.
-    // Thread tid holds lane maxima 4 (256 i + tid) .. + 3, i < S / 8.
+    // A quarter of them to a wave, 8 S quadruples: lane l holds quadruples l and l + 64 of its wave's (so far as there are any).
     struct alignas(4 * sizeof(LM)) Quad { LM v[4]; };
     float it[8];
     if (S <= 16) {
         Quad q[2];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) q[i] = ((const Quad *)lm)[min(256 * i + tid, S * 32 - 1)];
+        for (int i = 0; i < 2; ++i) q[i] = ((const Quad *)lm)[w * (8 * S) + min(64 * i + lane, 8 * S - 1)];
 #pragma unroll
         for (int j = 0; j < 8; ++j) it[j] = lane_max_value<BF16>(q[j >> 2].v[j & 3]);
     }
@@ -383,10 +383,10 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
     // Eight elements of lane maximum i (chunk, wave, pair of lanes), those of load n / 2 and lane n % 2 of the pair: the ones that
     // reach T become candidates, room for them with one LDS add.
     const int per_log2 = nl == 4 ? 3 : nl == 2 ? 2 : 1;  // groups of eight: chunk multipliers are 1, 2 or 4
-    auto reread = [&](int i, int n, float T) {
-        const int id0 = (i >> 7) * (256 * E) + ((i >> 5) & 3) * (64 * E) + (2 * (i & 31) + (n & 1)) * 8 + (n >> 1) * 512;
-        float xv[8];
-        const int start = load_octet<BF16>(a, g, id0, xv);
+    auto octet_of = [&](int i, int n) {
+        return (i >> 7) * (256 * E) + ((i >> 5) & 3) * (64 * E) + (2 * (i & 31) + (n & 1)) * 8 + (n >> 1) * 512;
+    };
+    auto keep_hits = [&](const float (&xv)[8], int start, float T) {
         int hits = 0;
 #pragma unroll
         for (int e = 0; e < 8; ++e) hits += xv[e] >= T ? 1 : 0;
@@ -399,6 +399,11 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
                     ++slot;
                 }
         }
+    };
+    auto reread = [&](int i, int n, float T) {
+        float xv[8];
+        const int start = load_octet<BF16>(a, g, octet_of(i, n), xv);
+        keep_hits(xv, start, T);
     };
     // candidate t ranks itself against all n2 keys (LDS broadcasts, eight in flight)
     auto rank_and_emit = [&](int n2) {
@@ -424,7 +429,7 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
     if (S <= 16) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            it[j] = 256 * (j >> 2) + tid < S * 32 ? it[j] : -INFINITY;
+            it[j] = 64 * (j >> 2) + lane < 8 * S ? it[j] : -INFINITY;
             tmax = fmaxf(tmax, it[j]);
         }
     } else {
@@ -454,10 +459,23 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
             int *list = s_hot + w * SEL_WAVE_CAP;
             for (int at = incl - mine; hot; hot &= hot - 1) {
                 const int j = __builtin_ctz(hot);
-                list[at++] = 4 * (256 * (j >> 2) + tid) + (j & 3);
+                list[at++] = 4 * (w * (8 * S) + 64 * (j >> 2) + lane) + (j & 3);
             }
             __builtin_amdgcn_wave_barrier();
-            for (int q = lane; q < h << per_log2; q += 64) reread(list[q >> per_log2], q & ((1 << per_log2) - 1), T0);
+            // Two on their way at a time: k = 27 is some sixty groups of eight to a wave.  (One after the other, and the lane maxima dealt
+            // to the threads so that of twelve chunks' two waves held two thirds: 336 rows of 12 chunks, k = 27, 11.4 us, 10.0 so,
+            // 340 of 16, k = 12, 8.7 and 8.4, each launch between two events.)
+            const int total = h << per_log2, mask = (1 << per_log2) - 1;
+            for (int q = lane; q - lane < total; q += 128) {
+                float x0[8], x1[8];
+                int s1 = 0;
+                const bool two = q - lane + 64 < total;  // uniform
+                const int q0 = min(q, total - 1), q1 = min(q + 64, total - 1);
+                const int s0 = load_octet<BF16>(a, g, octet_of(list[q0 >> per_log2], q0 & mask), x0);
+                if (two) s1 = load_octet<BF16>(a, g, octet_of(list[q1 >> per_log2], q1 & mask), x1);
+                if (q < total) keep_hits(x0, s0, T0);
+                if (two && q + 64 < total) keep_hits(x1, s1, T0);
+            }
         }
         __syncthreads();
         const int n2 = s_n2;
