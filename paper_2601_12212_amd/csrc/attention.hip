@@ -1781,14 +1781,35 @@ static int wave_splits(int D, int64_t units, int64_t nb) {
     return best;
 }
 
+// 32-key blocks of the longest sequence
+static int64_t max_blocks(const AttnArgs &a) { return ((int64_t)a.max_prefix_len + a.TT_cap + ATT_KB - 1) / ATT_KB; }
+
+// 128-wide heads: is the small-batch kernel ahead of the balanced schedule?  Its workgroups walk all keys of a row block: about 2 us and
+// 5 + nb / 4 for every 256 units, with splits that much fewer blocks; the schedule, which shares each key block among four
+// row blocks and cuts what is long, starts at 22 to 30 us and takes half as long a block.  Where a kv head has two row blocks, the schedule
+// still halves what is read, and both wait for the memory sooner; where it has one, there is nothing to share, but the schedule has as
+// many tiles as there are units.  Both sides, small-batch | balanced, us per layer:
+//   up to 256 units, 8B shape, 4 sequences of 60 nodes (256): 4,000 keys 40 | 51, 8,192 73 | 71; 3 (192): 4,000 33 | 42, 8,192 69 | 56;
+//     in two splits (2 sequences): 8,192 37 | 41, 16,000 78 | 63; two row blocks (13B shape), 2 sequences (160): 2,500 40 | 42, 4,000 58 | 54, 3 (240):
+//     4,000 62 | 65, 8,192 119 | 117; one (32 heads, 30 nodes), 4 sequences (128): 150 9 | 15, 4,000 54 | 69, 8 (256): 150 11 | 19, 2,000 55 | 62;
+//   up to 512, 8B shape, 8 sequences (512): 150 keys 17 | 26, 400 22 | 28, 1,000 28 | 32, 1,700 40 | 41, 2,100 49 | 50, 2,500 56 | 49; 6 (384): 2,100
+//     39 | 45, 3,000 60 | 54, 8,192 133 | 86; two row blocks, 4 sequences (320): 150 16.5 | 17.5, 400 22 | 28, 700 28 | 27; one, 12 (384): 150 17 | 14, 400 29 | 30;
+//   beyond, 12 sequences of the 8B shape (768): 30 keys 17 | 22, 150 23.5 | 22.8, 400 30 | 41, 1,000 43 | 40, and 6 of 128 nodes 400 32 | 28: no line.
+// The keys are the longest that the caller allows for, and a step that is captured once allows for more than most replays bring:
+// so up to 256 units of fewer than 128 tiles stay with the small-batch kernel, which loses little at the far end (8 % with 4
+// sequences of 8,192 keys) and is two and a half times as fast at a thousand.  (The line was 128 row tiles, whatever the keys.)
+static bool wave_ahead(int64_t units, int64_t tiles, int mblocks, int64_t nb) {
+    if (units <= 256) return tiles < 128 || nb <= (mblocks == 2 ? 150 : 200) * wave_splits(128, units, nb);
+    return units <= 512 && nb <= (mblocks == 1 ? 0 : mblocks == 2 ? 20 : 100 - units / 12);
+}
+
 // The small-batch kernel and, with key splits, its merge.
 template <int D>
 static int wave_launch(const AttnArgs &a, hipStream_t st, hipError_t *err) {
     const int G = a.Hq / a.Hkv;
     const int mblocks = (a.TT_cap * G + 31) / 32;
     const int64_t units = (int64_t)a.batch * a.Hkv * mblocks;
-    const int64_t nb_max = ((int64_t)a.max_prefix_len + a.TT_cap + ATT_KB - 1) / ATT_KB;
-    int KS = wave_splits(D, units, nb_max);
+    int KS = wave_splits(D, units, max_blocks(a));
     const size_t per_split = (size_t)units * wave_unit_bytes(D);
     if (KS > 1 && (!a.ws || (size_t)KS * per_split > a.ws_bytes)) KS = a.ws ? (int)(a.ws_bytes / per_split) : 1;
     if (KS < 1) KS = 1;
@@ -1841,18 +1862,20 @@ int attn_launch(const AttnArgs &a, hipStream_t st, hipError_t *err) {
     const int G = a.Hq / a.Hkv;
     const int mtiles = (a.TT_cap * G + ATT_MTILE - 1) / ATT_MTILE;
     const int base_wgs = a.batch * a.Hkv * mtiles;
-    // Few (sequence, kv head, row tile) items: the barrier-free small-batch kernel.  64-wide heads take it at every batch: the
+    // 64-wide heads take the small-batch kernel at every batch: the
     // large-batch tiles are laid out for 128 columns, and against the plain kernel (the same call on a cache whose strides keep
     // it off the matrix cores) it is ahead at both ends, one sequence of 8 nodes and 40 keys 5.1 us against 7.5, 3 of 64 and
     // 1,500 12.9 against 206, 64 of 128 and 4,000 455 against 19,500.
     if (a.D == 64) return wave_launch<64>(a, st, err);
-    if (base_wgs < 128) return wave_launch<128>(a, st, err);
     // The balanced schedule wherever its plan fits (one lane per sequence, a slot for every tile count): also for batches of
     // thousands of whole (sequence, kv head, row tile) items, whose lengths differ (64 sequences of 256 .. 4,096 keys: 295 us
     // with one workgroup per item, 234 balanced).
     const int P = 2 * a.n_cu / a.Hkv;
     const bool gang = a.batch <= 64 && mtiles <= 63 && P >= mtiles * (mtiles + 1) / 2 && a.ws &&
                       (size_t)a.Hkv * P * gang_slot_bytes(a.D) <= a.ws_bytes;
+    const int mblocks = (a.TT_cap * G + 31) / 32;
+    const int64_t units = (int64_t)a.batch * a.Hkv * mblocks;
+    if (wave_ahead(units, base_wgs, mblocks, max_blocks(a)) || (base_wgs < 128 && !gang)) return wave_launch<128>(a, st, err);
     if (!gang) {
         launch_kernel(KID_ATTN, st, attn_tile_kernel<128>, dim3(a.Hkv, mtiles, a.batch), dim3(256), TILE_LDS_BYTES, a);
         *err = hipGetLastError();

@@ -225,3 +225,12 @@ def test_shared_merge_at_its_edges():
                          [(64, 4, L) for L in (864, 865, 993, 1121, 1500, 1800)] + [(64, 72, 865), (64, 100, 1856), (64, 100, 1857)])
 def test_numbers_of_key_splits(D, Hkv, L):
     check_case(oracle_case(0, cfg=_cfg("bf16", D, [(32, 5, 6)], [L], Hkv, Hkv)))
+
+
+# both sides of the lines between the small-batch kernel and the balanced schedule: 320 units of four row blocks to a kv head,
+# 256 and 320 of two, 256 and 260 of one; one sequence of that length among short ones
+@pytest.mark.parametrize("B,Hq,Hkv,L", [(B, Hq, Hkv, L + i) for B, Hq, Hkv, L in ((40, 8, 2, 2336), (32, 8, 4, 4768), (40, 8, 4, 608),
+                                                                                 (64, 4, 4, 6368)) for i in (0, 1)] +
+                         [(52, 5, 5, 150)])
+def test_lines_between_the_two_kernels(B, Hq, Hkv, L):
+    check_case(oracle_case(0, cfg=_cfg("bf16", 128, [(32, 5, 6)] * B, [L] + [7 + 40 * (b % 3) for b in range(1, B)], Hq, Hkv)))
