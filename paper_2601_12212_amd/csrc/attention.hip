@@ -1795,12 +1795,16 @@ static int64_t max_blocks(const AttnArgs &a) { return ((int64_t)a.max_prefix_len
 //   up to 512, 8B shape, 8 sequences (512): 150 keys 17 | 26, 400 22 | 28, 1,000 28 | 32, 1,700 40 | 41, 2,100 49 | 50, 2,500 56 | 49; 6 (384): 2,100
 //     39 | 45, 3,000 60 | 54, 8,192 133 | 86; two row blocks, 4 sequences (320): 150 16.5 | 17.5, 400 22 | 28, 700 28 | 27; one, 12 (384): 150 17 | 14, 400 29 | 30;
 //   beyond, 12 sequences of the 8B shape (768): 30 keys 17 | 22, 150 23.5 | 22.8, 400 30 | 41, 1,000 43 | 40, and 6 of 128 nodes 400 32 | 28: no line.
-// The keys are the longest that the caller allows for, and a step that is captured once allows for more than most replays bring:
-// so up to 256 units of fewer than 128 tiles stay with the small-batch kernel, which loses little at the far end (8 % with 4
-// sequences of 8,192 keys) and is two and a half times as fast at a thousand.  (The line was 128 row tiles, whatever the keys.)
+// The keys are the longest that the caller allows for; a batch of differing lengths brings fewer, and so does most often a step that is
+// captured once.  The schedule gains less by short sequences than the small-batch kernel, whose work goes by units: at 280 units of 7
+// rows a node and lengths from a quarter of the longest up, 1,700 keys 24 | 37, 4,000 30 | 50, 8,192 54 | 49, at 392 39 | 43 and 85 | 56 with 4,000 and
+// 8,192, at 504 47 | 47 and 95 | 69.  So the lines above, of equal lengths, are for 128 tiles and more, and below them the schedule begins
+// where such a batch has caught up, and not at all up to 256 units, where the small-batch kernel loses little at the far end
+// (8 % with 4 sequences of 8,192 keys) and is two and a half times as fast at a thousand.
 static bool wave_ahead(int64_t units, int64_t tiles, int mblocks, int64_t nb) {
     if (units <= 256) return tiles < 128 || nb <= (mblocks == 2 ? 150 : 200) * wave_splits(128, units, nb);
-    return units <= 512 && nb <= (mblocks == 1 ? 0 : mblocks == 2 ? 20 : 100 - units / 12);
+    if (units > 512 || mblocks == 1) return false;
+    return nb <= (mblocks == 2 ? 20 : tiles < 128 ? 320 - units / 3 : 100 - units / 12);
 }
 
 // The small-batch kernel and, with key splits, its merge.

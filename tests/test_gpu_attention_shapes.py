@@ -229,7 +229,7 @@ def test_numbers_of_key_splits(D, Hkv, L):
 
 # both sides of the lines between the small-batch kernel and the balanced schedule: 320 units of four row blocks to a kv head,
 # 256 and 320 of two, 256 and 260 of one; one sequence of that length among short ones
-@pytest.mark.parametrize("B,Hq,Hkv,L", [(B, Hq, Hkv, L + i) for B, Hq, Hkv, L in ((40, 8, 2, 2336), (32, 8, 4, 4768), (40, 8, 4, 608),
+@pytest.mark.parametrize("B,Hq,Hkv,L", [(B, Hq, Hkv, L + i) for B, Hq, Hkv, L in ((40, 8, 2, 6816), (64, 8, 2, 1824), (32, 8, 4, 4768), (40, 8, 4, 608),
                                                                                  (64, 4, 4, 6368)) for i in (0, 1)] +
                          [(52, 5, 5, 150)])
 def test_lines_between_the_two_kernels(B, Hq, Hkv, L):
