@@ -294,14 +294,18 @@ __device__ __forceinline__ float key_edge(u32 k16) { return k16 <= 0x007Fu ? -IN
 // a workgroup took; 1,000 now).
 __device__ __forceinline__ u32 wave_kth_of_256(const u32 (&ky)[4], int k) {
     const u32 best = max(max(ky[0], ky[1]), max(ky[2], ky[3]));
-    u32 hi = best, rest = ~best;
+    // Groups without an element (past the row's end, where a wave's last lanes may hold nothing else) do not set the bottom: from -inf
+    // on the bisection is sixteen steps (28 rows of 74,365, k = 28, 10.3 us a call, 9.7 so).
+    const bool some = best > 0x007Fu;
+    u32 hi = best, rest = some ? ~best : 0u;
 #define STEP(CTRL, ROWS)                                               \
     hi = max(hi, (u32)dpp_mov<CTRL, ROWS>(0, (int)hi));                \
     rest = max(rest, (u32)dpp_mov<CTRL, ROWS>(0, (int)rest));
     STEP(0x111, 0xf) STEP(0x112, 0xf) STEP(0x114, 0xf) STEP(0x118, 0xf) STEP(0x142, 0xa) STEP(0x143, 0xc)
 #undef STEP
     hi = (u32)__builtin_amdgcn_readlane((int)hi, 63);
-    u32 lo = ~(u32)__builtin_amdgcn_readlane((int)rest, 63);  // reached by k keys, hi + 1 by none
+    // reached by k keys, hi + 1 by none
+    u32 lo = __popcll(__ballot(some)) >= k ? ~(u32)__builtin_amdgcn_readlane((int)rest, 63) : 0x007Fu;
     while (hi > lo) {
         const u32 mid = lo + ((hi - lo + 1u) >> 1);
         const int n = count_above<4>(ky, mid - 1u);
@@ -386,24 +390,28 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
     auto octet_of = [&](int i, int n) {
         return (i >> 7) * (256 * E) + ((i >> 5) & 3) * (64 * E) + (2 * (i & 31) + (n & 1)) * 8 + (n >> 1) * 512;
     };
-    auto keep_hits = [&](const float (&xv)[8], int start, float T) {
-        int hits = 0;
+    // (A bit for each hit and a loop over the bits, one as a rule: a branch for each element instead cost a quarter microsecond a call.)
+    auto keep_hits = [&](const auto &xv, int s0, int s1, float T) {  // eight elements from s0 on, and eight from s1 on
+        constexpr int N = sizeof(xv) / sizeof(float);
+        u32 hits = 0;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) hits += xv[e] >= T ? 1 : 0;
-        if (hits > 0) {
-            int slot = atomicAdd(&s_n2, hits);
+        for (int e = 0; e < N; ++e) hits |= (xv[e] >= T ? 1u : 0u) << e;
+        if (hits) {
+            int slot = atomicAdd(&s_n2, __popc(hits));
+            for (; hits; hits &= hits - 1) {
+                const int at = __builtin_ctz(hits);
+                float v = xv[0];
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if (xv[e] >= T) {
-                    if (slot < SEL_CAP) s_fin[slot] = make_key(xv[e], (u32)(start + e));
-                    ++slot;
-                }
+                for (int e = 1; e < N; ++e) v = at == e ? xv[e] : v;
+                if (slot < SEL_CAP) s_fin[slot] = make_key(v, (u32)((at < 8 ? s0 : s1 - 8) + at));
+                ++slot;
+            }
         }
     };
     auto reread = [&](int i, int n, float T) {
         float xv[8];
         const int start = load_octet<BF16>(a, g, octet_of(i, n), xv);
-        keep_hits(xv, start, T);
+        keep_hits(xv, start, start, T);
     };
     // candidate t ranks itself against all n2 keys (LDS broadcasts, eight in flight)
     auto rank_and_emit = [&](int n2) {
@@ -462,19 +470,25 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
                 list[at++] = 4 * (w * (8 * S) + 64 * (j >> 2) + lane) + (j & 3);
             }
             __builtin_amdgcn_wave_barrier();
-            // Two on their way at a time: k = 27 is some sixty groups of eight to a wave.  (One after the other, and the lane maxima dealt
-            // to the threads so that of twelve chunks' two waves held two thirds: 336 rows of 12 chunks, k = 27, 11.4 us, 10.0 so,
-            // 340 of 16, k = 12, 8.7 and 8.4, each launch between two events.)
-            const int total = h << per_log2, mask = (1 << per_log2) - 1;
-            for (int q = lane; q - lane < total; q += 128) {
-                float x0[8], x1[8];
-                int s1 = 0;
-                const bool two = q - lane + 64 < total;  // uniform
-                const int q0 = min(q, total - 1), q1 = min(q + 64, total - 1);
-                const int s0 = load_octet<BF16>(a, g, octet_of(list[q0 >> per_log2], q0 & mask), x0);
-                if (two) s1 = load_octet<BF16>(a, g, octet_of(list[q1 >> per_log2], q1 & mask), x1);
-                if (q < total) keep_hits(x0, s0, T0);
-                if (two && q + 64 < total) keep_hits(x1, s1, T0);
+            // A group to a lane, or the two neighbours of a load where there are more: k = 28 is some sixty groups to a wave.  (Each launch
+            // between two events, one group to a lane after the other and lane maxima dealt so that of twelve chunks' two waves held two
+            // thirds: 336 rows of 12 chunks, k = 27, 11.4 us; dealt evenly and two groups asked for at a time 10.0.  Top-k calls of 28 rows of
+            // 115,042, k = 28, replayed: so 9.8 us, with neighbours in a lane 9.65, with the loop over hits 9.05.)
+            const int total = h << per_log2;
+            if (total <= 64) {
+                if (lane < total) reread(list[lane >> per_log2], lane & ((1 << per_log2) - 1), T0);
+            } else {
+                const int pairs_log2 = per_log2 - 1, mask = (1 << pairs_log2) - 1;
+                for (int q = lane; q < total >> 1; q += 64) {
+                    float x[2][8];
+                    const int i = list[q >> pairs_log2], n = 2 * (q & mask);
+                    const int s0 = load_octet<BF16>(a, g, octet_of(i, n), x[0]);
+                    const int s1 = load_octet<BF16>(a, g, octet_of(i, n + 1), x[1]);
+                    float both[16];
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) both[e] = x[e >> 3][e & 7];
+                    keep_hits(both, s0, s1, T0);
+                }
             }
         }
         __syncthreads();

@@ -75,6 +75,20 @@ def check_repeated_rows(V, n, bf16):
     assert np.all(np.abs(lse.cpu().numpy() - wlse[which]) <= 4e-6 * np.maximum(1.0, np.abs(wlse[which])))
 
 
+@pytest.mark.parametrize("V", [18433, 34817, 36865, 67585, 74365, 126977])   # 10, 9, 10, 9, 10 and 16 chunks, the last one begun
+@pytest.mark.parametrize("bf16", [False, True])
+def test_topk_rows_whose_lanes_hold_unequal_shares(V, bf16):
+    x = (np.random.default_rng(V).standard_normal((6, V)) * 3).astype(np.float32)
+    x[1, V // 2:V // 2 + 16] += 30.0                          # neighbours in one lane or two
+    x[2, :V // 4] += 20.0                                     # one wave has all that is read again
+    x[3, 5::V // 40] += 25.0                                  # about one to each of its groups
+    x[4] = -np.inf
+    x[4, 3 * V // 4::V // 100] = np.arange(len(x[4, 3 * V // 4::V // 100]))   # viable entries in fewer groups than k
+    x[5, V - 9:] += 30.0                                      # the overlapping last group of eight
+    for k in (1, 13, 32):
+        check_topk(dt_synth.f32_to_bf16_bits(x) if bf16 else x, k)
+
+
 @pytest.mark.parametrize("V", [1001, 8190, 16381, 40001])
 def test_topk_rows_at_any_two_byte_address(V):
     import paper_2601_12212_amd as dt
