@@ -584,8 +584,8 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
 // trip to memory where the two passes take two and three.  NT threads: the fewest that hold the row with NL <= 4.
 // Behind that trip the waves' instructions bound it, four waves to a SIMD with 1,024 threads: T is found by wave 0 alone while the
 // others sum their exponentials (ONE), not by every wave for itself (by all, 50 rows of 8,000 / 16,000 / 32,000 bf16 entries 5.0 / 6.0 /
-// 7.1 us, 2,000 of 1,000 / 8,000 / 16,000 7.3 / 13.7 / 24.9; by one 4.6 / 5.2 / 6.7 and 6.4 / 12.3 / 20.9,
-// both before hits went by bits: 4.4 / 4.9 / 6.3 and 6.4 / 12.0 since).  In a small launch with a wave to a SIMD
+// 7.1 us, 2,000 of 1,000 / 8,000 / 16,000 7.3 / 13.7 / 24.9; by one 4.6 / 5.2 / 6.7 and 6.4 / 12.3 / 20.9;
+// both before hits went by bits, see keep_hits).  In a small launch with a wave to a SIMD
 // the barrier that this takes costs what it saves, or more (5 rows of 1,024 fp32 entries 3.53 and 3.61): there every wave finds T.
 template <int MODE, int NL, bool BF16, bool VEC, int NT, bool ONE>
 __global__ __launch_bounds__(NT, NL == 4 ? 4 : 8) void row_topk_kernel(RowArgs a, float *top_val, int32_t *top_id, float *lse, int out_stride) {
