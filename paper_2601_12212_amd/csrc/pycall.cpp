@@ -8,12 +8,14 @@
  *
  * Every function takes the positional arguments of its namesake in binding.py and returns the dt_status as an int.
  * Tensors are anything with data_ptr(), shape, stride(), dtype and nbytes.  Those of a torch.Tensor (not of a class derived from it,
- * which may have its own) are read without the interpreter.  The interpreter lock is released during the library call.
+ * which may have its own, nor while a torch-function mode is active, which has its own for all) are read without the interpreter.  The interpreter lock is released during the library call.
  */
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
 #include <torch/csrc/autograd/python_variable.h>
+
+#include <ATen/PythonTorchFunctionTLS.h>
 
 #include "../../include/dt.h"
 
@@ -30,7 +32,7 @@ struct Ptr {
 /* f(tensor) if t is a torch.Tensor.  False if it is not, or if f throws: the interpreter's way then says why. */
 template <typename F>
 static bool direct(PyObject *t, F f) {
-    if ((PyObject *)Py_TYPE(t) != THPVariableClass) return false;
+    if ((PyObject *)Py_TYPE(t) != THPVariableClass || at::impl::torch_function_mode_enabled()) return false;
     try {
         return f(THPVariable_Unpack(t));
     } catch (...) {

@@ -3,6 +3,7 @@ same pointers, sizes, strides, types and byte counts, and to refuse the same obj
 import pytest
 
 torch = pytest.importorskip("torch")
+import torch.overrides  # noqa: E402
 
 from paper_2601_12212_amd import _dtcall  # noqa: E402
 
@@ -70,3 +71,28 @@ def test_tensors_and_other_objects_are_read_alike(call, name):
     assert _outcome(call, args) == want
     assert _outcome(call, [a.as_subclass(Derived) if isinstance(a, torch.Tensor) and a.layout == torch.strided else a
                            for a in args]) == want
+
+
+class Redirected(torch.overrides.TorchFunctionMode):
+    """Sees every tensor function that the marshalling calls and answers data_ptr() itself."""
+
+    def __init__(self):
+        super().__init__()
+        self.seen = set()
+
+    def __torch_function__(self, func, types, args=(), kwargs=None):
+        self.seen.add(getattr(func, "__name__", str(func)))
+        if func is torch.Tensor.data_ptr:
+            return 0
+        return func(*args, **(kwargs or {}))
+
+
+def test_an_active_torch_function_mode_is_asked(call):
+    args = CASES["a misaligned workspace"]
+    plain = _outcome(call, args)
+    no_pointers = _outcome(call, [None if isinstance(a, torch.Tensor) and a is not args[0] else a for a in args])
+    with Redirected() as mode:
+        got = _outcome(call, args)
+    assert {"data_ptr", "stride"} <= mode.seen, mode.seen
+    assert got != plain and got == no_pointers     # the mode's answers went into the call
+    assert _outcome(call, args) == plain
