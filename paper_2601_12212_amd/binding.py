@@ -1,7 +1,11 @@
 """Binding of libdt.so.  Argument marshalling only: the launching entry points go through the native module _dtcall
-(csrc/pycall.cpp), the host-only ones through ctypes."""
+(csrc/pycall.c), the host-only ones through ctypes."""
 import ctypes as C
+import importlib.util
 import os
+import warnings
+
+from .build import reader_path
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libdt.so")
@@ -97,8 +101,24 @@ def _native():
 
         from . import _dtcall
         _dtcall.setup(torch.float32, torch.bfloat16, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+        _dtcall.set_reader(_tensor_reader(torch.__version__))
         _call = _dtcall
     return _call
+
+
+def _tensor_reader(torch_version):
+    """What reads tensors without the interpreter, if it was built against this torch (an extension of another torch is not
+    even loaded), else None: _dtcall then asks the tensors' methods, about 1 us a call more."""
+    path = reader_path(torch_version)
+    try:
+        spec = importlib.util.spec_from_file_location("_dttensor", path)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        return module.reader
+    except ImportError as e:
+        warnings.warn("dt: no tensor reader for torch %s (%s); run `python paper_2601_12212_amd/build.py`.  Arguments are read "
+                      "through the tensors' methods, about 1 us a call slower" % (torch_version, e), RuntimeWarning)
+        return None
 
 
 def _dtype(t):

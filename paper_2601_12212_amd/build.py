@@ -1,6 +1,6 @@
-"""Compile the HIP kernels and the C ABI into paper_2601_12212_amd/libdt.so (gfx950 only), and the argument marshalling of
-the Python binding into paper_2601_12212_amd/_dtcall.so (g++; finds libdt.so beside itself, torch's libraries where the
-interpreter has loaded them)."""
+"""Compile the HIP kernels and the C ABI into paper_2601_12212_amd/libdt.so (gfx950 only), the argument marshalling of
+the Python binding into paper_2601_12212_amd/_dtcall.so (gcc; finds libdt.so beside itself), and what reads a tensor's
+properties for it without the interpreter into _dttensor-<torch's version>.so (g++; against the torch that is installed)."""
 import os
 import subprocess
 import sys
@@ -39,17 +39,36 @@ def build(verbose=False):
     tmp = LIB + ".tmp%d" % os.getpid()
     subprocess.check_call([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs)
     os.replace(tmp, LIB)
+    include = "-I" + sysconfig.get_paths()["include"]
     tmp = PYCALL + ".tmp%d" % os.getpid()
-    import torch
+    subprocess.check_call(["gcc", "-O2", "-shared", "-fPIC", "-Wall", include, os.path.join(CSRC, "pycall.c"), "-o", tmp,
+                           "-L" + HERE, "-l:libdt.so", "-Wl,-rpath,$ORIGIN"])
+    os.replace(tmp, PYCALL)
+    build_reader(include)
+    return LIB
+
+
+def reader_path(torch_version):
+    """Where the tensor reader built against that torch is."""
+    return os.path.join(HERE, "_dttensor-%s.so" % torch_version)
+
+
+def build_reader(include):
+    try:
+        import torch
+    except ImportError:
+        print("no torch here: tensors will be read through their methods")
+        return
     tdir = os.path.dirname(torch.__file__)
-    subprocess.check_call(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-I" + sysconfig.get_paths()["include"],
+    path = reader_path(torch.__version__)
+    tmp = path + ".tmp%d" % os.getpid()
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", include,
                            "-isystem", os.path.join(tdir, "include"),
                            "-isystem", os.path.join(tdir, "include", "torch", "csrc", "api", "include"),
                            "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch.compiled_with_cxx11_abi(),
-                           os.path.join(CSRC, "pycall.cpp"), "-o", tmp, "-L" + HERE, "-l:libdt.so", "-Wl,-rpath,$ORIGIN",
+                           os.path.join(CSRC, "tensor_reader.cpp"), "-o", tmp,
                            "-L" + os.path.join(tdir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"])
-    os.replace(tmp, PYCALL)
-    return LIB
+    os.replace(tmp, path)
 
 
 if __name__ == "__main__":

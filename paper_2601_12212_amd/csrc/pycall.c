@@ -2,56 +2,36 @@
  * Argument marshalling between the Python binding and the C ABI: tensors -> device pointers, sizes and strides, the
  * current torch stream -> hipStream_t.  One native call per entry point: an eager step at batch 1 is six kernel launches
  * of about 3 us of host time each, and marshalling its three calls through ctypes and torch's Python-level stream
- * object cost another 5.5 us per call (2.8 of them the stream).  The fifteen arguments of a level step take 1.28 us through the
- * interpreter's methods of a tensor and 0.40 read from the tensor itself: the headline tree drafted level by level, bound by the
- * host, 101 -> 96 us.
+ * object cost another 5.5 us per call (2.8 of them the stream); here it is about 1 us.
  *
  * Every function takes the positional arguments of its namesake in binding.py and returns the dt_status as an int.
- * Tensors are anything with data_ptr(), shape, stride(), dtype and nbytes.  Those of a torch.Tensor (not of a class derived from it,
- * which may have its own, nor while a torch-function mode is active, which has its own for all) are read without the interpreter.  The interpreter lock is released during the library call.
+ * Tensors are anything with data_ptr(), shape, stride(), dtype and nbytes.  This module knows the interpreter and no torch; what
+ * can be read without the interpreter goes through a reader that was built for the torch that is running (tensor_reader.cpp), if
+ * set_reader() was given one.  The interpreter lock is released during the library call.
  */
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
-#include <torch/csrc/autograd/python_variable.h>
-
-#include <ATen/PythonTorchFunctionTLS.h>
-
 #include "../../include/dt.h"
+#include "tensor_reader.h"
 
 static PyObject *g_f32, *g_bf16, *g_get_device, *g_get_stream;  /* set by setup() */
 static PyObject *s_data_ptr, *s_shape, *s_stride, *s_dtype, *s_nbytes;
-
-/* a device pointer, or a stream: what the library's parameter is a pointer to */
-struct Ptr {
-    void *p;
-    template <typename T>
-    operator T *() const { return (T *)p; }
-};
-
-/* f(tensor) if t is a torch.Tensor.  False if it is not, or if f throws: the interpreter's way then says why. */
-template <typename F>
-static bool direct(PyObject *t, F f) {
-    if ((PyObject *)Py_TYPE(t) != THPVariableClass || at::impl::torch_function_mode_enabled()) return false;
-    try {
-        return f(THPVariable_Unpack(t));
-    } catch (...) {
-        return false;
-    }
-}
+static PyObject *g_capsule;                                     /* set by set_reader(); holds the reader */
+static const dt_tensor_reader *g_reader;
 
 /* Each helper does nothing once an error is set, so a call's arguments are converted in a row and checked once. */
-static Ptr ptr(PyObject *t) {
+static void *ptr(PyObject *t) {
     void *p = NULL;
     PyObject *r;
-    if (t == Py_None || PyErr_Occurred()) return Ptr{NULL};
-    if (direct(t, [&](const at::Tensor &x) { p = x.data_ptr(); return true; })) return Ptr{p};
+    if (t == Py_None || PyErr_Occurred()) return NULL;
+    if (g_reader && g_reader->data_ptr(t, &p)) return p;
     r = PyObject_CallMethodNoArgs(t, s_data_ptr);
     if (r) {
         p = PyLong_AsVoidPtr(r);
         Py_DECREF(r);
     }
-    return Ptr{p};
+    return p;
 }
 static long long num(PyObject *o) { return PyErr_Occurred() ? 0 : PyLong_AsLongLong(o); }
 static int inum(PyObject *o) {
@@ -67,13 +47,7 @@ static void shape(PyObject *t, int n, int exact, long long *out) {
     int i;
     for (i = 0; i < n; ++i) out[i] = 0;
     if (PyErr_Occurred()) return;
-    if (direct(t, [&](const at::Tensor &x) {
-            const auto sizes = x.sizes();
-            if (exact ? (int)sizes.size() != n : (int)sizes.size() < n) return false;
-            for (int j = 0; j < n; ++j) out[j] = sizes[j];
-            return true;
-        }))
-        return;
+    if (g_reader && g_reader->sizes(t, n, exact, out)) return;
     s = PyObject_GetAttr(t, s_shape);
     if (!s) return;
     if (!PyTuple_Check(s) || (exact ? PyTuple_GET_SIZE(s) != n : PyTuple_GET_SIZE(s) < n))
@@ -86,7 +60,7 @@ static long long stride(PyObject *t, long dim) {
     PyObject *d, *r;
     long long v = 0;
     if (PyErr_Occurred()) return 0;
-    if (direct(t, [&](const at::Tensor &x) { v = x.stride(dim); return true; })) return v;
+    if (g_reader && g_reader->stride(t, dim, &v)) return v;
     d = PyLong_FromLong(dim);
     r = d ? PyObject_CallMethodOneArg(t, s_stride, d) : NULL;
     if (r) v = num(r);
@@ -97,13 +71,9 @@ static long long stride(PyObject *t, long dim) {
 static dt_dtype dtype(PyObject *t) {
     dt_dtype v = DT_F32;
     PyObject *d;
+    int bf16;
     if (PyErr_Occurred()) return v;
-    if (direct(t, [&](const at::Tensor &x) {
-            const at::ScalarType s = x.scalar_type();
-            v = s == at::kBFloat16 ? DT_BF16 : DT_F32;
-            return s == at::kBFloat16 || s == at::kFloat;
-        }))
-        return v;
+    if (g_reader && g_reader->dtype(t, &bf16)) return bf16 ? DT_BF16 : DT_F32;
     d = PyObject_GetAttr(t, s_dtype);
     if (!d) return v;
     if (d == g_bf16) v = DT_BF16;
@@ -115,7 +85,7 @@ static size_t nbytes(PyObject *t) {
     PyObject *r;
     size_t v = 0;
     if (t == Py_None || PyErr_Occurred()) return 0;
-    if (direct(t, [&](const at::Tensor &x) { v = x.nbytes(); return true; })) return v;
+    if (g_reader && g_reader->nbytes(t, &v)) return v;
     r = PyObject_GetAttr(t, s_nbytes);
     if (r) {
         v = (size_t)num(r);
@@ -124,20 +94,20 @@ static size_t nbytes(PyObject *t) {
     return v;
 }
 /* torch's current stream on the current device */
-static Ptr stream(void) {
+static void *stream(void) {
     void *p = NULL;
     PyObject *dev, *st;
-    if (PyErr_Occurred()) return Ptr{NULL};
+    if (PyErr_Occurred()) return NULL;
     if (!g_get_stream) {
         PyErr_SetString(PyExc_RuntimeError, "setup() has not been called");
-        return Ptr{NULL};
+        return NULL;
     }
     dev = PyObject_CallNoArgs(g_get_device);
     st = dev ? PyObject_CallOneArg(g_get_stream, dev) : NULL;
     if (st) p = PyLong_AsVoidPtr(st);
     Py_XDECREF(dev);
     Py_XDECREF(st);
-    return Ptr{p};
+    return p;
 }
 
 #define NEED(n)                                                                                      \
@@ -157,7 +127,7 @@ static Ptr stream(void) {
 /* logits, k, top_val, top_id, lse, ws */
 FN(topk_rows) {
     NEED(6)
-    const Ptr st = stream(), x = ptr(a[0]), v = ptr(a[2]), i = ptr(a[3]), l = ptr(a[4]), w = ptr(a[5]);
+    void *const st = stream(), *const x = ptr(a[0]), *const v = ptr(a[2]), *const i = ptr(a[3]), *const l = ptr(a[4]), *const w = ptr(a[5]);
     const dt_dtype t = dtype(a[0]);
     const long long row = stride(a[0], 0);
     const int k = inum(a[1]);
@@ -169,7 +139,7 @@ FN(topk_rows) {
 /* logits, k, top_val, top_id, lse */
 FN(topk_rows_static) {
     NEED(5)
-    const Ptr st = stream(), x = ptr(a[0]), v = ptr(a[2]), i = ptr(a[3]), l = ptr(a[4]);
+    void *const st = stream(), *const x = ptr(a[0]), *const v = ptr(a[2]), *const i = ptr(a[3]), *const l = ptr(a[4]);
     const dt_dtype t = dtype(a[0]);
     const long long row = stride(a[0], 0);
     const int k = inum(a[1]);
@@ -181,9 +151,9 @@ FN(topk_rows_static) {
    anc_mask, ws, flags */
 FN(build_tree) {
     NEED(16)
-    const Ptr st = stream(), prm = ptr(a[0]), x = ptr(a[1]), off = ptr(a[2]), root = ptr(a[4]);
-    Ptr o[8];
-    const Ptr w = ptr(a[14]);
+    void *const st = stream(), *const prm = ptr(a[0]), *const x = ptr(a[1]), *const off = ptr(a[2]), *const root = ptr(a[4]);
+    void *o[8];
+    void *const w = ptr(a[14]);
     const dt_dtype t = dtype(a[1]);
     const long long row = stride(a[1], 0), rows = num(a[3]);
     const int cap = inum(a[5]), flags = inum(a[15]);
@@ -200,9 +170,9 @@ FN(build_tree) {
    anc_mask, scale, out, ws */
 FN(tree_attention) {
     NEED(14)
-    const Ptr st = stream();
-    Ptr p[7];
-    const Ptr mask = ptr(a[10]), out = ptr(a[12]), w = ptr(a[13]);
+    void *const st = stream();
+    void *p[7];
+    void *const mask = ptr(a[10]), *const out = ptr(a[12]), *const w = ptr(a[13]);
     const dt_dtype t = dtype(a[0]);
     const int maxlen = inum(a[7]);
     const long long stok = num(a[8]), shead = num(a[9]);
@@ -221,9 +191,9 @@ FN(tree_attention) {
    best_node, path_nodes, out_tokens, node_argmax, ws */
 FN(accept_tree) {
     NEED(17)
-    const Ptr st = stream(), x = ptr(a[2]);
-    Ptr p[6], o[5];
-    const Ptr w = ptr(a[16]);
+    void *const st = stream(), *const x = ptr(a[2]);
+    void *p[6], *o[5];
+    void *const w = ptr(a[16]);
     const int mode = inum(a[0]);
     const float temp = fnum(a[1]);
     const dt_dtype t = dtype(a[2]);
@@ -242,9 +212,9 @@ FN(accept_tree) {
    exp_pos, exp_mask, ws, flags */
 FN(expand_level) {
     NEED(15)
-    const Ptr st = stream(), prm = ptr(a[1]), x = ptr(a[2]), len = ptr(a[4]), state = ptr(a[6]);
-    Ptr o[6];
-    const Ptr w = ptr(a[13]);
+    void *const st = stream(), *const prm = ptr(a[1]), *const x = ptr(a[2]), *const len = ptr(a[4]), *const state = ptr(a[6]);
+    void *o[6];
+    void *const w = ptr(a[13]);
     const dt_dtype t = dtype(a[2]);
     const long long row = stride(a[2], 0);
     const int level = inum(a[0]), R = inum(a[3]), cap = inum(a[5]), flags = inum(a[14]);
@@ -260,8 +230,8 @@ FN(expand_level) {
 /* params, V, root_token, TT_cap, state, n_nodes, tokens, parents, depth, score, logp, src_row, anc_mask, flags */
 FN(finish_tree) {
     NEED(14)
-    const Ptr st = stream(), prm = ptr(a[0]), root = ptr(a[2]), state = ptr(a[4]);
-    Ptr o[8];
+    void *const st = stream(), *const prm = ptr(a[0]), *const root = ptr(a[2]), *const state = ptr(a[4]);
+    void *o[8];
     const int V = inum(a[1]), cap = inum(a[3]), flags = inum(a[13]);
     long long b[1];
     int i;
@@ -273,9 +243,9 @@ FN(finish_tree) {
    cached_action, params_out, action_out, queried_out, logits_out, ws */
 FN(policy_step) {
     NEED(19)
-    const Ptr st = stream();
-    Ptr p[8], o[6];
-    const Ptr w = ptr(a[18]);
+    void *const st = stream();
+    void *p[8], *o[6];
+    void *const w = ptr(a[18]);
     const dt_dtype t = dtype(a[0]);
     const long long row = stride(a[0], 0);
     const int interval = inum(a[8]), sample = inum(a[9]);
@@ -294,9 +264,9 @@ FN(policy_step) {
    kv_stride_head, n_nodes, path_nodes, accept_len, out_tokens, TT_cap, new_prefix_len, next_root_token */
 FN(commit) {
     NEED(18)
-    const Ptr st = stream();
-    Ptr p[6], q[4];
-    const Ptr len = ptr(a[16]), root = ptr(a[17]);
+    void *const st = stream();
+    void *p[6], *q[4];
+    void *const len = ptr(a[16]), *const root = ptr(a[17]);
     const dt_dtype t = dtype(a[0]);
     const int Hkv = inum(a[1]), D = inum(a[2]), cap = inum(a[15]);
     const long long stok = num(a[9]), shead = num(a[10]);
@@ -312,8 +282,8 @@ FN(commit) {
    elapsed_per_seq */
 FN(reward_step) {
     NEED(9)
-    const Ptr st = stream(), len = ptr(a[0]), per = ptr(a[8]);
-    Ptr p[5];
+    void *const st = stream(), *const len = ptr(a[0]), *const per = ptr(a[8]);
+    void *p[5];
     const int bonus = inum(a[1]);
     const float secs = fnum(a[2]);
     long long b[1];
@@ -332,11 +302,22 @@ FN(setup) {
     Py_XSETREF(g_get_stream, a[3]);
     Py_RETURN_NONE;
 }
+/* the `reader` of a tensor reader's module, or None: through the tensors' methods only */
+FN(set_reader) {
+    const dt_tensor_reader *r = NULL;
+    NEED(1)
+    if (a[0] != Py_None && !(r = (const dt_tensor_reader *)PyCapsule_GetPointer(a[0], DT_TENSOR_READER))) return NULL;
+    Py_INCREF(a[0]);
+    Py_XSETREF(g_capsule, a[0]);
+    g_reader = r;
+    Py_RETURN_NONE;
+}
 
 #define ENTRY(f) {#f, (PyCFunction)(void (*)(void))f, METH_FASTCALL, NULL}
 static PyMethodDef methods[] = {ENTRY(topk_rows), ENTRY(topk_rows_static), ENTRY(build_tree), ENTRY(tree_attention),
                                 ENTRY(accept_tree), ENTRY(expand_level), ENTRY(finish_tree), ENTRY(policy_step),
-                                ENTRY(commit), ENTRY(reward_step), ENTRY(setup), {NULL, NULL, 0, NULL}};
+                                ENTRY(commit), ENTRY(reward_step), ENTRY(setup), ENTRY(set_reader),
+                                {NULL, NULL, 0, NULL}};
 static struct PyModuleDef module = {PyModuleDef_HEAD_INIT, "_dtcall", NULL, -1, methods, NULL, NULL, NULL, NULL};
 
 PyMODINIT_FUNC PyInit__dtcall(void) {

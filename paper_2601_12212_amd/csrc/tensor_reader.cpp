@@ -1,0 +1,64 @@
+/*
+ * Reads a torch.Tensor's pointer, sizes, strides, type and byte count without the interpreter: the fifteen arguments of a level
+ * step take 1.28 us through the tensor's methods and 0.40 so; the headline tree drafted level by level, bound by the host, 101 -> 96 us.
+ *
+ * Built against one torch and named after its version; pycall.c runs without it.  Only objects whose type is torch.Tensor itself:
+ * a derived class may have methods of its own, and while a torch-function mode is active every tensor has the mode's.
+ */
+#include <torch/csrc/autograd/python_variable.h>
+
+#include <ATen/PythonTorchFunctionTLS.h>
+
+#include "tensor_reader.h"
+
+namespace {
+
+template <typename F>
+int read(PyObject *t, F f) {
+    if ((PyObject *)Py_TYPE(t) != THPVariableClass || at::impl::torch_function_mode_enabled()) return 0;
+    try {
+        return f(THPVariable_Unpack(t)) ? 1 : 0;
+    } catch (...) {
+        return 0;
+    }
+}
+
+int data_ptr(PyObject *t, void **out) {
+    return read(t, [&](const at::Tensor &x) { *out = x.data_ptr(); return true; });
+}
+int sizes(PyObject *t, int n, int exact, long long *out) {
+    return read(t, [&](const at::Tensor &x) {
+        const auto s = x.sizes();
+        if (exact ? (int)s.size() != n : (int)s.size() < n) return false;
+        for (int i = 0; i < n; ++i) out[i] = s[i];
+        return true;
+    });
+}
+int stride(PyObject *t, long dim, long long *out) {
+    return read(t, [&](const at::Tensor &x) { *out = x.stride(dim); return true; });
+}
+int dtype(PyObject *t, int *bf16) {
+    return read(t, [&](const at::Tensor &x) {
+        const at::ScalarType s = x.scalar_type();
+        *bf16 = s == at::kBFloat16;
+        return s == at::kBFloat16 || s == at::kFloat;
+    });
+}
+int nbytes(PyObject *t, size_t *out) {
+    return read(t, [&](const at::Tensor &x) { *out = x.nbytes(); return true; });
+}
+
+dt_tensor_reader table = {data_ptr, sizes, stride, dtype, nbytes};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_dttensor", NULL, -1, NULL, NULL, NULL, NULL, NULL};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__dttensor(void) {
+    PyObject *m = PyModule_Create(&module), *reader = m ? PyCapsule_New(&table, DT_TENSOR_READER, NULL) : NULL;
+    if (!reader || PyModule_AddObject(m, "reader", reader) < 0) {
+        Py_XDECREF(reader);
+        Py_XDECREF(m);
+        return NULL;
+    }
+    return m;
+}

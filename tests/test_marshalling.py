@@ -1,11 +1,15 @@
 """The native argument marshalling reads a torch.Tensor itself and anything else through its methods: both ways have to see the
 same pointers, sizes, strides, types and byte counts, and to refuse the same objects.  Every call here is refused before a launch."""
+import subprocess
+import sys
+
 import pytest
 
 torch = pytest.importorskip("torch")
 import torch.overrides  # noqa: E402
 
-from paper_2601_12212_amd import _dtcall  # noqa: E402
+from paper_2601_12212_amd import _dtcall, binding  # noqa: E402
+from tests.conftest import ROOT  # noqa: E402
 
 
 class Duck:
@@ -24,6 +28,10 @@ class Derived(torch.Tensor):
 
 @pytest.fixture
 def call():
+    binding._native()
+    reader = binding._tensor_reader(torch.__version__)
+    assert reader is not None                       # else both ways are one
+    _dtcall.set_reader(reader)
     _dtcall.setup(torch.float32, torch.bfloat16, lambda: 0, lambda device: 0)
     yield _dtcall
     _dtcall.setup(torch.float32, torch.bfloat16, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
@@ -96,3 +104,33 @@ def test_an_active_torch_function_mode_is_asked(call):
     assert {"data_ptr", "stride"} <= mode.seen, mode.seen
     assert got != plain and got == no_pointers     # the mode's answers went into the call
     assert _outcome(call, args) == plain
+
+
+def test_the_marshalling_needs_no_torch():
+    code = ("import sys\n"
+            "from paper_2601_12212_amd import _dtcall\n"
+            "assert 'torch' not in sys.modules\n"
+            "class T:\n"
+            "    shape, dtype, nbytes = (4, 64), 'bf16', 512\n"
+            "    def data_ptr(self): return 0\n"
+            "    def stride(self, dim): return 64\n"
+            "_dtcall.setup('f32', 'bf16', lambda: 0, lambda device: 0)\n"
+            "print(_dtcall.topk_rows(T(), 3, T(), T(), T(), None))\n")
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr
+    assert r.stdout.split() == ["-1"]               # null pointers
+
+
+def test_another_torch_is_named_and_its_tensors_read_through_their_methods(call):
+    with pytest.warns(RuntimeWarning, match="no tensor reader for torch 0.0.0"):
+        reader = binding._tensor_reader("0.0.0")
+    assert reader is None
+    want = {name: _outcome(call, args) for name, args in CASES.items()}
+    call.set_reader(None)
+    for name, args in CASES.items():
+        assert _outcome(call, args) == want[name], name
+
+
+def test_what_is_not_a_reader_is_refused(call):
+    with pytest.raises(ValueError):
+        call.set_reader(7)
