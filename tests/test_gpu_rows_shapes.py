@@ -123,3 +123,40 @@ def test_a_launch_of_more_threads_than_one_grid_dimension_takes():
     assert_tree_equal(st.tree(0), want)
     del st
     torch.cuda.empty_cache()
+
+
+def seconds_of_a_call(x, k, n=20):
+    """Median over replays of a graph of n calls."""
+    import paper_2601_12212_amd as dt
+    R, V = x.shape
+    val = torch.empty((R, k), dtype=torch.float32, device="cuda")
+    idx = torch.empty((R, k), dtype=torch.int32, device="cuda")
+    lse = torch.empty(R, dtype=torch.float32, device="cuda")
+    ws = torch.zeros(dt.dt_workspace_bytes(1, R, V, 8, 1, 64), dtype=torch.uint8, device="cuda")
+    call = lambda: dt.dt_topk_rows(x, k, val, idx, lse, ws)
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for _ in range(n):
+            call()
+    times = []
+    for _ in range(12):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        graph.replay()
+        b.record()
+        torch.cuda.synchronize()
+        times.append(a.elapsed_time(b))
+    return sorted(times)[6] / n
+
+
+# neighbours, and how many times as long as rows without them a call may take: 1.2 where they are spread over the bound's
+# slots, 2.3 where they fall into few of them
+@pytest.mark.parametrize("M,times", [(512, 1.7), (1024, 1.7)])
+def test_neighbours_among_the_best_do_not_slow_top_k_rows_down(M, times):
+    x = torch.randn((51, 128256), generator=torch.Generator("cuda").manual_seed(M), device="cuda") * 3
+    plain = x.bfloat16()
+    x[:, 1000:1000 + M] += 20
+    took = seconds_of_a_call(x.bfloat16(), 10), seconds_of_a_call(plain, 10)
+    assert took[0] <= times * took[1], took
