@@ -320,13 +320,26 @@ __device__ __forceinline__ u32 wave_kth_of_256(const u32 (&ky)[4], int k) {
 // only count).  A bit for each hit and a loop over the bits, one as a rule, behind one LDS add: a branch and an add for each element, in
 // waves that run alone or wait for each other at the next barrier, cost a selection of k = 28 0.25 us and rows that a workgroup holds
 // 0.3 to 0.7 of 5 to 7 (128 rows of 32,000 entries, k = 12, 6.93 -> 6.26, 500 of 4,000 5.71 -> 5.13, 2,000 of 8,000 12.8 -> 12.0).
+// A hit of the loop costs five times an element of the row of branches, so a wave with more than two to a lane takes the branches: where the
+// best of a row are neighbours, eight and more come to one lane (28 rows of 115,042, k = 28, 32 neighbours raised by 20 12.7 us by the loop, 9.5
+// so; 50 of 32,000, k = 12, 7.7 and 6.6; two and three to a lane the same).
+#define HITS_ONE_BY_ONE 2
 template <int N, class X, class Id>
 __device__ __forceinline__ void keep_hits(X x, Id id_of, float T, int *n, u64 *list) {
     u32 hits = 0;
 #pragma unroll
     for (int e = 0; e < N; ++e) hits |= (x(e) >= T ? 1u : 0u) << e;
     if (hits) {
-        int slot = atomicAdd(n, __popc(hits));
+        const int c = __popc(hits);
+        int slot = atomicAdd(n, c);
+        if (__builtin_amdgcn_ballot_w64(c > HITS_ONE_BY_ONE)) {  // uniform
+#pragma unroll
+            for (int e = 0; e < N; ++e) {
+                if ((hits >> e & 1u) && slot < SEL_CAP) list[slot] = make_key(x(e), (u32)id_of(e));
+                slot += hits >> e & 1;
+            }
+            return;
+        }
         for (; hits; hits &= hits - 1) {
             const int at = __builtin_ctz(hits);
             float v = x(0);

@@ -125,7 +125,7 @@ def test_a_launch_of_more_threads_than_one_grid_dimension_takes():
     torch.cuda.empty_cache()
 
 
-def seconds_of_a_call(x, k, n=20):
+def time_of_a_call(x, k, n=20):
     """Median over replays of a graph of n calls."""
     import paper_2601_12212_amd as dt
     R, V = x.shape
@@ -151,12 +151,12 @@ def seconds_of_a_call(x, k, n=20):
     return sorted(times)[6] / n
 
 
-# neighbours, and how many times as long as rows without them a call may take: 1.2 where they are spread over the bound's
-# slots, 2.3 where they fall into few of them
-@pytest.mark.parametrize("M,times", [(512, 1.7), (1024, 1.7)])
-def test_neighbours_among_the_best_do_not_slow_top_k_rows_down(M, times):
-    x = torch.randn((51, 128256), generator=torch.Generator("cuda").manual_seed(M), device="cuda") * 3
+# Neighbours, and how many times as long as rows without them a call may take.  1.1 and 2.2 where they are spread over the slots of the
+# bound and where they fall into few of them; 1.25 and 1.65 with the hits of a lane written in a row and in a loop.
+@pytest.mark.parametrize("n,V,k,M,times", [(51, 128256, 10, 512, 1.6), (51, 128256, 10, 1024, 1.6), (28, 115042, 28, 32, 1.45)])
+def test_neighbours_among_the_best_do_not_slow_top_k_rows_down(n, V, k, M, times):
+    x = torch.randn((n, V), generator=torch.Generator("cuda").manual_seed(M), device="cuda") * 3
     plain = x.bfloat16()
     x[:, 1000:1000 + M] += 20
-    took = seconds_of_a_call(x.bfloat16(), 10), seconds_of_a_call(plain, 10)
+    took = time_of_a_call(x.bfloat16(), k), time_of_a_call(plain, k)
     assert took[0] <= times * took[1], took
