@@ -152,11 +152,34 @@ def time_of_a_call(x, k, n=20):
 
 
 # Neighbours, and how many times as long as rows without them a call may take.  1.1 and 2.2 where they are spread over the slots of the
-# bound and where they fall into few of them; 1.25 and 1.65 with the hits of a lane written in a row and in a loop.
-@pytest.mark.parametrize("n,V,k,M,times", [(51, 128256, 10, 512, 1.6), (51, 128256, 10, 1024, 1.6), (28, 115042, 28, 32, 1.45)])
+# bound and where they fall into few of them; 1.25 and 1.65 with the hits of a lane written in a row and in a loop; 3.2 and 250 with
+# one pass over them and k over the row where fewer pairs of lanes than k hold them.
+@pytest.mark.parametrize("n,V,k,M,times", [(51, 128256, 10, 512, 1.6), (51, 128256, 10, 1024, 1.6), (28, 115042, 28, 32, 1.45), (51, 128256, 28, 256, 6)])
 def test_neighbours_among_the_best_do_not_slow_top_k_rows_down(n, V, k, M, times):
     x = torch.randn((n, V), generator=torch.Generator("cuda").manual_seed(M), device="cuda") * 3
     plain = x.bfloat16()
     x[:, 1000:1000 + M] += 20
     took = time_of_a_call(x.bfloat16(), k), time_of_a_call(plain, k)
     assert took[0] <= times * took[1], took
+
+
+# How many neighbours hold all of the best: fewer pairs of lanes than k (the first two bounds do not cut), as many as the list of
+# candidates has places and one more, and more.
+@pytest.mark.parametrize("M", [40, 127, 128, 129, 200, 255, 256, 257, 500, 3000])
+@pytest.mark.parametrize("V,bf16", [(20000, False), (40001, True), (128256, True), (131081, False)])
+def test_topk_rows_whose_best_are_neighbours(V, M, bf16):
+    rng = np.random.default_rng(M)
+    x = (rng.standard_normal((7, V)) * 3).astype(np.float32)
+    at = V // 3
+    x[0, at:at + M] += 20.0
+    x[1, at:at + M] = 20.0                                    # equal: the smallest ids
+    x[2, at:at + M] = 20.0 + rng.integers(0, 2, M)            # two values
+    # Many octaves.  (Not past 2^25: the log-sum-exp's exponents are x log2e rounded once, off by 2^-24 |x|, and no longer those of the
+    # maximum, 0, and the others, some 100 below, from 2^30 on.)
+    x[3, at:at + M] = np.exp2(rng.uniform(5, 25, M))
+    x[4] = -np.inf
+    x[4, at:at + M] = rng.standard_normal(M)                  # the only viable entries
+    x[5] = -x[0]                                              # the worst
+    x[6] = 1.0 + 2.0 ** -20 * rng.integers(0, 300, V)         # one leading half of the key (bf16: equal everywhere)
+    for k in (1, 13, 32):
+        check_topk(dt_synth.f32_to_bf16_bits(x) if bf16 else x, k)
