@@ -252,11 +252,13 @@ __global__ __launch_bounds__(256) void row_stream_kernel(RowArgs a, int S) {
 //      apart in the row (spread_max), little more than k lane maxima reach it, also where the best are neighbours;
 //   2. the 16*NL elements of the pairs of lanes that reach T are read again, (pair, group of eight) over the threads, and the elements
 //      >= T are keyed by (value, id) and ranked by counting.
-// More than 128 such elements (clusters, ties), or a vocabulary of more than 16 chunks, take a second bound first: a
+// More than SEL_CAP such elements (clusters, ties), or a vocabulary of more than 16 chunks, take a second bound first: a
 // histogram of the lane maxima that reach T names the bin of the k-th largest lane maximum.  If that leaves too many as
 // well (the best of the row in fewer pairs than k, ties, fewer than k finite entries), one pass over the pairs left keeps the k best so far.
 // The kernel is two dependent trips to memory (2 x 1.5 us) and the wave arithmetic between them.
-#define SEL_CAP 128
+// Candidates before another bound is taken.  (128, when a lane maximum stood for half as many elements; with pairs 702 rows of 128,256, k = 12, and 150
+// neighbours raised by 20 were 51.8 us, 38.1 so, 51 rows, k = 28, 100 of them 16.4 and 12.1; 2,000 held rows of 8,000, k = 20, 150 of them 81 and 16.8.)
+#define SEL_CAP 256
 #define SEL_LIST (SEL_CAP + 256)
 #define SEL_WAVE_CAP 64  // hot lanes of one wave
 // The eight elements from id0 on of row g; returns where they really start (group_start), those before id0 and past the
@@ -582,7 +584,7 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
     // ---- too many still: one pass over the elements of the lane maxima that reach T1 -----------------------------------------
     // Two groups of eight to a thread at a time.  What reaches the threshold goes on the list; when the list is long, the k best of it
     // stay and the k-th becomes the threshold, so that equal values later in the row no longer reach it.  -inf does not count.
-    // (51 rows of 128,256 bf16 entries, k = 28: 128 to 400 neighbours raised by 20, in fewer pairs than k, 25 to 30 us, all equal 78, all -inf 59, where
+    // (51 rows of 128,256 bf16 entries, k = 28: 256 to 400 neighbours raised by 20, in fewer pairs than k, 28 to 30 us, all equal 78, all -inf 59, where
     // taking the best k times from the whole row took 2,330; k = 10 23, 78 and 59 against 840; k = 1 9, 73 and 59 against 9, 101 and 95.)
     auto keep_best = [&](int n) {
         u64 key[2];

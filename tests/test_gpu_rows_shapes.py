@@ -153,8 +153,8 @@ def time_of_a_call(x, k, n=20):
 
 # Neighbours, and how many times as long as rows without them a call may take.  1.1 and 2.2 where they are spread over the slots of the
 # bound and where they fall into few of them; 1.25 and 1.65 with the hits of a lane written in a row and in a loop; 3.2 and 250 with
-# one pass over them and k over the row where fewer pairs of lanes than k hold them.
-@pytest.mark.parametrize("n,V,k,M,times", [(51, 128256, 10, 512, 1.6), (51, 128256, 10, 1024, 1.6), (28, 115042, 28, 32, 1.45), (51, 128256, 28, 256, 6)])
+# one pass over them and k over the row where fewer pairs of lanes than k hold them; 1.3 and 1.8 with room for 256 and 128 of them.
+@pytest.mark.parametrize("n,V,k,M,times", [(51, 128256, 10, 512, 1.6), (51, 128256, 10, 1024, 1.6), (28, 115042, 28, 32, 1.45), (51, 128256, 28, 256, 6), (51, 128256, 28, 100, 1.55)])
 def test_neighbours_among_the_best_do_not_slow_top_k_rows_down(n, V, k, M, times):
     x = torch.randn((n, V), generator=torch.Generator("cuda").manual_seed(M), device="cuda") * 3
     plain = x.bfloat16()
