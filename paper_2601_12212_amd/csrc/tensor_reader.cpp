@@ -3,7 +3,7 @@
  * step take 1.28 us through the tensor's methods and 0.40 so; the headline tree drafted level by level, bound by the host, 101 -> 96 us.
  *
  * Built against one torch and named after its version; pycall.c runs without it.  Only objects whose type is torch.Tensor itself:
- * a derived class may have methods of its own, and while a torch-function mode is active every tensor has the mode's.
+ * a derived class may have methods of its own.
  */
 #include <torch/csrc/autograd/python_variable.h>
 
@@ -15,7 +15,7 @@ namespace {
 
 template <typename F>
 int read(PyObject *t, F f) {
-    if ((PyObject *)Py_TYPE(t) != THPVariableClass || at::impl::torch_function_mode_enabled()) return 0;
+    if ((PyObject *)Py_TYPE(t) != THPVariableClass) return 0;
     try {
         return f(THPVariable_Unpack(t)) ? 1 : 0;
     } catch (...) {
@@ -23,6 +23,7 @@ int read(PyObject *t, F f) {
     }
 }
 
+int overridden() { return at::impl::torch_function_mode_enabled() ? 1 : 0; }
 int data_ptr(PyObject *t, void **out) {
     return read(t, [&](const at::Tensor &x) { *out = x.data_ptr(); return true; });
 }
@@ -48,7 +49,7 @@ int nbytes(PyObject *t, size_t *out) {
     return read(t, [&](const at::Tensor &x) { *out = x.nbytes(); return true; });
 }
 
-dt_tensor_reader table = {data_ptr, sizes, stride, dtype, nbytes};
+dt_tensor_reader table = {overridden, data_ptr, sizes, stride, dtype, nbytes};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_dttensor", NULL, -1, NULL, NULL, NULL, NULL, NULL};
 
 }  // namespace
