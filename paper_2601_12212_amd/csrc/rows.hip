@@ -351,7 +351,7 @@ __device__ __forceinline__ void keep_hits(X x, Id id_of, float T, int *n, u64 *l
 }
 
 // A slot's maximum from the two quadruples of neighbouring lane maxima that each lane holds: the lanes L, L ^ 16, L ^ 32 and L ^ 48 exchange
-// until each has one of the four places of all their quadruples, 2,048 and more entries of the row apart (v_permlane32_swap and
+// until each has one of the four places of all their quadruples, 4,096 and more entries of the row apart (v_permlane32_swap and
 // v_permlane16_swap exchange halves and odd and even rows of sixteen lanes of two registers, so this deals the maxima out anew
 // and loses none).  With a quadruple's four in one slot, the best of a row whose best are neighbours fell into few slots, the bound among the rest
 // and too much was read again.  Calls of 51 rows of 128,256 bf16 entries, k = 10, with 256 / 512 / 1,024 neighbours raised by 20: 16.9 / 18.5 / 19.7 us so,
@@ -380,13 +380,15 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
     // the lane maxima do not depend on the row's metadata (two dependent global reads): ask for them
     // first, and wave 3 for the row's (max, sum) partials.  Rows that turn out to be dead have their
     // slots in the workspace all the same.
-    // A quarter of them to a wave, 8 S quadruples: lane l holds quadruples l and l + 64 of its wave's (so far as there are any).
+    // A quarter of them to a wave, every fourth of the 32 S quadruples: lane l holds those in places l and l + 64 of its wave's (so far as there
+    // are any).  So the waves share what is read again also where the best are in one part of the row: with a quarter of the row to a wave,
+    // 51 rows of 128,256 bf16 entries, k = 28, that fall by 12 along the row 13.0 us, 9.35 so, by ln(1 + id) 12.8 and 10.2, evenly spread ones 9.3 and 9.1.
     struct alignas(4 * sizeof(LM)) Quad { LM v[4]; };
     float it[8];
     if (S <= 16) {
         Quad q[2];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) q[i] = ((const Quad *)lm)[w * (8 * S) + min(64 * i + lane, 8 * S - 1)];
+        for (int i = 0; i < 2; ++i) q[i] = ((const Quad *)lm)[4 * min(64 * i + lane, 8 * S - 1) + w];
 #pragma unroll
         for (int j = 0; j < 8; ++j) it[j] = lane_max_value<BF16>(q[j >> 2].v[j & 3]);
     }
@@ -498,7 +500,7 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
             int *list = s_hot + w * SEL_WAVE_CAP;
             for (int at = incl - mine; hot; hot &= hot - 1) {
                 const int j = __builtin_ctz(hot);
-                list[at++] = 4 * (w * (8 * S) + 64 * (j >> 2) + lane) + (j & 3);
+                list[at++] = 4 * (4 * (64 * (j >> 2) + lane) + w) + (j & 3);
             }
             __builtin_amdgcn_wave_barrier();
             // A group to a lane, or the two neighbours of a load where there are more: k = 28 is some sixty groups to a wave.  (Each launch

@@ -163,6 +163,14 @@ def test_neighbours_among_the_best_do_not_slow_top_k_rows_down(n, V, k, M, times
     assert took[0] <= times * took[1], took
 
 
+def test_top_k_rows_whose_best_are_in_one_part_take_no_longer():
+    """1.03 times as long as rows whose best are anywhere; 1.4 with a quarter of the row to a wave."""
+    x = torch.randn((51, 128256), generator=torch.Generator("cuda").manual_seed(5), device="cuda") * 3
+    falling = x - torch.linspace(0, 12, 128256, device="cuda")
+    took = time_of_a_call(falling.bfloat16(), 28), time_of_a_call(x.bfloat16(), 28)
+    assert took[0] <= 1.2 * took[1], took
+
+
 # How many neighbours hold all of the best: fewer pairs of lanes than k (the first two bounds do not cut), as many as the list of
 # candidates has places and one more, and more.
 @pytest.mark.parametrize("M", [40, 127, 128, 129, 200, 255, 256, 257, 500, 3000])
