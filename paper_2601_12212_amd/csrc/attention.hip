@@ -1761,7 +1761,8 @@ size_t attn_workspace_bytes(int batch, int TT_cap, int Hq, int D, int n_cu) {
 
 // Over how many workgroups the keys of a (sequence, kv head, 32-row block) are dealt: nb blocks of 32 keys, `units` such row blocks.
 // At most one workgroup per compute unit (more, with 64-wide heads, which leave room for them, lose: 84 units of 34 blocks 9.9
-// us in 3 splits, 11.2 in 4), and 8.  Split, the four waves of a workgroup take ceil(nb / 4 KS) rounds of about 0.8 us, and each split costs the
+// us in 3 splits, 11.2 in 4), and 8.  Split, the four waves of a workgroup take ceil(nb / 4 KS) rounds of about 0.8 us (8B shape, 2,048 to 4,096
+// keys: 0.79 from the L2s and the last-level cache, 1.05 from memory), and each split costs the
 // merge 0.12 us and 1/200 more for every unit: whichever number of splits is cheapest by that.
 // Unsplit, eight waves take half as many rounds as four and need no merge, but a round of theirs is longer, 128-wide heads' by
 // far more: the line lies where the two sides met, us per layer, unsplit against the best split:
@@ -1788,19 +1789,25 @@ static int64_t max_blocks(const AttnArgs &a) { return ((int64_t)a.max_prefix_len
 // 5 + nb / 4 for every 256 units, with splits that much fewer blocks; the schedule, which shares each key block among four
 // row blocks and cuts what is long, starts at 22 to 30 us and takes half as long a block.  Where a kv head has two row blocks, the schedule
 // still halves what is read, and both wait for the memory sooner; where it has one, there is nothing to share, but the schedule has as
-// many tiles as there are units.  Both sides, small-batch | balanced, us per layer:
-//   up to 256 units, 8B shape, 4 sequences of 60 nodes (256): 4,000 keys 40 | 51, 8,192 73 | 71; 3 (192): 4,000 33 | 42, 8,192 69 | 56;
-//     in two splits (2 sequences): 8,192 37 | 41, 16,000 78 | 63; two row blocks (13B shape), 2 sequences (160): 2,500 40 | 42, 4,000 58 | 54, 3 (240):
-//     4,000 62 | 65, 8,192 119 | 117; one (32 heads, 30 nodes), 4 sequences (128): 150 9 | 15, 4,000 54 | 69, 8 (256): 150 11 | 19, 2,000 55 | 62;
-//   up to 512, 8B shape, 8 sequences (512): 150 keys 17 | 26, 400 22 | 28, 1,000 28 | 32, 1,700 40 | 41, 2,100 49 | 50, 2,500 56 | 49; 6 (384): 2,100
-//     39 | 45, 3,000 60 | 54, 8,192 133 | 86; two row blocks, 4 sequences (320): 150 16.5 | 17.5, 400 22 | 28, 700 28 | 27; one, 12 (384): 150 17 | 14, 400 29 | 30;
-//   beyond, 12 sequences of the 8B shape (768): 30 keys 17 | 22, 150 23.5 | 22.8, 400 30 | 41, 1,000 43 | 40, and 6 of 128 nodes 400 32 | 28: no line.
-// The keys are the longest that the caller allows for; a batch of differing lengths brings fewer, and so does most often a step that is
-// captured once.  The schedule gains less by short sequences than the small-batch kernel, whose work goes by units: at 280 units of 7
-// rows a node and lengths from a quarter of the longest up, 1,700 keys 24 | 37, 4,000 30 | 50, 8,192 54 | 49, at 392 39 | 43 and 85 | 56 with 4,000 and
-// 8,192, at 504 47 | 47 and 95 | 69.  So the lines above, of equal lengths, are for 128 tiles and more, and below them the schedule begins
-// where such a batch has caught up, and not at all up to 256 units, where the small-batch kernel loses little at the far end
-// (8 % with 4 sequences of 8,192 keys) and is two and a half times as fast at a thousand.
+// many tiles as there are units.
+// What the rule has is the longest length that the caller allows for, max_prefix_len: one call's own, or, in a step that is captured once,
+// the most that any replay will have.  Both sides, small-batch | balanced, us per layer, all sequences as long as that ("equal") or from a
+// quarter of it up ("ragged"):
+//   up to 256 units, fewer than 128 tiles: always the small-batch kernel.  With 300 / 1,000 / 2,000 real keys under a bound of 16,000, one sequence
+//     of the 8B shape (60 nodes) 11 | 22, 13 | 22, 14 | 24, four 11 | 32, 18 | 44, 24 | 41.  That is what a line on the bound would lose; what none loses, where the bound
+//     is met: 8B shape, 4 sequences (256) 4,000 keys 36 | 49, 8,192 69 | 68, 16,000 136 | 101, ragged 8,192 58 | 57, 16,000 102 | 71; 3 (192) 4,000 35 | 40, 8,192 56 | 52, 12,000
+//     94 | 68, 16,000 125 | 79, ragged 8,192 39 | 40, 12,000 82 | 59; 2 (128) 8,192 36 | 39, 16,000 65 | 60; 70B shape, 2 (240) 4,000 36 | 51, 8,192 63 | 58, 16,000 119 | 87;
+//     13B shape (two row blocks), 2 (160) 2,500 29 | 37, 4,000 59 | 54, 8,192 109 | 88, 3 (240) 8,192 121 | 118: up to a quarter at 8,192 keys, two fifths at 16,000;
+//   up to 256 units, 128 tiles and more (one or two row blocks to a kv head): the line lies where equal and ragged lengths lose alike.  32 heads of
+//     30 nodes, 4 sequences (128) 150 keys 10 | 15, 4,000 56 | 69, 8,192 99 | 114, 12,000 145 | 153; 8 (256) 6,400 145 | 165, 8,192 182 | 205, 12,000 273 | 283, ragged 6,400 100 | 87,
+//     8,192 137 | 135, 12,000 199 | 198; of 60 nodes (two row blocks), 4 (256) 4,800 73 | 76, 8,192 116 | 120, ragged 4,800 57 | 60, 6,400 84 | 81, 8,192 106 | 103;
+//   up to 512 units, 128 tiles and more: 8B shape, 8 sequences (512) 400 keys 23 | 30, 1,000 30 | 34, 2,000 43 | 41, 3,000 57 | 49, ragged 2,000 35 | 39, 4,000 50 | 50, 6,400 66 | 47; two row
+//     blocks, 40 heads, 4 (320) 700 29 | 26, 1,000 33 | 35, 2,500 75 | 63, ragged 1,000 22 | 26, 4,000 83 | 66, 32 heads, 6 (384) 700 28 | 30, 2,500 77 | 67, ragged 2,500 30 | 34; one, 12
+//     sequences of 32 heads (384) 150 17 | 14, 400 29 | 30;
+//   up to 512 units, fewer than 128 tiles: where ragged lengths meet.  8B shape, 6 (384) ragged 4,000 41 | 45, 6,400 59 | 59, 8,192 70 | 61; equal ones are past the
+//     meeting before the line, 3,000 52 | 48, 4,000 63 | 57, 6,400 108 | 79;
+//   beyond 512: no line holds.  12 sequences of the 8B shape (768) 30 keys 18 | 24, 150 25 | 24, 400 32 | 43, 700 38 | 35, 1,000 43 | 36, ragged 700 35 | 40, 1,000 38 | 36, 16 (1,024) 30 23 | 25,
+//     150 32 | 26, 400 41 | 30; 6 of 128 nodes (768) 150 26 | 33, 400 33 | 30, 700 38 | 40.
 static bool wave_ahead(int64_t units, int64_t tiles, int mblocks, int64_t nb) {
     if (units <= 256) return tiles < 128 || nb <= (mblocks == 2 ? 150 : 200) * wave_splits(128, units, nb);
     if (units > 512 || mblocks == 1) return false;

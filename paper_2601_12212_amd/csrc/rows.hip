@@ -1005,6 +1005,9 @@ static int held_threads(int V) { return V <= 256 * 16 ? 256 : V <= 512 * 16 ? 51
 // While every row of 1,024 threads leaves another compute unit idle, its exponentials are summed there, by a workgroup of its own that
 // reads the row as well: 16 waves sum 32,000 exponentials in 0.6 us (50 rows of 32,000 bf16 entries 6.7 -> 6.1 us, 120 rows 7.1 -> 6.2,
 // 16,000 entries 5.2 -> 4.95 and 5.4 -> 5.05; 50 rows of 8,000, 512 threads, 4.65 -> 4.80).
+// With another stream busy the other half of the chip is not idle, and neither side gains: the same calls beside a bf16 product of 4,096
+// cubed, without | with, 20.2 | 19.7, 20.4 | 19.7, 19.0 | 18.8, 18.9 | 18.7 us, the product 114.3 | 115.0, 112.9 | 113.8, 113.6 | 113.2, 111.5 | 110.9; beside
+// an elementwise pass over 512 MB 15.4 | 15.2, 16.2 | 15.9, 13.0 | 13.7, 14.1 | 14.4, the pass 87.1 | 87.4, 87.3 | 88.1, 86.9 | 87.0, 87.2 | 87.7.
 #define APART_ROWS 128
 #define SMALL_ROWS 512  // most rows of a launch that leaves a SIMD a wave or two of 256-thread workgroups
 static hipError_t launch_held(const RowArgs &a_in, int64_t n_rows, float *top_val, int32_t *top_id, float *lse, int out_stride,
