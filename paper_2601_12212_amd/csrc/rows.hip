@@ -212,7 +212,7 @@ __global__ __launch_bounds__(256) void row_stream_kernel(RowArgs a, int S) {
     const int c0 = blockIdx.x * CPW;
     const int lane = lane_id(), w = threadIdx.x >> 6;
     const int base = c0 * (256 * E) + w * (64 * E) + lane * 8;
-    if (g >= a.n_rows) return;
+    if (g >= a.n_rows || c0 >= S) return;
     // early: the row's elements are on their way while the (dependent, scalar) reads of its metadata are waited for
     RawChunk<NL, BF16> raw[CPW > 1 ? 2 : 1];
     if (a.early_load) chunk_request<NL, BF16, true>(a, g, base, raw[0]);
@@ -222,7 +222,7 @@ __global__ __launch_bounds__(256) void row_stream_kernel(RowArgs a, int S) {
     for (int i = 0; i < CPW; ++i) {
         const int c = c0 + i;
         if (CPW > 1 && c >= S) return;
-        if (i + 1 < CPW) chunk_request<NL, BF16, true>(a, g, base + (i + 1) * (256 * E), raw[(i + 1) & 1]);  // past the row: its last elements again
+        if (i + 1 < CPW && c + 1 < S) chunk_request<NL, BF16, true>(a, g, base + (i + 1) * (256 * E), raw[(i + 1) & 1]);
         float x[E];
         chunk_finish<NL, BF16, true>(a, g, base + i * (256 * E), (c + 1) * (256 * E), raw[i & 1], x);
         float mx = x[0];
@@ -956,11 +956,18 @@ static void by_mode_and_type(const RowArgs &a, F f) {
 // that a policy may set on the device is mostly dead rows (two sequences, 450 rows of 128,256 for the widest action:
 // 21.8 us when all were read, 8-13 us when a row's liveness is looked up first).
 static const int64_t EARLY_LOAD_WGS = 2048;
-// Launches of more chunks than this take two to a workgroup: the trip in front of the loads (whose row is it, is it live) is made half
-// as often, and the second chunk's elements are on their way under the exponentials of the first.  1.55 GB of draft rows (96,700 chunks)
-// 291 -> 266 us, 667 MB (41,600) 125 -> 116, 357 MB (22,300) 65 -> 63.5; 156 MB (9,700) 30.1 against 30.6, 87 MB (5,400) 18.4 against
-// 19.8; four to a workgroup 267, - , - , 32.0, 21.4.
+// Launches of more chunks than this, of rows that are looked up, take two to a workgroup: the trip in front of the loads (whose row is it, is it
+// live) is made half as often, and the second chunk's elements are on their way under the exponentials of the first.  Draft rows,
+// one | two to a workgroup, traced: of 128,256 entries, 17,900 chunks 46.7 | 48.0 us, 25,800 70 | 69, 33,500 94 | 88, 60,600 174 | 163; of 128,257 57.5 | 57.5, 82 | 82, 111 | 106, 204 | 187; of
+// 90,001, 17,700 chunks 57 | 59, 24,200 80 | 80, 42,000 141 | 137; of 50,257, 18,200 38 | 34, 24,400 50 | 46, 61,300 125 | 111.  Below: 156 MB (9,700 chunks) 30.1 | 30.6, 87 MB (5,400)
+// 18.4 | 19.8.  Rows that need no look-up gain nothing (calls of 17,000 chunks: 128,256 53.2 | 54.9 us, 119,331 53.8 | 60.6, 65,537 53.4 | 57.8; of 60,000 172 | 171, 190 | 199,
+// 185 | 190).
 static const int64_t PAIR_CHUNKS = 16384;
+// Workgroups go to the eight XCDs in turn.  With an even number to a row each XCD reads the same columns of every row, with eight or sixteen one
+// or two chunks of them; an odd number deals every chunk to every XCD.  Where rows begin at any two-byte address that is up to a fifth (calls of 17,000 /
+// 60,000 chunks of 128,257 entries 68.3 | 221 us with sixteen, 53.9 | 192 with seventeen, the last of which leaves at once; 41 sequences' draft rows of 119,331,
+// eight or nine workgroups of two chunks, 81.8 and 67.9), in rows of 128,256 2 to 4 %.  Why unaligned rows mind most has not been found.
+static int odd(int64_t wgs) { return (int)wgs | 1; }
 
 // top-k rows, pass 1: lane maxima and (max, sum) partials
 static hipError_t launch_stream(const RowArgs &a_in, int64_t n_rows, int nl, hipStream_t st) {
@@ -976,10 +983,12 @@ static hipError_t launch_stream(const RowArgs &a_in, int64_t n_rows, int nl, hip
         auto launch = [&](auto nl_c) {
             constexpr int NL = decltype(nl_c)::value;
             auto with = [&](auto kernel, int cpw) {
-                launch_kernel(kid, st, kernel, rows_grid((int)((S + cpw - 1) / cpw), n_rows), dim3(256), 0, a, (int)S);
+                const int64_t wgs = (S + cpw - 1) / cpw;
+                launch_kernel(kid, st, kernel, rows_grid(a.early_load ? (int)wgs : odd(wgs), n_rows), dim3(256), 0, a, (int)S);
             };
-            if (n_rows * S > PAIR_CHUNKS) with(row_stream_kernel<MODE, NL, BF, 2>, 2);
-            else with(row_stream_kernel<MODE, NL, BF, 1>, 1);
+            if constexpr (MODE != ROWS_UNIFORM)
+                if (n_rows * S > PAIR_CHUNKS) return with(row_stream_kernel<MODE, NL, BF, 2>, 2);
+            with(row_stream_kernel<MODE, NL, BF, 1>, 1);
         };
         if (nl == 4) launch(integral_constant<int, 4>());
         else if (nl == 2) launch(integral_constant<int, 2>());

@@ -37,9 +37,43 @@ def test_topk_rows_of_many_rows(V, n):
 
 @pytest.mark.parametrize("V,n,bf16", [(32769, 1821, True), (65537, 1821, True), (131072, 1025, True), (131081, 1000, True),
                                       (16385, 1821, False), (65536, 1025, False)])
-def test_topk_rows_of_launches_that_take_two_chunks_to_a_workgroup(V, n, bf16):
+def test_topk_rows_of_launches_of_many_chunks(V, n, bf16):
     """More than 16,384 chunks: odd and even numbers of them to a row, a last one of one element, nine elements and whole."""
     check_repeated_rows(V, n, bf16)
+
+
+@pytest.mark.parametrize("V,bf16", [(32769, True), (61441, True), (65537, True), (119331, True), (131072, True), (131081, True),
+                                    (16385, False), (65536, False)])
+def test_draft_rows_of_launches_that_take_two_chunks_to_a_workgroup(V, bf16):
+    """More than 16,384 chunks of rows that are looked up: 9, 16, 9, 15, 16, 17, 9 and 16 to a row, a last one of one element, nine
+    elements, part of one and whole; a sequence in the middle without live rows."""
+    from paper_2601_12212_amd.step import Step
+    TT, d, k = 70, 4, 16
+    R = 1 + (d - 1) * k
+    nl = next(n for n in (1, 2, 4) if V <= 16 * 2048 * n or n == 4)
+    B = 16384 // (R * -(-V // (2048 * nl))) + 2
+    for seed in range(20):
+        rows = (np.random.default_rng(seed).standard_normal((R, V)) * 3).astype(np.float32)
+        rows[1, V - 1] = rows[2, 0] = 20.0
+        if bf16:
+            rows = dt_synth.f32_to_bf16_bits(rows)
+        want = ref.build_tree(rows, TT, d, k, 3)
+        if want["min_margin"] >= TREE_MARGIN:
+            break
+    assert want["min_margin"] >= TREE_MARGIN
+    params = [(TT, d, k)] * B
+    params[B // 2] = (1, d, k)
+    st = Step(params, [1] * B, 1, 1, 64, V, dtype=torch.bfloat16 if bf16 else torch.float32)
+    for b in range(B):
+        st.set_root_token(b, 3)
+        if b != B // 2:
+            st.set_draft(b, rows)
+    st.build_tree()
+    torch.cuda.synchronize()
+    for b in range(B):
+        if b != B // 2:
+            assert_tree_equal(st.tree(b), want, "sequence %d" % b)
+    assert st.tree(B // 2)["n_nodes"] == 1
 
 
 # the most rows whose exponentials workgroups of their own sum, and one more; the most 256-thread rows whose waves all find
