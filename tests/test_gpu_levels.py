@@ -112,6 +112,18 @@ def test_level_by_level_bf16_wide_levels():
     drive([(96, 4, 16), (64, 3, 32), (40, 5, 6)], [11, 12, 13], V=4099, bf16=True, seed=2)
 
 
+# vocabularies of both row paths: held by 1,024 threads with the log-sum-exps apart, two passes of one chunk to a workgroup;
+# sequences that end before the others leave rows of nodes that do not exist
+@pytest.mark.parametrize("V,bf16", [(20000, True), (50001, True), (50001, False), (128256, True)])
+def test_level_by_level_of_large_vocabularies(V, bf16):
+    drive([(40, 3, 12), (1, 2, 2), (30, 4, 5), (9, 1, 4), (25, 2, 12), (33, 5, 3)], [5, 0, 9, 1000, 77, 3], V=V, bf16=bf16, seed=1)
+
+
+def test_level_by_level_of_launches_that_take_two_chunks_to_a_workgroup():
+    # 33 sequences of 32 rows of 16 chunks, 16,896 in all, most of them of nodes that do not exist
+    drive([(30, 3, 4)] * 7 + [(70, 3, 32)] + [(5, 2, 2)] * 25, list(range(33)), V=61441, bf16=True, seed=1)
+
+
 def test_the_level_loop_can_be_captured_and_replayed():
     # The d-level loop with the finish call as one HIP graph (the draft model's passes would be nodes in
     # between; here each level's logits sit in their own buffer).  Replayed several times with the outputs
