@@ -111,7 +111,10 @@ inline ArgmaxScratch argmax_scratch(void *ws, int64_t rows, int S) {
     r.bytes = kb + align_up((size_t)rows * S * 8);
     return r;
 }
-struct TopkScratch {  // top-k rows: [rows, S*128] maxima of pairs of lanes (room for [rows, S*256] floats), [rows, S*4] (max, sum) pairs
+// top-k rows: [rows, S*128] maxima of pairs of lanes, [rows, S*4] (max, sum) pairs.  The room for maxima stays [rows, S*256] floats, one
+// for every lane as the stream once left them, two to four times what is written: the sizes that a caller's workspace must
+// have, and the rows that the static scratch takes, are part of the interface, and unwritten room costs no time.
+struct TopkScratch {
     float *lane_max;
     float2 *ms;
     size_t bytes;
