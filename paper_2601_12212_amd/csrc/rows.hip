@@ -334,7 +334,12 @@ __device__ __forceinline__ void keep_hits(X x, Id id_of, float T, int *n, u64 *l
         if (__builtin_amdgcn_ballot_w64(c > HITS_ONE_BY_ONE)) {  // uniform
 #pragma unroll
             for (int e = 0; e < N; ++e) {
-                if ((hits >> e & 1u) && slot < SEL_CAP) list[slot] = make_key(x(e), (u32)id_of(e));
+                if ((hits >> e & 1u) && slot < SEL_CAP) {
+                    float v = x(e);
+                    int id = id_of(e);
+                    asm("" : "+v"(v), "+v"(id));  // here, for the hits: the compiler would work out every element's key in front of the branch
+                    list[slot] = make_key(v, (u32)id);
+                }
                 slot += hits >> e & 1;
             }
             return;
