@@ -212,7 +212,8 @@ __global__ __launch_bounds__(256) void row_stream_kernel(RowArgs a, int S) {
     const int c0 = blockIdx.x * CPW;
     const int lane = lane_id(), w = threadIdx.x >> 6;
     const int base = c0 * (256 * E) + w * (64 * E) + lane * 8;
-    if (g >= a.n_rows || c0 >= S) return;
+    // (S stands at the end of the arguments: a comparison with it here cost launches of short chunks 1 %)
+    if (g >= a.n_rows || c0 * (256 * E) >= a.V) return;
     // early: the row's elements are on their way while the (dependent, scalar) reads of its metadata are waited for
     RawChunk<NL, BF16> raw[CPW > 1 ? 2 : 1];
     if (a.early_load) chunk_request<NL, BF16, true>(a, g, base, raw[0]);
