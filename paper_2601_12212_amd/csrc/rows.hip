@@ -969,11 +969,17 @@ static const int64_t EARLY_LOAD_WGS = 2048;
 // 18.4 | 19.8.  Rows that need no look-up gain nothing (calls of 17,000 chunks: 128,256 53.2 | 54.9 us, 119,331 53.8 | 60.6, 65,537 53.4 | 57.8; of 60,000 172 | 171, 190 | 199,
 // 185 | 190).
 static const int64_t PAIR_CHUNKS = 16384;
-// Workgroups go to the eight XCDs in turn.  With an even number to a row each XCD reads the same columns of every row, with eight or sixteen one
-// or two chunks of them; an odd number deals every chunk to every XCD.  Where rows begin at any two-byte address that is up to a fifth (calls of 17,000 /
-// 60,000 chunks of 128,257 entries 68.3 | 221 us with sixteen, 53.9 | 192 with seventeen, the last of which leaves at once; 41 sequences' draft rows of 119,331,
-// eight or nine workgroups of two chunks, 81.8 and 67.9), in rows of 128,256 2 to 4 %.  Why unaligned rows mind most has not been found.
-static int odd(int64_t wgs) { return (int)wgs | 1; }
+// How many workgroups a row has in launches bound by bandwidth.  They go to the eight XCDs in turn: with sixteen, or eight of two chunks, a
+// row's last, shorter one falls to the same XCD in every row, and rows that begin at odd two-byte addresses are read a fifth slower (why
+// has not been found; dealing each row's chunks out from another place on does not help).  One more, which leaves at once, deals every
+// chunk to every XCD.  Sixteen | seventeen, calls of 16,000 chunks of 128,257 bf16 entries 60.3 | 49.7 us, of 65,001 31.9 | 27.9, of 128,256 48.9 | 47.7, of 64,960 27.7 | 26.0;
+// eight | nine, 32 sequences' steps of 125,001 331 | 307, of 119,331 303 | 277; six | seven, of two chunks, of 93,001 245 | 238.  It costs where the
+// last one is whole (65,536 27.7 | 28.1, 98,304 in twelve 36.6 | 37.6), and with ten, twelve or fourteen of one chunk gains nothing: 93,001 73.1 | 74.0, 109,001 80.8 | 85.9.
+static int workgroups_per_row(const RowArgs &a, int64_t S, int nl, int cpw) {
+    const int wgs = (int)((S + cpw - 1) / cpw);
+    const bool last_is_whole = a.V % (256 * 8 * nl * cpw) == 0 && a.row_stride % 2 == 0;
+    return (wgs % 8 == 0 || (cpw == 2 && wgs % 2 == 0)) && !last_is_whole ? wgs + 1 : wgs;
+}
 
 // top-k rows, pass 1: lane maxima and (max, sum) partials
 static hipError_t launch_stream(const RowArgs &a_in, int64_t n_rows, int nl, hipStream_t st) {
@@ -989,8 +995,8 @@ static hipError_t launch_stream(const RowArgs &a_in, int64_t n_rows, int nl, hip
         auto launch = [&](auto nl_c) {
             constexpr int NL = decltype(nl_c)::value;
             auto with = [&](auto kernel, int cpw) {
-                const int64_t wgs = (S + cpw - 1) / cpw;
-                launch_kernel(kid, st, kernel, rows_grid(a.early_load ? (int)wgs : odd(wgs), n_rows), dim3(256), 0, a, (int)S);
+                const int wgs = a.early_load ? (int)S : workgroups_per_row(a, S, nl, cpw);
+                launch_kernel(kid, st, kernel, rows_grid(wgs, n_rows), dim3(256), 0, a, (int)S);
             };
             if constexpr (MODE != ROWS_UNIFORM)
                 if (n_rows * S > PAIR_CHUNKS) return with(row_stream_kernel<MODE, NL, BF, 2>, 2);
