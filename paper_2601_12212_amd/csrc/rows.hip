@@ -962,12 +962,13 @@ static void by_mode_and_type(const RowArgs &a, F f) {
 // that a policy may set on the device is mostly dead rows (two sequences, 450 rows of 128,256 for the widest action:
 // 21.8 us when all were read, 8-13 us when a row's liveness is looked up first).
 static const int64_t EARLY_LOAD_WGS = 2048;
-// Launches of more chunks than this, of rows that are looked up, take two to a workgroup: the trip in front of the loads (whose row is it, is it
-// live) is made half as often, and the second chunk's elements are on their way under the exponentials of the first.  Draft rows,
-// one | two to a workgroup, traced: of 128,256 entries, 17,900 chunks 46.7 | 48.0 us, 25,800 70 | 69, 33,500 94 | 88, 60,600 174 | 163; of 128,257 57.5 | 57.5, 82 | 82, 111 | 106, 204 | 187; of
-// 90,001, 17,700 chunks 57 | 59, 24,200 80 | 80, 42,000 141 | 137; of 50,257, 18,200 38 | 34, 24,400 50 | 46, 61,300 125 | 111.  Below: 156 MB (9,700 chunks) 30.1 | 30.6, 87 MB (5,400)
-// 18.4 | 19.8.  Rows that need no look-up gain nothing (calls of 17,000 chunks: 128,256 53.2 | 54.9 us, 119,331 53.8 | 60.6, 65,537 53.4 | 57.8; of 60,000 172 | 171, 190 | 199,
-// 185 | 190).
+// Launches of more chunks than this take two to a workgroup if the rows are looked up or the chunks are short: the trip in front of the loads
+// (whose row is it, is it live) is made half as often, and the second chunk's elements are on their way under the exponentials of the first.
+// Draft rows, one | two to a workgroup, traced: of 128,256 entries, 17,900 chunks 46.7 | 48.0 us, 25,800 70 | 69, 33,500 94 | 88, 60,600 174 | 163; of 128,257 57.5 | 57.5,
+// 82 | 82, 111 | 106, 204 | 187; of 90,001, 17,700 chunks 57 | 59, 24,200 80 | 80, 42,000 141 | 137; of 50,257, 18,200 38 | 34, 24,400 50 | 46, 61,300 125 | 111.  Below: 156 MB (9,700
+// chunks) 30.1 | 30.6, 87 MB (5,400) 18.4 | 19.8.  Rows that need no look-up gain only where a workgroup's life is short, chunks of 2,048: calls of 1,900 rows of 18,944
+// 29.8 | 24.6 us, of 22,976 33.9 | 26.5, of 30,976 42.1 | 32.0, of 31,001 42.3 | 34.7; of 40,001 (chunks of 4,096) 36.9 | 39.0, of 128,256 (8,192), 17,000 chunks 53.2 | 54.9, of 119,331
+// 53.8 | 60.6.
 static const int64_t PAIR_CHUNKS = 16384;
 // How many workgroups a row has in launches bound by bandwidth.  They go to the eight XCDs in turn: with sixteen, or eight of two chunks, a
 // row's last, shorter one falls to the same XCD in every row, and rows that begin at odd two-byte addresses are read a fifth slower (why
@@ -998,7 +999,7 @@ static hipError_t launch_stream(const RowArgs &a_in, int64_t n_rows, int nl, hip
                 const int wgs = a.early_load ? (int)S : workgroups_per_row(a, S, nl, cpw);
                 launch_kernel(kid, st, kernel, rows_grid(wgs, n_rows), dim3(256), 0, a, (int)S);
             };
-            if constexpr (MODE != ROWS_UNIFORM)
+            if constexpr (MODE != ROWS_UNIFORM || NL == 1)
                 if (n_rows * S > PAIR_CHUNKS) return with(row_stream_kernel<MODE, NL, BF, 2>, 2);
             with(row_stream_kernel<MODE, NL, BF, 1>, 1);
         };

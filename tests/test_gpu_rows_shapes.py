@@ -36,9 +36,11 @@ def test_topk_rows_of_many_rows(V, n):
 
 
 @pytest.mark.parametrize("V,n,bf16", [(32769, 1821, True), (65537, 1821, True), (131072, 1025, True), (131081, 1000, True),
-                                      (16385, 1821, False), (65536, 1025, False)])
+                                      (16385, 1821, False), (65536, 1025, False), (16385, 1821, True), (20000, 1640, True),
+                                      (31001, 1025, True), (32768, 1025, True), (65001, 129, True)])
 def test_topk_rows_of_launches_of_many_chunks(V, n, bf16):
-    """More than 16,384 chunks: odd and even numbers of them to a row, a last one of one element, nine elements and whole."""
+    """More than 16,384 chunks: odd and even numbers of them to a row, a last one of one element, nine elements and whole, one
+    and two to a workgroup.  2,064 chunks: a workgroup more to a row than there are chunks."""
     check_repeated_rows(V, n, bf16)
 
 
@@ -195,6 +197,13 @@ def test_neighbours_among_the_best_do_not_slow_top_k_rows_down(n, V, k, M, times
     x[:, 1000:1000 + M] += 20
     took = time_of_a_call(x.bfloat16(), k), time_of_a_call(plain, k)
     assert took[0] <= times * took[1], took
+
+
+def test_large_calls_of_short_chunks_are_not_one_chunk_to_a_workgroup():
+    """1,990 rows 1.2 times as long as 1,100, which take one; 1.55 if they did so too."""
+    x = torch.randn((1990, 26944), generator=torch.Generator("cuda").manual_seed(5), device="cuda").bfloat16()
+    took = time_of_a_call(x, 12), time_of_a_call(x[:1100], 12)
+    assert took[0] <= 1.4 * took[1], took
 
 
 def test_top_k_rows_whose_best_are_in_one_part_take_no_longer():
