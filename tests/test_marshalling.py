@@ -1,5 +1,6 @@
 """The native argument marshalling reads a torch.Tensor itself and anything else through its methods: both ways have to see the
 same pointers, sizes, strides, types and byte counts, and to refuse the same objects.  Every call here is refused before a launch."""
+import ctypes
 import subprocess
 import sys
 
@@ -134,3 +135,73 @@ def test_another_torch_is_named_and_its_tensors_read_through_their_methods(call)
 def test_what_is_not_a_reader_is_refused(call):
     with pytest.raises(ValueError):
         call.set_reader(7)
+
+
+PyObject, Int, Long, LL = ctypes.py_object, ctypes.c_int, ctypes.c_long, ctypes.c_longlong
+READER = [("overridden", ctypes.PYFUNCTYPE(Int)),
+          ("data_ptr", ctypes.PYFUNCTYPE(Int, PyObject, ctypes.POINTER(ctypes.c_void_p))),
+          ("sizes", ctypes.PYFUNCTYPE(Int, PyObject, Int, Int, ctypes.POINTER(LL))),
+          ("stride", ctypes.PYFUNCTYPE(Int, PyObject, Long, ctypes.POINTER(LL))),
+          ("dtype", ctypes.PYFUNCTYPE(Int, PyObject, ctypes.POINTER(Int))),
+          ("nbytes", ctypes.PYFUNCTYPE(Int, PyObject, ctypes.POINTER(ctypes.c_size_t)))]
+
+
+class Table(ctypes.Structure):
+    _fields_ = READER
+
+
+@pytest.fixture
+def table():
+    get = ctypes.PYFUNCTYPE(ctypes.c_void_p, PyObject, ctypes.c_char_p)(("PyCapsule_GetPointer", ctypes.pythonapi))
+    capsule = binding._tensor_reader(torch.__version__)
+    t = Table.from_address(get(capsule, b"paper_2601_12212_amd.tensor_reader"))
+    t.capsule = capsule
+    return t
+
+
+base = torch.zeros(6, 8, 10)
+TENSORS = {
+    "whole": base,
+    "a view with an offset": base[2:, 3:5],
+    "transposed": base.permute(2, 0, 1),
+    "every third column": base[..., ::3],
+    "expanded": base[:1].expand(5, 8, 10),
+    "an empty one": base[:, :0],
+    "no dimension": torch.zeros(()),
+    "one dimension": torch.zeros(7, dtype=torch.bfloat16)[1:],
+    "bfloat16, strided": torch.zeros(4, 64, dtype=torch.bfloat16).as_strided((3, 16), (20, 2), 5),
+    "with a gradient": torch.zeros(3, 4, requires_grad=True),
+    "integers": torch.zeros(3, 4, dtype=torch.int32),
+    "half precision": torch.zeros(3, 4, dtype=torch.float16),
+    "more than 2^31 bytes": torch.zeros(1).expand(3, 1 << 30),
+}
+
+
+@pytest.mark.parametrize("name", TENSORS)
+def test_the_reader_says_what_the_methods_say(table, name):
+    x = TENSORS[name]
+    p, v, n, bf16 = ctypes.c_void_p(), LL(), ctypes.c_size_t(), Int(-1)
+    assert table.overridden() == 0
+    assert table.data_ptr(x, p) == 1 and (p.value or 0) == x.data_ptr()
+    assert table.nbytes(x, n) == 1 and n.value == x.nbytes
+    for dim in range(-x.dim(), x.dim()):
+        assert table.stride(x, dim, v) == 1 and v.value == x.stride(dim)
+    assert table.stride(x, x.dim(), v) == 0                   # the method says what is wrong
+    for want in range(x.dim() + 2):
+        out = (LL * 8)(*[-7] * 8)
+        assert table.sizes(x, want, 1, out) == (want == x.dim())
+        assert list(out) == (list(x.shape) if want == x.dim() else []) + [-7] * (8 - x.dim() * (want == x.dim()))
+        assert table.sizes(x, want, 0, out) == (want <= x.dim())
+        if want <= x.dim():
+            assert list(out)[:want] == list(x.shape)[:want]
+    assert table.dtype(x, bf16) == (x.dtype in (torch.float32, torch.bfloat16))
+    if x.dtype in (torch.float32, torch.bfloat16):
+        assert bf16.value == (x.dtype == torch.bfloat16)
+
+
+@pytest.mark.parametrize("x", [7, None, Duck(base), base.as_subclass(Derived), torch.nn.Parameter(torch.zeros(3))],
+                         ids=["int", "None", "duck", "derived", "parameter"])
+def test_the_reader_leaves_other_objects_to_their_methods(table, x):
+    p, v, n, bf16 = ctypes.c_void_p(), LL(), ctypes.c_size_t(), Int()
+    assert table.data_ptr(x, p) == table.nbytes(x, n) == table.stride(x, 0, v) == table.dtype(x, bf16) == 0
+    assert table.sizes(x, 1, 0, v) == 0
