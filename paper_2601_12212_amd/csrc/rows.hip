@@ -969,7 +969,7 @@ static const int64_t EARLY_LOAD_WGS = 2048;
 // Draft rows, one | two to a workgroup, traced: of 128,256 entries, 17,900 chunks 46.7 | 48.0 us, 25,800 70 | 69, 33,500 94 | 88, 60,600 174 | 163; of 128,257 57.5 | 57.5,
 // 82 | 82, 111 | 106, 204 | 187; of 90,001, 17,700 chunks 57 | 59, 24,200 80 | 80, 42,000 141 | 137; of 50,257, 18,200 38 | 34, 24,400 50 | 46, 61,300 125 | 111.  Below: 156 MB (9,700
 // chunks) 30.1 | 30.6, 87 MB (5,400) 18.4 | 19.8.  Rows that need no look-up gain only where a workgroup's life is short, chunks of 2,048: calls of 1,900 rows of 18,944
-// 29.8 | 24.6 us, of 22,976 33.9 | 26.5, of 30,976 42.1 | 32.0, of 31,001 42.3 | 34.7; of 40,001 (chunks of 4,096) 36.9 | 39.0, of 128,256 (8,192), 17,000 chunks 53.2 | 54.9, of 119,331
+// 29.9 | 24.7 us, of 22,976 32.8 | 26.5, of 30,976 41.0 | 31.9, of 31,001 41.8 | 33.8; of 40,001 (chunks of 4,096) 36.9 | 39.0, of 128,256 (8,192), 17,000 chunks 53.2 | 54.9, of 119,331
 // 53.8 | 60.6.
 static const int64_t PAIR_CHUNKS = 16384;
 // How many workgroups a row has in launches bound by bandwidth.  They go to the eight XCDs in turn: with sixteen, or eight of two chunks, a
