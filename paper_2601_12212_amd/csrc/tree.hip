@@ -15,7 +15,7 @@
 //    (four 8-bit digits, one histogram and one barrier per digit, every wave scanning the 256 bins by itself).
 // Eight waves that shared every level (pairs counted for k <= 11, score buckets beyond), two to five barriers per level, took
 // 11.0 us for (TT, d, k) = (60, 6, 10), 10.9 for (64, 7, 8), 20 for (96, 8, 12) and 30 for the slowest of a batch with k up to
-// 32; this takes 7.5, 7.6, 12.7 and 22.5 (averages of kernel traces).  What a lane, a thread or a list holds is sized in steps by k and by the pool, since each
+// 32; this takes 7.8, 7.8, 12.6 and 21.2 (averages of kernel traces; other machines 0.1 to 0.5 off).  What a lane, a thread or a list holds is sized in steps by k and by the pool, since each
 // element more is instructions more in the chain (figures beside the steps: launches replayed one behind the other).
 #include <stddef.h>
 
