@@ -44,6 +44,12 @@ def test_topk_rows_of_launches_of_many_chunks(V, n, bf16):
     check_repeated_rows(V, n, bf16)
 
 
+@pytest.mark.parametrize("V,n,gap", [(65536, 129, 1), (65536, 129, 2), (131072, 129, 3), (32768, 1025, 1)])
+def test_topk_rows_of_whole_chunks_at_odd_addresses(V, n, gap):
+    """Sixteen whole chunks to a row: a workgroup more where the rows' stride is odd, none where it is even."""
+    check_repeated_rows(V, n, True, gap)
+
+
 @pytest.mark.parametrize("V,bf16", [(32769, True), (61441, True), (65537, True), (119331, True), (131072, True), (131081, True),
                                     (16385, False), (65536, False)])
 def test_draft_rows_of_launches_that_take_two_chunks_to_a_workgroup(V, bf16):
@@ -86,7 +92,7 @@ def test_topk_rows_that_a_workgroup_holds(V, n, bf16):
     check_repeated_rows(V, n, bf16)
 
 
-def check_repeated_rows(V, n, bf16):
+def check_repeated_rows(V, n, bf16, gap=0):
     import paper_2601_12212_amd as dt
     k, R = min(20, V), 7
     x = (np.random.default_rng(V + n).standard_normal((R, V)) * 3).astype(np.float32)
@@ -98,7 +104,7 @@ def check_repeated_rows(V, n, bf16):
     rows = dt_synth.f32_to_bf16_bits(x) if bf16 else x
     wval, widx, wlse = ref.topk_rows(rows, k)
     which = torch.arange(n, device="cuda") % R
-    logits = dev_logits(rows)[which].contiguous()
+    logits = torch.nn.functional.pad(dev_logits(rows)[which], (0, gap), value=1e9)[:, :V]   # row stride V + gap
     val = torch.empty((n, k), dtype=torch.float32, device="cuda")
     idx = torch.empty((n, k), dtype=torch.int32, device="cuda")
     lse = torch.empty(n, dtype=torch.float32, device="cuda")
