@@ -301,17 +301,28 @@ __device__ __forceinline__ void merge_shared(SharedMerge s) {
         for (int i = tid; i < s.pt.parts; i += 256) put_agent(s.marks + part_at(s.pt, i), 0);
 }
 
+// The words of a sequence, the same in all lanes.
+struct SeqWords {
+    int N, L;
+    u64 kpre, vpre;  // of the caches, as addresses
+};
+// x / G for x G < 2^32: the upper half of x * (2^32 / G + 1)
+struct GroupDiv {
+    int G;
+    u32 magic;
+    __device__ __forceinline__ int div(int x) const { return G == 1 ? x : (int)__umulhi((u32)x, magic); }
+};
+static GroupDiv group_div(int G) { return {G, (u32)(((u64)1 << 32) / G + 1)}; }
+
 // Rows m0 .. m0+127 of (sequence b, kv head h) against key blocks kb0 .. kb1-1 of that sequence.
 // Called by all 256 threads of the workgroup; ends behind a barrier, so calls can follow each other.
 template <int D>
-__device__ __forceinline__ void tile_segment(const AttnArgs &a, unsigned char *s_dyn, int h, int b, int m0, int rot, int kb0,
-                                             int kb1, const TileParts &pt, int slots, bool stay) {
+__device__ __forceinline__ void tile_segment(const AttnArgs &a, const GroupDiv &gd, const SeqWords &sq, unsigned char *s_dyn, int h,
+                                             int b, int m0, int rot, int kb0, int kb1, const TileParts &pt, int slots, bool stay) {
     static_assert(D == 128, "head dim");
     constexpr int KSTEPS = D / 16, DBLK = D / 32;
-    const int G = a.Hq / a.Hkv;
-    const int N = min(max(a.n_nodes[b], 1), a.TT_cap);
+    const int G = gd.G, N = sq.N, L = sq.L;
     const int M = N * G;
-    const int L = max(a.prefix_len[b], 0);
     const int Tk = L + N;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -323,15 +334,9 @@ __device__ __forceinline__ void tile_segment(const AttnArgs &a, unsigned char *s
     const bool active = m0 + 32 * rb < M;
     const int mq = m0 + 32 * rb + col;
     const bool qvalid = mq < M;
-    const int node = qvalid ? mq / G : 0;
-    const int hq = h * G + (qvalid ? mq % G : 0);
+    const int mr = qvalid ? mq : 0;  // rows past M read node 0: unused
+    const int node = gd.div(mr), hq = h * G + (mr - node * G);
 
-    bf16x8 qreg[KSTEPS];
-    {
-        const __bf16 *qp = (const __bf16 *)a.q + (((int64_t)b * a.TT_cap + node) * a.Hq + hq) * D;
-#pragma unroll
-        for (int s = 0; s < KSTEPS; ++s) qreg[s] = *(const bf16x8 *)(qp + 16 * s + 8 * half);  // rows past M read node 0: unused
-    }
     f32x16 oacc[DBLK];
 #pragma unroll
     for (int db = 0; db < DBLK; ++db)
@@ -340,8 +345,8 @@ __device__ __forceinline__ void tile_segment(const AttnArgs &a, unsigned char *s
     float m_run = -INFINITY, l_run = 0.f;
     const float c = a.scale * 1.4426950408889634f;
 
-    const gbf16p kpre = uniform_ptr((gbf16p)a.k_prefix[b] + (int64_t)h * a.kv_stride_head);
-    const gbf16p vpre = uniform_ptr((gbf16p)a.v_prefix[b] + (int64_t)h * a.kv_stride_head);
+    const gbf16p kpre = uniform_ptr((gbf16p)(uintptr_t)sq.kpre + (int64_t)h * a.kv_stride_head);
+    const gbf16p vpre = uniform_ptr((gbf16p)(uintptr_t)sq.vpre + (int64_t)h * a.kv_stride_head);
     const gbf16p ktree = (gbf16p)a.k_tree + ((int64_t)b * a.TT_cap * a.Hkv + h) * D;
     const gbf16p vtree = (gbf16p)a.v_tree + ((int64_t)b * a.TT_cap * a.Hkv + h) * D;
     const int64_t stok = a.kv_stride_tok, stree = (int64_t)a.Hkv * D;
@@ -385,6 +390,7 @@ __device__ __forceinline__ void tile_segment(const AttnArgs &a, unsigned char *s
     const int p16 = lane & 15, r0 = p16 >> 2, q4 = p16 & 3, grp = (lane >> 4) & 1;
     const u32 voff = lds0 + (u32)((4 * half + r0) * 64 + 32 * grp + 8 * q4);
 
+    bf16x8 qreg[KSTEPS];
     // Scores of a block: two 32x32 blocks, S[j] = keys 32 j .. 32 j + 31.
     struct Scores { f32x16 v[2]; };
     f32x16 zero16;
@@ -548,6 +554,11 @@ __device__ __forceinline__ void tile_segment(const AttnArgs &a, unsigned char *s
     };
     Scores S0, S1;
     fetch_k(kb0, 0);
+    {
+        const __bf16 *qp = (const __bf16 *)a.q + (((int64_t)b * a.TT_cap + node) * a.Hq + hq) * D;
+#pragma unroll
+        for (int s = 0; s < KSTEPS; ++s) qreg[s] = *(const bf16x8 *)(qp + 16 * s + 8 * half);
+    }
     fetch_v(kb0, 0);
     if (kb0 + 1 < kb1) fetch_k(kb0 + 1, 1);
     __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's part of the tiles is in LDS
@@ -702,15 +713,19 @@ __device__ __forceinline__ void tile_segment(const AttnArgs &a, unsigned char *s
 // round-robin by linear id, so all row tiles of one kv head land on one XCD and share its L2
 // copy of that head's K/V.
 template <int D>
-__global__ __launch_bounds__(256, 2) void attn_tile_kernel(AttnArgs a) {
+__global__ __launch_bounds__(256, 2) void attn_tile_kernel(AttnArgs a, GroupDiv gd) {
     extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];
     const int b = blockIdx.z, h = blockIdx.x, m0 = blockIdx.y * ATT_MTILE;
-    const int N = min(max(a.n_nodes[b], 1), a.TT_cap);
-    if (m0 >= N * (a.Hq / a.Hkv)) return;
-    const int nb = (max(a.prefix_len[b], 0) + N + TILE_KEYS - 1) / TILE_KEYS;
+    // the four words in one trip to memory: the compiler would fetch the others behind the test of the first
+    int n_raw = a.n_nodes[b], l_raw = a.prefix_len[b];
+    u64 kp_raw = (u64)(uintptr_t)a.k_prefix[b], vp_raw = (u64)(uintptr_t)a.v_prefix[b];
+    asm volatile("" : "+s"(n_raw), "+s"(l_raw), "+s"(kp_raw), "+s"(vp_raw));
+    const SeqWords sq = {min(max(n_raw, 1), a.TT_cap), max(l_raw, 0), kp_raw, vp_raw};
+    if (m0 >= sq.N * gd.G) return;
+    const int nb = (sq.L + sq.N + TILE_KEYS - 1) / TILE_KEYS;
     TileParts whole = {};
     whole.parts = 1;
-    tile_segment<D>(a, s_dyn, h, b, m0, blockIdx.y + blockIdx.z, 0, nb, whole, 0, false);
+    tile_segment<D>(a, gd, sq, s_dyn, h, b, m0, blockIdx.y + blockIdx.z, 0, nb, whole, 0, false);
 }
 
 // ---- balanced schedule -----------------------------------------------------------------------------
@@ -736,83 +751,108 @@ struct GangPartial {
     u64 tag;      // of this launch: what the memory held before it never looks like a count or a mark
 };
 
-__device__ __forceinline__ int wave_excl_scan_i32(int v, int lane) {
-    int x = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(x, o, 64);
-        if (lane >= o) x += t;
-    }
-    return x - v;
+// x / d for 0 <= x < 2^31 and d >= 1: two steps from the reciprocal, each off by a few units of its own result at most, and the last
+// unit by the remainder.  (The compiler's division is some forty instructions, and the plan has ten in a row.)
+__device__ __forceinline__ int div_small(int x, int d) {
+    const float inv = __builtin_amdgcn_rcpf((float)d);
+    int q = (int)((float)x * inv), r = x - q * d;
+    const int q1 = (int)((float)r * inv);
+    q += q1;
+    r -= q1 * d;
+    return q + (r >= d ? 1 : 0) - (r < 0 ? 1 : 0);
 }
 
 struct GangPlan {
     int mt, nb;        // lane b: row tiles and key blocks of sequence b (0 past the batch)
+    u64 classes;       // bit m: there are sequences of m row tiles
     int C, g, T;       // lane m: columns, gangs and columns per gang of class m
 };
 
-__device__ __forceinline__ GangPlan gang_plan(const AttnArgs &a, int P, int mt_max, int lane) {
+__device__ __forceinline__ GangPlan gang_plan(const SeqWords &mine, int G, int batch, int P, int lane) {
     GangPlan p;
     p.mt = 0;
     p.nb = 0;
-    if (lane < a.batch) {
-        const int N = min(max(a.n_nodes[lane], 1), a.TT_cap);
-        p.mt = (N * (a.Hq / a.Hkv) + ATT_MTILE - 1) / ATT_MTILE;
-        p.nb = (max(a.prefix_len[lane], 0) + N + TILE_KEYS - 1) / TILE_KEYS;
+    if (lane < batch) {
+        p.mt = (mine.N * G + ATT_MTILE - 1) / ATT_MTILE;
+        p.nb = (mine.L + mine.N + TILE_KEYS - 1) / TILE_KEYS;
     }
+    p.classes = 0;
     p.C = 0;
-    for (int m = 1; m <= mt_max; ++m) {
+    int W = 0;
+    for (u64 left = __builtin_amdgcn_ballot_w64(p.mt > 0); left;) {
+        const int m = __builtin_amdgcn_readlane(p.mt, __builtin_ctzll(left));
         const int c = wave_sum_i32(p.mt == m ? p.nb : 0);
         if (lane == m) p.C = c;
+        W += m * c;
+        p.classes |= 1ull << m;
+        left &= ~__builtin_amdgcn_ballot_w64(p.mt == m);
     }
-    const int W = wave_sum_i32(lane * p.C);
     // smallest T with sum_m m ceil(C_m / T) <= P: lane i probes T0 + i.  T = max C_m always fits
     // (the host checks P >= 1 + 2 + .. + mt_max), so the loop ends.
-    int T0 = max(1, (W + P - 1) / P), T;
+    int T0 = max(1, div_small(W + P - 1, P)), T;
     for (;;) {
         const int t = T0 + lane;
         int slots = 0;
-        for (int m = 1; m <= mt_max; ++m) slots += m * ((__builtin_amdgcn_readlane(p.C, m) + t - 1) / t);
-        const u64 ok = __ballot(slots <= P);
+        for (u64 left = p.classes; left; left &= left - 1) {
+            const int m = (int)__builtin_ctzll(left);
+            slots += m * div_small(__builtin_amdgcn_readlane(p.C, m) + t - 1, t);
+        }
+        const u64 ok = __builtin_amdgcn_ballot_w64(slots <= P);
         if (ok) {
             T = T0 + (int)__builtin_ctzll(ok);
             break;
         }
         T0 += 64;
     }
-    p.g = (p.C + T - 1) / T;
-    p.T = p.g > 0 ? (p.C + p.g - 1) / p.g : 0;
+    p.g = div_small(p.C + T - 1, T);
+    p.T = p.g > 0 ? div_small(p.C + p.g - 1, p.g) : 0;
     return p;
 }
 
 template <int D>
-__global__ __launch_bounds__(256, 2) void attn_gang_kernel(AttnArgs a, int P, int mt_max, GangPartial part) {
+__global__ __launch_bounds__(256, 2) void attn_gang_kernel(AttnArgs a, GroupDiv gd, int P, GangPartial part) {
     extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];
     const int h = blockIdx.x, y = blockIdx.y, lane = threadIdx.x & 63;
-    const GangPlan p = gang_plan(a, P, mt_max, lane);
+    // lane b: the words of sequence b, in one trip to memory (read again by every segment, a sequence's pointers behind its lengths,
+    // and with the compiler's divisions in the plan, a launch took 1.0 to 1.7 us longer: 8 sequences of the 8B shape, 112 nodes, 40 keys 23.7 us, now
+    // 22.8; 64 nodes, 1,100 keys 41.8 and 40.2; 4 of the 70B shape, 2,048 keys 45.8 and 44.8)
+    const int bl = min(lane, a.batch - 1);
+    const int n_raw = a.n_nodes[bl], l_raw = a.prefix_len[bl];
+    const SeqWords mine = {min(max(n_raw, 1), a.TT_cap), max(l_raw, 0), (u64)(uintptr_t)a.k_prefix[bl], (u64)(uintptr_t)a.v_prefix[bl]};
+    const GangPlan p = gang_plan(mine, gd.G, a.batch, P, lane);
     // class, gang and row tile of slot y
     int base = 0, cls = 0;
-    for (int m = 1; m <= mt_max; ++m) {
-        const int span = m * __builtin_amdgcn_readlane(p.g, m);
-        if (cls == 0) {
-            if (y < base + span) cls = m;
-            else base += span;
+    for (u64 left = p.classes; left; left &= left - 1) {
+        const int m = (int)__builtin_ctzll(left), span = m * __builtin_amdgcn_readlane(p.g, m);
+        if (y < base + span) {
+            cls = m;
+            break;
         }
+        base += span;
     }
     if (cls == 0) return;  // spare slot
-    const int j = (y - base) / cls, tile = (y - base) % cls;
+    const int j = __builtin_amdgcn_readfirstlane(div_small(y - base, cls)), tile = y - base - j * cls;
     const int Tc = __builtin_amdgcn_readlane(p.T, cls), Cc = __builtin_amdgcn_readlane(p.C, cls);
     const int lo = j * Tc, hi = min(Cc, lo + Tc);
     // first column of every sequence of this class
     const int val = p.mt == cls ? p.nb : 0;
-    const int cs = wave_excl_scan_i32(val, lane);
-    u64 segs = __ballot(val > 0 && cs < hi && cs + val > lo);
+    const int cs = wave_scan_incl_i32(val) - val;
+    u64 segs = __builtin_amdgcn_ballot_w64(val > 0 && cs < hi && cs + val > lo);
+    // What a segment needs of its sequence, out of the registers of the loop over its blocks.  Every wave writes the same.
+    __shared__ struct { SeqWords w; int cs, nb; } s_seq[64];
+    s_seq[lane].w = mine;
+    s_seq[lane].cs = cs;
+    s_seq[lane].nb = val;
     while (segs) {
         const int b = (int)__builtin_ctzll(segs);
         segs &= segs - 1;
-        const int csb = __builtin_amdgcn_readlane(cs, b), nbb = __builtin_amdgcn_readlane(val, b);
+        asm volatile("" ::: "memory");
+        const int csb = __builtin_amdgcn_readfirstlane(s_seq[b].cs), nbb = __builtin_amdgcn_readfirstlane(s_seq[b].nb);
+        const SeqWords sq = {__builtin_amdgcn_readfirstlane(s_seq[b].w.N), __builtin_amdgcn_readfirstlane(s_seq[b].w.L),
+                             readlane_u64(s_seq[b].w.kpre, 0), readlane_u64(s_seq[b].w.vpre, 0)};
         const int kb0 = max(lo, csb) - csb, kb1 = min(hi, csb + nbb) - csb;
-        const int jf = csb / Tc, jl = (csb + nbb - 1) / Tc;  // its first and last gang
+        // its first and its last gang
+        const int jf = __builtin_amdgcn_readfirstlane(div_small(csb, Tc)), jl = __builtin_amdgcn_readfirstlane(div_small(csb + nbb - 1, Tc));
         TileParts pt;
         pt.parts = jl - jf + 1;
         pt.me = j - jf;
@@ -822,7 +862,7 @@ __global__ __launch_bounds__(256, 2) void attn_gang_kernel(AttnArgs a, int P, in
         pt.ml = part.ml;
         pt.count = part.count + pt.slot;
         pt.tag = part.tag;
-        tile_segment<D>(a, s_dyn, h, b, tile * ATT_MTILE, j, kb0, kb1, pt, a.Hkv * P, !segs);
+        tile_segment<D>(a, gd, sq, s_dyn, h, b, tile * ATT_MTILE, j, kb0, kb1, pt, a.Hkv * P, !segs);
     }
 }
 
@@ -1888,7 +1928,7 @@ int attn_launch(const AttnArgs &a, hipStream_t st, hipError_t *err) {
     const int64_t units = (int64_t)a.batch * a.Hkv * mblocks;
     if (wave_ahead(units, base_wgs, mblocks, max_blocks(a)) || (base_wgs < 128 && !gang)) return wave_launch<128>(a, st, err);
     if (!gang) {
-        launch_kernel(KID_ATTN, st, attn_tile_kernel<128>, dim3(a.Hkv, mtiles, a.batch), dim3(256), TILE_LDS_BYTES, a);
+        launch_kernel(KID_ATTN, st, attn_tile_kernel<128>, dim3(a.Hkv, mtiles, a.batch), dim3(256), TILE_LDS_BYTES, a, group_div(G));
         *err = hipGetLastError();
         return *err == hipSuccess ? DT_OK : DT_ERR_HIP;
     }
@@ -1899,7 +1939,7 @@ int attn_launch(const AttnArgs &a, hipStream_t st, hipError_t *err) {
     part.ml = part.o + slots * 2 * ATT_MTILE * (a.D / 2);
     part.count = part.ml + slots * 2 * ATT_MTILE;
     part.tag = (launches.fetch_add(1, std::memory_order_relaxed) + 1) * 0x9e3779b97f4a7c15ull & ~(u64)0xffff;
-    launch_kernel(KID_ATTN, st, attn_gang_kernel<128>, dim3(a.Hkv, P), dim3(256), TILE_LDS_BYTES, a, P, mtiles, part);
+    launch_kernel(KID_ATTN, st, attn_gang_kernel<128>, dim3(a.Hkv, P), dim3(256), TILE_LDS_BYTES, a, group_div(G), P, part);
     *err = hipGetLastError();
     return *err == hipSuccess ? DT_OK : DT_ERR_HIP;
 }
