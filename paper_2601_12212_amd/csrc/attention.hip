@@ -738,7 +738,8 @@ __global__ __launch_bounds__(256, 2) void attn_tile_kernel(AttnArgs a, GroupDiv 
 // concatenated in batch order, form its C_m "columns" of cost m each.  Class m is given g_m
 // "gangs" of m slots (one per row tile, neighbours in launch order, so the tiles of a sequence walk
 // its K/V together and share it in L2); gang j takes columns [j T_m, (j+1) T_m) of the class, with
-// T_m = ceil(C_m / g_m), and the g_m are the ones that minimise max_m T_m under sum m g_m <= P.
+// T_m = ceil(C_m / g_m), and the g_m are the ones that minimise max_m T_m under sum m g_m <= P, or the next ones where fewer cuts
+// are worth more than slots (below); or every sequence has a gang of its own, where there are slots for all and that is cheaper still.
 // A slot therefore works through a few (sequence, tile, key range) segments of near-equal total
 // length.  A sequence cut by a range boundary leaves partials: per slot at most one "head" (its first
 // segment, when that sequence began in an earlier gang) and one "tail" (a sequence that began
@@ -748,6 +749,18 @@ __global__ __launch_bounds__(256, 2) void attn_tile_kernel(AttnArgs a, GroupDiv 
 // that ends with the tail.
 // Every wave derives the plan by itself from n_nodes / prefix_len with wave
 // operations (sequence b in lane b: batch <= 64; class m in lane m), so no barrier is involved.
+// How long a plan takes, in twentieths of a microsecond: a block of a slot that has its compute unit to itself, or shares it; a sequence in
+// parts (its partials written, counted in and, part after part, read back), and in so many that its workgroups share the merge.
+// A cut that fills the chip is not worth its partials where sequences are short: two workgroups of a compute unit take nearly twice as long for a
+// block as one.  The smallest T that fits, always, against this (us per layer, 8B shape unless said): 8 sequences of 112 nodes, 40 keys 23.2 | 13.1,
+// 400 26.7 | 18.9, 1,100 43.7 | 31.8; 14 of 64, 400 27.0 | 18.8, of 112, 400 33.5 | 25.4; 5 of 64, 1,600 keys 45.7 | 30.4, 2,400 40.8 | 30.4; four of
+// the 70B shape, 64 nodes, 1,600 38.4 | 28.6; 20 of seven query heads to each of two kv heads, 64 nodes, 400 39.9 | 18.5, 2,400 ragged 46.9 | 39.0.
+// Where the chip is full or one sequence is far longer than the others, the smallest T stays.
+#define COST_BLOCK 22
+#define COST_BLOCK_PAIR 36
+#define COST_CUT 60
+#define COST_PART 60
+#define COST_SHARED 500
 struct GangPartial {
     u64 *o;       // [Hkv, P, 2, D / 4, 256]
     u64 *ml;      // [Hkv, P, 2, 128]
@@ -770,6 +783,7 @@ struct GangPlan {
     int mt, nb;        // lane b: row tiles and key blocks of sequence b (0 past the batch)
     u64 classes;       // bit m: there are sequences of m row tiles
     int C, g, T;       // lane m: columns, gangs and columns per gang of class m
+    int pitch;         // > 0: every sequence has a gang of its own, `pitch` columns wide; 0: columns follow each other
 };
 
 __device__ __forceinline__ GangPlan gang_plan(const SeqWords &mine, int G, int batch, int P, int lane) {
@@ -782,34 +796,52 @@ __device__ __forceinline__ GangPlan gang_plan(const SeqWords &mine, int G, int b
     }
     p.classes = 0;
     p.C = 0;
-    int W = 0;
+    int W = 0, tiles = 0, count = 0;
     for (u64 left = __builtin_amdgcn_ballot_w64(p.mt > 0); left;) {
         const int m = __builtin_amdgcn_readlane(p.mt, __builtin_ctzll(left));
         const int c = wave_sum_i32(p.mt == m ? p.nb : 0);
-        if (lane == m) p.C = c;
+        const u64 members = __builtin_amdgcn_ballot_w64(p.mt == m);
+        const int n = __popcll(members);
+        if (lane == m) {
+            p.C = c;
+            count = n;
+        }
         W += m * c;
+        tiles += m * n;
         p.classes |= 1ull << m;
-        left &= ~__builtin_amdgcn_ballot_w64(p.mt == m);
+        left &= ~members;
     }
     // smallest T with sum_m m ceil(C_m / T) <= P: lane i probes T0 + i.  T = max C_m always fits
     // (the host checks P >= 1 + 2 + .. + mt_max), so the loop ends.
-    int T0 = max(1, div_small(W + P - 1, P)), T;
-    for (;;) {
-        const int t = T0 + lane;
+    auto slots_of = [&](int t) {
         int slots = 0;
         for (u64 left = p.classes; left; left &= left - 1) {
             const int m = (int)__builtin_ctzll(left);
             slots += m * div_small(__builtin_amdgcn_readlane(p.C, m) + t - 1, t);
         }
-        const u64 ok = __builtin_amdgcn_ballot_w64(slots <= P);
+        return slots;
+    };
+    int T0 = max(1, div_small(W + P - 1, P)), T;
+    for (;;) {
+        const u64 ok = __builtin_amdgcn_ballot_w64(slots_of(T0 + lane) <= P);
         if (ok) {
             T = T0 + (int)__builtin_ctzll(ok);
             break;
         }
         T0 += 64;
     }
-    p.g = div_small(p.C + T - 1, T);
-    p.T = p.g > 0 ? div_small(p.C + p.g - 1, p.g) : 0;
+    // What the plan costs with T and up to 63 larger ones, one to a lane; and with every sequence whole.
+    const int longest = wave_max_i32(p.nb);
+    const int step = max(1, (longest - T + 62) / 63);
+    const int t = T + step * lane, parts = div_small(longest + t - 1, t);
+    const int block = slots_of(t) <= P / 2 ? COST_BLOCK : COST_BLOCK_PAIR;
+    const u32 cost = (u32)(block * t + (parts > SERIAL_PARTS ? COST_SHARED : COST_CUT + COST_PART * max(parts, 2)));
+    const u32 best = ~wave_max_u32(~(cost << 6 | (u32)lane));  // of equal ones the smallest
+    T += step * (int)(best & 63u);
+    p.pitch = tiles <= P && (u32)((tiles <= P / 2 ? COST_BLOCK : COST_BLOCK_PAIR) * longest) <= best >> 6 ? longest : 0;
+    p.g = p.pitch ? count : div_small(p.C + T - 1, T);
+    p.T = p.pitch ? longest : p.g > 0 ? div_small(p.C + p.g - 1, p.g) : 0;
+    if (p.pitch) p.C = count * longest;
     return p;
 }
 
@@ -840,7 +872,7 @@ __global__ __launch_bounds__(256, 2) void attn_gang_kernel(AttnArgs a, GroupDiv 
     const int lo = j * Tc, hi = min(Cc, lo + Tc);
     // first column of every sequence of this class
     const int val = p.mt == cls ? p.nb : 0;
-    const int cs = wave_scan_incl_i32(val) - val;
+    const int cs = p.pitch ? (int)lanes_below(__builtin_amdgcn_ballot_w64(val > 0)) * p.pitch : wave_scan_incl_i32(val) - val;
     u64 segs = __builtin_amdgcn_ballot_w64(val > 0 && cs < hi && cs + val > lo);
     // What a segment needs of its sequence, out of the registers of the loop over its blocks.  Every wave writes the same.
     __shared__ struct { SeqWords w; int cs, nb; } s_seq[64];

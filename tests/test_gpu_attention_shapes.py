@@ -234,3 +234,48 @@ def test_numbers_of_key_splits(D, Hkv, L):
                          [(52, 5, 5, 150)])
 def test_lines_between_the_two_kernels(B, Hq, Hkv, L):
     check_case(oracle_case(0, cfg=_cfg("bf16", 128, [(32, 5, 6)] * B, [L] + [7 + 40 * (b % 3) for b in range(1, B)], Hq, Hkv)))
+
+
+# Plans of the balanced schedule: sequences whole, cut because that is cheaper, and cut because there are fewer slots than tiles.  Four sequences of three
+# tiles: whole, in two parts, of differing lengths; with two tiles each, 32 sequences have exactly the slots there are, 33 two too few.
+@pytest.mark.parametrize("Hq,Hkv,plen", [(64, 8, [1300] * 4), (64, 8, [1700] * 4), (64, 8, [2600, 1300, 70, 300]), (32, 8, [1300] + [130, 60] * 15 + [1]),
+                                         (32, 8, [1300] + [130, 60] * 16)])
+def test_plans_of_the_balanced_schedule(Hq, Hkv, plen):
+    check_case(oracle_case(0, cfg=_cfg("bf16", 128, [(40, 4, 6)] * len(plen), plen, Hq, Hkv)))
+
+
+def test_short_sequences_under_a_long_bound():
+    # the bound that the caller gives may be far above the lengths, which the plan then finds: against the oracle, and against the same call with a bound
+    # that sends it to the kernel of whole tiles
+    B, TT, long = 8, 64, 6000
+    cfg = _cfg("bf16", 128, [(TT, 5, 6)] * B, [long] * B, 32, 8)
+    case = oracle_case(0, cfg=cfg)
+    st = make_step(case)
+    st.build_tree()
+    n = case.trees[0]["n_nodes"]
+    for lengths in ([1, 40, 64 * 4 - n, 64 * 4 - n + 1, 300, 700, 0, 1000], [1100] * B):
+        for b, L in enumerate(lengths):
+            st.prefix_len[b] = L
+        st.tree_attention()
+        for b in (0, 2, 3, 7):
+            q, kt, vt, kp, vp = dt_synth.qkv(cfg, b)
+            want = ref.tree_attention(q[:n], kt[:n], vt[:n], kp[:lengths[b]], vp[:lengths[b]], case.trees[b]["anc_mask"], st.scale)
+            assert_attention(st.attention_out(b), want, "bf16", "%d keys" % lengths[b])
+
+
+def test_shared_merge_of_a_dozen_to_thirty_parts():
+    # one sequence of 90 to 210 blocks among 63 of 22, six or seven blocks to a part: the counts around those that are read together
+    B, TT = 64, 40
+    cfg = _cfg("bf16", 128, [(TT, 5, 6)] * B, [64 * 210 - TT] + [1368] * (B - 1), 2, 2)
+    case = oracle_case(0, cfg=cfg)
+    st = make_step(case)
+    st.build_tree()
+    n = case.trees[0]["n_nodes"]
+    assert n == TT
+    q, kt, vt, kp, vp = dt_synth.qkv(cfg, 0)
+    for blocks in range(90, 211, 8):
+        L = 64 * blocks - TT
+        st.prefix_len[0] = L
+        st.tree_attention()
+        want = ref.tree_attention(q[:n], kt[:n], vt[:n], kp[:L], vp[:L], case.trees[0]["anc_mask"], st.scale)
+        assert_attention(st.attention_out(0), want, "bf16", "%d blocks" % blocks)
