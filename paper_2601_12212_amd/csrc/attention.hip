@@ -712,8 +712,8 @@ __device__ __forceinline__ void tile_segment(const AttnArgs &a, const GroupDiv &
         }
 }
 
-// One workgroup per (kv head, row tile, sequence), the whole key range: for batches that the balanced schedule below does
-// not take.  blockIdx.x = kv head: workgroups are dealt to the 8 XCDs
+// One workgroup per (kv head, row tile, sequence), the whole key range: for short sequences, and for batches that the balanced
+// schedule below does not take.  blockIdx.x = kv head: workgroups are dealt to the 8 XCDs
 // round-robin by linear id, so all row tiles of one kv head land on one XCD and share its L2
 // copy of that head's K/V.
 template <int D>
@@ -1861,34 +1861,24 @@ static int wave_splits(int D, int64_t units, int64_t nb) {
 // 32-key blocks of the longest sequence
 static int64_t max_blocks(const AttnArgs &a) { return ((int64_t)a.max_prefix_len + a.TT_cap + ATT_KB - 1) / ATT_KB; }
 
-// 128-wide heads: is the small-batch kernel ahead of the balanced schedule?  Its workgroups walk all keys of a row block: about 2 us and
-// 5 + nb / 4 for every 256 units, with splits that much fewer blocks; the schedule, which shares each key block among four
-// row blocks and cuts what is long, starts at 22 to 30 us and takes half as long a block.  Where a kv head has two row blocks, the schedule
-// still halves what is read, and both wait for the memory sooner; where it has one, there is nothing to share, but the schedule has as
-// many tiles as there are units.
-// What the rule has is the longest length that the caller allows for, max_prefix_len: one call's own, or, in a step that is captured once,
-// the most that any replay will have.  Both sides, small-batch | balanced, us per layer, all sequences as long as that ("equal") or from a
-// quarter of it up ("ragged"):
-//   up to 256 units, fewer than 128 tiles: always the small-batch kernel.  With 300 / 1,000 / 2,000 real keys under a bound of 16,000, one sequence
-//     of the 8B shape (60 nodes) 11 | 22, 13 | 22, 14 | 24, four 11 | 32, 18 | 44, 24 | 41.  That is what a line on the bound would lose; what none loses, where the bound
-//     is met: 8B shape, 4 sequences (256) 4,000 keys 36 | 49, 8,192 69 | 68, 16,000 136 | 101, ragged 8,192 58 | 57, 16,000 102 | 71; 3 (192) 4,000 35 | 40, 8,192 56 | 52, 12,000
-//     94 | 68, 16,000 125 | 79, ragged 8,192 39 | 40, 12,000 82 | 59; 2 (128) 8,192 36 | 39, 16,000 65 | 60; 70B shape, 2 (240) 4,000 36 | 51, 8,192 63 | 58, 16,000 119 | 87;
-//     13B shape (two row blocks), 2 (160) 2,500 29 | 37, 4,000 59 | 54, 8,192 109 | 88, 3 (240) 8,192 121 | 118: up to a quarter at 8,192 keys, two fifths at 16,000;
-//   up to 256 units, 128 tiles and more (one or two row blocks to a kv head): the line lies where equal and ragged lengths lose alike.  32 heads of
-//     30 nodes, 4 sequences (128) 150 keys 10 | 15, 4,000 56 | 69, 8,192 99 | 114, 12,000 145 | 153; 8 (256) 6,400 145 | 165, 8,192 182 | 205, 12,000 273 | 283, ragged 6,400 100 | 87,
-//     8,192 137 | 135, 12,000 199 | 198; of 60 nodes (two row blocks), 4 (256) 4,800 73 | 76, 8,192 116 | 120, ragged 4,800 57 | 60, 6,400 84 | 81, 8,192 106 | 103;
-//   up to 512 units, 128 tiles and more: 8B shape, 8 sequences (512) 400 keys 23 | 30, 1,000 30 | 34, 2,000 43 | 41, 3,000 57 | 49, ragged 2,000 35 | 39, 4,000 50 | 50, 6,400 66 | 47; two row
-//     blocks, 40 heads, 4 (320) 700 29 | 26, 1,000 33 | 35, 2,500 75 | 63, ragged 1,000 22 | 26, 4,000 83 | 66, 32 heads, 6 (384) 700 28 | 30, 2,500 77 | 67, ragged 2,500 30 | 34; one, 12
-//     sequences of 32 heads (384) 150 17 | 14, 400 29 | 30;
-//   up to 512 units, fewer than 128 tiles: where ragged lengths meet.  8B shape, 6 (384) ragged 4,000 41 | 45, 6,400 59 | 59, 8,192 70 | 61; equal ones are past the
-//     meeting before the line, 3,000 52 | 48, 4,000 63 | 57, 6,400 108 | 79;
-//   beyond 512: no line holds.  12 sequences of the 8B shape (768) 30 keys 18 | 24, 150 25 | 24, 400 32 | 43, 700 38 | 35, 1,000 43 | 36, ragged 700 35 | 40, 1,000 38 | 36, 16 (1,024) 30 23 | 25,
-//     150 32 | 26, 400 41 | 30; 6 of 128 nodes (768) 150 26 | 33, 400 33 | 30, 700 38 | 40.
-static bool wave_ahead(int64_t units, int64_t tiles, int mblocks, int64_t nb) {
-    if (units <= 256) return tiles < 128 || nb <= (mblocks == 2 ? 150 : 200) * wave_splits(128, units, nb);
-    if (units > 512 || mblocks == 1) return false;
-    return nb <= (mblocks == 2 ? 20 : tiles < 128 ? 320 - units / 3 : 100 - units / 12);
-}
+// 128-wide heads: which kernel.  `units` (sequence, kv head, 32-row block)s, as the caller allows for them:
+//  - up to 256, one to a compute unit: the small-batch kernel, whatever the lengths;
+//  - more, and at most 40 blocks of 32 keys: workgroups that take whole tiles of 128 rows.  Each shares a key block among four row blocks, and on
+//    sequences this short nothing is gained by cutting them: the schedule finds that too, and takes 1 us to find it;
+//  - more keys: the balanced schedule, which cuts or does not cut by the lengths that it finds.
+// The lengths here are the most that the caller allows for (max_prefix_len): one call's own, or, in a step that is captured once, the most that any
+// replay will have.  us per layer, small-batch | balanced | whole tiles, all sequences as long as that ("equal") or from a quarter of it up ("ragged"):
+//   256 units and fewer: 4 sequences of the 8B shape, 64 nodes (256) 40 keys 7 | 9 | 9, 400 12 | 15 | 16, 1,100 17 | 27 | 27, 2,400 26 | 40 | 47, 4,000 36 | 35 | 70,
+//     8,000 62 | 55 | 130; 3 (192) 8,000 56 | 50, 12,000 81 | 63; 32 heads without groups, 4 sequences of 64 nodes (256) 400 12 | 15 | 15, 2,400 33 | 40 | 45, 8,000 114 | 120,
+//     ragged 107 | 107; 8 of 32 nodes (256) 400 16 | 15 | 15, 2,400 54 | 66 | 65, 8,000 179 | 196; 40 heads, 5 of 32 (200) ragged 12,000 190 | 174.  Long lengths that the balanced
+//     schedule would take up to a quarter faster are left to the small-batch kernel, because a bound that far above them would cost the short ones more;
+//   more: 5 of the 8B shape, 64 nodes (320) 40 keys 12 | 10 | 9, 400 19 | 16 | 16, 1,300 30 | 28 | 30, 1,600 33 | 30 | 33, ragged 22 | 27 | 32, 2,400 44 | 30 | 47, ragged 34 | 31 | 45;
+//     4 of 112 (448) 1,600 36 | 37 | 36, ragged 30 | 28 | 30, 4,000 66 | 57 | 73; 40 heads without groups, 4 of 64 (320) 1,300 36 | 31 | 29, 2,400 56 | 44 | 45;
+//   more tiles than there is room for at once: 32 sequences of the 70B shape, 64 nodes (1,024 tiles) ragged 200 keys 42 balanced | 31 whole, 1,100 73 | 67; 54 of 40 heads, 64
+//     nodes (2,160) 400 153 | 138, ragged 108 | 90, 1,100 316 | 289; 40 of four heads with four queries each, 112 nodes (640) 400 41 | 39, ragged (but then 500 or so) 28 | 36;
+//     16 of 40 heads (640) 1,100 103 | 96, 1,600 136 | 134, 2,400 181 | 199; 64 of the 8B shape, 256 to 4,096 keys 231 | 295.
+#define SMALL_UNITS 256
+#define WHOLE_BLOCKS 40
 
 // The small-batch kernel and, with key splits, its merge.
 template <int D>
@@ -1954,16 +1944,14 @@ int attn_launch(const AttnArgs &a, hipStream_t st, hipError_t *err) {
     // it off the matrix cores) it is ahead at both ends, one sequence of 8 nodes and 40 keys 5.1 us against 7.5, 3 of 64 and
     // 1,500 12.9 against 206, 64 of 128 and 4,000 455 against 19,500.
     if (a.D == 64) return wave_launch<64>(a, st, err);
-    // The balanced schedule wherever its plan fits (one lane per sequence, a slot for every tile count): also for batches of
-    // thousands of whole (sequence, kv head, row tile) items, whose lengths differ (64 sequences of 256 .. 4,096 keys: 295 us
-    // with one workgroup per item, 234 balanced).
+    // The balanced schedule needs a lane for every sequence and a slot for every tile count.
     const int P = 2 * a.n_cu / a.Hkv;
     const bool gang = a.batch <= 64 && mtiles <= 63 && P >= mtiles * (mtiles + 1) / 2 && a.ws &&
                       (size_t)a.Hkv * P * gang_slot_bytes(a.D) <= a.ws_bytes;
     const int mblocks = (a.TT_cap * G + 31) / 32;
     const int64_t units = (int64_t)a.batch * a.Hkv * mblocks;
-    if (wave_ahead(units, base_wgs, mblocks, max_blocks(a)) || (base_wgs < 128 && !gang)) return wave_launch<128>(a, st, err);
-    if (!gang) {
+    if (units <= SMALL_UNITS || (base_wgs < 128 && !gang)) return wave_launch<128>(a, st, err);
+    if (!gang || max_blocks(a) <= WHOLE_BLOCKS) {
         launch_kernel(KID_ATTN, st, attn_tile_kernel<128>, dim3(a.Hkv, mtiles, a.batch), dim3(256), TILE_LDS_BYTES, a, group_div(G));
         *err = hipGetLastError();
         return *err == hipSuccess ? DT_OK : DT_ERR_HIP;

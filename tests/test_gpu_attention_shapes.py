@@ -227,8 +227,8 @@ def test_numbers_of_key_splits(D, Hkv, L):
     check_case(oracle_case(0, cfg=_cfg("bf16", D, [(32, 5, 6)], [L], Hkv, Hkv)))
 
 
-# both sides of the lines between the small-batch kernel and the balanced schedule: 320 units of four row blocks to a kv head,
-# 256 and 320 of two, 256 and 260 of one; one sequence of that length among short ones
+# lengths and numbers of row blocks around which the small-batch kernel and the balanced schedule take as long as each other: 320 units of four row
+# blocks to a kv head, 256 and 320 of two, 256 and 260 of one; one sequence of that length among short ones
 @pytest.mark.parametrize("B,Hq,Hkv,L", [(B, Hq, Hkv, L + i) for B, Hq, Hkv, L in ((40, 8, 2, 6816), (64, 8, 2, 1824), (32, 8, 4, 4768), (40, 8, 4, 608),
                                                                                  (64, 4, 4, 6368)) for i in (0, 1)] +
                          [(52, 5, 5, 150)])
@@ -279,3 +279,10 @@ def test_shared_merge_of_a_dozen_to_thirty_parts():
         st.tree_attention()
         want = ref.tree_attention(q[:n], kt[:n], vt[:n], kp[:L], vp[:L], case.trees[0]["anc_mask"], st.scale)
         assert_attention(st.attention_out(0), want, "bf16", "%d blocks" % blocks)
+
+
+# 256 (sequence, kv head, 32-row block)s, which the small-batch kernel takes, and 264, which the kernel of whole tiles takes up to 40 blocks of 32 keys and the
+# balanced schedule from 41 on
+@pytest.mark.parametrize("B,L", [(32, 1248), (33, 100), (33, 1248), (33, 1249)])
+def test_lines_between_the_three_kernels(B, L):
+    check_case(oracle_case(0, cfg=_cfg("bf16", 128, [(32, 5, 6)] * B, [L] + [7 + 40 * (b % 3) for b in range(1, B)], 8, 8)))
