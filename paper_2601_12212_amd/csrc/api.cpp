@@ -402,6 +402,7 @@ int dt_expand_level(void *stream, int batch, int level, const dt_params *params,
     ta.expand_level = level; ta.prefix_len = prefix_len; ta.n_expand = n_expand; ta.state_n_exp = ls.n_exp;
     ta.exp_token = exp_token; ta.exp_parent_slot = exp_parent_slot; ta.exp_row = exp_row; ta.exp_pos = exp_pos;
     ta.exp_mask = (unsigned long long *)exp_mask;
+    ta.state_val = ls.top_val; ta.state_id = ls.top_id;
     ta.early_stop = flags & DT_TREE_EARLY_STOP;
     e = dt::tree_launch(ta, st);
     if (e != hipSuccess) return hip_fail(e);

@@ -82,6 +82,8 @@ struct TreeArgs {
     const int32_t *prefix_len;  // may be null (positions then count from 0)
     int32_t *n_expand, *state_n_exp, *exp_token, *exp_parent_slot, *exp_row, *exp_pos;  // [batch(, DT_K_MAX)]
     unsigned long long *exp_mask;  // [batch, DT_K_MAX, 4]
+    float *state_val;       // top_val and top_id, for the set that a level hands on to the next
+    int32_t *state_id;
 };
 hipError_t tree_init();  // once per device, before the first launch
 hipError_t tree_launch(const TreeArgs &a, hipStream_t st);

@@ -96,6 +96,22 @@ struct TreeLds {
     int p_end, n_exp, memn;
 };
 
+// What the expansion of level l hands on to that of level l + 1 when the tree is built level by level: the nodes it chose, the
+// token count, and which level it was.  It lies in the last rows of the sequence's state, which belong to the deepest level's pass and are
+// free until then.  Without it, or with another level's (a level asked for twice), the levels before are gone through again, from the
+// row results.  Each level gone through again took 0.5 us with k up to 16 and 1.7 beyond.  All calls of a step, replayed: (60, 6, 10), 128,256 tokens
+// 78.2 -> 74.7 us (with the kernels of their own); 16 sequences of up to (123, 8, 23), 1,152 tokens 125.6 -> 101.7; 4 of (66, 3, 8) 32.0 -> 31.7.
+#define CARRY_ROW (DT_STATE_ROWS - 4)  // four rows of values: DT_K_MAX Parents; two words of the ids
+#define CARRY_FROM 2  // level 1 expands the root's children: nothing to go through
+#define CARRY_LEVELS ((CARRY_ROW - 1) / DT_K_MAX)  // levels whose nodes' rows, at most l DT_K_MAX, end before it
+static_assert(4 * DT_K_MAX * sizeof(float) == DT_K_MAX * sizeof(Parent), "four rows");
+__device__ __forceinline__ int carry_tag(int level) { return 0x7A5C3000 | level; }
+__device__ __forceinline__ int64_t carry_at(int64_t seq_rows, int b) { return (b * seq_rows + CARRY_ROW) * DT_K_MAX; }
+// The level to start from, its nodes and the token count: level 0, nothing.
+struct Start {
+    int level, n_exp, tok_count;
+};
+
 // ---- selection inside a wave ---------------------------------------------------------------------------
 // The `keep` best of the keys that a wave holds (key q of lane i is candidate i + 64 q), equal keys by ascending candidate;
 // all viable ones if they are fewer.  The caller knows bounds: lo is KEY_NEG_INF or lies below at
@@ -271,10 +287,13 @@ __device__ __forceinline__ int choose_first(TreeLds &S, int k, float sc) {
     return __popcll(m);
 }
 // What the draft model is handed for its next pass, by one wave: node s of the set chosen at level l.
-__device__ __forceinline__ void emit_level(const TreeArgs &a, const TreeLds &S, int b, int l, int k, int n_exp) {
+__device__ __forceinline__ void emit_level(const TreeArgs &a, const TreeLds &S, int b, int l, int k, int n_exp, int tok_count) {
     const int lane = lane_id();
+    const bool carry = l >= CARRY_FROM && l <= CARRY_LEVELS;
+    const int64_t at = carry_at(a.seq_rows, b);
     if (lane < n_exp) {
         const Parent pr = S.par[l][lane];
+        if (carry) ((Parent *)(a.state_val + at))[lane] = pr;
         const Decoded dc = decode(pr.index, pool_shape(k));
         const int64_t e = (int64_t)b * DT_K_MAX + lane;
         a.exp_token[e] = S.tok[pr.index];
@@ -293,23 +312,28 @@ __device__ __forceinline__ void emit_level(const TreeArgs &a, const TreeLds &S, 
         a.exp_mask[e * 4] = w0; a.exp_mask[e * 4 + 1] = w1;
         a.exp_mask[e * 4 + 2] = w2; a.exp_mask[e * 4 + 3] = w3;
     }
-    if (lane == 0) { a.n_expand[b] = n_exp; a.state_n_exp[b] = n_exp; }
+    if (lane == 0) {
+        a.n_expand[b] = n_exp;
+        a.state_n_exp[b] = n_exp;
+        if (carry) *(int2 *)(a.state_id + at) = make_int2(carry_tag(l), tok_count);
+    }
 }
 
 // All levels, by one wave: G candidates per lane, 64 G >= k^2.  Returns the end of the pool (levels computed so far), or -1
 // when only level `xl` was wanted and has been written.  LDS is written and read by this wave alone, in order.
-template <int G>
-__device__ __forceinline__ int levels_narrow(const TreeArgs &a, TreeLds &S, int b, int k, int d, int TT) {
-    const int lane = lane_id(), xl = a.expand_level, kk = k * k;
+template <int G, bool EXPAND>
+__device__ __forceinline__ int levels_narrow(const TreeArgs &a, TreeLds &S, int b, int k, int d, int TT, const Start &from) {
+    const int lane = lane_id(), xl = EXPAND ? a.expand_level : 0, kk = k * k;
+    const int skip = from.level > 0 ? (from.level - 1) * kk : 0;  // candidates of the levels that are not gone through
     const PoolShape ps = pool_shape(k);
     int parent[G], at[G];  // of candidate lane + 64 q: its parent's slot, its pool index
     float own[G];          // of the next level: own log-probabilities, and of slot `lane`'s best child
-    int best_at = k + min(lane, k - 1) * k;
+    int best_at = k + skip + min(lane, k - 1) * k;
     float best_own = S.lp[best_at];
 #pragma unroll
     for (int q = 0; q < G; ++q) {
         parent[q] = lane + 64 * q < kk ? fdiv(lane + 64 * q, ps.inv_k) : DT_K_MAX;
-        at[q] = k + min(lane + 64 * q, kk - 1);  // no candidate: the last one's place, and a parent that does not exist
+        at[q] = k + skip + min(lane + 64 * q, kk - 1);  // no candidate: the last one's place, and a parent that does not exist
         own[q] = S.lp[at[q]];
     }
     if (lane < DT_D_MAX) S.par[lane][DT_K_MAX].score = -INFINITY;
@@ -319,10 +343,16 @@ __device__ __forceinline__ int levels_narrow(const TreeArgs &a, TreeLds &S, int 
     int tok_count = 1 + __popcll(__builtin_amdgcn_ballot_w64(sc1 > -INFINITY));
     const int l_end = xl > 0 ? xl + 1 : d;
     int l = 1, p_end = k, n_exp = 0;
-    if (l < l_end && !(a.early_stop && tok_count >= TT)) n_exp = choose_first(S, k, sc1);
+    if (from.level > 0) {
+        l = from.level;
+        n_exp = from.n_exp;
+        tok_count = from.tok_count;
+    } else if (l < l_end && !(a.early_stop && tok_count >= TT)) {
+        n_exp = choose_first(S, k, sc1);
+    }
     while (n_exp > 0) {
         if (l == xl) {
-            emit_level(a, S, b, l, k, n_exp);
+            emit_level(a, S, b, l, k, n_exp, tok_count);
             return -1;
         }
         // slots beyond the expanded set own no node: their candidates do not exist
@@ -407,10 +437,10 @@ __device__ __forceinline__ int choose_wide(TreeLds &S, int l, int lo, int k, int
 }
 // All levels of more than NARROW_K^2 candidates, by all waves: Q candidates per thread, k^2 <= Q TREE_NT.  As above.  (Two per thread,
 // and lists of up to 128 candidates cut four to a lane instead of two: (TT, d, k) = (80, 6, 20) 14.1 us, 13.3 so.)
-template <int Q>
-__device__ __forceinline__ int levels_wide(const TreeArgs &a, TreeLds &S, int b, int k, int d, int TT) {
+template <int Q, bool EXPAND>
+__device__ __forceinline__ int levels_wide(const TreeArgs &a, TreeLds &S, int b, int k, int d, int TT, const Start &from) {
     const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int xl = a.expand_level, kk = k * k;
+    const int xl = EXPAND ? a.expand_level : 0, kk = k * k;
     const PoolShape ps = pool_shape(k);
     int parent[Q];
 #pragma unroll
@@ -422,7 +452,8 @@ __device__ __forceinline__ int levels_wide(const TreeArgs &a, TreeLds &S, int b,
     u32 lo_key = KEY_NEG_INF, hi_key = 0u;
     int lo = 0, p_end = k, c = 0;
     const int l_end = xl > 0 ? xl + 1 : d;
-    for (int l = 1; l < l_end; ++l) {
+    if (from.level > 0) tok_count = from.tok_count;
+    for (int l = max(from.level, 1); l < l_end; ++l) {
         if (a.early_stop && tok_count >= TT) break;  // uniform
         const int nlo = k + (l - 1) * kk;
         float first = -INFINITY, own[Q] = {};
@@ -433,7 +464,8 @@ __device__ __forceinline__ int levels_wide(const TreeArgs &a, TreeLds &S, int b,
         }
         if (w == 0) {
             int n;
-            if (l == 1) n = choose_first(S, k, sc1);
+            if (l == from.level) n = from.n_exp;
+            else if (l == 1) n = choose_first(S, k, sc1);
             else if (c == 0) n = 0;
             else if (c <= 128)
                 n = choose_wide<2>(S, l, lo, k, c, lo_key, hi_key, S.list_score, [&](int i) { return (int)S.list[i]; });
@@ -445,7 +477,7 @@ __device__ __forceinline__ int levels_wide(const TreeArgs &a, TreeLds &S, int b,
                 n = choose_wide<16>(S, l, lo, k, kk, lo_key, hi_key, S.score + lo, [&](int i) { return lo + i; });
             if (lane >= n && lane < DT_K_MAX) S.par[l][lane].score = -INFINITY;
             if (lane == 0) S.n_exp = n;
-            if (l == xl) emit_level(a, S, b, l, k, n);
+            if (l == xl) emit_level(a, S, b, l, k, n, tok_count);
         }
         if (l == xl) return -1;
         __syncthreads();
@@ -624,6 +656,9 @@ __device__ __forceinline__ int block_select(const float *score, int n, float top
     return total;
 }
 
+// EXPAND: one level's choice; otherwise the whole tree.  (Two kernels: what one of them does not do would be instructions to fetch and scalar
+// registers spilled in the other's chain.)
+template <bool EXPAND>
 __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
     const int b = blockIdx.x, tid = threadIdx.x;
     // Row results of sequence b: rows b * seq_rows .. (the same block layout for the one-shot build and
@@ -643,21 +678,33 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
         et[j] = ti[e];
         el[j] = lse[e / DT_K_MAX];
     }
+    // what the level before has left, in the same trip
+    const int xl = EXPAND ? a.expand_level : 0;  // > 0: only the nodes of level xl that are expanded next
+    int2 head = make_int2(0, 0);
+    int carried = 0;
+    uint4 node = make_uint4(0, 0, 0, 0);
+    if (xl > CARRY_FROM) {
+        const int64_t at = carry_at(a.seq_rows, b);
+        head = *(const int2 *)(a.top_id + at);
+        carried = a.state_n_exp[b];
+        node = ((const uint4 *)(a.top_val + at))[tid & (DT_K_MAX - 1)];
+    }
     extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];  // 135 KB: more than a static array may hold
     TreeLds &S = *reinterpret_cast<TreeLds *>(s_dyn);
     static_assert(DT_P_MAX % 16 == 0 && offsetof(TreeLds, node) % 16 == 0 && offsetof(TreeLds, slot) % 16 == 0, "16-byte stores");
-    for (int i = tid; i < DT_P_MAX / 8; i += TREE_NT) ((uint4 *)S.node)[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
-    for (int i = tid; i < DT_P_MAX / 16; i += TREE_NT) ((uint4 *)S.slot)[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
-    if (tid < 256) S.hist[0][tid] = 0u;
-    if (tid < BUCKET_CAP) S.mem[tid] = 0ull;
-    if (tid == 0) S.memn = 0;
+    if constexpr (!EXPAND) {
+        for (int i = tid; i < DT_P_MAX / 8; i += TREE_NT) ((uint4 *)S.node)[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
+        for (int i = tid; i < DT_P_MAX / 16; i += TREE_NT) ((uint4 *)S.slot)[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
+        if (tid < 256) S.hist[0][tid] = 0u;
+        if (tid < BUCKET_CAP) S.mem[tid] = 0ull;
+        if (tid == 0) S.memn = 0;
+    }
     const dt_params prm = a.params[b];
     // one-shot build: rows past the span the sequence owns were never reduced; they count as rows
     // without a viable token (the level-at-a-time state has no such span: its rows arrive level by level)
     const int64_t span = a.row_off ? a.row_off[b + 1] - a.row_off[b] : (int64_t)DT_STATE_ROWS;
     const int TT = min(max(prm.TT, 1), a.TT_cap), d = min(max(prm.d, 1), DT_D_MAX);
     const int k = min(max(prm.k, 1), min(DT_K_MAX, a.V));
-    const int xl = a.expand_level;  // > 0: only the nodes of level xl that are expanded next
     const int64_t o = (int64_t)b * a.TT_cap;
 
     if (xl > 0 && (TT == 1 || xl >= d)) {  // nothing is drafted below level d
@@ -683,6 +730,14 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
     // produce pool index p is fixed by p alone (only its parent is decided later).
     // Entry (row, rank) with rank < k is candidate p = rank (row 0) or k + (row - 1) k + rank.
     const int R = xl > 0 ? 1 + (xl - 1) * k : 1 + (d - 1) * k;  // rows that hold candidates
+    Start from = {0, 0, 0};
+    if (xl > CARRY_FROM && __builtin_amdgcn_readfirstlane(head.x) == carry_tag(xl - 1))
+        from = {xl - 1, min(carried, k), __builtin_amdgcn_readfirstlane(head.y)};
+    if (from.level > 0 && tid < DT_K_MAX) {
+        if (tid >= from.n_exp) node.x = __float_as_uint(-INFINITY);
+        *(uint4 *)&S.par[from.level][tid] = node;
+    }
+    const int R0 = from.level > 0 ? 1 + (xl - 2) * k : 0;  // the first of them that is needed
     const int owned = (int)min(max(span, (int64_t)0), (int64_t)DT_STATE_ROWS);
     auto place = [&](int e, float v, int token, float row_lse) {
         const int row = e / DT_K_MAX, rank = e % DT_K_MAX;
@@ -705,7 +760,7 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
         int xt[MORE];
 #pragma unroll
         for (int j = 0; j < MORE; ++j)
-            if (j < more) {
+            if (j < more && (EARLY + j + 1) * TREE_NT > R0 * DT_K_MAX) {
                 const int e = min(tid + (EARLY + j) * TREE_NT, R * DT_K_MAX - 1);
                 xv[j] = tv[e];
                 xt[j] = ti[e];
@@ -713,7 +768,7 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
             }
 #pragma unroll
         for (int j = 0; j < MORE; ++j)
-            if (j < more) place(tid + (EARLY + j) * TREE_NT, xv[j], xt[j], xs[j]);
+            if (j < more && (EARLY + j + 1) * TREE_NT > R0 * DT_K_MAX) place(tid + (EARLY + j) * TREE_NT, xv[j], xt[j], xs[j]);
     }
     __syncthreads();
 
@@ -721,18 +776,18 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = lane_id();
     int p_end = 0;
     if (k > NARROW_K) {
-        p_end = k * k <= TREE_NT ? levels_wide<1>(a, S, b, k, d, TT) : levels_wide<2>(a, S, b, k, d, TT);
-        if (xl > 0) return;
+        p_end = k * k <= TREE_NT ? levels_wide<1, EXPAND>(a, S, b, k, d, TT, from) : levels_wide<2, EXPAND>(a, S, b, k, d, TT, from);
+        if constexpr (EXPAND) return;
         __syncthreads();  // the levels may have ended without one
     } else {
         if (w == 0) {
-            if (k <= 8) p_end = levels_narrow<1>(a, S, b, k, d, TT);
-            else if (k <= 11) p_end = levels_narrow<2>(a, S, b, k, d, TT);
-            else if (k <= 13) p_end = levels_narrow<3>(a, S, b, k, d, TT);  // four per lane: (96, 8, 12) 10.8 us, 10.4 so
-            else p_end = levels_narrow<4>(a, S, b, k, d, TT);
+            if (k <= 8) p_end = levels_narrow<1, EXPAND>(a, S, b, k, d, TT, from);
+            else if (k <= 11) p_end = levels_narrow<2, EXPAND>(a, S, b, k, d, TT, from);
+            else if (k <= 13) p_end = levels_narrow<3, EXPAND>(a, S, b, k, d, TT, from);  // four per lane: (96, 8, 12) 10.8 us, 10.4 so
+            else p_end = levels_narrow<4, EXPAND>(a, S, b, k, d, TT, from);
             if (lane == 0) S.p_end = p_end;
         }
-        if (xl > 0) return;
+        if constexpr (EXPAND) return;
         __syncthreads();
         p_end = S.p_end;
     }
@@ -871,12 +926,15 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
 
 // LDS beyond 64 KB has to be asked for, once per device (dt_init)
 hipError_t tree_init() {
-    return hipFuncSetAttribute((const void *)tree_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(TreeLds));
+    hipError_t e = hipFuncSetAttribute((const void *)tree_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(TreeLds));
+    if (e == hipSuccess)
+        e = hipFuncSetAttribute((const void *)tree_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(TreeLds));
+    return e;
 }
 
 hipError_t tree_launch(const TreeArgs &a, hipStream_t st) {
     if (a.batch <= 0) return hipSuccess;
-    launch_kernel(KID_TREE, st, tree_kernel, dim3(a.batch), dim3(TREE_NT), sizeof(TreeLds), a);
+    launch_kernel(KID_TREE, st, a.expand_level > 0 ? tree_kernel<true> : tree_kernel<false>, dim3(a.batch), dim3(TREE_NT), sizeof(TreeLds), a);
     return hipGetLastError();
 }
 

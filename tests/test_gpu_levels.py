@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 
-def drive(params, prefix_len, V, bf16, seed, flags=0):
+def drive(params, prefix_len, V, bf16, seed, flags=0, twice=False):
     import paper_2601_12212_amd as dt
     B = len(params)
     KR = max(p[2] for p in params)
@@ -51,8 +51,9 @@ def drive(params, prefix_len, V, bf16, seed, flags=0):
         dev = torch.from_numpy(logits).cuda()
         if bf16:
             dev = dev.to(torch.bfloat16)
-        dt.dt_expand_level(level, d_params, dev, KR, d_plen, TT_cap, state, n_exp, e_tok, e_par, e_row, e_pos, e_mask, ws,
-                           flags=flags)
+        for x in [dev.flip(-1), dev] if twice and level < min(p[1] for p in params) else [dev]:
+            dt.dt_expand_level(level, d_params, x.contiguous(), KR, d_plen, TT_cap, state, n_exp, e_tok, e_par, e_row, e_pos, e_mask,
+                               ws, flags=flags)
         torch.cuda.synchronize()
         for b in range(B):
             n = int(n_exp[b])
@@ -110,6 +111,15 @@ def test_level_by_level_with_the_token_count_exit():
 
 def test_level_by_level_bf16_wide_levels():
     drive([(96, 4, 16), (64, 3, 32), (40, 5, 6)], [11, 12, 13], V=4099, bf16=True, seed=2)
+
+
+@pytest.mark.parametrize("k", [2, 16, 17, 22, 23, 32])
+def test_level_by_level_to_the_deepest_level(k):
+    # each level starts from what the one before handed on, the last ones where the state's rows just leave room for it; and from the
+    # row results alone where a level is asked for a second time, with other logits
+    for d in (3, 4, 8):
+        drive([(100, d, k), (37, 8, max(2, k - 3))], [5, 0], V=300, bf16=False, seed=1)
+        drive([(100, d, k), (37, d, max(2, k - 3))], [5, 0], V=300, bf16=False, seed=1, twice=True)
 
 
 # vocabularies of both row paths: held by 1,024 threads with the log-sum-exps apart, two passes of one chunk to a workgroup;
