@@ -32,6 +32,7 @@ namespace dt {
 #define TREE_NW (TREE_NT / 64)    // its waves
 #define NARROW_K 16               // levels of at most NARROW_K^2 candidates: one wave
 #define LIST_CAP 1024             // most candidates that a thinning may leave
+#define CAND_CAP 512              // most candidates of a wide level that its bound may leave
 #define BUCKET_CAP 64             // most candidates of one score bucket that are ranked one against the other
 #define SHARE_MAX 15              // most candidates per thread of a pool, an odd number
 
@@ -89,6 +90,7 @@ struct TreeLds {
     u32 hist[4][256];              // one histogram per radix digit
     u32 best[TREE_NT];             // best key of every thread's share of a large pool
     u64 mem[BUCKET_CAP];           // (key, index) of the candidates in the bucket that holds the cut
+    Parent cand[CAND_CAP];         // candidates of a wide level above its bound, in pool order; `path`: their parents'
     float list_score[LIST_CAP];    // what a thinning leaves, in pool order
     int16_t list[LIST_CAP];
     int16_t sel[DT_TT_MAX];        // the kept candidates, in pool order
@@ -407,19 +409,30 @@ __device__ __forceinline__ int levels_narrow(const TreeArgs &a, TreeLds &S, int 
     return p_end;
 }
 
-// The k best of n candidates of level l, by one wave; index_at: their pool indices.
-template <int G, typename I>
-__device__ __forceinline__ int choose_wide(TreeLds &S, int l, int lo, int k, int n, u32 lo_key, u32 hi_key, const float *score,
-                                           I index_at) {
+// A bound close below the k best of a level: the best and second best children of k nodes (lane s: the best of slot s, lane 32 + s: the
+// second; rows descend) are candidates, so what k of those 64 keys lie above, at least k candidates do.  `lo` and `hi` as level_bounds has them.
+__device__ __forceinline__ u32 raise_bound(u32 key, int k, u32 lo, u32 hi) {
+    u32 width = hi - lo;
+    for (int step = 0; step < 7; ++step) {  // uniform
+        const u32 half = width >> 1, mid = lo + half;
+        const int c = __popcll(__builtin_amdgcn_ballot_w64(key > mid));
+        width -= half;
+        lo = c >= k ? mid : lo;
+        if (c == k) break;
+    }
+    return lo;
+}
+// The k best of n candidates of level l, by one wave; cand: one of them, with its parent's path.
+template <int G, typename C>
+__device__ __forceinline__ int choose_wide(TreeLds &S, int l, int k, int n, u32 lo_key, u32 hi_key, C cand) {
     const int lane = lane_id();
-    const PoolShape ps = pool_shape(k);
-    float sc[G];
+    Parent pr[G];
     u32 key[G];
     bool chosen[G];
 #pragma unroll
     for (int q = 0; q < G; ++q) {
-        sc[q] = score[min(lane + 64 * q, n - 1)];
-        key[q] = lane + 64 * q < n ? score_key(sc[q]) : 0u;
+        pr[q] = cand(min(lane + 64 * q, n - 1));
+        key[q] = lane + 64 * q < n ? score_key(pr[q].score) : 0u;
     }
     const int c = wave_select<G>(key, k, lo_key, hi_key, chosen);
     int before = 0;
@@ -427,10 +440,7 @@ __device__ __forceinline__ int choose_wide(TreeLds &S, int l, int lo, int k, int
     for (int q = 0; q < G; ++q) {
         const u64 m = __builtin_amdgcn_ballot_w64(chosen[q]);
         const int pos = (int)__builtin_amdgcn_mbcnt_hi((u32)(m >> 32), __builtin_amdgcn_mbcnt_lo((u32)m, (u32)before));
-        if (chosen[q]) {
-            const int index = index_at(lane + 64 * q);
-            put_parent(S, l, pos, sc[q], index, S.par[l - 1][fdiv(index - lo, ps.inv_k)].path);
-        }
+        if (chosen[q]) put_parent(S, l, pos, pr[q].score, pr[q].index, pr[q].path);
         before += __popcll(m);
     }
     return c;
@@ -458,7 +468,7 @@ __device__ __forceinline__ int levels_wide(const TreeArgs &a, TreeLds &S, int b,
         const int nlo = k + (l - 1) * kk;
         float first = -INFINITY, own[Q] = {};
         if (l != xl) {
-            first = S.lp[nlo + min(lane, k - 1) * k];
+            first = S.lp[nlo + min(lane & 31, k - 1) * k + (lane >> 5)];  // k > 1
 #pragma unroll
             for (int q = 0; q < Q; ++q) own[q] = S.lp[nlo + min(tid + TREE_NT * q, kk - 1)];
         }
@@ -467,14 +477,17 @@ __device__ __forceinline__ int levels_wide(const TreeArgs &a, TreeLds &S, int b,
             if (l == from.level) n = from.n_exp;
             else if (l == 1) n = choose_first(S, k, sc1);
             else if (c == 0) n = 0;
-            else if (c <= 128)
-                n = choose_wide<2>(S, l, lo, k, c, lo_key, hi_key, S.list_score, [&](int i) { return (int)S.list[i]; });
-            else if (c <= 256)
-                n = choose_wide<4>(S, l, lo, k, c, lo_key, hi_key, S.list_score, [&](int i) { return (int)S.list[i]; });
-            else if (c <= 512)
-                n = choose_wide<8>(S, l, lo, k, c, lo_key, hi_key, S.list_score, [&](int i) { return (int)S.list[i]; });
+            else if (c <= 64) n = choose_wide<1>(S, l, k, c, lo_key, hi_key, [&](int i) { return S.cand[i]; });
+            else if (c <= 128) n = choose_wide<2>(S, l, k, c, lo_key, hi_key, [&](int i) { return S.cand[i]; });
+            else if (c <= CAND_CAP) n = choose_wide<CAND_CAP / 64>(S, l, k, c, lo_key, hi_key, [&](int i) { return S.cand[i]; });
             else  // equal scores
-                n = choose_wide<16>(S, l, lo, k, kk, lo_key, hi_key, S.score + lo, [&](int i) { return lo + i; });
+                n = choose_wide<16>(S, l, k, kk, lo_key, hi_key, [&](int i) {
+                    Parent pr;
+                    pr.score = S.score[lo + i];
+                    pr.index = lo + i;
+                    pr.path = S.par[l - 1][fdiv(i, ps.inv_k)].path;
+                    return pr;
+                });
             if (lane >= n && lane < DT_K_MAX) S.par[l][lane].score = -INFINITY;
             if (lane == 0) S.n_exp = n;
             if (l == xl) emit_level(a, S, b, l, k, n, tok_count);
@@ -483,17 +496,23 @@ __device__ __forceinline__ int levels_wide(const TreeArgs &a, TreeLds &S, int b,
         __syncthreads();
         if (S.n_exp == 0) break;
         // every wave: the bound; Q candidates per thread scored; those above it into the list
-        const float f = S.par[l][min(lane, DT_K_MAX)].score + first;
-        float sc[Q];
+        const float f = S.par[l][(lane & 31) < k ? lane & 31 : DT_K_MAX].score + first;
+        Parent pr[Q];
         u32 key[Q];
 #pragma unroll
-        for (int q = 0; q < Q; ++q) sc[q] = S.par[l][parent[q]].score + own[q];
-        level_bounds(score_key(f), k, lo_key, hi_key);
+        for (int q = 0; q < Q; ++q) {
+            pr[q] = S.par[l][parent[q]];
+            pr[q].score += own[q];
+            pr[q].index = nlo + tid + TREE_NT * q;
+        }
+        const u32 fk = score_key(f);
+        level_bounds(fk, k, lo_key, hi_key);
+        lo_key = raise_bound(fk, k, lo_key, hi_key);
         u64 m[Q];
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
-            key[q] = score_key(sc[q]);
-            if (tid + TREE_NT * q < kk) S.score[nlo + tid + TREE_NT * q] = sc[q];
+            key[q] = score_key(pr[q].score);
+            if (tid + TREE_NT * q < kk) S.score[nlo + tid + TREE_NT * q] = pr[q].score;
             m[q] = __builtin_amdgcn_ballot_w64(key[q] > lo_key);
         }
         if (lane == 0) {
@@ -501,22 +520,18 @@ __device__ __forceinline__ int levels_wide(const TreeArgs &a, TreeLds &S, int b,
             S.wtot[TREE_NW + w] = Q == 2 ? __popcll(m[Q - 1]) : 0;
         }
         if (a.early_stop) {
-            tok_count += __syncthreads_count(sc[0] > -INFINITY);
-            if (Q == 2) tok_count += __syncthreads_count(sc[Q - 1] > -INFINITY);
+            tok_count += __syncthreads_count(pr[0].score > -INFINITY);
+            if (Q == 2) tok_count += __syncthreads_count(pr[Q - 1].score > -INFINITY);
         } else {
             __syncthreads();
         }
         const int wt = S.wtot[lane & (2 * TREE_NW - 1)], upto = wave_scan_incl_i32(wt);  // lanes 0 .. 15
         const int at[2] = {__builtin_amdgcn_readlane(upto - wt, w), __builtin_amdgcn_readlane(upto - wt, TREE_NW + w)};
         c = __builtin_amdgcn_readlane(upto, 2 * TREE_NW - 1);
-        if (c <= 512)
+        if (c <= CAND_CAP)
 #pragma unroll
             for (int q = 0; q < Q; ++q)
-                if (key[q] > lo_key) {
-                    const int i = at[q] + (int)lanes_below(m[q]);
-                    S.list_score[i] = sc[q];
-                    S.list[i] = (int16_t)(nlo + tid + TREE_NT * q);
-                }
+                if (key[q] > lo_key) S.cand[at[q] + (int)lanes_below(m[q])] = pr[q];
         __syncthreads();
         lo = nlo;
         p_end = nlo + kk;
