@@ -82,8 +82,12 @@ __device__ __forceinline__ bf16x8 lds_load128_at(u32 addr) {
     return v;
 }
 template <int N>
-__device__ __forceinline__ void lds_wait2(bf16x4 &lo, bf16x4 &hi) {
-    asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(lo), "+v"(hi) : "n"(N));
+__device__ __forceinline__ void lds_wait2(bf16x8 &a, bf16x8 &b) {
+    asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(a), "+v"(b) : "n"(N));
+}
+template <int N>
+__device__ __forceinline__ void lds_wait4(bf16x4 &a, bf16x4 &b, bf16x4 &c, bf16x4 &d) {
+    asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(a), "+v"(b), "+v"(c), "+v"(d) : "n"(N));
 }
 template <int OFF>
 __device__ __forceinline__ bf16x4 lds_load_tr4(u32 addr) {
@@ -122,7 +126,9 @@ __device__ __forceinline__ float half_swap_sum(float x) {
 #define ATT_ROWS_PER_WAVE 32
 #define ATT_WAVES 4
 #define ATT_MTILE (ATT_ROWS_PER_WAVE * ATT_WAVES)
-#define LAZY_LOG2 8.0f        // how far (in powers of two) a probability may exceed 1 before the reference maximum moves
+#define NEAR_LIMIT 0x1p8f     // sums of probabilities that cannot hurt, and
+#define REF_LIMIT 0x1p64f     // that send a key range of the large-batch kernel through a second time
+#define LAZY_LOG2 8.0f        // how far (in powers of two) a probability may exceed 1 before a reference that moves does
 
 // 32-bit visibility window of one query over keys t0 .. t0+31, where off = t0 - L (uniform): the
 // prefix keys (negative positions) are visible, tree key j is visible iff bit j of the node's
@@ -317,15 +323,18 @@ static GroupDiv group_div(int G) { return {G, (u32)(((u64)1 << 32) / G + 1)}; }
 // Rows m0 .. m0+127 of (sequence b, kv head h) against key blocks kb0 .. kb1-1 of that sequence.
 // Called by all 256 threads of the workgroup; ends behind a barrier, so calls can follow each other.
 template <int D>
-__device__ __forceinline__ void tile_segment(const AttnArgs &a, const GroupDiv &gd, const SeqWords &sq, unsigned char *s_dyn, int h,
-                                             int b, int m0, int rot, int kb0, int kb1, const TileParts &pt, int slots, bool stay) {
+__device__ __forceinline__ bool tile_segment(const AttnArgs &a, const GroupDiv &gd, const SeqWords &sq, unsigned char *s_dyn, int h,
+                                             int b, int m0, int rot, int kb0, int kb1, const TileParts &pt, int slots, bool stay, bool exact) {
     static_assert(D == 128, "head dim");
     constexpr int KSTEPS = D / 16, DBLK = D / 32;
-    const int G = gd.G, N = sq.N, L = sq.L;
+    int G = gd.G, N = sq.N, L = sq.L;
+    asm volatile("" : "+s"(G), "+s"(N), "+s"(L));
     const int M = N * G;
     const int Tk = L + N;
 
-    const int tid = threadIdx.x, lane = tid & 63;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid), "+s"(h), "+s"(b), "+s"(m0));  // what follows from these is worked out here, not kept in registers from segment to segment
+    const int lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, col = lane & 31;
     // Wave w works on rows 32 rb .. of the tile.  Waves past the last row only help with the loads; `rot` spreads them over
@@ -411,11 +420,14 @@ __device__ __forceinline__ void tile_segment(const AttnArgs &a, const GroupDiv &
             for (int i = 0; i < 16; ++i) S.v[j][i] = ((vis >> (8 * (i >> 2) + (i & 3))) & 1u) ? S.v[j][i] : -INFINITY;
         }
     };
-    // m_run is a reference, not the exact running maximum: it moves only when a block's maximum
-    // lies more than LAZY_LOG2 binary orders above it.  Until then probabilities may reach
-    // 2^LAZY_LOG2 instead of 1 (harmless in fp32 sums and in bf16's relative precision) and the 64
-    // multiplies that rescale the output accumulators are not spent: with unit-variance keys the
-    // reference settles on the first block.  (-inf - -inf is NaN: a fully hidden block moves nothing.)
+    // m_run is a reference, not the running maximum: the maximum of the range's first block, and it stays (0 where that block is
+    // hidden).  Later scores may lie above it, and their probabilities above 1, which neither 32-bit sums nor bf16's relative precision
+    // mind as long as everything stays a number: sums of a lane's probabilities up to NEAR_LIMIT cannot hurt; above that the range's accumulators are
+    // looked at when it ends, and past REF_LIMIT, or if one of them is not finite, the workgroup goes through the range once more (`exact`).  Then the
+    // reference moves when a block's maximum lies more than LAZY_LOG2 binary orders above it, so that probabilities stay below 2^LAZY_LOG2,
+    // at the price of a maximum over every block and, when it moves, of 64 multiplies.  A maximum in every block, in the shadow of
+    // the second product, cost a lone workgroup of a compute unit 0.1 us of 0.95 a block, four sequences of a 70B step 3.4 % of their attention.
+    // (-inf - -inf is NaN: a fully hidden block moves nothing.)
     float nmc = 0.f;
     auto move_reference = [&](float mloc) {
         mloc = half_swap_max(mloc);
@@ -426,7 +438,7 @@ __device__ __forceinline__ void tile_segment(const AttnArgs &a, const GroupDiv &
         nmc = -m_use * c;
         l_run *= alpha;
         m_run = m_new;
-        if (__ballot(alpha != 1.0f)) {  // the reference moved for some query of this wave
+        if (__builtin_expect(__ballot(alpha != 1.0f) != 0, 0)) {  // the reference moved for some query of this wave
 #pragma unroll
             for (int db = 0; db < DBLK; ++db)
 #pragma unroll
@@ -434,23 +446,52 @@ __device__ __forceinline__ void tile_segment(const AttnArgs &a, const GroupDiv &
         }
     };
 
+    // (as instructions: fmaxf on MFMA results costs two more per pair to quiet NaNs)
+    auto block_max = [](const Scores &S) {
+        asm volatile("s_nop 15\n\ts_nop 3");  // the distance from the last MFMA, which the compiler does not keep for what it does not know
+        float m = -INFINITY, m1 = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < 16; i += 2) {
+            asm volatile("v_max3_f32 %0, %0, %1, %2" : "+v"(m) : "v"(S.v[0][i]), "v"(S.v[0][i + 1]));
+            asm volatile("v_max3_f32 %0, %0, %1, %2" : "+v"(m1) : "v"(S.v[1][i]), "v"(S.v[1][i + 1]));
+        }
+        return fmaxf(m, m1);
+    };
+    __shared__ int s_again;
+    auto sums_fine = [&]() {  // uniform
+        if (!__builtin_amdgcn_ballot_w64(!(l_run <= NEAR_LIMIT))) return true;
+        asm volatile("s_nop 15\n\ts_nop 3");  // as above
+        float top[DBLK];
+#pragma unroll
+        for (int db = 0; db < DBLK; ++db) {
+            top[db] = 0.f;
+#pragma unroll
+            for (int i = 0; i < 16; i += 2)
+                asm volatile("v_maximum3_f32 %0, %0, |%1|, |%2|" : "+v"(top[db]) : "v"(oacc[db][i]), "v"(oacc[db][i + 1]));
+        }
+        asm volatile("v_maximum3_f32 %0, %0, %1, %2" : "+v"(top[0]) : "v"(top[1]), "v"(top[2]));
+        const bool fine = l_run <= REF_LIMIT && top[0] < INFINITY && top[3] < INFINITY;  // false for a NaN
+        return !__builtin_amdgcn_ballot_w64(!fine);
+    };
     // One block: O += V(kb)^T P(kb)^T, and under it the scores of block kb + 1.  A wave that runs S^T, softmax and O^T of
     // the same block one after the other leaves the matrix pipe idle during its softmax and the vector pipe during its
     // MFMAs, and two such waves on a SIMD fall into step.  Here the two products of different blocks are independent of
     // the softmax arithmetic between them, so every MFMA is followed by a few vector instructions of the other block, which
     // issue while it runs:
-    //   MFMA s of K(kb + 1) Q^T:  exponentials of block kb (20 of a lane's 32)
-    //   MFMA n of V(kb)^T P^T:    the other 12, then the maximum of block kb + 1
+    //   MFMA s of K(kb + 1) Q^T:  exponentials of block kb (16 of a lane's 32)
+    //   MFMA n of V(kb)^T P^T:    the other 16, in time for the MFMA that takes them
+    // What bounds a wave that has its SIMD to itself is the bytes of its instructions (some eight cycles for eight of them), and two to
+    // a SIMD the power that the chip may draw (it clocks at 1.7 to 1.9 GHz then) and the loads into LDS: without them, for timing, a layer of the
+    // 70B step takes 103 us instead of 121, without the exponentials 118, without the waits for the loads 121.
     // All LDS operand reads are bare instructions with hand-kept waits, eight K reads or seven V read pairs ahead of their
     // MFMA (V pairs start behind the last K reads).  P: CUR is the stage of V(kb); K(kb + 1) is in stage CUR ^ 1.
     // EXP_A(e), EXP_B(e): elements 2e and 2e + 1 of the lane's 32 (element i of S[j] is 16 j + i).  The multiply-add as an
     // instruction and the empty asm statements keep each of them where it is written: left alone, the compiler gathers the
     // multiply-adds in front of all MFMAs and the conversions behind them.
 #define PIN(x) asm volatile("" : "+v"(x));
-    // Behind a statement of this kind whose result the very next instruction reads, the compiler puts an s_nop.  So multiply-add and
-    // exponential are one statement, two maxima in a row as well, and a wait for an operand stands in front of the vector work of the
-    // MFMA before its own: 54 of some 400 instructions of a block fewer (four sequences of a 70B step 121.9 -> 121.0 us, eight long
-    // sequences, four layers 482 -> 479).
+    // Behind a statement of this kind whose result one of the next two instructions reads, the compiler puts an s_nop.  So multiply-add and
+    // exponential are one statement, and one wait releases the operands of two MFMAs, in front of the vector work of the MFMA before them.
+    // A block of a lone workgroup, with the maxima left out as well: 0.95 -> 0.83 us.
 #define SCALED_EXP(p, e)                                                                                      \
         asm volatile("v_fma_f32 %0, %1, %2, %3\n\tv_exp_f32 %0, %0" : "=v"(p) : "v"(S.v[(e) >> 4][(e) & 15]), "v"(c), "v"(nmc));
 #define EXP_A(e) SCALED_EXP(pe, 2 * (e))
@@ -466,28 +507,20 @@ __device__ __forceinline__ void tile_segment(const AttnArgs &a, const GroupDiv &
         }
 #define K_READ(i) ka[i] = lds_load128_at<(CUR ^ 1) * TILE_BYTES + ((i) >> 2) * SUB_BYTES + ((i) & 1) * 32 * 64>(koff[((i) >> 1) & 1]);
 #define K_WAIT(i, W) lds_wait<W>(ka[i]);
+#define K_WAIT2(i, W) lds_wait2<W>(ka[i], ka[(i) + 1]);
 #define QK_MFMA(i)                                                                                            \
         T.v[(i) & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[i], qreg[(i) >> 1], (i) < 2 ? zero16 : T.v[(i) & 1], 0, 0, 0); \
         __builtin_amdgcn_sched_barrier(0);
 #define V_READ(n)                                                                                             \
         vlo[n] = lds_load_tr4<(2 + CUR) * TILE_BYTES + ((n) & 3) * SUB_BYTES + 16 * ((n) >> 2) * 64>(voff);         \
         vhi[n] = lds_load_tr4<(2 + CUR) * TILE_BYTES + ((n) & 3) * SUB_BYTES + (16 * ((n) >> 2) + 8) * 64>(voff);
-#define V_WAIT(n, W) lds_wait2<W>(vlo[n], vhi[n]);
+#define V_WAIT2(n, W) lds_wait4<W>(vlo[n], vhi[n], vlo[(n) + 1], vhi[(n) + 1]);
 #define PV_MFMA(n)                                                                                            \
         oacc[(n) & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(                                               \
             __builtin_shufflevector(vlo[n], vhi[n], 0, 1, 2, 3, 4, 5, 6, 7), p_operand(&pw[4 * ((n) >> 2)]),   \
             oacc[(n) & 3], 0, 0, 0);                                                                           \
         __builtin_amdgcn_sched_barrier(0);
 #define FENCE __builtin_amdgcn_sched_barrier(0);
-    // (an instruction of its own: fmaxf on MFMA results costs two more per pair to quiet NaNs.  The scores were finished by
-    // MFMAs at least three MFMAs back, longer than the distance the hardware asks for before a vector read.)
-#define MAX2(i)                                                                                               \
-        asm volatile("v_max3_f32 %0, %0, %1, %2" : "+v"(mloc) : "v"(T.v[(i) >> 3][(2 * (i)) & 15]), "v"(T.v[(i) >> 3][(2 * (i) + 1) & 15]));
-#define MAX4(i)                                                                                               \
-        asm volatile("v_max3_f32 %0, %0, %1, %2\n\tv_max3_f32 %0, %0, %3, %4"                                  \
-                     : "+v"(mloc)                                                                              \
-                     : "v"(T.v[(i) >> 3][(2 * (i)) & 15]), "v"(T.v[(i) >> 3][(2 * (i) + 1) & 15]),             \
-                       "v"(T.v[(i) >> 3][(2 * (i) + 2) & 15]), "v"(T.v[(i) >> 3][(2 * (i) + 3) & 15]));
     auto p_operand = [](const u32 *wd) {
         const uint4 v = make_uint4(wd[0], wd[1], wd[2], wd[3]);
         return __builtin_bit_cast(bf16x8, v);
@@ -504,48 +537,48 @@ __device__ __forceinline__ void tile_segment(const AttnArgs &a, const GroupDiv &
             if (next) {
                 bf16x8 ka[16];  // read i: k-step i / 2, half i % 2
                 K_READ(0) K_READ(1) K_READ(2) K_READ(3) K_READ(4) K_READ(5) K_READ(6) K_READ(7) FENCE
-                K_WAIT(0, 7) EXP_A(0) FENCE
-                QK_MFMA(0) K_READ(8) K_WAIT(1, 7) EXP_B(0) FENCE
-                QK_MFMA(1) K_READ(9) K_WAIT(2, 7) EXP_A(1) FENCE
-                QK_MFMA(2) K_READ(10) K_WAIT(3, 7) EXP_B(1) FENCE
-                QK_MFMA(3) K_READ(11) K_WAIT(4, 7) EXP_A(2) FENCE
-                QK_MFMA(4) K_READ(12) K_WAIT(5, 7) EXP_B(2) FENCE
-                QK_MFMA(5) K_READ(13) K_WAIT(6, 7) EXP_A(3) FENCE
-                QK_MFMA(6) K_READ(14) K_WAIT(7, 7) EXP_B(3) FENCE
-                QK_MFMA(7) K_READ(15) K_WAIT(8, 7) EXP_A(4) FENCE
-                QK_MFMA(8) V_READ(0) K_WAIT(9, 8) EXP_B(4) FENCE
-                QK_MFMA(9) V_READ(1) K_WAIT(10, 9) EXP_A(5) FENCE
-                QK_MFMA(10) V_READ(2) K_WAIT(11, 10) EXP_B(5) FENCE
-                QK_MFMA(11) V_READ(3) K_WAIT(12, 11) EXP_A(6) FENCE
-                QK_MFMA(12) V_READ(4) K_WAIT(13, 12) EXP_B(6) EXP_A(7) FENCE
-                QK_MFMA(13) V_READ(5) K_WAIT(14, 13) EXP_B(7) EXP_A(8) FENCE
-                QK_MFMA(14) V_READ(6) K_WAIT(15, 14) EXP_B(8) EXP_A(9) FENCE
-                QK_MFMA(15) EXP_B(9) FENCE
+                K_WAIT2(0, 6) FENCE
+                QK_MFMA(0) K_READ(8) K_WAIT2(2, 5) EXP_A(0) FENCE
+                QK_MFMA(1) K_READ(9) EXP_B(0) FENCE
+                QK_MFMA(2) K_READ(10) K_WAIT2(4, 5) EXP_A(1) FENCE
+                QK_MFMA(3) K_READ(11) EXP_B(1) FENCE
+                QK_MFMA(4) K_READ(12) K_WAIT2(6, 5) EXP_A(2) FENCE
+                QK_MFMA(5) K_READ(13) EXP_B(2) FENCE
+                QK_MFMA(6) K_READ(14) K_WAIT2(8, 5) EXP_A(3) FENCE
+                QK_MFMA(7) K_READ(15) EXP_B(3) FENCE
+                QK_MFMA(8) V_READ(0) K_WAIT2(10, 6) EXP_A(4) FENCE
+                QK_MFMA(9) V_READ(1) EXP_B(4) FENCE
+                QK_MFMA(10) V_READ(2) K_WAIT2(12, 8) EXP_A(5) FENCE
+                QK_MFMA(11) V_READ(3) EXP_B(5) FENCE
+                QK_MFMA(12) V_READ(4) K_WAIT2(14, 10) EXP_A(6) FENCE
+                QK_MFMA(13) V_READ(5) EXP_B(6) FENCE
+                QK_MFMA(14) V_READ(6) V_WAIT2(0, 10) EXP_A(7) FENCE
+                QK_MFMA(15) EXP_B(7) FENCE
             } else {
                 V_READ(0) V_READ(1) V_READ(2) V_READ(3) V_READ(4) V_READ(5) V_READ(6) FENCE
-                EXP_A(0) EXP_B(0) EXP_A(1) EXP_B(1) EXP_A(2) EXP_B(2) EXP_A(3) EXP_B(3) EXP_A(4) EXP_B(4)
-                EXP_A(5) EXP_B(5) EXP_A(6) EXP_B(6) EXP_A(7) EXP_B(7) EXP_A(8) EXP_B(8) EXP_A(9) EXP_B(9) FENCE
+                EXP_A(0) EXP_B(0) EXP_A(1) EXP_B(1) EXP_A(2) EXP_B(2) EXP_A(3) EXP_B(3)
+                EXP_A(4) EXP_B(4) EXP_A(5) EXP_B(5) EXP_A(6) EXP_B(6) V_WAIT2(0, 10) EXP_A(7) EXP_B(7) FENCE
             }
-            V_WAIT(0, 12) PV_MFMA(0) V_READ(7) V_WAIT(1, 12) EXP_A(10) FENCE
-            PV_MFMA(1) V_READ(8) EXP_B(10) FENCE
+            PV_MFMA(0) V_READ(7) V_WAIT2(2, 8) EXP_A(8) FENCE
+            PV_MFMA(1) V_READ(8) EXP_B(8) FENCE
             if (next) mask(kb + 1, T);
-            float mloc = -INFINITY;
-            V_WAIT(2, 12) PV_MFMA(2) V_READ(9) V_WAIT(3, 12) EXP_A(11) MAX2(0) FENCE
-            PV_MFMA(3) V_READ(10) V_WAIT(4, 12) EXP_B(11) MAX2(1) FENCE
-            PV_MFMA(4) V_READ(11) V_WAIT(5, 12) EXP_A(12) MAX2(2) FENCE
-            PV_MFMA(5) V_READ(12) V_WAIT(6, 12) EXP_B(12) MAX2(3) FENCE
-            PV_MFMA(6) V_READ(13) V_WAIT(7, 12) EXP_A(13) MAX2(4) FENCE
-            PV_MFMA(7) V_READ(14) V_WAIT(8, 12) EXP_B(13) MAX2(5) FENCE
-            PV_MFMA(8) V_READ(15) V_WAIT(9, 12) EXP_A(14) MAX2(6) FENCE
-            PV_MFMA(9) V_WAIT(10, 10) EXP_B(14) MAX2(7) FENCE
-            PV_MFMA(10) V_WAIT(11, 8) EXP_A(15) MAX2(8) FENCE
-            PV_MFMA(11) V_WAIT(12, 6) EXP_B(15) MAX2(9) FENCE
-            PV_MFMA(12) V_WAIT(13, 4) MAX4(10) FENCE
-            PV_MFMA(13) V_WAIT(14, 2) MAX4(12) FENCE
-            PV_MFMA(14) V_WAIT(15, 0) MAX4(14) FENCE
+            PV_MFMA(2) V_READ(9) V_WAIT2(4, 8) EXP_A(9) FENCE
+            PV_MFMA(3) V_READ(10) EXP_B(9) EXP_A(10) FENCE
+            PV_MFMA(4) V_READ(11) V_WAIT2(6, 8) EXP_B(10) FENCE
+            PV_MFMA(5) V_READ(12) EXP_A(11) FENCE
+            PV_MFMA(6) V_READ(13) V_WAIT2(8, 8) EXP_B(11) EXP_A(12) FENCE
+            PV_MFMA(7) V_READ(14) EXP_B(12) FENCE
+            PV_MFMA(8) V_READ(15) V_WAIT2(10, 8) EXP_A(13) FENCE
+            PV_MFMA(9) EXP_B(13) EXP_A(14) FENCE
+            PV_MFMA(10) V_WAIT2(12, 4) EXP_B(14) EXP_A(15) FENCE
+            PV_MFMA(11) EXP_B(15) FENCE
+            PV_MFMA(12) V_WAIT2(14, 0) FENCE
+            PV_MFMA(13) FENCE
+            PV_MFMA(14) FENCE
             PV_MFMA(15)
             l_run += psum0 + psum1;
-            if (next) move_reference(mloc);
+            if (__builtin_expect(exact && next, 0)) move_reference(block_max(T));
+            if (!next && !exact && !sums_fine() && lane == 0) s_again = 1;
             // the "memory" clobber keeps the next block's loads into these stages behind this block's reads
             asm volatile("" ::: "memory");
         }
@@ -563,6 +596,7 @@ __device__ __forceinline__ void tile_segment(const AttnArgs &a, const GroupDiv &
     if (kb0 + 1 < kb1) fetch_k(kb0 + 1, 1);
     __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's part of the tiles is in LDS
     __syncthreads();
+    if (tid == 0) s_again = 0;  // every wave has read the segment before's
     if (active) {  // scores of the first block
         constexpr int CUR = 1;
         Scores &T = S0;
@@ -577,12 +611,8 @@ __device__ __forceinline__ void tile_segment(const AttnArgs &a, const GroupDiv &
         K_WAIT(12, 3) QK_MFMA(12) FENCE K_WAIT(13, 2) QK_MFMA(13) FENCE
         K_WAIT(14, 1) QK_MFMA(14) FENCE K_WAIT(15, 0) QK_MFMA(15)
         mask(kb0, S0);
-        float mloc = -INFINITY;
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) mloc = fmaxf(mloc, S0.v[j][i]);
-        move_reference(mloc);
+        move_reference(block_max(S0));
+        if (!exact && m_run == -INFINITY) m_run = 0.f;  // what nmc says
         asm volatile("" ::: "memory");
     }
     __syncthreads();  // K stage 0 is free
@@ -597,19 +627,19 @@ __device__ __forceinline__ void tile_segment(const AttnArgs &a, const GroupDiv &
         if (odd_slot) __builtin_amdgcn_s_setprio(0);
         if (kb + 1 < kb1) block(std::integral_constant<int, 1>(), kb + 1, S1, S0);
     }
+    if (__builtin_expect(s_again, 0)) return true;
 #undef PIN
 #undef SCALED_EXP
 #undef EXP_A
 #undef EXP_B
 #undef K_READ
 #undef K_WAIT
+#undef K_WAIT2
 #undef QK_MFMA
 #undef V_READ
-#undef V_WAIT
+#undef V_WAIT2
 #undef PV_MFMA
 #undef FENCE
-#undef MAX2
-#undef MAX4
 
     // ---- epilogue -------------------------------------------------------------------------------
     float l_tot = half_swap_sum(l_run);
@@ -646,11 +676,11 @@ __device__ __forceinline__ void tile_segment(const AttnArgs &a, const GroupDiv &
                 sm.m0 = m0; sm.rb = rb; sm.M = M; sm.G = G; sm.Hq = a.Hq;
                 sm.c = c;
                 merge_shared<D>(sm);
-                return;
+                return false;
             }
             if (tid == 0) s_last[1] = arrive_last(pt.count, pt.tag, pt.parts, seen);
             __syncthreads();
-            if (!s_last[1]) return;
+            if (!s_last[1]) return false;
         } else if (tid == 0) {
             put_agent(pt.count, 0);
         }
@@ -696,7 +726,7 @@ __device__ __forceinline__ void tile_segment(const AttnArgs &a, const GroupDiv &
             for (int db = 0; db < DBLK; ++db) oacc[db] = acc[db];
         }
     }
-    if (!qvalid) return;
+    if (!qvalid) return false;
     const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
     int h4 = 4 * half;
     asm volatile("" : "+v"(h4));  // as above
@@ -710,6 +740,7 @@ __device__ __forceinline__ void tile_segment(const AttnArgs &a, const GroupDiv &
             for (int e = 0; e < 4; ++e) o4[e] = (__bf16)(oacc[db][q * 4 + e] * inv);
             *(bf16x4 *)(op + 32 * db + 8 * q) = o4;
         }
+    return false;
 }
 
 // One workgroup per (kv head, row tile, sequence), the whole key range: for short sequences, and for batches that the balanced
@@ -729,7 +760,8 @@ __global__ __launch_bounds__(256, 2) void attn_tile_kernel(AttnArgs a, GroupDiv 
     const int nb = (sq.L + sq.N + TILE_KEYS - 1) / TILE_KEYS;
     TileParts whole = {};
     whole.parts = 1;
-    tile_segment<D>(a, gd, sq, s_dyn, h, b, m0, blockIdx.y + blockIdx.z, 0, nb, whole, 0, false);
+    bool exact = false;
+    while (tile_segment<D>(a, gd, sq, s_dyn, h, b, m0, blockIdx.y + blockIdx.z, 0, nb, whole, 0, false, exact)) exact = true;
 }
 
 // ---- balanced schedule -----------------------------------------------------------------------------
@@ -879,9 +911,9 @@ __global__ __launch_bounds__(256, 2) void attn_gang_kernel(AttnArgs a, GroupDiv 
     s_seq[lane].w = mine;
     s_seq[lane].cs = cs;
     s_seq[lane].nb = val;
+    bool exact = false;
     while (segs) {
         const int b = (int)__builtin_ctzll(segs);
-        segs &= segs - 1;
         asm volatile("" ::: "memory");
         const int csb = __builtin_amdgcn_readfirstlane(s_seq[b].cs), nbb = __builtin_amdgcn_readfirstlane(s_seq[b].nb);
         const SeqWords sq = {__builtin_amdgcn_readfirstlane(s_seq[b].w.N), __builtin_amdgcn_readfirstlane(s_seq[b].w.L),
@@ -898,7 +930,8 @@ __global__ __launch_bounds__(256, 2) void attn_gang_kernel(AttnArgs a, GroupDiv 
         pt.ml = part.ml;
         pt.count = part.count + pt.slot;
         pt.tag = part.tag;
-        tile_segment<D>(a, gd, sq, s_dyn, h, b, tile * ATT_MTILE, j, kb0, kb1, pt, a.Hkv * P, !segs);
+        exact = tile_segment<D>(a, gd, sq, s_dyn, h, b, tile * ATT_MTILE, j, kb0, kb1, pt, a.Hkv * P, !(segs & (segs - 1)), exact);
+        if (!exact) segs &= segs - 1;
     }
 }
 

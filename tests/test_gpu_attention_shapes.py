@@ -286,3 +286,62 @@ def test_shared_merge_of_a_dozen_to_thirty_parts():
 @pytest.mark.parametrize("B,L", [(32, 1248), (33, 100), (33, 1248), (33, 1249)])
 def test_lines_between_the_three_kernels(B, L):
     check_case(oracle_case(0, cfg=_cfg("bf16", 128, [(32, 5, 6)] * B, [L] + [7 + 40 * (b % 3) for b in range(1, B)], 8, 8)))
+
+
+# Shapes of the kernel of whole tiles, and of the balanced schedule with sequences whole and cut.
+FAR = {"whole tiles": (8, 8, [60, 300, 700] + [10] * 30), "schedule, whole": (8, 8, [1250, 300, 700] + [10] * 30),
+       "schedule, cut": (64, 8, [1700, 1700, 1500, 1600])}
+
+
+@pytest.mark.parametrize("top", [12.0, 60.0])
+@pytest.mark.parametrize("shape", list(FAR))
+def test_scores_far_above_those_of_the_first_block(shape, top):
+    # The softmax reference is that of a range's first block; ranges whose sums come near the end of the exponents are gone through again with a
+    # reference that moves.  Scores that climb by some 100 and 600 powers of two along the keys, of one sequence only in the even heads
+    Hq, Hkv, plen = FAR[shape]
+    cfg = _cfg("bf16", 128, [(40, 4, 6)] * len(plen), plen, Hq, Hkv)
+    case = oracle_case(0, cfg=cfg)
+    st = make_step(case)
+    st.build_tree()
+    for b in range(4):
+        q, kt, vt, kp, vp = (dt_synth.as_f32(x).copy() for x in dt_synth.qkv(cfg, b))
+        N, L = case.trees[b]["n_nodes"], kp.shape[0]
+        q[:] = np.abs(q)
+        ramp = np.linspace(0.05, top, L + N, dtype=np.float32)[:, None, None]
+        heads = slice(0, None, 2) if b == 1 else slice(None)
+        kp[:, heads] = np.abs(kp[:, heads]) * ramp[:L]
+        kt[:N, heads] = np.abs(kt[:N, heads]) * ramp[L:]
+        ops = [dt_synth.f32_to_bf16_bits(x) for x in (q, kt, vt, kp, vp)]
+        st.set_qkv(b, *ops)
+        st.tree_attention()
+        want = ref.tree_attention(ops[0][:N], ops[1][:N], ops[2][:N], ops[3], ops[4], case.trees[b]["anc_mask"], st.scale)
+        # nearly all weight on one or two keys with |v| up to 4.5: the rounding of the probabilities, 2^-9, alone is worth 9e-3
+        assert_attention(st.attention_out(b), want, "bf16", "%s seq %d" % (shape, b), own_abs=1e-2)
+
+
+@pytest.mark.parametrize("shape", list(FAR))
+def test_values_near_the_end_of_the_exponents(shape):
+    # finite values of 1e35 under probabilities that leave their sums finite stay finite, an infinity shows in its column and nowhere else
+    Hq, Hkv, plen = FAR[shape]
+    cfg = _cfg("bf16", 128, [(40, 4, 6)] * len(plen), plen, Hq, Hkv)
+    case = oracle_case(0, cfg=cfg)
+    st = make_step(case)
+    st.build_tree()
+    st.tree_attention()
+    n = case.trees[0]["n_nodes"]
+    clean = st.out[0, :n].float()
+    L = plen[0]
+    for value, t in ((1e35, 0), (1e35, L - 1), (float("inf"), 0), (float("inf"), L - 1), (float("nan"), L // 2)):
+        keep = st.v_prefix[0][t].clone()
+        st.v_prefix[0][t, :, 5] = value
+        st.tree_attention()
+        got = st.out[0, :n].float()
+        column = got[:, :, 5]
+        if value == 1e35:
+            assert bool((torch.isfinite(column) & (column > 0)).all()), (value, t)
+        else:
+            assert bool((torch.isposinf(column) if value == float("inf") else torch.isnan(column)).all()), (value, t)
+        others = [c for c in range(128) if c != 5]
+        # one bf16 ulp of the result: a range gone through again has another reference
+        assert bool(((got - clean)[:, :, others].abs() <= clean[:, :, others].abs() * 2.0 ** -7 + 1e-6).all()), (value, t)
+        st.v_prefix[0][t] = keep
