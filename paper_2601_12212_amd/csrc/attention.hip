@@ -369,9 +369,9 @@ __device__ __forceinline__ bool tile_segment(const AttnArgs &a, const GroupDiv &
     // Every load is unconditional.  Keys past the end are read from the last valid row; their
     // scores are masked to -inf below, so their probabilities are exactly 0 and the duplicated V
     // rows contribute nothing.
-    auto fetch = [&](int kb, u32 tile, gbf16p pre, gbf16p tree, u32 poff, int chunk) {
+    auto fetch = [&](auto inside, int kb, u32 tile, gbf16p pre, gbf16p tree, u32 poff, int chunk) __attribute__((always_inline)) {
         const ldsp dst = (ldsp)s_dyn + tile + w * 1024;
-        if (small_stride && kb * TILE_KEYS + TILE_KEYS <= L) {  // block inside the prefix (uniform test)
+        if (decltype(inside)::value || (small_stride && kb * TILE_KEYS + TILE_KEYS <= L)) {  // block inside the prefix (uniform test)
             const u32 dl = (u32)(uintptr_t)dst;
             const gbytep base = (gbytep)(pre + (int64_t)kb * TILE_KEYS * stok);
             load4_to_lds16<SUB_BYTES>(base, poff, dl);
@@ -383,8 +383,9 @@ __device__ __forceinline__ bool tile_segment(const AttnArgs &a, const GroupDiv &
                 __builtin_amdgcn_global_load_lds((gbytep)(src + 32 * i), dst + i * SUB_BYTES, 16, 0, 0);
         }
     };
-    auto fetch_k = [&](int kb, int stage) { fetch(kb, stage * TILE_BYTES, kpre, ktree, koffp, kchunk); };
-    auto fetch_v = [&](int kb, int stage) { fetch(kb, 2 * TILE_BYTES + stage * TILE_BYTES, vpre, vtree, voffp, vchunk); };
+    const std::false_type anywhere;
+    auto fetch_k = [&](auto inside, int kb, int stage) { fetch(inside, kb, stage * TILE_BYTES, kpre, ktree, koffp, kchunk); };
+    auto fetch_v = [&](auto inside, int kb, int stage) { fetch(inside, kb, 2 * TILE_BYTES + stage * TILE_BYTES, vpre, vtree, voffp, vchunk); };
 
     // Operand read addresses; everything but the lane's own part is an immediate offset.
     // K, A operand of S^T: lane (col, half), k-step s reads chunk 2s + half of row 32 j + col: sub-tile s / 2, chunk
@@ -525,12 +526,15 @@ __device__ __forceinline__ bool tile_segment(const AttnArgs &a, const GroupDiv &
         const uint4 v = make_uint4(wd[0], wd[1], wd[2], wd[3]);
         return __builtin_bit_cast(bf16x8, v);
     };
-    auto block = [&](auto cur_c, int kb, Scores &S, Scores &T) {
+    // inside: blocks kb + 1 and kb + 2 are there and hold prefix keys only, and nothing else is to be asked either: no branches
+    // (some fifteen in a block; taken ones cost a lone wave up to twenty cycles).
+    auto block = [&](auto cur_c, auto inside, int kb, Scores &S, Scores &T) {
         constexpr int CUR = decltype(cur_c)::value;
-        const bool next = kb + 1 < kb1;  // uniform
-        if (kb + 2 < kb1) fetch_k(kb + 2, CUR);      // K(kb) was last read before the previous barrier,
-        if (next) fetch_v(kb + 1, CUR ^ 1);          // V(kb - 1) too
-        if (active) {
+        constexpr bool IN = decltype(inside)::value;
+        const bool next = IN || kb + 1 < kb1;  // uniform
+        if (IN || kb + 2 < kb1) fetch_k(inside, kb + 2, CUR);  // K(kb) was last read before the previous barrier,
+        if (next) fetch_v(inside, kb + 1, CUR ^ 1);            // V(kb - 1) too
+        if (IN || active) {
             float psum0 = 0.f, psum1 = 0.f, pe;
             u32 pw[16];  // the probabilities as pairs of bf16
             bf16x4 vlo[16], vhi[16];
@@ -561,7 +565,7 @@ __device__ __forceinline__ bool tile_segment(const AttnArgs &a, const GroupDiv &
             }
             PV_MFMA(0) V_READ(7) V_WAIT2(2, 8) EXP_A(8) FENCE
             PV_MFMA(1) V_READ(8) EXP_B(8) FENCE
-            if (next) mask(kb + 1, T);
+            if (!IN && next) mask(kb + 1, T);
             PV_MFMA(2) V_READ(9) V_WAIT2(4, 8) EXP_A(9) FENCE
             PV_MFMA(3) V_READ(10) EXP_B(9) EXP_A(10) FENCE
             PV_MFMA(4) V_READ(11) V_WAIT2(6, 8) EXP_B(10) FENCE
@@ -577,7 +581,7 @@ __device__ __forceinline__ bool tile_segment(const AttnArgs &a, const GroupDiv &
             PV_MFMA(14) FENCE
             PV_MFMA(15)
             l_run += psum0 + psum1;
-            if (__builtin_expect(exact && next, 0)) move_reference(block_max(T));
+            if (!IN && __builtin_expect(exact && next, 0)) move_reference(block_max(T));
             if (!next && !exact && !sums_fine() && lane == 0) s_again = 1;
             // the "memory" clobber keeps the next block's loads into these stages behind this block's reads
             asm volatile("" ::: "memory");
@@ -586,14 +590,14 @@ __device__ __forceinline__ bool tile_segment(const AttnArgs &a, const GroupDiv &
         __syncthreads();
     };
     Scores S0, S1;
-    fetch_k(kb0, 0);
+    fetch_k(anywhere, kb0, 0);
     {
         const __bf16 *qp = (const __bf16 *)a.q + (((int64_t)b * a.TT_cap + node) * a.Hq + hq) * D;
 #pragma unroll
         for (int s = 0; s < KSTEPS; ++s) qreg[s] = *(const bf16x8 *)(qp + 16 * s + 8 * half);
     }
-    fetch_v(kb0, 0);
-    if (kb0 + 1 < kb1) fetch_k(kb0 + 1, 1);
+    fetch_v(anywhere, kb0, 0);
+    if (kb0 + 1 < kb1) fetch_k(anywhere, kb0 + 1, 1);
     __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's part of the tiles is in LDS
     __syncthreads();
     if (tid == 0) s_again = 0;  // every wave has read the segment before's
@@ -621,11 +625,21 @@ __device__ __forceinline__ bool tile_segment(const AttnArgs &a, const GroupDiv &
     // goes first in every other block instead: both end within 5 us (4 sequences of a 70B step 121 -> 117 us, 64 wide trees
     // 240 -> 231; odd slots first in every block: 120 and 236).
     const bool odd_slot = __builtin_amdgcn_s_getreg((3 << 11) | 4) & 1;  // HW_ID, 4 bits from bit 0: wave slot of the SIMD
-    for (int kb = kb0; kb < kb1; kb += 2) {
+    const std::integral_constant<int, 0> even;
+    const std::integral_constant<int, 1> odd;
+    int kb = kb0;
+    if (active && small_stride && !exact)
+        for (const int end = min(kb1, L / TILE_KEYS); kb + 3 < end; kb += 2) {
+            if (odd_slot) __builtin_amdgcn_s_setprio(1);
+            block(even, std::true_type(), kb, S0, S1);
+            if (odd_slot) __builtin_amdgcn_s_setprio(0);
+            block(odd, std::true_type(), kb + 1, S1, S0);
+        }
+    for (; kb < kb1; kb += 2) {
         if (odd_slot) __builtin_amdgcn_s_setprio(1);
-        block(std::integral_constant<int, 0>(), kb, S0, S1);
+        block(even, anywhere, kb, S0, S1);
         if (odd_slot) __builtin_amdgcn_s_setprio(0);
-        if (kb + 1 < kb1) block(std::integral_constant<int, 1>(), kb + 1, S1, S0);
+        if (kb + 1 < kb1) block(odd, anywhere, kb + 1, S1, S0);
     }
     if (__builtin_expect(s_again, 0)) return true;
 #undef PIN
