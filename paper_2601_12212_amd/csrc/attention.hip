@@ -161,7 +161,7 @@ __device__ __forceinline__ u32 vis_window(int off, u64 mask0, u64 mask1) {
 #define TILE_KEYS 64
 #define TILE_BYTES (TILE_KEYS * 256)     // one K or V tile
 #define SUB_BYTES (TILE_KEYS * 64)       // a quarter of its columns
-#define TILE_LDS_BYTES (4 * TILE_BYTES)  // two K tiles, then two V tiles
+#define TILE_LDS_BYTES(NS) (2 * (NS) * TILE_BYTES)  // NS K tiles, then NS V tiles
 typedef char __attribute__((address_space(3))) *ldsp;
 
 // One key range of a (sequence, row tile): the `me`-th of `parts`.  With more than one, the workgroups leave partials
@@ -322,10 +322,16 @@ static GroupDiv group_div(int G) { return {G, (u32)(((u64)1 << 32) / G + 1)}; }
 
 // Rows m0 .. m0+127 of (sequence b, kv head h) against key blocks kb0 .. kb1-1 of that sequence.
 // Called by all 256 threads of the workgroup; ends behind a barrier, so calls can follow each other.
-template <int D>
+//
+// NS tiles of K and of V are in LDS.  Two (64 KB) where two workgroups share a compute unit and each covers the other's waits.  Four where a
+// workgroup is alone: with two its loads are asked for one block before they are read, and a block of a cache that comes from memory then takes
+// 1.3 us in place of 0.7; with four they are asked for three blocks before.  us per layer, two | four: 16 layers of 8 sequences of 1,100 keys (8B
+// shape) 32.6 | 27.5, 32 of 400 18.1 | 17.1; one layer, its cache in the last level: 200 keys 13.0 | 13.6, 1,100 25.2 | 26.6 (the counted waits and
+// stages found at run time).
+template <int D, int NS>
 __device__ __forceinline__ bool tile_segment(const AttnArgs &a, const GroupDiv &gd, const SeqWords &sq, unsigned char *s_dyn, int h,
                                              int b, int m0, int rot, int kb0, int kb1, const TileParts &pt, int slots, bool stay, bool exact) {
-    static_assert(D == 128, "head dim");
+    static_assert(D == 128 && (NS == 2 || NS == 4), "shape");
     constexpr int KSTEPS = D / 16, DBLK = D / 32;
     int G = gd.G, N = sq.N, L = sq.L;
     asm volatile("" : "+s"(G), "+s"(N), "+s"(L));
@@ -384,8 +390,9 @@ __device__ __forceinline__ bool tile_segment(const AttnArgs &a, const GroupDiv &
         }
     };
     const std::false_type anywhere;
-    auto fetch_k = [&](auto inside, int kb, int stage) { fetch(inside, kb, stage * TILE_BYTES, kpre, ktree, koffp, kchunk); };
-    auto fetch_v = [&](auto inside, int kb, int stage) { fetch(inside, kb, 2 * TILE_BYTES + stage * TILE_BYTES, vpre, vtree, voffp, vchunk); };
+    auto stage_of = [&](int kb) { return (u32)((kb - kb0) & (NS - 1)); };
+    auto fetch_k = [&](auto inside, int kb, u32 stage) { fetch(inside, kb, stage * TILE_BYTES, kpre, ktree, koffp, kchunk); };
+    auto fetch_v = [&](auto inside, int kb, u32 stage) { fetch(inside, kb, (NS + stage) * TILE_BYTES, vpre, vtree, voffp, vchunk); };
 
     // Operand read addresses; everything but the lane's own part is an immediate offset.
     // K, A operand of S^T: lane (col, half), k-step s reads chunk 2s + half of row 32 j + col: sub-tile s / 2, chunk
@@ -398,7 +405,7 @@ __device__ __forceinline__ bool tile_segment(const AttnArgs &a, const GroupDiv &
     // a 16-lane group lane p16 = 4 r0 + q points at key r0 of the quadruple, columns 4q .. 4q+3 of
     // the group's 16 columns: sub-tile db, byte 32 grp + 8 q of the row (grp = second 16-lane group of the half).
     const int p16 = lane & 15, r0 = p16 >> 2, q4 = p16 & 3, grp = (lane >> 4) & 1;
-    const u32 voff = lds0 + (u32)((4 * half + r0) * 64 + 32 * grp + 8 * q4);
+    const u32 voff = lds0 + NS * TILE_BYTES + (u32)((4 * half + r0) * 64 + 32 * grp + 8 * q4);
 
     bf16x8 qreg[KSTEPS];
     // Scores of a block: two 32x32 blocks, S[j] = keys 32 j .. 32 j + 31.
@@ -506,15 +513,15 @@ __device__ __forceinline__ bool tile_segment(const AttnArgs &a, const GroupDiv &
             pw[e] = __builtin_bit_cast(u32, pk);                                                               \
             PIN(pw[e])                                                                                         \
         }
-#define K_READ(i) ka[i] = lds_load128_at<(CUR ^ 1) * TILE_BYTES + ((i) >> 2) * SUB_BYTES + ((i) & 1) * 32 * 64>(koff[((i) >> 1) & 1]);
+#define K_READ(i) ka[i] = lds_load128_at<(NS == 2 ? (CUR ^ 1) * TILE_BYTES : 0) + ((i) >> 2) * SUB_BYTES + ((i) & 1) * 32 * 64>(kat[((i) >> 1) & 1]);
 #define K_WAIT(i, W) lds_wait<W>(ka[i]);
 #define K_WAIT2(i, W) lds_wait2<W>(ka[i], ka[(i) + 1]);
 #define QK_MFMA(i)                                                                                            \
         T.v[(i) & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[i], qreg[(i) >> 1], (i) < 2 ? zero16 : T.v[(i) & 1], 0, 0, 0); \
         __builtin_amdgcn_sched_barrier(0);
 #define V_READ(n)                                                                                             \
-        vlo[n] = lds_load_tr4<(2 + CUR) * TILE_BYTES + ((n) & 3) * SUB_BYTES + 16 * ((n) >> 2) * 64>(voff);         \
-        vhi[n] = lds_load_tr4<(2 + CUR) * TILE_BYTES + ((n) & 3) * SUB_BYTES + (16 * ((n) >> 2) + 8) * 64>(voff);
+        vlo[n] = lds_load_tr4<(NS == 2 ? CUR * TILE_BYTES : 0) + ((n) & 3) * SUB_BYTES + 16 * ((n) >> 2) * 64>(vat);         \
+        vhi[n] = lds_load_tr4<(NS == 2 ? CUR * TILE_BYTES : 0) + ((n) & 3) * SUB_BYTES + (16 * ((n) >> 2) + 8) * 64>(vat);
 #define V_WAIT2(n, W) lds_wait4<W>(vlo[n], vhi[n], vlo[(n) + 1], vhi[(n) + 1]);
 #define PV_MFMA(n)                                                                                            \
         oacc[(n) & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(                                               \
@@ -526,14 +533,17 @@ __device__ __forceinline__ bool tile_segment(const AttnArgs &a, const GroupDiv &
         const uint4 v = make_uint4(wd[0], wd[1], wd[2], wd[3]);
         return __builtin_bit_cast(bf16x8, v);
     };
-    // inside: blocks kb + 1 and kb + 2 are there and hold prefix keys only, and nothing else is to be asked either: no branches
+    // inside: the blocks up to kb + NS are there and hold prefix keys only, and nothing else is to be asked either: no branches
     // (some fifteen in a block; taken ones cost a lone wave up to twenty cycles).
     auto block = [&](auto cur_c, auto inside, int kb, Scores &S, Scores &T) {
         constexpr int CUR = decltype(cur_c)::value;
         constexpr bool IN = decltype(inside)::value;
         const bool next = IN || kb + 1 < kb1;  // uniform
-        if (IN || kb + 2 < kb1) fetch_k(inside, kb + 2, CUR);  // K(kb) was last read before the previous barrier,
-        if (next) fetch_v(inside, kb + 1, CUR ^ 1);            // V(kb - 1) too
+        // K(kb) was last read before the previous barrier, V(kb - 1) too: their stages take K(kb + NS) and V(kb + NS - 1)
+        if (IN || kb + NS < kb1) fetch_k(inside, kb + NS, NS == 2 ? CUR : stage_of(kb));
+        if (IN || kb + NS - 1 < kb1) fetch_v(inside, kb + NS - 1, NS == 2 ? CUR ^ 1 : stage_of(kb - 1));
+        const u32 kst = NS == 2 ? 0 : stage_of(kb + 1) * TILE_BYTES, vst = NS == 2 ? 0 : stage_of(kb) * TILE_BYTES;
+        const u32 kat[2] = {koff[0] + kst, koff[1] + kst}, vat = voff + vst;
         if (IN || active) {
             float psum0 = 0.f, psum1 = 0.f, pe;
             u32 pw[16];  // the probabilities as pairs of bf16
@@ -586,23 +596,55 @@ __device__ __forceinline__ bool tile_segment(const AttnArgs &a, const GroupDiv &
             // the "memory" clobber keeps the next block's loads into these stages behind this block's reads
             asm volatile("" ::: "memory");
         }
-        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's part of the next tiles has landed
-        __syncthreads();
+        if constexpr (NS == 2) {
+            __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's part of the next tiles has landed
+            __syncthreads();
+        } else {
+            // K(kb + 2) and V(kb + 1), asked for two blocks ago, have to be there; what was asked for since (four loads a tile) may be on its way
+            const int left = kb1 - kb;
+            if (IN || left > 4) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+            else if (left == 4) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+            else if (left == 3) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+            else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+        }
     };
     Scores S0, S1;
-    fetch_k(anywhere, kb0, 0);
-    {
-        const __bf16 *qp = (const __bf16 *)a.q + (((int64_t)b * a.TT_cap + node) * a.Hq + hq) * D;
+    const __bf16 *qp = (const __bf16 *)a.q + (((int64_t)b * a.TT_cap + node) * a.Hq + hq) * D + 8 * half;
+    if constexpr (NS == 2) {
+        fetch_k(anywhere, kb0, 0);
 #pragma unroll
-        for (int s = 0; s < KSTEPS; ++s) qreg[s] = *(const bf16x8 *)(qp + 16 * s + 8 * half);
+        for (int s = 0; s < KSTEPS; ++s) qreg[s] = *(const bf16x8 *)(qp + 16 * s);
+        fetch_v(anywhere, kb0, 0);
+        if (kb0 + 1 < kb1) fetch_k(anywhere, kb0 + 1, 1);
+        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's part of the tiles is in LDS
+        __syncthreads();
+    } else {
+        // in the order in which they are needed; the queries as instructions, since the compiler would wait for everything behind them
+        fetch_k(anywhere, kb0, 0);
+#define Q_LOAD(s) asm volatile("global_load_dwordx4 %0, %1, off offset:%2" : "=v"(qreg[s]) : "v"(qp), "n"(32 * (s)) : "memory");
+        Q_LOAD(0) Q_LOAD(1) Q_LOAD(2) Q_LOAD(3) Q_LOAD(4) Q_LOAD(5) Q_LOAD(6) Q_LOAD(7)
+#undef Q_LOAD
+        fetch_v(anywhere, kb0, 0);
+        for (int i = 1; i < 4; ++i)
+            if (kb0 + i < kb1) {
+                fetch_k(anywhere, kb0 + i, i);
+                if (i < 3) fetch_v(anywhere, kb0 + i, i);
+            }
+        const int n = kb1 - kb0;  // the first K tile and the queries
+        if (n >= 4) asm volatile("s_waitcnt vmcnt(24)" ::: "memory");
+        else if (n == 3) asm volatile("s_waitcnt vmcnt(20)" ::: "memory");
+        else if (n == 2) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+        asm volatile("" : "+v"(qreg[0]), "+v"(qreg[1]), "+v"(qreg[2]), "+v"(qreg[3]), "+v"(qreg[4]), "+v"(qreg[5]), "+v"(qreg[6]), "+v"(qreg[7]));
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
     }
-    fetch_v(anywhere, kb0, 0);
-    if (kb0 + 1 < kb1) fetch_k(anywhere, kb0 + 1, 1);
-    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's part of the tiles is in LDS
-    __syncthreads();
     if (tid == 0) s_again = 0;  // every wave has read the segment before's
     if (active) {  // scores of the first block
         constexpr int CUR = 1;
+        const u32 kat[2] = {koff[0], koff[1]};
         Scores &T = S0;
         bf16x8 ka[16];
         K_READ(0) K_READ(1) K_READ(2) K_READ(3) K_READ(4) K_READ(5) K_READ(6) K_READ(7) FENCE
@@ -619,7 +661,18 @@ __device__ __forceinline__ bool tile_segment(const AttnArgs &a, const GroupDiv &
         if (!exact && m_run == -INFINITY) m_run = 0.f;  // what nmc says
         asm volatile("" ::: "memory");
     }
-    __syncthreads();  // K stage 0 is free
+    if constexpr (NS == 2) {
+        __syncthreads();  // K stage 0 is free
+    } else {              // and V(kb0) and K(kb0 + 1) are there
+        const int n = kb1 - kb0;
+        if (n >= 4) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+        else if (n == 3) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+        else if (n == 2) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    }
     // The two workgroups of a compute unit have equal work, but a SIMD issues the older of two ready waves, so the first to
     // arrive finished 15 us of 110 before the second, which then ran alone at 60 % of the pair's rate.  The wave in the odd slot
     // goes first in every other block instead: both end within 5 us (4 sequences of a 70B step 121 -> 117 us, 64 wide trees
@@ -629,7 +682,7 @@ __device__ __forceinline__ bool tile_segment(const AttnArgs &a, const GroupDiv &
     const std::integral_constant<int, 1> odd;
     int kb = kb0;
     if (active && small_stride && !exact)
-        for (const int end = min(kb1, L / TILE_KEYS); kb + 3 < end; kb += 2) {
+        for (const int end = min(kb1, L / TILE_KEYS); kb + NS + 1 < end; kb += 2) {
             if (odd_slot) __builtin_amdgcn_s_setprio(1);
             block(even, std::true_type(), kb, S0, S1);
             if (odd_slot) __builtin_amdgcn_s_setprio(0);
@@ -761,7 +814,7 @@ __device__ __forceinline__ bool tile_segment(const AttnArgs &a, const GroupDiv &
 // schedule below does not take.  blockIdx.x = kv head: workgroups are dealt to the 8 XCDs
 // round-robin by linear id, so all row tiles of one kv head land on one XCD and share its L2
 // copy of that head's K/V.
-template <int D>
+template <int D, int NS>
 __global__ __launch_bounds__(256, 2) void attn_tile_kernel(AttnArgs a, GroupDiv gd) {
     extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];
     const int b = blockIdx.z, h = blockIdx.x, m0 = blockIdx.y * ATT_MTILE;
@@ -775,7 +828,7 @@ __global__ __launch_bounds__(256, 2) void attn_tile_kernel(AttnArgs a, GroupDiv 
     TileParts whole = {};
     whole.parts = 1;
     bool exact = false;
-    while (tile_segment<D>(a, gd, sq, s_dyn, h, b, m0, blockIdx.y + blockIdx.z, 0, nb, whole, 0, false, exact)) exact = true;
+    while (tile_segment<D, NS>(a, gd, sq, s_dyn, h, b, m0, blockIdx.y + blockIdx.z, 0, nb, whole, 0, false, exact)) exact = true;
 }
 
 // ---- balanced schedule -----------------------------------------------------------------------------
@@ -944,7 +997,7 @@ __global__ __launch_bounds__(256, 2) void attn_gang_kernel(AttnArgs a, GroupDiv 
         pt.ml = part.ml;
         pt.count = part.count + pt.slot;
         pt.tag = part.tag;
-        exact = tile_segment<D>(a, gd, sq, s_dyn, h, b, tile * ATT_MTILE, j, kb0, kb1, pt, a.Hkv * P, !(segs & (segs - 1)), exact);
+        exact = tile_segment<D, 2>(a, gd, sq, s_dyn, h, b, tile * ATT_MTILE, j, kb0, kb1, pt, a.Hkv * P, !(segs & (segs - 1)), exact);
         if (!exact) segs &= segs - 1;
     }
 }
@@ -1859,9 +1912,11 @@ hipError_t attn_init() {
         e = hipFuncSetAttribute((const void *)attn_wave_kernel<128, 4, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 WD_LDS_BYTES);
     if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)attn_tile_kernel<128>, hipFuncAttributeMaxDynamicSharedMemorySize, TILE_LDS_BYTES);
+        e = hipFuncSetAttribute((const void *)attn_tile_kernel<128, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, TILE_LDS_BYTES(2));
     if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)attn_gang_kernel<128>, hipFuncAttributeMaxDynamicSharedMemorySize, TILE_LDS_BYTES);
+        e = hipFuncSetAttribute((const void *)attn_tile_kernel<128, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, TILE_LDS_BYTES(4));
+    if (e == hipSuccess)
+        e = hipFuncSetAttribute((const void *)attn_gang_kernel<128>, hipFuncAttributeMaxDynamicSharedMemorySize, TILE_LDS_BYTES(2));
     return e;
 }
 
@@ -1910,8 +1965,10 @@ static int64_t max_blocks(const AttnArgs &a) { return ((int64_t)a.max_prefix_len
 
 // 128-wide heads: which kernel.  `units` (sequence, kv head, 32-row block)s, as the caller allows for them:
 //  - up to 256, one to a compute unit: the small-batch kernel, whatever the lengths;
-//  - more, and at most 40 blocks of 32 keys: workgroups that take whole tiles of 128 rows.  Each shares a key block among four row blocks, and on
-//    sequences this short nothing is gained by cutting them: the schedule finds that too, and takes 1 us to find it;
+//  - more, and at most 40 blocks of 32 keys (56 where every tile has a compute unit to itself): workgroups that take whole tiles of 128 rows.  Each
+//    shares a key block among four row blocks, and on sequences this short nothing is gained by cutting them: the schedule finds that too, and takes
+//    1 us to find it.  A workgroup alone on its compute unit keeps four tiles of each kind in LDS in place of two (NS): nothing but its own loads in
+//    flight hides their latency;
 //  - more keys: the balanced schedule, which cuts or does not cut by the lengths that it finds.
 // The lengths here are the most that the caller allows for (max_prefix_len): one call's own, or, in a step that is captured once, the most that any
 // replay will have.  us per layer, small-batch | balanced | whole tiles, all sequences as long as that ("equal") or from a quarter of it up ("ragged"):
@@ -1923,9 +1980,14 @@ static int64_t max_blocks(const AttnArgs &a) { return ((int64_t)a.max_prefix_len
 //     4 of 112 (448) 1,600 36 | 37 | 36, ragged 30 | 28 | 30, 4,000 66 | 57 | 73; 40 heads without groups, 4 of 64 (320) 1,300 36 | 31 | 29, 2,400 56 | 44 | 45;
 //   more tiles than there is room for at once: 32 sequences of the 70B shape, 64 nodes (1,024 tiles) ragged 200 keys 42 balanced | 31 whole, 1,100 73 | 67; 54 of 40 heads, 64
 //     nodes (2,160) 400 153 | 138, ragged 108 | 90, 1,100 316 | 289; 40 of four heads with four queries each, 112 nodes (640) 400 41 | 39, ragged (but then 500 or so) 28 | 36;
-//     16 of 40 heads (640) 1,100 103 | 96, 1,600 136 | 134, 2,400 181 | 199; 64 of the 8B shape, 256 to 4,096 keys 231 | 295.
+//     16 of 40 heads (640) 1,100 103 | 96, 1,600 136 | 134, 2,400 181 | 199; 64 of the 8B shape, 256 to 4,096 keys 231 | 295;
+//   a compute unit to each tile, with layers whose caches come from memory, balanced | whole, two tiles in LDS | whole, four (mean of 4 to 14 sequences of the 8B shape, 20 of
+//     2 kv heads, 6 of 32): ragged 400 keys 18.5 | 17.0 | 16.6, 1,100 32.3 | 30.8 | 27.1, 1,600 36.0 | 39.0 | 32.9, 2,400 46.8 | 56.9 | 46.9, 4,000 57 | 86 | 68; equal 1,600
+//     43.0 | 43.5 | 37.2.  With the caches in the last level, balanced | four: ragged 1,600 30.5 | 29.5, 2,400 39.8 | 40.3; one sequence of 1,600 among 11 of 200 31.2 | 30.0,
+//     of 2,400 33.6 | 40.3.
 #define SMALL_UNITS 256
 #define WHOLE_BLOCKS 40
+#define WHOLE_BLOCKS_ONE 56
 
 // The small-batch kernel and, with key splits, its merge.
 template <int D>
@@ -1998,8 +2060,11 @@ int attn_launch(const AttnArgs &a, hipStream_t st, hipError_t *err) {
     const int mblocks = (a.TT_cap * G + 31) / 32;
     const int64_t units = (int64_t)a.batch * a.Hkv * mblocks;
     if (units <= SMALL_UNITS || (base_wgs < 128 && !gang)) return wave_launch<128>(a, st, err);
-    if (!gang || max_blocks(a) <= WHOLE_BLOCKS) {
-        launch_kernel(KID_ATTN, st, attn_tile_kernel<128>, dim3(a.Hkv, mtiles, a.batch), dim3(256), TILE_LDS_BYTES, a, group_div(G));
+    const bool one = base_wgs <= a.n_cu;
+    if (!gang || max_blocks(a) <= (one ? WHOLE_BLOCKS_ONE : WHOLE_BLOCKS)) {
+        const dim3 grid(a.Hkv, mtiles, a.batch);
+        if (one) launch_kernel(KID_ATTN, st, attn_tile_kernel<128, 4>, grid, dim3(256), TILE_LDS_BYTES(4), a, group_div(G));
+        else launch_kernel(KID_ATTN, st, attn_tile_kernel<128, 2>, grid, dim3(256), TILE_LDS_BYTES(2), a, group_div(G));
         *err = hipGetLastError();
         return *err == hipSuccess ? DT_OK : DT_ERR_HIP;
     }
@@ -2010,7 +2075,7 @@ int attn_launch(const AttnArgs &a, hipStream_t st, hipError_t *err) {
     part.ml = part.o + slots * 2 * ATT_MTILE * (a.D / 2);
     part.count = part.ml + slots * 2 * ATT_MTILE;
     part.tag = (launches.fetch_add(1, std::memory_order_relaxed) + 1) * 0x9e3779b97f4a7c15ull & ~(u64)0xffff;
-    launch_kernel(KID_ATTN, st, attn_gang_kernel<128>, dim3(a.Hkv, P), dim3(256), TILE_LDS_BYTES, a, group_div(G), P, part);
+    launch_kernel(KID_ATTN, st, attn_gang_kernel<128>, dim3(a.Hkv, P), dim3(256), TILE_LDS_BYTES(2), a, group_div(G), P, part);
     *err = hipGetLastError();
     return *err == hipSuccess ? DT_OK : DT_ERR_HIP;
 }

@@ -281,6 +281,20 @@ def test_shared_merge_of_a_dozen_to_thirty_parts():
         assert_attention(st.attention_out(0), want, "bf16", "%d blocks" % blocks)
 
 
+@pytest.mark.parametrize("B", [32, 33])
+def test_whole_tiles_of_every_length(B):
+    # 256 tiles, one to a compute unit, four K and V tiles in LDS, and 264, two: ranges of one to a dozen 64-key blocks, ragged and not
+    TT = 40
+    lens = [0, 1, 23, 24, 25, 80, 88, 89] + [64 * n - TT + (n % 3 - 1) * (n % 2) for n in range(3, 27)] + [500]
+    check_case(oracle_case(0, cfg=_cfg("bf16", 128, [(TT, 5, 6)] * B, lens[:B], 8, 8)))
+
+
+# 136 tiles, a compute unit to each, are whole up to 56 blocks of 32 keys
+@pytest.mark.parametrize("L", [1752, 1753])
+def test_line_of_a_tile_to_each_compute_unit(L):
+    check_case(oracle_case(0, cfg=_cfg("bf16", 128, [(40, 5, 6)] * 17, [L] + [7 + 100 * b for b in range(1, 17)], 8, 8)))
+
+
 # 256 (sequence, kv head, 32-row block)s, which the small-batch kernel takes, and 264, which the kernel of whole tiles takes up to 40 blocks of 32 keys and the
 # balanced schedule from 41 on
 @pytest.mark.parametrize("B,L", [(32, 1248), (33, 100), (33, 1248), (33, 1249)])
@@ -289,7 +303,7 @@ def test_lines_between_the_three_kernels(B, L):
 
 
 # Shapes of the kernel of whole tiles, and of the balanced schedule with sequences whole and cut.
-FAR = {"whole tiles": (8, 8, [60, 300, 700] + [10] * 30), "schedule, whole": (8, 8, [1250, 300, 700] + [10] * 30),
+FAR = {"whole tiles": (8, 8, [60, 300, 700] + [10] * 30), "whole tiles, a compute unit each": (8, 8, [60, 300, 1100] + [10] * 14), "schedule, whole": (8, 8, [1250, 300, 700] + [10] * 30),
        "schedule, cut": (64, 8, [1700, 1700, 1500, 1600])}
 
 
