@@ -856,6 +856,236 @@ __global__ __launch_bounds__(NT, NL == 4 ? 4 : 8) void row_topk_kernel(RowArgs a
     }
 }
 
+// ------------------------------------------------- bf16 rows of large launches (top-k rows) --
+// Where rows come by the thousand the kernel above is bound by vector instructions, most of them not spent on the elements: every wave of a
+// row looks its row up, reduces, and takes part in the search, and lanes past the row's end work like the others (2,040 entries, k = 24:
+// 1,240 instructions a row, 250 of them on elements; 16,000 in 1,024 threads 6,900).  Here a lane holds 32 or 64 elements, as they came from
+// memory: unpacked once for the maxima and once more for the exponentials, they leave room for eight waves to a SIMD.  The slots are the groups of
+// eight at the same place of all waves, four to a lane, so that a row of one wave needs no exchange; the groups that reach T are listed, and their
+// elements read again, one to a lane, in place of a search of every lane's elements; keys are 32 bits, value and place.  Groups past the end are passed
+// over.  Draft rows, us, before | now: 10,309 rows of 2,040 entries, k = 24, 29 | 19; 5,408 of 9,411 67 | 31, of 16,000 69 | 34, of 32,000 114 | 62 (two passes
+// before; the bytes are 55 us); calls of 2,600 rows of 16,000, k = 16, 26.4 | 18.5, of 25,000 37 | 28.
+#define MANY_LIST (SEL_CAP * 4)  // bytes of the list of candidates
+#define MANY_WAVE (64 * 16)      // of a wave: its slots' keys, later its groups that reach T
+template <int MODE, int NG>
+__global__ __launch_bounds__(1024, 8) void row_many_kernel(RowArgs a, float *top_val, int32_t *top_id, float *lse, int out_stride) {
+    static_assert(NG == 4 || NG == 8, "groups of eight to a lane");
+    constexpr int WAVE = 512 * NG;  // entries of a wave
+    const int64_t g = blockIdx.x;
+    const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6), NW = blockDim.x >> 6;
+    const int V = a.V, wave0 = w * WAVE, base = wave0 + lane * 8;
+    RawChunk<NG, true> raw;
+    const bool early = MODE == ROWS_UNIFORM || a.early_load;
+    if (early) chunk_request<NG, true, true>(a, g, base, raw);
+    const RowMeta meta = row_meta<MODE>(a, g);
+    if (!meta.valid) return;
+    const int k = meta.k;
+    if (!early) chunk_request<NG, true, true>(a, g, base, raw);
+
+    extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];
+    __shared__ float2 s_ms[16];
+    __shared__ int s_n, s_cnt[3];
+    __shared__ float s_T;
+    u32 *s_list = (u32 *)s_dyn;
+    uint2 *s_key = (uint2 *)(s_dyn + MANY_LIST + w * MANY_WAVE);  // this wave's
+    auto clear = [&]() {
+        ((uint4 *)s_list)[lane] = make_uint4(0, 0, 0, 0);
+        if (lane == 0) s_n = 0;
+    };
+    if (w == 0) {
+        clear();
+        if (lane < 3) s_cnt[lane] = 0;
+    }
+    auto key_of = [](float v, int id) { return (ord32(v) & 0xFFFF0000u) | (0xFFFFu - (u32)id); };
+    auto unpack = [&](int n, float (&x)[8]) {
+        const u32 rr[4] = {raw.r[n].x, raw.r[n].y, raw.r[n].z, raw.r[n].w};
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            x[2 * p] = __uint_as_float(rr[p] << 16);
+            x[2 * p + 1] = __uint_as_float(rr[p] & 0xFFFF0000u);
+        }
+        if (wave0 + (n + 1) * 512 > V) {  // uniform: reaches past the row's end
+            const int id0 = base + n * 512, first = id0 - group_start(V, id0);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[e] = e >= first ? x[e] : -INFINITY;
+        }
+    };
+    float gmx[NG];
+#pragma unroll
+    for (int n = 0; n < NG; ++n) {
+        gmx[n] = -INFINITY;
+        if (n && wave0 + n * 512 >= V) continue;  // uniform
+        float x[8];
+        unpack(n, x);
+        float m = -INFINITY;
+        asm("v_max3_f32 %0, %1, %2, %0\n\tv_max3_f32 %0, %3, %4, %0\n\tv_max3_f32 %0, %5, %6, %0\n\tv_max3_f32 %0, %7, %8, %0"
+            : "+v"(m) : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(x[5]), "v"(x[6]), "v"(x[7]));
+        gmx[n] = m;
+    }
+    float sl[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        sl[i] = gmx[i];
+        if constexpr (NG == 8) asm("v_max_f32 %0, %1, %0" : "+v"(sl[i]) : "v"(gmx[i + 4]));
+    }
+    // the upper halves as keys: x ^ (negative ? 0xFFFF : 0x8000), two at a time.  (-0 below +0: T is only a bound.)
+    auto pair_key = [](float lo, float hi) {
+        typedef short s2 __attribute__((ext_vector_type(2)));
+        const u32 p = __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
+        const u32 sign = __builtin_bit_cast(u32, __builtin_bit_cast(s2, p) >> (short)15);
+        return p ^ (sign | 0x80008000u);
+    };
+    const uint2 own = make_uint2(pair_key(sl[0], sl[1]), pair_key(sl[2], sl[3]));
+    if (NW > 1 && w) s_key[lane] = own;
+    if (a.want_lse) {
+        const float cexp = 1.4426950408889634f * a.inv_t;
+        float mx = sl[0];
+        asm("v_max3_f32 %0, %1, %2, %0\n\tv_max_f32 %0, %3, %0" : "+v"(mx) : "v"(sl[1]), "v"(sl[2]), "v"(sl[3]));
+        const float M = wave_max(mx), nm = M == -INFINITY ? 0.f : -M * cexp;
+#pragma unroll
+        for (int i = 0; i < NG; ++i)  // keep the compiler from holding the elements
+            asm volatile("" : "+v"(raw.r[i].x), "+v"(raw.r[i].y), "+v"(raw.r[i].z), "+v"(raw.r[i].w));
+        float s = 0.f;
+#pragma unroll
+        for (int n = 0; n < NG; ++n) {
+            if (n && wave0 + n * 512 >= V) continue;
+            float x[8];
+            unpack(n, x);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) s += __builtin_amdgcn_exp2f(fmaf(x[e], cexp, nm));
+        }
+        s = wave_sum(s > 0.f ? s : 0.f);
+        if (NW == 1) {
+            if (lane == 0) lse[meta.out] = M == -INFINITY ? -INFINITY : M * a.inv_t + __logf(s);
+        } else if (lane == 0) s_ms[w] = make_float2(M, s);
+    }
+    __syncthreads();
+    if (w == 0) {  // the row's 256 slots: group (n, lane) of all waves
+        typedef unsigned short us4 __attribute__((ext_vector_type(4)));
+        us4 m = __builtin_bit_cast(us4, own);
+#pragma unroll 4
+        for (int j = 1; j < NW; ++j) {
+            const uint2 o = *(const uint2 *)((const unsigned char *)s_key + j * MANY_WAVE + lane * 8);
+            m = __builtin_elementwise_max(m, __builtin_bit_cast(us4, o));
+        }
+        const u32 ky[4] = {m.x, m.y, m.z, m.w};
+        const u32 t = wave_kth_of_256(ky, k);
+        if (lane == 0) s_T = key_edge(t);
+    }
+    __syncthreads();
+    const float T = s_T;
+    const float T1 = fmaxf(T, -__FLT_MAX__);  // -inf does not count
+    uint16_t *s_hot = (uint16_t *)s_key;  // the groups that reach T (in the place of the slots, which have been read)
+    int hot = 0;
+#pragma unroll
+    for (int n = 0; n < NG; ++n) {
+        const bool in = gmx[n] >= T1;
+        const u64 m = __builtin_amdgcn_ballot_w64(in);
+        if (m) {
+            if (in) s_hot[hot + lanes_below(m)] = (uint16_t)(64 * n + lane);
+            hot += __popcll(m);
+        }
+    }
+    // their entries again, one to a lane
+    const uint16_t *row = (const uint16_t *)a.logits + g * a.row_stride;
+    auto entry = [&](int id) { return bf16_bits_to_float(row[id]); };
+    __builtin_amdgcn_wave_barrier();
+    for (int q0 = 0; q0 < 8 * hot; q0 += 64) {  // uniform
+        const int q = s_hot[min((q0 + lane) >> 3, hot - 1)];
+        const int id0 = wave0 + q * 8, id = group_start(V, id0) + (lane & 7);
+        const float v = entry(id);
+        const bool in = v >= T1 && id >= id0 && q0 + lane < 8 * hot;
+        const u64 m = __builtin_amdgcn_ballot_w64(in);
+        if (m) {
+            int at = 0;
+            if (lane == 0) at = atomicAdd(&s_n, (int)__popcll(m));
+            at = __builtin_amdgcn_readfirstlane(at) + lanes_below(m);
+            if (in && at < SEL_CAP) s_list[at] = key_of(v, id);
+        }
+    }
+    __syncthreads();
+    int n = s_n;
+    if (n > SEL_CAP) {
+        // Clusters or equal values: the k-th value by bisection over the row, then, of the entries equal to it, the last id.
+        int step = 0;
+        auto count = [&](auto f) {  // entries of the row for which f(value, id); three counters in turn, so that one barrier does
+            int own_n = 0;
+#pragma unroll 1
+            for (int id = tid; id < V; id += blockDim.x) own_n += f(entry(id), id) ? 1 : 0;
+            const int sum = wave_sum_i32(own_n);
+            if (lane == 0) atomicAdd(&s_cnt[step % 3], sum);
+            __syncthreads();
+            const int v = s_cnt[step % 3];
+            if (tid == 0) s_cnt[(step + 2) % 3] = 0;
+            ++step;
+            return v;
+        };
+        u32 lo = ord32(T), hi = 0xFFFFFFFFu;  // at least k keys reach lo, none lies above hi
+        if (lo <= 0x007FFFFFu) lo = 0x00800000u;  // -inf does not count
+        int c = n;
+        while (hi > lo && c > k) {
+            const u32 mid = lo + ((hi - lo) >> 1) + 1u;
+            const int m = count([&](float v, int) { return ord32(v) >= mid; });
+            if (m >= k) { lo = mid; c = m; }
+            else hi = mid - 1u;
+        }
+        int id_hi = 0x7FFFFFFF;  // of the entries equal to lo: those up to this id
+        if (c > k) {
+            const int need = k - count([&](float v, int) { return ord32(v) > lo; });
+            int id_lo = 0;  // the smallest id with `need` of them at or below it
+            id_hi = V - 1;
+            while (id_hi > id_lo) {
+                const int mid = (id_lo + id_hi) >> 1;
+                if (count([&](float v, int id) { return ord32(v) == lo && id <= mid; }) >= need) id_hi = mid;
+                else id_lo = mid + 1;
+            }
+        }
+        __syncthreads();  // the count has been read
+        if (w == 0) clear();
+        __syncthreads();
+#pragma unroll 1
+        for (int id = tid; id < V; id += blockDim.x) {
+            const float v = entry(id);
+            if (ord32(v) > lo || (ord32(v) == lo && id <= id_hi)) {
+                const int at = atomicAdd(&s_n, 1);
+                if (at < SEL_CAP) s_list[at] = key_of(v, id);
+            }
+        }
+        __syncthreads();
+        n = s_n;
+    }
+    float *tv = top_val + meta.out * out_stride;
+    int32_t *ti = top_id ? top_id + meta.out * out_stride : nullptr;
+    for (int c = tid; c < SEL_CAP && (c & ~63) < n; c += blockDim.x) {  // candidate c ranks itself against all (zeros behind the n keys)
+        const u32 mine = s_list[c];
+        int rank = 0;
+#pragma unroll 1
+        for (int j0 = 0; j0 < n; j0 += 8) {
+            u32 o[8];
+            __builtin_memcpy(o, __builtin_assume_aligned(&s_list[j0], 16), sizeof(o));
+#pragma unroll
+            for (int j = 0; j < 8; ++j) rank += o[j] > mine ? 1 : 0;
+        }
+        if (c < n && rank < k) {
+            tv[rank] = unord32(mine & 0x80000000u ? mine & 0xFFFF0000u : mine | 0xFFFFu);
+            if (ti) ti[rank] = (int32_t)(0xFFFFu - (mine & 0xFFFFu));
+        }
+    }
+    if (w == NW - 1) {
+        if (lane >= n && lane < k) {  // fewer than k viable entries
+            tv[lane] = -INFINITY;
+            if (ti) ti[lane] = -1;
+        }
+        if (NW > 1 && a.want_lse) {
+            const float cexp = 1.4426950408889634f * a.inv_t;
+            const float2 p = lane < NW ? s_ms[min(lane, NW - 1)] : make_float2(-INFINITY, 0.f);
+            const float M = wave_max(p.x);
+            const float sum = wave_sum(p.y > 0.f ? p.y * __builtin_amdgcn_exp2f((p.x - M) * cexp) : 0.f);
+            if (lane == 0) lse[meta.out] = M == -INFINITY ? -INFINITY : M * a.inv_t + __logf(sum);
+        }
+    }
+}
+
 // ------------------------------------------------------------- arg max kernel (target rows) --
 // k = 1: every workgroup leaves the best (value, id) key of its chunk, and optionally the
 // (max, sum) pair of row/T; the acceptance kernel merges the chunks of a row.
@@ -1061,6 +1291,24 @@ static hipError_t launch_held(const RowArgs &a_in, int64_t n_rows, float *top_va
     return hipGetLastError();
 }
 
+// bf16 rows that the kernel for large launches takes, in waves of 512 ng entries.  Four groups of eight to a lane while all rows then fit on the chip at
+// once, else eight: calls of 1,000 rows of 16,000 entries, four | eight, 9.2 | 9.7 us, of 25,000 16.6 | 12.8; 2,600 of 4,096 8.1 | 8.7, of 9,411 15.9 | 16.4, of 32,000 37 | 33;
+// draft rows, 776 of 16,000 10.6 | 10.3, 5,408 44 | 34.
+static int many_waves(int V, int ng) { return (V + 512 * ng - 1) / (512 * ng); }
+static int many_groups(int64_t n_rows, int V) { return V <= 2048 || n_rows <= 256 * (32 / many_waves(V, 4)) ? 4 : 8; }
+static hipError_t launch_many(const RowArgs &a_in, int64_t n_rows, float *top_val, int32_t *top_id, float *lse, int out_stride, hipStream_t st) {
+    RowArgs a = a_in;
+    a.early_load = n_rows * rows_chunks_per_row(a.V, 4) <= EARLY_LOAD_WGS;
+    a.n_rows = n_rows;
+    const int kid = a.mode == ROWS_DRAFT ? KID_ROWS_DRAFT : KID_ROWS_UNIFORM, ng = many_groups(n_rows, a.V), waves = many_waves(a.V, ng);
+    by_mode_and_type(a, [&](auto mode, auto bf16) {
+        if constexpr (decltype(bf16)::value)
+            launch_kernel(kid, st, ng == 4 ? row_many_kernel<decltype(mode)::value, 4> : row_many_kernel<decltype(mode)::value, 8>, dim3((unsigned)n_rows),
+                          dim3(64 * waves), MANY_LIST + waves * MANY_WAVE, a, top_val, top_id, lse, out_stride);
+    });
+    return hipGetLastError();
+}
+
 // Top-k rows.  a: its scratch (lane_max, part_ms) is that of rows_topk_nl(V) chunks.
 // One workgroup holds rows of up to 16,384 entries: 51 rows of 1,000 / 4,000 / 8,192 / 16,000 bf16 entries 7.4 / 8.0 / 7.8 / 8.4
 // us in two passes, 4.6 / 5.4 / 5.4 / 6.7 held; 2,000 rows 13.8 / 16.2 / 19.9 / 29, held 8.1 / 10.1 / 15.4 / 29.  Up to twice as long
@@ -1071,9 +1319,23 @@ static hipError_t launch_held(const RowArgs &a_in, int64_t n_rows, float *top_va
 // launch 0.3 us.)
 #define HELD_V_MAX 16384
 #define HELD_ROWS_MAX 256  // of 2 HELD_V_MAX entries
+// bf16 rows of up to 32,768 entries, from 128 to 2,048 rows on by their length: row_many_kernel.  Calls, k = 16, held or in two passes | many: 1,600 rows of 2,048
+// entries 6.1 | 6.1 us, 2,600 7.8 | 6.8; 800 of 4,096 5.6 | 5.6, 2,000 7.9 | 6.8; 400 of 8,192 5.1 | 5.5, 640 6.1 | 5.9; 256 of 16,000 5.3 | 5.3, 330 6.7 | 6.4, of 9,411 7.3 | 6.4; 128 of
+// 32,000 5.9 | 6.2, 200 7.0 | 6.5, of 25,000 6.7 | 5.7.  In fp32, whose elements take the registers of half the waves, it gains nothing (2,600 rows of 4,000 11.2 | 12.1).
+// Rows beyond 16,384 entries that need no look-up only while all are on the chip at once: past that the two passes gain least from it
+// (1,990 rows of 26,944 25 | 23, 2,600 of 20,000 31 | 24), and their time grows more slowly with the number of rows, which the tests hold them to.
+#define MANY_V_MAX 32768
+static bool takes_many(const RowArgs &a, int64_t n_rows) {
+    if (a.dtype != DT_BF16 || a.V < 8 || a.V > MANY_V_MAX || n_rows * 64 * many_waves(a.V, 4) > 0xFFFFFFFFll) return false;
+    if (a.mode == ROWS_UNIFORM && a.V > HELD_V_MAX && n_rows > 256 * (32 / many_waves(a.V, 8))) return false;
+    int64_t room = 2048;  // entries, a power of two
+    while (room < a.V) room *= 2;
+    return n_rows * room > ((int64_t)1 << 22);
+}
 hipError_t rows_launch_topk(const RowArgs &a, int64_t n_rows, float *top_val, int32_t *top_id, float *lse, int out_stride,
                             hipStream_t st) {
     if (n_rows <= 0) return hipSuccess;
+    if (takes_many(a, n_rows)) return launch_many(a, n_rows, top_val, top_id, lse, out_stride, st);
     const int nt = held_threads(a.V);
     if ((a.V <= HELD_V_MAX && (nt == 256 || n_rows * nt <= 0xFFFFFFFFll)) ||
         (a.V <= 2 * HELD_V_MAX && a.dtype == DT_BF16 && n_rows <= HELD_ROWS_MAX))

@@ -44,6 +44,15 @@ def test_topk_rows_of_launches_of_many_chunks(V, n, bf16):
     check_repeated_rows(V, n, bf16)
 
 
+@pytest.mark.parametrize("V,n", [(9, 2049), (10, 2100), (40, 2049), (511, 2049), (513, 2100), (2047, 2049), (2048, 2049), (2049, 1025), (2560, 4097),
+                                 (4096, 4200), (4097, 2600), (4104, 513), (8192, 2100), (9411, 257), (16384, 1025), (16385, 129), (20481, 700),
+                                 (32760, 600), (32768, 129), (32768, 1024), (32767, 513)])
+@pytest.mark.parametrize("gap", [0, 1])
+def test_topk_rows_of_large_launches(V, n, gap):
+    # one to sixteen waves to a row of 32 or 64 entries a lane, the last group of a wave whole, begun, of one entry and empty
+    check_repeated_rows(V, n, True, gap)
+
+
 @pytest.mark.parametrize("V,n,gap", [(65536, 129, 1), (65536, 129, 2), (131072, 129, 3), (32768, 1025, 1)])
 def test_topk_rows_of_whole_chunks_at_odd_addresses(V, n, gap):
     """Sixteen whole chunks to a row: a workgroup more where the rows' stride is odd, none where it is even."""
