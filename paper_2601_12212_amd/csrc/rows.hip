@@ -159,8 +159,10 @@ __device__ __forceinline__ void chunk_finish(const RowArgs &a, int64_t g, int ba
         }
     }
     if (cend > V) {  // the row's last chunk
+        const int wave0 = __builtin_amdgcn_readfirstlane(base);
 #pragma unroll
         for (int n = 0; n < NL; ++n) {
+            if (wave0 + (n + 1) * 512 <= V) continue;  // uniform
             const int first = base + n * 512 - group_start(V, base + n * 512);  // eight and more: none of the group exists
 #pragma unroll
             for (int e = 0; e < 8; ++e) x[n * 8 + e] = e >= first ? x[n * 8 + e] : -INFINITY;
@@ -1089,16 +1091,19 @@ __global__ __launch_bounds__(1024, 8) void row_many_kernel(RowArgs a, float *top
 // ------------------------------------------------------------- arg max kernel (target rows) --
 // k = 1: every workgroup leaves the best (value, id) key of its chunk, and optionally the
 // (max, sum) pair of row/T; the acceptance kernel merges the chunks of a row.
+// Small vocabularies in large launches are bound by vector instructions: rows of one chunk have only the waves that they fill, groups that end inside the
+// row are not masked, the first of the best entries is looked for in the one group that has it, and the exponentials refer to the wave's maximum.
+// (7,686 rows of 1,728 entries, greedy: 266 instructions in each of four waves -> 125 in one, 17.2 -> 8.9 us; with sums 22.7 -> 8.3; 3,200 rows of 128,256 with sums, which were bound so too, 145 -> 126.)
 template <int NL, bool BF16, bool VEC>
 __global__ __launch_bounds__(256) void row_argmax_kernel(RowArgs a) {
     constexpr int E = 8 * NL;
     const int64_t g = (int64_t)blockIdx.z * gridDim.y + blockIdx.y;
     const int c = blockIdx.x;
-    const int lane = lane_id(), w = threadIdx.x >> 6;
+    const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), NW = blockDim.x >> 6;
     __shared__ u64 s_wout[4];
     __shared__ float s_m[4], s_s[4];
 
-    const int base = c * (256 * E) + w * (64 * E) + lane * 8;
+    const int wave0 = c * (256 * E) + w * (64 * E), base = wave0 + lane * 8;
     if (g >= a.n_rows) return;
     // early: the row's elements are on their way while the (dependent, scalar) reads of its metadata are waited for
     float x[E];
@@ -1106,39 +1111,54 @@ __global__ __launch_bounds__(256) void row_argmax_kernel(RowArgs a) {
     if (a.early_load) chunk_request<NL, BF16, VEC>(a, g, base, raw);
     const RowMeta meta = row_meta<ROWS_TARGET>(a, g);
     if (!meta.valid) return;
-    if (!a.early_load) chunk_request<NL, BF16, VEC>(a, g, base, raw);
-    chunk_finish<NL, BF16, VEC>(a, g, base, (c + 1) * (256 * E), raw, x);
-    float mx = x[0];
-#pragma unroll
-    for (int j = 1; j < E; ++j) mx = fmaxf(mx, x[j]);
-    if (a.want_lse) {
-        const float2 p = wave_lse_partial<E>(x, mx, a.inv_t);
-        if (lane == 0) { s_m[w] = p.x; s_s[w] = p.y; }
-    }
-    // the wave's best key: lanes holding the wave maximum find their first such element
-    const float T = wave_max(mx);
     u64 key = 0ull;
-    if (mx == T) {
-        int jbest = 0;
+    float T = -INFINITY, s = 0.f;
+    if (wave0 < a.V) {  // uniform
+        if (!a.early_load) chunk_request<NL, BF16, VEC>(a, g, base, raw);
+        chunk_finish<NL, BF16, VEC>(a, g, base, (c + 1) * (256 * E), raw, x);
+        float gmx[NL], mx = -INFINITY;
 #pragma unroll
-        for (int j = E - 1; j >= 0; --j) jbest = x[j] == T ? j : jbest;
-        const int id0 = base + (jbest >> 3) * 512;
-        key = make_key(T, (u32)((VEC ? group_start(a.V, id0) : id0) + (jbest & 7)));
+        for (int n = 0; n < NL; ++n) {
+            gmx[n] = x[8 * n];
+#pragma unroll
+            for (int e = 1; e < 8; ++e) gmx[n] = fmaxf(gmx[n], x[8 * n + e]);
+            mx = fmaxf(mx, gmx[n]);
+        }
+        T = wave_max(mx);
+        if (a.want_lse) {
+            const float cexp = 1.4426950408889634f * a.inv_t, nm = T == -INFINITY ? 0.f : -T * cexp;
+#pragma unroll
+            for (int j = 0; j < E; ++j) s += __builtin_amdgcn_exp2f(fmaf(x[j], cexp, nm));
+            s = wave_sum(s > 0.f ? s : 0.f);
+        }
+        // the wave's best key: the first group that holds its maximum, the first lane of that, the first such element
+#pragma unroll
+        for (int n = 0; n < NL; ++n) {
+            const u64 m = __builtin_amdgcn_ballot_w64(gmx[n] == T);
+            if (m && key == 0ull) {  // uniform
+                const int first = (int)__builtin_ctzll(m), id0 = wave0 + n * 512 + 8 * first;
+                int at = 0;
+#pragma unroll
+                for (int e = 7; e >= 0; --e) at = x[8 * n + e] == T ? e : at;
+                key = make_key(T, (u32)((VEC ? group_start(a.V, id0) : id0) + __builtin_amdgcn_readlane(at, first)));
+            }
+        }
     }
-    key = wave_max_u64(key);
-    if (lane == 0) s_wout[w] = key;
+    if (lane == 0) {
+        s_wout[w] = key;
+        s_m[w] = T;
+        s_s[w] = s;
+    }
     __syncthreads();
     if (threadIdx.x == 0) {
         const int64_t slot = g * gridDim.x + c;
-        u64 b01 = s_wout[0] > s_wout[1] ? s_wout[0] : s_wout[1];
-        u64 b23 = s_wout[2] > s_wout[3] ? s_wout[2] : s_wout[3];
-        a.part_keys[slot] = b01 > b23 ? b01 : b23;
+        for (int q = 1; q < NW; ++q) key = s_wout[q] > key ? s_wout[q] : key;
+        a.part_keys[slot] = key;
         if (a.want_lse) {
             const float cexp = 1.4426950408889634f * a.inv_t;
-            float M = s_m[0], S = s_s[0];
-#pragma unroll
-            for (int q = 1; q < 4; ++q) {
-                float M2 = fmaxf(M, s_m[q]);
+            float M = T, S = s;
+            for (int q = 1; q < NW; ++q) {
+                const float M2 = fmaxf(M, s_m[q]);
                 if (M2 != -INFINITY)
                     S = S * __builtin_amdgcn_exp2f((M - M2) * cexp) + s_s[q] * __builtin_amdgcn_exp2f((s_m[q] - M2) * cexp);
                 M = M2;
@@ -1354,7 +1374,9 @@ hipError_t rows_launch_argmax(const RowArgs &a_in, int64_t n_rows, int nl, hipSt
     const dim3 grid = rows_grid(rows_chunks_per_row(a.V, nl), n_rows);
     auto go = [&](auto bf16) {
         constexpr bool BF = decltype(bf16)::value;
-        auto launch = [&](auto kernel) { launch_kernel(KID_ROWS_TARGET, st, kernel, grid, dim3(256), 0, a); };
+        // a row of one chunk: the waves that it fills
+        const int threads = a.V <= 3 * 512 * nl ? 64 * ((a.V + 512 * nl - 1) / (512 * nl)) : 256;
+        auto launch = [&](auto kernel) { launch_kernel(KID_ROWS_TARGET, st, kernel, grid, dim3(threads), 0, a); };
         if (a.V < 8) launch(row_argmax_kernel<1, BF, false>);  // no 16-byte group: element loads
         else if (nl == 4) launch(row_argmax_kernel<4, BF, true>);
         else if (nl == 2) launch(row_argmax_kernel<2, BF, true>);
