@@ -88,13 +88,15 @@ __device__ __forceinline__ int sample_row_block(const AcceptArgs &a, int64_t g, 
     const int cstar = passed ? (int)__builtin_ctzll(passed) : massy ? 63 - (int)__builtin_clzll(massy) : 0;
     const double before = readlane_f64(cum - mass, cstar);
     const int epl = a.chunk_elems / 256;
-    const int lo = cstar * a.chunk_elems, hi = min(a.V, lo + a.chunk_elems);
-    const int id0 = lo + tid * epl;
+    const int begin = cstar * a.chunk_elems - row_shift(a.target, a.dtype == DT_BF16, a.V, a.row_stride, g);  // as the row kernel counts
+    const int lo = max(begin, 0), hi = min(a.V, begin + a.chunk_elems);
+    const int id0 = begin + tid * epl;
     const bool vec_ok = a.V >= 8;
     // a thread owns at most 32 entries (four octets): all asked for at once, their masses kept, so that the thread that
     // holds the crossing finds it in its registers
     float x[4][8];
     load_logits32(row, a.dtype, id0, epl, hi, vec_ok, x);
+    if (id0 < 0) x[0][0] = -INFINITY;
     double oct[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {

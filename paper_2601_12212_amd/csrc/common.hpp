@@ -47,6 +47,15 @@ __device__ __forceinline__ uint4 load16(const float *p) {
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 
+// A bf16 row of an odd vocabulary at an odd two-byte address is read from one entry before its first on (the last of the row before, masked), at
+// multiples of four bytes: the loads of such rows took more than twice as long, those at four-byte addresses as long as aligned ones (4,324
+// target rows of 9,664 / 9,665 / 9,666 entries 16.1 / 27.0 / 17.6 us, 1,024 of 128,256 / 128,257 / 128,258 40.4 / 54.0 / 39.8; 9,665 and 128,257 so 17.7 and 39.7).
+// Everything that finds a place in the row by chunk, lane and group counts from there.  (An even vocabulary may end with its last chunk; the
+// first row has nothing before it.)
+__device__ __forceinline__ int row_shift(const void *logits, bool bf16, int V, int64_t row_stride, int64_t g) {
+    return bf16 && (V & 1) && V >= 8 && g > 0 ? (int)(((uintptr_t)logits >> 1) + (uint64_t)(g * row_stride)) & 1 : 0;
+}
+
 // ---- wave64 primitives -------------------------------------------------------------------
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & 63); }
 

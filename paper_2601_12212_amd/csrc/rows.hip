@@ -158,8 +158,9 @@ __device__ __forceinline__ void chunk_finish(const RowArgs &a, int64_t g, int ba
             x[n * 4 + 2] = __uint_as_float(raw.r[n].z); x[n * 4 + 3] = __uint_as_float(raw.r[n].w);
         }
     }
+    const int wave0 = __builtin_amdgcn_readfirstlane(base);
+    if (BF16 && wave0 < 0) x[0] = base < 0 ? -INFINITY : x[0];  // the entry before the row (row_shift)
     if (cend > V) {  // the row's last chunk
-        const int wave0 = __builtin_amdgcn_readfirstlane(base);
 #pragma unroll
         for (int n = 0; n < NL; ++n) {
             if (wave0 + (n + 1) * 512 <= V) continue;  // uniform
@@ -213,7 +214,7 @@ __global__ __launch_bounds__(256) void row_stream_kernel(RowArgs a, int S) {
     const int64_t g = (int64_t)blockIdx.z * gridDim.y + blockIdx.y;
     const int c0 = blockIdx.x * CPW;
     const int lane = lane_id(), w = threadIdx.x >> 6;
-    const int base = c0 * (256 * E) + w * (64 * E) + lane * 8;
+    const int base = c0 * (256 * E) + w * (64 * E) + lane * 8 - row_shift(a.logits, BF16, a.V, a.row_stride, g);
     // (S stands at the end of the arguments: a comparison with it here cost launches of short chunks 1 %)
     if (g >= a.n_rows || c0 * (256 * E) >= a.V) return;
     // early: the row's elements are on their way while the (dependent, scalar) reads of its metadata are waited for
@@ -285,7 +286,7 @@ __device__ __forceinline__ int load_octet(const RowArgs &a, int64_t g, int id0, 
         for (int e = 0; e < 8; ++e) xv[e] = __uint_as_float(rr[e]);
     }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) xv[e] = start + e >= id0 ? xv[e] : -INFINITY;
+    for (int e = 0; e < 8; ++e) xv[e] = start + e >= max(id0, 0) ? xv[e] : -INFINITY;
     return start;
 }
 // smallest float whose ordered image has these upper 16 bits (the bin of -inf holds nothing else)
@@ -447,8 +448,9 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
     // Eight elements of lane maximum i (chunk, wave, pair of lanes), those of load n / 2 and lane n % 2 of the pair: the ones that
     // reach T become candidates, room for them with one LDS add.
     const int per_log2 = nl == 4 ? 3 : nl == 2 ? 2 : 1;  // groups of eight: chunk multipliers are 1, 2 or 4
+    const int shift = row_shift(a.logits, BF16, V, a.row_stride, g);
     auto octet_of = [&](int i, int n) {
-        return (i >> 7) * (256 * E) + ((i >> 5) & 3) * (64 * E) + (2 * (i & 31) + (n & 1)) * 8 + (n >> 1) * 512;
+        return (i >> 7) * (256 * E) + ((i >> 5) & 3) * (64 * E) + (2 * (i & 31) + (n & 1)) * 8 + (n >> 1) * 512 - shift;
     };
     auto reread = [&](int i, int n, float T) {
         float xv[8];
@@ -689,7 +691,7 @@ __global__ __launch_bounds__(NT, NL == 4 ? 4 : 8) void row_topk_kernel(RowArgs a
     const bool lse_wg = NT == 1024 && a.lse_apart && (int64_t)blockIdx.x >= a.n_rows;
     const int64_t g = lse_wg ? (int64_t)blockIdx.x - a.n_rows : (int64_t)blockIdx.x;
     const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int V = a.V, base = w * (64 * E) + lane * 8;
+    const int V = a.V, base = w * (64 * E) + lane * 8 - row_shift(a.logits, BF16 && VEC, a.V, a.row_stride, g);
     RawChunk<NL, BF16> raw;
     if (a.early_load) chunk_request<NL, BF16, VEC>(a, g, base, raw);
     const RowMeta meta = row_meta<MODE>(a, g);
@@ -875,7 +877,7 @@ __global__ __launch_bounds__(1024, 8) void row_many_kernel(RowArgs a, float *top
     constexpr int WAVE = 512 * NG;  // entries of a wave
     const int64_t g = blockIdx.x;
     const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6), NW = blockDim.x >> 6;
-    const int V = a.V, wave0 = w * WAVE, base = wave0 + lane * 8;
+    const int V = a.V, wave0 = w * WAVE - row_shift(a.logits, true, a.V, a.row_stride, g), base = wave0 + lane * 8;
     RawChunk<NG, true> raw;
     const bool early = MODE == ROWS_UNIFORM || a.early_load;
     if (early) chunk_request<NG, true, true>(a, g, base, raw);
@@ -906,6 +908,7 @@ __global__ __launch_bounds__(1024, 8) void row_many_kernel(RowArgs a, float *top
             x[2 * p] = __uint_as_float(rr[p] << 16);
             x[2 * p + 1] = __uint_as_float(rr[p] & 0xFFFF0000u);
         }
+        if (n == 0 && wave0 < 0) x[0] = lane == 0 ? -INFINITY : x[0];
         if (wave0 + (n + 1) * 512 > V) {  // uniform: reaches past the row's end
             const int id0 = base + n * 512, first = id0 - group_start(V, id0);
 #pragma unroll
@@ -996,7 +999,7 @@ __global__ __launch_bounds__(1024, 8) void row_many_kernel(RowArgs a, float *top
         const int q = s_hot[min((q0 + lane) >> 3, hot - 1)];
         const int id0 = wave0 + q * 8, id = group_start(V, id0) + (lane & 7);
         const float v = entry(id);
-        const bool in = v >= T1 && id >= id0 && q0 + lane < 8 * hot;
+        const bool in = v >= T1 && id >= max(id0, 0) && q0 + lane < 8 * hot;
         const u64 m = __builtin_amdgcn_ballot_w64(in);
         if (m) {
             int at = 0;
@@ -1103,7 +1106,7 @@ __global__ __launch_bounds__(256) void row_argmax_kernel(RowArgs a) {
     __shared__ u64 s_wout[4];
     __shared__ float s_m[4], s_s[4];
 
-    const int wave0 = c * (256 * E) + w * (64 * E), base = wave0 + lane * 8;
+    const int wave0 = c * (256 * E) + w * (64 * E) - row_shift(a.logits, BF16 && VEC, a.V, a.row_stride, g), base = wave0 + lane * 8;
     if (g >= a.n_rows) return;
     // early: the row's elements are on their way while the (dependent, scalar) reads of its metadata are waited for
     float x[E];
@@ -1140,7 +1143,8 @@ __global__ __launch_bounds__(256) void row_argmax_kernel(RowArgs a) {
                 int at = 0;
 #pragma unroll
                 for (int e = 7; e >= 0; --e) at = x[8 * n + e] == T ? e : at;
-                key = make_key(T, (u32)((VEC ? group_start(a.V, id0) : id0) + __builtin_amdgcn_readlane(at, first)));
+                // (a row without a finite entry: its first, not the one before it)
+                key = make_key(T, (u32)max((VEC ? group_start(a.V, id0) : id0) + __builtin_amdgcn_readlane(at, first), 0));
             }
         }
     }
@@ -1223,11 +1227,10 @@ static const int64_t EARLY_LOAD_WGS = 2048;
 // 53.8 | 60.6.
 static const int64_t PAIR_CHUNKS = 16384;
 // How many workgroups a row has in launches bound by bandwidth.  They go to the eight XCDs in turn: with sixteen, or eight of two chunks, a
-// row's last, shorter one falls to the same XCD in every row, and rows that begin at odd two-byte addresses are read a fifth slower (why
-// has not been found; dealing each row's chunks out from another place on does not help).  One more, which leaves at once, deals every
-// chunk to every XCD.  Sixteen | seventeen, calls of 16,000 chunks of 128,257 bf16 entries 60.3 | 49.7 us, of 65,001 31.9 | 27.9, of 128,256 48.9 | 47.7, of 64,960 27.7 | 26.0;
-// eight | nine, 32 sequences' steps of 125,001 331 | 307, of 119,331 303 | 277; six | seven, of two chunks, of 93,001 245 | 238.  It costs where the
-// last one is whole (65,536 27.7 | 28.1, 98,304 in twelve 36.6 | 37.6), and with ten, twelve or fourteen of one chunk gains nothing: 93,001 73.1 | 74.0, 109,001 80.8 | 85.9.
+// row's last, shorter one falls to the same XCD in every row.  One more, which leaves at once, deals every chunk to every XCD.  Sixteen | seventeen, calls
+// of 1,000 rows of 128,257 bf16 entries 48.8 | 47.8 us, of 128,256 49.2 | 48.4, of 125,001 50.9 | 47.2, of 65,001 30.1 | 29.2; eight | nine, draft rows of 61
+// sequences of 125,001 504 | 489, of 119,331 489 | 467.  With ten, twelve or fourteen it gains nothing, and it costs where the
+// last one is whole (65,536 27.7 | 28.1, 98,304 in twelve 36.6 | 37.6).
 static int workgroups_per_row(const RowArgs &a, int64_t S, int nl, int cpw) {
     const int wgs = (int)((S + cpw - 1) / cpw);
     const bool last_is_whole = a.V % (256 * 8 * nl * cpw) == 0 && a.row_stride % 2 == 0;

@@ -47,7 +47,7 @@ def test_topk_rows_of_launches_of_many_chunks(V, n, bf16):
 @pytest.mark.parametrize("V,n", [(9, 2049), (10, 2100), (40, 2049), (511, 2049), (513, 2100), (2047, 2049), (2048, 2049), (2049, 1025), (2560, 4097),
                                  (4096, 4200), (4097, 2600), (4104, 513), (8192, 2100), (9411, 257), (16384, 1025), (16385, 129), (20481, 700),
                                  (32760, 600), (32768, 129), (32768, 1024), (32767, 513)])
-@pytest.mark.parametrize("gap", [0, 1])
+@pytest.mark.parametrize("gap", [0, 1, 2])
 def test_topk_rows_of_large_launches(V, n, gap):
     # one to sixteen waves to a row of 32 or 64 entries a lane, the last group of a wave whole, begun, of one entry and empty
     check_repeated_rows(V, n, True, gap)
@@ -154,6 +154,44 @@ def test_topk_rows_at_any_two_byte_address(V):
     torch.cuda.synchronize()
     wval, widx, _ = ref.topk_rows(np.ascontiguousarray(buf[:, 1:V + 1]), k)
     assert np.array_equal(idx.cpu().numpy(), widx) and np.array_equal(val.cpu().numpy(), wval)
+
+
+@pytest.mark.parametrize("V", [7, 9, 301, 2047, 8193, 16383, 20001, 40001, 128257])
+@pytest.mark.parametrize("gap", [0, 2])
+def test_topk_rows_of_odd_vocabularies(V, gap):
+    # every other row begins at an odd two-byte address and is read from the entry before it on (with a gap a large one)
+    check_repeated_rows(V, 14, True, gap) if V > 8 else check_topk(dt_synth.f32_to_bf16_bits(np.random.default_rng(V).standard_normal((14, V)).astype(np.float32)), 3)
+
+
+@pytest.mark.parametrize("V", [7, 9, 301, 2049, 8193, 16383, 20001, 128257])
+@pytest.mark.parametrize("mode", [dt_synth.GREEDY, dt_synth.STOCHASTIC, dt_synth.SAMPLED])
+def test_target_rows_at_odd_addresses(V, mode):
+    # the same rows at even and at odd two-byte addresses behind a large entry: the best first, last, everywhere, nowhere
+    from paper_2601_12212_amd.step import Step
+    B, TT = 3, 24
+    st = Step([(TT, 4, 5)] * B, [1] * B, 1, 1, 64, V, mode=mode, temperature=0.7)
+    gen = torch.Generator("cuda").manual_seed(V)
+    st.draft_logits.copy_(torch.randn(st.draft_logits.shape, generator=gen, device="cuda") * 2)
+    st.build_tree()
+    x = (torch.randn((B, TT, V), generator=gen, device="cuda") * 2).bfloat16()
+    x[:, 1, 0] = 30.0
+    x[:, 2, V - 1] = 30.0
+    x[:, 3] = 1.0
+    if mode == dt_synth.GREEDY:
+        x[:, 4] = -float("inf")
+    got = []
+    for gap in (7, 2):  # V is odd: rows at even and at odd addresses
+        st.target_logits = torch.nn.functional.pad(x, (0, gap), value=100.0)[:, :, :V]
+        st.accept()
+        torch.cuda.synchronize()
+        got.append([t.clone() for t in (st.accept_len, st.best_node, st.path_nodes, st.out_tokens, st.node_argmax)])
+    for even, odd in zip(*got):
+        assert torch.equal(even, odd)
+    if mode != dt_synth.SAMPLED:
+        n = st.n_nodes.tolist()
+        for b in range(B):
+            # the first of equal entries
+            assert torch.equal(got[1][4][b, :n[b]].long().cpu(), torch.from_numpy(np.argmax(x[b, :n[b]].float().cpu().numpy(), axis=1)))
 
 
 def test_a_launch_of_more_threads_than_one_grid_dimension_takes():
