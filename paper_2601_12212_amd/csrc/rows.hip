@@ -1363,7 +1363,11 @@ hipError_t rows_launch_topk(const RowArgs &a, int64_t n_rows, float *top_val, in
     if ((a.V <= HELD_V_MAX && (nt == 256 || n_rows * nt <= 0xFFFFFFFFll)) ||
         (a.V <= 2 * HELD_V_MAX && a.dtype == DT_BF16 && n_rows <= HELD_ROWS_MAX))
         return launch_held(a, n_rows, top_val, top_id, lse, out_stride, st);
-    const int nl = rows_topk_nl(a.V);
+    // Chunks of 4,096 entries, for launches that have too few of 8,192, cost larger ones 3 to 18 %: calls of 1,000 rows of 50,257 entries, 4,096 | 8,192, 25.3 | 23.4 us,
+    // of 65,536 29.3 | 26.9, 200 of 36,000 9.0 | 9.1, fp32 500 of 40,001 21.9 | 21.9, 1,000 38.8 | 36.6; draft rows 776 of 64,960 31.8 | 26.0, 10,309 293 | 264.  (The scratch
+    // was sized for the smaller ones.)
+    int nl = rows_topk_nl(a.V);
+    if (nl == 2 && n_rows * rows_chunks_per_row(a.V, 4) > EARLY_LOAD_WGS) nl = 4;
     const hipError_t e = launch_stream(a, n_rows, nl, st);
     return e != hipSuccess ? e : launch_select(a, n_rows, nl, top_val, top_id, lse, out_stride, st);
 }

@@ -46,10 +46,11 @@ def test_topk_rows_of_launches_of_many_chunks(V, n, bf16):
 
 @pytest.mark.parametrize("V,n", [(9, 2049), (10, 2100), (40, 2049), (511, 2049), (513, 2100), (2047, 2049), (2048, 2049), (2049, 1025), (2560, 4097),
                                  (4096, 4200), (4097, 2600), (4104, 513), (8192, 2100), (9411, 257), (16384, 1025), (16385, 129), (20481, 700),
-                                 (32760, 600), (32768, 129), (32768, 1024), (32767, 513)])
+                                 (32760, 600), (32768, 129), (32768, 1024), (32767, 513), (32769, 410), (40961, 342), (65535, 257), (65536, 257)])
 @pytest.mark.parametrize("gap", [0, 1, 2])
 def test_topk_rows_of_large_launches(V, n, gap):
-    # one to sixteen waves to a row of 32 or 64 entries a lane, the last group of a wave whole, begun, of one entry and empty
+    # one to sixteen waves to a row of 32 or 64 entries a lane, the last group of a wave whole, begun, of one entry and empty; and
+    # chunks of 8,192 entries, five to eight to a row
     check_repeated_rows(V, n, True, gap)
 
 
