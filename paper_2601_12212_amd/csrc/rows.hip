@@ -393,13 +393,12 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
     // are any).  So the waves share what is read again also where the best are in one part of the row: with a quarter of the row to a wave,
     // 51 rows of 128,256 bf16 entries, k = 28, that fall by 12 along the row 13.0 us, 9.35 so, by ln(1 + id) 12.8 and 10.2, evenly spread ones 9.3 and 9.1.
     struct alignas(4 * sizeof(LM)) Quad { LM v[4]; };
-    float it[8];
+    // (As they came: converted here, they were waited for before the metadata was asked for, a trip more.  Traced inside steps: 51 rows of 128,256 4.85 ->
+    // 4.56 us, 569 6.14 -> 5.93, ten of a level 4.92 -> 4.61.)
+    Quad q[2];
     if (S <= 16) {
-        Quad q[2];
 #pragma unroll
         for (int i = 0; i < 2; ++i) q[i] = ((const Quad *)lm)[4 * min(64 * i + lane, 8 * S - 1) + w];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) it[j] = lane_max_value<BF16>(q[j >> 2].v[j & 3]);
     }
     const bool lse_wave = w == 3 && a.want_lse && lse;
     float2 pm = make_float2(-INFINITY, 0.f);
@@ -478,10 +477,10 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
     };
 
     // ---- 1. thread maxima and T -------------------------------------------------------------------
-    float tmax = -INFINITY;
+    float it[8], tmax = -INFINITY;
     if (S <= 16) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) it[j] = 64 * (j >> 2) + lane < 8 * S ? it[j] : -INFINITY;
+        for (int j = 0; j < 8; ++j) it[j] = 64 * (j >> 2) + lane < 8 * S ? lane_max_value<BF16>(q[j >> 2].v[j & 3]) : -INFINITY;
         tmax = spread_max(it);
     } else {
         for (int i = tid; i < n_lm; i += 256) tmax = fmaxf(tmax, lane_max_value<BF16>(lm[i]));
