@@ -1552,9 +1552,11 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_wave_kernel(AttnArgs a, int K
 // is used and before the node count that says which rows exist (a loop that waited for each partial's statistics and then
 // for its values was up to six trips to memory long: 4.7 us on the 8B shape with three splits).  Fewer than four are read as
 // what they are: the last one again, weighed by zero, in the place of a missing fourth turned an infinity of that split into a
-// NaN, and its loads cost 0.4 us a launch (32 layers of the 8B shape, three splits: 380 us; this: 367).
+// NaN, and its loads cost 0.4 us a launch (32 layers of the 8B shape, three splits: 380 us; this: 367).  Two waves to a SIMD are
+// enough of them: with registers for more the compiler asks for the last of three partials when the first are there (the same layers with that
+// and the node count in front 365 us, the count behind 356, this 352).
 template <int D>
-__global__ __launch_bounds__(2 * D) void attn_wave_merge_kernel(AttnArgs a, int KS, SplitBuf sb) {
+__global__ __launch_bounds__(2 * D) __attribute__((amdgpu_waves_per_eu(1, 2))) void attn_wave_merge_kernel(AttnArgs a, int KS, SplitBuf sb) {
     constexpr int DBLK = D / 32;
     const int G = a.Hq / a.Hkv;
     const int b = blockIdx.z, h = blockIdx.x;
@@ -1564,7 +1566,10 @@ __global__ __launch_bounds__(2 * D) void attn_wave_merge_kernel(AttnArgs a, int 
     const int mq = m0 + col;
     const float c = a.scale * 1.4426950408889634f;
     const int64_t unit = ((int64_t)b * a.Hkv + h) * gridDim.y + blockIdx.y;
-    const int n_raw = a.n_nodes[b];
+    // By a vector load: a scalar one is waited for with the kernel's arguments, in front of the partials' loads.
+    int zero;
+    asm volatile("v_mov_b32 %0, 0" : "=v"(zero));
+    const int n_raw = a.n_nodes[b + zero];
     float M = -INFINITY, Lsum = 0.f;
     float res[16];
 #pragma unroll
