@@ -1990,12 +1990,14 @@ static int64_t max_blocks(const AttnArgs &a) { return ((int64_t)a.max_prefix_len
 //     2 kv heads, 6 of 32): ragged 400 keys 18.5 | 17.0 | 16.6, 1,100 32.3 | 30.8 | 27.1, 1,600 36.0 | 39.0 | 32.9, 2,400 46.8 | 56.9 | 46.9, 4,000 57 | 86 | 68; equal 1,600
 //     43.0 | 43.5 | 37.2.  With the caches in the last level, balanced | four: ragged 1,600 30.5 | 29.5, 2,400 39.8 | 40.3; one sequence of 1,600 among 11 of 200 31.2 | 30.0,
 //     of 2,400 33.6 | 40.3;
-//   few tiles (112 and fewer) in up to 512 units: where sequences end early, or their trees are smaller than the largest, the units that are left often have a compute unit
+//   few tiles (144 and fewer) in up to 400 units: where sequences end early, or their trees are smaller than the largest, the units that are left often have a compute unit
 //     each, and few tiles are as long as the longest sequence.  Ragged, small-batch | whole: 260 to 320 units 8.2 | 11.5, 9.2 | 13.2, 11.3 | 11.2, 12.1 | 17.2, 13.0 | 10.0, 16.6 |
-//     20.5, 21.5 | 20.7 (22 shapes on average 0.95 the time), 336 to 400 units beyond 32 blocks 15.4 | 21.0, 19.8 | 22.8, equal 28.4 | 25.9; up to 32 blocks 17.1 | 15.8, 13.2 | 11.1, 16.8 | 14.2.
+//     20.5, 21.5 | 20.7 (22 shapes on average 0.95 the time); 336 to 400 units beyond 32 blocks 15.4 | 21.0, 19.8 | 22.8, 22.4 | 25.6, equal 28.4 | 25.9, up to 32 blocks 17.1 | 15.8,
+//     13.2 | 11.1, 16.8 | 14.2; 448 to 512 units beyond 32 blocks 22.7 | 23.2, 24.4 | 23.9, 25.5 | 22.7, 28.5 | 28.5, equal 39.0 | 33.7.
 #define SMALL_UNITS 256
-#define FEW_TILES 112
-#define FEW_TILES_UNITS 320
+#define FEW_TILES 144
+#define FEW_TILES_UNITS 320        // at any length
+#define FEW_TILES_UNITS_LONG 400   // beyond FEW_TILES_BLOCKS
 #define FEW_TILES_BLOCKS 32
 #define WHOLE_BLOCKS 40
 #define WHOLE_BLOCKS_ONE 56
@@ -2072,8 +2074,8 @@ int attn_launch(const AttnArgs &a, hipStream_t st, hipError_t *err) {
     const int64_t units = (int64_t)a.batch * a.Hkv * mblocks;
     if (units <= SMALL_UNITS || (base_wgs < 128 && !gang)) return wave_launch<128>(a, st, err);
     const bool one = base_wgs <= a.n_cu;
-    if (base_wgs <= FEW_TILES && units <= 2 * SMALL_UNITS && max_blocks(a) <= WHOLE_BLOCKS_ONE &&
-        (units <= FEW_TILES_UNITS || max_blocks(a) > FEW_TILES_BLOCKS))
+    if (base_wgs <= FEW_TILES && max_blocks(a) <= WHOLE_BLOCKS_ONE &&
+        units <= (max_blocks(a) > FEW_TILES_BLOCKS ? FEW_TILES_UNITS_LONG : FEW_TILES_UNITS))
         return wave_launch<128>(a, st, err);
     if (!gang || max_blocks(a) <= (one ? WHOLE_BLOCKS_ONE : WHOLE_BLOCKS)) {
         const dim3 grid(a.Hkv, mtiles, a.batch);
