@@ -289,10 +289,17 @@ def test_whole_tiles_of_every_length(B):
     check_case(oracle_case(0, cfg=_cfg("bf16", 128, [(TT, 5, 6)] * B, lens[:B], 8, 8)))
 
 
-# 136 tiles, a compute unit to each, are whole up to 56 blocks of 32 keys
+# 152 tiles, a compute unit to each, are whole up to 56 blocks of 32 keys
 @pytest.mark.parametrize("L", [1752, 1753])
 def test_line_of_a_tile_to_each_compute_unit(L):
-    check_case(oracle_case(0, cfg=_cfg("bf16", 128, [(40, 5, 6)] * 17, [L] + [7 + 100 * b for b in range(1, 17)], 8, 8)))
+    check_case(oracle_case(0, cfg=_cfg("bf16", 128, [(40, 5, 6)] * 19, [L] + [7 + 90 * b for b in range(1, 19)], 8, 8)))
+
+
+# few tiles: up to 144 the small-batch kernel keeps 320 row blocks, and 400 from 33 blocks of 32 keys on (152 tiles of 304 row blocks; 120 of 400 at 32 and
+# 33 blocks, of 440; 144 of 288 at 56 and 57)
+@pytest.mark.parametrize("Hq,B,TT,L", [(8, 19, 40, 300), (8, 18, 40, 300), (32, 5, 80, 944), (32, 5, 80, 945), (32, 5, 81, 1000), (8, 18, 40, 1752), (8, 18, 40, 1753)])
+def test_lines_of_few_tiles(Hq, B, TT, L):
+    check_case(oracle_case(0, cfg=_cfg("bf16", 128, [(TT, 5, 6)] * B, [L] + [7 + 40 * (b % 5) for b in range(1, B)], Hq, 8)))
 
 
 # 256 (sequence, kv head, 32-row block)s, which the small-batch kernel takes, and 264, which the kernel of whole tiles takes up to 40 blocks of 32 keys and the
@@ -303,7 +310,7 @@ def test_lines_between_the_three_kernels(B, L):
 
 
 # Shapes of the kernel of whole tiles, and of the balanced schedule with sequences whole and cut.
-FAR = {"whole tiles": (8, 8, [60, 300, 700] + [10] * 30), "whole tiles, a compute unit each": (8, 8, [60, 300, 1100] + [10] * 14), "schedule, whole": (8, 8, [1250, 300, 700] + [10] * 30),
+FAR = {"whole tiles": (8, 8, [60, 300, 700] + [10] * 30), "whole tiles, a compute unit each": (8, 8, [60, 300, 1100] + [10] * 16), "schedule, whole": (8, 8, [1250, 300, 700] + [10] * 30),
        "schedule, cut": (64, 8, [1700, 1700, 1500, 1600])}
 
 
