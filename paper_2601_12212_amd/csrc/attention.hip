@@ -428,8 +428,8 @@ __device__ __forceinline__ bool tile_segment(const AttnArgs &a, const GroupDiv &
             for (int i = 0; i < 16; ++i) S.v[j][i] = ((vis >> (8 * (i >> 2) + (i & 3))) & 1u) ? S.v[j][i] : -INFINITY;
         }
     };
-    // m_run is a reference, not the running maximum: the maximum of the range's first block, and it stays (0 where that block is
-    // hidden).  Later scores may lie above it, and their probabilities above 1, which neither 32-bit sums nor bf16's relative precision
+    // m_run is a reference, not the running maximum: the maximum of the range's first block, and it stays (unless one of the wave's
+    // queries sees nothing there).  Later scores may lie above it, and their probabilities above 1, which neither 32-bit sums nor bf16's relative precision
     // mind as long as everything stays a number: sums of a lane's probabilities up to NEAR_LIMIT cannot hurt; above that the range's accumulators are
     // looked at when it ends, and past REF_LIMIT, or if one of them is not finite, the workgroup goes through the range once more (`exact`).  Then the
     // reference moves when a block's maximum lies more than LAZY_LOG2 binary orders above it, so that probabilities stay below 2^LAZY_LOG2,
@@ -658,7 +658,9 @@ __device__ __forceinline__ bool tile_segment(const AttnArgs &a, const GroupDiv &
         K_WAIT(14, 1) QK_MFMA(14) FENCE K_WAIT(15, 0) QK_MFMA(15)
         mask(kb0, S0);
         move_reference(block_max(S0));
-        if (!exact && m_run == -INFINITY) m_run = 0.f;  // what nmc says
+        // Nothing of the block for some query (a range that begins among the tree's keys, a mask without them): no reference to stay with, and the scores to
+        // come may be so low that 0 in its place would leave nothing of them.  This wave's moves.
+        exact = exact || __builtin_amdgcn_ballot_w64(m_run == -INFINITY) != 0;
         asm volatile("" ::: "memory");
     }
     if constexpr (NS == 2) {

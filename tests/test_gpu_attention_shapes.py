@@ -366,3 +366,56 @@ def test_values_near_the_end_of_the_exponents(shape):
         # one bf16 ulp of the result: a range gone through again has another reference
         assert bool(((got - clean)[:, :, others].abs() <= clean[:, :, others].abs() * 2.0 ** -7 + 1e-6).all()), (value, t)
         st.v_prefix[0][t] = keep
+
+
+def low_scores(cfg, st, b, n, L, mask=None, samples=None):
+    """Sequence b with its first n nodes and L prefix keys: scores around -80, -89, -100 and -200 in turn from kv head to kv head, the tree's keys
+    some natural units above the prefix's, so that both have weight.  Against the oracle."""
+    q, kt, vt, kp, vp = (dt_synth.as_f32(x).copy() for x in dt_synth.qkv(cfg, b))
+    q, kt, vt, kp, vp = q[:n], kt[:n], vt[:n], kp[:L], vp[:L]
+    q[:] = 1.0
+    level = np.array([-80.0, -89.0, -100.0, -200.0], np.float32)[np.arange(cfg.Hkv) % 4]
+    per_unit = np.float32(1.0 / (st.scale * cfg.D))
+    for k, above in ((kp, 0.0), (kt, np.log(max(L, 1)) - 1.0)):
+        k *= 0.3
+        k += ((level + np.float32(above)) * per_unit)[None, :, None]
+    ops = [dt_synth.f32_to_bf16_bits(x) for x in (q, kt, vt, kp, vp)]
+    st.set_qkv(b, *ops)
+    st.prefix_len[b] = L
+    words = np.zeros((n, 2), np.uint64)
+    for i in range(n):
+        for j in mask(i):
+            words[i, j // 64] |= np.uint64(1) << np.uint64(j % 64)
+    st.anc_mask[b, :n] = torch.from_numpy(words.view(np.int64)).cuda()
+    st.n_nodes[b] = n
+    st.tree_attention()
+    got = st.out[b, :n].float().cpu().numpy()
+    want = ref.tree_attention(*ops, words, st.scale, samples=samples)
+    if samples is not None:
+        got = got[samples[:, 0], samples[:, 1]]
+    # a few keys with nearly all the weight: the bound of scores that climb, above
+    assert_attention(got, want, "bf16", "%d keys" % L, own_abs=1e-2)
+
+
+def test_key_ranges_that_begin_behind_what_a_query_sees():
+    # Trees of 128 nodes over 64 n + 20 prefix keys have three blocks of tree keys, and some of these plans cut in front of the second.  A node of the third whose
+    # ancestors are in the first then finds nothing in its range's first block, and scores far below 0 behind it.
+    plen = [2900, 1900, 2300]
+    cfg = _cfg("bf16", 128, [(128, 8, 20)] * 3, plen, 64, 8)
+    case = oracle_case(0, cfg=cfg)
+    st = make_step(case)
+    st.build_tree()
+    samples = np.array([(i, 8 * h + i % 8) for i in (0, 43, 44, 107, 108, 113, 120, 127) for h in range(8)], np.int32)
+    for L in range(1428, 2900, 64):
+        low_scores(cfg, st, 0, 128, L, mask=lambda i: {0, i // 8, i}, samples=samples)
+
+
+@pytest.mark.parametrize("Hq,Hkv,B,bound", [(8, 8, 33, 100), (8, 8, 19, 100), (64, 8, 4, 2600)], ids=["whole tiles", "whole tiles, a compute unit each", "schedule"])
+def test_masks_that_hide_the_first_block(Hq, Hkv, B, bound):
+    # no prefix, or a few keys of one, and nodes that see themselves and one more behind the first 64 keys
+    cfg = _cfg("bf16", 128, [(128, 8, 20)] + [(40, 4, 6)] * (B - 1), [bound] * B, Hq, Hkv)
+    case = oracle_case(0, cfg=cfg)
+    st = make_step(case)
+    st.build_tree()
+    for L, n in ((0, 128), (0, 66), (1, 128), (40, 120)):
+        low_scores(cfg, st, 0, n, L, mask=lambda i: {i, max(i - 3, 0)} if i >= 64 else {i})
