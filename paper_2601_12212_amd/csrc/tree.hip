@@ -98,16 +98,18 @@ struct TreeLds {
     int p_end, n_exp, memn;
 };
 
-// What the expansion of level l hands on to that of level l + 1 when the tree is built level by level: the nodes it chose, the
+// What the expansion of level l hands on to that of level l + 1 when the tree is built level by level: the nodes it chose, how many, the
 // token count, and which level it was.  It lies in the last rows of the sequence's state, which belong to the deepest level's pass and are
-// free until then.  Without it, or with another level's (a level asked for twice), the levels before are gone through again, from the
-// row results.  Each level gone through again took 0.5 us with k up to 16 and 1.7 beyond.  All calls of a step, replayed: (60, 6, 10), 128,256 tokens
+// free until then.  Without it, or with another level's (a level asked for again), the levels before are gone through again, from the
+// row results.  (How many, in the same word as the level: the state's own count is that of the last call, which may have been a later level's.)  Each level gone through again took 0.5 us with k up to 16 and 1.7 beyond.  All calls of a step, replayed: (60, 6, 10), 128,256 tokens
 // 78.2 -> 74.7 us (with the kernels of their own); 16 sequences of up to (123, 8, 23), 1,152 tokens 125.6 -> 101.7; 4 of (66, 3, 8) 32.0 -> 31.7.
 #define CARRY_ROW (DT_STATE_ROWS - 4)  // four rows of values: DT_K_MAX Parents; two words of the ids
 #define CARRY_FROM 2  // level 1 expands the root's children: nothing to go through
 #define CARRY_LEVELS ((CARRY_ROW - 1) / DT_K_MAX)  // levels whose nodes' rows, at most l DT_K_MAX, end before it
 static_assert(4 * DT_K_MAX * sizeof(float) == DT_K_MAX * sizeof(Parent), "four rows");
-__device__ __forceinline__ int carry_tag(int level) { return 0x7A5C3000 | level; }
+#define CARRY_COUNT 0x3F0  // where the tag holds the number of nodes
+__device__ __forceinline__ int carry_tag(int level, int n_exp) { return 0x7A5C3000 | n_exp << 4 | level; }
+static_assert(DT_D_MAX < 16 && DT_K_MAX <= CARRY_COUNT >> 4, "the tag's fields");
 __device__ __forceinline__ int64_t carry_at(int64_t seq_rows, int b) { return (b * seq_rows + CARRY_ROW) * DT_K_MAX; }
 // The level to start from, its nodes and the token count: level 0, nothing.
 struct Start {
@@ -288,6 +290,10 @@ __device__ __forceinline__ int choose_first(TreeLds &S, int k, float sc) {
     if ((m >> lane) & 1ull) put_parent(S, 1, (int)lanes_below(m), sc, lane, 0ull);
     return __popcll(m);
 }
+// The head of what level l hands on, by one thread.
+__device__ __forceinline__ void carry_head(const TreeArgs &a, int b, int l, int n_exp, int tok_count) {
+    if (l >= CARRY_FROM && l <= CARRY_LEVELS) *(int2 *)(a.state_id + carry_at(a.seq_rows, b)) = make_int2(carry_tag(l, n_exp), tok_count);
+}
 // What the draft model is handed for its next pass, by one wave: node s of the set chosen at level l.
 __device__ __forceinline__ void emit_level(const TreeArgs &a, const TreeLds &S, int b, int l, int k, int n_exp, int tok_count) {
     const int lane = lane_id();
@@ -317,7 +323,7 @@ __device__ __forceinline__ void emit_level(const TreeArgs &a, const TreeLds &S, 
     if (lane == 0) {
         a.n_expand[b] = n_exp;
         a.state_n_exp[b] = n_exp;
-        if (carry) *(int2 *)(a.state_id + at) = make_int2(carry_tag(l), tok_count);
+        carry_head(a, b, l, n_exp, tok_count);
     }
 }
 
@@ -403,7 +409,11 @@ __device__ __forceinline__ int levels_narrow(const TreeArgs &a, TreeLds &S, int 
         }
     }
     if (xl > 0) {  // an earlier level had nothing viable to expand, or the token count ended the expansion
-        if (lane == 0) { a.n_expand[b] = 0; a.state_n_exp[b] = 0; }
+        if (lane == 0) {
+            a.n_expand[b] = 0;
+            a.state_n_exp[b] = 0;
+            carry_head(a, b, xl, 0, tok_count);
+        }
         return -1;
     }
     return p_end;
@@ -537,7 +547,11 @@ __device__ __forceinline__ int levels_wide(const TreeArgs &a, TreeLds &S, int b,
         p_end = nlo + kk;
     }
     if (xl > 0) {
-        if (tid == 0) { a.n_expand[b] = 0; a.state_n_exp[b] = 0; }
+        if (tid == 0) {
+            a.n_expand[b] = 0;
+            a.state_n_exp[b] = 0;
+            carry_head(a, b, xl, 0, tok_count);
+        }
         return -1;
     }
     return p_end;
@@ -702,12 +716,10 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
     // what the level before has left, in the same trip
     const int xl = EXPAND ? a.expand_level : 0;  // > 0: only the nodes of level xl that are expanded next
     int2 head = make_int2(0, 0);
-    int carried = 0;
     uint4 node = make_uint4(0, 0, 0, 0);
     if (xl > CARRY_FROM) {
         const int64_t at = carry_at(a.seq_rows, b);
         head = *(const int2 *)(a.top_id + at);
-        carried = a.state_n_exp[b];
         node = ((const uint4 *)(a.top_val + at))[tid & (DT_K_MAX - 1)];
     }
     extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];  // 135 KB: more than a static array may hold
@@ -752,8 +764,9 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
     // Entry (row, rank) with rank < k is candidate p = rank (row 0) or k + (row - 1) k + rank.
     const int R = xl > 0 ? 1 + (xl - 1) * k : 1 + (d - 1) * k;  // rows that hold candidates
     Start from = {0, 0, 0};
-    if (xl > CARRY_FROM && __builtin_amdgcn_readfirstlane(head.x) == carry_tag(xl - 1))
-        from = {xl - 1, min(carried, k), __builtin_amdgcn_readfirstlane(head.y)};
+    const int tag = __builtin_amdgcn_readfirstlane(head.x);
+    if (xl > CARRY_FROM && (tag & ~CARRY_COUNT) == carry_tag(xl - 1, 0))
+        from = {xl - 1, min((tag & CARRY_COUNT) >> 4, k), __builtin_amdgcn_readfirstlane(head.y)};
     if (from.level > 0 && tid < DT_K_MAX) {
         if (tid >= from.n_exp) node.x = __float_as_uint(-INFINITY);
         *(uint4 *)&S.par[from.level][tid] = node;

@@ -15,7 +15,25 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 
-def drive(params, prefix_len, V, bf16, seed, flags=0, twice=False):
+def toy_logits_3(seed, string, V):
+    return toy_logits(seed, string, V, sigma=3.0)
+
+
+def few_viable(seed, string, V):
+    """A row of the toy model with few viable tokens: enough for every k near the root; below, none or one on every other level, and three to eight
+    on those between (which levels, by the seed)."""
+    x = toy_logits(seed, string, V, sigma=3.0)
+    r = np.random.default_rng([seed, 7, len(string)] + [t + 1 for t in string])
+    n = 32 if len(string) < 2 else int(r.integers(0, 2)) if (len(string) + seed) % 2 else int(r.integers(3, 9))
+    keep = r.permutation(V)[:n]
+    row = np.full(V, -np.inf, np.float32)
+    row[keep] = x[keep]
+    return row
+
+
+def drive(params, prefix_len, V, bf16, seed, flags=0, twice=False, rows=toy_logits_3, again={}, state=None):
+    """again: levels; behind each one's call the calls from that many levels back on are made again, with the same logits.  Returns the numbers of
+    nodes of every level, sequence by sequence."""
     import paper_2601_12212_amd as dt
     B = len(params)
     KR = max(p[2] for p in params)
@@ -24,7 +42,8 @@ def drive(params, prefix_len, V, bf16, seed, flags=0, twice=False):
     i32 = dict(dtype=torch.int32, device="cuda")
     d_params = torch.tensor(params, **i32)
     d_plen = torch.tensor(prefix_len, **i32)
-    state = torch.full((dt.dt_level_state_bytes(B),), 0xEE, dtype=torch.uint8, device="cuda")   # never cleared
+    if state is None:
+        state = torch.full((dt.dt_level_state_bytes(B),), 0xEE, dtype=torch.uint8, device="cuda")   # never cleared
     ws = torch.empty(dt.dt_workspace_bytes(B, B * KR, V, TT_cap, 1, 1), dtype=torch.uint8, device="cuda")
     n_exp = torch.full((B,), -5, **i32)
     e_tok = torch.full((B, 32), -5, **i32); e_par = torch.full((B, 32), -5, **i32)
@@ -32,12 +51,13 @@ def drive(params, prefix_len, V, bf16, seed, flags=0, twice=False):
     e_mask = torch.zeros((B, 32, 4), dtype=torch.int64, device="cuda")
 
     def fn(b, s):
-        x = toy_logits(seed * 100 + b, s, V, sigma=3.0)
+        x = rows(seed * 100 + b, s, V)
         return dt_synth.bf16_bits_to_f32(dt_synth.f32_to_bf16_bits(x)) if bf16 else x
 
     rows_all = [np.zeros((1 + (d - 1) * k, V), np.float32) for (TT, d, k) in params]
     strings = [{0: [()]} for _ in range(B)]
     got_levels = [dict() for _ in range(B)]
+    given = {}
     rng = np.random.default_rng(seed)
     for level in range(1, max_d + 1):
         R = 1 if level == 1 else KR
@@ -51,8 +71,12 @@ def drive(params, prefix_len, V, bf16, seed, flags=0, twice=False):
         dev = torch.from_numpy(logits).cuda()
         if bf16:
             dev = dev.to(torch.bfloat16)
-        for x in [dev.flip(-1), dev] if twice and level < min(p[1] for p in params) else [dev]:
-            dt.dt_expand_level(level, d_params, x.contiguous(), KR, d_plen, TT_cap, state, n_exp, e_tok, e_par, e_row, e_pos, e_mask,
+        given[level] = dev
+        calls = [(level, dev.flip(-1)), (level, dev)] if twice and level < min(p[1] for p in params) else [(level, dev)]
+        if level in again:
+            calls += [(l, given[l]) for l in range(max(1, level - again[level]), level + 1)]
+        for l, x in calls:
+            dt.dt_expand_level(l, d_params, x.contiguous(), KR, d_plen, TT_cap, state, n_exp, e_tok, e_par, e_row, e_pos, e_mask,
                                ws, flags=flags)
         torch.cuda.synchronize()
         for b in range(B):
@@ -74,8 +98,8 @@ def drive(params, prefix_len, V, bf16, seed, flags=0, twice=False):
                       flags=flags)
     torch.cuda.synchronize()
     for b, (TT, d, k) in enumerate(params):
-        rows = dt_synth.f32_to_bf16_bits(rows_all[b]) if bf16 else rows_all[b]
-        want = ref.build_tree(rows, TT, d, k, 100 + b, with_levels=True, early_stop=bool(flags))
+        host = dt_synth.f32_to_bf16_bits(rows_all[b]) if bf16 else rows_all[b]
+        want = ref.build_tree(host, TT, d, k, 100 + b, with_levels=True, early_stop=bool(flags))
         assert want["min_margin"] >= TREE_MARGIN, ("pick another seed", b, want["min_margin"])
         N = int(n_nodes[b])
         got = dict(n_nodes=N, tokens=tokens[b, :N].cpu().numpy(), parents=parents[b, :N].cpu().numpy(),
@@ -94,6 +118,7 @@ def drive(params, prefix_len, V, bf16, seed, flags=0, twice=False):
             assert np.array_equal(g["rows"], w["rows"]), (b, level)
             assert np.array_equal(g["mask"], w["mask"]), (b, level)
             assert (g["pos"] == prefix_len[b] + level).all()
+    return [[len(got_levels[b][level]["tokens"]) for level in range(1, max_d + 1)] for b in range(B)]
 
 
 def test_level_by_level_fp32_ragged_batch():
@@ -120,6 +145,31 @@ def test_level_by_level_to_the_deepest_level(k):
     for d in (3, 4, 8):
         drive([(100, d, k), (37, 8, max(2, k - 3))], [5, 0], V=300, bf16=False, seed=1)
         drive([(100, d, k), (37, d, max(2, k - 3))], [5, 0], V=300, bf16=False, seed=1, twice=True)
+
+
+FEW = [(100, 8), (60, 8), (90, 7)]
+
+
+@pytest.mark.parametrize("back", [0, 1, 3, 7])
+@pytest.mark.parametrize("k,seed", [(4, 1), (12, 2), (20, 1), (32, 1)])
+def test_levels_asked_for_again(k, seed, back):
+    # levels of fewer nodes than k, more or fewer than the level before: a level asked for again starts from the nodes of the one before it, however
+    # many a later call has chosen
+    for level in range(2, 9):
+        counts = drive([(TT, d, k) for TT, d in FEW], [5, 0, 9], V=300, bf16=False, seed=seed, rows=few_viable, again={level: back})
+        assert any(c[6] > c[5] > 0 for c in counts) and any(0 < c[6] < c[5] for c in counts), counts
+
+
+@pytest.mark.parametrize("k", [8, 20])
+def test_a_state_that_an_earlier_step_has_left(k):
+    # trees that the token count ends at their first or second level, on what trees of three and more levels have handed on
+    import paper_2601_12212_amd as dt
+    state = torch.full((dt.dt_level_state_bytes(2),), 0xEE, dtype=torch.uint8, device="cuda")
+    for d in (3, 4, 8):
+        drive([(100, d, k), (90, d, 3)], [5, 0], V=300, bf16=False, seed=1, state=state)
+        drive([(5, 8, k), (12, 8, 3)], [5, 0], V=300, bf16=False, seed=4, state=state, flags=dt.DT_TREE_EARLY_STOP)
+        drive([(100, d, k), (90, d, 3)], [5, 0], V=300, bf16=False, seed=1, state=state)
+        drive([(90, 8, k), (90, 8, 3)], [5, 0], V=300, bf16=False, seed=3, state=state, rows=few_viable)
 
 
 # vocabularies of both row paths: held by 1,024 threads with the log-sum-exps apart, two passes of one chunk to a workgroup;
