@@ -260,6 +260,7 @@ int dt_accept(void *stream, int batch, dt_accept_mode mode, float temperature, c
  *   exp_pos         [batch, DT_K_MAX]  position id prefix_len[b] + l (prefix_len may be NULL: l)
  *   exp_mask        [batch, DT_K_MAX, 4]  draft-side tree mask over draft rows (bit r: row r belongs to
  *                                      the node or one of its ancestors; row 0 = root)
+ * A level may be asked for again, with other logits too; then the levels behind it are asked for again as well.
  * Workspace: dt_workspace_bytes(batch, batch*R, V, TT_cap, 1, 1) bytes.
  * dt_finish_tree reranks and emits exactly what dt_build_tree would from the same rows.
  * flags as for dt_build_tree, the same value in every call of a step: with DT_TREE_EARLY_STOP the draft

@@ -133,7 +133,7 @@ struct LevelState {  // row results of one sequence after the other, then the pe
     float *top_val;    // [batch, DT_STATE_ROWS, DT_K_MAX]
     int32_t *top_id;
     float *lse;        // [batch, DT_STATE_ROWS]
-    int32_t *n_exp;    // [batch] nodes expanded at the last level processed
+    int32_t *n_exp;    // [batch] the last level processed and the nodes expanded there, level << 8 | nodes
     size_t bytes;
 };
 inline LevelState level_state(void *st, int batch) {

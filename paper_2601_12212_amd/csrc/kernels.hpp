@@ -46,7 +46,7 @@ struct RowArgs {
     float2 *part_ms;      // (max, sum exp((x-max)*inv_t)): [rows, S] (arg max rows), [rows, S*4] (top-k rows)
     // ROWS_LEVEL: rows of one level of every sequence, results scattered into the build state
     int level, rows_per_seq, state_rows;
-    const int32_t *n_exp_prev;  // [batch] nodes expanded one level up
+    const int32_t *n_exp_prev;  // [batch] of the last call: its level and the nodes that it expanded, level << 8 | nodes
     bool lse_apart;  // set by the launch functions: workgroups n_rows .. 2 n_rows - 1 are there for the rows' log-sum-exps
     int64_t n_rows;  // set by the launch functions: rows of the launch (the grid may overhang)
     // set by the launch functions: read a row's chunk before the row is known to be live (the loads then

@@ -36,7 +36,9 @@ __device__ __forceinline__ RowMeta row_meta(const RowArgs &a, int64_t g) {
         const dt_params p = a.params[b];
         const int TT = min(max(p.TT, 1), a.TT_cap), d = min(max(p.d, 1), DT_D_MAX);
         const int k = min(max(p.k, 1), min(DT_K_MAX, a.V));
-        const int cnt = a.level == 1 ? 1 : min(max(a.n_exp_prev[b], 0), k);
+        // Where the last call was not the level's before this one (it is asked for again), every row: results of rows that belong to no node are not used.
+        const int last = a.n_exp_prev[b];
+        const int cnt = a.level == 1 ? 1 : last >> 8 == a.level - 1 ? min(last & 255, k) : k;
         m.k = k;
         m.valid = TT > 1 && a.level <= d && s < cnt;
         m.out = (int64_t)b * a.state_rows + (a.level == 1 ? 0 : 1 + (a.level - 2) * k + s);

@@ -322,7 +322,7 @@ __device__ __forceinline__ void emit_level(const TreeArgs &a, const TreeLds &S, 
     }
     if (lane == 0) {
         a.n_expand[b] = n_exp;
-        a.state_n_exp[b] = n_exp;
+        a.state_n_exp[b] = l << 8 | n_exp;
         carry_head(a, b, l, n_exp, tok_count);
     }
 }
@@ -411,7 +411,7 @@ __device__ __forceinline__ int levels_narrow(const TreeArgs &a, TreeLds &S, int 
     if (xl > 0) {  // an earlier level had nothing viable to expand, or the token count ended the expansion
         if (lane == 0) {
             a.n_expand[b] = 0;
-            a.state_n_exp[b] = 0;
+            a.state_n_exp[b] = xl << 8;
             carry_head(a, b, xl, 0, tok_count);
         }
         return -1;
@@ -549,7 +549,7 @@ __device__ __forceinline__ int levels_wide(const TreeArgs &a, TreeLds &S, int b,
     if (xl > 0) {
         if (tid == 0) {
             a.n_expand[b] = 0;
-            a.state_n_exp[b] = 0;
+            a.state_n_exp[b] = xl << 8;
             carry_head(a, b, xl, 0, tok_count);
         }
         return -1;
@@ -741,7 +741,7 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
     if constexpr (!EXPAND) asm volatile("" : "+s"(root));  // here: the compiler would move the load to the store
 
     if (xl > 0 && (TT == 1 || xl >= d)) {  // nothing is drafted below level d
-        if (tid == 0) { a.n_expand[b] = 0; a.state_n_exp[b] = 0; }
+        if (tid == 0) { a.n_expand[b] = 0; a.state_n_exp[b] = xl << 8; }
         return;
     }
     if (tid == 0 && xl == 0) {

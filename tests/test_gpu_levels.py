@@ -31,8 +31,9 @@ def few_viable(seed, string, V):
     return row
 
 
-def drive(params, prefix_len, V, bf16, seed, flags=0, twice=False, rows=toy_logits_3, again={}, state=None):
-    """again: levels; behind each one's call the calls from that many levels back on are made again, with the same logits.  Returns the numbers of
+def drive(params, prefix_len, V, bf16, seed, flags=0, twice=False, rows=toy_logits_3, again={}, state=None, other=False):
+    """again: levels; behind each one's call the calls from that many levels back on are made again, with the same logits.  other: and that level's
+    first call has other logits.  Returns the numbers of
     nodes of every level, sequence by sequence."""
     import paper_2601_12212_amd as dt
     B = len(params)
@@ -74,6 +75,7 @@ def drive(params, prefix_len, V, bf16, seed, flags=0, twice=False, rows=toy_logi
         given[level] = dev
         calls = [(level, dev.flip(-1)), (level, dev)] if twice and level < min(p[1] for p in params) else [(level, dev)]
         if level in again:
+            calls[0] = (level, dev.flip(-1) if other else dev)
             calls += [(l, given[l]) for l in range(max(1, level - again[level]), level + 1)]
         for l, x in calls:
             dt.dt_expand_level(l, d_params, x.contiguous(), KR, d_plen, TT_cap, state, n_exp, e_tok, e_par, e_row, e_pos, e_mask,
@@ -170,6 +172,14 @@ def test_a_state_that_an_earlier_step_has_left(k):
         drive([(5, 8, k), (12, 8, 3)], [5, 0], V=300, bf16=False, seed=4, state=state, flags=dt.DT_TREE_EARLY_STOP)
         drive([(100, d, k), (90, d, 3)], [5, 0], V=300, bf16=False, seed=1, state=state)
         drive([(90, 8, k), (90, 8, 3)], [5, 0], V=300, bf16=False, seed=3, state=state, rows=few_viable)
+
+
+@pytest.mark.parametrize("back", [0, 1, 3, 7])
+@pytest.mark.parametrize("k,seed", [(4, 1), (12, 2), (20, 1), (32, 1)])
+def test_levels_asked_for_again_with_other_logits(k, seed, back):
+    # the call that counts finds every node's row, also where a call between has chosen fewer nodes than the level before, the last level's among them
+    for level in range(2, 9):
+        drive([(TT, d, k) for TT, d in FEW], [5, 0, 9], V=300, bf16=False, seed=seed, rows=few_viable, again={level: back}, other=True)
 
 
 # vocabularies of both row paths: held by 1,024 threads with the log-sum-exps apart, two passes of one chunk to a workgroup;
