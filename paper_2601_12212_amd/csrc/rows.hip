@@ -1005,19 +1005,39 @@ __global__ __launch_bounds__(1024, 8) void row_many_kernel(RowArgs a, float *top
         if (m) {
             int at = 0;
             if (lane == 0) at = atomicAdd(&s_n, (int)__popcll(m));
-            at = __builtin_amdgcn_readfirstlane(at) + lanes_below(m);
+            at = __builtin_amdgcn_readfirstlane(at);
+            at += lanes_below(m);
             if (in && at < SEL_CAP) s_list[at] = key_of(v, id);
         }
     }
     __syncthreads();
     int n = s_n;
     if (n > SEL_CAP) {
-        // Clusters or equal values: the k-th value by bisection over the row, then, of the entries equal to it, the last id.
+        // Clusters or equal values: the k-th value by bisection, then, of the entries equal to it, the last id.  Over the registers, filled again here (held
+        // until now they would cost waves), with the 16 bits that a value has as keys, two to a word.  Calls of equal rows, every step over the row in memory
+        // with 32-bit keys | so: 2,000 of 8,000 entries 563 | 73 us, 5,000 of 4,001 1,081 | 97, 300 of 16,384 260 | 42, 200 of 30,000 248 | 43 (by the kernel that holds
+        // rows 121, 133, 66; in two passes 68).
+        typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+        typedef short s2 __attribute__((ext_vector_type(2)));
+        int first0 = base;
+        asm volatile("" : "+v"(first0));  // the addresses are worked out again
+        chunk_request<NG, true, true>(a, g, first0, raw);
+        auto word = [&](int i, int p) -> u32 & { return p == 0 ? raw.r[i].x : p == 1 ? raw.r[i].y : p == 2 ? raw.r[i].z : raw.r[i].w; };
+#pragma unroll
+        for (int i = 0; i < NG; ++i) {
+            const int id0 = first0 + i * 512, first = id0 < 0 ? 1 : id0 - group_start(V, id0);  // elements before it are not the group's
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                u32 &x = word(i, p);
+                const u32 sign = __builtin_bit_cast(u32, __builtin_bit_cast(s2, x) >> (short)15);
+                const us2 y = __builtin_bit_cast(us2, x ^ (sign | 0x80008000u)), minus_zero = {0x7FFF, 0x7FFF};
+                const u32 key = __builtin_bit_cast(u32, y + us2{1, 1} - __builtin_elementwise_min(y ^ minus_zero, us2{1, 1}));  // -0 as +0
+                x = key & ((2 * p >= first ? 0xFFFFu : 0u) | (2 * p + 1 >= first ? 0xFFFF0000u : 0u));
+                asm volatile("" : "+v"(x));
+            }
+        }
         int step = 0;
-        auto count = [&](auto f) {  // entries of the row for which f(value, id); three counters in turn, so that one barrier does
-            int own_n = 0;
-#pragma unroll 1
-            for (int id = tid; id < V; id += blockDim.x) own_n += f(entry(id), id) ? 1 : 0;
+        auto total = [&](int own_n) {  // sum over the workgroup; three counters in turn, so that one barrier does
             const int sum = wave_sum_i32(own_n);
             if (lane == 0) atomicAdd(&s_cnt[step % 3], sum);
             __syncthreads();
@@ -1026,36 +1046,57 @@ __global__ __launch_bounds__(1024, 8) void row_many_kernel(RowArgs a, float *top
             ++step;
             return v;
         };
-        u32 lo = ord32(T), hi = 0xFFFFFFFFu;  // at least k keys reach lo, none lies above hi
-        if (lo <= 0x007FFFFFu) lo = 0x00800000u;  // -inf does not count
+        auto reach = [&](u32 key) {  // this lane's entries that reach a key of 1 and more
+            const unsigned short below = (unsigned short)(key - 1u);
+            us2 sum = {0, 0};
+#pragma unroll
+            for (int i = 0; i < 4 * NG; ++i)
+                sum += __builtin_elementwise_min(__builtin_elementwise_sub_sat(__builtin_bit_cast(us2, word(i / 4, i % 4)), us2{below, below}), us2{1, 1});
+            return (int)sum.x + (int)sum.y;
+        };
+        u32 lo = ord32(T) >> 16, hi = 0xFFFFu;  // at least k keys reach lo, none lies above hi
+        if (lo <= 0x007Fu) lo = 0x0080u;  // -inf does not count
         int c = n;
         while (hi > lo && c > k) {
             const u32 mid = lo + ((hi - lo) >> 1) + 1u;
-            const int m = count([&](float v, int) { return ord32(v) >= mid; });
+            const int m = total(reach(mid));
             if (m >= k) { lo = mid; c = m; }
             else hi = mid - 1u;
         }
-        int id_hi = 0x7FFFFFFF;  // of the entries equal to lo: those up to this id
+        u64 above = 0, equal = 0;  // bit 8 i + e: element e of group i
+#pragma unroll
+        for (int i = 0; i < 4 * NG; ++i) {
+            const u32 y = word(i / 4, i % 4), y0 = y & 0xFFFFu, y1 = y >> 16;
+            above |= (u64)((y0 > lo ? 1u : 0u) | (y1 > lo ? 2u : 0u)) << (2 * i);
+            equal |= (u64)((y0 == lo ? 1u : 0u) | (y1 == lo ? 2u : 0u)) << (2 * i);
+            asm volatile("" : "+v"(above), "+v"(equal));
+        }
         if (c > k) {
-            const int need = k - count([&](float v, int) { return ord32(v) > lo; });
-            int id_lo = 0;  // the smallest id with `need` of them at or below it
-            id_hi = V - 1;
+            const int need = k - total(__popcll(above));
+            auto up_to = [&](int id) {  // of those equal to lo
+                u64 m = 0;
+#pragma unroll
+                for (int i = 0; i < NG; ++i) {
+                    const int last = min(id - group_start(V, first0 + i * 512), 7);
+                    m |= (u64)(last < 0 ? 0u : (2u << last) - 1u) << (8 * i);
+                }
+                return equal & m;
+            };
+            int id_lo = 0, id_hi = V - 1;  // the smallest id with `need` of them at or below it
             while (id_hi > id_lo) {
                 const int mid = (id_lo + id_hi) >> 1;
-                if (count([&](float v, int id) { return ord32(v) == lo && id <= mid; }) >= need) id_hi = mid;
+                if (total(__popcll(up_to(mid))) >= need) id_hi = mid;
                 else id_lo = mid + 1;
             }
+            equal = up_to(id_hi);
         }
         __syncthreads();  // the count has been read
         if (w == 0) clear();
         __syncthreads();
-#pragma unroll 1
-        for (int id = tid; id < V; id += blockDim.x) {
-            const float v = entry(id);
-            if (ord32(v) > lo || (ord32(v) == lo && id <= id_hi)) {
-                const int at = atomicAdd(&s_n, 1);
-                if (at < SEL_CAP) s_list[at] = key_of(v, id);
-            }
+        for (u64 left = above | equal; left; left &= left - 1) {  // k of the row's
+            const int i = (int)__builtin_ctzll(left), id = group_start(V, first0 + (i >> 3) * 512) + (i & 7);
+            const int at = atomicAdd(&s_n, 1);
+            if (at < SEL_CAP) s_list[at] = key_of(entry(id), id);
         }
         __syncthreads();
         n = s_n;

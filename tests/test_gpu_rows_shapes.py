@@ -54,6 +54,38 @@ def test_topk_rows_of_large_launches(V, n, gap):
     check_repeated_rows(V, n, True, gap)
 
 
+# where the bisection over the registers can go wrong: one to eight waves of 32 or 64 entries a lane, the last group of a wave whole, begun, of one entry
+# and empty, an entry before the row
+@pytest.mark.parametrize("V,n", [(300, 2100), (2048, 2049), (2049, 1030), (4103, 2600), (8192, 2100), (9411, 260), (16384, 1025), (16385, 140), (32767, 520), (32768, 1024)])
+def test_ties_of_large_launches(V, n):
+    import paper_2601_12212_amd as dt
+    rng = np.random.default_rng(V)
+    k = 32
+    x = np.zeros((9, V), np.float32)
+    x[1] = np.where(rng.random(V) < 0.5, 0.0, -0.0)           # equal under two signs
+    x[2] = np.where(rng.random(V) < 0.5, 0.0, -0.0)
+    x[2, rng.permutation(V)[:k // 2]] = 2.0 ** -130           # a denormal number
+    x[3] = -1.0
+    x[3, rng.permutation(V)[:k]] = -0.0                       # as many as are asked for
+    x[4] = -np.inf
+    x[4, V - 290:] = -3.0e38                                  # equal at the end, nothing else viable
+    x[5] = 1.0 + np.arange(V) % 2                             # two values, every other entry
+    x[6] = np.floor(np.arange(V) / (V / 64))                  # runs
+    x[7] = -x[6]
+    x[8] = rng.integers(-3, 1, V)
+    rows = dt_synth.f32_to_bf16_bits(x)
+    wval, widx, _ = ref.topk_rows(rows, k)
+    which = torch.arange(n, device="cuda") % 9
+    val, idx = torch.empty((n, k), device="cuda"), torch.empty((n, k), dtype=torch.int32, device="cuda")
+    lse = torch.empty(n, device="cuda")
+    ws = torch.full((dt.dt_workspace_bytes(1, n, V, 8, 1, 64),), 0x7f, dtype=torch.uint8, device="cuda")
+    dt.dt_topk_rows(dev_logits(rows)[which], k, val, idx, lse, ws)
+    torch.cuda.synchronize()
+    which = which.cpu().numpy()
+    assert np.array_equal(idx.cpu().numpy(), widx[which])
+    assert np.array_equal(val.cpu().numpy(), wval[which])
+
+
 @pytest.mark.parametrize("V,n,gap", [(65536, 129, 1), (65536, 129, 2), (131072, 129, 3), (32768, 1025, 1)])
 def test_topk_rows_of_whole_chunks_at_odd_addresses(V, n, gap):
     """Sixteen whole chunks to a row: a workgroup more where the rows' stride is odd, none where it is even."""
@@ -253,6 +285,14 @@ def test_neighbours_among_the_best_do_not_slow_top_k_rows_down(n, V, k, M, times
     x[:, 1000:1000 + M] += 20
     took = times_in_turn([x.bfloat16(), plain], k)
     assert took[0] <= times * took[1], took
+
+
+@pytest.mark.parametrize("n,V", [(2000, 8000), (2600, 2048), (300, 16384), (200, 30000)])
+def test_ties_of_large_launches_are_not_looked_up_in_memory(n, V):
+    """5 to 7 times as long as rows of differing values; 35 to 75 with every step of the search over the row in memory."""
+    x = torch.randn((n, V), generator=torch.Generator("cuda").manual_seed(5), device="cuda").bfloat16()
+    took = times_in_turn([torch.ones_like(x), x], 24, 5)
+    assert took[0] <= 12 * took[1], took
 
 
 def test_large_calls_of_short_chunks_are_not_one_chunk_to_a_workgroup():
