@@ -312,11 +312,16 @@ struct SeqWords {
     int N, L;
     u64 kpre, vpre;  // of the caches, as addresses
 };
-// x / G for x G < 2^32: the upper half of x * (2^32 / G + 1)
+// x / G for x >= 0: the upper half of x * (2^32 / G + 1), which is never too small and, for x G of 2^32 and more (thousands of query heads to a kv head),
+// may be one too large
 struct GroupDiv {
     int G;
     u32 magic;
-    __device__ __forceinline__ int div(int x) const { return G == 1 ? x : (int)__umulhi((u32)x, magic); }
+    __device__ __forceinline__ int div(int x) const {
+        if (G == 1) return x;
+        const int q = (int)((u64)(u32)x * magic >> 32);
+        return q - (q * G > x ? 1 : 0);
+    }
 };
 static GroupDiv group_div(int G) { return {G, (u32)(((u64)1 << 32) / G + 1)}; }
 

@@ -419,3 +419,29 @@ def test_masks_that_hide_the_first_block(Hq, Hkv, B, bound):
     st.build_tree()
     for L, n in ((0, 128), (0, 66), (1, 128), (40, 120)):
         low_scores(cfg, st, 0, n, L, mask=lambda i: {i, max(i - 3, 0)} if i >= 64 else {i})
+
+
+@pytest.mark.parametrize("Hq,Hkv,TT", [(65535, 1, 3), (65534, 2, 8), (65535, 3, 16), (12000, 2, 16)])
+def test_thousands_of_query_heads_to_a_kv_head(Hq, Hkv, TT):
+    # rows are told apart by a multiplication with a rounded reciprocal of their number to a node, which the last rows of a node find one too large from about
+    # 2^32 / Hq^2 nodes on (not in the last shape)
+    from paper_2601_12212_amd.step import Step
+    G, L, D = Hq // Hkv, 37, 128
+    st = Step([(TT, 4, 6)], [L], Hq, Hkv, D, 1031)
+    gen = torch.Generator("cuda").manual_seed(TT)
+    for t in (st.draft_logits, st.q, st.k_tree, st.v_tree, st.k_prefix[0], st.v_prefix[0]):
+        t.copy_(torch.randn(t.shape, generator=gen, device="cuda") * (3.0 if t is st.draft_logits else 1.0))
+    st.build_tree()
+    st.out.fill_(7.0)
+    st.tree_attention()
+    assert st.tree(0)["n_nodes"] == TT
+    bits = st.anc_mask[0, :, 0, None] >> torch.arange(TT, device="cuda") & 1
+    sees = torch.cat([torch.ones((TT, L), dtype=torch.bool, device="cuda"), bits.bool()], 1)
+    for h in range(Hkv):
+        k, v = (torch.cat([p[0][:, h], t[0, :, h]]).float() for p, t in ((st.k_prefix, st.k_tree), (st.v_prefix, st.v_tree)))
+        for i in range(TT):
+            q, got = (t[0, i, h * G:(h + 1) * G].float() for t in (st.q, st.out))
+            want = torch.softmax((q @ k.t() * st.scale).masked_fill(~sees[i], -float("inf")), 1) @ v
+            # one ulp for each side's rounding, and the rounded probabilities of some forty keys
+            over = ((got - want).abs() - 2.0 ** -6 * want.abs()).max()
+            assert float(over) <= 4e-3, (h, i, float(over))
