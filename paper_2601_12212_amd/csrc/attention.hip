@@ -1050,8 +1050,8 @@ struct WaveArea {
 struct SplitBuf {
     float4 *o;    // [unit, KS, D/32 waves, 4, 64 lanes]: the owner waves' output registers
     float2 *ml;   // [unit, KS, 32]: (max, sum) per query row
-    int G;                  // query heads per kv head
-    u32 g_magic, ks_magic;  // x / d = the upper half of x * (2^32 / d + 1), for x d < 2^32 and d > 1
+    GroupDiv gd;   // by the query heads per kv head
+    u32 ks_magic;  // x / KS = the upper half of x * (2^32 / KS + 1), for x KS < 2^32 and KS > 1: x is a workgroup's place
 };
 
 template <int D, int NW, bool DIRECT>
@@ -1059,7 +1059,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_wave_kernel(AttnArgs a, int K
     static_assert((D == 128 || D == 64) && (NW == 4 || NW == 8) && (!DIRECT || (NW == 4 && D == 128)), "shape");
     constexpr int KSTEPS = D / 16, DBLK = D / 32;
     constexpr int K_PITCH = WaveTile<D>::K_PITCH, V_PITCH = WaveTile<D>::V_PITCH;
-    const int G = sb.G;
+    const int G = sb.gd.G;
     // blockIdx.x = kv head: workgroups are dealt to the 8 XCDs round-robin by linear id, so every
     // row block and split of one kv head lands on one XCD and shares its L2 copy of that head's K/V
     const int b = __builtin_amdgcn_readfirstlane(KS == 1 ? blockIdx.z : __umulhi(blockIdx.z, sb.ks_magic));
@@ -1082,7 +1082,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_wave_kernel(AttnArgs a, int K
     const int mq = m0 + col;
     const bool qvalid = mq < M;
     const int mr = qvalid ? mq : 0;  // rows past M read node 0: unused
-    const int node = G == 1 ? mr : (int)__umulhi((u32)mr, sb.g_magic);
+    const int node = sb.gd.div(mr);
     const int hq = h * G + (mr - node * G);
 
     // LDS: NW private tiles during the loop, then the exchange area of the partial results
@@ -2020,8 +2020,7 @@ static int wave_launch(const AttnArgs &a, hipStream_t st, hipError_t *err) {
     if (KS > 1 && (!a.ws || (size_t)KS * per_split > a.ws_bytes)) KS = a.ws ? (int)(a.ws_bytes / per_split) : 1;
     if (KS < 1) KS = 1;
     SplitBuf sb;
-    sb.G = G;
-    sb.g_magic = (u32)(((u64)1 << 32) / G + 1);
+    sb.gd = group_div(G);
     sb.ks_magic = (u32)(((u64)1 << 32) / KS + 1);
     sb.o = (float4 *)a.ws;
     sb.ml = (float2 *)((char *)a.ws + (size_t)units * KS * (D / 32) * 4 * 64 * 16);
