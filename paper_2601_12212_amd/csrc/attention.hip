@@ -494,8 +494,9 @@ __device__ __forceinline__ bool tile_segment(const AttnArgs &a, const GroupDiv &
     //   MFMA s of K(kb + 1) Q^T:  exponentials of block kb (16 of a lane's 32)
     //   MFMA n of V(kb)^T P^T:    the other 16, in time for the MFMA that takes them
     // What bounds a wave that has its SIMD to itself is the bytes of its instructions (some eight cycles for eight of them), and two to
-    // a SIMD the power that the chip may draw (it clocks at 1.7 to 1.9 GHz then) and the loads into LDS: without them, for timing, a layer of the
-    // 70B step takes 103 us instead of 121, without the exponentials 118, without the waits for the loads 121.
+    // a SIMD the power that the chip may draw (long sequences hold it at 1,350 to 1,400 of 1,400 W, where it clocks at 1.73 to 1.94 GHz of 2.4) and the loads into LDS:
+    // a layer of the 70B step takes 113 us, for timing without the loads 97, without the exponentials 110, without both 93; eight long sequences of
+    // the 8B shape 117, 94, 113 and 92; sixteen ragged ones (2.25 GHz), whose time is not in this loop alone, 64, 61, 63 and 59.
     // All LDS operand reads are bare instructions with hand-kept waits, eight K reads or seven V read pairs ahead of their
     // MFMA (V pairs start behind the last K reads).  P: CUR is the stage of V(kb); K(kb + 1) is in stage CUR ^ 1.
     // EXP_A(e), EXP_B(e): elements 2e and 2e + 1 of the lane's 32 (element i of S[j] is 16 j + i).  The multiply-add as an
@@ -1975,32 +1976,25 @@ static int wave_splits(int D, int64_t units, int64_t nb) {
 // 32-key blocks of the longest sequence
 static int64_t max_blocks(const AttnArgs &a) { return ((int64_t)a.max_prefix_len + a.TT_cap + ATT_KB - 1) / ATT_KB; }
 
-// 128-wide heads: which kernel.  `units` (sequence, kv head, 32-row block)s, as the caller allows for them:
-//  - up to 256, one to a compute unit: the small-batch kernel, whatever the lengths;
-//  - more, and at most 40 blocks of 32 keys (56 where every tile has a compute unit to itself): workgroups that take whole tiles of 128 rows.  Each
-//    shares a key block among four row blocks, and on sequences this short nothing is gained by cutting them: the schedule finds that too, and takes
-//    1 us to find it.  A workgroup alone on its compute unit keeps four tiles of each kind in LDS in place of two (NS): nothing but its own loads in
-//    flight hides their latency;
-//  - more keys: the balanced schedule, which cuts or does not cut by the lengths that it finds.
-// The lengths here are the most that the caller allows for (max_prefix_len): one call's own, or, in a step that is captured once, the most that any
-// replay will have.  us per layer, small-batch | balanced | whole tiles, all sequences as long as that ("equal") or from a quarter of it up ("ragged"):
-//   256 units and fewer: 4 sequences of the 8B shape, 64 nodes (256) 40 keys 7 | 9 | 9, 400 12 | 15 | 16, 1,100 17 | 27 | 27, 2,400 26 | 40 | 47, 4,000 36 | 35 | 70,
-//     8,000 62 | 55 | 130; 3 (192) 8,000 56 | 50, 12,000 81 | 63; 32 heads without groups, 4 sequences of 64 nodes (256) 400 12 | 15 | 15, 2,400 33 | 40 | 45, 8,000 114 | 120,
-//     ragged 107 | 107; 8 of 32 nodes (256) 400 16 | 15 | 15, 2,400 54 | 66 | 65, 8,000 179 | 196; 40 heads, 5 of 32 (200) ragged 12,000 190 | 174.  Long lengths that the balanced
-//     schedule would take up to a quarter faster are left to the small-batch kernel, because a bound that far above them would cost the short ones more;
-//   more: 5 of the 8B shape, 64 nodes (320) 40 keys 12 | 10 | 9, 400 19 | 16 | 16, 1,300 30 | 28 | 30, 1,600 33 | 30 | 33, ragged 22 | 27 | 32, 2,400 44 | 30 | 47, ragged 34 | 31 | 45;
-//     4 of 112 (448) 1,600 36 | 37 | 36, ragged 30 | 28 | 30, 4,000 66 | 57 | 73; 40 heads without groups, 4 of 64 (320) 1,300 36 | 31 | 29, 2,400 56 | 44 | 45;
-//   more tiles than there is room for at once: 32 sequences of the 70B shape, 64 nodes (1,024 tiles) ragged 200 keys 42 balanced | 31 whole, 1,100 73 | 67; 54 of 40 heads, 64
-//     nodes (2,160) 400 153 | 138, ragged 108 | 90, 1,100 316 | 289; 40 of four heads with four queries each, 112 nodes (640) 400 41 | 39, ragged (but then 500 or so) 28 | 36;
-//     16 of 40 heads (640) 1,100 103 | 96, 1,600 136 | 134, 2,400 181 | 199; 64 of the 8B shape, 256 to 4,096 keys 231 | 295;
-//   a compute unit to each tile, with layers whose caches come from memory, balanced | whole, two tiles in LDS | whole, four (mean of 4 to 14 sequences of the 8B shape, 20 of
-//     2 kv heads, 6 of 32): ragged 400 keys 18.5 | 17.0 | 16.6, 1,100 32.3 | 30.8 | 27.1, 1,600 36.0 | 39.0 | 32.9, 2,400 46.8 | 56.9 | 46.9, 4,000 57 | 86 | 68; equal 1,600
-//     43.0 | 43.5 | 37.2.  With the caches in the last level, balanced | four: ragged 1,600 30.5 | 29.5, 2,400 39.8 | 40.3; one sequence of 1,600 among 11 of 200 31.2 | 30.0,
-//     of 2,400 33.6 | 40.3;
-//   few tiles (144 and fewer) in up to 400 units: where sequences end early, or their trees are smaller than the largest, the units that are left often have a compute unit
-//     each, and few tiles are as long as the longest sequence.  Ragged, small-batch | whole: 260 to 320 units 8.2 | 11.5, 9.2 | 13.2, 11.3 | 11.2, 12.1 | 17.2, 13.0 | 10.0, 16.6 |
-//     20.5, 21.5 | 20.7 (22 shapes on average 0.95 the time); 336 to 400 units beyond 32 blocks 15.4 | 21.0, 19.8 | 22.8, 22.4 | 25.6, equal 28.4 | 25.9, up to 32 blocks 17.1 | 15.8,
-//     13.2 | 11.1, 16.8 | 14.2; 448 to 512 units beyond 32 blocks 22.7 | 23.2, 24.4 | 23.9, 25.5 | 22.7, 28.5 | 28.5, equal 39.0 | 33.7.
+// 128-wide heads: which kernel, by what the caller allows for (max_prefix_len, TT_cap; in a step that is captured once the most that any replay will have):
+// units of (sequence, kv head, 32 rows), tiles of (sequence, kv head, 128 rows), blocks of 32 keys of the longest sequence.
+//   1. up to 256 units:                                                    small-batch
+//   2. up to 144 tiles and 56 blocks, and up to 320 units (400 beyond 32 blocks): small-batch
+//   3. up to 40 blocks, 56 where every tile has a compute unit to itself:   whole tiles, four of K and V in LDS where it has, else two
+//   4. otherwise, if the plan fits:                                        balanced (if not, as 3, or with fewer than 128 tiles as 1)
+// us per layer, all sequences as long as said, or from a quarter of it up ("ragged"); 8B shape and 64 nodes unless said.
+//   1: every unit has a compute unit.  Small-batch | balanced | whole: 4 sequences of 40 keys 7 | 9 | 9, 400 12 | 15 | 16, 2,400 26 | 40 | 47, 4,000 36 | 35 | 70; 32 heads without groups,
+//      4 of 2,400 33 | 40 | 45, 8 of 32 nodes 54 | 66 | 65.  Longer ones gain by the schedule, 8,000 keys 62 | 55, 3 of 12,000 81 | 63, and stay: the lengths are bounds, and under a
+//      bound that far above them the short ones would lose more.
+//   3: four row blocks share a key block, and short sequences are not worth cutting, which the schedule finds too, in 1 us.  Balanced | whole: 32 of the 70B shape, ragged 200
+//      keys 42 | 31, 1,100 73 | 67; 54 of 40 heads without groups 400 153 | 138, 1,100 316 | 289; 16 of them 1,100 103 | 96, 1,600 136 | 134, 2,400 181 | 199.  A compute unit to each
+//      tile, caches from memory, balanced | whole with two | with four tiles in LDS (means over 4 to 14 sequences, 20 of 2 kv heads, 6 of 32): ragged 400 18.5 | 17.0 | 16.6, 1,100 32.3 | 30.8 | 27.1, 1,600 36.0 | 39.0 |
+//      32.9, 2,400 46.8 | 56.9 | 46.9; equal 1,600 43.0 | 43.5 | 37.2.
+//   4: small-batch | balanced: 5 sequences (320 units) 1,600 keys 33 | 30, 2,400 44 | 30; 4 of 112 nodes (448) 4,000 66 | 57; whole | balanced: 64 of 256 to 4,096 keys 295 | 231.
+//   2: a compromise between batches that these bounds do not tell apart.  Where sequences end early or their trees are smaller than the largest, the units that are left have a
+//      compute unit each, and a few tiles take as long as the longest sequence; where all are equal, whole tiles are ahead.  Small-batch | whole, from the best to the worst of the rule:
+//      260 to 320 units ragged 8.2 | 11.5, 12.1 | 17.2, 16.6 | 20.5, 21.5 | 20.7, 13.0 | 10.0 (22 shapes 0.70 to 1.3 times as long, 0.95 on average); 336 to 400 beyond 32 blocks
+//      ragged 15.4 | 21.0, 19.8 | 22.8, 22.4 | 25.6, equal 28.4 | 25.9.  Not taken: 336 to 400 up to 32 blocks 17.1 | 15.8, 13.2 | 11.1; 448 to 512 22.7 | 23.2, 25.5 | 22.7, equal 39.0 | 33.7.
 #define SMALL_UNITS 256
 #define FEW_TILES 144
 #define FEW_TILES_UNITS 320        // at any length

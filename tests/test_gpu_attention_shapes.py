@@ -227,8 +227,9 @@ def test_numbers_of_key_splits(D, Hkv, L):
     check_case(oracle_case(0, cfg=_cfg("bf16", D, [(32, 5, 6)], [L], Hkv, Hkv)))
 
 
-# lengths and numbers of row blocks around which the small-batch kernel and the balanced schedule take as long as each other: 320 units of four row
-# blocks to a kv head, 256 and 320 of two, 256 and 260 of one; one sequence of that length among short ones
+# one sequence far longer than the others, in every kernel: the balanced schedule (320 and 512 row blocks, four to a kv head), the small-batch kernel with key
+# splits (256, two and one to a kv head) and whole tiles (320, two to a kv head; 260, one, more tiles than compute units).  (The lines between the kernels lie
+# elsewhere: test_lines_between_the_three_kernels and the two before it.)
 @pytest.mark.parametrize("B,Hq,Hkv,L", [(B, Hq, Hkv, L + i) for B, Hq, Hkv, L in ((40, 8, 2, 6816), (64, 8, 2, 1824), (32, 8, 4, 4768), (40, 8, 4, 608),
                                                                                  (64, 4, 4, 6368)) for i in (0, 1)] +
                          [(52, 5, 5, 150)])
