@@ -425,8 +425,8 @@ def test_masks_that_hide_the_first_block(Hq, Hkv, B, bound):
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("Hq,Hkv,TT", [(65535, 1, 3), (65534, 2, 8), (65535, 3, 16), (12000, 2, 16)])
 def test_thousands_of_query_heads_to_a_kv_head(Hq, Hkv, TT, D):
-    # rows are told apart by a multiplication with a rounded reciprocal of their number to a node, which the last rows of a node find one too large from about
-    # 2^32 / Hq^2 nodes on (not in the last shape)
+    # rows are told apart by a multiplication with the reciprocal of their number to a node: rounded to 32 bits behind the point, it would find the last rows of a
+    # node one too large from about 2^32 / (Hq / Hkv)^2 nodes on (not in the last shape)
     from paper_2601_12212_amd.step import Step
     G, L = Hq // Hkv, 37
     st = Step([(TT, 4, 6)], [L], Hq, Hkv, D, 1031)
