@@ -8,7 +8,7 @@
 // product, 64-wide heads keep it whole.  K and V tiles are staged in LDS
 // row-major; the V operand comes from the transposing LDS read.  The keys of a sequence may be split
 // across workgroups, which leave partial max / sum / O, when a batch offers too few
-// (sequence, kv head, row tile) items to fill the chip (small batches, merged by a second kernel) or items of
+// (sequence, kv head, row tile) items to fill the chip (small batches, merged by those that wait for the others) or items of
 // different lengths (large batches, merged by the workgroup that comes last, or by all that stayed to see it come).
 // The ancestor bitset is applied only to key blocks that contain tree keys.
 //
@@ -1043,35 +1043,256 @@ struct WaveArea {
 };
 #define WD_LDS_BYTES (4 * 2 * WD_STAGE)         // four waves, two stages: 128 KB
 
-// With KS > 1 the key blocks are additionally dealt over KS workgroups per (sequence, kv head,
-// row block); each leaves its partial (max, sum, O) in global scratch for a small merge kernel.
-// (Merging in the last workgroup to arrive, as the large-batch schedule does, loses here: store, count and read
-// back are three trips to the memory side one after the other, 15.2 us on the 8B shape at batch 1 against 10.1 + 2.9 for
-// two kernels.)
+// With KS > 1 the key blocks are additionally dealt over KS workgroups per (sequence, kv head, row block), whose waves put their
+// partials together in the same launch (join_splits).
 struct SplitBuf {
-    float4 *o;    // [unit, KS, D/32 waves, 4, 64 lanes]: the owner waves' output registers
-    float2 *ml;   // [unit, KS, 32]: (max, sum) per query row
-    GroupDiv gd;   // by the query heads per kv head
-    u32 ks_magic;  // x / KS = the upper half of x * (2^32 / KS + 1), for x KS < 2^32 and KS > 1: x is a workgroup's place
+    float4 *o;     // [unit, D/32 waves, KS, 4, 64 lanes]: a wave's output registers
+    float2 *ml;    // [unit, D/32 waves, KS, 32]: (max, sum) per query row
+    u64 *offers;   // [unit, D/32 waves, KS], a cache line each: `tag` and an XCD's number while a partial is on offer in its L2
+    u64 *marks;    // [unit, D/32 waves, KS]: `tag` once a partial is at the memory side
+    u64 tag;       // of this launch: what the memory held before it never looks like a mark
+    GroupDiv gd, hd, md;  // by the query heads per kv head, the kv heads, the row blocks
+    int units;
+    u32 ks_magic;  // x / KS = x * ks_magic / 4096 for x < 64
 };
+#define MAX_SPLITS 8
+#define LINE_WORDS 16     // of 64 bits in a cache line
+#define OFFER_TICKS 1000  // of 10 ns
 
-template <int D, int NW, bool DIRECT>
+// Sixteen and eight bytes to the memory side, past the L2s (not coherent between the XCDs inside a launch): a relaxed atomic at
+// agent scope for more than a word.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef u64 u64x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void put16_agent(float4 *p, f32x4 v) { asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(p), "v"(v) : "memory"); }
+__device__ __forceinline__ void put8_agent(float2 *p, f32x2 v) { asm volatile("global_store_dwordx2 %0, %1, off sc1" ::"v"(p), "v"(v) : "memory"); }
+// N partials (four times 1,024 bytes of a wave from o[u] on, with STATS the statistics at ml[u] too) in one trip, past the L1: from this XCD's L2 what
+// was written there, else from the memory side.  With them, in the lanes of `lanes`, *word is exchanged for the first half of `swap` where it is the
+// second (within the XCD); `was`, in those lanes, is what it was.  One statement, since the registers hold nothing that may be copied before the wait.
+template <int N, bool STATS>
+__device__ __forceinline__ void get_partials(const float4 *const (&o)[N], const u64 *const (&ml)[N], f32x4 (&p)[N][4], u64 (&st)[N], u64 lanes, u64 *word,
+                                             u64x2 swap, u64 &was) {
+#define PART_LOADS(o, p0, p1, p2, p3)                                                                              \
+    "global_load_dwordx4 " p0 ", " o ", off sc1\n\tglobal_load_dwordx4 " p1 ", " o ", off offset:1024 sc1\n\t"    \
+    "global_load_dwordx4 " p2 ", " o ", off offset:2048 sc1\n\tglobal_load_dwordx4 " p3 ", " o ", off offset:3072 sc1\n\t"
+#define PART_STAT(st, ml) "global_load_dwordx2 " st ", " ml ", off sc1\n\t"
+#define PART_SWAP "s_mov_b64 %1, exec\n\ts_mov_b64 exec, %[lanes]\n\tglobal_atomic_cmpswap_x2 %0, %[word], %[swap], off sc0\n\ts_mov_b64 exec, %1\n\t"
+#define PART_OUT(u) "=&v"(p[u][0]), "=&v"(p[u][1]), "=&v"(p[u][2]), "=&v"(p[u][3])
+#define PART_SWAP_OUT "=&v"(was), "=&s"(all)
+#define PART_SWAP_IN [lanes] "s"(lanes), [word] "v"(word), [swap] "v"(swap)
+    u64 all;
+    if constexpr (!STATS && N == 1)
+        asm volatile(PART_SWAP PART_LOADS("%6", "%2", "%3", "%4", "%5") "s_waitcnt vmcnt(0)"
+                     : PART_SWAP_OUT, PART_OUT(0) : "v"(o[0]), PART_SWAP_IN : "memory");
+    else if constexpr (!STATS && N == 2)
+        asm volatile(PART_SWAP PART_LOADS("%10", "%2", "%3", "%4", "%5") PART_LOADS("%11", "%6", "%7", "%8", "%9") "s_waitcnt vmcnt(0)"
+                     : PART_SWAP_OUT, PART_OUT(0), PART_OUT(1) : "v"(o[0]), "v"(o[1]), PART_SWAP_IN : "memory");
+    else if constexpr (!STATS)
+        asm volatile(PART_SWAP PART_LOADS("%14", "%2", "%3", "%4", "%5") PART_LOADS("%15", "%6", "%7", "%8", "%9")
+                     PART_LOADS("%16", "%10", "%11", "%12", "%13") "s_waitcnt vmcnt(0)"
+                     : PART_SWAP_OUT, PART_OUT(0), PART_OUT(1), PART_OUT(2) : "v"(o[0]), "v"(o[1]), "v"(o[2]), PART_SWAP_IN : "memory");
+    else if constexpr (N == 1)
+        asm volatile(PART_SWAP PART_STAT("%6", "%8") PART_LOADS("%7", "%2", "%3", "%4", "%5") "s_waitcnt vmcnt(0)"
+                     : PART_SWAP_OUT, PART_OUT(0), "=&v"(st[0]) : "v"(o[0]), "v"(ml[0]), PART_SWAP_IN : "memory");
+    else if constexpr (N == 2)
+        asm volatile(PART_SWAP PART_STAT("%10", "%14") PART_STAT("%11", "%15") PART_LOADS("%12", "%2", "%3", "%4", "%5")
+                     PART_LOADS("%13", "%6", "%7", "%8", "%9") "s_waitcnt vmcnt(0)"
+                     : PART_SWAP_OUT, PART_OUT(0), PART_OUT(1), "=&v"(st[0]), "=&v"(st[1]) : "v"(o[0]), "v"(o[1]), "v"(ml[0]), "v"(ml[1]), PART_SWAP_IN : "memory");
+    else
+        asm volatile(PART_SWAP PART_STAT("%14", "%20") PART_STAT("%15", "%21") PART_STAT("%16", "%22") PART_LOADS("%17", "%2", "%3", "%4", "%5")
+                     PART_LOADS("%18", "%6", "%7", "%8", "%9") PART_LOADS("%19", "%10", "%11", "%12", "%13") "s_waitcnt vmcnt(0)"
+                     : PART_SWAP_OUT, PART_OUT(0), PART_OUT(1), PART_OUT(2), "=&v"(st[0]), "=&v"(st[1]), "=&v"(st[2])
+                     : "v"(o[0]), "v"(o[1]), "v"(o[2]), "v"(ml[0]), "v"(ml[1]), "v"(ml[2]), PART_SWAP_IN : "memory");
+#undef PART_LOADS
+#undef PART_STAT
+#undef PART_SWAP
+#undef PART_OUT
+#undef PART_SWAP_OUT
+#undef PART_SWAP_IN
+}
+
+// Split ks of KS of a row block: one wave's column block, res (unnormalised), M and Lsum (of the lane's query), against those of its
+// fellows in the other splits; `at` is the column block's number in the launch.  One split owns the block (another one for each wave, so that
+// its workgroup reads little): it keeps its own partial in registers, waits for the others' and adds them up.  True for a wave that
+// has them all, with the results in res and Lsum.
+//
+// A partial goes to the owner in one of two ways.  The workgroups of a row block are numbered so that the same XCD gets them all (but `apart`): the
+// partial is left in its L2 and offered there by a word, with the XCD's number in it, that an owner on the same XCD exchanges for 0 when it takes it
+// (loads at agent scope find what lies written in their own XCD's L2).  An offer that nobody has taken for OFFER_TICKS is withdrawn the same
+// way; then the partial is written to the memory side and marked there, for an owner anywhere.
+//
+// What bounds it are trips within the XCD, about 0.4 us each when all workgroups make them at once: the partial is written, the offer seen, the partials and the exchange
+// of the offer fetched together, 1.7 us of a layer where a merge kernel took 2.9 and a launch of the host (8B shape, 64 nodes, 1,024 keys, three splits: 32 layers
+// 352 -> 331 us; 16 layers, whose caches lie closer, 10.8 -> 9.3 a layer; one of 40 heads 2,048 keys 12.8 -> 11.5).  Through the memory side only, as far fellows go, 336.
+//
+// Nothing depends on which workgroups run at once or where.  An owner that has waited for STAY_TICKS and taken nothing leaves its own partial and a mark
+// at the memory side; its fellows' offers run out, and of those that mark their partials the last to come sees all marks and takes the
+// block (of the last two at least one sees the other's mark; both taking it write the same, since partials are added in the order of
+// their splits).  Offers end as 0, and marks are taken away by whoever has seen them all: a replayed graph has the same tag.
+__device__ __forceinline__ u32 xcc_id() { return __builtin_amdgcn_s_getreg(20 | 3 << 11); }  // HW_REG_XCC_ID, four bits
+template <int DBLK>
+__device__ __forceinline__ bool join_splits(const SplitBuf &sb, int64_t at, int KS, int ks, bool apart, int w, int lane, float c, float (&res)[16], float M, float &Lsum) {
+    const int col = lane & 31, peer = min(lane, KS - 1);
+    float4 *const o = sb.o + at * KS * 4 * 64 + lane;
+    float2 *const ml = sb.ml + at * KS * 32 + col;
+    u64 *const offer = sb.offers + (at * KS + peer) * LINE_WORDS;
+    u64 *const mark = sb.marks + at * KS + peer;
+    const u64 here = sb.tag | (xcc_id() + 1);
+    auto leave = [&]() {  // at the memory side; true if all are there
+#pragma unroll
+        for (int q = 0; q < 4; ++q) put16_agent(o + (ks * 4 + q) * 64, f32x4{res[4 * q], res[4 * q + 1], res[4 * q + 2], res[4 * q + 3]});
+        if (lane < 32) put8_agent(ml + ks * 32, f32x2{M, Lsum});
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (lane == ks) put_agent(mark, sb.tag);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        return __builtin_amdgcn_ballot_w64(get_agent(mark) != sb.tag) == 0ull;
+    };
+    const u32 t0 = (u32)__builtin_amdgcn_s_memrealtime();
+    bool marked = true, taking = false;  // whose mark is there; whose offer is to be taken
+    if (ks == KS - 1 - (w >= KS ? w - KS : w)) {  // w % KS: four waves, two splits and more
+        bool offered;
+        for (;;) {
+            offered = lane < KS && lane != ks && get_agent(offer) == here;
+            marked = lane < KS && lane != ks && get_agent(mark) == sb.tag;
+            if (__builtin_amdgcn_ballot_w64(offered || marked || lane >= KS || lane == ks) == ~0ull) break;
+            if ((u32)__builtin_amdgcn_s_memrealtime() - t0 > STAY_TICKS) {
+                if (!leave()) return false;
+                offered = false;
+                marked = true;
+                break;
+            }
+        }
+        taking = offered && !marked;
+    } else if (apart) {
+        if (!leave()) return false;
+    } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) *(f32x4 *)(o + (ks * 4 + q) * 64) = f32x4{res[4 * q], res[4 * q + 1], res[4 * q + 2], res[4 * q + 3]};
+        if (lane < 32) *(f32x2 *)(ml + ks * 32) = f32x2{M, Lsum};
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (lane == ks) __hip_atomic_store(offer, here, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        while (__builtin_amdgcn_ballot_w64(lane == ks && get_agent(offer) == here)) {
+            if ((u32)__builtin_amdgcn_s_memrealtime() - t0 > OFFER_TICKS) break;
+        }
+        u64 was = here;
+        if (lane == ks) __hip_atomic_compare_exchange_strong(offer, &was, 0, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (__builtin_amdgcn_ballot_w64(was != here) || !leave()) return false;
+    }
+    asm volatile("" ::: "memory");
+    // Partial j of the others is split j + (j >= ks)'s.  All their statistics, and three partials at a time, are in flight together; the sum is over the
+    // splits in their order, whoever makes it.
+    const u64 take = __builtin_amdgcn_ballot_w64(taking);
+    u64 was = here;
+    float acc[16], l = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+    auto add = [&](auto n_c) __attribute__((always_inline)) {  // sized for every number of splits: branches for each partial cost 0.4 us
+        constexpr int n = decltype(n_c)::value;
+        constexpr bool one = n <= 3;  // all in one statement
+        u64 st[n];
+        const u64 *mp[n];
+#pragma unroll
+        for (int j = 0; j < n; ++j) mp[j] = (const u64 *)(ml + (j + (j >= ks)) * 32);
+        if constexpr (!one)
+#pragma unroll
+            for (int j = 0; j < n; ++j) st[j] = get_agent((u64 *)mp[j]);
+        float mu = M, f_own = 0.f, f[n];
+        auto weights = [&]() {
+#pragma unroll
+            for (int j = 0; j < n; ++j) mu = fmaxf(mu, __builtin_bit_cast(f32x2, st[j]).x);
+            mu = mu == -INFINITY ? 0.f : mu;
+            f_own = __builtin_amdgcn_exp2f((M - mu) * c);
+#pragma unroll
+            for (int j = 0; j < n; ++j) f[j] = __builtin_amdgcn_exp2f((__builtin_bit_cast(f32x2, st[j]).x - mu) * c);
+        };
+        auto own = [&]() {
+            l += Lsum * f_own;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[i] += res[i] * f_own;
+        };
+        auto some = [&](auto j_c) __attribute__((always_inline)) {
+            constexpr int j0 = decltype(j_c)::value, m = n - j0 < 3 ? n - j0 : 3;
+            if constexpr (m > 0) {
+                const float4 *op[m];
+#pragma unroll
+                for (int u = 0; u < m; ++u) op[u] = o + (j0 + u + (j0 + u >= ks)) * 4 * 64;
+                f32x4 p[m][4];
+                u64 none;
+                if constexpr (one) get_partials<m, true>(op, mp, p, st, take, offer, u64x2{0, here}, was);
+                else {
+                    const u64 *no_stats[m];
+                    u64 stats[m];
+                    get_partials<m, false>(op, no_stats, p, stats, j0 == 0 ? take : 0, offer, u64x2{0, here}, j0 == 0 ? was : none);
+                }
+                if constexpr (j0 == 0) weights();
+#pragma unroll
+                for (int u = 0; u < m; ++u) {
+                    if (j0 + u == ks) own();
+                    l += __builtin_bit_cast(f32x2, st[j0 + u]).y * f[j0 + u];
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) acc[i] += p[u][i >> 2][i & 3] * f[j0 + u];
+                }
+            }
+        };
+        some(std::integral_constant<int, 0>());
+        some(std::integral_constant<int, 3>());
+        some(std::integral_constant<int, 6>());
+        if (ks == n) own();
+    };
+    using std::integral_constant;
+    if (KS == 3) add(integral_constant<int, 2>());
+    else if (KS == 4) add(integral_constant<int, 3>());
+    else if (KS == 2) add(integral_constant<int, 1>());
+    else if (KS == 5) add(integral_constant<int, 4>());
+    else if (KS == 6) add(integral_constant<int, 5>());
+    else if (KS == 7) add(integral_constant<int, 6>());
+    else add(integral_constant<int, MAX_SPLITS - 1>());
+    // Who withdrew its offer a moment ago is on the way to its mark (what has been read of it is what it writes there).
+    const bool late = taking && was != here;
+    while (__builtin_amdgcn_ballot_w64(late && get_agent(mark) != sb.tag)) {}
+    if (lane < KS && (marked || late)) put_agent(mark, 0);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) res[i] = acc[i];
+    Lsum = l;
+    return true;
+}
+
+// APART: the units past the last multiple of eight have their workgroups dealt one to an XCD in turn (a compilation of its own: the test took 0.17 us a launch).
+template <int D, int NW, bool DIRECT, bool APART>
 __global__ __launch_bounds__(64 * NW, 2) void attn_wave_kernel(AttnArgs a, int KS, SplitBuf sb) {
     static_assert((D == 128 || D == 64) && (NW == 4 || NW == 8) && (!DIRECT || (NW == 4 && D == 128)), "shape");
     constexpr int KSTEPS = D / 16, DBLK = D / 32;
     constexpr int K_PITCH = WaveTile<D>::K_PITCH, V_PITCH = WaveTile<D>::V_PITCH;
     const int G = sb.gd.G;
-    // blockIdx.x = kv head: workgroups are dealt to the 8 XCDs round-robin by linear id, so every
-    // row block and split of one kv head lands on one XCD and shares its L2 copy of that head's K/V
-    const int b = __builtin_amdgcn_readfirstlane(KS == 1 ? blockIdx.z : __umulhi(blockIdx.z, sb.ks_magic));
-    const int ks = blockIdx.z - b * KS, h = blockIdx.x;
+    // Workgroups are dealt to the 8 XCDs round-robin by linear id.  With the kv head in x (or in the unit's number, kv heads
+    // first), every row block of a kv head lands on one XCD, where their number is a multiple of eight, and shares its L2 copy of that head's K/V; the splits
+    // of a unit are eight apart.
+    int b = blockIdx.z, h = blockIdx.x, ks = 0, rows = blockIdx.y, unit = 0;
+    bool apart = false;  // this unit's are
+    if constexpr (NW == 4) {
+        unit = 8 * blockIdx.y + (blockIdx.x & 7);
+        ks = blockIdx.x >> 3;
+        if constexpr (APART)
+            if ((int)blockIdx.y == sb.units >> 3) {
+                const int i = (int)(blockIdx.x * sb.ks_magic >> 12);
+                unit = (sb.units & ~7) + i;
+                ks = blockIdx.x - i * KS;
+                apart = true;
+            }
+        if (unit >= sb.units) return;
+        const int t = __builtin_amdgcn_readfirstlane(sb.hd.div(unit));
+        h = unit - t * sb.hd.G;
+        b = __builtin_amdgcn_readfirstlane(sb.md.div(t));
+        rows = t - b * sb.md.G;
+    }
     // The four per-sequence words in one trip to memory: the compiler would fetch the others behind the test of the first.
     int n_raw = a.n_nodes[b], l_raw = a.prefix_len[b];
     u64 kp_raw = (u64)(uintptr_t)a.k_prefix[b], vp_raw = (u64)(uintptr_t)a.v_prefix[b];
     asm volatile("" : "+s"(n_raw), "+s"(l_raw), "+s"(kp_raw), "+s"(vp_raw));
     const int N = min(max(n_raw, 1), a.TT_cap);
     const int M = N * G;
-    const int m0 = blockIdx.y * 32;
+    const int m0 = rows * 32;
     if (m0 >= M) return;
     const int L = max(l_raw, 0);
     const int Tk = L + N;
@@ -1505,13 +1726,27 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_wave_kernel(AttnArgs a, int K
     }
     __syncthreads();
     if (w >= DBLK) return;
-    float Mx = fmaxf(fmaxf(s_m[0][col], s_m[1][col]), fmaxf(s_m[2][col], s_m[3][col]));
+    // the fellows' shares in turn from the next wave on, all of them asked for before the first is used (behind a branch for each fellow they came two at
+    // a time)
+    float4 o[3][4];
+    float mw[4], lw[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        mw[j] = s_m[(w + j) & 3][col];
+        lw[j] = s_l[(w + j) & 3][col];
+    }
+#pragma unroll
+    for (int j = 1; j < 4; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) o[j - 1][q] = xv((w + j) & 3)[(w * 4 + q) * 64 + lane];
+    __builtin_amdgcn_sched_barrier(0);
+    float Mx = fmaxf(fmaxf(mw[0], mw[1]), fmaxf(mw[2], mw[3]));
     const float Mu = Mx == -INFINITY ? 0.f : Mx;
     float f[4], Lsum = 0.f;
 #pragma unroll
-    for (int ww = 0; ww < 4; ++ww) {
-        f[ww] = __builtin_amdgcn_exp2f((s_m[ww][col] - Mu) * c);
-        Lsum += f[ww] * s_l[ww][col];
+    for (int j = 0; j < 4; ++j) {
+        f[j] = __builtin_amdgcn_exp2f((mw[j] - Mu) * c);
+        Lsum += f[j] * lw[j];
     }
     float res[16];
 #pragma unroll
@@ -1520,112 +1755,20 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_wave_kernel(AttnArgs a, int K
     for (int db = 0; db < DBLK; ++db)  // own block (db == w) from registers; static indexing only
         if (db == w)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) res[i] = oacc[db][i] * f[db];
+            for (int i = 0; i < 16; ++i) res[i] = oacc[db][i] * f[0];
 #pragma unroll
-    for (int ww = 0; ww < 4; ++ww) {
-        if (ww == w) continue;
+    for (int j = 1; j < 4; ++j)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const float4 o = xv(ww)[(w * 4 + q) * 64 + lane];
-            res[4 * q] += o.x * f[ww];
-            res[4 * q + 1] += o.y * f[ww];
-            res[4 * q + 2] += o.z * f[ww];
-            res[4 * q + 3] += o.w * f[ww];
+            res[4 * q] += o[j - 1][q].x * f[j];
+            res[4 * q + 1] += o[j - 1][q].y * f[j];
+            res[4 * q + 2] += o[j - 1][q].z * f[j];
+            res[4 * q + 3] += o[j - 1][q].w * f[j];
         }
-    }
-    if (KS > 1) {
-        // ---- leave this workgroup's partial for the merge kernel ---------------------------------
-        const int64_t unit = ((int64_t)b * a.Hkv + h) * gridDim.y + blockIdx.y;
-        float4 *pw = sb.o + ((unit * KS + ks) * DBLK + w) * 4 * 64;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) pw[q * 64 + lane] = make_float4(res[4 * q], res[4 * q + 1], res[4 * q + 2], res[4 * q + 3]);
-        if (w == 0 && half == 0) sb.ml[(unit * KS + ks) * 32 + col] = make_float2(Mx, Lsum);
-        return;
+    if constexpr (NW == 4) {  // (eight waves take all keys of a unit)
+        if (!join_splits<DBLK>(sb, (int64_t)unit * DBLK + w, KS, ks, apart, w, lane, c, res, Mx, Lsum)) return;
     }
     if (!qvalid) return;
-    const float inv = Lsum > 0.f ? 1.0f / Lsum : 0.f;
-    __bf16 *op = (__bf16 *)a.out + (((int64_t)b * a.TT_cap + node) * a.Hq + hq) * D + 32 * w;
-#pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4) {
-        bf16x4 o4;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o4[e] = (__bf16)(res[q4 * 4 + e] * inv);
-        *(bf16x4 *)(op + 8 * q4 + 4 * half) = o4;
-    }
-}
-
-// Merge of the KS partials of every (sequence, kv head, 32-row block): thread (w, lane) owns the
-// same 16 output values it would own in the single-split epilogue, so the partials are read
-// back in exactly the layout they were written in.  Four partials at a time, all their loads asked for before the first
-// is used and before the node count that says which rows exist (a loop that waited for each partial's statistics and then
-// for its values was up to six trips to memory long: 4.7 us on the 8B shape with three splits).  Fewer than four are read as
-// what they are: the last one again, weighed by zero, in the place of a missing fourth turned an infinity of that split into a
-// NaN, and its loads cost 0.4 us a launch (32 layers of the 8B shape, three splits: 380 us; this: 367).  Two waves to a SIMD are
-// enough of them: with registers for more the compiler asks for the last of three partials when the first are there (the same layers with that
-// and the node count in front 365 us, the count behind 356, this 352).
-template <int D>
-__global__ __launch_bounds__(2 * D) __attribute__((amdgpu_waves_per_eu(1, 2))) void attn_wave_merge_kernel(AttnArgs a, int KS, SplitBuf sb) {
-    constexpr int DBLK = D / 32;
-    const int G = a.Hq / a.Hkv;
-    const int b = blockIdx.z, h = blockIdx.x;
-    const int m0 = blockIdx.y * 32;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int half = lane >> 5, col = lane & 31;
-    const int mq = m0 + col;
-    const float c = a.scale * 1.4426950408889634f;
-    const int64_t unit = ((int64_t)b * a.Hkv + h) * gridDim.y + blockIdx.y;
-    // By a vector load: a scalar one is waited for with the kernel's arguments, in front of the partials' loads.
-    int zero;
-    asm volatile("v_mov_b32 %0, 0" : "=v"(zero));
-    const int n_raw = a.n_nodes[b + zero];
-    float M = -INFINITY, Lsum = 0.f;
-    float res[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) res[i] = 0.f;
-    auto join = [&](auto n_c, int s0) {  // partials s0 .. s0 + n - 1
-        constexpr int n = decltype(n_c)::value;
-        float2 ml[n];
-        float4 o[n][4];
-#pragma unroll
-        for (int u = 0; u < n; ++u) ml[u] = sb.ml[(unit * KS + s0 + u) * 32 + col];
-#pragma unroll
-        for (int u = 0; u < n; ++u) {
-            const float4 *pr = sb.o + ((unit * KS + s0 + u) * DBLK + w) * 4 * 64;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) o[u][q] = pr[q * 64 + lane];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        float Mn = M;
-#pragma unroll
-        for (int u = 0; u < n; ++u) Mn = fmaxf(Mn, ml[u].x);
-        const float Mu = Mn == -INFINITY ? 0.f : Mn;
-        const float keep = __builtin_amdgcn_exp2f((M - Mu) * c);
-        Lsum *= keep;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) res[i] *= keep;
-#pragma unroll
-        for (int u = 0; u < n; ++u) {
-            const float fs = __builtin_amdgcn_exp2f((ml[u].x - Mu) * c);
-            Lsum += ml[u].y * fs;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                res[4 * q] += o[u][q].x * fs;
-                res[4 * q + 1] += o[u][q].y * fs;
-                res[4 * q + 2] += o[u][q].z * fs;
-                res[4 * q + 3] += o[u][q].w * fs;
-            }
-        }
-        M = Mn;
-    };
-    using std::integral_constant;
-    int s0 = 0;
-    for (; s0 + 4 <= KS; s0 += 4) join(integral_constant<int, 4>(), s0);
-    if (KS - s0 == 3) join(integral_constant<int, 3>(), s0);
-    else if (KS - s0 == 2) join(integral_constant<int, 2>(), s0);
-    else if (KS - s0 == 1) join(integral_constant<int, 1>(), s0);
-    const int N = min(max(n_raw, 1), a.TT_cap);
-    if (mq >= N * G) return;
-    const int node = mq / G, hq = h * G + mq % G;
     const float inv = Lsum > 0.f ? 1.0f / Lsum : 0.f;
     __bf16 *op = (__bf16 *)a.out + (((int64_t)b * a.TT_cap + node) * a.Hq + hq) * D + 32 * w;
 #pragma unroll
@@ -1916,13 +2059,16 @@ __global__ __launch_bounds__(512) void attn_f32_kernel(AttnArgs a) {
 // ------------------------------------------------------------------------------- launchers --
 // LDS beyond 64 KB has to be asked for, once per device (dt_init)
 hipError_t attn_init() {
-    hipError_t e = hipFuncSetAttribute((const void *)attn_wave_kernel<128, 8, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    hipError_t e = hipFuncSetAttribute((const void *)attn_wave_kernel<128, 8, false, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        8 * WaveTile<128>::ELEMS * 2);
     if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)attn_wave_kernel<64, 8, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+        e = hipFuncSetAttribute((const void *)attn_wave_kernel<64, 8, false, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 8 * WaveTile<64>::ELEMS * 2);
     if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)attn_wave_kernel<128, 4, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+        e = hipFuncSetAttribute((const void *)attn_wave_kernel<128, 4, true, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                WD_LDS_BYTES);
+    if (e == hipSuccess)
+        e = hipFuncSetAttribute((const void *)attn_wave_kernel<128, 4, true, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 WD_LDS_BYTES);
     if (e == hipSuccess)
         e = hipFuncSetAttribute((const void *)attn_tile_kernel<128, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, TILE_LDS_BYTES(2));
@@ -1939,36 +2085,38 @@ static size_t gang_slot_bytes(int D) { return 2 * ATT_MTILE * ((size_t)D * 4 + 8
 static size_t gang_bytes(int D, int n_cu) { return (size_t)2 * n_cu * gang_slot_bytes(D); }
 
 // scratch of one key split of the small-batch kernel, per (sequence, kv head, 32-row block)
-static size_t wave_unit_bytes(int D) { return (size_t)(D / 32) * 4 * 64 * 16 + 32 * 8; }
+static size_t wave_unit_bytes(int D) { return (size_t)(D / 32) * (4 * 64 * 16 + 32 * 8 + LINE_WORDS * 8 + 8); }
 
 size_t attn_workspace_bytes(int batch, int TT_cap, int Hq, int D, int n_cu) {
     if (D != 128 && D != 64) return 0;
     const size_t units = (size_t)batch * ((TT_cap * Hq + 31) / 32 + Hq);
-    const size_t w8 = units * wave_unit_bytes(D) * 8, g = D == 128 ? gang_bytes(D, n_cu) : 0;
+    const size_t w8 = units * wave_unit_bytes(D) * MAX_SPLITS, g = D == 128 ? gang_bytes(D, n_cu) : 0;
     const size_t cap = (size_t)256 << 20;
     const size_t want = w8 > g ? w8 : g;
     return want < cap ? want : cap;
 }
 
 // Over how many workgroups the keys of a (sequence, kv head, 32-row block) are dealt: nb blocks of 32 keys, `units` such row blocks.
-// At most one workgroup per compute unit (more, with 64-wide heads, which leave room for them, lose: 84 units of 34 blocks 9.9
-// us in 3 splits, 11.2 in 4), and 8.  Split, the four waves of a workgroup take ceil(nb / 4 KS) rounds of about 0.8 us (8B shape, 2,048 to 4,096
-// keys: 0.79 from the L2s and the last-level cache, 1.05 from memory), and each split costs the
-// merge 0.12 us and 1/200 more for every unit: whichever number of splits is cheapest by that.
-// Unsplit, eight waves take half as many rounds as four and need no merge, but a round of theirs is longer, 128-wide heads' by
-// far more: the line lies where the two sides met, us per layer, unsplit against the best split:
-//   128-wide heads, 16 units: 8 blocks 7.6 | 7.3, 9: 8.0 | 7.6, 13: 10.0 | 8.3, 23: 12.2 | 9.0;  64 units: 10: 8.5 | 8.5, 13: 10.1 | 9.2,
-//     21: 11.9 | 9.7, 30: 13.4 | 10.2;  80 units: 9: 9.0 | 9.2, 11: 9.5 | 9.2, 21: 13.1 | 10.7;  128 units: 11: 9.0 | 9.7, 13: 10.3 | 9.7;
-//   64-wide heads, 28 units: 27: 8.6 | 8.9, 31: 9.8 | 9.2, 43: 11.4 | 9.8;  84 units: 27: 9.2 | 9.9, 31: 10.1 | 9.9, 43: 11.5 | 10.8, in two
-//     splits 52: 12.5 | 12.7, 66: 14.9 | 14.5.
-// (A split for every eleven blocks: 64 units of 21 blocks 11.9, of 30 10.7, 80 units of 31 14.4; 64-wide heads, 84 units of 27 10.3.)
+// At most one workgroup per compute unit, and MAX_SPLITS.  Split, the four waves of a workgroup take ceil(nb / 4 KS) rounds of about 0.75 us (0.84 of
+// 64-wide heads), and the exchange costs the more the more partials an owner reads: from four splits on each workgroup owns one column block or none.
+// Unsplit, eight waves share the four SIMDs, 0.55 us for every four blocks, and there is nothing to exchange.  Whatever is cheapest by that, in 1/100 us, from six
+// blocks on.
+// us per layer, 16 layers, unsplit | two | three | four | eight splits:
+//   128-wide heads, 4 units: 5 blocks 6.6 | 6.6 | 6.7 | 6.8 | 7.4, 7: 7.1 | 6.3 | 6.6 | 6.5 | 7.4, 32: 12.5 | 8.9 | 8.4 | 7.8 | 8.0, 63: 18.2 | 11.3 | 10.2 | 9.0 | 8.7;
+//     64 units: 7: 7.7 | 7.1 | 7.6 | 7.3, 9: 8.0 | 8.1 | 7.7 | 7.6, 13: 9.6 | 8.4 | 8.4 | 7.5, 34: 13.0 | 10.2 | 9.3 | 9.1, 127: 33.2 | 20.6 | 16.5 | 14.3;
+//     128 units: 7: 7.8 | 7.6, 9: 8.4 | 8.4, 11: 8.6 | 8.6, 13: 9.8 | 8.6, 34: 13.2 | 10.6;
+//   64-wide heads, 28 units: 7: 6.1 | 6.4 | 6.6 | 6.4 | 7.2, 11: 6.5 | 7.1 | 6.6 | 6.6 | 7.2, 15: 7.5 | 7.1 | 7.3 | 6.7 | 7.2, 46: 12.0 | 10.7 | 9.3 | 8.6 | 8.4;
+//     128 units: 10: 6.5 | 7.4, 15: 7.8 | 7.8, 26: 8.8 | 9.3, 46: 12.1 | 10.9.
+// (With a merge kernel behind them, splits paid from 9 to 13 blocks on, 29 to 60 of 64-wide heads: 64 units of 13 blocks 9.8, of 34 10.8, 28 units of 46 9.8.)
 static int wave_splits(int D, int64_t units, int64_t nb) {
-    const int most = (int)std::min<int64_t>(8, 256 / units);
-    const int least = D == 128 ? (most == 8 ? 9 : most >= 3 ? 11 : 13) : (most >= 3 ? 29 : 60);
-    if (most < 2 || nb < least) return 1;
-    int best = 2;
-    auto cost = [&](int n) { return 80 * ((nb + 4 * n - 1) / (4 * n)) + (12 + units / 2) * n; };
-    for (int n = 3; n <= most; ++n)
+    const int most = (int)std::min<int64_t>(MAX_SPLITS, 256 / units);
+    auto cost = [&](int64_t n) -> int64_t {
+        if (n == 1) return 55 * ((nb + 3) / 4);
+        const int64_t rounds = (nb + 4 * n - 1) / (4 * n);
+        return (D == 128 ? 25 + 75 * rounds : 80 + 84 * rounds) + (n > 4 ? 20 + 15 * (n - 4) : 5 * (n - 2));
+    };
+    int best = 1;
+    for (int n = 2; n <= most && nb > 5; ++n)
         if (cost(n) < cost(best)) best = n;
     return best;
 }
@@ -2003,7 +2151,13 @@ static int64_t max_blocks(const AttnArgs &a) { return ((int64_t)a.max_prefix_len
 #define WHOLE_BLOCKS 40
 #define WHOLE_BLOCKS_ONE 56
 
-// The small-batch kernel and, with key splits, its merge.
+// A number for the marks and counts of a launch: an odd multiplier's multiples, the low 16 bits free.
+static u64 launch_tag() {
+    static std::atomic<u64> launches{0};
+    return (launches.fetch_add(1, std::memory_order_relaxed) + 1) * 0x9e3779b97f4a7c15ull & ~(u64)0xffff;
+}
+
+// The small-batch kernel.
 template <int D>
 static int wave_launch(const AttnArgs &a, hipStream_t st, hipError_t *err) {
     const int G = a.Hq / a.Hkv;
@@ -2013,22 +2167,34 @@ static int wave_launch(const AttnArgs &a, hipStream_t st, hipError_t *err) {
     const size_t per_split = (size_t)units * wave_unit_bytes(D);
     if (KS > 1 && (!a.ws || (size_t)KS * per_split > a.ws_bytes)) KS = a.ws ? (int)(a.ws_bytes / per_split) : 1;
     if (KS < 1) KS = 1;
-    SplitBuf sb;
+    SplitBuf sb = {};
     sb.gd = group_div(G);
-    sb.ks_magic = (u32)(((u64)1 << 32) / KS + 1);
-    sb.o = (float4 *)a.ws;
-    sb.ml = (float2 *)((char *)a.ws + (size_t)units * KS * (D / 32) * 4 * 64 * 16);
-    dim3 grid(a.Hkv, mblocks, a.batch * KS);
     if (KS > 1) {  // several workgroups per unit: four waves each
-        if constexpr (D == 128)  // one workgroup per compute unit (128 KB of LDS)
-            launch_kernel(KID_ATTN, st, attn_wave_kernel<D, 4, true>, grid, dim3(256), WD_LDS_BYTES, a, KS, sb);
-        else
-            launch_kernel(KID_ATTN, st, attn_wave_kernel<D, 4, false>, grid, dim3(256), 4 * WaveTile<D>::ELEMS * 2, a, KS, sb);
-        *err = hipGetLastError();
-        if (*err != hipSuccess) return DT_ERR_HIP;
-        launch_kernel(KID_ATTN_COMBINE, st, attn_wave_merge_kernel<D>, dim3(a.Hkv, mblocks, a.batch), dim3(2 * D), 0, a, KS, sb);
+        const size_t parts = (size_t)units * (D / 32) * KS;
+        sb.offers = (u64 *)a.ws;
+        sb.o = (float4 *)(sb.offers + parts * LINE_WORDS);
+        sb.ml = (float2 *)(sb.o + parts * 4 * 64);
+        sb.marks = (u64 *)(sb.ml + parts * 32);
+        sb.tag = launch_tag();
+        sb.hd = group_div(a.Hkv);
+        sb.md = group_div(mblocks);
+        sb.units = (int)units;
+        sb.ks_magic = (u32)((4096 + KS - 1) / KS);
+        const dim3 grid(8 * KS, (unsigned)((units + 7) / 8));
+        auto go = [&](auto kernel, size_t lds) { launch_kernel(KID_ATTN, st, kernel, grid, dim3(256), lds, a, KS, sb); };
+        // Where an XCD has no compute unit for one more unit, the last of them, fewer than eight, are spread over all (84 units of 64-wide heads in
+        // three splits of 127 blocks 18.1 us with 33 workgroups on an XCD, 15.8 so; 4 units of 7 blocks, spread 7.7, on four XCDs 6.6).
+        const bool apart = (units + 7) / 8 * KS * 8 > a.n_cu;
+        if constexpr (D == 128) {  // one workgroup per compute unit (128 KB of LDS)
+            if (apart) go(attn_wave_kernel<D, 4, true, true>, WD_LDS_BYTES);
+            else go(attn_wave_kernel<D, 4, true, false>, WD_LDS_BYTES);
+        } else {
+            if (apart) go(attn_wave_kernel<D, 4, false, true>, 4 * WaveTile<D>::ELEMS * 2);
+            else go(attn_wave_kernel<D, 4, false, false>, 4 * WaveTile<D>::ELEMS * 2);
+        }
     } else {       // one workgroup per unit: eight waves (two per SIMD)
-        launch_kernel(KID_ATTN, st, attn_wave_kernel<D, 8, false>, grid, dim3(512), 8 * WaveTile<D>::ELEMS * 2, a, KS, sb);
+        const dim3 grid(a.Hkv, mblocks, a.batch);
+        launch_kernel(KID_ATTN, st, attn_wave_kernel<D, 8, false, false>, grid, dim3(512), 8 * WaveTile<D>::ELEMS * 2, a, KS, sb);
     }
     *err = hipGetLastError();
     return *err == hipSuccess ? DT_OK : DT_ERR_HIP;
@@ -2084,13 +2250,12 @@ int attn_launch(const AttnArgs &a, hipStream_t st, hipError_t *err) {
         *err = hipGetLastError();
         return *err == hipSuccess ? DT_OK : DT_ERR_HIP;
     }
-    static std::atomic<u64> launches{0};
     const size_t slots = (size_t)a.Hkv * P;
     GangPartial part;
     part.o = (u64 *)a.ws;
     part.ml = part.o + slots * 2 * ATT_MTILE * (a.D / 2);
     part.count = part.ml + slots * 2 * ATT_MTILE;
-    part.tag = (launches.fetch_add(1, std::memory_order_relaxed) + 1) * 0x9e3779b97f4a7c15ull & ~(u64)0xffff;
+    part.tag = launch_tag();
     launch_kernel(KID_ATTN, st, attn_gang_kernel<128>, dim3(a.Hkv, P), dim3(256), TILE_LDS_BYTES(2), a, group_div(G), P, part);
     *err = hipGetLastError();
     return *err == hipSuccess ? DT_OK : DT_ERR_HIP;

@@ -227,6 +227,47 @@ def test_numbers_of_key_splits(D, Hkv, L):
     check_case(oracle_case(0, cfg=_cfg("bf16", D, [(32, 5, 6)], [L], Hkv, Hkv)))
 
 
+# Splits of a row block that meet in one XCD, in two to eight; and, 84 row blocks in three splits, the last four of them spread over the XCDs, where
+# partials go by the memory side.  Rows and keys that end early (one sequence of one node), the same bits whatever the workspace
+# held before and from a replayed graph whose launch keeps its number, lengths and workspace changing between the replays.
+@pytest.mark.parametrize("D,Hkv,B,L", [(128, 4, 1, 700), (128, 4, 1, 330), (64, 4, 1, 1300), (128, 20, 1, 1000), (64, 28, 3, 1100), (128, 28, 3, 460)])
+def test_key_splits_meet(D, Hkv, B, L):
+    params = [(32, 5, 6) if b != 1 else (1, 1, 1) for b in range(B)]
+    case = oracle_case(0, cfg=_cfg("bf16", D, params, [L - 7 * b for b in range(B)], Hkv, Hkv))
+    st = check_case(case)
+    lengths = [st.prefix_len.clone(), torch.clamp(st.prefix_len // 3, min=1)]
+
+    def run():
+        st.tree_attention()
+        return [st.out[b, :case.trees[b]["n_nodes"]].view(torch.int16).clone() for b in range(B)]
+
+    want = []
+    for plen in lengths:
+        st.prefix_len.copy_(plen)
+        want.append(run())
+        for fill in (0x00, 0xff, 0x3f):
+            st.ws.fill_(fill)
+            st.out.fill_(7.0)
+            assert all(torch.equal(x, y) for x, y in zip(run(), want[-1])), fill
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        g = torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(g, stream=side):
+            st.tree_attention()
+            st.tree_attention()
+    for rep, (which, fill) in enumerate([(0, None), (0, None), (1, None), (0, 0x5a), (1, 0xff), (0, None)]):
+        st.prefix_len.copy_(lengths[which])
+        if fill is not None:
+            st.ws.fill_(fill)
+        st.out.fill_(7.0)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        got = [st.out[b, :case.trees[b]["n_nodes"]].view(torch.int16) for b in range(B)]
+        assert all(torch.equal(x, y) for x, y in zip(got, want[which])), rep
+
+
 # one sequence far longer than the others, in every kernel: the balanced schedule (320 and 512 row blocks, four to a kv head), the small-batch kernel with key
 # splits (256, two and one to a kv head) and whole tiles (320, two to a kv head; 260, one, more tiles than compute units).  (The lines between the kernels lie
 # elsewhere: test_lines_between_the_three_kernels and the two before it.)
