@@ -16,7 +16,6 @@
 // strides are not multiples of 16 bytes: attn_simple_kernel.  Plain ALU kernels, one workgroup per (node, head).
 
 #include <algorithm>
-#include <atomic>
 #include <type_traits>
 
 #include "common.hpp"
@@ -176,10 +175,6 @@ struct TileParts {
     u64 *count;   // partials left so far, in the low 16 bits, if the others are `tag`; anything else counts as none
     u64 tag;
 };
-// Partials and counts cross between workgroups that may sit on different XCDs, whose L2 caches are not coherent: relaxed
-// atomics at agent scope go through to the memory side word by word, where a fence would write back and drop the whole L2.
-__device__ __forceinline__ void put_agent(u64 *p, u64 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ u64 get_agent(u64 *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 // One more partial is there: true for the last of `parts`, which also clears the count.  `old`: what the count was a moment ago (the
 // reader of the count before the partials, handed on: a trip less, 12 shapes of 80 to 144 tiles 38.5 -> 38.3 us on average).
 __device__ __forceinline__ bool arrive_last(u64 *count, u64 tag, int parts, u64 old) {
@@ -203,7 +198,6 @@ __device__ __forceinline__ bool arrive_last(u64 *count, u64 tag, int parts, u64 
 // sequences in up to 3 parts 155 us a step, 177 shared; 8 of up to 5, four layers, 497 and 507 to 522.
 #define SERIAL_PARTS 8
 #define MERGE_SLICES 16
-#define STAY_TICKS 5000  // of 10 ns
 struct SharedMerge {
     TileParts pt;
     u64 *marks;   // [slots, 2] `tag` once a partial has been left, anything else before
@@ -1056,14 +1050,11 @@ struct SplitBuf {
     u32 ks_magic;  // x / KS = x * ks_magic / 4096 for x < 64
 };
 #define MAX_SPLITS 8
-#define LINE_WORDS 16     // of 64 bits in a cache line
-#define OFFER_TICKS 1000  // of 10 ns
 
 // Sixteen and eight bytes to the memory side, past the L2s (not coherent between the XCDs inside a launch): a relaxed atomic at
 // agent scope for more than a word.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef u64 u64x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ void put16_agent(float4 *p, f32x4 v) { asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(p), "v"(v) : "memory"); }
 __device__ __forceinline__ void put8_agent(float2 *p, f32x2 v) { asm volatile("global_store_dwordx2 %0, %1, off sc1" ::"v"(p), "v"(v) : "memory"); }
 // N partials (four times 1,024 bytes of a wave from o[u] on, with STATS the statistics at ml[u] too) in one trip, past the L1: from this XCD's L2 what
@@ -1129,7 +1120,6 @@ __device__ __forceinline__ void get_partials(const float4 *const (&o)[N], const 
 // at the memory side; its fellows' offers run out, and of those that mark their partials the last to come sees all marks and takes the
 // block (of the last two at least one sees the other's mark; both taking it write the same, since partials are added in the order of
 // their splits).  Offers end as 0, and marks are taken away by whoever has seen them all: a replayed graph has the same tag.
-__device__ __forceinline__ u32 xcc_id() { return __builtin_amdgcn_s_getreg(20 | 3 << 11); }  // HW_REG_XCC_ID, four bits
 template <int DBLK>
 __device__ __forceinline__ bool join_splits(const SplitBuf &sb, int64_t at, int KS, int ks, bool apart, int w, int lane, float c, float (&res)[16], float M, float &Lsum) {
     const int col = lane & 31, peer = min(lane, KS - 1);
@@ -2150,12 +2140,6 @@ static int64_t max_blocks(const AttnArgs &a) { return ((int64_t)a.max_prefix_len
 #define FEW_TILES_BLOCKS 32
 #define WHOLE_BLOCKS 40
 #define WHOLE_BLOCKS_ONE 56
-
-// A number for the marks and counts of a launch: an odd multiplier's multiples, the low 16 bits free.
-static u64 launch_tag() {
-    static std::atomic<u64> launches{0};
-    return (launches.fetch_add(1, std::memory_order_relaxed) + 1) * 0x9e3779b97f4a7c15ull & ~(u64)0xffff;
-}
 
 // The small-batch kernel.
 template <int D>

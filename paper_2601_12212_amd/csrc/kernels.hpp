@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "../../include/dt.h"
 
 namespace dt {
@@ -21,6 +23,13 @@ inline void launch_kernel(int kid, hipStream_t st, F kernel, dim3 grid, dim3 blo
     hipEvent_t e0, e1;
     if (prof_next(kid, &e0, &e1)) hipExtLaunchKernelGGL(kernel, grid, block, (unsigned)lds, st, e0, e1, 0, args...);
     else hipLaunchKernelGGL(kernel, grid, block, (unsigned)lds, st, args...);
+}
+
+// A number for the marks and counts that the workgroups of a launch leave each other in scratch memory, so that what the memory held before
+// never looks like one: an odd multiplier's multiples, the low 16 bits free.
+inline unsigned long long launch_tag() {
+    static std::atomic<unsigned long long> launches{0};
+    return (launches.fetch_add(1, std::memory_order_relaxed) + 1) * 0x9e3779b97f4a7c15ull & ~0xffffull;
 }
 
 // ------------------------------------------------------------------ row kernels (rows.hip)
@@ -47,6 +56,8 @@ struct RowArgs {
     // ROWS_LEVEL: rows of one level of every sequence, results scattered into the build state
     int level, rows_per_seq, state_rows;
     const int32_t *n_exp_prev;  // [batch] of the last call: its level and the nodes that it expanded, level << 8 | nodes
+    unsigned long long *hands;  // top-k rows in one launch: [rows, 16] offers, [rows, 17] marks
+    unsigned long long tag;     // and its number (launch_tag)
     bool lse_apart;  // set by the launch functions: workgroups n_rows .. 2 n_rows - 1 are there for the rows' log-sum-exps
     int64_t n_rows;  // set by the launch functions: rows of the launch (the grid may overhang)
     // set by the launch functions: read a row's chunk before the row is known to be live (the loads then

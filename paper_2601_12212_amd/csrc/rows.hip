@@ -1,7 +1,8 @@
 // Row kernels: top-k and log-sum-exp over vocabulary rows (draft rows: k best + lse;
 // target rows: arg max, and lse of row/T for stochastic acceptance).
 //
-// Top-k rows of up to 16,384 entries are held by one workgroup each (row_topk_kernel).  Longer ones take two passes.  The
+// Top-k rows of up to 16,384 entries are held by one workgroup each (row_topk_kernel).  Longer ones take two passes, of one launch while
+// that has room on the chip (row_pass_kernel).  The
 // first is a pure stream: a row is cut into chunks of
 // 256*8*NL elements, each lane reads 8*NL of them with coalesced 16-byte loads, and a pair of lanes leaves
 // only its maximum (plus one (max, sum-exp) pair per wave).  The second works on those lane
@@ -106,21 +107,21 @@ struct RawChunk {
 };
 __device__ __forceinline__ int group_start(int V, int id0) { return min(id0, V - 8); }
 
-template <int NL, bool BF16, bool VEC>
+template <int NL, bool BF16, bool VEC, bool KEEP = false>
 __device__ __forceinline__ void chunk_request(const RowArgs &a, int64_t g, int base, RawChunk<NL, BF16> &raw) {
     if (!VEC) return;
     const int V = a.V;
     if (BF16) {
         const uint16_t *row = (const uint16_t *)a.logits + g * a.row_stride;
 #pragma unroll
-        for (int n = 0; n < NL; ++n) raw.r[n] = load16(row + group_start(V, base + n * 512));
+        for (int n = 0; n < NL; ++n) raw.r[n] = load16<KEEP>(row + group_start(V, base + n * 512));
     } else {
         const float *row = (const float *)a.logits + g * a.row_stride;
 #pragma unroll
         for (int n = 0; n < NL; ++n) {
             const float *p = row + group_start(V, base + n * 512);
-            raw.r[2 * n] = load16(p);
-            raw.r[2 * n + 1] = load16(p + 4);
+            raw.r[2 * n] = load16<KEEP>(p);
+            raw.r[2 * n + 1] = load16<KEEP>(p + 4);
         }
     }
     __builtin_amdgcn_sched_barrier(0);  // every request is out before anything that follows
@@ -271,11 +272,11 @@ __global__ __launch_bounds__(256) void row_stream_kernel(RowArgs a, int S) {
 #define SEL_WAVE_CAP 64  // hot lanes of one wave
 // The eight elements from id0 on of row g; returns where they really start (group_start), those before id0 and past the
 // row are -inf.
-template <bool BF16>
+template <bool BF16, bool KEEP>
 __device__ __forceinline__ int load_octet(const RowArgs &a, int64_t g, int id0, float (&xv)[8]) {
     const int start = group_start(a.V, id0);
     if (BF16) {
-        const uint4 r = load16((const uint16_t *)a.logits + g * a.row_stride + start);
+        const uint4 r = load16<KEEP>((const uint16_t *)a.logits + g * a.row_stride + start);
         const u32 rr[4] = {r.x, r.y, r.z, r.w};
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
@@ -284,7 +285,7 @@ __device__ __forceinline__ int load_octet(const RowArgs &a, int64_t g, int id0, 
         }
     } else {
         const float *src = (const float *)a.logits + g * a.row_stride + start;
-        const uint4 r0 = load16(src), r1 = load16(src + 4);
+        const uint4 r0 = load16<KEEP>(src), r1 = load16<KEEP>(src + 4);
         const u32 rr[8] = {r0.x, r0.y, r0.z, r0.w, r1.x, r1.y, r1.z, r1.w};
 #pragma unroll
         for (int e = 0; e < 8; ++e) xv[e] = __uint_as_float(rr[e]);
@@ -380,11 +381,30 @@ __device__ __forceinline__ float spread_max(const float (&it)[8]) {
     return fmaxf(lo, hi);
 }
 
-// (eight waves per SIMD: left alone the compiler takes 76 registers in one mode, 29.3 us for 64 sequences instead of 26.3)
-template <int MODE, bool BF16>
-__global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, int S, float *top_val,
-                                                         int32_t *top_id, float *lse, int out_stride) {
-    const int64_t g = blockIdx.x;
+// A lane maximum, or four, that another workgroup of the launch may have written (SAME) or an earlier launch.
+template <bool BF16>
+struct alignas(4 * sizeof(LaneMax<BF16>)) Quad { LaneMax<BF16> v[4]; };
+template <bool BF16, bool SAME>
+__device__ __forceinline__ Quad<BF16> quad_at(const LaneMax<BF16> *lm, int i) {
+    const Quad<BF16> *p = (const Quad<BF16> *)lm + i;
+    if constexpr (!SAME) return *p;
+    else {
+        u64 v[sizeof(Quad<BF16>) / 8];
+#pragma unroll
+        for (int j = 0; j < (int)(sizeof(Quad<BF16>) / 8); ++j) v[j] = get_agent((u64 *)p + j);
+        return __builtin_bit_cast(Quad<BF16>, v);
+    }
+}
+template <bool BF16, bool SAME>
+__device__ __forceinline__ LaneMax<BF16> lane_max_at(const LaneMax<BF16> *lm, int i) {
+    if constexpr (SAME) return __hip_atomic_load(lm + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else return lm[i];
+}
+// SAME: the maxima are made in this launch (row_pass_kernel), of rows of up to 16 chunks; ready() waits for them, all threads, and says whether this workgroup selects;
+// asked() is called once they have been asked for.
+template <int MODE, bool BF16, bool SAME, typename Ready, typename Asked>
+__device__ __forceinline__ void select_row(const RowArgs &a, int64_t g, int nl, int S, float *top_val, int32_t *top_id, float *lse, int out_stride, Ready ready,
+                                           Asked asked) {
     const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int V = a.V, E = 8 * nl;
     const int n_lm = S * 128;
@@ -396,19 +416,29 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
     // A quarter of them to a wave, every fourth of the 32 S quadruples: lane l holds those in places l and l + 64 of its wave's (so far as there
     // are any).  So the waves share what is read again also where the best are in one part of the row: with a quarter of the row to a wave,
     // 51 rows of 128,256 bf16 entries, k = 28, that fall by 12 along the row 13.0 us, 9.35 so, by ln(1 + id) 12.8 and 10.2, evenly spread ones 9.3 and 9.1.
-    struct alignas(4 * sizeof(LM)) Quad { LM v[4]; };
     // (As they came: converted here, they were waited for before the metadata was asked for, a trip more.  Traced inside steps: 51 rows of 128,256 4.85 ->
     // 4.56 us, 569 6.14 -> 5.93, ten of a level 4.92 -> 4.61.)
-    Quad q[2];
-    if (S <= 16) {
+    RowMeta meta;
+    if constexpr (SAME) {
+        meta = row_meta<MODE>(a, g);
+        if (!meta.valid || !ready()) return;
+    }
+    Quad<BF16> q[2];
+    if (SAME || S <= 16) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) q[i] = ((const Quad *)lm)[4 * min(64 * i + lane, 8 * S - 1) + w];
+        for (int i = 0; i < 2; ++i) q[i] = quad_at<BF16, SAME>(lm, 4 * min(64 * i + lane, 8 * S - 1) + w);
     }
     const bool lse_wave = w == 3 && a.want_lse && lse;
     float2 pm = make_float2(-INFINITY, 0.f);
-    if (lse_wave && S <= 16) pm = a.part_ms[g * S * 4 + min(lane, S * 4 - 1)];
-    const RowMeta meta = row_meta<MODE>(a, g);
-    if (!meta.valid) return;
+    if (lse_wave && (SAME || S <= 16)) {
+        const float2 *p = a.part_ms + g * S * 4 + min(lane, S * 4 - 1);
+        pm = SAME ? __builtin_bit_cast(float2, get_agent((u64 *)p)) : *p;
+    }
+    if constexpr (SAME) asked();
+    else {
+        meta = row_meta<MODE>(a, g);
+        if (!meta.valid) return;
+    }
     const int k = meta.k;
 
     __shared__ __attribute__((aligned(16))) uint16_t s_key[256];
@@ -432,7 +462,7 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
         if (!lse_wave) return;
         const float cexp = 1.4426950408889634f * a.inv_t;
         float M = -INFINITY, Ssum = 0.f;
-        if (S <= 16) {
+        if (SAME || S <= 16) {
             if (lane < S * 4) { M = pm.x; Ssum = pm.y; }
         } else {
             for (int i = lane; i < S * 4; i += 64) {
@@ -457,7 +487,7 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
     };
     auto reread = [&](int i, int n, float T) {
         float xv[8];
-        const int start = load_octet<BF16>(a, g, octet_of(i, n), xv);
+        const int start = load_octet<BF16, SAME>(a, g, octet_of(i, n), xv);
         keep_hits<8>([&](int e) { return xv[e]; }, [&](int e) { return start + e; }, T, &s_n2, s_fin);
     };
     // candidate t ranks itself against all n2 keys (LDS broadcasts, eight in flight)
@@ -482,7 +512,7 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
 
     // ---- 1. thread maxima and T -------------------------------------------------------------------
     float it[8], tmax = -INFINITY;
-    if (S <= 16) {
+    if (SAME || S <= 16) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) it[j] = 64 * (j >> 2) + lane < 8 * S ? lane_max_value<BF16>(q[j >> 2].v[j & 3]) : -INFINITY;
         tmax = spread_max(it);
@@ -499,7 +529,7 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
     const float T0 = key_edge(key0);
 
     // ---- 2. the lanes that reach T, read again ------------------------------------------------------
-    if (S <= 16) {
+    if (SAME || S <= 16) {
         // Every wave by itself: its hot lanes into a list of its own (a prefix sum over the lanes instead of an LDS
         // counter, no barrier), then (hot lane, load n) pairs over its lanes.
         u32 hot = 0;
@@ -528,8 +558,8 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
                 for (int q = lane; q < total >> 1; q += 64) {
                     float x[2][8];
                     const int i = list[q >> pairs_log2], n = 2 * (q & mask);
-                    const int s0 = load_octet<BF16>(a, g, octet_of(i, n), x[0]);
-                    const int s1 = load_octet<BF16>(a, g, octet_of(i, n + 1), x[1]);
+                    const int s0 = load_octet<BF16, SAME>(a, g, octet_of(i, n), x[0]);
+                    const int s1 = load_octet<BF16, SAME>(a, g, octet_of(i, n + 1), x[1]);
                     keep_hits<16>([&](int e) { return x[e >> 3][e & 7]; }, [&](int e) { return (e < 8 ? s0 : s1 - 8) + e; }, T0, &s_n2, s_fin);
                 }
             }
@@ -549,7 +579,7 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
     }
 
     // ---- second bound: histogram of the lane maxima >= T0; its scan from the top gives T1 ------------
-    auto lane_val = [&](int i) { return lane_max_value<BF16>(lm[i]); };
+    auto lane_val = [&](int i) { return lane_max_value<BF16>(lane_max_at<BF16, SAME>(lm, i)); };
     s_hist[tid] = 0u;
     __syncthreads();
     for (int i = tid; i < n_lm; i += 256) {
@@ -642,8 +672,8 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
         u32 todo = 0;
         if (q < total && (listed || lane_val(i) >= T1)) {
             const int m = 2 * (q & ((1 << pairs_log2) - 1));
-            s0 = load_octet<BF16>(a, g, octet_of(i, m), x[0]);
-            s1 = load_octet<BF16>(a, g, octet_of(i, m + 1), x[1]);
+            s0 = load_octet<BF16, SAME>(a, g, octet_of(i, m), x[0]);
+            s1 = load_octet<BF16, SAME>(a, g, octet_of(i, m + 1), x[1]);
 #pragma unroll
             for (int e = 0; e < 16; ++e)
                 todo |= (make_key(x[e >> 3][e & 7], (u32)((e < 8 ? s0 : s1 - 8) + e)) >= threshold ? 1u : 0u) << e;
@@ -677,6 +707,75 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, i
     }
     rank_and_emit(n);
     if (tid >= n && tid < k) emit(tid, make_key(-INFINITY, 0u));
+}
+
+// (eight waves per SIMD: left alone the compiler takes 76 registers in one mode, 29.3 us for 64 sequences instead of 26.3)
+template <int MODE, bool BF16>
+__global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, int S, float *top_val, int32_t *top_id, float *lse, int out_stride) {
+    select_row<MODE, BF16, false>(a, blockIdx.x, nl, S, top_val, top_id, lse, out_stride, [] { return true; }, [] {});
+}
+
+// ------------------------------------------------------------- both passes in one launch (top-k rows) --
+// Workgroups of the stream, and one to a row that waits for the row's chunks and selects (select_row).  Between two launches lie the first one's end, the
+// second's start, its arguments and its rows' metadata; here the maxima go through the L2 of the XCD that has the row, in three trips of 0.4 us (written, offered, read),
+// and what is read again comes from there as well, since the stream asks for it to stay.  51 rows of 128,256 bf16 entries, from memory: elements there after 2.1 us on average
+// (3.2 the last), their maxima 0.5 later, all of a row's at its selecting workgroup after 4.0, bound 1.6 later, hits 1.1, end 0.5.  (As many of
+// a row's entries to a workgroup as it can hold, each finding its own k best, and lists of those merged: 11.7 us a call against 9.6 in two launches: 16
+// waves take 1.7 us to their bound, and the merge 2.7.)
+template <int MODE, int NL, bool BF16>
+__global__ __launch_bounds__(256, 8) void row_pass_kernel(RowArgs a, int S, float *top_val, int32_t *top_id, float *lse, int out_stride) {
+    constexpr int E = 8 * NL;
+    // The workgroups of a row, a chunk each and one that selects, are eight apart: dealt to the XCDs in turn, they fall to one.
+    const int64_t g = 8 * blockIdx.y + (blockIdx.x & 7);
+    const int c = blockIdx.x >> 3;
+    if (g >= a.n_rows) return;
+    const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    __shared__ int s_go;
+    const Hands hands = {a.hands + g * 16, a.hands + a.n_rows * 16 + g * 17, a.tag, S};
+    bool taking = false;
+    if (c < S) {
+        const int base = c * (256 * E) + w * (64 * E) + lane * 8 - row_shift(a.logits, BF16, a.V, a.row_stride, g);
+        RawChunk<NL, BF16> raw;
+        chunk_request<NL, BF16, true, true>(a, g, base, raw);
+        if (!row_meta<MODE>(a, g).valid) return;
+        float x[E];
+        chunk_finish<NL, BF16, true, BF16>(a, g, base, (c + 1) * (256 * E), raw, x);
+        float mx = x[0];
+#pragma unroll
+        for (int j = 1; j < E; ++j) mx = fmaxf(mx, x[j]);
+        const float mx2 = fmaxf(mx, __int_as_float(dpp_mov<0xB1, 0xf>(0, __float_as_int(mx))));  // lane ^ 1
+        const LaneMax<BF16> pair = lane_max_pack<BF16>(mx2);
+        float2 p = make_float2(0.f, 0.f);
+        if (a.want_lse) p = wave_lse_partial<E>(x, mx, a.inv_t);
+        LaneMax<BF16> *lm = (LaneMax<BF16> *)a.lane_max + (g * S + c) * 128 + w * 32 + (lane >> 1);
+        u64 *ms = (u64 *)(a.part_ms + (g * S + c) * 4 + w);
+        if ((lane & 1) == 0) *lm = pair;
+        if (lane == 0) *ms = __builtin_bit_cast(u64, p);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (w == 0) {
+            const bool taken = hand_offer(hands, c, lane);
+            if (lane == 0) s_go = !taken;
+        }
+        __syncthreads();
+        if (!s_go) return;
+        if ((lane & 1) == 0) __hip_atomic_store(lm, pair, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (lane == 0) put_agent(ms, __builtin_bit_cast(u64, p));
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+    }
+    select_row<MODE, BF16, true>(a, g, NL, S, top_val, top_id, lse, out_stride,
+                                 [&] {
+                                     if (w == 0) {
+                                         const bool all = c < S ? hand_mark(hands, c, lane) : hand_await(hands, lane, taking);
+                                         if (lane == 0) s_go = all;
+                                     }
+                                     __syncthreads();
+                                     return s_go != 0;
+                                 },
+                                 [&] {
+                                     if (w == 0) hand_settle(hands, lane, taking);
+                                 });
 }
 
 // ---------------------------------------------------- rows that one workgroup holds (top-k rows) --
@@ -1321,6 +1420,38 @@ static hipError_t launch_select(const RowArgs &a, int64_t n_rows, int nl, float 
     return hipGetLastError();
 }
 
+// Both passes in one launch: while all its workgroups are on the chip at once, and in bf16 up to some 13 MB of entries.  Beyond, the stream is bound by bandwidth and
+// the exponentials, and what the launch saves goes into more workgroups to a compute unit; fp32 rows, without the exponentials' weight, gain
+// throughout, since a row is selected while others still stream.  Calls, k = 12, two launches | one: bf16 of 128,256 entries 10 rows 7.8 | 6.7 us, 28 8.1 | 7.2, 44
+// 8.4 | 8.1, 64 9.0 | 9.5, 80 9.6 | 10.1; of 90,001 48 rows 9.0 | 7.2, 72 9.1 | 8.7, 100 9.6 | 9.6; of 50,001 28 8.0 | 6.6, 64 8.0 | 7.1, 112 9.0 | 8.3, 144 9.2 | 9.5; of
+// 36,000 112 8.9 | 7.5; fp32 of 128,256 28 rows 9.2 | 8.8, 64 11.9 | 11.5, 120 17.1 | 15.6; of 50,001 61 9.15 | 8.19, 144 12.0 | 11.5; of 20,001 112 8.9 | 7.6.
+#define PASS_WGS 2048
+#define PASS_ENTRIES ((int64_t)13 << 19)
+static bool takes_pass(const RowArgs &a, int64_t n_rows, int nl) {
+    const int64_t S = rows_chunks_per_row(a.V, nl);
+    return S <= 16 && (n_rows + 7) / 8 * 8 * (S + 1) <= PASS_WGS && (a.dtype == DT_F32 || n_rows * a.V <= PASS_ENTRIES);
+}
+static hipError_t launch_pass(const RowArgs &a_in, int64_t n_rows, int nl, float *top_val, int32_t *top_id, float *lse, int out_stride, hipStream_t st) {
+    RowArgs a = a_in;
+    const int S = rows_chunks_per_row(a.V, nl);
+    a.early_load = 1;
+    a.n_rows = n_rows;
+    a.hands = (unsigned long long *)((char *)a.lane_max + n_rows * S * 512);  // behind the maxima, whose room is twice that
+    a.tag = launch_tag();
+    const int kid = a.mode == ROWS_DRAFT ? KID_ROWS_DRAFT : KID_ROWS_UNIFORM;
+    by_mode_and_type(a, [&](auto mode, auto bf16) {
+        constexpr int MODE = decltype(mode)::value;
+        constexpr bool BF = decltype(bf16)::value;
+        auto go = [&](auto kernel) {
+            launch_kernel(kid, st, kernel, dim3(8 * (S + 1), (unsigned)((n_rows + 7) / 8)), dim3(256), 0, a, S, top_val, top_id, lse, out_stride);
+        };
+        if (nl == 4) go(row_pass_kernel<MODE, 4, BF>);
+        else if (nl == 2) go(row_pass_kernel<MODE, 2, BF>);
+        else go(row_pass_kernel<MODE, 1, BF>);
+    });
+    return hipGetLastError();
+}
+
 // Rows that a workgroup holds.
 static int held_threads(int V) { return V <= 256 * 16 ? 256 : V <= 512 * 16 ? 512 : 1024; }
 // While every row of 1,024 threads leaves another compute unit idle, its exponentials are summed there, by a workgroup of its own that
@@ -1412,6 +1543,7 @@ hipError_t rows_launch_topk(const RowArgs &a, int64_t n_rows, float *top_val, in
     // was sized for the smaller ones.)
     int nl = rows_topk_nl(a.V);
     if (nl == 2 && n_rows * rows_chunks_per_row(a.V, 4) > EARLY_LOAD_WGS) nl = 4;
+    if (takes_pass(a, n_rows, nl)) return launch_pass(a, n_rows, nl, top_val, top_id, lse, out_stride, st);
     const hipError_t e = launch_stream(a, n_rows, nl, st);
     return e != hipSuccess ? e : launch_select(a, n_rows, nl, top_val, top_id, lse, out_stride, st);
 }

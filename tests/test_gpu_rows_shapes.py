@@ -6,7 +6,7 @@ import pytest
 
 import dt_synth
 from oracle import ref
-from paper_2601_12212_amd import dt_workspace_bytes
+from paper_2601_12212_amd import dt_topk_rows, dt_workspace_bytes
 from tests._cases import TREE_MARGIN, assert_tree_equal
 from tests.test_gpu_parity import check_topk, dev_logits
 
@@ -157,6 +157,41 @@ def check_repeated_rows(V, n, bf16, gap=0):
     assert np.array_equal(idx.cpu().numpy(), widx[which]) and np.array_equal(val.cpu().numpy(), wval[which])
     # as for smaller launches: fp32 partial sums against double ones
     assert np.all(np.abs(lse.cpu().numpy() - wlse[which]) <= 4e-6 * np.maximum(1.0, np.abs(wlse[which])))
+
+
+# Both passes in one launch and the first sizes beyond: 13 * 2^19 bf16 entries, 2,048 workgroups of which each row has one more than chunks; one row, rows that do not
+# fill the last eight; then the same bits whatever the workspace held before, and from a replayed graph whose launch keeps its number.
+@pytest.mark.parametrize("V,n,bf16", [(128256, 53, True), (128256, 54, True), (32769, 200, True), (65537, 1, True), (16385, 200, False), (16385, 201, False),
+                                      (131072, 120, False), (131072, 121, False), (131073, 9, False)])
+def test_topk_rows_in_one_launch_of_both_passes(V, n, bf16):
+    check_repeated_rows(V, n, bf16, 1)
+    k = 13
+    x = torch.randn((n, V), device="cuda", generator=torch.Generator("cuda").manual_seed(V)).mul_(3).to(torch.bfloat16 if bf16 else torch.float32)
+    ws = torch.empty(dt_workspace_bytes(1, n, V, 8, 1, 64), dtype=torch.uint8, device="cuda")
+    out = [torch.empty((n, k), device="cuda"), torch.empty((n, k), dtype=torch.int32, device="cuda"), torch.empty(n, device="cuda")]
+    want = None
+    for fill in (0x00, 0xff, 0x3f):
+        ws.fill_(fill)
+        dt_topk_rows(x, k, *out, ws)
+        got = [o.clone() for o in out]
+        assert want is None or all(torch.equal(a, b) for a, b in zip(got, want)), fill
+        want = got
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        g = torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(g, stream=side):
+            dt_topk_rows(x, k, *out, ws)
+            dt_topk_rows(x, k, *out, ws)
+    for rep, fill in enumerate((None, None, 0x5a, None)):
+        if fill is not None:
+            ws.fill_(fill)
+        for o in out:
+            o.zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(out, want)), rep
 
 
 @pytest.mark.parametrize("V", [18433, 34817, 36865, 67585, 74365, 126977])   # 10, 9, 10, 9, 10 and 16 chunks, the last one begun
