@@ -56,8 +56,6 @@ struct RowArgs {
     // ROWS_LEVEL: rows of one level of every sequence, results scattered into the build state
     int level, rows_per_seq, state_rows;
     const int32_t *n_exp_prev;  // [batch] of the last call: its level and the nodes that it expanded, level << 8 | nodes
-    unsigned long long *hands;  // top-k rows in one launch: [rows, 16] offers, [rows, 17] marks
-    unsigned long long tag;     // and its number (launch_tag)
     bool lse_apart;  // set by the launch functions: workgroups n_rows .. 2 n_rows - 1 are there for the rows' log-sum-exps
     int64_t n_rows;  // set by the launch functions: rows of the launch (the grid may overhang)
     // set by the launch functions: read a row's chunk before the row is known to be live (the loads then

@@ -2,7 +2,7 @@
 // target rows: arg max, and lse of row/T for stochastic acceptance).
 //
 // Top-k rows of up to 16,384 entries are held by one workgroup each (row_topk_kernel).  Longer ones take two passes, of one launch while
-// that has room on the chip (row_pass_kernel).  The
+// that has room on the chip (row_select_kernel).  The
 // first is a pure stream: a row is cut into chunks of
 // 256*8*NL elements, each lane reads 8*NL of them with coalesced 16-byte loads, and a pair of lanes leaves
 // only its maximum (plus one (max, sum-exp) pair per wave).  The second works on those lane
@@ -400,42 +400,97 @@ __device__ __forceinline__ LaneMax<BF16> lane_max_at(const LaneMax<BF16> *lm, in
     if constexpr (SAME) return __hip_atomic_load(lm + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     else return lm[i];
 }
-// SAME: the maxima are made in this launch (row_pass_kernel), of rows of up to 16 chunks; ready() waits for them, all threads, and says whether this workgroup selects;
-// asked() is called once they have been asked for.
-template <int MODE, bool BF16, bool SAME, typename Ready, typename Asked>
-__device__ __forceinline__ void select_row(const RowArgs &a, int64_t g, int nl, int S, float *top_val, int32_t *top_id, float *lse, int out_stride, Ready ready,
-                                           Asked asked) {
+// PASS: the maxima are made in the same launch, in chunks of 2,048 PASS entries, up to 16 of them.  0: by the launch before.
+// Both passes in one launch: workgroups of the stream, and one to a row that waits for the row's chunks and selects.  Between two launches lie the first one's end, the
+// second's start, its arguments and its rows' metadata; here the maxima go through the L2 of the XCD that has the row, in three trips of 0.4 us (written, offered, read),
+// and what is read again comes from there as well, since the stream asks for it to stay.  51 rows of 128,256 bf16 entries, from memory: elements there after 2.1 us on average
+// (3.2 the last), their maxima 0.5 later, all of a row's at its selecting workgroup after 4.0, bound 1.6 later, hits 1.1, end 0.5.  (As many of
+// a row's entries to a workgroup as it can hold, each finding its own k best, and lists of those merged: 11.7 us a call against 9.6 in two launches: 16
+// waves take 1.7 us to their bound, and the merge 2.7.)
+// (eight waves per SIMD: left alone the compiler takes 76 registers in one mode, 29.3 us for 64 sequences instead of 26.3)
+template <int MODE, bool BF16, int PASS>
+__global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl_, int S, float *top_val, int32_t *top_id, float *lse, int out_stride, u64 tag) {
+    constexpr bool SAME = PASS > 0;
+    const int nl = SAME ? PASS : nl_;
+    // (PASS: the workgroups of a row are eight apart: dealt to the XCDs in turn, they fall to one)
+    const int64_t g = SAME ? 8 * blockIdx.y + (blockIdx.x & 7) : blockIdx.x;
     const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int V = a.V, E = 8 * nl;
     const int n_lm = S * 128;
     typedef LaneMax<BF16> LM;
     const LM *lm = (const LM *)a.lane_max + g * n_lm;
-    // the lane maxima do not depend on the row's metadata (two dependent global reads): ask for them
-    // first, and wave 3 for the row's (max, sum) partials.  Rows that turn out to be dead have their
-    // slots in the workspace all the same.
-    // A quarter of them to a wave, every fourth of the 32 S quadruples: lane l holds those in places l and l + 64 of its wave's (so far as there
-    // are any).  So the waves share what is read again also where the best are in one part of the row: with a quarter of the row to a wave,
-    // 51 rows of 128,256 bf16 entries, k = 28, that fall by 12 along the row 13.0 us, 9.35 so, by ln(1 + id) 12.8 and 10.2, evenly spread ones 9.3 and 9.1.
-    // (As they came: converted here, they were waited for before the metadata was asked for, a trip more.  Traced inside steps: 51 rows of 128,256 4.85 ->
-    // 4.56 us, 569 6.14 -> 5.93, ten of a level 4.92 -> 4.61.)
-    RowMeta meta;
-    if constexpr (SAME) {
-        meta = row_meta<MODE>(a, g);
-        if (!meta.valid || !ready()) return;
-    }
     Quad<BF16> q[2];
-    if (SAME || S <= 16) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i) q[i] = quad_at<BF16, SAME>(lm, 4 * min(64 * i + lane, 8 * S - 1) + w);
-    }
     const bool lse_wave = w == 3 && a.want_lse && lse;
     float2 pm = make_float2(-INFINITY, 0.f);
-    if (lse_wave && (SAME || S <= 16)) {
-        const float2 *p = a.part_ms + g * S * 4 + min(lane, S * 4 - 1);
-        pm = SAME ? __builtin_bit_cast(float2, get_agent((u64 *)p)) : *p;
-    }
-    if constexpr (SAME) asked();
-    else {
+    RowMeta meta;
+    if constexpr (SAME) {
+        const int c = blockIdx.x >> 3;
+        if (g >= a.n_rows) return;
+        __shared__ int s_go;
+        // offers and marks behind the maxima, whose room is twice what they take: a cache line and 17 words to a row
+        u64 *const words = (u64 *)((char *)a.lane_max + a.n_rows * S * 512);
+        const Hands hands = {words + g * LINE_WORDS, words + a.n_rows * LINE_WORDS + g * 17, tag, S};
+        if (c < S) {
+            constexpr int EC = 8 * PASS;
+            const int base = c * (256 * EC) + w * (64 * EC) + lane * 8 - row_shift(a.logits, BF16, a.V, a.row_stride, g);
+            RawChunk<PASS, BF16> raw;
+            chunk_request<PASS, BF16, true, true>(a, g, base, raw);
+            meta = row_meta<MODE>(a, g);
+            if (!meta.valid) return;
+            float x[EC];
+            chunk_finish<PASS, BF16, true, BF16>(a, g, base, (c + 1) * (256 * EC), raw, x);
+            float mx = x[0];
+#pragma unroll
+            for (int j = 1; j < EC; ++j) mx = fmaxf(mx, x[j]);
+            const float mx2 = fmaxf(mx, __int_as_float(dpp_mov<0xB1, 0xf>(0, __float_as_int(mx))));  // lane ^ 1
+            const LM pair = lane_max_pack<BF16>(mx2);
+            float2 p = make_float2(0.f, 0.f);
+            if (a.want_lse) p = wave_lse_partial<EC>(x, mx, a.inv_t);
+            LM *own = (LM *)a.lane_max + (g * S + c) * 128 + w * 32 + (lane >> 1);
+            u64 *ms = (u64 *)(a.part_ms + (g * S + c) * 4 + w);
+            if ((lane & 1) == 0) *own = pair;
+            if (lane == 0) *ms = __builtin_bit_cast(u64, p);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            if (w == 0) {
+                const bool taken = hand_offer(hands, c, lane);
+                if (lane == 0) s_go = !taken;
+            }
+            __syncthreads();
+            if (!s_go) return;
+            if ((lane & 1) == 0) __hip_atomic_store(own, pair, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (lane == 0) put_agent(ms, __builtin_bit_cast(u64, p));
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+        } else {
+            meta = row_meta<MODE>(a, g);
+            if (!meta.valid) return;
+        }
+        bool taking = false;
+        if (w == 0) {
+            const bool all = c < S ? hand_mark(hands, c, lane) : hand_await(hands, lane, taking);
+            if (lane == 0) s_go = all;
+        }
+        __syncthreads();
+        if (!s_go) return;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) q[i] = quad_at<BF16, true>(lm, 4 * min(64 * i + lane, 8 * S - 1) + w);
+        if (lse_wave) pm = __builtin_bit_cast(float2, get_agent((u64 *)(a.part_ms + g * S * 4 + min(lane, S * 4 - 1))));
+        if (w == 0) hand_settle(hands, lane, taking);
+    } else {
+        // the lane maxima do not depend on the row's metadata (two dependent global reads): ask for them
+        // first, and wave 3 for the row's (max, sum) partials.  Rows that turn out to be dead have their
+        // slots in the workspace all the same.
+        // A quarter of them to a wave, every fourth of the 32 S quadruples: lane l holds those in places l and l + 64 of its wave's (so far as there
+        // are any).  So the waves share what is read again also where the best are in one part of the row: with a quarter of the row to a wave,
+        // 51 rows of 128,256 bf16 entries, k = 28, that fall by 12 along the row 13.0 us, 9.35 so, by ln(1 + id) 12.8 and 10.2, evenly spread ones 9.3 and 9.1.
+        // (As they came: converted here, they were waited for before the metadata was asked for, a trip more.  Traced inside steps: 51 rows of 128,256 4.85 ->
+        // 4.56 us, 569 6.14 -> 5.93, ten of a level 4.92 -> 4.61.)
+        if (S <= 16) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) q[i] = quad_at<BF16, false>(lm, 4 * min(64 * i + lane, 8 * S - 1) + w);
+        }
+        if (lse_wave && S <= 16) pm = a.part_ms[g * S * 4 + min(lane, S * 4 - 1)];
         meta = row_meta<MODE>(a, g);
         if (!meta.valid) return;
     }
@@ -707,75 +762,6 @@ __device__ __forceinline__ void select_row(const RowArgs &a, int64_t g, int nl, 
     }
     rank_and_emit(n);
     if (tid >= n && tid < k) emit(tid, make_key(-INFINITY, 0u));
-}
-
-// (eight waves per SIMD: left alone the compiler takes 76 registers in one mode, 29.3 us for 64 sequences instead of 26.3)
-template <int MODE, bool BF16>
-__global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl, int S, float *top_val, int32_t *top_id, float *lse, int out_stride) {
-    select_row<MODE, BF16, false>(a, blockIdx.x, nl, S, top_val, top_id, lse, out_stride, [] { return true; }, [] {});
-}
-
-// ------------------------------------------------------------- both passes in one launch (top-k rows) --
-// Workgroups of the stream, and one to a row that waits for the row's chunks and selects (select_row).  Between two launches lie the first one's end, the
-// second's start, its arguments and its rows' metadata; here the maxima go through the L2 of the XCD that has the row, in three trips of 0.4 us (written, offered, read),
-// and what is read again comes from there as well, since the stream asks for it to stay.  51 rows of 128,256 bf16 entries, from memory: elements there after 2.1 us on average
-// (3.2 the last), their maxima 0.5 later, all of a row's at its selecting workgroup after 4.0, bound 1.6 later, hits 1.1, end 0.5.  (As many of
-// a row's entries to a workgroup as it can hold, each finding its own k best, and lists of those merged: 11.7 us a call against 9.6 in two launches: 16
-// waves take 1.7 us to their bound, and the merge 2.7.)
-template <int MODE, int NL, bool BF16>
-__global__ __launch_bounds__(256, 8) void row_pass_kernel(RowArgs a, int S, float *top_val, int32_t *top_id, float *lse, int out_stride) {
-    constexpr int E = 8 * NL;
-    // The workgroups of a row, a chunk each and one that selects, are eight apart: dealt to the XCDs in turn, they fall to one.
-    const int64_t g = 8 * blockIdx.y + (blockIdx.x & 7);
-    const int c = blockIdx.x >> 3;
-    if (g >= a.n_rows) return;
-    const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    __shared__ int s_go;
-    const Hands hands = {a.hands + g * 16, a.hands + a.n_rows * 16 + g * 17, a.tag, S};
-    bool taking = false;
-    if (c < S) {
-        const int base = c * (256 * E) + w * (64 * E) + lane * 8 - row_shift(a.logits, BF16, a.V, a.row_stride, g);
-        RawChunk<NL, BF16> raw;
-        chunk_request<NL, BF16, true, true>(a, g, base, raw);
-        if (!row_meta<MODE>(a, g).valid) return;
-        float x[E];
-        chunk_finish<NL, BF16, true, BF16>(a, g, base, (c + 1) * (256 * E), raw, x);
-        float mx = x[0];
-#pragma unroll
-        for (int j = 1; j < E; ++j) mx = fmaxf(mx, x[j]);
-        const float mx2 = fmaxf(mx, __int_as_float(dpp_mov<0xB1, 0xf>(0, __float_as_int(mx))));  // lane ^ 1
-        const LaneMax<BF16> pair = lane_max_pack<BF16>(mx2);
-        float2 p = make_float2(0.f, 0.f);
-        if (a.want_lse) p = wave_lse_partial<E>(x, mx, a.inv_t);
-        LaneMax<BF16> *lm = (LaneMax<BF16> *)a.lane_max + (g * S + c) * 128 + w * 32 + (lane >> 1);
-        u64 *ms = (u64 *)(a.part_ms + (g * S + c) * 4 + w);
-        if ((lane & 1) == 0) *lm = pair;
-        if (lane == 0) *ms = __builtin_bit_cast(u64, p);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (w == 0) {
-            const bool taken = hand_offer(hands, c, lane);
-            if (lane == 0) s_go = !taken;
-        }
-        __syncthreads();
-        if (!s_go) return;
-        if ((lane & 1) == 0) __hip_atomic_store(lm, pair, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (lane == 0) put_agent(ms, __builtin_bit_cast(u64, p));
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-    }
-    select_row<MODE, BF16, true>(a, g, NL, S, top_val, top_id, lse, out_stride,
-                                 [&] {
-                                     if (w == 0) {
-                                         const bool all = c < S ? hand_mark(hands, c, lane) : hand_await(hands, lane, taking);
-                                         if (lane == 0) s_go = all;
-                                     }
-                                     __syncthreads();
-                                     return s_go != 0;
-                                 },
-                                 [&] {
-                                     if (w == 0) hand_settle(hands, lane, taking);
-                                 });
 }
 
 // ---------------------------------------------------- rows that one workgroup holds (top-k rows) --
@@ -1414,8 +1400,8 @@ static hipError_t launch_select(const RowArgs &a, int64_t n_rows, int nl, float 
                                 int out_stride, hipStream_t st) {
     const int S = rows_chunks_per_row(a.V, nl);
     by_mode_and_type(a, [&](auto mode, auto bf16) {
-        launch_kernel(KID_ROWS_MERGE, st, row_select_kernel<decltype(mode)::value, decltype(bf16)::value>, dim3((unsigned)n_rows),
-                      dim3(256), 0, a, nl, S, top_val, top_id, lse, out_stride);
+        launch_kernel(KID_ROWS_MERGE, st, row_select_kernel<decltype(mode)::value, decltype(bf16)::value, 0>, dim3((unsigned)n_rows),
+                      dim3(256), 0, a, nl, S, top_val, top_id, lse, out_stride, 0ull);
     });
     return hipGetLastError();
 }
@@ -1436,18 +1422,17 @@ static hipError_t launch_pass(const RowArgs &a_in, int64_t n_rows, int nl, float
     const int S = rows_chunks_per_row(a.V, nl);
     a.early_load = 1;
     a.n_rows = n_rows;
-    a.hands = (unsigned long long *)((char *)a.lane_max + n_rows * S * 512);  // behind the maxima, whose room is twice that
-    a.tag = launch_tag();
     const int kid = a.mode == ROWS_DRAFT ? KID_ROWS_DRAFT : KID_ROWS_UNIFORM;
     by_mode_and_type(a, [&](auto mode, auto bf16) {
         constexpr int MODE = decltype(mode)::value;
         constexpr bool BF = decltype(bf16)::value;
         auto go = [&](auto kernel) {
-            launch_kernel(kid, st, kernel, dim3(8 * (S + 1), (unsigned)((n_rows + 7) / 8)), dim3(256), 0, a, S, top_val, top_id, lse, out_stride);
+            launch_kernel(kid, st, kernel, dim3(8 * (S + 1), (unsigned)((n_rows + 7) / 8)), dim3(256), 0, a, nl, S, top_val, top_id, lse, out_stride,
+                          launch_tag());
         };
-        if (nl == 4) go(row_pass_kernel<MODE, 4, BF>);
-        else if (nl == 2) go(row_pass_kernel<MODE, 2, BF>);
-        else go(row_pass_kernel<MODE, 1, BF>);
+        if (nl == 4) go(row_select_kernel<MODE, BF, 4>);
+        else if (nl == 2) go(row_select_kernel<MODE, BF, 2>);
+        else go(row_select_kernel<MODE, BF, 1>);
     });
     return hipGetLastError();
 }
