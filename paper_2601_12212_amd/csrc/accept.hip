@@ -180,9 +180,87 @@ __global__ __launch_bounds__(256) void node_sample_kernel(AcceptArgs a) {
     if (threadIdx.x == 0) a.samples[g] = tok;
 }
 
+// The best (value, id) key of row g and, with SUM, its (max, sum exp((x - max) inv_t)), by one wave that holds the row, 8 to ROW_V_MAX
+// entries.  What row_argmax_kernel leaves for a row of one chunk, and as there.
+#define ROW_V_MAX 2048
+#define ACCEPT_WAVES 16
+template <bool BF16, bool SUM>
+__device__ __forceinline__ u64 wave_row(const AcceptArgs &a, int64_t g, float inv_t, float2 &ms) {
+    constexpr int NG = ROW_V_MAX / 512;
+    const int V = a.V, lane = lane_id();
+    uint4 raw[NG][2];
+#pragma unroll
+    for (int n = 0; n < NG; ++n) {
+        const int start = min(512 * n + 8 * lane, V - 8);  // a group that reaches past the end: the row's last eight
+        if (BF16) raw[n][0] = load16((const uint16_t *)a.target + g * a.row_stride + start);
+        else {
+            const float *p = (const float *)a.target + g * a.row_stride + start;
+            raw[n][0] = load16(p);
+            raw[n][1] = load16(p + 4);
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    float x[NG][8], gmx[NG], mx = -INFINITY;
+#pragma unroll
+    for (int n = 0; n < NG; ++n) {
+        gmx[n] = -INFINITY;
+        if (n && 512 * n >= V) continue;  // uniform
+        const u32 lo[4] = {raw[n][0].x, raw[n][0].y, raw[n][0].z, raw[n][0].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (BF16) {
+                x[n][2 * e] = __uint_as_float(lo[e] << 16);
+                x[n][2 * e + 1] = __uint_as_float(lo[e] & 0xFFFF0000u);
+            } else {
+                const u32 hi[4] = {raw[n][1].x, raw[n][1].y, raw[n][1].z, raw[n][1].w};
+                x[n][e] = __uint_as_float(lo[e]);
+                x[n][4 + e] = __uint_as_float(hi[e]);
+            }
+        }
+        if (512 * (n + 1) > V) {  // uniform
+            const int first = 512 * n + 8 * lane - min(512 * n + 8 * lane, V - 8);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[n][e] = e >= first ? x[n][e] : -INFINITY;
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) gmx[n] = fmaxf(gmx[n], x[n][e]);
+        mx = fmaxf(mx, gmx[n]);
+    }
+    const float T = wave_max(mx);
+    if constexpr (SUM) {
+        const float cexp = 1.4426950408889634f * inv_t, nm = T == -INFINITY ? 0.f : -T * cexp;
+        float s = 0.f;
+#pragma unroll
+        for (int n = 0; n < NG; ++n) {
+            if (n && 512 * n >= V) continue;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) s += __builtin_amdgcn_exp2f(fmaf(x[n][e], cexp, nm));
+        }
+        ms = make_float2(T, wave_sum(s > 0.f ? s : 0.f));
+    }
+    // the first group that holds the maximum, the first lane of that, the first such element
+    u64 key = 0ull;
+#pragma unroll
+    for (int n = 0; n < NG; ++n) {
+        if (n && 512 * n >= V) continue;
+        const u64 m = __builtin_amdgcn_ballot_w64(gmx[n] == T);
+        if (m && key == 0ull) {  // uniform
+            const int first = (int)__builtin_ctzll(m);
+            int at = 0;
+#pragma unroll
+            for (int e = 7; e >= 0; --e) at = x[n][e] == T ? e : at;
+            key = make_key(T, (u32)(min(512 * n + 8 * first, V - 8) + __builtin_amdgcn_readlane(at, first)));
+        }
+    }
+    return key;
+}
+
+// ROWS: the rows are reduced here as well, a wave to a row, in the place of a launch in front of this one.
+//
 // The stochastic mode asks for a node's own logit and makes its uniforms while the row partials are on their way or being
 // merged, and keeps the partials for the bonus token: 10.2 -> 8.5 us for four sequences of 96 nodes.
-__global__ __launch_bounds__(256) void accept_kernel(AcceptArgs a) {
+template <bool ROWS>
+__global__ __launch_bounds__(ROWS ? 64 * ACCEPT_WAVES : 256) void accept_kernel(AcceptArgs a) {
     const int b = blockIdx.x, tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
     const int n_raw = a.n_nodes[b];
     const int64_t o = (int64_t)b * a.TT_cap;
@@ -210,9 +288,26 @@ __global__ __launch_bounds__(256) void accept_kernel(AcceptArgs a) {
     const int part = tid & 3;
     u64 key0[2][4];
     float2 p0[2][4];
+    __shared__ u64 s_key[ROWS ? ACCEPT_WAVES : 1];
+    __shared__ float2 s_sum[ROWS ? ACCEPT_WAVES : 1];
+    if constexpr (ROWS) {
+        auto row = [&](int i) {
+            float2 ms = make_float2(0.f, 0.f);
+            const u64 key = a.dtype == DT_BF16 ? stochastic ? wave_row<true, true>(a, o + i, inv_t, ms) : wave_row<true, false>(a, o + i, inv_t, ms)
+                                               : stochastic ? wave_row<false, true>(a, o + i, inv_t, ms) : wave_row<false, false>(a, o + i, inv_t, ms);
+            if (lane == 0) {
+                s_key[i] = key;
+                s_sum[i] = ms;
+            }
+        };
+        const int wave = __builtin_amdgcn_readfirstlane(w);
+        if (wave < a.TT_cap) row(wave);  // a wave to a row, without waiting for the node count: the row is inside the buffer either way
+        __syncthreads();
+        if (wave >= 4) return;  // (a barrier waits for the waves that are left)
+    }
 #pragma unroll
     for (int h = 0; h < 2; ++h)
-        if (64 * h < a.TT_cap) {  // uniform
+        if (!ROWS && 64 * h < a.TT_cap) {  // uniform
             const int64_t g = o + min(64 * h + (tid >> 2), a.TT_cap - 1);
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
@@ -256,11 +351,19 @@ __global__ __launch_bounds__(256) void accept_kernel(AcceptArgs a) {
                     }
                 }
             };
-            take(part, key0[h], p0[h]);
-            if (stochastic && S <= 16)
+            if constexpr (ROWS) {
+                best = s_key[min(i, N - 1)];
+                if (stochastic) {
+                    const float2 p = s_sum[min(i, N - 1)];
+                    M = p.x;
+                    Ssum = part == 0 ? p.y : 0.f;
+                    if (part == 0) s_ms[i][0] = p;
+                }
+            } else take(part, key0[h], p0[h]);
+            if (!ROWS && stochastic && S <= 16)
 #pragma unroll
                 for (int u = 0; u < 4; ++u) s_ms[i][part + 4 * u] = p0[h][u];
-            for (int c0 = part + 16; c0 < S; c0 += 16) {  // four chunks per trip to memory
+            for (int c0 = part + 16; !ROWS && c0 < S; c0 += 16) {  // four chunks per trip to memory
                 u64 key[4];
                 float2 p[4];
 #pragma unroll
@@ -360,6 +463,13 @@ __global__ __launch_bounds__(256) void accept_kernel(AcceptArgs a) {
     if (tid == 0 && len <= DT_D_MAX) a.out_tokens[(int64_t)b * (DT_D_MAX + 1) + len] = bonus;
 }
 
+// Rows that a wave holds, a wave of the workgroup to each: one launch in place of two.  us a step, graph | eager, two launches -> one: 8 rows of 1,024 fp32
+// entries 22.5 -> 21.9 | 19.0 -> 16.9; graphs, greedy and stochastic, 16 rows of 1,000 bf16 entries 23.7 -> 22.5, 26.8 -> 26.4, of 2,000 fp32 22.3 -> 21.5,
+// 26.3 -> 25.4; but two rows to a wave, 32 of 1,001 24.4 -> 25.1, 27.5 -> 29.1.  (Longer rows, 2,048 entries at a time, and four waves: 16 rows of 2,000 23.5 -> 25.2.)
+bool accept_takes_rows(const AcceptArgs &a) {
+    return a.mode != DT_ACCEPT_SAMPLED && a.V >= 8 && a.V <= ROW_V_MAX && a.TT_cap <= ACCEPT_WAVES;
+}
+
 hipError_t accept_launch(const AcceptArgs &a, hipStream_t st) {
     if (a.batch <= 0) return hipSuccess;
     if (a.mode == DT_ACCEPT_SAMPLED) {
@@ -367,7 +477,7 @@ hipError_t accept_launch(const AcceptArgs &a, hipStream_t st) {
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    launch_kernel(KID_ACCEPT, st, accept_kernel, dim3(a.batch), dim3(256), 0, a);
+    launch_kernel(KID_ACCEPT, st, a.rows_here ? accept_kernel<true> : accept_kernel<false>, dim3(a.batch), dim3(a.rows_here ? 64 * ACCEPT_WAVES : 256), 0, a);
     return hipGetLastError();
 }
 

@@ -343,9 +343,6 @@ int dt_accept(void *stream, int batch, dt_accept_mode mode, float temperature, c
     a.part_keys = rs.keys; a.part_ms = rs.ms;
     hipStream_t st = (hipStream_t)stream;
     (void)hipGetLastError();  // a stale error left by another HIP user of this process is not ours
-    hipError_t e = dt::rows_launch_argmax(a, rows, nl, st);
-    if (e != hipSuccess) return hip_fail(e);
-
     dt::AcceptArgs aa = {};
     aa.batch = batch; aa.mode = mode; aa.temperature = temperature; aa.target = target_logits; aa.dtype = t;
     aa.V = V; aa.row_stride = row_stride; aa.n_nodes = n_nodes; aa.tokens = tokens; aa.parents = parents;
@@ -353,6 +350,15 @@ int dt_accept(void *stream, int batch, dt_accept_mode mode, float temperature, c
     aa.seed = philox_seed; aa.step = philox_step; aa.accept_len = accept_len; aa.best_node = best_node;
     aa.path_nodes = path_nodes; aa.out_tokens = out_tokens; aa.node_argmax = node_argmax;
     aa.part_keys = rs.keys; aa.part_ms = rs.ms; aa.S = S; aa.chunk_elems = 256 * 8 * nl; aa.samples = samples;
+    hipError_t e = hipSuccess;
+    aa.rows_here = dt::accept_takes_rows(aa);
+    if (aa.rows_here) {
+        aa.S = 1;
+        aa.chunk_elems = 8192;
+    } else {
+        e = dt::rows_launch_argmax(a, rows, nl, st);
+        if (e != hipSuccess) return hip_fail(e);
+    }
     e = dt::accept_launch(aa, st);
     if (e != hipSuccess) return hip_fail(e);
     return DT_OK;

@@ -137,7 +137,9 @@ struct AcceptArgs {
     int S;            // chunks per row
     int chunk_elems;  // vocabulary entries per chunk
     int32_t *samples; // [batch*TT_cap] target-sampled mode: the token every node drew
+    bool rows_here;   // the rows are reduced by accept_kernel itself (accept_takes_rows); S is 1, chunk_elems 8,192
 };
+bool accept_takes_rows(const AcceptArgs &a);
 hipError_t accept_launch(const AcceptArgs &a, hipStream_t st);
 
 // --------------------------------------------------------------- input update (commit.hip)

@@ -7,8 +7,8 @@ import pytest
 import dt_synth
 from oracle import ref
 from paper_2601_12212_amd import dt_topk_rows, dt_workspace_bytes
-from tests._cases import TREE_MARGIN, assert_tree_equal
-from tests.test_gpu_parity import check_topk, dev_logits
+from tests._cases import TREE_MARGIN, assert_tree_equal, oracle_case
+from tests.test_gpu_parity import check_case, check_topk, dev_logits
 
 pytestmark = pytest.mark.gpu
 
@@ -260,6 +260,35 @@ def test_target_rows_at_odd_addresses(V, mode):
         for b in range(B):
             # the first of equal entries
             assert torch.equal(got[1][4][b, :n[b]].long().cpu(), torch.from_numpy(np.argmax(x[b, :n[b]].float().cpu().numpy(), axis=1)))
+
+
+# Target rows that the acceptance reduces itself: up to 16 nodes and 2,048 entries, a wave to a row of up to four groups of 512; one more of either.  Against the oracle,
+# and rows whose best is first, last, everywhere and nowhere against numpy.
+@pytest.mark.parametrize("V", [8, 9, 511, 513, 1024, 2047, 2048, 2049])
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("mode", [dt_synth.GREEDY, dt_synth.STOCHASTIC])
+def test_target_rows_that_the_acceptance_reduces(V, bf16, mode):
+    from paper_2601_12212_amd.step import Step
+    for TT in (1, 15, 16, 17):
+        cfg = dt_synth.StepConfig("rows", "bf16" if bf16 else "f32", 2, 1, 64, V, [(TT, 3, 4), (min(TT, 5), 2, 3)], [3, 9], mode=mode, seed=3)
+        check_case(oracle_case(0, cfg=cfg))
+    TT = 16
+    st = Step([(TT, 4, min(5, V - 1))], [1], 1, 1, 64, V, dtype=torch.bfloat16 if bf16 else torch.float32, mode=mode, temperature=0.7)
+    gen = torch.Generator("cuda").manual_seed(V)
+    st.draft_logits.copy_(torch.randn(st.draft_logits.shape, generator=gen, device="cuda") * 2)
+    st.build_tree()
+    x = torch.randn((1, TT, V), generator=gen, device="cuda") * 2
+    x[:, 1, 0] = x[:, 2, V - 1] = 30.0
+    x[:, 3] = 1.0
+    x[:, 4, V // 2:] = 3.0e4
+    if mode == dt_synth.GREEDY:
+        x[:, 5] = -float("inf")
+    for gap in (0, 1):
+        st.target_logits = torch.nn.functional.pad(x.to(st.draft_logits.dtype), (0, gap), value=1e9)[:, :, :V]
+        st.accept()
+        n = int(st.n_nodes[0])
+        want = np.argmax(st.target_logits[0, :n].float().cpu().numpy(), axis=1)   # the first of equal entries
+        assert torch.equal(st.node_argmax[0, :n].long().cpu(), torch.from_numpy(want))
 
 
 def test_a_launch_of_more_threads_than_one_grid_dimension_takes():
