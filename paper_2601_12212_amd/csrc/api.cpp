@@ -399,9 +399,6 @@ int dt_expand_level(void *stream, int batch, int level, const dt_params *params,
     a.lane_max = rs.lane_max; a.part_ms = rs.ms;
     hipStream_t st = (hipStream_t)stream;
     (void)hipGetLastError();  // a stale error left by another HIP user of this process is not ours
-    hipError_t e = dt::rows_launch_topk(a, total_rows, ls.top_val, ls.top_id, ls.lse, DT_K_MAX, st);
-    if (e != hipSuccess) return hip_fail(e);
-
     dt::TreeArgs ta = {};
     ta.batch = batch; ta.params = params; ta.V = V; ta.seq_rows = DT_STATE_ROWS;
     ta.TT_cap = TT_cap; ta.top_val = ls.top_val; ta.top_id = ls.top_id; ta.lse = ls.lse;
@@ -410,7 +407,10 @@ int dt_expand_level(void *stream, int batch, int level, const dt_params *params,
     ta.exp_mask = (unsigned long long *)exp_mask;
     ta.state_val = ls.top_val; ta.state_id = ls.top_id;
     ta.early_stop = flags & DT_TREE_EARLY_STOP;
-    e = dt::tree_launch(ta, st);
+    bool to_expand = true;
+    hipError_t e = dt::rows_launch_topk(a, total_rows, ls.top_val, ls.top_id, ls.lse, DT_K_MAX, st, &ta, &to_expand);
+    if (e != hipSuccess) return hip_fail(e);
+    if (to_expand) e = dt::tree_launch(ta, st);
     if (e != hipSuccess) return hip_fail(e);
     return DT_OK;
 }

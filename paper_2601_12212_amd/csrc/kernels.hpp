@@ -36,6 +36,7 @@ inline unsigned long long launch_tag() {
 enum RowMode { ROWS_UNIFORM = 0, ROWS_DRAFT = 1, ROWS_TARGET = 2, ROWS_LEVEL = 3 };
 #define DT_STATE_ROWS (1 + (DT_D_MAX - 1) * DT_K_MAX)  // draft rows a sequence can own
 
+struct TreeArgs;
 struct RowArgs {
     const void *logits;
     int dtype;           // dt_dtype
@@ -55,7 +56,7 @@ struct RowArgs {
     float2 *part_ms;      // (max, sum exp((x-max)*inv_t)): [rows, S] (arg max rows), [rows, S*4] (top-k rows)
     // ROWS_LEVEL: rows of one level of every sequence, results scattered into the build state
     int level, rows_per_seq, state_rows;
-    const int32_t *n_exp_prev;  // [batch] of the last call: its level and the nodes that it expanded, level << 8 | nodes
+    const int32_t *n_exp_prev;  // [batch] how many nodes the levels have expanded (level_note)
     bool lse_apart;  // set by the launch functions: workgroups n_rows .. 2 n_rows - 1 are there for the rows' log-sum-exps
     int64_t n_rows;  // set by the launch functions: rows of the launch (the grid may overhang)
     // set by the launch functions: read a row's chunk before the row is known to be live (the loads then
@@ -66,8 +67,9 @@ struct RowArgs {
 int rows_chunks_per_row(int V, int nl);
 int rows_topk_nl(int V);                    // chunk multiplier of the top-k passes
 int rows_pick_nl(int64_t n_rows, int V);    // chunk multiplier of the arg max pass
+// tree: with it the launch of a level's rows may choose the level's nodes as well, and clears *to_expand then.
 hipError_t rows_launch_topk(const RowArgs &a, int64_t n_rows, float *top_val, int32_t *top_id, float *lse, int out_stride,
-                            hipStream_t st);
+                            hipStream_t st, const TreeArgs *tree = nullptr, bool *to_expand = nullptr);
 hipError_t rows_launch_argmax(const RowArgs &a, int64_t n_rows, int nl, hipStream_t st);
 
 // ------------------------------------------------------------------ tree kernel (tree.hip)

@@ -10,10 +10,11 @@
 // largest element from below, so only the ~k pairs that reach it are read again and their
 // elements ranked by 64-bit (value, id) keys -- exact under (value desc, id asc).  Where
 // that bound leaves too many, a pass over them keeps the k best so far.
+#include <stddef.h>
+
 #include <type_traits>
 
-#include "common.hpp"
-#include "kernels.hpp"
+#include "level.hpp"
 
 namespace dt {
 
@@ -22,6 +23,8 @@ struct RowMeta {
     bool valid;
     int k;
     int64_t out;  // row index of the results (top-k values, ids, lse)
+    int seq, slot, rows;  // ROWS_LEVEL: the sequence, which of its rows, how many are reduced
+    bool expands;         // and whether its level is to be chosen
 };
 
 template <int MODE>
@@ -37,12 +40,17 @@ __device__ __forceinline__ RowMeta row_meta(const RowArgs &a, int64_t g) {
         const dt_params p = a.params[b];
         const int TT = min(max(p.TT, 1), a.TT_cap), d = min(max(p.d, 1), DT_D_MAX);
         const int k = min(max(p.k, 1), min(DT_K_MAX, a.V));
-        // Where the last call was not the level's before this one (it is asked for again), every row: results of rows that belong to no node are not used.
-        const int last = a.n_exp_prev[b];
-        const int cnt = a.level == 1 ? 1 : last >> 8 == a.level - 1 ? min(last & 255, k) : k;
+        // Where what the level before expanded is not known (this one is asked for again after later ones), every row: results of rows that belong to no
+        // node are not used.
+        const int last = level_count((u32)a.n_exp_prev[b], a.level - 1);
+        const int cnt = a.level == 1 ? 1 : last >= 0 ? min(last, k) : k;
         m.k = k;
         m.valid = TT > 1 && a.level <= d && s < cnt;
         m.out = (int64_t)b * a.state_rows + (a.level == 1 ? 0 : 1 + (a.level - 2) * k + s);
+        m.seq = b;
+        m.slot = s;
+        m.rows = min(cnt, a.rows_per_seq);
+        m.expands = a.level < d;
     } else if constexpr (MODE == ROWS_DRAFT) {
         // sequence b with row_off[b] <= g < row_off[b+1].  A few sequences: bisection, every step one scalar read.  More:
         // lane j looks at sequence j (of each group of 64), offsets and limits together, one trip to memory instead of
@@ -400,6 +408,58 @@ __device__ __forceinline__ LaneMax<BF16> lane_max_at(const LaneMax<BF16> *lm, in
     if constexpr (SAME) return __hip_atomic_load(lm + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     else return lm[i];
 }
+// ---- rows of a level whose nodes are chosen in the same launch ----
+struct NoTail {};
+template <int MODE>
+using Tail = std::conditional_t<MODE == ROWS_LEVEL, LevelTail, NoTail>;
+// A row's results, which another workgroup of the launch may read.
+template <int MODE, typename T>
+__device__ __forceinline__ void put_result(T *p, T v) {
+    if constexpr (MODE == ROWS_LEVEL) put32_agent(p, v);
+    else *p = v;
+}
+// The tail's arguments, at `offset` of the kernel's.  Read from there and not as the argument that it is: its twenty pointers would be asked for
+// at the kernel's start and held, 60 scalar registers spilled to vector ones in every workgroup of a row.
+__device__ __forceinline__ const LevelTail &tail_at(size_t offset) {
+    typedef __attribute__((address_space(4))) const char Arg;
+    Arg *p = (Arg *)__builtin_amdgcn_kernarg_segment_ptr() + offset;
+    asm volatile("" : "+s"(p));
+    return *(const LevelTail *)p;
+}
+struct SelectArgs { RowArgs a; int nl, S; float *top_val; int32_t *top_id; float *lse; int out_stride; u64 tag; LevelTail tail; };  // as the kernels have them
+struct HeldArgs { RowArgs a; float *top_val; int32_t *top_id; float *lse; int out_stride; LevelTail tail; };
+__device__ __forceinline__ LevelLds &level_lds() {
+    __shared__ LevelLds s_level;
+    return s_level;
+}
+// The end of a row's workgroup.
+template <int MODE, size_t OFFSET>
+__device__ __forceinline__ void level_row_end(const RowMeta &meta, bool lse_wg) {
+    if constexpr (MODE == ROWS_LEVEL) {
+        const LevelTail &tail = tail_at(OFFSET);
+        if (!tail.words || !meta.expands) return;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (threadIdx.x >= 64) return;
+        const int lane = lane_id(), b = __builtin_amdgcn_readfirstlane(meta.seq);
+        if (!level_row_done(tail, b, meta.slot + (lse_wg ? NARROW_K : 0), meta.rows, lane)) return;
+        level_expand(tail, level_lds(), b, level_in(tail.t, tail.rows, b, lane), lane);
+    }
+}
+// True for the workgroups that wait for a sequence's rows, which have then done so; wg: the workgroup's number.
+template <int MODE, size_t OFFSET>
+__device__ __forceinline__ bool level_waits(const Tail<MODE> &arg, u32 wg) {
+    if constexpr (MODE == ROWS_LEVEL) {
+        if (wg >= (u32)arg.first_wg) {
+            const LevelTail &tail = tail_at(OFFSET);
+            const int b = (int)(wg - (u32)tail.first_wg);
+            if (threadIdx.x < 64 && b < tail.t.batch) level_wait_and_expand(tail, level_lds(), b, lane_id());
+            return true;
+        }
+    }
+    return false;
+}
+
 // PASS: the maxima are made in the same launch, in chunks of 2,048 PASS entries, up to 16 of them.  0: by the launch before.
 // Both passes in one launch: workgroups of the stream, and one to a row that waits for the row's chunks and selects.  Between two launches lie the first one's end, the
 // second's start, its arguments and its rows' metadata; here the maxima go through the L2 of the XCD that has the row, in three trips of 0.4 us (written, offered, read),
@@ -409,8 +469,10 @@ __device__ __forceinline__ LaneMax<BF16> lane_max_at(const LaneMax<BF16> *lm, in
 // waves take 1.7 us to their bound, and the merge 2.7.)
 // (eight waves per SIMD: left alone the compiler takes 76 registers in one mode, 29.3 us for 64 sequences instead of 26.3)
 template <int MODE, bool BF16, int PASS>
-__global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl_, int S, float *top_val, int32_t *top_id, float *lse, int out_stride, u64 tag) {
+__global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl_, int S, float *top_val, int32_t *top_id, float *lse, int out_stride, u64 tag, Tail<MODE> tail) {
     constexpr bool SAME = PASS > 0;
+    if constexpr (SAME)
+        if (level_waits<MODE, offsetof(SelectArgs, tail)>(tail, blockIdx.y * gridDim.x + blockIdx.x)) return;
     const int nl = SAME ? PASS : nl_;
     // (PASS: the workgroups of a row are eight apart: dealt to the XCDs in turn, they fall to one)
     const int64_t g = SAME ? 8 * blockIdx.y + (blockIdx.x & 7) : blockIdx.x;
@@ -509,8 +571,8 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl_, 
         float v = key_val(key);
         u32 id = key_idx(key);
         bool viable = (v > -INFINITY) && (id < (u32)V);
-        tv[r] = viable ? v : -INFINITY;
-        if (ti) ti[r] = viable ? (int32_t)id : -1;
+        put_result<MODE>(tv + r, viable ? v : -INFINITY);
+        if (ti) put_result<MODE>(ti + r, viable ? (int32_t)id : -1);
     };
     // ---- the row's log-sum-exp, by wave 3 ----------------------------------------------------------------
     auto row_lse = [&]() {
@@ -531,7 +593,7 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl_, 
         const float Mw = wave_max(M);
         float term = (Ssum > 0.f) ? Ssum * __builtin_amdgcn_exp2f((M - Mw) * cexp) : 0.f;
         term = wave_sum(term);
-        if (lane == 0) lse[meta.out] = (Mw == -INFINITY) ? -INFINITY : Mw * a.inv_t + __logf(term);
+        if (lane == 0) put_result<MODE>(lse + meta.out, (Mw == -INFINITY) ? -INFINITY : Mw * a.inv_t + __logf(term));
     };
     // Eight elements of lane maximum i (chunk, wave, pair of lanes), those of load n / 2 and lane n % 2 of the pair: the ones that
     // reach T become candidates, room for them with one LDS add.
@@ -565,203 +627,206 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl_, 
         }
     };
 
-    // ---- 1. thread maxima and T -------------------------------------------------------------------
-    float it[8], tmax = -INFINITY;
-    if (SAME || S <= 16) {
+    do {
+        // ---- 1. thread maxima and T -------------------------------------------------------------------
+        float it[8], tmax = -INFINITY;
+        if (SAME || S <= 16) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) it[j] = 64 * (j >> 2) + lane < 8 * S ? lane_max_value<BF16>(q[j >> 2].v[j & 3]) : -INFINITY;
-        tmax = spread_max(it);
-    } else {
-        for (int i = tid; i < n_lm; i += 256) tmax = fmaxf(tmax, lane_max_value<BF16>(lm[i]));
-    }
-    s_key[tid] = (uint16_t)(ord32(tmax) >> 16);
-    if (tid < SEL_CAP) s_fin[tid] = 0ull;
-    if (tid == 0) { s_n2 = 0; s_h = 0; }
-    __syncthreads();
-    const uint2 k4 = ((const uint2 *)s_key)[lane];
-    const u32 ky[4] = {k4.x & 0xFFFFu, k4.x >> 16, k4.y & 0xFFFFu, k4.y >> 16};
-    const u32 key0 = wave_kth_of_256(ky, k);
-    const float T0 = key_edge(key0);
-
-    // ---- 2. the lanes that reach T, read again ------------------------------------------------------
-    if (SAME || S <= 16) {
-        // Every wave by itself: its hot lanes into a list of its own (a prefix sum over the lanes instead of an LDS
-        // counter, no barrier), then (hot lane, load n) pairs over its lanes.
-        u32 hot = 0;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) hot |= (it[j] >= T0 ? 1u : 0u) << j;
-        const int mine = __popc(hot), incl = wave_scan_incl_i32(mine);
-        const int h = __builtin_amdgcn_readlane(incl, 63);
-        if (h > SEL_WAVE_CAP) {  // ties: this bound does not cut
-            if (lane == 0) s_n2 = SEL_CAP + 1;
+            for (int j = 0; j < 8; ++j) it[j] = 64 * (j >> 2) + lane < 8 * S ? lane_max_value<BF16>(q[j >> 2].v[j & 3]) : -INFINITY;
+            tmax = spread_max(it);
         } else {
-            int *list = s_hot + w * SEL_WAVE_CAP;
-            for (int at = incl - mine; hot; hot &= hot - 1) {
-                const int j = __builtin_ctz(hot);
-                list[at++] = 4 * (4 * (64 * (j >> 2) + lane) + w) + (j & 3);
-            }
-            __builtin_amdgcn_wave_barrier();
-            // A group to a lane, or the two neighbours of a load where there are more: k = 28 is some sixty groups to a wave.  (Each launch
-            // between two events, one group to a lane after the other and lane maxima dealt so that of twelve chunks' two waves held two
-            // thirds: 336 rows of 12 chunks, k = 27, 11.4 us; dealt evenly and two groups asked for at a time 10.0.  Top-k calls of 28 rows of
-            // 115,042, k = 28, replayed: so 9.8 us, with neighbours in a lane 9.65, with the loop over hits 9.05.)
-            const int total = h << per_log2;
-            if (total <= 64) {
-                if (lane < total) reread(list[lane >> per_log2], lane & ((1 << per_log2) - 1), T0);
+            for (int i = tid; i < n_lm; i += 256) tmax = fmaxf(tmax, lane_max_value<BF16>(lm[i]));
+        }
+        s_key[tid] = (uint16_t)(ord32(tmax) >> 16);
+        if (tid < SEL_CAP) s_fin[tid] = 0ull;
+        if (tid == 0) { s_n2 = 0; s_h = 0; }
+        __syncthreads();
+        const uint2 k4 = ((const uint2 *)s_key)[lane];
+        const u32 ky[4] = {k4.x & 0xFFFFu, k4.x >> 16, k4.y & 0xFFFFu, k4.y >> 16};
+        const u32 key0 = wave_kth_of_256(ky, k);
+        const float T0 = key_edge(key0);
+
+        // ---- 2. the lanes that reach T, read again ------------------------------------------------------
+        if (SAME || S <= 16) {
+            // Every wave by itself: its hot lanes into a list of its own (a prefix sum over the lanes instead of an LDS
+            // counter, no barrier), then (hot lane, load n) pairs over its lanes.
+            u32 hot = 0;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) hot |= (it[j] >= T0 ? 1u : 0u) << j;
+            const int mine = __popc(hot), incl = wave_scan_incl_i32(mine);
+            const int h = __builtin_amdgcn_readlane(incl, 63);
+            if (h > SEL_WAVE_CAP) {  // ties: this bound does not cut
+                if (lane == 0) s_n2 = SEL_CAP + 1;
             } else {
-                const int pairs_log2 = per_log2 - 1, mask = (1 << pairs_log2) - 1;
-                for (int q = lane; q < total >> 1; q += 64) {
-                    float x[2][8];
-                    const int i = list[q >> pairs_log2], n = 2 * (q & mask);
-                    const int s0 = load_octet<BF16, SAME>(a, g, octet_of(i, n), x[0]);
-                    const int s1 = load_octet<BF16, SAME>(a, g, octet_of(i, n + 1), x[1]);
-                    keep_hits<16>([&](int e) { return x[e >> 3][e & 7]; }, [&](int e) { return (e < 8 ? s0 : s1 - 8) + e; }, T0, &s_n2, s_fin);
+                int *list = s_hot + w * SEL_WAVE_CAP;
+                for (int at = incl - mine; hot; hot &= hot - 1) {
+                    const int j = __builtin_ctz(hot);
+                    list[at++] = 4 * (4 * (64 * (j >> 2) + lane) + w) + (j & 3);
+                }
+                __builtin_amdgcn_wave_barrier();
+                // A group to a lane, or the two neighbours of a load where there are more: k = 28 is some sixty groups to a wave.  (Each launch
+                // between two events, one group to a lane after the other and lane maxima dealt so that of twelve chunks' two waves held two
+                // thirds: 336 rows of 12 chunks, k = 27, 11.4 us; dealt evenly and two groups asked for at a time 10.0.  Top-k calls of 28 rows of
+                // 115,042, k = 28, replayed: so 9.8 us, with neighbours in a lane 9.65, with the loop over hits 9.05.)
+                const int total = h << per_log2;
+                if (total <= 64) {
+                    if (lane < total) reread(list[lane >> per_log2], lane & ((1 << per_log2) - 1), T0);
+                } else {
+                    const int pairs_log2 = per_log2 - 1, mask = (1 << pairs_log2) - 1;
+                    for (int q = lane; q < total >> 1; q += 64) {
+                        float x[2][8];
+                        const int i = list[q >> pairs_log2], n = 2 * (q & mask);
+                        const int s0 = load_octet<BF16, SAME>(a, g, octet_of(i, n), x[0]);
+                        const int s1 = load_octet<BF16, SAME>(a, g, octet_of(i, n + 1), x[1]);
+                        keep_hits<16>([&](int e) { return x[e >> 3][e & 7]; }, [&](int e) { return (e < 8 ? s0 : s1 - 8) + e; }, T0, &s_n2, s_fin);
+                    }
+                }
+            }
+            __syncthreads();
+            const int n2 = s_n2;
+            row_lse();
+            if (n2 <= SEL_CAP) {
+                rank_and_emit(n2);
+                break;
+            }
+            __syncthreads();  // s_n2 has been read
+            if (tid < SEL_CAP) s_fin[tid] = 0ull;
+            if (tid == 0) s_n2 = 0;
+        } else {
+            row_lse();
+        }
+
+        // ---- second bound: histogram of the lane maxima >= T0; its scan from the top gives T1 ------------
+        auto lane_val = [&](int i) { return lane_max_value<BF16>(lane_max_at<BF16, SAME>(lm, i)); };
+        s_hist[tid] = 0u;
+        __syncthreads();
+        for (int i = tid; i < n_lm; i += 256) {
+            const float v = lane_val(i);
+            if (v >= T0) atomicAdd(&s_hist[min((ord32(v) >> 16) - key0, 255u)], 1u);
+        }
+        __syncthreads();
+        // every wave by itself: lane L holds bins 4(63-L) .. 4(63-L)+3, so an ascending lane scan walks the
+        // bins downwards; at least k lane maxima reach T0, so the scan finds its bin
+        int n_hot;      // lane maxima >= T1
+        float T1;
+        {
+            const uint4 hb = *(const uint4 *)&s_hist[4 * (63 - lane)];
+            const int c4 = (int)(hb.x + hb.y + hb.z + hb.w);
+            const int incl = wave_scan_incl_i32(c4);
+            const u64 m = __ballot(incl >= k);
+            const int ls = m ? (int)__builtin_ctzll(m) : 63;
+            int acc = __builtin_amdgcn_readlane(incl - c4, ls);
+            const int h3 = __builtin_amdgcn_readlane((int)hb.w, ls), h2 = __builtin_amdgcn_readlane((int)hb.z, ls),
+                      h1 = __builtin_amdgcn_readlane((int)hb.y, ls), h0 = __builtin_amdgcn_readlane((int)hb.x, ls);
+            int dg;
+            if (acc + h3 >= k) { dg = 3; acc += h3; }
+            else if (acc + h3 + h2 >= k) { dg = 2; acc += h3 + h2; }
+            else if (acc + h3 + h2 + h1 >= k) { dg = 1; acc += h3 + h2 + h1; }
+            else { dg = 0; acc += h3 + h2 + h1 + h0; }
+            n_hot = acc;
+            // the lower edge of that bin: the smallest float whose upper 16 key bits are the bin's (bin 255 also
+            // holds everything farther up: its lower edge still bounds all of it)
+            T1 = key_edge(key0 + (u32)(4 * (63 - ls) + dg));
+        }
+        if (n_hot <= SEL_CAP) {  // uniform over the workgroup
+            for (int i = tid; i < n_lm; i += 256)
+                if (lane_val(i) >= T1) {
+                    const int at = atomicAdd(&s_h, 1);
+                    if (at < SEL_CAP) s_hot[at] = i;
+                }
+            __syncthreads();
+            for (int q = tid; q < n_hot << per_log2; q += 256) reread(s_hot[q >> per_log2], q & ((1 << per_log2) - 1), T1);
+            __syncthreads();
+            const int n2 = s_n2;
+            if (n2 <= SEL_CAP) {
+                rank_and_emit(n2);
+                break;
+            }
+        }
+
+        // ---- too many still: one pass over the elements of the lane maxima that reach T1 -----------------------------------------
+        // Two groups of eight to a thread at a time.  What reaches the threshold goes on the list; when the list is long, the k best of it
+        // stay and the k-th becomes the threshold, so that equal values later in the row no longer reach it.  -inf does not count.
+        // (51 rows of 128,256 bf16 entries, k = 28: 256 to 400 neighbours raised by 20, in fewer pairs than k, 28 to 30 us, all equal 78, all -inf 59, where
+        // taking the best k times from the whole row took 2,330; k = 10 23, 78 and 59 against 840; k = 1 9, 73 and 59 against 9, 101 and 95.)
+        auto keep_best = [&](int n) {
+            u64 key[2];
+            int rank[2] = {0, 0};
+#pragma unroll
+            for (int h = 0; h < 2; ++h) key[h] = tid + 256 * h < SEL_LIST ? s_fin[tid + 256 * h] : 0ull;
+            for (int j0 = 0; j0 < n; j0 += 4) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const u64 o = s_fin[j0 + j];
+                    rank[0] += o > key[0] ? 1 : 0;
+                    rank[1] += o > key[1] ? 1 : 0;
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                if (tid + 256 * h < SEL_LIST) s_fin[tid + 256 * h] = 0ull;
+            __syncthreads();
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                if (tid + 256 * h < n && rank[h] < k) s_fin[rank[h]] = key[h];
+            if (tid == 0) s_n2 = k;
+            __syncthreads();
+            return s_fin[k - 1] + 1ull;
+        };
+        __syncthreads();  // s_n2 has been read
+        for (int i = tid; i < SEL_LIST; i += 256) s_fin[i] = 0ull;
+        if (tid == 0) s_n2 = 0;
+        if (tid < 3) s_cnt[tid] = 0;
+        __syncthreads();
+        u64 threshold = (u64)max(ord32(T1), 0x00800000u) << 32;
+        const bool listed = n_hot <= SEL_CAP;
+        const int pairs_log2 = per_log2 - 1, total = (listed ? n_hot : n_lm) << pairs_log2;
+        int n = 0, step = 0;
+        for (int q0 = 0; q0 < total; q0 += 256) {
+            const int q = q0 + tid, at = min(q, total - 1) >> pairs_log2, i = listed ? s_hot[at] : at;
+            float x[2][8];
+            int s0 = 0, s1 = 0;
+            u32 todo = 0;
+            if (q < total && (listed || lane_val(i) >= T1)) {
+                const int m = 2 * (q & ((1 << pairs_log2) - 1));
+                s0 = load_octet<BF16, SAME>(a, g, octet_of(i, m), x[0]);
+                s1 = load_octet<BF16, SAME>(a, g, octet_of(i, m + 1), x[1]);
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    todo |= (make_key(x[e >> 3][e & 7], (u32)((e < 8 ? s0 : s1 - 8) + e)) >= threshold ? 1u : 0u) << e;
+            }
+            for (bool all = false; !all;) {
+                // how many of the workgroup's elements wait; three counters in turn, so that one barrier does
+                const int sum = wave_sum_i32(__popc(todo));
+                if (lane == 0 && sum) atomicAdd(&s_cnt[step % 3], sum);
+                __syncthreads();
+                const int waiting = s_cnt[step % 3];
+                if (tid == 0) s_cnt[(step + 2) % 3] = 0;
+                ++step;
+                if (waiting == 0) break;
+                all = n + waiting <= SEL_LIST;  // else one of each thread's: at most 256 behind at most SEL_CAP
+                for (u32 now = all ? todo : todo & (0u - todo); now; now &= now - 1) {
+                    const int e = __builtin_ctz(now);
+                    float v = x[0][0];
+#pragma unroll
+                    for (int j = 1; j < 16; ++j) v = e == j ? x[j >> 3][j & 7] : v;
+                    const u64 key = make_key(v, (u32)((e < 8 ? s0 : s1 - 8) + e));
+                    if (key >= threshold) s_fin[atomicAdd(&s_n2, 1)] = key;
+                }
+                todo &= todo - 1;
+                __syncthreads();
+                n = s_n2;
+                if (n > SEL_CAP) {
+                    threshold = keep_best(n);
+                    n = k;
                 }
             }
         }
-        __syncthreads();
-        const int n2 = s_n2;
-        row_lse();
-        if (n2 <= SEL_CAP) {
-            rank_and_emit(n2);
-            return;
-        }
-        __syncthreads();  // s_n2 has been read
-        if (tid < SEL_CAP) s_fin[tid] = 0ull;
-        if (tid == 0) s_n2 = 0;
-    } else {
-        row_lse();
-    }
-
-    // ---- second bound: histogram of the lane maxima >= T0; its scan from the top gives T1 ------------
-    auto lane_val = [&](int i) { return lane_max_value<BF16>(lane_max_at<BF16, SAME>(lm, i)); };
-    s_hist[tid] = 0u;
-    __syncthreads();
-    for (int i = tid; i < n_lm; i += 256) {
-        const float v = lane_val(i);
-        if (v >= T0) atomicAdd(&s_hist[min((ord32(v) >> 16) - key0, 255u)], 1u);
-    }
-    __syncthreads();
-    // every wave by itself: lane L holds bins 4(63-L) .. 4(63-L)+3, so an ascending lane scan walks the
-    // bins downwards; at least k lane maxima reach T0, so the scan finds its bin
-    int n_hot;      // lane maxima >= T1
-    float T1;
-    {
-        const uint4 hb = *(const uint4 *)&s_hist[4 * (63 - lane)];
-        const int c4 = (int)(hb.x + hb.y + hb.z + hb.w);
-        const int incl = wave_scan_incl_i32(c4);
-        const u64 m = __ballot(incl >= k);
-        const int ls = m ? (int)__builtin_ctzll(m) : 63;
-        int acc = __builtin_amdgcn_readlane(incl - c4, ls);
-        const int h3 = __builtin_amdgcn_readlane((int)hb.w, ls), h2 = __builtin_amdgcn_readlane((int)hb.z, ls),
-                  h1 = __builtin_amdgcn_readlane((int)hb.y, ls), h0 = __builtin_amdgcn_readlane((int)hb.x, ls);
-        int dg;
-        if (acc + h3 >= k) { dg = 3; acc += h3; }
-        else if (acc + h3 + h2 >= k) { dg = 2; acc += h3 + h2; }
-        else if (acc + h3 + h2 + h1 >= k) { dg = 1; acc += h3 + h2 + h1; }
-        else { dg = 0; acc += h3 + h2 + h1 + h0; }
-        n_hot = acc;
-        // the lower edge of that bin: the smallest float whose upper 16 key bits are the bin's (bin 255 also
-        // holds everything farther up: its lower edge still bounds all of it)
-        T1 = key_edge(key0 + (u32)(4 * (63 - ls) + dg));
-    }
-    if (n_hot <= SEL_CAP) {  // uniform over the workgroup
-        for (int i = tid; i < n_lm; i += 256)
-            if (lane_val(i) >= T1) {
-                const int at = atomicAdd(&s_h, 1);
-                if (at < SEL_CAP) s_hot[at] = i;
-            }
-        __syncthreads();
-        for (int q = tid; q < n_hot << per_log2; q += 256) reread(s_hot[q >> per_log2], q & ((1 << per_log2) - 1), T1);
-        __syncthreads();
-        const int n2 = s_n2;
-        if (n2 <= SEL_CAP) {
-            rank_and_emit(n2);
-            return;
-        }
-    }
-
-    // ---- too many still: one pass over the elements of the lane maxima that reach T1 -----------------------------------------
-    // Two groups of eight to a thread at a time.  What reaches the threshold goes on the list; when the list is long, the k best of it
-    // stay and the k-th becomes the threshold, so that equal values later in the row no longer reach it.  -inf does not count.
-    // (51 rows of 128,256 bf16 entries, k = 28: 256 to 400 neighbours raised by 20, in fewer pairs than k, 28 to 30 us, all equal 78, all -inf 59, where
-    // taking the best k times from the whole row took 2,330; k = 10 23, 78 and 59 against 840; k = 1 9, 73 and 59 against 9, 101 and 95.)
-    auto keep_best = [&](int n) {
-        u64 key[2];
-        int rank[2] = {0, 0};
-#pragma unroll
-        for (int h = 0; h < 2; ++h) key[h] = tid + 256 * h < SEL_LIST ? s_fin[tid + 256 * h] : 0ull;
-        for (int j0 = 0; j0 < n; j0 += 4) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const u64 o = s_fin[j0 + j];
-                rank[0] += o > key[0] ? 1 : 0;
-                rank[1] += o > key[1] ? 1 : 0;
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-            if (tid + 256 * h < SEL_LIST) s_fin[tid + 256 * h] = 0ull;
-        __syncthreads();
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-            if (tid + 256 * h < n && rank[h] < k) s_fin[rank[h]] = key[h];
-        if (tid == 0) s_n2 = k;
-        __syncthreads();
-        return s_fin[k - 1] + 1ull;
-    };
-    __syncthreads();  // s_n2 has been read
-    for (int i = tid; i < SEL_LIST; i += 256) s_fin[i] = 0ull;
-    if (tid == 0) s_n2 = 0;
-    if (tid < 3) s_cnt[tid] = 0;
-    __syncthreads();
-    u64 threshold = (u64)max(ord32(T1), 0x00800000u) << 32;
-    const bool listed = n_hot <= SEL_CAP;
-    const int pairs_log2 = per_log2 - 1, total = (listed ? n_hot : n_lm) << pairs_log2;
-    int n = 0, step = 0;
-    for (int q0 = 0; q0 < total; q0 += 256) {
-        const int q = q0 + tid, at = min(q, total - 1) >> pairs_log2, i = listed ? s_hot[at] : at;
-        float x[2][8];
-        int s0 = 0, s1 = 0;
-        u32 todo = 0;
-        if (q < total && (listed || lane_val(i) >= T1)) {
-            const int m = 2 * (q & ((1 << pairs_log2) - 1));
-            s0 = load_octet<BF16, SAME>(a, g, octet_of(i, m), x[0]);
-            s1 = load_octet<BF16, SAME>(a, g, octet_of(i, m + 1), x[1]);
-#pragma unroll
-            for (int e = 0; e < 16; ++e)
-                todo |= (make_key(x[e >> 3][e & 7], (u32)((e < 8 ? s0 : s1 - 8) + e)) >= threshold ? 1u : 0u) << e;
-        }
-        for (bool all = false; !all;) {
-            // how many of the workgroup's elements wait; three counters in turn, so that one barrier does
-            const int sum = wave_sum_i32(__popc(todo));
-            if (lane == 0 && sum) atomicAdd(&s_cnt[step % 3], sum);
-            __syncthreads();
-            const int waiting = s_cnt[step % 3];
-            if (tid == 0) s_cnt[(step + 2) % 3] = 0;
-            ++step;
-            if (waiting == 0) break;
-            all = n + waiting <= SEL_LIST;  // else one of each thread's: at most 256 behind at most SEL_CAP
-            for (u32 now = all ? todo : todo & (0u - todo); now; now &= now - 1) {
-                const int e = __builtin_ctz(now);
-                float v = x[0][0];
-#pragma unroll
-                for (int j = 1; j < 16; ++j) v = e == j ? x[j >> 3][j & 7] : v;
-                const u64 key = make_key(v, (u32)((e < 8 ? s0 : s1 - 8) + e));
-                if (key >= threshold) s_fin[atomicAdd(&s_n2, 1)] = key;
-            }
-            todo &= todo - 1;
-            __syncthreads();
-            n = s_n2;
-            if (n > SEL_CAP) {
-                threshold = keep_best(n);
-                n = k;
-            }
-        }
-    }
-    rank_and_emit(n);
-    if (tid >= n && tid < k) emit(tid, make_key(-INFINITY, 0u));
+        rank_and_emit(n);
+        if (tid >= n && tid < k) emit(tid, make_key(-INFINITY, 0u));
+    } while (false);
+    level_row_end<MODE, offsetof(SelectArgs, tail)>(meta, false);
 }
 
 // ---------------------------------------------------- rows that one workgroup holds (top-k rows) --
@@ -774,7 +839,8 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl_, 
 // both before hits went by bits, see keep_hits).  In a small launch with a wave to a SIMD
 // the barrier that this takes costs what it saves, or more (5 rows of 1,024 fp32 entries 3.53 and 3.61): there every wave finds T.
 template <int MODE, int NL, bool BF16, bool VEC, int NT, bool ONE>
-__global__ __launch_bounds__(NT, NL == 4 ? 4 : 8) void row_topk_kernel(RowArgs a, float *top_val, int32_t *top_id, float *lse, int out_stride) {
+__global__ __launch_bounds__(NT, NL == 4 ? 4 : 8) void row_topk_kernel(RowArgs a, float *top_val, int32_t *top_id, float *lse, int out_stride, Tail<MODE> tail) {
+    if (level_waits<MODE, offsetof(HeldArgs, tail)>(tail, blockIdx.x)) return;
     constexpr int E = 8 * NL, NW = NT / 64;
     const bool lse_wg = NT == 1024 && a.lse_apart && (int64_t)blockIdx.x >= a.n_rows;
     const int64_t g = lse_wg ? (int64_t)blockIdx.x - a.n_rows : (int64_t)blockIdx.x;
@@ -819,133 +885,136 @@ __global__ __launch_bounds__(NT, NL == 4 ? 4 : 8) void row_topk_kernel(RowArgs a
         const float2 p = lane < NW ? s_ms[min(lane, NW - 1)] : make_float2(-INFINITY, 0.f);
         const float M = wave_max(p.x);
         const float sum = wave_sum(p.y > 0.f ? p.y * __builtin_amdgcn_exp2f((p.x - M) * cexp) : 0.f);
-        if (lane == 0) lse[meta.out] = M == -INFINITY ? -INFINITY : M * a.inv_t + __logf(sum);
+        if (lane == 0) put_result<MODE>(lse + meta.out, M == -INFINITY ? -INFINITY : M * a.inv_t + __logf(sum));
     };
-    if (lse_wg) {  // uniform over the workgroup
-        lse_partial();
-        __syncthreads();
-        if (w == 0) row_lse();
-        return;
-    }
-    if (!ONE && want_lse) lse_partial();
-    __syncthreads();
-    // 256 slots of NW / 4 threads each: k slots that reach T hold k elements that do
-    float T;
-    if (!ONE || w == 0) {
-        u32 ky[4];
-        uint16_t kv[NW];
-        __builtin_memcpy(kv, __builtin_assume_aligned(&s_key[lane * NW], NW * 2), NW * 2);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            ky[i] = kv[i];
-#pragma unroll
-            for (int j = i + 4; j < NW; j += 4) ky[i] = max(ky[i], (u32)kv[j]);
-        }
-        T = key_edge(wave_kth_of_256(ky, k));
-    }
-    if constexpr (ONE) {
-        if (w == 0) {
-            if (lane == 0) s_T = T;
-        } else if (want_lse) {
+    do {
+        if (lse_wg) {  // uniform over the workgroup
             lse_partial();
-        }
-        __syncthreads();
-        T = s_T;
-        if (w == 0 && want_lse) lse_partial();
-    }
-    auto id_of = [&](int n, int e) {
-        const int id0 = base + n * 512;
-        return (VEC ? group_start(V, id0) : id0) + e;
-    };
-    auto push = [&](bool in, int j) {
-        if (__builtin_amdgcn_ballot_w64(in)) {  // uniform: few elements get here
-            if (in) {
-                const int at = atomicAdd(&s_n, 1);
-                if (at < SEL_CAP) s_fin[at] = make_key(x[j], (u32)id_of(j >> 3, j & 7));
-            }
-        }
-    };
-    const float T1 = fmaxf(T, -__FLT_MAX__);  // -inf does not count
-#pragma unroll
-    for (int n = 0; n < NL; ++n)
-        if (__builtin_amdgcn_ballot_w64(gmx[n] >= T1))
-            keep_hits<8>([&](int e) { return x[8 * n + e]; }, [&](int e) { return id_of(n, e); }, T1, &s_n, s_fin);
-    __syncthreads();
-    int n = s_n;
-    if (n > SEL_CAP) {
-        // Clusters or equal values: the exact k-th key by bisection, then, of the elements equal to it, the exact last id.
-        int step = 0;
-        auto total = [&](int own) {  // sum over the workgroup; three counters in turn, so that one barrier does
-            const int sum = wave_sum_i32(own);
-            if (lane == 0) atomicAdd(&s_cnt[step % 3], sum);
             __syncthreads();
-            const int v = s_cnt[step % 3];
-            if (tid == 0) s_cnt[(step + 2) % 3] = 0;
-            ++step;
-            return v;
-        };
-        u32 lo = ord32(T), hi = 0xFFFFFFFFu;  // at least k keys reach lo, none lies above hi
-        if (lo <= 0x007FFFFFu) lo = 0x00800000u;  // -inf does not count
-        int c = n;
-        while (hi > lo && c > k) {
-            const u32 mid = lo + ((hi - lo) >> 1) + 1u;
-            int own = 0;
-#pragma unroll
-            for (int j = 0; j < E; ++j) own += ord32(x[j]) >= mid ? 1 : 0;
-            const int m = total(own);
-            if (m >= k) { lo = mid; c = m; }
-            else hi = mid - 1u;
+            if (w == 0) row_lse();
+            break;
         }
-        int id_hi = 0x7FFFFFFF;  // of the elements equal to lo: those up to this id
-        if (c > k) {
-            int own = 0;
+        if (!ONE && want_lse) lse_partial();
+        __syncthreads();
+        // 256 slots of NW / 4 threads each: k slots that reach T hold k elements that do
+        float T;
+        if (!ONE || w == 0) {
+            u32 ky[4];
+            uint16_t kv[NW];
+            __builtin_memcpy(kv, __builtin_assume_aligned(&s_key[lane * NW], NW * 2), NW * 2);
 #pragma unroll
-            for (int j = 0; j < E; ++j) own += ord32(x[j]) > lo ? 1 : 0;
-            const int need = k - total(own);
-            int id_lo = 0;  // the smallest id with `need` of them at or below it
-            id_hi = V - 1;
-            while (id_hi > id_lo) {
-                const int mid = (id_lo + id_hi) >> 1;
-                own = 0;
+            for (int i = 0; i < 4; ++i) {
+                ky[i] = kv[i];
 #pragma unroll
-                for (int j = 0; j < E; ++j) own += ord32(x[j]) == lo && id_of(j >> 3, j & 7) <= mid ? 1 : 0;
-                if (total(own) >= need) id_hi = mid;
-                else id_lo = mid + 1;
+                for (int j = i + 4; j < NW; j += 4) ky[i] = max(ky[i], (u32)kv[j]);
+            }
+            T = key_edge(wave_kth_of_256(ky, k));
+        }
+        if constexpr (ONE) {
+            if (w == 0) {
+                if (lane == 0) s_T = T;
+            } else if (want_lse) {
+                lse_partial();
+            }
+            __syncthreads();
+            T = s_T;
+            if (w == 0 && want_lse) lse_partial();
+        }
+        auto id_of = [&](int n, int e) {
+            const int id0 = base + n * 512;
+            return (VEC ? group_start(V, id0) : id0) + e;
+        };
+        auto push = [&](bool in, int j) {
+            if (__builtin_amdgcn_ballot_w64(in)) {  // uniform: few elements get here
+                if (in) {
+                    const int at = atomicAdd(&s_n, 1);
+                    if (at < SEL_CAP) s_fin[at] = make_key(x[j], (u32)id_of(j >> 3, j & 7));
+                }
+            }
+        };
+        const float T1 = fmaxf(T, -__FLT_MAX__);  // -inf does not count
+#pragma unroll
+        for (int n = 0; n < NL; ++n)
+            if (__builtin_amdgcn_ballot_w64(gmx[n] >= T1))
+                keep_hits<8>([&](int e) { return x[8 * n + e]; }, [&](int e) { return id_of(n, e); }, T1, &s_n, s_fin);
+        __syncthreads();
+        int n = s_n;
+        if (n > SEL_CAP) {
+            // Clusters or equal values: the exact k-th key by bisection, then, of the elements equal to it, the exact last id.
+            int step = 0;
+            auto total = [&](int own) {  // sum over the workgroup; three counters in turn, so that one barrier does
+                const int sum = wave_sum_i32(own);
+                if (lane == 0) atomicAdd(&s_cnt[step % 3], sum);
+                __syncthreads();
+                const int v = s_cnt[step % 3];
+                if (tid == 0) s_cnt[(step + 2) % 3] = 0;
+                ++step;
+                return v;
+            };
+            u32 lo = ord32(T), hi = 0xFFFFFFFFu;  // at least k keys reach lo, none lies above hi
+            if (lo <= 0x007FFFFFu) lo = 0x00800000u;  // -inf does not count
+            int c = n;
+            while (hi > lo && c > k) {
+                const u32 mid = lo + ((hi - lo) >> 1) + 1u;
+                int own = 0;
+#pragma unroll
+                for (int j = 0; j < E; ++j) own += ord32(x[j]) >= mid ? 1 : 0;
+                const int m = total(own);
+                if (m >= k) { lo = mid; c = m; }
+                else hi = mid - 1u;
+            }
+            int id_hi = 0x7FFFFFFF;  // of the elements equal to lo: those up to this id
+            if (c > k) {
+                int own = 0;
+#pragma unroll
+                for (int j = 0; j < E; ++j) own += ord32(x[j]) > lo ? 1 : 0;
+                const int need = k - total(own);
+                int id_lo = 0;  // the smallest id with `need` of them at or below it
+                id_hi = V - 1;
+                while (id_hi > id_lo) {
+                    const int mid = (id_lo + id_hi) >> 1;
+                    own = 0;
+#pragma unroll
+                    for (int j = 0; j < E; ++j) own += ord32(x[j]) == lo && id_of(j >> 3, j & 7) <= mid ? 1 : 0;
+                    if (total(own) >= need) id_hi = mid;
+                    else id_lo = mid + 1;
+                }
+            }
+            __syncthreads();  // the count has been read
+            if (tid < SEL_CAP) s_fin[tid] = 0ull;
+            if (tid == 0) s_n = 0;
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < E; ++j) push(ord32(x[j]) > lo || (ord32(x[j]) == lo && id_of(j >> 3, j & 7) <= id_hi), j);
+            __syncthreads();
+            n = s_n;
+        }
+        float *tv = top_val + meta.out * out_stride;
+        int32_t *ti = top_id + meta.out * out_stride;
+        if (tid < SEL_CAP && (tid & ~63) < n) {  // candidate tid ranks itself against all (zeros behind the n keys)
+            const u64 mine = s_fin[tid];
+            int rank = 0;
+            for (int j0 = 0; j0 < n; j0 += 8) {
+                u64 o[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) o[j] = s_fin[j0 + j];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) rank += o[j] > mine ? 1 : 0;
+            }
+            if (tid < n && rank < k) {
+                put_result<MODE>(tv + rank, key_val(mine));
+                put_result<MODE>(ti + rank, (int32_t)key_idx(mine));
             }
         }
-        __syncthreads();  // the count has been read
-        if (tid < SEL_CAP) s_fin[tid] = 0ull;
-        if (tid == 0) s_n = 0;
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < E; ++j) push(ord32(x[j]) > lo || (ord32(x[j]) == lo && id_of(j >> 3, j & 7) <= id_hi), j);
-        __syncthreads();
-        n = s_n;
-    }
-    float *tv = top_val + meta.out * out_stride;
-    int32_t *ti = top_id + meta.out * out_stride;
-    if (tid < SEL_CAP && (tid & ~63) < n) {  // candidate tid ranks itself against all (zeros behind the n keys)
-        const u64 mine = s_fin[tid];
-        int rank = 0;
-        for (int j0 = 0; j0 < n; j0 += 8) {
-            u64 o[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) o[j] = s_fin[j0 + j];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) rank += o[j] > mine ? 1 : 0;
+        if (w == NW - 1) {
+            if (lane >= n && lane < k) {  // fewer than k viable entries
+                put_result<MODE>(tv + lane, -INFINITY);
+                put_result<MODE>(ti + lane, (int32_t)-1);
+            }
+            if (want_lse) row_lse();
         }
-        if (tid < n && rank < k) {
-            tv[rank] = key_val(mine);
-            ti[rank] = (int32_t)key_idx(mine);
-        }
-    }
-    if (w == NW - 1) {
-        if (lane >= n && lane < k) {  // fewer than k viable entries
-            tv[lane] = -INFINITY;
-            ti[lane] = -1;
-        }
-        if (want_lse) row_lse();
-    }
+    } while (false);
+    level_row_end<MODE, offsetof(HeldArgs, tail)>(meta, lse_wg);
 }
 
 // ------------------------------------------------- bf16 rows of large launches (top-k rows) --
@@ -1396,12 +1465,31 @@ static hipError_t launch_stream(const RowArgs &a_in, int64_t n_rows, int nl, hip
 }
 
 // top-k rows, pass 2: selection on the lane maxima
+// What a launch of a level's rows needs to choose the level's nodes, with `first_wg` workgroups of rows and its words at `words` (null: it does not).
+template <int MODE>
+static Tail<MODE> level_tail(const RowArgs &a, const TreeArgs *tree, void *words, unsigned first_wg) {
+    if constexpr (MODE == ROWS_LEVEL) {
+        LevelTail h = {};
+        h.first_wg = -1;  // as a number without sign: no workgroup reaches it
+        if (!tree) return h;
+        h.t = *tree;
+        h.words = (u64 *)words;
+        h.tag = launch_tag();
+        h.first_wg = (int)first_wg;
+        h.rows = a.rows_per_seq;
+        h.lse_apart = a.lse_apart;
+        return h;
+    } else {
+        return NoTail();
+    }
+}
+
 static hipError_t launch_select(const RowArgs &a, int64_t n_rows, int nl, float *top_val, int32_t *top_id, float *lse,
                                 int out_stride, hipStream_t st) {
     const int S = rows_chunks_per_row(a.V, nl);
     by_mode_and_type(a, [&](auto mode, auto bf16) {
         launch_kernel(KID_ROWS_MERGE, st, row_select_kernel<decltype(mode)::value, decltype(bf16)::value, 0>, dim3((unsigned)n_rows),
-                      dim3(256), 0, a, nl, S, top_val, top_id, lse, out_stride, 0ull);
+                      dim3(256), 0, a, nl, S, top_val, top_id, lse, out_stride, 0ull, level_tail<decltype(mode)::value>(a, nullptr, nullptr, 0));
     });
     return hipGetLastError();
 }
@@ -1417,7 +1505,7 @@ static bool takes_pass(const RowArgs &a, int64_t n_rows, int nl) {
     const int64_t S = rows_chunks_per_row(a.V, nl);
     return S <= 16 && (n_rows + 7) / 8 * 8 * (S + 1) <= PASS_WGS && (a.dtype == DT_F32 || n_rows * a.V <= PASS_ENTRIES);
 }
-static hipError_t launch_pass(const RowArgs &a_in, int64_t n_rows, int nl, float *top_val, int32_t *top_id, float *lse, int out_stride, hipStream_t st) {
+static hipError_t launch_pass(const RowArgs &a_in, int64_t n_rows, int nl, float *top_val, int32_t *top_id, float *lse, int out_stride, hipStream_t st, const TreeArgs *tree) {
     RowArgs a = a_in;
     const int S = rows_chunks_per_row(a.V, nl);
     a.early_load = 1;
@@ -1427,8 +1515,10 @@ static hipError_t launch_pass(const RowArgs &a_in, int64_t n_rows, int nl, float
         constexpr int MODE = decltype(mode)::value;
         constexpr bool BF = decltype(bf16)::value;
         auto go = [&](auto kernel) {
-            launch_kernel(kid, st, kernel, dim3(8 * (S + 1), (unsigned)((n_rows + 7) / 8)), dim3(256), 0, a, nl, S, top_val, top_id, lse, out_stride,
-                          launch_tag());
+            const unsigned x = 8 * (S + 1), y = (unsigned)((n_rows + 7) / 8), more = tree ? (unsigned)((tree->batch + x - 1) / x) : 0;
+            // a level's words lie behind those of the rows (row_select_kernel)
+            const auto tail = level_tail<MODE>(a, tree, (char *)a.lane_max + n_rows * (S * 512 + (LINE_WORDS + 17) * 8), x * y);
+            launch_kernel(kid, st, kernel, dim3(x, y + more), dim3(256), 0, a, nl, S, top_val, top_id, lse, out_stride, launch_tag(), tail);
         };
         if (nl == 4) go(row_select_kernel<MODE, BF, 4>);
         else if (nl == 2) go(row_select_kernel<MODE, BF, 2>);
@@ -1448,7 +1538,7 @@ static int held_threads(int V) { return V <= 256 * 16 ? 256 : V <= 512 * 16 ? 51
 #define APART_ROWS 128
 #define SMALL_ROWS 512  // most rows of a launch that leaves a SIMD a wave or two of 256-thread workgroups
 static hipError_t launch_held(const RowArgs &a_in, int64_t n_rows, float *top_val, int32_t *top_id, float *lse, int out_stride,
-                              hipStream_t st) {
+                              hipStream_t st, const TreeArgs *tree) {
     RowArgs a = a_in;
     a.early_load = n_rows * rows_chunks_per_row(a.V, 4) <= EARLY_LOAD_WGS;
     a.n_rows = n_rows;
@@ -1459,7 +1549,8 @@ static hipError_t launch_held(const RowArgs &a_in, int64_t n_rows, float *top_va
         constexpr int MODE = decltype(mode)::value;
         constexpr bool BF = decltype(bf16)::value;
         auto go = [&](auto kernel, int nt) {
-            launch_kernel(kid, st, kernel, dim3((unsigned)wgs), dim3(nt), 0, a, top_val, top_id, lse, out_stride);
+            launch_kernel(kid, st, kernel, dim3((unsigned)(wgs + (tree ? tree->batch : 0))), dim3(nt), 0, a, top_val, top_id, lse, out_stride,
+                          level_tail<MODE>(a, tree, a.lane_max, (unsigned)wgs));
         };
         const bool one = n_rows > SMALL_ROWS;
         if (a.V < 8) go(row_topk_kernel<MODE, 1, BF, false, 256, false>, 256);  // no 16-byte group: element loads
@@ -1516,19 +1607,26 @@ static bool takes_many(const RowArgs &a, int64_t n_rows) {
     return n_rows * room > ((int64_t)1 << 22);
 }
 hipError_t rows_launch_topk(const RowArgs &a, int64_t n_rows, float *top_val, int32_t *top_id, float *lse, int out_stride,
-                            hipStream_t st) {
+                            hipStream_t st, const TreeArgs *tree, bool *to_expand) {
     if (n_rows <= 0) return hipSuccess;
+    // A level's nodes are chosen by one wave (level_expand): the first level's, or those of up to NARROW_K parents.
+    if (tree && a.level > 1 && a.rows_per_seq > NARROW_K) tree = nullptr;
     if (takes_many(a, n_rows)) return launch_many(a, n_rows, top_val, top_id, lse, out_stride, st);
     const int nt = held_threads(a.V);
     if ((a.V <= HELD_V_MAX && (nt == 256 || n_rows * nt <= 0xFFFFFFFFll)) ||
-        (a.V <= 2 * HELD_V_MAX && a.dtype == DT_BF16 && n_rows <= HELD_ROWS_MAX))
-        return launch_held(a, n_rows, top_val, top_id, lse, out_stride, st);
+        (a.V <= 2 * HELD_V_MAX && a.dtype == DT_BF16 && n_rows <= HELD_ROWS_MAX)) {
+        if (tree) *to_expand = false;
+        return launch_held(a, n_rows, top_val, top_id, lse, out_stride, st, tree);
+    }
     // Chunks of 4,096 entries, for launches that have too few of 8,192, cost larger ones 3 to 18 %: calls of 1,000 rows of 50,257 entries, 4,096 | 8,192, 25.3 | 23.4 us,
     // of 65,536 29.3 | 26.9, 200 of 36,000 9.0 | 9.1, fp32 500 of 40,001 21.9 | 21.9, 1,000 38.8 | 36.6; draft rows 776 of 64,960 31.8 | 26.0, 10,309 293 | 264.  (The scratch
     // was sized for the smaller ones.)
     int nl = rows_topk_nl(a.V);
     if (nl == 2 && n_rows * rows_chunks_per_row(a.V, 4) > EARLY_LOAD_WGS) nl = 4;
-    if (takes_pass(a, n_rows, nl)) return launch_pass(a, n_rows, nl, top_val, top_id, lse, out_stride, st);
+    if (takes_pass(a, n_rows, nl)) {
+        if (tree) *to_expand = false;
+        return launch_pass(a, n_rows, nl, top_val, top_id, lse, out_stride, st, tree);
+    }
     const hipError_t e = launch_stream(a, n_rows, nl, st);
     return e != hipSuccess ? e : launch_select(a, n_rows, nl, top_val, top_id, lse, out_stride, st);
 }

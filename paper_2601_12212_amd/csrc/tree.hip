@@ -21,65 +21,18 @@
 
 #include <type_traits>
 
-#include "common.hpp"
-#include "kernels.hpp"
+#include "level.hpp"
 
 namespace dt {
-
 
 #define DT_P_MAX (DT_K_MAX + (DT_D_MAX - 1) * DT_K_MAX * DT_K_MAX)
 #define TREE_NT 512               // threads of the workgroup
 #define TREE_NW (TREE_NT / 64)    // its waves
-#define NARROW_K 16               // levels of at most NARROW_K^2 candidates: one wave
 #define LIST_CAP 1024             // most candidates that a thinning may leave
 #define CAND_CAP 512              // most candidates of a wide level that its bound may leave
 #define BUCKET_CAP 64             // most candidates of one score bucket that are ranked one against the other
 #define SHARE_MAX 15              // most candidates per thread of a pool, an odd number
 
-// order-preserving integer image of a score (ord32; adding zero folds -0 onto +0)
-__device__ __forceinline__ u32 score_key(float s) {
-    const u32 u = __float_as_uint(s + 0.0f);
-    return u ^ ((u32)((int)u >> 31) | 0x80000000u);
-}
-#define KEY_NEG_INF 0x007FFFFFu   // key of -inf: a candidate that does not exist
-
-// x / dv for 0 <= x < 8192 and 1 <= dv <= 1024 with inv = 1.0f / dv (any rounding within two ulp):
-// (x + 0.5) / dv is at least 0.5 / dv away from every integer, far more than the product's error.
-__device__ __forceinline__ int fdiv(int x, float inv) { return (int)(((float)x + 0.5f) * inv); }
-
-struct Decoded {
-    int level, slot, rank, row;
-};
-struct PoolShape {
-    int k, kk;
-    float inv_k, inv_kk;
-};
-__device__ __forceinline__ PoolShape pool_shape(int k) {
-    PoolShape s;
-    s.k = k; s.kk = k * k;
-    s.inv_k = 1.0f / (float)k; s.inv_kk = 1.0f / (float)(k * k);
-    return s;
-}
-// pool index -> (level, slot of the parent in its level's expanded set, rank in the parent's row, draft row)
-__device__ __forceinline__ Decoded decode(int p, const PoolShape &s) {
-    Decoded d;
-    if (p < s.k) {
-        d.level = 1; d.slot = 0; d.rank = p; d.row = 0;
-    } else {
-        const int q = p - s.k;
-        const int l2 = fdiv(q, s.inv_kk), rem = q - l2 * s.kk;
-        d.level = l2 + 2; d.slot = fdiv(rem, s.inv_k); d.rank = rem - d.slot * s.k;
-        d.row = 1 + l2 * s.k + d.slot;
-    }
-    return d;
-}
-
-// An expanded node: score, pool index, and the slots of its ancestors and itself, five bits per level.
-struct __attribute__((aligned(16))) Parent {
-    float score;
-    int index;
-    u64 path;
-};
 struct TreeLds {
     float score[DT_P_MAX];         // cumulative score of a candidate
     float lp[DT_P_MAX];            // its own log-probability (finite, or -inf: does not exist) and token, kept for the
@@ -98,70 +51,6 @@ struct TreeLds {
     int p_end, n_exp, memn;
 };
 
-// What the expansion of level l hands on to that of level l + 1 when the tree is built level by level: the nodes it chose, how many, the
-// token count, and which level it was.  It lies in the last rows of the sequence's state, which belong to the deepest level's pass and are
-// free until then.  Without it, or with another level's (a level asked for again), the levels before are gone through again, from the
-// row results.  (How many, in the same word as the level: the state's own count is that of the last call, which may have been a later level's.)  Each level gone through again took 0.5 us with k up to 16 and 1.7 beyond.  All calls of a step, replayed: (60, 6, 10), 128,256 tokens
-// 78.2 -> 74.7 us (with the kernels of their own); 16 sequences of up to (123, 8, 23), 1,152 tokens 125.6 -> 101.7; 4 of (66, 3, 8) 32.0 -> 31.7.
-#define CARRY_ROW (DT_STATE_ROWS - 4)  // four rows of values: DT_K_MAX Parents; two words of the ids
-#define CARRY_FROM 2  // level 1 expands the root's children: nothing to go through
-#define CARRY_LEVELS ((CARRY_ROW - 1) / DT_K_MAX)  // levels whose nodes' rows, at most l DT_K_MAX, end before it
-static_assert(4 * DT_K_MAX * sizeof(float) == DT_K_MAX * sizeof(Parent), "four rows");
-#define CARRY_COUNT 0x3F0  // where the tag holds the number of nodes
-__device__ __forceinline__ int carry_tag(int level, int n_exp) { return 0x7A5C3000 | n_exp << 4 | level; }
-static_assert(DT_D_MAX < 16 && DT_K_MAX <= CARRY_COUNT >> 4, "the tag's fields");
-__device__ __forceinline__ int64_t carry_at(int64_t seq_rows, int b) { return (b * seq_rows + CARRY_ROW) * DT_K_MAX; }
-// The level to start from, its nodes and the token count: level 0, nothing.
-struct Start {
-    int level, n_exp, tok_count;
-};
-
-// ---- selection inside a wave ---------------------------------------------------------------------------
-// The `keep` best of the keys that a wave holds (key q of lane i is candidate i + 64 q), equal keys by ascending candidate;
-// all viable ones if they are fewer.  The caller knows bounds: lo is KEY_NEG_INF or lies below at
-// least `keep` keys, no key lies above hi.  Returns how many were chosen (uniform).
-template <int G>
-__device__ __forceinline__ int wave_select(const u32 (&key)[G], int keep, u32 lo, u32 hi, bool (&chosen)[G]) {
-    int c = count_above<G>(key, lo), equal = 0;  // equal > 0: that many of the keys equal to lo are chosen too
-    if (c > keep) {
-        // more than `keep` above lo, fewer above hi = lo + width
-        u32 width = hi - lo;
-        for (int step = 0; step < (G < 4 ? 7 : 10); ++step) {
-            const u32 half = width >> 1, mid = lo + half;
-            c = count_above<G>(key, mid);
-            width -= half;
-            lo = c >= keep ? mid : lo;
-            if (c == keep) break;
-        }
-        hi = lo + width;
-        // Candidates close together, or equal: from here on a candidate of those in (lo, hi] divides them.
-        while (c != keep) {
-            u32 any = 0u;
-#pragma unroll
-            for (int q = 0; q < G; ++q) any = key[q] > lo && key[q] <= hi ? key[q] : any;
-            const u32 pivot = (u32)__builtin_amdgcn_readlane((int)any, __builtin_ctzll(__builtin_amdgcn_ballot_w64(any != 0u)));
-            c = count_above<G>(key, pivot - 1u);
-            if (c < keep) hi = pivot - 1u;
-            else if (c == keep) lo = pivot - 1u;
-            else {
-                lo = pivot;
-                c = count_above<G>(key, pivot);
-                if (c < keep) { equal = keep - c; c = keep; }
-            }
-        }
-    }
-#pragma unroll
-    for (int q = 0; q < G; ++q) chosen[q] = key[q] > lo;
-    if (equal) {
-#pragma unroll
-        for (int q = 0; q < G; ++q) {
-            const u64 eq = __builtin_amdgcn_ballot_w64(key[q] == lo);
-            chosen[q] = chosen[q] || (key[q] == lo && (int)lanes_below(eq) < equal);
-            equal -= min(equal, (int)__popcll(eq));
-        }
-    }
-    return c;
-}
 // ---- radix selection ---------------------------------------------------------------------------------
 // Key of the keep-th best of score[0..n), keep = min(keep_max, #viable): returns keep (uniform), thr and
 // need_eq = how many candidates with key == thr belong to the chosen set.  Whole workgroup; ends
@@ -262,19 +151,6 @@ __device__ __forceinline__ int block_enumerate(const float *score, int n, u32 th
 }
 
 // ---- expansion ---------------------------------------------------------------------------------------
-// Bounds of a level's cut: the best children of k nodes (lane s < k: key `fk` of slot s's, rows descend) are k candidates, so
-// at least k lie above `lo`; none lies above `hi`.
-__device__ __forceinline__ void level_bounds(u32 fk, int k, u32 &lo, u32 &hi) {
-    const bool viable = lane_id() < k && fk > KEY_NEG_INF;
-    u32 x = viable ? fk : 0u, y = viable ? ~fk : 0u;  // the maxima over lanes 0 .. 31 end in lane 31
-#define STEP(CTRL, ROWS)                                          \
-    x = max(x, (u32)dpp_mov<CTRL, ROWS>(0, (int)x));              \
-    y = max(y, (u32)dpp_mov<CTRL, ROWS>(0, (int)y));
-    STEP(0x111, 0xf) STEP(0x112, 0xf) STEP(0x114, 0xf) STEP(0x118, 0xf) STEP(0x142, 0xa)
-#undef STEP
-    hi = (u32)__builtin_amdgcn_readlane((int)x, 31);
-    lo = __popcll(__builtin_amdgcn_ballot_w64(viable)) == k ? ~(u32)__builtin_amdgcn_readlane((int)y, 31) - 1u : KEY_NEG_INF;
-}
 __device__ __forceinline__ void put_parent(TreeLds &S, int l, int pos, float score, int index, u64 above) {
     Parent pr;
     pr.score = score;
@@ -290,47 +166,16 @@ __device__ __forceinline__ int choose_first(TreeLds &S, int k, float sc) {
     if ((m >> lane) & 1ull) put_parent(S, 1, (int)lanes_below(m), sc, lane, 0ull);
     return __popcll(m);
 }
-// The head of what level l hands on, by one thread.
-__device__ __forceinline__ void carry_head(const TreeArgs &a, int b, int l, int n_exp, int tok_count) {
-    if (l >= CARRY_FROM && l <= CARRY_LEVELS) *(int2 *)(a.state_id + carry_at(a.seq_rows, b)) = make_int2(carry_tag(l, n_exp), tok_count);
-}
-// What the draft model is handed for its next pass, by one wave: node s of the set chosen at level l.
-__device__ __forceinline__ void emit_level(const TreeArgs &a, const TreeLds &S, int b, int l, int k, int n_exp, int tok_count) {
-    const int lane = lane_id();
-    const bool carry = l >= CARRY_FROM && l <= CARRY_LEVELS;
-    const int64_t at = carry_at(a.seq_rows, b);
-    if (lane < n_exp) {
-        const Parent pr = S.par[l][lane];
-        if (carry) ((Parent *)(a.state_val + at))[lane] = pr;
-        const Decoded dc = decode(pr.index, pool_shape(k));
-        const int64_t e = (int64_t)b * DT_K_MAX + lane;
-        a.exp_token[e] = S.tok[pr.index];
-        a.exp_parent_slot[e] = l == 1 ? -1 : dc.slot;
-        a.exp_row[e] = 1 + (l - 1) * k + lane;
-        a.exp_pos[e] = (a.prefix_len ? max(a.prefix_len[b], 0) : 0) + l;
-        // draft-side mask over draft rows: the root's row, the rows of the ancestors, its own
-        u64 w0 = 1ull, w1 = 0ull, w2 = 0ull, w3 = 0ull;
-        for (int j = 1; j <= l; ++j) {
-            const int r = 1 + (j - 1) * k + (int)((pr.path >> (5 * (j - 1))) & 31);
-            const u64 bit = 1ull << (r & 63);
-            const int wd = r >> 6;
-            w0 |= wd == 0 ? bit : 0ull; w1 |= wd == 1 ? bit : 0ull;
-            w2 |= wd == 2 ? bit : 0ull; w3 |= wd == 3 ? bit : 0ull;
-        }
-        a.exp_mask[e * 4] = w0; a.exp_mask[e * 4 + 1] = w1;
-        a.exp_mask[e * 4 + 2] = w2; a.exp_mask[e * 4 + 3] = w3;
-    }
-    if (lane == 0) {
-        a.n_expand[b] = n_exp;
-        a.state_n_exp[b] = l << 8 | n_exp;
-        carry_head(a, b, l, n_exp, tok_count);
-    }
+__device__ __forceinline__ Parent node_of(const TreeLds &S, int l, int slot, int &token) {
+    const Parent pr = S.par[l][slot];
+    token = S.tok[pr.index];
+    return pr;
 }
 
 // All levels, by one wave: G candidates per lane, 64 G >= k^2.  Returns the end of the pool (levels computed so far), or -1
 // when only level `xl` was wanted and has been written.  LDS is written and read by this wave alone, in order.
 template <int G, bool EXPAND>
-__device__ __forceinline__ int levels_narrow(const TreeArgs &a, TreeLds &S, int b, int k, int d, int TT, const Start &from) {
+__device__ __forceinline__ int levels_narrow(const TreeArgs &a, TreeLds &S, int b, int k, int d, int TT, const Start &from, u32 word) {
     const int lane = lane_id(), xl = EXPAND ? a.expand_level : 0, kk = k * k;
     const int skip = from.level > 0 ? (from.level - 1) * kk : 0;  // candidates of the levels that are not gone through
     const PoolShape ps = pool_shape(k);
@@ -360,7 +205,7 @@ __device__ __forceinline__ int levels_narrow(const TreeArgs &a, TreeLds &S, int 
     }
     while (n_exp > 0) {
         if (l == xl) {
-            emit_level(a, S, b, l, k, n_exp, tok_count);
+            emit_level(a, b, l, k, n_exp, tok_count, word, a.prefix_len ? a.prefix_len[b] : 0, [&](int s, int &token) { return node_of(S, l, s, token); });
             return -1;
         }
         // slots beyond the expanded set own no node: their candidates do not exist
@@ -410,8 +255,7 @@ __device__ __forceinline__ int levels_narrow(const TreeArgs &a, TreeLds &S, int 
     }
     if (xl > 0) {  // an earlier level had nothing viable to expand, or the token count ended the expansion
         if (lane == 0) {
-            a.n_expand[b] = 0;
-            a.state_n_exp[b] = xl << 8;
+            emit_nothing(a, b, xl, word);
             carry_head(a, b, xl, 0, tok_count);
         }
         return -1;
@@ -458,7 +302,7 @@ __device__ __forceinline__ int choose_wide(TreeLds &S, int l, int k, int n, u32 
 // All levels of more than NARROW_K^2 candidates, by all waves: Q candidates per thread, k^2 <= Q TREE_NT.  As above.  (Two per thread,
 // and lists of up to 128 candidates cut four to a lane instead of two: (TT, d, k) = (80, 6, 20) 14.1 us, 13.3 so.)
 template <int Q, bool EXPAND>
-__device__ __forceinline__ int levels_wide(const TreeArgs &a, TreeLds &S, int b, int k, int d, int TT, const Start &from) {
+__device__ __forceinline__ int levels_wide(const TreeArgs &a, TreeLds &S, int b, int k, int d, int TT, const Start &from, u32 word) {
     const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int xl = EXPAND ? a.expand_level : 0, kk = k * k;
     const PoolShape ps = pool_shape(k);
@@ -500,7 +344,7 @@ __device__ __forceinline__ int levels_wide(const TreeArgs &a, TreeLds &S, int b,
                 });
             if (lane >= n && lane < DT_K_MAX) S.par[l][lane].score = -INFINITY;
             if (lane == 0) S.n_exp = n;
-            if (l == xl) emit_level(a, S, b, l, k, n, tok_count);
+            if (l == xl) emit_level(a, b, l, k, n, tok_count, word, a.prefix_len ? a.prefix_len[b] : 0, [&](int s, int &token) { return node_of(S, l, s, token); });
         }
         if (l == xl) return -1;
         __syncthreads();
@@ -548,8 +392,7 @@ __device__ __forceinline__ int levels_wide(const TreeArgs &a, TreeLds &S, int b,
     }
     if (xl > 0) {
         if (tid == 0) {
-            a.n_expand[b] = 0;
-            a.state_n_exp[b] = xl << 8;
+            emit_nothing(a, b, xl, word);
             carry_head(a, b, xl, 0, tok_count);
         }
         return -1;
@@ -711,6 +554,7 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
     // done: four trees of a 70B step 13.2 -> 12.8 us, sixteen ragged ones 8.9 -> 8.6, one of (64, 7, 8) 7.6 -> 7.05.)
     const dt_params prm = a.params[b];
     int root = EXPAND ? 0 : a.root_token[b];
+    const u32 word = EXPAND ? (u32)a.state_n_exp[b] : 0u;
     int64_t row_begin = 0, row_end = 0;
     if (a.row_off) { row_begin = a.row_off[b]; row_end = a.row_off[b + 1]; }
     // what the level before has left, in the same trip
@@ -741,7 +585,7 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
     if constexpr (!EXPAND) asm volatile("" : "+s"(root));  // here: the compiler would move the load to the store
 
     if (xl > 0 && (TT == 1 || xl >= d)) {  // nothing is drafted below level d
-        if (tid == 0) { a.n_expand[b] = 0; a.state_n_exp[b] = xl << 8; }
+        if (tid == 0) emit_nothing(a, b, xl, word);
         return;
     }
     if (tid == 0 && xl == 0) {
@@ -810,15 +654,15 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = lane_id();
     int p_end = 0;
     if (k > NARROW_K) {
-        p_end = k * k <= TREE_NT ? levels_wide<1, EXPAND>(a, S, b, k, d, TT, from) : levels_wide<2, EXPAND>(a, S, b, k, d, TT, from);
+        p_end = k * k <= TREE_NT ? levels_wide<1, EXPAND>(a, S, b, k, d, TT, from, word) : levels_wide<2, EXPAND>(a, S, b, k, d, TT, from, word);
         if constexpr (EXPAND) return;
         __syncthreads();  // the levels may have ended without one
     } else {
         if (w == 0) {
-            if (k <= 8) p_end = levels_narrow<1, EXPAND>(a, S, b, k, d, TT, from);
-            else if (k <= 11) p_end = levels_narrow<2, EXPAND>(a, S, b, k, d, TT, from);
-            else if (k <= 13) p_end = levels_narrow<3, EXPAND>(a, S, b, k, d, TT, from);  // four per lane: (96, 8, 12) 10.8 us, 10.4 so
-            else p_end = levels_narrow<4, EXPAND>(a, S, b, k, d, TT, from);
+            if (k <= 8) p_end = levels_narrow<1, EXPAND>(a, S, b, k, d, TT, from, word);
+            else if (k <= 11) p_end = levels_narrow<2, EXPAND>(a, S, b, k, d, TT, from, word);
+            else if (k <= 13) p_end = levels_narrow<3, EXPAND>(a, S, b, k, d, TT, from, word);  // four per lane: (96, 8, 12) 10.8 us, 10.4 so
+            else p_end = levels_narrow<4, EXPAND>(a, S, b, k, d, TT, from, word);
             if (lane == 0) S.p_end = p_end;
         }
         if constexpr (EXPAND) return;

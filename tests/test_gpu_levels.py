@@ -189,6 +189,14 @@ def test_level_by_level_of_large_vocabularies(V, bf16):
     drive([(40, 3, 12), (1, 2, 2), (30, 4, 5), (9, 1, 4), (25, 2, 12), (33, 5, 3)], [5, 0, 9, 1000, 77, 3], V=V, bf16=bf16, seed=1)
 
 
+# a level's nodes chosen in the launch of its rows: every kernel of rows that does it, at the ends of its vocabularies; one and four candidates to a lane, and the
+# first width that has a launch of its own (17)
+@pytest.mark.parametrize("V,bf16", [(2048, True), (8192, True), (8193, False), (16384, True), (16385, False), (32769, True)])
+@pytest.mark.parametrize("k", [1, 8, 9, 16, 17])
+def test_levels_chosen_beside_their_rows(V, bf16, k):
+    drive([(60, 4, k), (1, 2, 2), (33, 3, max(1, k - 7)), (20, 1, k), (9, 2, 1)], [5, 0, 9, 1000, 77], V=V, bf16=bf16, seed=1)
+
+
 def test_level_by_level_of_launches_that_take_two_chunks_to_a_workgroup():
     # 33 sequences of 32 rows of 16 chunks, 16,896 in all, most of them of nodes that do not exist
     drive([(30, 3, 4)] * 7 + [(70, 3, 32)] + [(5, 2, 2)] * 25, list(range(33)), V=61441, bf16=True, seed=1)
