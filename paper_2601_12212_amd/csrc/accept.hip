@@ -182,62 +182,16 @@ __global__ __launch_bounds__(256) void node_sample_kernel(AcceptArgs a) {
 
 // The best (value, id) key of row g and, with SUM, its (max, sum exp((x - max) inv_t)), by one wave that holds the row, 8 to ROW_V_MAX
 // entries.  What row_argmax_kernel leaves for a row of one chunk, and as there.
-#define ROW_V_MAX 2048
 #define ACCEPT_WAVES 16
 template <bool BF16, bool SUM>
 __device__ __forceinline__ u64 wave_row(const AcceptArgs &a, int64_t g, float inv_t, float2 &ms) {
-    constexpr int NG = ROW_V_MAX / 512;
-    const int V = a.V, lane = lane_id();
+    constexpr int NG = ROW_NG;
+    const int V = a.V;
     uint4 raw[NG][2];
-#pragma unroll
-    for (int n = 0; n < NG; ++n) {
-        const int start = min(512 * n + 8 * lane, V - 8);  // a group that reaches past the end: the row's last eight
-        if (BF16) raw[n][0] = load16((const uint16_t *)a.target + g * a.row_stride + start);
-        else {
-            const float *p = (const float *)a.target + g * a.row_stride + start;
-            raw[n][0] = load16(p);
-            raw[n][1] = load16(p + 4);
-        }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    float x[NG][8], gmx[NG], mx = -INFINITY;
-#pragma unroll
-    for (int n = 0; n < NG; ++n) {
-        gmx[n] = -INFINITY;
-        if (n && 512 * n >= V) continue;  // uniform
-        const u32 lo[4] = {raw[n][0].x, raw[n][0].y, raw[n][0].z, raw[n][0].w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            if (BF16) {
-                x[n][2 * e] = __uint_as_float(lo[e] << 16);
-                x[n][2 * e + 1] = __uint_as_float(lo[e] & 0xFFFF0000u);
-            } else {
-                const u32 hi[4] = {raw[n][1].x, raw[n][1].y, raw[n][1].z, raw[n][1].w};
-                x[n][e] = __uint_as_float(lo[e]);
-                x[n][4 + e] = __uint_as_float(hi[e]);
-            }
-        }
-        if (512 * (n + 1) > V) {  // uniform
-            const int first = 512 * n + 8 * lane - min(512 * n + 8 * lane, V - 8);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) x[n][e] = e >= first ? x[n][e] : -INFINITY;
-        }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) gmx[n] = fmaxf(gmx[n], x[n][e]);
-        mx = fmaxf(mx, gmx[n]);
-    }
-    const float T = wave_max(mx);
-    if constexpr (SUM) {
-        const float cexp = 1.4426950408889634f * inv_t, nm = T == -INFINITY ? 0.f : -T * cexp;
-        float s = 0.f;
-#pragma unroll
-        for (int n = 0; n < NG; ++n) {
-            if (n && 512 * n >= V) continue;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) s += __builtin_amdgcn_exp2f(fmaf(x[n][e], cexp, nm));
-        }
-        ms = make_float2(T, wave_sum(s > 0.f ? s : 0.f));
-    }
+    wave_row_request<BF16>(a.target, g * a.row_stride, V, raw);
+    float x[NG][8], gmx[NG];
+    const float T = wave_max(wave_row_unpack<BF16>(V, raw, x, gmx));
+    if constexpr (SUM) ms = make_float2(T, wave_row_sum(V, x, T, inv_t));
     // the first group that holds the maximum, the first lane of that, the first such element
     u64 key = 0ull;
 #pragma unroll

@@ -266,10 +266,15 @@ int dt_build_tree(void *stream, int batch, const dt_params *params, const void *
     a.lane_max = rs.lane_max; a.part_ms = rs.ms;
     hipStream_t st = (hipStream_t)stream;
     (void)hipGetLastError();  // a stale error left by another HIP user of this process is not ours
-    hipError_t e = dt::rows_launch_topk(a, total_rows, top_val, top_id, lse, DT_K_MAX, st);
-    if (e != hipSuccess) return hip_fail(e);
-
+    hipError_t e = hipSuccess;
     dt::TreeArgs ta = {};
+    if (dt::tree_takes_rows(total_rows, batch, V)) {
+        ta.logits = draft_logits; ta.dtype = t; ta.row_stride = row_stride; ta.total_rows = (int)total_rows;
+    } else {
+        e = dt::rows_launch_topk(a, total_rows, top_val, top_id, lse, DT_K_MAX, st);
+        if (e != hipSuccess) return hip_fail(e);
+    }
+
     ta.batch = batch; ta.params = params; ta.V = V; ta.seq_rows = DT_STATE_ROWS; ta.root_token = root_token;
     ta.TT_cap = TT_cap; ta.top_val = top_val; ta.top_id = top_id; ta.lse = lse; ta.row_off = row_off;
     ta.early_stop = flags & DT_TREE_EARLY_STOP;

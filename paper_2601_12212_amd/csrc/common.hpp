@@ -178,6 +178,100 @@ __device__ __forceinline__ float philox_uniform(u64 seed, u64 step, u32 seq, u32
     return (float)(x >> 8) * (1.0f / 16777216.0f);
 }
 
+// ---- rows ---------------------------------------------------------------------------------------
+// smallest float whose ordered image has these upper 16 bits (the bin of -inf holds nothing else)
+__device__ __forceinline__ float key_edge(u32 k16) { return k16 <= 0x007Fu ? -INFINITY : unord32(k16 << 16); }
+// The k-th largest, or a key between it and the next, of the 16-bit keys that a wave holds, G to a lane (k <= 64).
+// Bisection between the worst and the best of the lanes' best keys (64 keys reach the worst), about four steps of a
+// hundred cycles (the exact k-th between fixed ends, counted pair by pair, was nine steps and 1,600 cycles of the 10,200 that
+// a workgroup took; 1,000 now).
+template <int G>
+__device__ __forceinline__ u32 wave_kth(const u32 (&ky)[G], int k) {
+    u32 best = ky[0];
+    if constexpr (G == 4) best = max(max(ky[0], ky[1]), max(ky[2], ky[3]));
+    static_assert(G == 1 || G == 4, "keys of a lane");
+    // Groups without an element (past the row's end, where a wave's last lanes may hold nothing else) do not set the bottom: from -inf
+    // on the bisection is sixteen steps (28 rows of 74,365, k = 28, 10.3 us a call, 9.7 so).
+    const bool some = best > 0x007Fu;
+    u32 hi = best, rest = some ? ~best : 0u;
+#define STEP(CTRL, ROWS)                                               \
+    hi = max(hi, (u32)dpp_mov<CTRL, ROWS>(0, (int)hi));                \
+    rest = max(rest, (u32)dpp_mov<CTRL, ROWS>(0, (int)rest));
+    STEP(0x111, 0xf) STEP(0x112, 0xf) STEP(0x114, 0xf) STEP(0x118, 0xf) STEP(0x142, 0xa) STEP(0x143, 0xc)
+#undef STEP
+    hi = (u32)__builtin_amdgcn_readlane((int)hi, 63);
+    // reached by k keys, hi + 1 by none
+    u32 lo = __popcll(__ballot(some)) >= k ? ~(u32)__builtin_amdgcn_readlane((int)rest, 63) : 0x007Fu;
+    while (hi > lo) {
+        const u32 mid = lo + ((hi - lo + 1u) >> 1);
+        const int n = count_above<G>(ky, mid - 1u);
+        if (n >= k) lo = mid;
+        else hi = mid - 1u;
+        if (n == k) break;
+    }
+    return lo;
+}
+// A row of 8 to ROW_V_MAX entries that one wave holds, groups of eight to a lane, 512 entries apart: asked for, and unpacked, with the groups' maxima and the
+// lane's.  A group that reaches past the row's end is its last eight entries, those before the group -inf; of groups behind the end there is only the maximum, -inf.
+#define ROW_V_MAX 2048
+#define ROW_NG (ROW_V_MAX / 512)
+__device__ __forceinline__ int row_group(int V, int n) { return min(512 * n + 8 * lane_id(), V - 8); }
+template <bool BF16>
+__device__ __forceinline__ void wave_row_request(const void *logits, int64_t at, int V, uint4 (&raw)[ROW_NG][2]) {
+#pragma unroll
+    for (int n = 0; n < ROW_NG; ++n) {
+        if (BF16) raw[n][0] = load16((const uint16_t *)logits + at + row_group(V, n));
+        else {
+            const float *p = (const float *)logits + at + row_group(V, n);
+            raw[n][0] = load16(p);
+            raw[n][1] = load16(p + 4);
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+}
+template <bool BF16>
+__device__ __forceinline__ float wave_row_unpack(int V, const uint4 (&raw)[ROW_NG][2], float (&x)[ROW_NG][8], float (&gmx)[ROW_NG]) {
+    float mx = -INFINITY;
+#pragma unroll
+    for (int n = 0; n < ROW_NG; ++n) {
+        gmx[n] = -INFINITY;
+        if (n && 512 * n >= V) continue;  // uniform
+        const u32 lo[4] = {raw[n][0].x, raw[n][0].y, raw[n][0].z, raw[n][0].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (BF16) {
+                x[n][2 * e] = __uint_as_float(lo[e] << 16);
+                x[n][2 * e + 1] = __uint_as_float(lo[e] & 0xFFFF0000u);
+            } else {
+                const u32 hi[4] = {raw[n][1].x, raw[n][1].y, raw[n][1].z, raw[n][1].w};
+                x[n][e] = __uint_as_float(lo[e]);
+                x[n][4 + e] = __uint_as_float(hi[e]);
+            }
+        }
+        if (512 * (n + 1) > V) {  // uniform
+            const int first = 512 * n + 8 * lane_id() - row_group(V, n);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[n][e] = e >= first ? x[n][e] : -INFINITY;
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) gmx[n] = fmaxf(gmx[n], x[n][e]);
+        mx = fmaxf(mx, gmx[n]);
+    }
+    return mx;
+}
+// Sum of exp((x - T) inv_t), T the row's maximum.
+__device__ __forceinline__ float wave_row_sum(int V, const float (&x)[ROW_NG][8], float T, float inv_t) {
+    const float cexp = 1.4426950408889634f * inv_t, nm = T == -INFINITY ? 0.f : -T * cexp;
+    float s = 0.f;
+#pragma unroll
+    for (int n = 0; n < ROW_NG; ++n) {
+        if (n && 512 * n >= V) continue;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s += __builtin_amdgcn_exp2f(fmaf(x[n][e], cexp, nm));
+    }
+    return wave_sum(s > 0.f ? s : 0.f);
+}
+
 // ---- words between the workgroups of a launch ----------------------------------------------------
 // They may sit on different XCDs, whose L2 caches are not coherent: relaxed atomics at agent scope go through to the memory side word by
 // word, where a fence would write back and drop the whole L2.  A load at agent scope finds what lies written in its own XCD's L2.

@@ -87,6 +87,10 @@ struct TreeArgs {
     float *score, *logp;
     unsigned long long *anc_mask;
     int64_t seq_rows;
+    const void *logits;     // one-shot build that reduces its rows itself (tree_takes_rows): as in RowArgs, rows of the launch
+    int dtype;
+    int64_t row_stride;
+    int total_rows;
     int early_stop;         // expansion also ends once the root and the candidates proposed so far number TT
     // level-at-a-time build
     int expand_level;       // 0: whole tree; l > 0: only the set of level-l nodes to expand
@@ -97,6 +101,7 @@ struct TreeArgs {
     int32_t *state_id;
 };
 hipError_t tree_init();  // once per device, before the first launch
+bool tree_takes_rows(int64_t total_rows, int batch, int V);
 hipError_t tree_launch(const TreeArgs &a, hipStream_t st);
 
 // -------------------------------------------------------------- attention (attention.hip)

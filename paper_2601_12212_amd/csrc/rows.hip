@@ -302,36 +302,6 @@ __device__ __forceinline__ int load_octet(const RowArgs &a, int64_t g, int id0, 
     for (int e = 0; e < 8; ++e) xv[e] = start + e >= max(id0, 0) ? xv[e] : -INFINITY;
     return start;
 }
-// smallest float whose ordered image has these upper 16 bits (the bin of -inf holds nothing else)
-__device__ __forceinline__ float key_edge(u32 k16) { return k16 <= 0x007Fu ? -INFINITY : unord32(k16 << 16); }
-// The k-th largest, or a key between it and the next, of the 256 16-bit keys held four to a lane (k <= 64).
-// Bisection between the worst and the best of the lanes' best keys (64 keys reach the worst), about four steps of a
-// hundred cycles (the exact k-th between fixed ends, counted pair by pair, was nine steps and 1,600 cycles of the 10,200 that
-// a workgroup took; 1,000 now).
-__device__ __forceinline__ u32 wave_kth_of_256(const u32 (&ky)[4], int k) {
-    const u32 best = max(max(ky[0], ky[1]), max(ky[2], ky[3]));
-    // Groups without an element (past the row's end, where a wave's last lanes may hold nothing else) do not set the bottom: from -inf
-    // on the bisection is sixteen steps (28 rows of 74,365, k = 28, 10.3 us a call, 9.7 so).
-    const bool some = best > 0x007Fu;
-    u32 hi = best, rest = some ? ~best : 0u;
-#define STEP(CTRL, ROWS)                                               \
-    hi = max(hi, (u32)dpp_mov<CTRL, ROWS>(0, (int)hi));                \
-    rest = max(rest, (u32)dpp_mov<CTRL, ROWS>(0, (int)rest));
-    STEP(0x111, 0xf) STEP(0x112, 0xf) STEP(0x114, 0xf) STEP(0x118, 0xf) STEP(0x142, 0xa) STEP(0x143, 0xc)
-#undef STEP
-    hi = (u32)__builtin_amdgcn_readlane((int)hi, 63);
-    // reached by k keys, hi + 1 by none
-    u32 lo = __popcll(__ballot(some)) >= k ? ~(u32)__builtin_amdgcn_readlane((int)rest, 63) : 0x007Fu;
-    while (hi > lo) {
-        const u32 mid = lo + ((hi - lo + 1u) >> 1);
-        const int n = count_above<4>(ky, mid - 1u);
-        if (n >= k) lo = mid;
-        else hi = mid - 1u;
-        if (n == k) break;
-    }
-    return lo;
-}
-
 // Candidates: of a thread's N elements those that reach T, value x(e), id id_of(e), behind the *n keys already in the list (past its end they
 // only count).  A bit for each hit and a loop over the bits, one as a rule, behind one LDS add: a branch and an add for each element, in
 // waves that run alone or wait for each other at the next barrier, cost a selection of k = 28 0.25 us and rows that a workgroup holds
@@ -643,7 +613,7 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl_, 
         __syncthreads();
         const uint2 k4 = ((const uint2 *)s_key)[lane];
         const u32 ky[4] = {k4.x & 0xFFFFu, k4.x >> 16, k4.y & 0xFFFFu, k4.y >> 16};
-        const u32 key0 = wave_kth_of_256(ky, k);
+        const u32 key0 = wave_kth<4>(ky, k);
         const float T0 = key_edge(key0);
 
         // ---- 2. the lanes that reach T, read again ------------------------------------------------------
@@ -908,7 +878,7 @@ __global__ __launch_bounds__(NT, NL == 4 ? 4 : 8) void row_topk_kernel(RowArgs a
 #pragma unroll
                 for (int j = i + 4; j < NW; j += 4) ky[i] = max(ky[i], (u32)kv[j]);
             }
-            T = key_edge(wave_kth_of_256(ky, k));
+            T = key_edge(wave_kth<4>(ky, k));
         }
         if constexpr (ONE) {
             if (w == 0) {
@@ -1131,7 +1101,7 @@ __global__ __launch_bounds__(1024, 8) void row_many_kernel(RowArgs a, float *top
             m = __builtin_elementwise_max(m, __builtin_bit_cast(us4, o));
         }
         const u32 ky[4] = {m.x, m.y, m.z, m.w};
-        const u32 t = wave_kth_of_256(ky, k);
+        const u32 t = wave_kth<4>(ky, k);
         if (lane == 0) s_T = key_edge(t);
     }
     __syncthreads();

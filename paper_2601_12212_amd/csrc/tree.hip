@@ -528,9 +528,97 @@ __device__ __forceinline__ int block_select(const float *score, int n, float top
     return total;
 }
 
-// EXPAND: one level's choice; otherwise the whole tree.  (Two kernels: what one of them does not do would be instructions to fetch and scalar
+// ---- rows of small trees ------------------------------------------------------------------------------------
+// The k best entries of a row that the wave holds, place(rank, value, token) by some lane for every rank below k (value -inf: there are no more), and its log-sum-exp.
+// As row_topk_kernel does it, with a slot to a lane: T, the k-th best of the lanes' best entries or little below, and the entries that reach it ranked one against the
+// other in `list`.
+#define ROW_LIST 64
+template <typename F>
+__device__ __forceinline__ float wave_row_topk(int V, int k, const float (&x)[ROW_NG][8], const float (&gmx)[ROW_NG], float mx, u64 *list, F place) {
+    const int lane = lane_id();
+    auto id_of = [&](int n, int e) { return row_group(V, n) + e; };
+    auto for_groups = [&](auto f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int n = 0; n < ROW_NG; ++n)
+            if (n == 0 || 512 * n < V) f(n);  // uniform
+    };
+    const u32 key16[1] = {ord32(mx) >> 16};
+    const float T = key_edge(wave_kth<1>(key16, k)), T1 = fmaxf(T, -__FLT_MAX__);  // -inf does not count
+    list[lane] = 0ull;
+    u32 hits = 0;  // bit 8 n + e: element e of group n
+    for_groups([&](int n) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) hits |= (x[n][e] >= T1 ? 1u : 0u) << (8 * n + e);
+    });
+    int n_hits = wave_sum_i32(__popc(hits));
+    if (n_hits > ROW_LIST) {
+        // Clusters or equal values: the k-th key by bisection, then, of the entries equal to it, the last id.
+        auto mask = [&](auto in) {
+            u32 m = 0;
+            for_groups([&](int n) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) m |= (in(x[n][e], id_of(n, e)) ? 1u : 0u) << (8 * n + e);
+            });
+            return m;
+        };
+        auto count = [&](u32 m) { return wave_sum_i32(__popc(m)); };
+        u32 lo = max(ord32(T1), 0x00800000u), hi = 0xFFFFFFFFu;  // at least k keys reach lo, or all there are; none lies above hi
+        int c = n_hits;
+        while (hi > lo && c > k) {
+            const u32 mid = lo + ((hi - lo) >> 1) + 1u;
+            const int m = count(mask([&](float v, int) { return ord32(v) >= mid; }));
+            if (m >= k) { lo = mid; c = m; }
+            else hi = mid - 1u;
+        }
+        int id_hi = 0x7FFFFFFF;  // of the entries equal to lo: those up to this id
+        if (c > k) {
+            const int need = k - count(mask([&](float v, int) { return ord32(v) > lo; }));
+            int id_lo = 0;  // the smallest id with `need` of them at or below it
+            id_hi = V - 1;
+            while (id_hi > id_lo) {
+                const int mid = (id_lo + id_hi) >> 1;
+                if (count(mask([&](float v, int id) { return ord32(v) == lo && id <= mid; })) >= need) id_hi = mid;
+                else id_lo = mid + 1;
+            }
+        }
+        hits = mask([&](float v, int id) { return ord32(v) > lo || (ord32(v) == lo && id <= id_hi); });
+        n_hits = count(hits);
+    }
+    const int own = __popc(hits);
+    int at = wave_scan_incl_i32(own) - own;
+    for_groups([&](int n) {
+        u32 left = hits >> (8 * n) & 0xFFu;
+        if (__builtin_amdgcn_ballot_w64(left != 0u))  // uniform
+            for (; left; left &= left - 1) {
+                const int e = __builtin_ctz(left);
+                float v = x[n][0];
+#pragma unroll
+                for (int j = 1; j < 8; ++j) v = e == j ? x[n][j] : v;
+                if (at < ROW_LIST) list[at] = make_key(v, (u32)id_of(n, e));
+                ++at;
+            }
+    });
+    const float M = wave_max(mx), sum = wave_row_sum(V, x, M, 1.0f);
+    __builtin_amdgcn_wave_barrier();
+    const u64 mine = list[lane];
+    int rank = 0;
+    for (int j0 = 0; j0 < n_hits; j0 += 8) {  // zeros behind the keys
+        u64 o[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) o[j] = list[j0 + j];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) rank += o[j] > mine ? 1 : 0;
+    }
+    if (lane < n_hits && rank < k) place(rank, key_val(mine), (int)key_idx(mine));
+    else if (lane >= n_hits && lane < k) place(lane, -INFINITY, -1);
+    return M == -INFINITY ? -INFINITY : M + __logf(sum);
+}
+
+// EXPAND: one level's choice; otherwise the whole tree.  (Kernels of their own: what one of them does not do would be instructions to fetch and scalar
 // registers spilled in the other's chain.)
-template <bool EXPAND>
+// ROWS: the rows are reduced here as well, a wave to a row (LOGITS_F32, LOGITS_BF16), in the place of a launch in front of this one.
+enum { NO_ROWS, LOGITS_F32, LOGITS_BF16 };
+template <bool EXPAND, int ROWS>
 __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
     const int b = blockIdx.x, tid = threadIdx.x;
     // Row results of sequence b: rows b * seq_rows .. (the same block layout for the one-shot build and
@@ -543,8 +631,11 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
     constexpr int EARLY = 6;  // entries per thread read ahead: rows 0 .. EARLY * TREE_NT / DT_K_MAX - 1
     float ev[EARLY], el[EARLY];
     int et[EARLY];
+    uint4 raw[ROW_NG][2];
+    const int row_wave = __builtin_amdgcn_readfirstlane(tid >> 6), early_row = min(row_wave, a.total_rows - 1);  // the first sequence's, as a rule the only one's
+    if constexpr (ROWS) wave_row_request<ROWS == LOGITS_BF16>(a.logits, early_row * a.row_stride, a.V, raw);
 #pragma unroll
-    for (int j = 0; j < EARLY; ++j) {
+    for (int j = 0; j < (ROWS ? 0 : EARLY); ++j) {
         const int e = tid + j * TREE_NT;  // entry (row e / 32, rank e % 32)
         ev[j] = tv[e];
         et[j] = ti[e];
@@ -628,11 +719,35 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
             S.tok[p] = token;
         }
     };
+    if constexpr (ROWS) {
+        for (int row = row_wave; row < R; row += TREE_NW) {
+            if (row < owned) {
+                const int64_t g = row_begin + row;
+                if (g != early_row) wave_row_request<ROWS == LOGITS_BF16>(a.logits, g * a.row_stride, a.V, raw);
+                float x[ROW_NG][8], gmx[ROW_NG];
+                const float mx = wave_row_unpack<ROWS == LOGITS_BF16>(a.V, raw, x, gmx);
+                float *const lp = S.lp + (row == 0 ? 0 : k + (row - 1) * k);
+                int *const tok = S.tok + (row == 0 ? 0 : k + (row - 1) * k);
+                const float row_lse = wave_row_topk(a.V, k, x, gmx, mx, (u64 *)S.cand + row_wave * ROW_LIST, [&](int rank, float v, int token) {
+                    lp[rank] = v;
+                    tok[rank] = token;
+                });
+                __builtin_amdgcn_wave_barrier();
+                if (lane_id() < k) {
+                    const float own = lp[lane_id()] - row_lse;
+                    lp[lane_id()] = own < INFINITY ? own : -INFINITY;
+                }
+            } else if (lane_id() < k) {
+                S.lp[k + (row - 1) * k + lane_id()] = -INFINITY;
+            }
+        }
+        static_assert(sizeof(S.cand) >= TREE_NW * ROW_LIST * sizeof(u64), "the waves' lists");
+    }
 #pragma unroll
-    for (int j = 0; j < EARLY; ++j) place(tid + j * TREE_NT, ev[j], et[j], el[j]);
+    for (int j = 0; j < (ROWS ? 0 : EARLY); ++j) place(tid + j * TREE_NT, ev[j], et[j], el[j]);
     // the other rows in one more trip
     constexpr int MORE = (DT_STATE_ROWS * DT_K_MAX + TREE_NT - 1) / TREE_NT - EARLY;
-    const int more = (R * DT_K_MAX + TREE_NT - 1) / TREE_NT - EARLY;
+    const int more = ROWS ? 0 : (R * DT_K_MAX + TREE_NT - 1) / TREE_NT - EARLY;
     if (more > 0) {
         float xv[MORE], xs[MORE];
         int xt[MORE];
@@ -804,15 +919,26 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
 
 // LDS beyond 64 KB has to be asked for, once per device (dt_init)
 hipError_t tree_init() {
-    hipError_t e = hipFuncSetAttribute((const void *)tree_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(TreeLds));
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)tree_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(TreeLds));
+    const void *const kernels[] = {(const void *)tree_kernel<false, NO_ROWS>, (const void *)tree_kernel<true, NO_ROWS>,
+                                   (const void *)tree_kernel<false, LOGITS_F32>, (const void *)tree_kernel<false, LOGITS_BF16>};
+    hipError_t e = hipSuccess;
+    for (const void *k : kernels)
+        if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(TreeLds));
     return e;
 }
 
+// Rows that a wave holds, few enough for a wave of the workgroup to each, whichever sequence has more than the one that all have: one launch in place of two.
+// us a step, two launches -> one, graph | eager: 5 rows of 1,024 fp32 entries 21.4 -> 19.5 | 18.0 -> 16.3, bf16 22.1 -> 20.2 | 18.5 -> 17.1; 7 of 2,048 22.4 -> 21.3 | 18.9 -> 18.0, bf16
+// 22.7 -> 21.8 | 19.2 -> 18.2; but two rows to a wave, 10 of 2,047 22.6 -> 23.0, 16 of 2,048 22.8 -> 24.3, bf16 23.1 -> 25.0.
+bool tree_takes_rows(int64_t total_rows, int batch, int V) { return total_rows - (batch - 1) <= TREE_NW && V >= 8 && V <= ROW_V_MAX; }
+
 hipError_t tree_launch(const TreeArgs &a, hipStream_t st) {
     if (a.batch <= 0) return hipSuccess;
-    launch_kernel(KID_TREE, st, a.expand_level > 0 ? tree_kernel<true> : tree_kernel<false>, dim3(a.batch), dim3(TREE_NT), sizeof(TreeLds), a);
+    auto go = [&](auto kernel) { launch_kernel(KID_TREE, st, kernel, dim3(a.batch), dim3(TREE_NT), sizeof(TreeLds), a); };
+    if (a.expand_level > 0) go(tree_kernel<true, NO_ROWS>);
+    else if (!a.logits) go(tree_kernel<false, NO_ROWS>);
+    else if (a.dtype == DT_BF16) go(tree_kernel<false, LOGITS_BF16>);
+    else go(tree_kernel<false, LOGITS_F32>);
     return hipGetLastError();
 }
 

@@ -291,6 +291,41 @@ def test_target_rows_that_the_acceptance_reduces(V, bf16, mode):
         assert torch.equal(st.node_argmax[0, :n].long().cpu(), torch.from_numpy(want))
 
 
+# Draft rows that the tree kernel reduces itself, a wave to a row: up to eight rows of 2,048 entries.  Against the general path, which a ninth row that belongs to no tree
+# selects; log-sum-exps of sums in another order differ by two ulp of 10 at most.  Rows whose best are more neighbours than a list holds, equal, few and none.
+@pytest.mark.parametrize("V", [8, 9, 63, 511, 513, 1024, 2047, 2048])
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("params", [[(16, 3, 3)], [(16, 2, 7)], [(30, 3, 3), (1, 2, 2)], [(20, 2, 32)]])
+def test_draft_rows_that_the_tree_kernel_reduces(V, bf16, params):
+    from paper_2601_12212_amd.step import Step
+    B, R = len(params), min(8, 1 + (params[0][1] - 1) * params[0][2])       # of 33 rows all but eight do not exist
+    total = R + B - 1
+    gen = torch.Generator("cuda").manual_seed(V + R)
+    x = torch.randn((total + 9, V), generator=gen, device="cuda") * 3
+    x[1, :min(V, 100)] += 20.0
+    x[2] = x[2].round()
+    x[3] = 1.0
+    x[4, 3:] = -float("inf")
+    x[5] = -float("inf")
+    got = []
+    for gap in (0, 1):
+        for n in (total, total + 9):
+            st = Step(params, [1] * B, 1, 1, 64, V, dtype=torch.bfloat16 if bf16 else torch.float32)
+            st.draft_logits, st.total_rows = torch.nn.functional.pad(x[:n].to(st.draft_logits.dtype), (0, gap), value=1e9)[:, :V], n
+            st.ws = torch.empty(dt_workspace_bytes(B, n, V, st.TT_cap, 1, 64), dtype=torch.uint8, device="cuda")
+            st.row_off.copy_(torch.tensor([0, R, total][:B + 1]))
+            st.root_token.fill_(1)
+            st.build_tree()
+            N = st.n_nodes.tolist()
+            got.append([st.n_nodes.clone()] + [t[b, :N[b]].clone() for b in range(B) for t in (st.tokens, st.parents, st.depth, st.src_row, st.anc_mask, st.score, st.logp)])
+    for other in got[1:]:
+        for u, v in zip(got[0], other):
+            if u.dtype == torch.float32:
+                assert torch.allclose(u, v, rtol=2e-6, atol=2e-6)
+            else:
+                assert torch.equal(u, v)
+
+
 def test_a_launch_of_more_threads_than_one_grid_dimension_takes():
     # 2^22 rows, each held by a workgroup of 1,024 threads; all but the tree's own rows belong to no tree (and are not read)
     from paper_2601_12212_amd.step import Step
