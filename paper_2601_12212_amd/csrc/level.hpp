@@ -69,14 +69,19 @@ __device__ __forceinline__ int level_note(u32 before, int level, int n) {
 // free until then.  Without it, or with another level's (a level asked for again), the levels before are gone through again, from the
 // row results.  (How many, in the same word as the level: the state's own word may have been a later level's since.)  Each level gone through again took 0.5 us with k up to 16 and 1.7 beyond.  All calls of a step, replayed: (60, 6, 10), 128,256 tokens
 // 78.2 -> 74.7 us (with the kernels of their own); 16 sequences of up to (123, 8, 23), 1,152 tokens 125.6 -> 101.7; 4 of (66, 3, 8) 32.0 -> 31.7.
+// Up to k = NARROW_K there is room for every level's, and the tree is finished from them where all are there: the candidates scored side by side in
+// place of a chain of levels.  A level that is chosen takes away what later ones have left.  (All calls, replayed, the chain | so: (60, 6, 10) 68.4 | 67.1 us, (96, 8, 12)
+// 90.0 | 85.9, 16 sequences of (60, 6, 16) 77.1 | 73.5.)
 #define CARRY_ROW (DT_STATE_ROWS - 4)  // four rows of values: DT_K_MAX Parents; two words of the ids
 #define CARRY_FROM 2  // level 1 expands the root's children: nothing to go through
 #define CARRY_LEVELS ((CARRY_ROW - 1) / DT_K_MAX)  // levels whose nodes' rows, at most l DT_K_MAX, end before it
+static_assert(1 + (DT_D_MAX - 1) * NARROW_K <= CARRY_ROW - 4 * (DT_D_MAX - 1), "rows of narrow levels end before all of these");
 static_assert(4 * DT_K_MAX * sizeof(float) == DT_K_MAX * sizeof(Parent), "four rows");
 #define CARRY_COUNT 0x3F0  // where the tag holds the number of nodes
-__device__ __forceinline__ int carry_tag(int level, int n_exp) { return 0x7A5C3000 | n_exp << 4 | level; }
+__device__ __forceinline__ int carry_tag(int level, int n_exp, int early_stop) { return 0x7A5C3000 | (early_stop ? 0x400 : 0) | n_exp << 4 | level; }
 static_assert(DT_D_MAX < 16 && DT_K_MAX <= CARRY_COUNT >> 4, "the tag's fields");
-__device__ __forceinline__ int64_t carry_at(int64_t seq_rows, int b) { return (b * seq_rows + CARRY_ROW) * DT_K_MAX; }
+__device__ __forceinline__ int64_t carry_at(int64_t seq_rows, int b, int level, bool narrow) { return (b * seq_rows + CARRY_ROW - (narrow ? 4 * level : 0)) * DT_K_MAX; }
+__device__ __forceinline__ bool carries(int level, bool narrow) { return narrow ? level >= 1 : level >= CARRY_FROM && level <= CARRY_LEVELS; }
 // The level to start from, its nodes and the token count: level 0, nothing.
 struct Start {
     int level, n_exp, tok_count;
@@ -143,15 +148,18 @@ __device__ __forceinline__ void level_bounds(u32 fk, int k, u32 &lo, u32 &hi) {
     lo = __popcll(__builtin_amdgcn_ballot_w64(viable)) == k ? ~(u32)__builtin_amdgcn_readlane((int)y, 31) - 1u : KEY_NEG_INF;
 }
 // The head of what level l hands on, by one thread.
-__device__ __forceinline__ void carry_head(const TreeArgs &a, int b, int l, int n_exp, int tok_count) {
-    if (l >= CARRY_FROM && l <= CARRY_LEVELS) *(int2 *)(a.state_id + carry_at(a.seq_rows, b)) = make_int2(carry_tag(l, n_exp), tok_count);
+__device__ __forceinline__ void carry_head(const TreeArgs &a, int b, int l, int k, int n_exp, int tok_count) {
+    const bool narrow = k <= NARROW_K;
+    if (carries(l, narrow)) *(int2 *)(a.state_id + carry_at(a.seq_rows, b, l, narrow)) = make_int2(carry_tag(l, n_exp, a.early_stop), tok_count);
+    if (narrow)
+        for (int j = l + 1; j < DT_D_MAX; ++j) a.state_id[carry_at(a.seq_rows, b, j, true)] = 0;
 }
 // What the draft model is handed for its next pass, by one wave: node s of the set chosen at level l, node(s, token).
 template <typename F>
 __device__ __forceinline__ void emit_level(const TreeArgs &a, int b, int l, int k, int n_exp, int tok_count, u32 before, int prefix, F node) {
     const int lane = lane_id();
-    const bool carry = l >= CARRY_FROM && l <= CARRY_LEVELS;
-    const int64_t at = carry_at(a.seq_rows, b);
+    const bool carry = carries(l, k <= NARROW_K);
+    const int64_t at = carry_at(a.seq_rows, b, l, k <= NARROW_K);
     if (lane < n_exp) {
         int token;
         const Parent pr = node(lane, token);
@@ -177,7 +185,7 @@ __device__ __forceinline__ void emit_level(const TreeArgs &a, int b, int l, int 
     if (lane == 0) {
         a.n_expand[b] = n_exp;
         a.state_n_exp[b] = level_note(before, l, n_exp);
-        carry_head(a, b, l, n_exp, tok_count);
+        carry_head(a, b, l, k, n_exp, tok_count);
     }
 }
 
@@ -267,7 +275,7 @@ __device__ __forceinline__ bool level_await(const LevelTail &h, int b, int rows,
 __device__ __forceinline__ LevelIn level_in(const TreeArgs &a, int rows, int b, int lane) {
     LevelIn in;
     const int xl = a.expand_level;
-    const int64_t at = carry_at(a.seq_rows, b), r0 = (int64_t)b * a.seq_rows;
+    const int64_t at = carry_at(a.seq_rows, b, max(xl - 1, 1), true), r0 = (int64_t)b * a.seq_rows;
     const dt_params prm = a.params[b];
     in.word = (u32)a.state_n_exp[b];
     in.prefix = a.prefix_len ? a.prefix_len[b] : 0;
@@ -281,7 +289,7 @@ __device__ __forceinline__ LevelIn level_in(const TreeArgs &a, int rows, int b, 
     in.k = min(max(prm.k, 1), min(DT_K_MAX, a.V));
     const int last = level_count(in.word, xl - 1);
     in.rows = min(xl == 1 ? 1 : last >= 0 ? min(last, in.k) : in.k, rows);
-    in.carried = xl > CARRY_FROM && (head.x & ~CARRY_COUNT) == carry_tag(xl - 1, 0);
+    in.carried = xl > 1 && (head.x & ~CARRY_COUNT) == carry_tag(xl - 1, 0, a.early_stop);
     in.n_exp = min((head.x & CARRY_COUNT) >> 4, in.k);
     in.tok_count = head.y;
     return in;
@@ -377,7 +385,7 @@ __device__ __forceinline__ void level_expand(const LevelTail &h, LevelLds &L, in
         });
     } else if (lane == 0) {
         emit_nothing(a, b, xl, in.word);
-        carry_head(a, b, xl, 0, tok_count);
+        carry_head(a, b, xl, k, 0, tok_count);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     if (lane <= LEVEL_CLAIM) put_agent(h.words + (int64_t)b * LEVEL_WORDS + lane, 0);

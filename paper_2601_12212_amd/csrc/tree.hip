@@ -256,7 +256,7 @@ __device__ __forceinline__ int levels_narrow(const TreeArgs &a, TreeLds &S, int 
     if (xl > 0) {  // an earlier level had nothing viable to expand, or the token count ended the expansion
         if (lane == 0) {
             emit_nothing(a, b, xl, word);
-            carry_head(a, b, xl, 0, tok_count);
+            carry_head(a, b, xl, k, 0, tok_count);
         }
         return -1;
     }
@@ -393,7 +393,7 @@ __device__ __forceinline__ int levels_wide(const TreeArgs &a, TreeLds &S, int b,
     if (xl > 0) {
         if (tid == 0) {
             emit_nothing(a, b, xl, word);
-            carry_head(a, b, xl, 0, tok_count);
+            carry_head(a, b, xl, k, 0, tok_count);
         }
         return -1;
     }
@@ -650,12 +650,20 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
     if (a.row_off) { row_begin = a.row_off[b]; row_end = a.row_off[b + 1]; }
     // what the level before has left, in the same trip
     const int xl = EXPAND ? a.expand_level : 0;  // > 0: only the nodes of level xl that are expanded next
-    int2 head = make_int2(0, 0);
-    uint4 node = make_uint4(0, 0, 0, 0);
-    if (xl > CARRY_FROM) {
-        const int64_t at = carry_at(a.seq_rows, b);
+    int2 head = make_int2(0, 0), narrow_head = make_int2(0, 0);
+    uint4 node = make_uint4(0, 0, 0, 0), narrow_node = make_uint4(0, 0, 0, 0);
+    if (xl > 1) {
+        const int64_t at = carry_at(a.seq_rows, b, xl - 1, false), narrow_at = carry_at(a.seq_rows, b, xl - 1, true);
         head = *(const int2 *)(a.top_id + at);
         node = ((const uint4 *)(a.top_val + at))[tid & (DT_K_MAX - 1)];
+        narrow_head = *(const int2 *)(a.top_id + narrow_at);
+        narrow_node = ((const uint4 *)(a.top_val + narrow_at))[tid & (DT_K_MAX - 1)];
+    }
+    // or all levels have left: lane l - 1 of every wave the head of level l's, thread 16 (l - 1) + s its node s
+    const bool finish = !EXPAND && !ROWS && !a.row_off;
+    if (finish) {
+        narrow_head = *(const int2 *)(a.top_id + carry_at(a.seq_rows, b, min((tid & 63) + 1, DT_D_MAX - 1), true));
+        narrow_node = ((const uint4 *)(a.top_val + carry_at(a.seq_rows, b, min(tid / NARROW_K + 1, DT_D_MAX - 1), true)))[tid % NARROW_K];
     }
     extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];  // 135 KB: more than a static array may hold
     TreeLds &S = *reinterpret_cast<TreeLds *>(s_dyn);
@@ -699,8 +707,12 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
     // Entry (row, rank) with rank < k is candidate p = rank (row 0) or k + (row - 1) k + rank.
     const int R = xl > 0 ? 1 + (xl - 1) * k : 1 + (d - 1) * k;  // rows that hold candidates
     Start from = {0, 0, 0};
+    if (EXPAND && k <= NARROW_K) {
+        head = narrow_head;
+        node = narrow_node;
+    }
     const int tag = __builtin_amdgcn_readfirstlane(head.x);
-    if (xl > CARRY_FROM && (tag & ~CARRY_COUNT) == carry_tag(xl - 1, 0))
+    if (carries(xl - 1, k <= NARROW_K) && (tag & ~CARRY_COUNT) == carry_tag(xl - 1, 0, a.early_stop))
         from = {xl - 1, min((tag & CARRY_COUNT) >> 4, k), __builtin_amdgcn_readfirstlane(head.y)};
     if (from.level > 0 && tid < DT_K_MAX) {
         if (tid >= from.n_exp) node.x = __float_as_uint(-INFINITY);
@@ -763,12 +775,37 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
         for (int j = 0; j < MORE; ++j)
             if (j < more && (EARLY + j + 1) * TREE_NT > R0 * DT_K_MAX) place(tid + (EARLY + j) * TREE_NT, xv[j], xt[j], xs[j]);
     }
+    int levels = -1;  // whose nodes are known
+    if (finish && k <= NARROW_K) {
+        const int l = (tid & 63) + 1, n = (narrow_head.x & CARRY_COUNT) >> 4;
+        const bool there = l < DT_D_MAX && (narrow_head.x & ~CARRY_COUNT) == carry_tag(l, 0, a.early_stop) && n <= k;
+        const u64 ok = __builtin_amdgcn_ballot_w64(there), last = __builtin_amdgcn_ballot_w64(there && n == 0) | 1ull << (d - 1);
+        const int up_to = __builtin_ctzll(last);  // levels with nodes; the one behind them has none, or is the deepest
+        const u64 needed = (2ull << min(up_to, max(d - 2, 0))) - 1ull;
+        if (d == 1 || (ok & needed) == needed) levels = up_to;
+        const int of = tid / NARROW_K + 1, mine = __shfl(n, of - 1);
+        if (of <= levels) {
+            if (tid % NARROW_K >= mine) narrow_node.x = __float_as_uint(-INFINITY);
+            *(uint4 *)&S.par[of][tid % NARROW_K] = narrow_node;
+        }
+    }
     __syncthreads();
 
     // ---- expansion -------------------------------------------------------------------------------
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = lane_id();
     int p_end = 0;
-    if (k > NARROW_K) {
+    if (levels >= 0) {  // uniform
+        p_end = k + levels * k * k;
+        const int of = tid / NARROW_K + 1;
+        const Parent own = __builtin_bit_cast(Parent, narrow_node);
+        if (of <= levels && own.score > -INFINITY) S.slot[min(max(own.index, 0), DT_P_MAX - 1)] = (int8_t)(tid % NARROW_K);
+        const PoolShape ps = pool_shape(k);
+        for (int p = tid; p < p_end; p += TREE_NT) {
+            const Decoded dc = decode(p, ps);
+            S.score[p] = p < k ? S.lp[p] : S.par[dc.level - 1][dc.slot].score + S.lp[p];
+        }
+        __syncthreads();
+    } else if (k > NARROW_K) {
         p_end = k * k <= TREE_NT ? levels_wide<1, EXPAND>(a, S, b, k, d, TT, from, word) : levels_wide<2, EXPAND>(a, S, b, k, d, TT, from, word);
         if constexpr (EXPAND) return;
         __syncthreads();  // the levels may have ended without one

@@ -31,9 +31,9 @@ def few_viable(seed, string, V):
     return row
 
 
-def drive(params, prefix_len, V, bf16, seed, flags=0, twice=False, rows=toy_logits_3, again={}, state=None, other=False):
+def drive(params, prefix_len, V, bf16, seed, flags=0, twice=False, rows=toy_logits_3, again={}, state=None, other=False, last=0):
     """again: levels; behind each one's call the calls from that many levels back on are made again, with the same logits.  other: and that level's
-    first call has other logits.  Returns the numbers of
+    first call has other logits.  last: that level's call is made again before the tree is finished.  Returns the numbers of
     nodes of every level, sequence by sequence."""
     import paper_2601_12212_amd as dt
     B = len(params)
@@ -90,6 +90,8 @@ def drive(params, prefix_len, V, bf16, seed, flags=0, twice=False, rows=toy_logi
                                         pos=e_pos[b, :n].cpu().numpy(),
                                         mask=e_mask[b, :n].cpu().numpy().view(np.uint64))
     # finish
+    if last:
+        dt.dt_expand_level(last, d_params, given[last].contiguous(), KR, d_plen, TT_cap, state, n_exp, e_tok, e_par, e_row, e_pos, e_mask, ws, flags=flags)
     n_nodes = torch.zeros(B, **i32)
     mk = lambda dtype: torch.zeros((B, TT_cap), dtype=dtype, device="cuda")
     tokens, parents, depth, src_row = mk(torch.int32), mk(torch.int32), mk(torch.int32), mk(torch.int32)
@@ -180,6 +182,16 @@ def test_levels_asked_for_again_with_other_logits(k, seed, back):
     # the call that counts finds every node's row, also where a call between has chosen fewer nodes than the level before, the last level's among them
     for level in range(2, 9):
         drive([(TT, d, k) for TT, d in FEW], [5, 0, 9], V=300, bf16=False, seed=seed, rows=few_viable, again={level: back}, other=True)
+
+
+@pytest.mark.parametrize("last", [1, 2, 5, 7, 8])
+@pytest.mark.parametrize("k,seed,few", [(3, 1, False), (16, 1, False), (17, 1, False), (4, 1, True), (12, 2, True), (20, 1, True)])
+def test_a_tree_finished_behind_a_level_asked_for_again(k, seed, few, last):
+    # what later levels have left does not follow from that one any more; the last one's does
+    if few:
+        drive([(TT, d, k) for TT, d in FEW], [5, 0, 9], V=300, bf16=False, seed=seed, rows=few_viable, last=min(last, 7))
+    else:
+        drive([(100, 8, k), (37, 8, max(2, k - 3)), (9, 2, 4), (5, 1, 2)], [5, 0, 9, 1], V=300, bf16=False, seed=seed, last=last)
 
 
 # vocabularies of both row paths: held by 1,024 threads with the log-sum-exps apart, two passes of one chunk to a workgroup;
