@@ -616,10 +616,12 @@ __device__ __forceinline__ float wave_row_topk(int V, int k, const float (&x)[RO
 
 // EXPAND: one level's choice; otherwise the whole tree.  (Kernels of their own: what one of them does not do would be instructions to fetch and scalar
 // registers spilled in the other's chain.)
-// ROWS: the rows are reduced here as well, a wave to a row (LOGITS_F32, LOGITS_BF16), in the place of a launch in front of this one.
-enum { NO_ROWS, LOGITS_F32, LOGITS_BF16 };
-template <bool EXPAND, int ROWS>
+// FROM: whose rows have been reduced: the launch's before (ONE_SHOT), level by level (LEVELS); or reduced here, a wave to a row (LOGITS_F32, LOGITS_BF16), in
+// the place of a launch in front of this one.  (The finish of a tree built level by level in the kernel of the one-shot build cost that 0.7 us of 7.6, k = 27.)
+enum { ONE_SHOT, LEVELS, LOGITS_F32, LOGITS_BF16 };
+template <bool EXPAND, int FROM>
 __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
+    constexpr bool ROWS = FROM == LOGITS_F32 || FROM == LOGITS_BF16, FINISH = !EXPAND && FROM == LEVELS;
     const int b = blockIdx.x, tid = threadIdx.x;
     // Row results of sequence b: rows b * seq_rows .. (the same block layout for the one-shot build and
     // the level-at-a-time state), so nothing about them depends on the sequence's parameters.  The first
@@ -633,7 +635,7 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
     int et[EARLY];
     uint4 raw[ROW_NG][2];
     const int row_wave = __builtin_amdgcn_readfirstlane(tid >> 6), early_row = min(row_wave, a.total_rows - 1);  // the first sequence's, as a rule the only one's
-    if constexpr (ROWS) wave_row_request<ROWS == LOGITS_BF16>(a.logits, early_row * a.row_stride, a.V, raw);
+    if constexpr (ROWS) wave_row_request<FROM == LOGITS_BF16>(a.logits, early_row * a.row_stride, a.V, raw);
 #pragma unroll
     for (int j = 0; j < (ROWS ? 0 : EARLY); ++j) {
         const int e = tid + j * TREE_NT;  // entry (row e / 32, rank e % 32)
@@ -660,8 +662,7 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
         narrow_node = ((const uint4 *)(a.top_val + narrow_at))[tid & (DT_K_MAX - 1)];
     }
     // or all levels have left: lane l - 1 of every wave the head of level l's, thread 16 (l - 1) + s its node s
-    const bool finish = !EXPAND && !ROWS && !a.row_off;
-    if (finish) {
+    if constexpr (FINISH) {
         narrow_head = *(const int2 *)(a.top_id + carry_at(a.seq_rows, b, min((tid & 63) + 1, DT_D_MAX - 1), true));
         narrow_node = ((const uint4 *)(a.top_val + carry_at(a.seq_rows, b, min(tid / NARROW_K + 1, DT_D_MAX - 1), true)))[tid % NARROW_K];
     }
@@ -735,9 +736,9 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
         for (int row = row_wave; row < R; row += TREE_NW) {
             if (row < owned) {
                 const int64_t g = row_begin + row;
-                if (g != early_row) wave_row_request<ROWS == LOGITS_BF16>(a.logits, g * a.row_stride, a.V, raw);
+                if (g != early_row) wave_row_request<FROM == LOGITS_BF16>(a.logits, g * a.row_stride, a.V, raw);
                 float x[ROW_NG][8], gmx[ROW_NG];
-                const float mx = wave_row_unpack<ROWS == LOGITS_BF16>(a.V, raw, x, gmx);
+                const float mx = wave_row_unpack<FROM == LOGITS_BF16>(a.V, raw, x, gmx);
                 float *const lp = S.lp + (row == 0 ? 0 : k + (row - 1) * k);
                 int *const tok = S.tok + (row == 0 ? 0 : k + (row - 1) * k);
                 const float row_lse = wave_row_topk(a.V, k, x, gmx, mx, (u64 *)S.cand + row_wave * ROW_LIST, [&](int rank, float v, int token) {
@@ -776,7 +777,7 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
             if (j < more && (EARLY + j + 1) * TREE_NT > R0 * DT_K_MAX) place(tid + (EARLY + j) * TREE_NT, xv[j], xt[j], xs[j]);
     }
     int levels = -1;  // whose nodes are known
-    if (finish && k <= NARROW_K) {
+    if (FINISH && k <= NARROW_K) {
         const int l = (tid & 63) + 1, n = (narrow_head.x & CARRY_COUNT) >> 4;
         const bool there = l < DT_D_MAX && (narrow_head.x & ~CARRY_COUNT) == carry_tag(l, 0, a.early_stop) && n <= k;
         const u64 ok = __builtin_amdgcn_ballot_w64(there), last = __builtin_amdgcn_ballot_w64(there && n == 0) | 1ull << (d - 1);
@@ -794,7 +795,7 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
     // ---- expansion -------------------------------------------------------------------------------
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = lane_id();
     int p_end = 0;
-    if (levels >= 0) {  // uniform
+    if (FINISH && levels >= 0) {  // uniform
         p_end = k + levels * k * k;
         const int of = tid / NARROW_K + 1;
         const Parent own = __builtin_bit_cast(Parent, narrow_node);
@@ -956,7 +957,7 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
 
 // LDS beyond 64 KB has to be asked for, once per device (dt_init)
 hipError_t tree_init() {
-    const void *const kernels[] = {(const void *)tree_kernel<false, NO_ROWS>, (const void *)tree_kernel<true, NO_ROWS>,
+    const void *const kernels[] = {(const void *)tree_kernel<false, ONE_SHOT>, (const void *)tree_kernel<false, LEVELS>, (const void *)tree_kernel<true, LEVELS>,
                                    (const void *)tree_kernel<false, LOGITS_F32>, (const void *)tree_kernel<false, LOGITS_BF16>};
     hipError_t e = hipSuccess;
     for (const void *k : kernels)
@@ -972,8 +973,9 @@ bool tree_takes_rows(int64_t total_rows, int batch, int V) { return total_rows -
 hipError_t tree_launch(const TreeArgs &a, hipStream_t st) {
     if (a.batch <= 0) return hipSuccess;
     auto go = [&](auto kernel) { launch_kernel(KID_TREE, st, kernel, dim3(a.batch), dim3(TREE_NT), sizeof(TreeLds), a); };
-    if (a.expand_level > 0) go(tree_kernel<true, NO_ROWS>);
-    else if (!a.logits) go(tree_kernel<false, NO_ROWS>);
+    if (a.expand_level > 0) go(tree_kernel<true, LEVELS>);
+    else if (!a.row_off) go(tree_kernel<false, LEVELS>);
+    else if (!a.logits) go(tree_kernel<false, ONE_SHOT>);
     else if (a.dtype == DT_BF16) go(tree_kernel<false, LOGITS_BF16>);
     else go(tree_kernel<false, LOGITS_F32>);
     return hipGetLastError();
