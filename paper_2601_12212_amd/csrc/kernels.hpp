@@ -33,7 +33,7 @@ inline unsigned long long launch_tag() {
 }
 
 // ------------------------------------------------------------------ row kernels (rows.hip)
-enum RowMode { ROWS_UNIFORM = 0, ROWS_DRAFT = 1, ROWS_TARGET = 2, ROWS_LEVEL = 3 };
+enum RowMode { ROWS_UNIFORM = 0, ROWS_DRAFT = 1, ROWS_TARGET = 2, ROWS_LEVEL = 3, ROWS_CHOOSE = 4 };  // ROWS_CHOOSE: a level's, by kernels that choose its nodes, too
 #define DT_STATE_ROWS (1 + (DT_D_MAX - 1) * DT_K_MAX)  // draft rows a sequence can own
 
 struct TreeArgs;

@@ -211,7 +211,7 @@ __device__ __forceinline__ void emit_nothing(const TreeArgs &a, int b, int l, u3
 #define LEVEL_CLAIM (2 * NARROW_K + 1)
 struct LevelTail {
     TreeArgs t;
-    u64 *words;     // [batch, LEVEL_WORDS]; null: the launch is of rows only
+    u64 *words;     // [batch, LEVEL_WORDS]
     u64 tag;
     int first_wg;   // of the workgroups that wait
     int rows;       // rows of a sequence in the launch

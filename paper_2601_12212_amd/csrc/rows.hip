@@ -23,7 +23,7 @@ struct RowMeta {
     bool valid;
     int k;
     int64_t out;  // row index of the results (top-k values, ids, lse)
-    int seq, slot, rows;  // ROWS_LEVEL: the sequence, which of its rows, how many are reduced
+    int seq, slot, rows;  // ROWS_LEVEL, ROWS_CHOOSE: the sequence, which of its rows, how many are reduced
     bool expands;         // and whether its level is to be chosen
 };
 
@@ -33,7 +33,7 @@ __device__ __forceinline__ RowMeta row_meta(const RowArgs &a, int64_t g) {
     m.valid = true;
     m.k = a.k_uniform;
     m.out = g;
-    if constexpr (MODE == ROWS_LEVEL) {
+    if constexpr (MODE == ROWS_LEVEL || MODE == ROWS_CHOOSE) {
         // level-at-a-time build: row s of sequence b in this call is the row of the s-th node expanded
         // one level up (level 1: the root's row); its results go to the sequence's row slot in the state
         const int b = (int)((u32)g / (u32)a.rows_per_seq), s = (int)((u32)g % (u32)a.rows_per_seq);  // fewer than 2^31 rows
@@ -379,13 +379,15 @@ __device__ __forceinline__ LaneMax<BF16> lane_max_at(const LaneMax<BF16> *lm, in
     else return lm[i];
 }
 // ---- rows of a level whose nodes are chosen in the same launch ----
+// (ROWS_CHOOSE, kernels of their own: where the level's nodes are chosen by a launch behind it, two sequences of up to (83, 6, 31) and 16,640 entries, the tail's
+// test and stores to the memory side cost a launch of rows 6.99 -> 7.57 us.)
 struct NoTail {};
 template <int MODE>
-using Tail = std::conditional_t<MODE == ROWS_LEVEL, LevelTail, NoTail>;
+using Tail = std::conditional_t<MODE == ROWS_CHOOSE, LevelTail, NoTail>;
 // A row's results, which another workgroup of the launch may read.
 template <int MODE, typename T>
 __device__ __forceinline__ void put_result(T *p, T v) {
-    if constexpr (MODE == ROWS_LEVEL) put32_agent(p, v);
+    if constexpr (MODE == ROWS_CHOOSE) put32_agent(p, v);
     else *p = v;
 }
 // The tail's arguments, at `offset` of the kernel's.  Read from there and not as the argument that it is: its twenty pointers would be asked for
@@ -405,9 +407,9 @@ __device__ __forceinline__ LevelLds &level_lds() {
 // The end of a row's workgroup.
 template <int MODE, size_t OFFSET>
 __device__ __forceinline__ void level_row_end(const RowMeta &meta, bool lse_wg) {
-    if constexpr (MODE == ROWS_LEVEL) {
+    if constexpr (MODE == ROWS_CHOOSE) {
+        if (!meta.expands) return;
         const LevelTail &tail = tail_at(OFFSET);
-        if (!tail.words || !meta.expands) return;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if (threadIdx.x >= 64) return;
@@ -419,7 +421,7 @@ __device__ __forceinline__ void level_row_end(const RowMeta &meta, bool lse_wg) 
 // True for the workgroups that wait for a sequence's rows, which have then done so; wg: the workgroup's number.
 template <int MODE, size_t OFFSET>
 __device__ __forceinline__ bool level_waits(const Tail<MODE> &arg, u32 wg) {
-    if constexpr (MODE == ROWS_LEVEL) {
+    if constexpr (MODE == ROWS_CHOOSE) {
         if (wg >= (u32)arg.first_wg) {
             const LevelTail &tail = tail_at(OFFSET);
             const int b = (int)(wg - (u32)tail.first_wg);
@@ -433,14 +435,14 @@ __device__ __forceinline__ bool level_waits(const Tail<MODE> &arg, u32 wg) {
 // PASS: the maxima are made in the same launch, in chunks of 2,048 PASS entries, up to 16 of them.  0: by the launch before.
 // Both passes in one launch: workgroups of the stream, and one to a row that waits for the row's chunks and selects.  Between two launches lie the first one's end, the
 // second's start, its arguments and its rows' metadata; here the maxima go through the L2 of the XCD that has the row, in three trips of 0.4 us (written, offered, read),
-// and what is read again comes from there as well, since the stream asks for it to stay.  51 rows of 128,256 bf16 entries, from memory: elements there after 2.1 us on average
+// and what is read again mostly comes from there as well.  51 rows of 128,256 bf16 entries, from memory: elements there after 2.1 us on average
 // (3.2 the last), their maxima 0.5 later, all of a row's at its selecting workgroup after 4.0, bound 1.6 later, hits 1.1, end 0.5.  (As many of
 // a row's entries to a workgroup as it can hold, each finding its own k best, and lists of those merged: 11.7 us a call against 9.6 in two launches: 16
 // waves take 1.7 us to their bound, and the merge 2.7.)
 // (eight waves per SIMD: left alone the compiler takes 76 registers in one mode, 29.3 us for 64 sequences instead of 26.3)
 template <int MODE, bool BF16, int PASS>
 __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl_, int S, float *top_val, int32_t *top_id, float *lse, int out_stride, u64 tag, Tail<MODE> tail) {
-    constexpr bool SAME = PASS > 0;
+    constexpr bool SAME = PASS > 0, KEEP = SAME && MODE == ROWS_UNIFORM;
     if constexpr (SAME)
         if (level_waits<MODE, offsetof(SelectArgs, tail)>(tail, blockIdx.y * gridDim.x + blockIdx.x)) return;
     const int nl = SAME ? PASS : nl_;
@@ -466,7 +468,7 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl_, 
             constexpr int EC = 8 * PASS;
             const int base = c * (256 * EC) + w * (64 * EC) + lane * 8 - row_shift(a.logits, BF16, a.V, a.row_stride, g);
             RawChunk<PASS, BF16> raw;
-            chunk_request<PASS, BF16, true, true>(a, g, base, raw);
+            chunk_request<PASS, BF16, true, KEEP>(a, g, base, raw);
             meta = row_meta<MODE>(a, g);
             if (!meta.valid) return;
             float x[EC];
@@ -574,7 +576,7 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl_, 
     };
     auto reread = [&](int i, int n, float T) {
         float xv[8];
-        const int start = load_octet<BF16, SAME>(a, g, octet_of(i, n), xv);
+        const int start = load_octet<BF16, KEEP>(a, g, octet_of(i, n), xv);
         keep_hits<8>([&](int e) { return xv[e]; }, [&](int e) { return start + e; }, T, &s_n2, s_fin);
     };
     // candidate t ranks itself against all n2 keys (LDS broadcasts, eight in flight)
@@ -646,8 +648,8 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl_, 
                     for (int q = lane; q < total >> 1; q += 64) {
                         float x[2][8];
                         const int i = list[q >> pairs_log2], n = 2 * (q & mask);
-                        const int s0 = load_octet<BF16, SAME>(a, g, octet_of(i, n), x[0]);
-                        const int s1 = load_octet<BF16, SAME>(a, g, octet_of(i, n + 1), x[1]);
+                        const int s0 = load_octet<BF16, KEEP>(a, g, octet_of(i, n), x[0]);
+                        const int s1 = load_octet<BF16, KEEP>(a, g, octet_of(i, n + 1), x[1]);
                         keep_hits<16>([&](int e) { return x[e >> 3][e & 7]; }, [&](int e) { return (e < 8 ? s0 : s1 - 8) + e; }, T0, &s_n2, s_fin);
                     }
                 }
@@ -760,8 +762,8 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl_, 
             u32 todo = 0;
             if (q < total && (listed || lane_val(i) >= T1)) {
                 const int m = 2 * (q & ((1 << pairs_log2) - 1));
-                s0 = load_octet<BF16, SAME>(a, g, octet_of(i, m), x[0]);
-                s1 = load_octet<BF16, SAME>(a, g, octet_of(i, m + 1), x[1]);
+                s0 = load_octet<BF16, KEEP>(a, g, octet_of(i, m), x[0]);
+                s1 = load_octet<BF16, KEEP>(a, g, octet_of(i, m + 1), x[1]);
 #pragma unroll
                 for (int e = 0; e < 16; ++e)
                     todo |= (make_key(x[e >> 3][e & 7], (u32)((e < 8 ? s0 : s1 - 8) + e)) >= threshold ? 1u : 0u) << e;
@@ -1380,6 +1382,14 @@ static void by_mode_and_type(const RowArgs &a, F f) {
     else if (a.mode == ROWS_LEVEL) typed(integral_constant<int, ROWS_LEVEL>());
     else typed(integral_constant<int, ROWS_UNIFORM>());
 }
+// the same for launches that may choose a level's nodes
+template <typename F>
+static void by_mode_and_type(const RowArgs &a, const TreeArgs *tree, F f) {
+    using std::integral_constant;
+    if (!tree) by_mode_and_type(a, f);
+    else if (a.dtype == DT_BF16) f(integral_constant<int, ROWS_CHOOSE>(), integral_constant<bool, true>());
+    else f(integral_constant<int, ROWS_CHOOSE>(), integral_constant<bool, false>());
+}
 
 // Launches of at most this many workgroups are latency bound: their rows are read before they are known
 // to be live.  Larger ones are bandwidth bound, and the bytes of a dead row would cost time: a launch sized for the limits
@@ -1435,13 +1445,11 @@ static hipError_t launch_stream(const RowArgs &a_in, int64_t n_rows, int nl, hip
 }
 
 // top-k rows, pass 2: selection on the lane maxima
-// What a launch of a level's rows needs to choose the level's nodes, with `first_wg` workgroups of rows and its words at `words` (null: it does not).
+// What a launch of a level's rows needs to choose the level's nodes, with `first_wg` workgroups of rows and its words at `words`.
 template <int MODE>
 static Tail<MODE> level_tail(const RowArgs &a, const TreeArgs *tree, void *words, unsigned first_wg) {
-    if constexpr (MODE == ROWS_LEVEL) {
+    if constexpr (MODE == ROWS_CHOOSE) {
         LevelTail h = {};
-        h.first_wg = -1;  // as a number without sign: no workgroup reaches it
-        if (!tree) return h;
         h.t = *tree;
         h.words = (u64 *)words;
         h.tag = launch_tag();
@@ -1481,7 +1489,7 @@ static hipError_t launch_pass(const RowArgs &a_in, int64_t n_rows, int nl, float
     a.early_load = 1;
     a.n_rows = n_rows;
     const int kid = a.mode == ROWS_DRAFT ? KID_ROWS_DRAFT : KID_ROWS_UNIFORM;
-    by_mode_and_type(a, [&](auto mode, auto bf16) {
+    by_mode_and_type(a, tree, [&](auto mode, auto bf16) {
         constexpr int MODE = decltype(mode)::value;
         constexpr bool BF = decltype(bf16)::value;
         auto go = [&](auto kernel) {
@@ -1515,7 +1523,7 @@ static hipError_t launch_held(const RowArgs &a_in, int64_t n_rows, float *top_va
     a.lse_apart = a.want_lse && n_rows <= APART_ROWS && held_threads(a.V) == 1024;
     const int64_t wgs = a.lse_apart ? 2 * n_rows : n_rows;
     const int kid = a.mode == ROWS_DRAFT ? KID_ROWS_DRAFT : KID_ROWS_UNIFORM;
-    by_mode_and_type(a, [&](auto mode, auto bf16) {
+    by_mode_and_type(a, tree, [&](auto mode, auto bf16) {
         constexpr int MODE = decltype(mode)::value;
         constexpr bool BF = decltype(bf16)::value;
         auto go = [&](auto kernel, int nt) {
