@@ -756,14 +756,17 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
         }
         static_assert(sizeof(S.cand) >= TREE_NW * ROW_LIST * sizeof(u64), "the waves' lists");
     }
-#pragma unroll
-    for (int j = 0; j < (ROWS ? 0 : EARLY); ++j) place(tid + j * TREE_NT, ev[j], et[j], el[j]);
-    // the other rows in one more trip
+    // The other rows in one more trip, asked for before the early ones are placed (behind them the trip began 0.4 us later: a step of one sequence, (67, 7, 29),
+    // 2,368 entries, 25.0 -> 24.6 us).
     constexpr int MORE = (DT_STATE_ROWS * DT_K_MAX + TREE_NT - 1) / TREE_NT - EARLY;
     const int more = ROWS ? 0 : (R * DT_K_MAX + TREE_NT - 1) / TREE_NT - EARLY;
+    float xv[MORE], xs[MORE];
+    int xt[MORE];
+    auto place_early = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < (ROWS ? 0 : EARLY); ++j) place(tid + j * TREE_NT, ev[j], et[j], el[j]);
+    };
     if (more > 0) {
-        float xv[MORE], xs[MORE];
-        int xt[MORE];
 #pragma unroll
         for (int j = 0; j < MORE; ++j)
             if (j < more && (EARLY + j + 1) * TREE_NT > R0 * DT_K_MAX) {
@@ -772,9 +775,12 @@ __global__ __launch_bounds__(TREE_NT) void tree_kernel(TreeArgs a) {
                 xt[j] = ti[e];
                 xs[j] = lse[e / DT_K_MAX];
             }
+        place_early();
 #pragma unroll
         for (int j = 0; j < MORE; ++j)
             if (j < more && (EARLY + j + 1) * TREE_NT > R0 * DT_K_MAX) place(tid + (EARLY + j) * TREE_NT, xv[j], xt[j], xs[j]);
+    } else {
+        place_early();
     }
     int levels = -1;  // whose nodes are known
     if (FINISH && k <= NARROW_K) {
