@@ -227,7 +227,7 @@ __device__ __forceinline__ bool mark_and_stay(const SharedMerge &s, int lane) {
             mine = mine || __builtin_amdgcn_ballot_w64(there && i == s.pt.me) != 0ull;
         }
         if (all) return true;
-        if (!mine || !s.stay || (u32)__builtin_amdgcn_s_memrealtime() - t0 > STAY_TICKS) return false;
+        if (!mine || !s.stay || (u32)__builtin_amdgcn_s_memrealtime() - t0 > STAY_TICKS(t0)) return false;
         __builtin_amdgcn_s_sleep(8);
     }
 }
@@ -1145,7 +1145,7 @@ __device__ __forceinline__ bool join_splits(const SplitBuf &sb, int64_t at, int 
             offered = lane < KS && lane != ks && get_agent(offer) == here;
             marked = lane < KS && lane != ks && get_agent(mark) == sb.tag;
             if (__builtin_amdgcn_ballot_w64(offered || marked || lane >= KS || lane == ks) == ~0ull) break;
-            if ((u32)__builtin_amdgcn_s_memrealtime() - t0 > STAY_TICKS) {
+            if ((u32)__builtin_amdgcn_s_memrealtime() - t0 > STAY_TICKS(t0)) {
                 if (!leave()) return false;
                 offered = false;
                 marked = true;
@@ -1163,7 +1163,7 @@ __device__ __forceinline__ bool join_splits(const SplitBuf &sb, int64_t at, int 
         if (lane == ks) __hip_atomic_store(offer, here, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         while (__builtin_amdgcn_ballot_w64(lane == ks && get_agent(offer) == here)) {
-            if ((u32)__builtin_amdgcn_s_memrealtime() - t0 > OFFER_TICKS) break;
+            if ((u32)__builtin_amdgcn_s_memrealtime() - t0 > OFFER_TICKS(t0)) break;
         }
         u64 was = here;
         if (lane == ks) __hip_atomic_compare_exchange_strong(offer, &was, 0, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);

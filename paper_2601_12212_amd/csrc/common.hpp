@@ -279,70 +279,18 @@ __device__ __forceinline__ float wave_row_sum(int V, const float (&x)[ROW_NG][8]
 // word, where a fence would write back and drop the whole L2.  A load at agent scope finds what lies written in its own XCD's L2.
 __device__ __forceinline__ void put_agent(u64 *p, u64 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ u64 get_agent(u64 *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ u64 swap_agent(u64 *p, u64 v) { return __hip_atomic_exchange(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void put_local(u64 *p, u64 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
+__device__ __forceinline__ u64 swap_local(u64 *p, u64 from, u64 to) {
+    __hip_atomic_compare_exchange_strong(p, &from, to, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    return from;
+}
+__device__ __forceinline__ void drain() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ u64 ballot(bool b) { return __builtin_amdgcn_ballot_w64(b); }
 __device__ __forceinline__ u32 xcc_id() { return __builtin_amdgcn_s_getreg(20 | 3 << 11); }  // HW_REG_XCC_ID, four bits
+__device__ __forceinline__ u32 ticks() { return (u32)__builtin_amdgcn_s_memrealtime(); }
 typedef u64 u64x2 __attribute__((ext_vector_type(2)));
-#define LINE_WORDS 16     // of 64 bits in a cache line
-#define STAY_TICKS 5000   // of 10 ns: how long a workgroup stays for the others of its launch
-#define OFFER_TICKS 1000  // and how long it offers them what it has in its XCD's L2
-
-// n workgroups that hand what they have to one more, which waits for them; one wave of each speaks for it.
-//
-// What they have goes in one of two ways.  On the waiting one's XCD it is left in that L2 and offered by a word, with the XCD's number in it, which the waiting
-// one exchanges for 0 when it takes what is there.  An offer that nobody has taken for OFFER_TICKS is withdrawn the same way; then all of it is written
-// to the memory side and marked there, for a reader anywhere.  Nothing depends on which workgroups run at once or where: if the waiting one has
-// waited for STAY_TICKS and taken nothing, it leaves a mark as well and goes; the offers run out, and of those that mark what they have the last to come
-// sees all marks and does its work (of the last two at least one sees the other's mark; both then do the same).  Offers end as 0, and
-// marks are taken away by whoever has seen them all: a replayed graph has the same tag.
-struct Hands {
-    u64 *offers;  // [n]: `tag` and an XCD's number while something is on offer in its L2
-    u64 *marks;   // [n + 1]: `tag` once it is at the memory side; the last one's, once it has gone
-    u64 tag;      // of this launch: what the memory held before it never looks like an offer or a mark
-    int n;        // up to 63
-};
-// What is offered has reached the L2.  True if it has been taken.
-__device__ __forceinline__ bool hand_offer(const Hands &h, int me, int lane) {
-    const u64 here = h.tag | (xcc_id() + 1);
-    u64 *const own = h.offers + me;
-    if (lane == 0) __hip_atomic_store(own, here, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    const u32 t0 = (u32)__builtin_amdgcn_s_memrealtime();
-    while (__builtin_amdgcn_ballot_w64(lane == 0 && get_agent(own) == here)) {
-        if ((u32)__builtin_amdgcn_s_memrealtime() - t0 > OFFER_TICKS) break;
-    }
-    u64 was = here;
-    if (lane == 0) __hip_atomic_compare_exchange_strong(own, &was, 0, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    return __builtin_amdgcn_ballot_w64(was != here) != 0ull;
-}
-// What is marked has reached the memory side.  True if all are there, the waiting one's mark among them.
-__device__ __forceinline__ bool hand_mark(const Hands &h, int me, int lane) {
-    if (lane == 0) put_agent(h.marks + me, h.tag);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    return __builtin_amdgcn_ballot_w64(get_agent(h.marks + min(lane, h.n)) != h.tag) == 0ull;
-}
-// The waiting one: true if all are there, with `taking` in the lanes of offers that hand_settle is to take.
-__device__ __forceinline__ bool hand_await(const Hands &h, int lane, bool &taking) {
-    const u64 here = h.tag | (xcc_id() + 1);
-    const int peer = min(lane, h.n - 1);
-    const u32 t0 = (u32)__builtin_amdgcn_s_memrealtime();
-    for (;;) {
-        const bool offered = get_agent(h.offers + peer) == here, marked = get_agent(h.marks + peer) == h.tag;
-        taking = offered && !marked && lane < h.n;
-        if (__builtin_amdgcn_ballot_w64(offered || marked) == ~0ull) return true;
-        if ((u32)__builtin_amdgcn_s_memrealtime() - t0 > STAY_TICKS) {
-            taking = false;
-            return hand_mark(h, h.n, lane);
-        }
-    }
-}
-// Whoever has all, once what was on offer has been asked for.  Who withdrew its offer a moment ago is on the way to its mark (what it writes there
-// is what it had offered).
-__device__ __forceinline__ void hand_settle(const Hands &h, int lane, bool taking) {
-    u64 was = h.tag | (xcc_id() + 1);
-    const u64 here = was;
-    if (taking) __hip_atomic_compare_exchange_strong(h.offers + min(lane, h.n - 1), &was, 0, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    const bool late = taking && was != here;
-    while (__builtin_amdgcn_ballot_w64(late && get_agent(h.marks + min(lane, h.n)) != h.tag)) {}
-    if (lane <= h.n && (!taking || late)) put_agent(h.marks + lane, 0);
-}
 
 }  // namespace dt
+
+#include "hands.hpp"

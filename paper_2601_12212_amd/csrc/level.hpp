@@ -202,16 +202,12 @@ __device__ __forceinline__ void emit_nothing(const TreeArgs &a, int b, int l, u3
 // of its own -> so: one sequence of (60, 6, 10) and 128,256 tokens 70 to 78 | 71.4 -> 66.7 | 68.8 us, 1,000 tokens 69 to 76 | 58.0 -> 55 | 52.3; (64, 7, 8), 8,192 80 to 89 |
 // 65.2 -> 63 | 58.9; 16 of (60, 6, 16), 4,001 69 to 78 | 67.8 -> 62 | 64.5.
 //
-// The words of a sequence: a mark for each row that is reduced and one for its log-sum-exp where a workgroup of its own makes that, at the memory side like
-// the results; one of the waiting workgroup if it has waited for STAY_TICKS and goes, in whose place the last of the others to come then does its work; and one by which
-// either claims that (each may see all marks; what is handed on must not be read by one while the other writes it).  All are 0 again at the end: a
-// replayed graph has the same tag.
-#define LEVEL_WORDS 40
-#define LEVEL_GONE (2 * NARROW_K)
-#define LEVEL_CLAIM (2 * NARROW_K + 1)
+// The words of a sequence (Marks): one for each row that is reduced and one for its log-sum-exp where a workgroup of its own makes that, at the memory
+// side like the results.  Who does the waiting one's work has claimed it: what is handed on must not be read by one while another writes it.
+static_assert(2 * NARROW_K <= MARK_GONE, "a row's and its log-sum-exp's");
 struct LevelTail {
     TreeArgs t;
-    u64 *words;     // [batch, LEVEL_WORDS]
+    u64 *words;     // [batch, MARK_WORDS]
     u64 tag;
     int first_wg;   // of the workgroups that wait
     int rows;       // rows of a sequence in the launch
@@ -240,37 +236,10 @@ __device__ __forceinline__ void put32_agent(T *p, T v) {
     static_assert(sizeof(T) == 4, "a word");
     __hip_atomic_store((u32 *)p, __builtin_bit_cast(u32, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// Lanes whose marks a sequence's level waits for.
-__device__ __forceinline__ u64 level_marks(const LevelTail &h, int rows) {
+// The marks of a sequence's level, `rows` of its rows being reduced.
+__device__ __forceinline__ Marks level_marks(const LevelTail &h, int b, int rows) {
     const u64 m = (1ull << rows) - 1ull;
-    return h.lse_apart ? m | m << NARROW_K : m;
-}
-__device__ __forceinline__ bool level_claim(u64 *words, u64 tag, int lane) {
-    u64 was = 0;
-    if (lane == 0) was = __hip_atomic_exchange(words + LEVEL_CLAIM, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return __builtin_amdgcn_ballot_w64(was == tag) == 0ull;
-}
-// One wave of a row's workgroup, whose results have reached the memory side; true: the level is this one's to choose.
-__device__ __forceinline__ bool level_row_done(const LevelTail &h, int b, int me, int rows, int lane) {
-    u64 *const words = h.words + (int64_t)b * LEVEL_WORDS;
-    if (lane == 0) put_agent(words + me, h.tag);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    const u64 there = __builtin_amdgcn_ballot_w64(get_agent(words + min(lane, LEVEL_GONE)) == h.tag), all = level_marks(h, rows) | 1ull << LEVEL_GONE;
-    return (there & all) == all && level_claim(words, h.tag, lane);
-}
-__device__ __forceinline__ bool level_await(const LevelTail &h, int b, int rows, int lane) {
-    u64 *const words = h.words + (int64_t)b * LEVEL_WORDS;
-    const u64 all = level_marks(h, rows);
-    const u32 t0 = (u32)__builtin_amdgcn_s_memrealtime();
-    auto there = [&]() { return (__builtin_amdgcn_ballot_w64(get_agent(words + min(lane, LEVEL_GONE)) == h.tag) & all) == all; };
-    while (!there()) {
-        if ((u32)__builtin_amdgcn_s_memrealtime() - t0 > STAY_TICKS) {
-            if (lane == 0) put_agent(words + LEVEL_GONE, h.tag);
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            return there() && level_claim(words, h.tag, lane);
-        }
-    }
-    return true;
+    return {h.words + (int64_t)b * MARK_WORDS, h.tag, h.lse_apart ? m | m << NARROW_K : m};
 }
 __device__ __forceinline__ LevelIn level_in(const TreeArgs &a, int rows, int b, int lane) {
     LevelIn in;
@@ -350,7 +319,7 @@ __device__ __forceinline__ int level_next(const TreeArgs &a, LevelLds &L, int b,
     return n;
 }
 // The level, by one wave; its rows' results are at the memory side.
-__device__ __forceinline__ void level_expand(const LevelTail &h, LevelLds &L, int b, LevelIn in, int lane) {
+__device__ __forceinline__ void level_expand(const LevelTail &h, const Marks &marks, LevelLds &L, int b, LevelIn in, int lane) {
     const TreeArgs &a = h.t;
     const int xl = a.expand_level;
     // (rows_per_seq reaches every k: of more than NARROW_K nodes there is level 1 only)
@@ -387,8 +356,8 @@ __device__ __forceinline__ void level_expand(const LevelTail &h, LevelLds &L, in
         emit_nothing(a, b, xl, in.word);
         carry_head(a, b, xl, k, 0, tok_count);
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if (lane <= LEVEL_CLAIM) put_agent(h.words + (int64_t)b * LEVEL_WORDS + lane, 0);
+    drain();
+    mark_clear(marks, lane);
 }
 // The waiting workgroup of sequence b, one wave.
 __device__ __forceinline__ void level_wait_and_expand(const LevelTail &h, LevelLds &L, int b, int lane) {
@@ -397,7 +366,8 @@ __device__ __forceinline__ void level_wait_and_expand(const LevelTail &h, LevelL
         if (lane == 0) emit_nothing(h.t, b, h.t.expand_level, in.word);
         return;
     }
-    if (level_await(h, b, in.rows, lane)) level_expand(h, L, b, in, lane);
+    const Marks marks = level_marks(h, b, in.rows);
+    if (mark_await(marks, lane)) level_expand(h, marks, L, b, in, lane);
 }
 
 }  // namespace dt

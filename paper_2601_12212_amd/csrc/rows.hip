@@ -414,8 +414,9 @@ __device__ __forceinline__ void level_row_end(const RowMeta &meta, bool lse_wg) 
         __syncthreads();
         if (threadIdx.x >= 64) return;
         const int lane = lane_id(), b = __builtin_amdgcn_readfirstlane(meta.seq);
-        if (!level_row_done(tail, b, meta.slot + (lse_wg ? NARROW_K : 0), meta.rows, lane)) return;
-        level_expand(tail, level_lds(), b, level_in(tail.t, tail.rows, b, lane), lane);
+        const Marks marks = level_marks(tail, b, meta.rows);
+        if (!mark_done(marks, meta.slot + (lse_wg ? NARROW_K : 0), lane)) return;
+        level_expand(tail, marks, level_lds(), b, level_in(tail.t, tail.rows, b, lane), lane);
     }
 }
 // True for the workgroups that wait for a sequence's rows, which have then done so; wg: the workgroup's number.
@@ -432,6 +433,7 @@ __device__ __forceinline__ bool level_waits(const Tail<MODE> &arg, u32 wg) {
     return false;
 }
 
+#define ROW_MARKS 18  // marks of a row's chunks and of the workgroup that waits for them, and a claim
 // PASS: the maxima are made in the same launch, in chunks of 2,048 PASS entries, up to 16 of them.  0: by the launch before.
 // Both passes in one launch: workgroups of the stream, and one to a row that waits for the row's chunks and selects.  Between two launches lie the first one's end, the
 // second's start, its arguments and its rows' metadata; here the maxima go through the L2 of the XCD that has the row, in three trips of 0.4 us (written, offered, read),
@@ -461,9 +463,9 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl_, 
         const int c = blockIdx.x >> 3;
         if (g >= a.n_rows) return;
         __shared__ int s_go;
-        // offers and marks behind the maxima, whose room is twice what they take: a cache line and 17 words to a row
-        u64 *const words = (u64 *)((char *)a.lane_max + a.n_rows * S * 512);
-        const Hands hands = {words + g * LINE_WORDS, words + a.n_rows * LINE_WORDS + g * 17, tag, S};
+        // offers, and marks and a claim, behind the maxima, whose room is twice what they take
+        u64 *const words = (u64 *)((char *)a.lane_max + a.n_rows * S * 512), *const marks = words + a.n_rows * LINE_WORDS + g * ROW_MARKS;
+        const Hands<1> hands = {words + g * LINE_WORDS, marks, marks + ROW_MARKS - 1, tag, S};
         if (c < S) {
             constexpr int EC = 8 * PASS;
             const int base = c * (256 * EC) + w * (64 * EC) + lane * 8 - row_shift(a.logits, BF16, a.V, a.row_stride, g);
@@ -502,7 +504,7 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl_, 
         }
         bool taking = false;
         if (w == 0) {
-            const bool all = c < S ? hand_mark(hands, c, lane) : hand_await(hands, lane, taking);
+            const bool all = c < S ? hand_mark(hands, c, lane) : hand_await(hands, lane, taking) || hand_leave(hands, lane);
             if (lane == 0) s_go = all;
         }
         __syncthreads();
@@ -510,7 +512,7 @@ __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl_, 
 #pragma unroll
         for (int i = 0; i < 2; ++i) q[i] = quad_at<BF16, true>(lm, 4 * min(64 * i + lane, 8 * S - 1) + w);
         if (lse_wave) pm = __builtin_bit_cast(float2, get_agent((u64 *)(a.part_ms + g * S * 4 + min(lane, S * 4 - 1))));
-        if (w == 0) hand_settle(hands, lane, taking);
+        if (w == 0) hand_settle(hands, lane, taking, hand_take(hands, lane, taking));
     } else {
         // the lane maxima do not depend on the row's metadata (two dependent global reads): ask for them
         // first, and wave 3 for the row's (max, sum) partials.  Rows that turn out to be dead have their
@@ -1495,7 +1497,7 @@ static hipError_t launch_pass(const RowArgs &a_in, int64_t n_rows, int nl, float
         auto go = [&](auto kernel) {
             const unsigned x = 8 * (S + 1), y = (unsigned)((n_rows + 7) / 8), more = tree ? (unsigned)((tree->batch + x - 1) / x) : 0;
             // a level's words lie behind those of the rows (row_select_kernel)
-            const auto tail = level_tail<MODE>(a, tree, (char *)a.lane_max + n_rows * (S * 512 + (LINE_WORDS + 17) * 8), x * y);
+            const auto tail = level_tail<MODE>(a, tree, (char *)a.lane_max + n_rows * (S * 512 + (LINE_WORDS + ROW_MARKS) * 8), x * y);
             launch_kernel(kid, st, kernel, dim3(x, y + more), dim3(256), 0, a, nl, S, top_val, top_id, lse, out_stride, launch_tag(), tail);
         };
         if (nl == 4) go(row_select_kernel<MODE, BF, 4>);
