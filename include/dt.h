@@ -21,7 +21,8 @@
  *     has reached that point.
  *   - `ws` is caller-owned device scratch of at least dt_workspace_bytes() bytes, 256-byte
  *     aligned; its contents need not survive between calls.  Calls that share one workspace
- *     must be ordered on one stream.
+ *     must be ordered on one stream: calls that overlap on one end, but with undefined results, and
+ *     so do later replays of a graph that holds one of them until the workspace has been overwritten.
  *   - Per-sequence limits live in a DEVICE array of dt_params so that a policy running on
  *     the GPU can set them without a host round trip.  Values are clamped on the device
  *     to 1 <= TT <= TT_cap, 1 <= d <= DT_D_MAX, 1 <= k <= min(DT_K_MAX, V).
@@ -115,7 +116,9 @@ int dt_topk_rows(void *stream, const void *logits, dt_dtype t, int64_t n_rows, i
  * More -> DT_ERR_LIMIT, nothing is launched.  Other errors as dt_topk_rows.
  * All calls on one device share that device's scratch, which keeps the previous call's contents (none
  * of it needs clearing): calls that overlap on one device -- different streams, or graphs that replay
- * concurrently -- race; order them.
+ * concurrently -- race; order them.  Such calls end, but their results are undefined, and so are those of later
+ * replays of a graph that holds one of them (the words by which its workgroups find each other may be left as
+ * the other call wrote them); capture it again.
  */
 #define DT_STATIC_SCRATCH_BYTES (8u << 20)
 int dt_topk_rows_static(void *stream, const void *logits, dt_dtype t, int64_t n_rows, int V, int64_t row_stride,

@@ -1042,9 +1042,9 @@ struct WaveArea {
 struct SplitBuf {
     float4 *o;     // [unit, D/32 waves, KS, 4, 64 lanes]: a wave's output registers
     float2 *ml;    // [unit, D/32 waves, KS, 32]: (max, sum) per query row
-    u64 *offers;   // [unit, D/32 waves, KS], a cache line each: `tag` and an XCD's number while a partial is on offer in its L2
-    u64 *marks;    // [unit, D/32 waves, KS]: `tag` once a partial is at the memory side
-    u64 tag;       // of this launch: what the memory held before it never looks like a mark
+    u64 *offers;   // [unit, D/32 waves, KS], a cache line each (Hands)
+    u64 *marks;    // [unit, D/32 waves, KS]
+    u64 tag;       // of this launch
     GroupDiv gd, hd, md;  // by the query heads per kv head, the kv heads, the row blocks
     int units;
     u32 ks_magic;  // x / KS = x * ks_magic / 4096 for x < 64
@@ -1104,75 +1104,53 @@ __device__ __forceinline__ void get_partials(const float4 *const (&o)[N], const 
 
 // Split ks of KS of a row block: one wave's column block, res (unnormalised), M and Lsum (of the lane's query), against those of its
 // fellows in the other splits; `at` is the column block's number in the launch.  One split owns the block (another one for each wave, so that
-// its workgroup reads little): it keeps its own partial in registers, waits for the others' and adds them up.  True for a wave that
+// its workgroup reads little): it keeps its own partial in registers, waits for the others' and adds them up (Hands).  True for a wave that
 // has them all, with the results in res and Lsum.
 //
-// A partial goes to the owner in one of two ways.  The workgroups of a row block are numbered so that the same XCD gets them all (but `apart`): the
-// partial is left in its L2 and offered there by a word, with the XCD's number in it, that an owner on the same XCD exchanges for 0 when it takes it
-// (loads at agent scope find what lies written in their own XCD's L2).  An offer that nobody has taken for OFFER_TICKS is withdrawn the same
-// way; then the partial is written to the memory side and marked there, for an owner anywhere.
+// The workgroups of a row block are numbered so that the same XCD gets them all (but `apart`, whose partials go to the memory side at once): what is handed over
+// is left in its L2, and loads at agent scope find what lies written in their own XCD's L2.
 //
 // What bounds it are trips within the XCD, about 0.4 us each when all workgroups make them at once: the partial is written, the offer seen, the partials and the exchange
 // of the offer fetched together, 1.7 us of a layer where a merge kernel took 2.9 and a launch of the host (8B shape, 64 nodes, 1,024 keys, three splits: 32 layers
 // 352 -> 331 us; 16 layers, whose caches lie closer, 10.8 -> 9.3 a layer; one of 40 heads 2,048 keys 12.8 -> 11.5).  Through the memory side only, as far fellows go, 336.
-//
-// Nothing depends on which workgroups run at once or where.  An owner that has waited for STAY_TICKS and taken nothing leaves its own partial and a mark
-// at the memory side; its fellows' offers run out, and of those that mark their partials the last to come sees all marks and takes the
-// block (of the last two at least one sees the other's mark; both taking it write the same, since partials are added in the order of
-// their splits).  Offers end as 0, and marks are taken away by whoever has seen them all: a replayed graph has the same tag.
 template <int DBLK>
 __device__ __forceinline__ bool join_splits(const SplitBuf &sb, int64_t at, int KS, int ks, bool apart, int w, int lane, float c, float (&res)[16], float M, float &Lsum) {
-    const int col = lane & 31, peer = min(lane, KS - 1);
+    const int col = lane & 31;
     float4 *const o = sb.o + at * KS * 4 * 64 + lane;
     float2 *const ml = sb.ml + at * KS * 32 + col;
-    u64 *const offer = sb.offers + (at * KS + peer) * LINE_WORDS;
-    u64 *const mark = sb.marks + at * KS + peer;
-    const u64 here = sb.tag | (xcc_id() + 1);
-    auto leave = [&]() {  // at the memory side; true if all are there
+    // the members are the other splits in their order; the line of an offer more holds the claim
+    u64 *const offers = sb.offers + at * KS * LINE_WORDS;
+    const Hands<LINE_WORDS> hands = {offers, sb.marks + at * KS, offers + (KS - 1) * LINE_WORDS, sb.tag, KS - 1};
+    const int owner = KS - 1 - (w >= KS ? w - KS : w);  // w % KS: four waves, two splits and more
+    auto leave = [&]() {  // at the memory side
 #pragma unroll
         for (int q = 0; q < 4; ++q) put16_agent(o + (ks * 4 + q) * 64, f32x4{res[4 * q], res[4 * q + 1], res[4 * q + 2], res[4 * q + 3]});
         if (lane < 32) put8_agent(ml + ks * 32, f32x2{M, Lsum});
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        if (lane == ks) put_agent(mark, sb.tag);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        return __builtin_amdgcn_ballot_w64(get_agent(mark) != sb.tag) == 0ull;
+        drain();
     };
-    const u32 t0 = (u32)__builtin_amdgcn_s_memrealtime();
-    bool marked = true, taking = false;  // whose mark is there; whose offer is to be taken
-    if (ks == KS - 1 - (w >= KS ? w - KS : w)) {  // w % KS: four waves, two splits and more
-        bool offered;
-        for (;;) {
-            offered = lane < KS && lane != ks && get_agent(offer) == here;
-            marked = lane < KS && lane != ks && get_agent(mark) == sb.tag;
-            if (__builtin_amdgcn_ballot_w64(offered || marked || lane >= KS || lane == ks) == ~0ull) break;
-            if ((u32)__builtin_amdgcn_s_memrealtime() - t0 > STAY_TICKS(t0)) {
-                if (!leave()) return false;
-                offered = false;
-                marked = true;
-                break;
-            }
+    bool taking = false;
+    if (ks == owner) {
+        if (!hand_await(hands, lane, taking)) {
+            leave();
+            if (!hand_leave(hands, lane)) return false;
         }
-        taking = offered && !marked;
-    } else if (apart) {
-        if (!leave()) return false;
     } else {
+        const int me = ks - (ks > owner);
+        if (!apart) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) *(f32x4 *)(o + (ks * 4 + q) * 64) = f32x4{res[4 * q], res[4 * q + 1], res[4 * q + 2], res[4 * q + 3]};
-        if (lane < 32) *(f32x2 *)(ml + ks * 32) = f32x2{M, Lsum};
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        if (lane == ks) __hip_atomic_store(offer, here, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        while (__builtin_amdgcn_ballot_w64(lane == ks && get_agent(offer) == here)) {
-            if ((u32)__builtin_amdgcn_s_memrealtime() - t0 > OFFER_TICKS(t0)) break;
+            for (int q = 0; q < 4; ++q) *(f32x4 *)(o + (ks * 4 + q) * 64) = f32x4{res[4 * q], res[4 * q + 1], res[4 * q + 2], res[4 * q + 3]};
+            if (lane < 32) *(f32x2 *)(ml + ks * 32) = f32x2{M, Lsum};
+            drain();
+            if (hand_offer(hands, me, lane)) return false;
         }
-        u64 was = here;
-        if (lane == ks) __hip_atomic_compare_exchange_strong(offer, &was, 0, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (__builtin_amdgcn_ballot_w64(was != here) || !leave()) return false;
+        leave();
+        if (!hand_mark(hands, me, lane)) return false;
     }
     asm volatile("" ::: "memory");
     // Partial j of the others is split j + (j >= ks)'s.  All their statistics, and three partials at a time, are in flight together; the sum is over the
     // splits in their order, whoever makes it.
-    const u64 take = __builtin_amdgcn_ballot_w64(taking);
+    const u64 take = ballot(taking), here = sb.tag | (xcc_id() + 1);
+    u64 *const offer = offers + min(lane, KS - 2) * LINE_WORDS;
     u64 was = here;
     float acc[16], l = 0.f;
 #pragma unroll
@@ -1238,10 +1216,7 @@ __device__ __forceinline__ bool join_splits(const SplitBuf &sb, int64_t at, int 
     else if (KS == 6) add(integral_constant<int, 5>());
     else if (KS == 7) add(integral_constant<int, 6>());
     else add(integral_constant<int, MAX_SPLITS - 1>());
-    // Who withdrew its offer a moment ago is on the way to its mark (what has been read of it is what it writes there).
-    const bool late = taking && was != here;
-    while (__builtin_amdgcn_ballot_w64(late && get_agent(mark) != sb.tag)) {}
-    if (lane < KS && (marked || late)) put_agent(mark, 0);
+    hand_settle(hands, lane, taking, was);
 #pragma unroll
     for (int i = 0; i < 16; ++i) res[i] = acc[i];
     Lsum = l;

@@ -37,7 +37,7 @@ struct Hands {
     u64 tag;      // of this launch, the low 16 bits free: what the memory held before it never looks like an offer or a mark
     int n;        // up to 63
 };
-#define HAND_HAD 0x100  // with the tag, a member's mark: there is no need of it any more; the claim: made
+#define HAND_HAD 0x100  // with the tag, in the place of a member's mark: the waiting one has what it is about to mark; of the claim: made
 // What is offered has reached the L2.  True if it has been taken.
 template <int STRIDE>
 __device__ __forceinline__ bool hand_offer(const Hands<STRIDE> &h, int me, int lane) {
@@ -51,7 +51,7 @@ __device__ __forceinline__ bool hand_offer(const Hands<STRIDE> &h, int me, int l
     }
     u64 was = here;
     if (lane == 0) was = swap_local(own, here, 0);
-    return ballot(was != here) != 0ull;
+    return ballot(lane == 0 && was == 0) != 0ull;  // (anything else is not this launch's: as if nobody had taken it)
 }
 __device__ __forceinline__ bool hand_claim(u64 *claim, u64 tag, int lane) {
     u64 was = 0;
@@ -61,8 +61,13 @@ __device__ __forceinline__ bool hand_claim(u64 *claim, u64 tag, int lane) {
 // What is marked has reached the memory side.  True for one, if all are there, the waiting one's mark among them.
 template <int STRIDE>
 __device__ __forceinline__ bool hand_mark(const Hands<STRIDE> &h, int me, int lane) {
-    if (lane == 0) put_agent(h.marks + me, h.tag);
+    u64 was = 0;
+    if (lane == 0) was = swap_agent(h.marks + me, h.tag);
     drain();
+    if (ballot(was == (h.tag | HAND_HAD))) {
+        if (lane == 0) put_agent(h.marks + me, 0);
+        return false;
+    }
     return ballot(get_agent(h.marks + min(lane, h.n)) != h.tag) == 0ull && hand_claim(h.claim, h.tag, lane);
 }
 // The waiting one: true if all are there, with `taking` in the lanes of offers that hand_take is to take.  False if it has waited for long enough.
@@ -94,12 +99,14 @@ __device__ __forceinline__ u64 hand_take(const Hands<STRIDE> &h, int lane, bool 
     const u64 here = h.tag | (xcc_id() + 1);
     return taking ? swap_local(h.offers + min(lane, h.n - 1) * STRIDE, here, 0) : here;
 }
-// Whoever has all.  Who withdrew its offer a moment ago is on the way to its mark (what it writes there is what it had offered).
+// Whoever has all.  Who withdrew its offer a moment ago is on the way to its mark, with what it had offered: it finds there that it is not needed any more, and
+// takes that away.  (Nobody waits for the other: where two launches overlap on one memory, against the rules, it may never come.)
 template <int STRIDE>
 __device__ __forceinline__ void hand_settle(const Hands<STRIDE> &h, int lane, bool taking, u64 was) {
     const bool late = taking && was != (h.tag | (xcc_id() + 1));
-    while (ballot(late && get_agent(h.marks + min(lane, h.n)) != h.tag)) {}
-    if (lane <= h.n && (!taking || late)) put_agent(h.marks + lane, 0);
+    u64 mark = h.tag;
+    if (late) mark = swap_agent(h.marks + min(lane, h.n), h.tag | HAND_HAD);
+    if (lane <= h.n && (!taking || (late && mark == h.tag))) put_agent(h.marks + lane, 0);
 }
 
 // Marks alone: who waits for others' results at the memory side and has nothing of its own there.  One word to each of them, one of the waiting one if it

@@ -1,6 +1,6 @@
 // csrc/hands.hpp on the host: workgroups' waves as sets of fibers that a scheduler with a seed runs operation by operation, in any order that the
 // hardware may, with stores that arrive late unless they are waited for and a clock that jumps, so that every wait runs out now and then.
-// Launch after launch with the same tag, as a replayed graph has it.  usage: hand_overs rows|levels|apart seeds
+// Launch after launch with the same tag, as a replayed graph has it.  usage: hand_overs rows|apart|levels|overlap seeds
 #include <stdint.h>
 #include <stdio.h>
 #include <stdlib.h>
@@ -131,7 +131,7 @@ void run(int lanes_of_a_wave) {
     }
     int left = (int)waves.size();
     for (int step = 0; left; ++step) {
-        CHECK(step < 40000000, "a wait without an end");
+        CHECK(step < 4000000, "a wait without an end");
         Wave &w = waves[pick((int)waves.size())];
         if (step < w.start) continue;
         // the wave's next lane that can run; all of them waiting for each other: on
@@ -182,7 +182,7 @@ struct Row {
     int result = 0, taken = 0;
 };
 
-void launches(int rows, int members, bool level, bool apart, int n_launches) {
+void launches(int rows, int members, bool level, bool apart, int n_launches, bool overlap = false) {
     const u64 litter = pick(3) == 0 ? 0 : pick(2) ? 0xEEEEEEEEEEEEEEEEull : TAG + (5ull << 20) + 1;
     std::vector<Row> row(rows);
     for (Row &r : row) {
@@ -195,7 +195,7 @@ void launches(int rows, int members, bool level, bool apart, int n_launches) {
     const Marks marks = {words.data(), TAG, (1ull << rows) - 1ull};
     int version = 0, expanded = 0;
     auto expand = [&](int lane) {
-        if (lane < rows) CHECK(row[lane].result == version, "a level from another launch's row");
+        if (lane < rows) CHECK(overlap || row[lane].result == version, "a level from another launch's row");
         if (lane == 0) ++expanded;
         drain();
         mark_clear(marks, lane);
@@ -205,7 +205,7 @@ void launches(int rows, int members, bool level, bool apart, int n_launches) {
         yield();
         if (lane <= members && lane != me) {
             const Data &d = of.data[lane];
-            CHECK((d.xcd == xcc_id() ? std::max(d.local, d.memory) : d.memory) == version, "a result of another launch");
+            CHECK(overlap || (d.xcd == xcc_id() ? std::max(d.local, d.memory) : d.memory) == version, "a result of another launch");
         }
         const u64 was = hand_take(h, lane, taking);
         hand_settle(h, lane, taking, was);
@@ -248,7 +248,19 @@ void launches(int rows, int members, bool level, bool apart, int n_launches) {
             }
         }
         if (level) waves.push_back({[&](int lane) { if (mark_await(marks, lane)) expand(lane); }, (u32)pick(8), 0, 0, 0});
+        if (overlap)  // a launch that writes to the same memory meanwhile
+            waves.push_back({[&](int lane) {
+                                 for (int i = 0; lane == 0 && i < 40; ++i) {
+                                     Row &r = row[pick(rows)];
+                                     u64 *const words[] = {&r.offers[pick(members)], &r.marks[pick(members + 1)], &r.claim};
+                                     const u64 values[] = {0, litter, (TAG + (7ull << 20)) | (u64)pick(17), ~TAG};
+                                     put_local(words[pick(3)], values[pick(4)]);
+                                     for (int n = pick(40); n; --n) yield();
+                                 }
+                             },
+                             0, 0, 0, 0});
         run(level ? MARK_CLAIM : members + 2);
+        if (overlap) continue;  // what such launches leave is not defined, but they end
         for (const Row &r : row) {
             CHECK(r.taken == 1, "launch %d: a row taken %d times", version, r.taken);
             for (u64 o : r.offers) CHECK(apart || o == 0, "launch %d: an offer %llx is left", version, o);
@@ -270,6 +282,7 @@ int main(int argc, char **argv) {
         if (!strcmp(argv[1], "rows")) launches(1, 1 + pick(4), false, false, 8);
         else if (!strcmp(argv[1], "apart")) launches(1, 1 + pick(4), false, true, 8);
         else if (!strcmp(argv[1], "levels")) launches(1 + pick(2), 1 + pick(2), true, false, 6);
+        else if (!strcmp(argv[1], "overlap")) launches(1 + pick(2), 1 + pick(3), pick(2), false, 4, true);
         else return 2;
     }
     printf("ok\n");

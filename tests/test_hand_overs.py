@@ -16,8 +16,9 @@ def program(tmp_path_factory):
 
 
 # rows of one to four chunks; the same past the L2s throughout; levels of one or two such rows.  (With two workgroups that may both take a row, "levels" fails at its
-# second seed, and with a level that two may choose at its fourth.)
-@pytest.mark.parametrize("scenario,seeds", [("rows", 1000), ("apart", 1000), ("levels", 400)])
+# second seed, and with a level that two may choose at its fourth.)  And launches whose words another one overwrites meanwhile, which only
+# have to end ("overlap").
+@pytest.mark.parametrize("scenario,seeds", [("rows", 1000), ("apart", 1000), ("levels", 400), ("overlap", 600)])
 def test_any_order_of_the_hand_overs(program, scenario, seeds):
     done = subprocess.run([program, scenario, str(seeds)], capture_output=True, text=True, timeout=300)
     assert done.returncode == 0, done.stdout
