@@ -1,6 +1,7 @@
 """Compile the HIP kernels and the C ABI into paper_2601_12212_amd/libdt.so (gfx950 only), the argument marshalling of
 the Python binding into paper_2601_12212_amd/_dtcall.so (gcc; finds libdt.so beside itself), and what reads a tensor's
-properties for it without the interpreter into _dttensor-<torch's version>.so (g++; against the torch that is installed)."""
+properties for it without the interpreter into _dttensor-<torch's version>.so (g++; against the torch that is installed).
+For the tests, both once more with waits that end early (SHORT_WAITS in csrc/hands.hpp), in _build."""
 import os
 import subprocess
 import sys
@@ -11,6 +12,9 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdt.so")
 PYCALL = os.path.join(HERE, "_dtcall.so")
 SOURCES = ["api.cpp", "profile.cpp", "rows.hip", "tree.hip", "attention.hip", "accept.hip", "commit.hip", "policy.hip"]
+WAITING = ["rows.hip", "attention.hip"]   # kernels whose workgroups wait for each other
+BUILD = os.path.join(HERE, "_build")
+LIB_SHORT, PYCALL_SHORT = os.path.join(BUILD, "libdt_short_waits.so"), os.path.join(BUILD, "_dtcall.so")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          # packed-FP32 code generation is switched off: some of its instruction forms have given wrong
          # results on this hardware now and then, without any error
@@ -20,15 +24,12 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
 
 def build(verbose=False):
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    objs = []
     procs = []
-    bdir = os.path.join(HERE, "_build")
-    os.makedirs(bdir, exist_ok=True)
-    for src in SOURCES:
-        obj = os.path.join(bdir, src + ".o")
-        cmd = [hipcc] + FLAGS + ["-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
+    os.makedirs(BUILD, exist_ok=True)
+    obj = lambda src, kind="": os.path.join(BUILD, src + kind + ".o")
+    for src, kind, more in [(src, "", []) for src in SOURCES] + [(src, ".short_waits", ["-DSHORT_WAITS"]) for src in WAITING]:
+        cmd = [hipcc] + FLAGS + more + ["-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj(src, kind)]
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
-        objs.append(obj)
     for src, p in procs:
         out, _ = p.communicate()
         out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l)
@@ -36,14 +37,16 @@ def build(verbose=False):
             raise RuntimeError("hipcc failed on %s:\n%s" % (src, out))
         if verbose and out.strip():
             print(out)
-    tmp = LIB + ".tmp%d" % os.getpid()
-    subprocess.check_call([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs)
-    os.replace(tmp, LIB)
     include = "-I" + sysconfig.get_paths()["include"]
-    tmp = PYCALL + ".tmp%d" % os.getpid()
-    subprocess.check_call(["gcc", "-O2", "-shared", "-fPIC", "-Wall", include, os.path.join(CSRC, "pycall.c"), "-o", tmp,
-                           "-L" + HERE, "-l:libdt.so", "-Wl,-rpath,$ORIGIN"])
-    os.replace(tmp, PYCALL)
+    for lib, pycall, kind in ((LIB, PYCALL, ""), (LIB_SHORT, PYCALL_SHORT, ".short_waits")):
+        tmp = lib + ".tmp%d" % os.getpid()
+        subprocess.check_call([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] +
+                              [obj(src, kind if src in WAITING else "") for src in SOURCES])
+        os.replace(tmp, lib)
+        tmp = pycall + ".tmp%d" % os.getpid()
+        subprocess.check_call(["gcc", "-O2", "-shared", "-fPIC", "-Wall", include, os.path.join(CSRC, "pycall.c"), "-o", tmp,
+                               "-L" + os.path.dirname(lib), "-l:" + os.path.basename(lib), "-Wl,-rpath,$ORIGIN"])
+        os.replace(tmp, pycall)
     build_reader(include)
     return LIB
 
