@@ -1595,6 +1595,7 @@ hipError_t rows_launch_topk(const RowArgs &a, int64_t n_rows, float *top_val, in
     const int nt = held_threads(a.V);
     if ((a.V <= HELD_V_MAX && (nt == 256 || n_rows * nt <= 0xFFFFFFFFll)) ||
         (a.V <= 2 * HELD_V_MAX && a.dtype == DT_BF16 && n_rows <= HELD_ROWS_MAX)) {
+        if (tree && (n_rows + tree->batch) * nt > 0xFFFFFFFFll) tree = nullptr;  // no room for the workgroups that wait
         if (tree) *to_expand = false;
         return launch_held(a, n_rows, top_val, top_id, lse, out_stride, st, tree);
     }

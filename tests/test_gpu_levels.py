@@ -209,6 +209,39 @@ def test_levels_chosen_beside_their_rows(V, bf16, k):
     drive([(60, 4, k), (1, 2, 2), (33, 3, max(1, k - 7)), (20, 1, k), (9, 2, 1)], [5, 0, 9, 1000, 77], V=V, bf16=bf16, seed=1)
 
 
+def test_a_level_whose_waiting_workgroups_find_no_room_in_the_grid():
+    # 16 million rows of 256 threads are within 2^32 threads, with a workgroup more to each of a million sequences they are not: the level's nodes are then
+    # chosen by a launch of their own.  All but three of the sequences draft nothing.
+    import paper_2601_12212_amd as dt
+    if torch.cuda.mem_get_info()[0] < 95e9:
+        pytest.skip("needs 80 GB of device memory")
+    B, V, R, live = 1000000, 8, 16, [0, 77777, 999999]
+    gen = torch.Generator("cuda").manual_seed(3)
+    logits = [torch.randn((B * r, V), generator=gen, device="cuda") for r in (1, R)]
+    limits = torch.ones((B, 3), dtype=torch.int32, device="cuda")
+    limits[live] = torch.tensor([30, 3, 4], dtype=torch.int32, device="cuda")
+
+    def levels(limits, logits):
+        n = len(limits)
+        state = torch.empty(dt.dt_level_state_bytes(n), dtype=torch.uint8, device="cuda")
+        ws = torch.empty(dt.dt_workspace_bytes(n, n * R, V, 30, 1, 1), dtype=torch.uint8, device="cuda")
+        out = []
+        for l, x in enumerate(logits):
+            n_exp = torch.zeros(n, dtype=torch.int32, device="cuda")
+            exp = [torch.zeros((n, 32), dtype=torch.int32, device="cuda") for _ in range(4)] + [torch.zeros((n, 32, 4), dtype=torch.int64, device="cuda")]
+            dt.dt_expand_level(l + 1, limits, x, R, None, 30, state, n_exp, *exp, ws)
+            out += [n_exp] + exp
+        return out
+
+    few = levels(limits[live], [x.view(B, -1, V)[live].reshape(-1, V) for x in logits])
+    many = levels(limits, logits)
+    assert few[0].tolist() == few[6].tolist() == [4, 4, 4] and int(many[6].sum()) == 12
+    for a, b in zip(few, many):
+        assert torch.equal(a, b[live])
+    del many, logits
+    torch.cuda.empty_cache()
+
+
 def test_level_by_level_of_launches_that_take_two_chunks_to_a_workgroup():
     # 33 sequences of 32 rows of 16 chunks, 16,896 in all, most of them of nodes that do not exist
     drive([(30, 3, 4)] * 7 + [(70, 3, 32)] + [(5, 2, 2)] * 25, list(range(33)), V=61441, bf16=True, seed=1)
