@@ -420,8 +420,16 @@ __global__ __launch_bounds__(ROWS ? 64 * ACCEPT_WAVES : 256) void accept_kernel(
 // Rows that a wave holds, a wave of the workgroup to each: one launch in place of two.  us a step, graph | eager, two launches -> one: 8 rows of 1,024 fp32
 // entries 22.5 -> 21.9 | 19.0 -> 16.9; graphs, greedy and stochastic, 16 rows of 1,000 bf16 entries 23.7 -> 22.5, 26.8 -> 26.4, of 2,000 fp32 22.3 -> 21.5,
 // 26.3 -> 25.4; but two rows to a wave, 32 of 1,001 24.4 -> 25.1, 27.5 -> 29.1.  (Longer rows, 2,048 entries at a time, and four waves: 16 rows of 2,000 23.5 -> 25.2.)
+// Beyond a compute unit to a sequence they come in turns of a whole acceptance, and rows past a sequence's nodes are read for nothing: greedy | stochastic, three nodes of 16,
+// two launches -> one, 256 sequences of 1,000 bf16 entries 7.5 -> 4.5 | 11.3 -> 8.3, 264 7.6 -> 7.1 | 12.0 -> 14.6, 1,024 13.4 -> 14.3 | 20.1 -> 29.9; of 2,048 fp32 320 7.8 -> 12.3 | 12.4 -> 19.3.
+// And from 32 sequences on more than 120 KB of rows to a workgroup take longer than a launch that passes over the dead ones: fp32 of 1,920 entries, 64 sequences 6.3 -> 5.0 | 9.6 -> 8.5, of 2,000
+// 6.1 -> 6.8 | 9.5 -> 10.3 (32 5.9 -> 6.4), of 2,048 192 sequences 6.8 -> 7.9 | 10.4 -> 11.4, with room for 10 nodes 6.7 -> 5.0 | 10.2 -> 8.6.
+#define ACCEPT_BATCH 256
+#define ACCEPT_BATCH_LONG 16
+#define ACCEPT_LONG (120 << 10)
 bool accept_takes_rows(const AcceptArgs &a) {
-    return a.mode != DT_ACCEPT_SAMPLED && a.V >= 8 && a.V <= ROW_V_MAX && a.TT_cap <= ACCEPT_WAVES;
+    const int bytes = a.TT_cap * a.V * (a.dtype == DT_BF16 ? 2 : 4);
+    return a.mode != DT_ACCEPT_SAMPLED && a.V >= 8 && a.V <= ROW_V_MAX && a.TT_cap <= ACCEPT_WAVES && a.batch <= (bytes > ACCEPT_LONG ? ACCEPT_BATCH_LONG : ACCEPT_BATCH);
 }
 
 hipError_t accept_launch(const AcceptArgs &a, hipStream_t st) {

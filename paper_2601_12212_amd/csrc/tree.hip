@@ -974,7 +974,12 @@ hipError_t tree_init() {
 // Rows that a wave holds, few enough for a wave of the workgroup to each, whichever sequence has more than the one that all have: one launch in place of two.
 // us a step, two launches -> one, graph | eager: 5 rows of 1,024 fp32 entries 21.4 -> 19.5 | 18.0 -> 16.3, bf16 22.1 -> 20.2 | 18.5 -> 17.1; 7 of 2,048 22.4 -> 21.3 | 18.9 -> 18.0, bf16
 // 22.7 -> 21.8 | 19.2 -> 18.2; but two rows to a wave, 10 of 2,047 22.6 -> 23.0, 16 of 2,048 22.8 -> 24.3, bf16 23.1 -> 25.0.
-bool tree_takes_rows(int64_t total_rows, int batch, int V) { return total_rows - (batch - 1) <= TREE_NW && V >= 8 && V <= ROW_V_MAX; }
+// While every sequence has a compute unit to itself (the tree's LDS leaves room for one): 256 sequences of 2,048 bf16 entries, one of eight rows, the others of one, 9.3 -> 8.2, 257 12.1 -> 13.0, 1,031 rows
+// 22.6 -> 24.8; fp32 9.6 -> 8.4, 12.2 -> 13.3, 23.4 -> 25.8.
+#define TREE_ROWS_BATCH 256
+bool tree_takes_rows(int64_t total_rows, int batch, int V) {
+    return batch <= TREE_ROWS_BATCH && total_rows - (batch - 1) <= TREE_NW && V >= 8 && V <= ROW_V_MAX;
+}
 
 hipError_t tree_launch(const TreeArgs &a, hipStream_t st) {
     if (a.batch <= 0) return hipSuccess;

@@ -291,6 +291,56 @@ def test_target_rows_that_the_acceptance_reduces(V, bf16, mode):
         assert torch.equal(st.node_argmax[0, :n].long().cpu(), torch.from_numpy(want))
 
 
+# The most sequences whose rows the acceptance reduces itself, and one more, of up to 120 KB of rows and of more; room for a node more has a launch of rows.
+@pytest.mark.parametrize("B,V", [(256, 1001), (257, 1001), (16, 2048), (17, 2048)])
+def test_target_rows_of_many_sequences(B, V):
+    got = [[t.clone() for t in (st.accept_len, st.best_node, st.out_tokens, st.node_argmax[:, :5])] for st in accepted(B, V, dt_synth.GREEDY)]
+    assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
+@pytest.mark.parametrize("mode", [dt_synth.GREEDY, dt_synth.STOCHASTIC])
+def test_target_rows_of_many_sequences_do_not_come_in_turns(mode):
+    """Equal times; with the rows of 320 sequences reduced by the acceptance, one and a half times as long as by a launch of rows."""
+    sides = accepted(320, 2048, mode)
+    times = [[], []]
+    for _ in range(15):
+        for st, of in zip(sides, times):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            torch.cuda.synchronize()
+            a.record()
+            st.graph.replay()
+            b.record()
+            torch.cuda.synchronize()
+            of.append(a.elapsed_time(b))
+    took = [sorted(of)[7] for of in times]
+    assert took[0] <= 1.25 * took[1], took
+
+
+def accepted(B, V, mode):
+    """Steps whose trees, three to five nodes of fp32 rows, have been accepted, once in room for 16 nodes and once for 17; and graphs of 20 acceptances."""
+    from paper_2601_12212_amd.step import Step
+    sides = []
+    for cap in (16, 17):
+        gen = torch.Generator("cuda").manual_seed(V)
+        st = Step([(3 + b % 3, 4, 5) for b in range(B)], [1] * B, 1, 1, 64, V, dtype=torch.float32, mode=mode, temperature=0.7, TT_cap=cap)
+        st.draft_logits.copy_(torch.randn(st.draft_logits.shape, generator=gen, device="cuda") * 3)
+        st.build_tree()
+        st.target_logits[:, :5].copy_(torch.randn((B, 5, V), generator=gen, device="cuda") * 3)
+        for i in range(1, 5):   # most nodes are their parents' best
+            par = st.parents[:, i].clamp(min=0).long()
+            at = torch.arange(B, device="cuda")
+            st.target_logits[at, par, st.tokens[:, i].clamp(min=0).long()] += 30.0 * (at % 4 != i % 4) * (st.parents[:, i] >= 0)
+        st.node_argmax.fill_(-3)
+        st.accept()
+        torch.cuda.synchronize()
+        st.graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(st.graph):
+            for _ in range(20):
+                st.accept()
+        sides.append(st)
+    return sides
+
+
 # Draft rows that the tree kernel reduces itself, a wave to a row: up to eight rows of 2,048 entries.  Against the general path, which a ninth row that belongs to no tree
 # selects; log-sum-exps of sums in another order differ by two ulp of 10 at most.  Rows whose best are more neighbours than a list holds, equal, few and none.
 @pytest.mark.parametrize("V", [8, 9, 63, 511, 513, 1024, 2047, 2048])
@@ -324,6 +374,24 @@ def test_draft_rows_that_the_tree_kernel_reduces(V, bf16, params):
                 assert torch.allclose(u, v, rtol=2e-6, atol=2e-6)
             else:
                 assert torch.equal(u, v)
+
+
+# The most sequences whose rows the tree kernel reduces itself, and one more.
+@pytest.mark.parametrize("B", [256, 257])
+def test_draft_rows_of_many_sequences(B):
+    from paper_2601_12212_amd.step import Step
+    got, V = [], 1001
+    for more in (0, 9):   # nine rows that belong to no tree: a launch of rows
+        st = Step([(8, 1, 5)] * (B - 1) + [(16, 2, 7)], [1] * B, 1, 1, 64, V)
+        gen = torch.Generator("cuda").manual_seed(B)
+        st.total_rows += more
+        st.draft_logits = torch.randn((st.total_rows, V), generator=gen, device="cuda").mul_(3).bfloat16()
+        st.ws = torch.empty(dt_workspace_bytes(B, st.total_rows, V, st.TT_cap, 1, 64), dtype=torch.uint8, device="cuda")
+        st.build_tree()
+        got.append([t.clone() for t in (st.n_nodes, st.tokens, st.parents, st.depth, st.src_row, st.anc_mask, st.score, st.logp)])
+    assert got[0][0].tolist() == [6] * (B - 1) + [16]
+    for a, b in zip(*got):
+        assert torch.allclose(a, b, rtol=2e-6, atol=2e-6) if a.dtype == torch.float32 else torch.equal(a, b)
 
 
 def test_a_launch_of_more_threads_than_one_grid_dimension_takes():
