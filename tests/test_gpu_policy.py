@@ -98,6 +98,35 @@ def test_policy_every_step_and_one_sequence():
     run_policy(B=1, F=3 * 5120, H=128, bf16=True, N=1, sample=0, steps=5, seed=3)
 
 
+# Which sequences decide: the first, the last, none, of as many as have their flags read with the weights and of more; the others keep their actions.
+@pytest.mark.parametrize("B,who", [(1, []), (64, [63]), (64, []), (65, [63]), (65, [64]), (65, []), (129, [128]), (330, [0, 329])])
+def test_policy_of_sequences_out_of_phase(B, who):
+    import paper_2601_12212_amd as dt
+    F, H, N, rng = 200, 64, 5, np.random.default_rng(B)
+    table = np.array(dt.dt_action_table(), np.int32)
+    A = len(table)
+    W = [(rng.standard_normal(sh) * sc).astype(np.float32) for sh, sc in (((F, H), F ** -0.5), ((H,), 0.1), ((H, H), H ** -0.5), ((H,), 0.1), ((H, A), 1.0), ((A,), 0.1))]
+    x = rng.standard_normal((B, F)).astype(np.float32)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    i32 = dict(dtype=torch.int32, device="cuda")
+    step, cached = 1 + torch.arange(B, **i32) % (N - 1), torch.arange(B, **i32) % A
+    before = step.clone()
+    for i, b in enumerate(who):          # an interval that is over, or no action yet
+        if i % 2: cached[b] = -1
+        else: step[b] = 0
+    logits, queried, action = torch.full((B, A), -77.0, device="cuda"), torch.full((B,), -3, **i32), torch.zeros(B, **i32)
+    limits, ws = torch.zeros((B, 3), **i32), torch.empty(dt.dt_policy_workspace_bytes(B, F, H), dtype=torch.uint8, device="cuda")
+    dt.dt_policy_step(dev(x), *[dev(w) for w in W], dev(table), N, 0, 0, 0, step, cached, limits, action, queried, logits, ws)
+    decides = np.isin(np.arange(B), who)
+    assert queried.bool().cpu().numpy().tolist() == decides.tolist()
+    for b in who:
+        want = ref.policy_logits(x[b], *W)
+        assert np.abs(logits[b].cpu().numpy() - want).max() < LOGIT_TOL and want.max() - want[int(action[b])] < GREEDY_GUARD and int(step[b]) == 1
+    keep = torch.from_numpy(~decides).cuda()
+    assert (logits[keep] == -77.0).all() and torch.equal(step[keep], (before[keep] + 1) % N) and torch.equal(action[keep], (torch.arange(B, **i32) % A)[keep])
+    assert torch.equal(limits, dev(table)[action.long()])
+
+
 @pytest.mark.parametrize("N,bonus,per_seq", [(4, 1, False), (10, 0, True), (1, 1, False)])
 def test_reward_averaged_over_the_cache_interval(N, bonus, per_seq):
     """dt_policy_step and dt_reward_step driven together over several intervals: the device accumulators,
