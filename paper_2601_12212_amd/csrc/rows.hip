@@ -444,7 +444,7 @@ __device__ __forceinline__ bool level_waits(const Tail<MODE> &arg, u32 wg) {
 // (eight waves per SIMD: left alone the compiler takes 76 registers in one mode, 29.3 us for 64 sequences instead of 26.3)
 template <int MODE, bool BF16, int PASS>
 __global__ __launch_bounds__(256, 8) void row_select_kernel(RowArgs a, int nl_, int S, float *top_val, int32_t *top_id, float *lse, int out_stride, u64 tag, Tail<MODE> tail) {
-    constexpr bool SAME = PASS > 0, KEEP = SAME && MODE == ROWS_UNIFORM;
+    constexpr bool SAME = PASS > 0, KEEP = SAME && MODE == ROWS_UNIFORM && !BF16;
     if constexpr (SAME)
         if (level_waits<MODE, offsetof(SelectArgs, tail)>(tail, blockIdx.y * gridDim.x + blockIdx.x)) return;
     const int nl = SAME ? PASS : nl_;
