@@ -30,11 +30,12 @@ __global__ __launch_bounds__(256) void policy_layer1_kernel(PolicyArgs a) {
     __shared__ float s_acc[POLICY_BCH][128];
     __shared__ int s_need[POLICY_BCH];
     // A sequence decides in one turn of N, as a rule; where none does there is nothing to do.  Every wave looks at all flags, asked for in front of the weights and used
-    // when they are there, without a wait for the weights.  (Flags in front, weights in a trip behind them, cost turns that decide 0.5 to 0.9 us; with the flags of
-    // eight sequences at a time behind the weights, turns whose actions are cached wait for these.)  Both kernels, 12,288 inputs, called and replayed, eight at a time
-    // | in front, a trip | so: turns that decide of two sequences 12.7 | 13.4 | 12.4 us, of 32 24.0 | 24.6 | 22.9, one of 32 15.9 | 16.8 | 15.7; cached ones 4.2 | 3.2 | 3.2 and 7.3 | 3.4 | 3.3.
-    // (Of more than 64 sequences in a trip before: the weights wait for it, a hundredth of a turn that decides.)
-    if (a.batch > 64) {
+    // when they are there, without a wait for the weights; but the flags first and the weights in a trip behind them, which cost turns that decide 0.5 to 0.9 us, where most turns have
+    // none that does even if the sequences are out of phase: 6 MB of weights less to read there, 0.5 us of a whole turn of two sequences (59.0 -> 58.4).  (And of more than 64 sequences,
+    // where the trip is a hundredth of a turn that decides.)  Both kernels, 12,288 inputs, called and replayed, the flags of eight sequences at a time behind the weights | in front |
+    // with them: turns that decide of two sequences 12.7 | 13.4 | 12.4 us, of 32 24.0 | 24.6 | 22.9, one of 32 15.9 | 16.8 | 15.7; cached ones 4.2 | 3.2 | 3.2 and 7.3 | 3.4 | 3.3.
+    const bool flags_first = a.batch > 64 || a.N >= 4 * a.batch;
+    if (flags_first) {
         bool some = false;
         for (int b = tid; b < a.batch; b += (int)blockDim.x) some = some || policy_needed(a, b);
         if (!__syncthreads_or(some)) return;
@@ -47,7 +48,7 @@ __global__ __launch_bounds__(256) void policy_layer1_kernel(PolicyArgs a) {
 #pragma unroll
     for (int i = 0; i < POLICY_KS / 2; ++i) wreg[i] = a.W1[(int64_t)min(k0 + part * half + i, a.F - 1) * H + o];
     __builtin_amdgcn_sched_barrier(0);
-    if (a.batch <= 64 && ballot(step0 == 0 || act0 < 0) == 0ull) return;
+    if (!flags_first && ballot(step0 == 0 || act0 < 0) == 0ull) return;  // the same in every wave
     for (int b0 = 0; b0 < a.batch; b0 += POLICY_BCH) {
         const int nb = min(POLICY_BCH, a.batch - b0);
         // the inputs are read before the flags that say which sequences need them are back
