@@ -24,7 +24,7 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBPS = 8000.0
 MFMA_BF16_PEAK_TFLOPS = 2500.0        # dense bf16, published
-STEP_KERNEL_IDS = range(7)            # draft rows, row merge, tree, attention, attention combine, target rows, accept
+STEP_KERNEL_IDS = (0, 1, 2, 3, 5, 6)  # draft rows, row merge, tree, attention, target rows, accept
 
 
 def log(*a):
@@ -149,8 +149,7 @@ class Workload:
             pk = json.load(open(path))["kernels"]
             for ours, prefix in (("rows_target_chunk", "dt::row_argmax_kernel"), ("rows_draft_chunk", "dt::row_stream_kernel"),
                                  ("attention", "dt::attn_")):
-                # the merge / combine launches of the attention are timed as a kernel of their own
-                hit = [v for k, v in pk.items() if k.startswith(prefix) and "merge" not in k and "combine" not in k]
+                hit = [v for k, v in pk.items() if k.startswith(prefix)]
                 if not hit and ours == "rows_draft_chunk":      # both passes in one launch
                     hit = [v for k, v in pk.items() if k.startswith("dt::row_select_kernel")]
                 if hit:

@@ -364,7 +364,7 @@ int dt_commit(void *stream, int batch, int n_layers, dt_dtype t, int Hkv, int D,
  * launched by the calls above then carries an event pair on its dispatch that records the
  * kernel's own begin and end (not usable while the stream is being captured into a graph).
  * dt_profile_enable(0) switches it off.  dt_profile_read sums, for one kernel id
- * (0 draft row chunks, 1 row merge, 2 tree, 3 attention, 4 attention combine, 5 target row
+ * (0 draft row chunks, 1 row merge, 2 tree, 3 attention, 4 reserved (no launch), 5 target row
  * chunks, 6 accept, 7 dt_topk_rows chunks, 8 commit, 9 policy layer 1, 10 policy head, 11 per-node target samples,
  * 12 reward), the elapsed milliseconds of the launches recorded
  * since the last enable, waiting for them to finish.  Not thread-safe.

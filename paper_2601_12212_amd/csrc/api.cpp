@@ -133,7 +133,7 @@ struct LevelState {  // row results of one sequence after the other, then the pe
     float *top_val;    // [batch, DT_STATE_ROWS, DT_K_MAX]
     int32_t *top_id;
     float *lse;        // [batch, DT_STATE_ROWS]
-    int32_t *n_exp;    // [batch] the last level processed and the nodes expanded there, level << 8 | nodes
+    int32_t *n_exp;    // [batch] the last two levels processed and the nodes expanded there (level_note)
     size_t bytes;
 };
 inline LevelState level_state(void *st, int batch) {
@@ -229,8 +229,8 @@ int dt_topk_rows_static(void *stream, const void *logits, dt_dtype t, int64_t n_
     if (int rc = ensure_init(nullptr)) return rc;
     void *ws = device_scratch();
     if (!ws) return DT_ERR_HIP;
-    // nothing in this scratch has to start from zero: every word the selection reads is written by the
-    // streaming pass of the same call
+    // nothing in this scratch has to start from zero: every result that the selection reads is written by the streaming pass of the
+    // same call, and the words by which it knows that carry the launch's tag
     return dt_topk_rows(stream, logits, t, n_rows, V, row_stride, k, top_val, top_id, lse, ws, DT_STATIC_SCRATCH_BYTES);
 }
 

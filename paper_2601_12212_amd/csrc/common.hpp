@@ -41,8 +41,8 @@ typedef u32 u32x4_any4 __attribute__((ext_vector_type(4), aligned(4)));
 // KEEP: left in the caches, to be read again from the same XCD: fp32 rows in calls of rows on their own, both passes in one launch.  On rows that are new to each call, without | with: from
 // memory (1.2 GB of them in turn) 61 of 50,001 entries 9.5 | 9.4 us, 28 of 128,256 10.3 | 9.9, 144 of 50,001 13.5 | 12.7, 120 of 128,256 19.3 | 18.0; from the last-level cache 9.7 | 9.0,
 // 10.9 | 9.5, 13.5 | 12.3; the call and what has just written them: a product 59.0 | 59.0, 66.9 | 67.5, 91 | 90, 210 | 206, a conversion from bf16 16.5 | 16.9, 18.0 | 18.1, 22.7 | 22.7, 35.2 | 31.0, a copy from
-// memory 15.6 | 16.5, 17.5 | 18.0, 26.4 | 24.7, 43 | 39.  (The same rows again 8.0 | 7.8.)  Not in bf16: from memory 10 of 128,256 7.2 | 7.7, 44 9.2 | 9.5, 61 of 50,001 8.0 | 8.4, 112 of 36,000 8.4 | 8.8, and
-// no gain from the last level or behind a writer.  Not in a step: left in the caches, the draft rows displace the keys and values that the attention behind them finds on the memory side,
+// memory 15.6 | 16.5, 17.5 | 18.0, 26.4 | 24.7, 43 | 39.  (The same rows again 8.0 | 7.8.)  Not in bf16: from memory 10 of 128,256 7.2 | 7.7, 44 9.2 | 9.5, 61 of 50,001 8.0 | 8.4, 112 of 36,000 8.5 | 8.8;
+// from the last level 7.3 | 7.4, 9.3 | 9.3, 8.2 | 8.1, 8.9 | 8.6, behind a copy 28 of 128,256 14.2 | 14.6.  Not in a step: left in the caches, the draft rows displace the keys and values that the attention behind them finds on the memory side,
 // 11.4 us a launch against 10.45, a step of the 8B shape over 16 input sets 36.8 us against 35.3; a tree level by level takes 65.1 us and 64.6.
 template <bool KEEP = false>
 __device__ __forceinline__ uint4 load16(const uint16_t *p) {

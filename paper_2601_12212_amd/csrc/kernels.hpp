@@ -14,7 +14,7 @@ namespace dt {
 // Off by default.  When switched on (dt_profile_enable), every kernel is launched with a pair
 // of pre-created HIP events attached to its dispatch (hipExtLaunchKernelGGL), which record the
 // kernel's own begin and end; dt_profile_read sums the elapsed times per kernel id.
-enum KernelId { KID_ROWS_DRAFT = 0, KID_ROWS_MERGE, KID_TREE, KID_ATTN, KID_ATTN_COMBINE, KID_ROWS_TARGET,
+enum KernelId { KID_ROWS_DRAFT = 0, KID_ROWS_MERGE, KID_TREE, KID_ATTN, KID_RESERVED_4 /* no launch; the others keep their numbers */, KID_ROWS_TARGET,
                 KID_ACCEPT, KID_ROWS_UNIFORM, KID_COMMIT, KID_POLICY_L1, KID_POLICY_HEAD, KID_NODE_SAMPLE, KID_REWARD, KID_COUNT };
 bool prof_next(int kid, hipEvent_t *start, hipEvent_t *stop);  // false when timing is off
 

@@ -218,13 +218,21 @@ def test_shared_merge_at_its_edges():
         assert_attention(st.attention_out(0), want, "bf16", "%d parts" % blocks)
 
 
-# four units (a kv head's 32 rows each) of one block up to 1 to 8 splits, and both sides of the lines where splits begin: 9, 11
-# and 13 blocks of 128-wide heads with room for eight, three and two, 29 and 60 blocks of 64-wide ones with room for three and two
+# four units (a kv head's 32 rows each) in two to eight splits; 72 and 100 of them, with room for three and two
 @pytest.mark.parametrize("D,Hkv,L", [(128, 4, L) for L in (224, 225, 352, 353, 480, 608, 736, 864, 992)] +
                          [(128, 72, L) for L in (288, 289, 353, 481)] + [(128, 100, L) for L in (352, 353, 481)] +
                          [(64, 4, L) for L in (864, 865, 993, 1121, 1500, 1800)] + [(64, 72, 865), (64, 100, 1856), (64, 100, 1857)])
 def test_numbers_of_key_splits(D, Hkv, L):
     check_case(oracle_case(0, cfg=_cfg("bf16", D, [(32, 5, 6)], [L], Hkv, Hkv)))
+
+
+# Both sides of the lines where splits begin, and of those where two become three, three four and two (or three) one again: blocks of 32 keys, the last of one
+# key, whole, or one less; with room for eight, three and two.  And 129 units, which have room for one.
+@pytest.mark.parametrize("D,Hkv,blocks", [(128, 4, n) for n in (5, 6, 8, 9, 12, 13, 16, 17)] + [(128, 72, n) for n in (12, 13, 16, 17)] + [(128, 100, n) for n in (5, 6, 8, 9, 12, 13)] +
+                         [(64, 4, n) for n in (12, 13, 16, 17)] + [(64, 72, n) for n in (16, 17)] + [(64, 100, n) for n in (28, 29, 32, 33, 36, 37)] + [(128, 129, 20), (64, 129, 40)])
+def test_lines_where_key_splits_begin(D, Hkv, blocks):
+    for L in (32 * (blocks - 1), 32 * (blocks - 1) - 31, 32 * (blocks - 1) - 1):   # and 32 nodes
+        check_case(oracle_case(0, cfg=_cfg("bf16", D, [(32, 5, 6)], [L], Hkv, Hkv)))
 
 
 # Splits of a row block that meet in one XCD, in two to eight; and, 84 row blocks in three splits, the last four of them spread over the XCDs, where

@@ -236,7 +236,7 @@ def test_empty_prefix_and_tt1_decode_and_fp32_heads():
 
 def test_attention_key_splits_and_long_prefix():
     # few (sequence, kv head) pairs and a long prefix: the small-batch kernel splits the keys over
-    # several workgroups and a merge kernel joins the partials
+    # several workgroups, whose partials meet in the same launch
     check_case(oracle_case(0, cfg=small_cfg([(30, 4, 3)], [2000], Hq=8, Hkv=2)))
     check_case(oracle_case(0, cfg=small_cfg([(128, 6, 6), (7, 2, 3)], [4097, 640], Hq=4, Hkv=4)))
 
@@ -548,11 +548,11 @@ def _attention_shapes():
     rng = np.random.default_rng(31)
     tile_params = [(int(rng.choice([5, 40])), 3, 3) for _ in range(70)]
     return {
-        # one workgroup per (sequence, kv head, 32 rows), no key splits
-        "wave": small_cfg([(60, 6, 10)], [300], V=1500, Hq=8, Hkv=2),
-        # the same kernel with the keys dealt over several workgroups and the merge launch
+        # one workgroup per (sequence, kv head, 32 rows), 144 of them: no key splits
+        "wave": small_cfg([(60, 6, 10)], [300], V=1500, Hq=72, Hkv=18),
+        # the same kernel with the keys dealt over several workgroups
         "wave_split": small_cfg([(60, 6, 10), (33, 4, 8)], [2000, 1700], V=1500, Hq=8, Hkv=2),
-        # balanced large-batch schedule (partials + combine)
+        # balanced large-batch schedule (partials, merged by a workgroup of the launch)
         "gang": small_cfg([(64, 5, 6)] * 12 + [(96, 4, 6)] * 4, [300 + 211 * i for i in range(16)], V=1031, Hq=32, Hkv=8),
         # one workgroup per (sequence, kv head, 128-row tile): more than 64 sequences
         "tile": small_cfg(tile_params, [int(rng.integers(0, 200)) for _ in range(70)], V=1031, Hq=8, Hkv=2),
