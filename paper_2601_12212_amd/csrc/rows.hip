@@ -1479,6 +1479,8 @@ static hipError_t launch_select(const RowArgs &a, int64_t n_rows, int nl, float 
 // throughout, since a row is selected while others still stream.  Calls, k = 12, two launches | one: bf16 of 128,256 entries 10 rows 7.8 | 6.7 us, 28 8.1 | 7.2, 44
 // 8.4 | 8.1, 64 9.0 | 9.5, 80 9.6 | 10.1; of 90,001 48 rows 9.0 | 7.2, 72 9.1 | 8.7, 100 9.6 | 9.6; of 50,001 28 8.0 | 6.6, 64 8.0 | 7.1, 112 9.0 | 8.3, 144 9.2 | 9.5; of
 // 36,000 112 8.9 | 7.5; fp32 of 128,256 28 rows 9.2 | 8.8, 64 11.9 | 11.5, 120 17.1 | 15.6; of 50,001 61 9.15 | 8.19, 144 12.0 | 11.5; of 20,001 112 8.9 | 7.6.
+// Beside a busy stream the workgroups that wait have no place, or others have none because of them, and a launch less is still worth more: 51 bf16 rows of 128,256, two launches | one, beside
+// a product of 4,096 cubed 160 | 119 us a call, beside an elementwise pass over 512 MB 27.3 | 22.6, to which a call adds 3.7 | 4.6; 61 fp32 rows of 50,001 172 | 116, 29.6 | 22.0, 3.7 | 4.3.
 #define PASS_WGS 2048
 #define PASS_ENTRIES ((int64_t)13 << 19)
 static bool takes_pass(const RowArgs &a, int64_t n_rows, int nl) {
