@@ -25,7 +25,8 @@ namespace dt {
 // one exchanges for 0 when it takes what is there.  An offer that nobody has taken for OFFER_TICKS is withdrawn the same way; then all of it is written
 // to the memory side and marked there, for a reader anywhere.  Nothing depends on which workgroups run at once or where: if the waiting one has
 // waited for STAY_TICKS and taken nothing, it leaves a mark as well and goes; the offers run out, and of those that mark what they have the last to come
-// sees all marks and does its work.  Of the last two both may: the first to claim it does, alone (a row that two had taken could end a level twice).
+// sees all marks and does its work.  Of the last two both may: the first to claim it does, alone (of a row that two had taken the second mark for
+// its level could come behind the level's choice, and stay).
 //
 // No wait is for anything but a limited time.  Offers end as 0, and marks are taken away by who has seen them all: a replayed graph has the same
 // tag.  The claim is not: another may be on the way to it.  It is cleared by the waiting one before its own mark, without which nobody claims.
